@@ -13,6 +13,7 @@
 #include "sf_backproject_tiled.h"
 #include "sf_project_columns.h"
 #include "md_backproject_tiled.h"
+#include "sf_flat.h"
 #include <thread>
 #include "sd_backproject_tiled.h"
 
@@ -329,6 +330,45 @@ static void select_footprint_columns(leap_geometry *G)
             G->major[(size_t)a * nbundles + b] = (unsigned char)sf_ray_lines(view_geom(G, a), G->views[a], b * G->fp_cw, G->fp_cw).xmajor;
 }
 
+// Footprint model, scans of one detector row and one voxel layer: limits of the flat kernels (sf_flat.h) in both
+// directions.  Wider footprints, coarser detectors and beams that fan out too far stay with the general kernels.
+static void select_footprint_flat(leap_geometry *G)
+{
+    const leap_geometry_desc *d = &G->desc;
+    const SfGeom &g = G->g;
+    if (!(d->type == LEAP_FAN || (d->type == LEAP_PARALLEL && d->nrows == 1 && d->nz == 1))) return;
+    // widest footprint of any voxel, on the detector or beside it (footprint_bounds looks at the detector's fan only)
+    const double rx = std::fabs(d->center_x) + 0.5 * d->nx * d->voxel_xy, ry = std::fabs(d->center_y) + 0.5 * d->ny * d->voxel_xy;
+    const double reach = std::sqrt(rx * rx + ry * ry);
+    double widest = d->voxel_xy * std::sqrt(2.0) / d->pixel_u;
+    if (d->type == LEAP_FAN) widest *= d->sdd / (d->sod - reach) / std::sqrt(1.0 - (reach / d->sod) * (reach / d->sod));
+    if (!(widest <= FLAT_MAX_COLS) || !((double)d->nx * d->ny < 268435456.0)) return;       // 32-bit offsets within a slice
+    int span = 0;
+    for (int a = 0; a < d->nviews; ++a)
+        for (int c0 = 0; c0 < d->ncols; c0 += FLAT_RAYS) {
+            const int c1 = std::min(c0 + FLAT_RAYS, d->ncols) - 1;
+            const int xmajor = sf_flat_xmajor(g, G->views[a], c0);
+            const SfRayLines L0 = sf_ray_lines<0>(g, G->views[a], c0, 1, xmajor), L1 = sf_ray_lines<0>(g, G->views[a], c1, 1, xmajor);
+            // nearly parallel beams: slopes of at most 2 and no column between the two that leaves their span
+            if (!(L0.spread <= 1.0f && L1.spread <= 1.0f && std::fabs(L0.b0) < 1e6f && std::fabs(L1.b0) < 1e6f)) return;
+            const int ends[2] = {0, (xmajor ? d->nx : d->ny) - 1};
+            for (int n : ends) {
+                int f0, l0, f1, l1;
+                sf_candidates(L0, n, f0, l0);
+                sf_candidates(L1, n, f1, l1);
+                span = std::max(span, std::max(l0, l1) - std::min(f0, f1) + 1);
+            }
+        }
+    span += 4;                                       // host and device floats may round apart
+    if (span > FLAT_MAX_SPAN) return;
+    G->flat = true;
+    G->flat_span = (span + 63) / 64 * 64;
+    if (d->type == LEAP_PARALLEL) {                  // the layer's overlap with the row
+        const double lo = g.kvd * g.zlo0d + g.row_offd, hi = lo + g.kvd * g.Tzd;
+        G->flat_fv = (float)std::fmax(std::fmin(1.0, hi) - std::fmax(0.0, lo), 0.0);
+    }
+}
+
 // Siddon model: static limits of the two fast kernels.
 static void select_siddon_fast_kernels(leap_geometry *G)
 {
@@ -538,6 +578,7 @@ static void select_fast_kernels(leap_geometry *G)
     if (G->desc.model == LEAP_MODEL_SF) {
         select_footprint_tiled(G);
         select_footprint_columns(G);
+        select_footprint_flat(G);
     } else {
         select_siddon_fast_kernels(G);
     }
@@ -621,6 +662,24 @@ static void allocate_forward_scratch(leap_geometry *G)
     G->slab_width = width;
 }
 
+// Flat scans: room for the batch-fastest copy of up to 16 slices, 128 MiB at most.  Without it every item of a batch is
+// projected by itself.
+static void allocate_flat_scratch(leap_geometry *G)
+{
+    const double slice = 4.0 * G->desc.nx * (double)G->desc.ny;
+    double items = std::fmin(16.0, std::floor(128.0 * 1048576.0 / slice));
+    if (!(items >= 2.0)) return;
+    G->scratch_bytes = (size_t)(items * slice);
+    hipError_t e = hipMalloc((void **)&G->d_volz, G->scratch_bytes);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&G->scratch_event, hipEventDisableTiming);
+    if (e == hipSuccess) return;
+    if (G->d_volz) (void)hipFree(G->d_volz);
+    G->d_volz = nullptr;
+    G->scratch_bytes = 0;
+    G->note = "scratch allocation failed: the items of a batch are projected one by one";
+    (void)hipGetLastError();
+}
+
 static void free_handle(leap_geometry *G)
 {
     if (!G) return;
@@ -695,6 +754,7 @@ static int finish_handle(leap_geometry *G, leap_geometry **out)
     if (e == hipSuccess) (void)leap_static_scratch_init(G->device);   // set-up for leap_project_static_scratch; it reports a failure itself
     if (e == hipSuccess && !G->views.empty()) e = upload((void **)&G->d_views, G->views.data(), sizeof(SfView) * G->views.size());
     if (e == hipSuccess) allocate_forward_scratch(G);
+    if (e == hipSuccess && G->flat) allocate_flat_scratch(G);
     if (e == hipSuccess && !G->raycols.empty()) e = upload((void **)&G->d_raycols, G->raycols.data(), sizeof(SdRayCol) * G->raycols.size());
     if (e == hipSuccess && !G->geoms.empty()) e = upload((void **)&G->d_geoms, G->geoms.data(), sizeof(SfGeom) * G->geoms.size());
     if (e == hipSuccess && !G->poses.empty()) e = upload((void **)&G->d_poses, G->poses.data(), sizeof(MdPose) * G->poses.size());
@@ -990,7 +1050,7 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
         std::snprintf(fwd, sizeof fwd, "columns(nq=%d/%d,nkp=%d,rg=%d,cw=%d,slab=%d)", G->fp_need_q, G->fp_nq, G->fp_nkp,
                       G->fp_rg, G->fp_cw, G->slab_width);
     else
-        std::snprintf(fwd, sizeof fwd, "general");
+        std::snprintf(fwd, sizeof fwd, G->flat ? "general(flat,span=%d)" : "general", G->flat_span);
     if (G->bp_tiled && G->d_mdbp)
         std::snprintf(back, sizeof back, "tiled(zc=%d,window=%dx%d)", MD_BP_SHAPES[G->bp_shape].zc, G->bp_need_w, G->bp_need_h);
     else if (G->bp_tiled && siddon)
@@ -999,7 +1059,7 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
         std::snprintf(back, sizeof back, "tiled(nc=%d,nv=%d,zc=%d,window=%dx%d)", G->bp_nc, G->bp_nv, BP_SHAPES[G->bp_shape].zc,
                       G->bp_need_w, G->bp_need_h);
     else
-        std::snprintf(back, sizeof back, "general");
+        std::snprintf(back, sizeof back, G->flat ? "general(flat)" : "general");
     const char *modules = G->g.type != SF_MODULAR ? "" : (G->geoms.empty() ? " (tilted modules)" : " (upright modules)");
     std::snprintf(buf, (size_t)cap, "type=%d model=%s A=%s AT=%s scratch=%zu%s cols/voxel<=%.2f rows/voxel<=%.2f voxels/row<=%.2f%s%s",
                   G->g.type, siddon ? "siddon" : "sf", fwd, back, G->scratch_bytes, modules, G->max_cols_per_voxel,

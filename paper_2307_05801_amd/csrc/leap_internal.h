@@ -40,6 +40,9 @@ struct leap_geometry {
     int fp_rg = 0;                      // row groups per wave (footprints: groups of 128 rows; Siddon: of 64)
     int fp_cw = 4, fp_vb = 128, fp_tb = 1;   // detector columns per wave; block order: views per run, tiles per chunk
     bool fp_columns = false;
+    bool flat = false;                  // one row, one layer: the kernels of sf_flat.h in both directions
+    int flat_span = 0;                  // voxels of a slab that the beams of 64 adjacent columns cover, rounded up to 64
+    float flat_fv = 1.0f;               // the scan's one axial weight
     float *d_volz = nullptr;            // the scratch: scratch_items copies of one slab
     size_t scratch_bytes = 0;           // bytes allocated at d_volz
     int slab_width = 0;                 // voxel layers across the marching axis per slab when one volume is projected

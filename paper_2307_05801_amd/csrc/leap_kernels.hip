@@ -8,6 +8,7 @@
 #include "sf_general.h"
 #include "sf_backproject_tiled.h"
 #include "sf_project_columns.h"
+#include "sf_flat.h"
 #include "sd_project_columns.h"
 #include "md_project_columns.h"
 #include "sd_backproject_tiled.h"
@@ -420,10 +421,129 @@ static int run_forward_columns(const leap_geometry *G, const FwdScratch &S, cons
     return LEAP_OK;
 }
 
+// ------------------------------------------------------------------------------------------------
+// Flat scans (sf_flat.h).
+// ------------------------------------------------------------------------------------------------
+
+// Waves of a workgroup that share one output tile's slabs or views: as many as it takes to put about eight waves on each of
+// the chip's 1024 SIMDs, while each keeps at least four of its `steps` (slabs, views).  A 64^2 slice has 64 tiles and 180
+// beams' waves: one wave each took 112 us (A) and 131 us (A^T), 16 of them 11 us each with their launches.
+static int flat_waves(double tiles, int steps)
+{
+    int w = 1;
+    while (w < FLAT_MAX_WAVES && tiles * w < 8192.0 && steps / (2 * w) >= 4) w *= 2;
+    return w;
+}
+
+template <int NB>
+static void launch_project_flat(const leap_geometry *G, const float *src, float *d_sino, int items, hipStream_t stream)
+{
+    const SfGeom &g = G->g;
+    const int tiles = (int)cdiv(g.ncols, FLAT_RAYS);
+    const unsigned groups = cdiv((unsigned)items, NB);
+    int waves = flat_waves((double)tiles * g.nviews * groups, g.nx < g.ny ? g.nx : g.ny);
+    while ((size_t)waves * G->flat_span * sizeof(SfFlatRec) > 65536) waves /= 2;        // (spans of up to 256: at least 8 fit)
+    const size_t lds = (size_t)waves * G->flat_span * sizeof(SfFlatRec);
+    hipLaunchKernelGGL(sf_project_flat<NB>, dim3((unsigned)tiles * (unsigned)g.nviews, groups), dim3(64 * waves), lds, stream, g, G->d_views,
+                       src, d_sino, tiles, G->flat_span, items, G->flat_fv);
+}
+
+template <int NB>
+static void launch_interleaved_flat(const leap_geometry *G, const float *d_vol, float *d_sino, int items, hipStream_t stream)
+{
+    const unsigned nvol = (unsigned)G->g.nx * (unsigned)G->g.ny;
+    hipLaunchKernelGGL(sf_interleave<NB>, dim3(cdiv(nvol, 256), cdiv((unsigned)items, NB)), dim3(256), 0, stream, d_vol, G->d_volz, nvol, items);
+    launch_project_flat<NB>(G, G->d_volz, d_sino, items, stream);
+}
+
+// The forward projection of `batch` slices.  With the handle's scratch a weight serves up to eight items; calls on one
+// handle then share the scratch and are ordered on the device.  A call that is being captured, or that must not touch the
+// scratch (scratch == false), takes the slices one by one as they lie: the same sums in the same order, bit for bit.
+static int project_flat(const leap_geometry *G, const float *d_vol, float *d_sino, int batch, hipStream_t stream, bool scratch)
+{
+    const SfGeom &g = G->g;
+    const size_t nvol = (size_t)g.nx * g.ny, nsino = (size_t)g.nviews * g.ncols;
+    if (scratch && batch > 1 && G->d_volz) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        LEAP_HIP_CHECK(hipStreamIsCapturing(stream, &capture));
+        scratch = capture == hipStreamCaptureStatusNone;
+    }
+    if (!scratch || batch == 1 || !G->d_volz) {
+        for (int b = 0; b < batch; b += 32768) {
+            const int items = batch - b < 32768 ? batch - b : 32768;
+            launch_project_flat<1>(G, d_vol + b * nvol, d_sino + b * nsino, items, stream);
+        }
+        LEAP_HIP_CHECK(hipGetLastError());
+        return LEAP_OK;
+    }
+    std::lock_guard<std::mutex> lock(G->scratch_mutex);
+    if (G->scratch_used && G->scratch_stream != stream) LEAP_HIP_CHECK(hipStreamWaitEvent(stream, G->scratch_event, 0));
+    const int room = (int)(G->scratch_bytes / (nvol * sizeof(float)));          // whole slices the scratch holds
+    for (int b = 0; b < batch;) {
+        const float *vol = d_vol + b * nvol;
+        float *sino = d_sino + b * nsino;
+        const int left = batch - b;
+        int items;
+        if (left >= 8 && room >= 8) {                                            // whole groups of eight
+            items = (left < room ? left : room) / 8 * 8;
+            launch_interleaved_flat<8>(G, vol, sino, items, stream);
+        } else if (left > 4 && room >= 8) {
+            items = left;
+            launch_interleaved_flat<8>(G, vol, sino, items, stream);
+        } else if (left > 2 && room >= 4) {
+            items = left < 4 ? left : 4;
+            launch_interleaved_flat<4>(G, vol, sino, items, stream);
+        } else if (left > 1) {
+            items = 2;
+            launch_interleaved_flat<2>(G, vol, sino, items, stream);
+        } else {
+            items = 1;
+            launch_project_flat<1>(G, vol, sino, items, stream);
+        }
+        b += items;
+    }
+    LEAP_HIP_CHECK(hipGetLastError());
+    LEAP_HIP_CHECK(hipEventRecord(G->scratch_event, stream));
+    G->scratch_stream = stream;
+    G->scratch_used = true;
+    return LEAP_OK;
+}
+
+template <int NB>
+static void launch_backproject_flat(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
+{
+    const SfGeom &g = G->g;
+    const unsigned tiles_x = cdiv(g.nx, FLAT_T), tiles_y = cdiv(g.ny, FLAT_T), groups = cdiv((unsigned)items, NB);
+    const int waves = flat_waves((double)tiles_x * tiles_y * groups, g.nviews);
+    hipLaunchKernelGGL(sf_backproject_flat<NB>, dim3(tiles_x * tiles_y, groups), dim3(64 * waves), (size_t)waves * 64 * NB * sizeof(float),
+                       stream, g, G->d_views, d_sino, d_vol, (int)tiles_x, items, G->flat_fv);
+}
+
+static int backproject_flat(const leap_geometry *G, const float *d_sino, float *d_vol, int batch, hipStream_t stream)
+{
+    const SfGeom &g = G->g;
+    const size_t nvol = (size_t)g.nx * g.ny, nsino = (size_t)g.nviews * g.ncols;
+    for (int b = 0; b < batch;) {
+        const float *sino = d_sino + b * nsino;
+        float *vol = d_vol + b * nvol;
+        const int left = batch - b;
+        int items = left < 8 * 4096 ? left : 8 * 4096;
+        if (left >= 8) launch_backproject_flat<8>(G, sino, vol, items = items / 8 * 8, stream);
+        else if (left > 4) launch_backproject_flat<8>(G, sino, vol, items, stream);
+        else if (left > 2) launch_backproject_flat<4>(G, sino, vol, items, stream);
+        else if (left > 1) launch_backproject_flat<2>(G, sino, vol, items, stream);
+        else launch_backproject_flat<1>(G, sino, vol, items, stream);
+        b += items;
+    }
+    LEAP_HIP_CHECK(hipGetLastError());
+    return LEAP_OK;
+}
+
 int leap_launch_project_batch(const leap_geometry *G, const float *d_vol, float *d_sino, int batch, hipStream_t stream)
 {
     const SfGeom &g = G->g;
     const size_t nvol = (size_t)g.nx * g.ny * g.nz, nsino = (size_t)g.nviews * g.nrows * g.ncols;
+    if (G->flat) return project_flat(G, d_vol, d_sino, batch, stream, true);
     const bool footprint_fast = g.model != SF_MODEL_SIDDON && G->fp_columns;
     const bool siddon_fast = g.model == SF_MODEL_SIDDON && G->sd_columns;
     if (footprint_fast || siddon_fast) {
@@ -456,6 +576,7 @@ int leap_launch_project(const leap_geometry *G, const float *d_vol, float *d_sin
 {
     const SfGeom &g = G->g;
     if (g.model == SF_MODEL_SIDDON) return launch_sd_project(G, d_vol, d_sino, stream);
+    if (G->flat) return project_flat(G, d_vol, d_sino, 1, stream, false);
     if (G->fp_columns) return leap_launch_project_batch(G, d_vol, d_sino, 1, stream);
     if (G->d_mfviews) {                     // sizes were checked against the grid limits at creation
         dim3 grid(cdiv(g.ncols, 64), cdiv(cdiv(g.nrows, MF_RC), 4), g.nviews);
@@ -553,6 +674,7 @@ int leap_launch_backproject_batch(const leap_geometry *G, const float *d_sino, f
 {
     const SfGeom &g = G->g;
     const size_t nvol = (size_t)g.nx * g.ny * g.nz, nsino = (size_t)g.nviews * g.nrows * g.ncols;
+    if (G->flat) return backproject_flat(G, d_sino, d_vol, batch, stream);
     if (G->bp_tiled) {
         // up to 16 items per launch (a batch of small training volumes fills the chip better that way)
         for (int b = 0; b < batch; b += 16) {
@@ -574,6 +696,7 @@ int leap_launch_backproject(const leap_geometry *G, const float *d_sino, float *
 {
     const SfGeom &g = G->g;
     if (g.model == SF_MODEL_SIDDON) return launch_sd_backproject(G, d_sino, d_vol, stream);
+    if (G->flat) return backproject_flat(G, d_sino, d_vol, 1, stream);
     if (G->bp_tiled) return launch_bp_items(G, d_sino, d_vol, 1, stream);
     if (G->d_mfviews) {
         dim3 grid(cdiv(g.nx, 64), cdiv(g.ny, 4), g.nz);
@@ -650,6 +773,7 @@ extern "C" int leap_project_static_scratch(const leap_geometry *G, const float *
     const bool siddon_fast = g.model == SF_MODEL_SIDDON && G->sd_columns;
     if (!footprint_fast && !siddon_fast) {
         // this geometry runs on kernels that read the caller's volume directly: no scratch is involved at all
+        if (G->flat) return project_flat(G, d_vol, d_sino, batch, stream, false);
         const size_t nvol = (size_t)g.nx * g.ny * g.nz, nsino = (size_t)g.nviews * g.nrows * g.ncols;
         for (int b = 0; b < batch; ++b) {
             const int rc = leap_launch_project(G, d_vol + b * nvol, d_sino + b * nsino, stream);
