@@ -14,6 +14,7 @@
 #include "sf_project_columns.h"
 #include "md_backproject_tiled.h"
 #include "sf_flat.h"
+#include "md_footprint_tiled.h"
 #include <thread>
 #include "sd_backproject_tiled.h"
 
@@ -569,6 +570,58 @@ static void select_tilted_siddon_kernels(leap_geometry *G)
     G->bp_tiled = true;
 }
 
+// Footprint model, scans with tilted modules: the fast kernels of md_footprint_tiled.h.
+static void select_tilted_footprint_kernels(leap_geometry *G)
+{
+    const leap_geometry_desc *d = &G->desc;
+    const SfGeom &g = G->g;
+    long v;
+    if (debug_option("general", v) && v == 1) return;
+    // Forward: layers are walked along x or y, whichever a tile's central ray advances faster on.  Modules seen from above,
+    // whose rays advance fastest along z, have beams that cross such a layer in long strips: they stay with the general
+    // kernel, which can walk along z.
+    G->mf_tiles = tilted_rays_stay_flat(G, d->voxel_xy / d->voxel_z);
+    // Back: the staged window of every (view, tile, chunk) must fit.  The boxes' corners are the points of one lattice; the
+    // views are shared out among a few threads.
+    const int tiles_x = (d->nx + MF_T - 1) / MF_T, tiles_y = (d->ny + MF_T - 1) / MF_T, chunks = (d->nz + MF_ZC - 1) / MF_ZC;
+    const int lx = tiles_x + 1, ly = tiles_y + 1, lz = chunks + 1;
+    const int workers = (int)std::max<size_t>(1, std::min<size_t>(8, G->mfviews.size() / 8));
+    std::vector<int> need(workers, 0);
+    auto scan = [&](int t) {
+        std::vector<float> xi((size_t)lx * ly * lz), eta(xi.size());
+        int worst = 0;
+        for (size_t a = t; a < G->mfviews.size(); a += workers) {
+            const MfView &V = G->mfviews[a];
+            for (int z = 0; z < lz; ++z)
+                for (int y = 0; y < ly; ++y)
+                    for (int x = 0; x < lx; ++x) {
+                        const size_t o = ((size_t)z * ly + y) * lx + x;
+                        // corner 0 of the box that starts here: the lattice point itself
+                        mf_box_corner(g, V, std::min(x * MF_T, d->nx), 0, std::min(y * MF_T, d->ny), 0, std::min(z * MF_ZC, d->nz), 0, 0, xi[o], eta[o]);
+                    }
+            for (int z = 0; z < chunks; ++z)
+                for (int y = 0; y < tiles_y; ++y)
+                    for (int x = 0; x < tiles_x; ++x) {
+                        float a0 = 3.0e38f, a1 = -3.0e38f, b0 = 3.0e38f, b1 = -3.0e38f;
+                        for (int q = 0; q < 8; ++q) {
+                            const size_t o = ((size_t)(z + (q >> 2)) * ly + y + ((q >> 1) & 1)) * lx + x + (q & 1);
+                            a0 = std::min(a0, xi[o]); a1 = std::max(a1, xi[o]);
+                            b0 = std::min(b0, eta[o]); b1 = std::max(b1, eta[o]);
+                        }
+                        const MfWindow w = mf_window(a0, a1, b0, b1);
+                        // one spare row and column: host and device may round apart
+                        worst = std::max(worst, a1 - a0 < 4096.0f && b1 - b0 < 4096.0f ? (w.w + 1) * (w.h + 1) : 1 << 30);
+                    }
+        }
+        need[t] = worst;
+    };
+    std::vector<std::thread> pool;
+    for (int t = 1; t < workers; ++t) pool.emplace_back(scan, t);
+    scan(0);
+    for (auto &th : pool) th.join();
+    G->mf_tiled = *std::max_element(need.begin(), need.end()) <= MF_PATCH;
+}
+
 // Picks the kernels of a validated scan (circular scanners, or modular scans made of upright modules).
 static void select_fast_kernels(leap_geometry *G)
 {
@@ -927,6 +980,7 @@ static int create_modular(const leap_geometry_desc *d, leap_geometry **out)
                 return LEAP_UNSUPPORTED;
             }
         }
+        select_tilted_footprint_kernels(G);
     }
     return finish_handle(G, out);
 }
@@ -1050,7 +1104,7 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
         std::snprintf(fwd, sizeof fwd, "columns(nq=%d/%d,nkp=%d,rg=%d,cw=%d,slab=%d)", G->fp_need_q, G->fp_nq, G->fp_nkp,
                       G->fp_rg, G->fp_cw, G->slab_width);
     else
-        std::snprintf(fwd, sizeof fwd, G->flat ? "general(flat,span=%d)" : "general", G->flat_span);
+        std::snprintf(fwd, sizeof fwd, G->flat ? "general(flat,span=%d)" : (G->mf_tiles ? "general(tiles)" : "general"), G->flat_span);
     if (G->bp_tiled && G->d_mdbp)
         std::snprintf(back, sizeof back, "tiled(zc=%d,window=%dx%d)", MD_BP_SHAPES[G->bp_shape].zc, G->bp_need_w, G->bp_need_h);
     else if (G->bp_tiled && siddon)
@@ -1059,7 +1113,7 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
         std::snprintf(back, sizeof back, "tiled(nc=%d,nv=%d,zc=%d,window=%dx%d)", G->bp_nc, G->bp_nv, BP_SHAPES[G->bp_shape].zc,
                       G->bp_need_w, G->bp_need_h);
     else
-        std::snprintf(back, sizeof back, G->flat ? "general(flat)" : "general");
+        std::snprintf(back, sizeof back, G->flat ? "general(flat)" : (G->mf_tiled ? "general(tiled)" : "general"));
     const char *modules = G->g.type != SF_MODULAR ? "" : (G->geoms.empty() ? " (tilted modules)" : " (upright modules)");
     std::snprintf(buf, (size_t)cap, "type=%d model=%s A=%s AT=%s scratch=%zu%s cols/voxel<=%.2f rows/voxel<=%.2f voxels/row<=%.2f%s%s",
                   G->g.type, siddon ? "siddon" : "sf", fwd, back, G->scratch_bytes, modules, G->max_cols_per_voxel,

@@ -69,6 +69,7 @@ struct leap_geometry {
     // footprint model on tilted modules: per-view table of the general kernels (md_footprint.h)
     std::vector<MfView> mfviews;
     MfView *d_mfviews = nullptr;
+    bool mf_tiles = false, mf_tiled = false;   // the fast kernels of md_footprint_tiled.h, forward / back
     void *d_colcs = nullptr;            // cylinder, tiled back projection: (cos, sin) of every column's fan angle, then the (tile, view) table
     // leap_project_host / leap_backproject_host: created by the first such call, freed with the handle
     mutable LeapHostStage *host_stage = nullptr;

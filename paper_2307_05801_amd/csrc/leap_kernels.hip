@@ -13,6 +13,7 @@
 #include "md_project_columns.h"
 #include "sd_backproject_tiled.h"
 #include "md_backproject_tiled.h"
+#include "md_footprint_tiled.h"
 
 // ------------------------------------------------------------------------------------------------
 // General kernels: plain loop nests over global memory, valid for every validated geometry.
@@ -578,6 +579,12 @@ int leap_launch_project(const leap_geometry *G, const float *d_vol, float *d_sin
     if (g.model == SF_MODEL_SIDDON) return launch_sd_project(G, d_vol, d_sino, stream);
     if (G->flat) return project_flat(G, d_vol, d_sino, 1, stream, false);
     if (G->fp_columns) return leap_launch_project_batch(G, d_vol, d_sino, 1, stream);
+    if (G->mf_tiles) {
+        dim3 grid(cdiv(cdiv(g.ncols, MF_TC), 4), cdiv(g.nrows, MF_TR), g.nviews);
+        hipLaunchKernelGGL(mf_project_tiles, grid, dim3(256), 0, stream, g, G->d_mfviews, d_vol, d_sino);
+        LEAP_HIP_CHECK(hipGetLastError());
+        return LEAP_OK;
+    }
     if (G->d_mfviews) {                     // sizes were checked against the grid limits at creation
         dim3 grid(cdiv(g.ncols, 64), cdiv(cdiv(g.nrows, MF_RC), 4), g.nviews);
         hipLaunchKernelGGL(mf_project_general, grid, dim3(64, 4, 1), 0, stream, g, G->d_mfviews, d_vol, d_sino);
@@ -698,6 +705,13 @@ int leap_launch_backproject(const leap_geometry *G, const float *d_sino, float *
     if (g.model == SF_MODEL_SIDDON) return launch_sd_backproject(G, d_sino, d_vol, stream);
     if (G->flat) return backproject_flat(G, d_sino, d_vol, 1, stream);
     if (G->bp_tiled) return launch_bp_items(G, d_sino, d_vol, 1, stream);
+    if (G->mf_tiled) {
+        const unsigned tiles_x = cdiv(g.nx, MF_T), tiles_y = cdiv(g.ny, MF_T);
+        hipLaunchKernelGGL(mf_backproject_tiled, dim3(tiles_x * tiles_y, cdiv(g.nz, MF_ZC)), dim3(256), 0, stream, g, G->d_mfviews, d_sino,
+                           d_vol, (int)tiles_x);
+        LEAP_HIP_CHECK(hipGetLastError());
+        return LEAP_OK;
+    }
     if (G->d_mfviews) {
         dim3 grid(cdiv(g.nx, 64), cdiv(g.ny, 4), g.nz);
         hipLaunchKernelGGL(mf_backproject_general, grid, dim3(64, 4, 1), 0, stream, g, G->d_mfviews, d_sino, d_vol);

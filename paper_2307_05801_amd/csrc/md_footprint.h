@@ -26,6 +26,10 @@ struct MfView {
     double ipu, ipv;                         // 1 / pixel pitch along the column / row axis, 1/mm
     double pad_u, pad_v;                     // mm: how far the column coordinate of a voxel's corner / the row coordinate
                                              // of a face centre can lie from those of the voxel's centre (upper bounds)
+    // for the fast kernels: the point S + d projects to column d.euP / d.nP + xi0 and row coordinate d.evP / d.nP + eta0;
+    // nA, uA (nB, uB): what the in-plane corner (+T/2, +T/2) ((+T/2, -T/2)) adds to d.nP and d.euP, with their squares and
+    // products; dN, dU, dW: what one voxel up adds to d.nP, d.euP and d.evP
+    double nP[3], euP[3], evP[3], xi0, eta0, nA, nB, uA, uB, nA2, nB2, unA, unB, dN, dU, dW;
 };
 
 // Host: fills the derived members of V (S, C, eu, ev set) for the volume of g.  Returns false if the view has no
@@ -43,6 +47,18 @@ inline bool mf_prepare_view(const SfGeom &g, MfView &V)
         V.sv += (V.S[q] - V.C[q]) * V.ev[q];
     }
     if (!(V.gap > 0.0) && !(V.gap < 0.0)) return false;
+    for (int q = 0; q < 3; ++q) {
+        V.nP[q] = V.n[q] / V.gap;
+        V.euP[q] = V.eu[q] * V.ipu;
+        V.evP[q] = V.ev[q] * V.ipv;
+    }
+    V.xi0 = V.su * V.ipu + g.col_offd;
+    V.eta0 = (V.sv - g.v0d) * V.ipv + 0.5;
+    V.nA = 0.5 * g.Td * (V.nP[0] + V.nP[1]); V.nB = 0.5 * g.Td * (V.nP[0] - V.nP[1]);
+    V.uA = 0.5 * g.Td * (V.euP[0] + V.euP[1]); V.uB = 0.5 * g.Td * (V.euP[0] - V.euP[1]);
+    V.nA2 = V.nA * V.nA; V.nB2 = V.nB * V.nB;
+    V.unA = V.uA * V.nA; V.unB = V.uB * V.nB;
+    V.dN = g.Tzd * V.nP[2]; V.dU = g.Tzd * V.euP[2]; V.dW = g.Tzd * V.evP[2];
     // over the volume's box: the smallest distance from the source along n and the largest tangents of the angle
     // between a point's ray and n (ratios of linear functions: extremes at the corners)
     const double lo[3] = {g.x0d - 0.5 * g.Td, g.y0d - 0.5 * g.Td, g.zlo0d};
