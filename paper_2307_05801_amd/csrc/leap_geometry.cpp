@@ -56,7 +56,8 @@ static void build_ray_table(leap_geometry *G)
     const leap_geometry_desc &d = G->desc;
     const double T = d.voxel_xy, Tz = d.voxel_z;
     G->raycols.resize((size_t)d.nviews * d.ncols);
-    double max_slope = 0.0;
+    double max_slope = 0.0, min_h = 1e300, max_h = 0.0;
+    G->sd_max_z = 0.0;
     for (int a = 0; a < d.nviews; ++a) {
         // modular scans with upright modules bring one parameter block per view: a circular cone-beam view of the
         // translated scene, with its own source distance, detector distance and column offset
@@ -100,11 +101,17 @@ static void build_ray_table(leap_geometry *G)
                 R.h0 = 0.0; R.dh = 0.0; R.vscale = 0.0f;
             }
             max_dh = std::fmax(max_dh, std::fabs(R.dh));
+            const double h_near = R.h0, h_far = R.h0 + R.dh * (R.xmajor ? d.nx : d.ny);
+            min_h = std::fmin(min_h, std::fmin(h_near, h_far));
+            max_h = std::fmax(max_h, std::fmax(h_near, h_far));
             G->raycols[(size_t)a * d.ncols + col] = R;
         }
         const double vmax = std::fmax(std::fabs(g.v0d), std::fabs(g.v0d + (d.nrows - 1) * g.pvd));
         max_slope = std::fmax(max_slope, max_dh * vmax);
+        G->sd_max_z = std::fmax(G->sd_max_z, std::fabs(g.zk0d) + (vmax + 1024.0 * d.pixel_v) * max_h);
     }
+    G->sd_min_row_step = min_h * d.pixel_v;
+    G->sd_max_row_step = max_h * d.pixel_v;
     G->sd_max_axial_slope = max_slope;
 }
 
@@ -381,6 +388,10 @@ static void select_siddon_fast_kernels(leap_geometry *G)
         G->sd_columns = true;
         static const int single_groups[] = {1, 2, 4, 8};
         G->fp_rg = row_groups(d->nrows, 64, single_groups, 4);
+        // Two rows per lane where adjacent rows lie less than two voxels apart (their cells then fit one 16-byte load) and Z
+        // fits the placement's fixed point.  Detectors of up to 64 rows would leave half the lanes idle: one row each.
+        if (G->fp_rg >= 2 && G->sd_min_row_step > 0.0 && G->sd_max_row_step < 2.0 - 1e-6 && G->sd_max_z < 500000.0)
+            G->sd_pairs = G->sd_min_row_step > 1.0 + 1e-6 ? 2 : 1;
         block_order_options(G);
     }
 
@@ -1099,7 +1110,7 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
     char fwd[160], back[96];
     const bool siddon = G->g.model == SF_MODEL_SIDDON;
     if (siddon && G->sd_columns)
-        std::snprintf(fwd, sizeof fwd, "columns(rg=%d,slab=%d)", G->fp_rg, G->slab_width);
+        std::snprintf(fwd, sizeof fwd, "columns(rg=%d,slab=%d%s)", G->fp_rg, G->slab_width, G->sd_pairs == 2 ? ",pairs apart" : (G->sd_pairs ? ",pairs" : ""));
     else if (!siddon && G->fp_columns)
         std::snprintf(fwd, sizeof fwd, "columns(nq=%d/%d,nkp=%d,rg=%d,cw=%d,slab=%d)", G->fp_need_q, G->fp_nq, G->fp_nkp,
                       G->fp_rg, G->fp_cw, G->slab_width);

@@ -60,6 +60,8 @@ struct leap_geometry {
     std::vector<SdRayCol> raycols;
     SdRayCol *d_raycols = nullptr;
     double sd_max_axial_slope = 0;      // largest |dZ/dX| of any ray: voxels of z crossed per slab
+    double sd_min_row_step = 0, sd_max_row_step = 0, sd_max_z = 0;   // voxels of z between adjacent rows; largest |Z| of any ray
+    int sd_pairs = 0;                   // two rows per lane (sd_project_pairs): 0 no, 1 rows closer than a voxel somewhere, 2 nowhere
     // modular geometry: per-view poses, host copy and device copy
     std::vector<MdPose> poses;
     MdPose *d_poses = nullptr;

@@ -209,8 +209,39 @@ static void launch_sd_columns(const leap_geometry *G, const FwdScratch &S, const
                            slab, (const SfGeom *)nullptr);
 }
 
+// Two rows per lane; RG pair groups of 128 rows.
+template <int RG>
+static void launch_sd_pairs(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
+{
+    const SfGeom &g = G->g;
+    const int col_tiles = (int)cdiv(g.ncols, 4), bands = (int)cdiv(g.nrows, RG * 128);
+    const int vb = G->fp_vb, tb = G->fp_tb;
+    const int views_pad = (int)cdiv(g.nviews, vb) * vb;
+    const int tiles_per_xcd_pad = (int)cdiv(cdiv(col_tiles, 8), tb) * tb;
+    dim3 grid((unsigned)(8 * tiles_per_xcd_pad * views_pad * bands), (unsigned)items, 1);
+    auto go = [&](auto kernel, const SfGeom *geoms) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, g, G->d_raycols, S.volz, d_sino, G->nzp, S.item_floats, col_tiles, bands, vb,
+                           tb, views_pad, tiles_per_xcd_pad, slab, geoms);
+    };
+    if (g.type == SF_MODULAR) {
+        if (G->sd_pairs == 2) go(sd_project_pairs<RG, true, true>, G->d_geoms);
+        else go(sd_project_pairs<RG, false, true>, G->d_geoms);
+    } else {
+        if (G->sd_pairs == 2) go(sd_project_pairs<RG, true, false>, nullptr);
+        else go(sd_project_pairs<RG, false, false>, nullptr);
+    }
+}
+
 static bool launch_sd_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
 {
+    if (G->sd_pairs) {
+        switch (G->fp_rg) {
+        case 2: launch_sd_pairs<1>(G, S, slab, d_sino, stream, items); return true;
+        case 4: launch_sd_pairs<2>(G, S, slab, d_sino, stream, items); return true;
+        case 8: launch_sd_pairs<4>(G, S, slab, d_sino, stream, items); return true;
+        default: return false;
+        }
+    }
     switch (G->fp_rg) {
     case 1: launch_sd_columns<1>(G, S, slab, d_sino, stream, items); return true;
     case 2: launch_sd_columns<2>(G, S, slab, d_sino, stream, items); return true;

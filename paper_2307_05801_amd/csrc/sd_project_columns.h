@@ -78,7 +78,228 @@ SF_HD float sd_gather_two(const float *__restrict__ xa, const float *__restrict_
     return fmaf(omf - b_low, xb[1], t);
 }
 
+// ---- two adjacent rows per lane ("sd_project_pairs" below) -------------------------------------------------------------
+//
+// The vector cache charges a wave-wide load for its lanes, not for their width (four lanes per clock, 4 bytes or 16), and
+// the one-row kernel, with an 8-byte load per row, slab and in-plane cell, is bound by that.  Two adjacent rows lie less
+// than two voxels apart where this kernel is chosen, so the two cells of either lie within four consecutive voxels: one
+// 16-byte load per pair and cell.
+//
+// Placement without conversions, from the UPPER end of a row's piece: Z is formed by one double FMA to which 1.5 * 2^20 has
+// been added, so the sum's low word is 2^32 times the fraction, which is the way down to the face below, and its high word
+// is a constant plus the upper cell.  The share of the slab spent in the upper cell is that way over |dZ|, at most 1; the
+// rest is spent in the cell below.
+
+struct SdPairRow {
+    double vr, zadj;
+    float inv;           // 1 / (2^32 |dZ per slab|)
+    bool inc;
+};
+
+SF_HD SdPairRow sd_pair_row(const SfGeom &g, const SdRayCol &R, int r)
+{
+    SdPairRow A;
+    A.vr = sd_row_v(g, r);
+    const double mz = A.vr * R.dh;
+    const float amz = fabsf((float)mz);
+    const bool level = !(amz > 1e-30f);
+    A.zadj = g.zk0d + (double)FP_PAD + FP_KAP_MAGIC + fmax(mz, 0.0);
+    // a ray that runs level stays in its upper cell, on a face in the cell above it: the nudge of two units of the fraction
+    // keeps the share of a ray exactly on a face at 1
+    if (level) A.zadj += 4.6566128730773926e-10;
+    A.inv = (level ? 1e30f : 1.0f / amz) * 2.3283064365386963e-10f;
+    A.inc = mz >= 0.0;
+    return A;
+}
+
+// Upper cell (FP_KAP_HI plus its index in the padded column) and the share of the slab spent in it.
+SF_HD void sd_pair_place(const SdPairRow &A, double h, unsigned &hi, float &share)
+{
+    const double q = fma(A.vr, h, A.zadj);
+    unsigned long long bits;
+    __builtin_memcpy(&bits, &q, 8);
+    hi = (unsigned)(bits >> 32);
+    share = sf_clamp((float)(unsigned)bits * A.inv, 0.0f, 1.0f);
+}
+
+// A slab whose piece stays in one in-plane cell: lo, up are the lower and the upper axial cell's voxel.
+SF_HD float sd_pair_one(float lo, float up, float share, float acc) { return fmaf(share, up - lo, acc + lo); }
+
+// A slab whose piece changes from in-plane cell a to b at tau = f (omf = 1 - f).  A rising ray is in the upper cell last: for
+// `share` of the slab, as far as that reaches in b and then in a; a falling ray first, in a and then in b.
+SF_HD float sd_pair_two(float alo, float aup, float blo, float bup, bool inc, float f, float omf, float share, float acc)
+{
+    const float first = inc ? bup - blo : aup - alo, second = inc ? aup - alo : bup - blo;
+    const float over = sf_clamp(share - (inc ? omf : f), 0.0f, 1.0f);       // what of the share reaches into the other cell
+    const float t = fmaf(f, alo, fmaf(omf, blo, acc));
+    return fmaf(over, second - first, fmaf(share, first, t));
+}
+
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
+
+// RG: groups of 128 rows per wave: lane l owns the row pairs band0 + 128 g + 2 l + {0, 1}.  SPREAD: adjacent rows are at least
+// one voxel apart everywhere (one test tells where the upper row's cells lie in the load instead of two).  MOD as below.
+// Slabs whose cells both lie outside the volume are skipped; a single cell outside is read through an empty buffer
+// descriptor, which returns zeros without touching memory.
+template <int RG, bool SPREAD, bool MOD>
+__global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCol *__restrict__ rays, const float *__restrict__ volz,
+                                                        float *__restrict__ sino, int nzp, size_t item_stride, int col_tiles, int bands,
+                                                        int vb, int tb, int views_pad, int tiles_per_xcd_pad, SfSlab slab,
+                                                        const SfGeom *__restrict__ geoms)
+{
+    constexpr int WAVES = 4, ROWS = RG * 128;
+    __shared__ float4 recs[WAVES][64];
+    __shared__ float4 out[ROWS];                     // [row][column]: the workgroup's share of the sinogram
+    __shared__ int live_waves[WAVES];
+    volz += (size_t)blockIdx.y * item_stride;
+    sino += (size_t)blockIdx.y * gk.nviews * gk.nrows * gk.ncols;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int ct, band, a;
+    {   // block -> (view, band, column tile) in the XCD-aware order of sd_project_columns
+        const int xcd = blockIdx.x & 7, sq = blockIdx.x >> 3;
+        const int per_chunk = tb * views_pad;
+        const int chunk = sq / per_chunk, r = sq - chunk * per_chunk;
+        const int vblk = r / (tb * vb), r2 = r - vblk * (tb * vb);
+        const int tloc = r2 / vb, v_in = r2 - tloc * vb;
+        const int tchunks = tiles_per_xcd_pad / tb;
+        band = chunk / tchunks;
+        ct = ((chunk - band * tchunks) * tb + tloc) * 8 + xcd;
+        a = vblk * vb + v_in;
+        if (ct >= col_tiles || a >= gk.nviews || band >= bands) return;   // whole workgroups
+    }
+    const int c = ct * WAVES + wave;
+    const SfGeom &g = MOD ? geoms[a] : gk;
+    const int band0 = band * ROWS;
+    const SdRayCol R = rays[(size_t)a * g.ncols + (c < g.ncols ? c : g.ncols - 1)];
+    const bool live = c < g.ncols && R.xmajor == slab.xmajor;        // this column's rays read this kind of slab
+
+    SdPairRow A[RG][2];
+    float acc[RG][2];
+#pragma unroll
+    for (int gq = 0; gq < RG; ++gq)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            A[gq][p] = sd_pair_row(g, R, band0 + 128 * gq + 2 * lane + p);
+            acc[gq][p] = 0.0f;
+        }
+    if (live) {
+        const int n_major = slab.n1, n_minor = R.xmajor ? g.ny : g.nx;
+        const unsigned col_bytes = (unsigned)nzp * 4u;
+        const unsigned off_k = 0u - (FP_KAP_HI << 2) - 4u;           // byte offset of the cell below the lower row's upper cell
+        for (int nb = slab.n0; nb < n_major; nb += 64) {
+            // ---- lane-parallel: the in-plane part of slab nb + lane
+            const int n = nb + lane;
+            const SdSplit s = sd_slab_split(R, n);
+            const bool in_n = n < n_major, two = s.qa != s.qb;
+            const bool a_ok = in_n && s.qa >= 0 && s.qa < n_minor, b_ok = in_n && two && s.qb >= 0 && s.qb < n_minor;
+            const unsigned base_a = a_ok ? sf_slab_column(slab, g.nx, R.xmajor ? n : s.qa, R.xmajor ? s.qa : n) * (unsigned)nzp : 0u;
+            const unsigned base_b = b_ok ? sf_slab_column(slab, g.nx, R.xmajor ? n : s.qb, R.xmajor ? s.qb : n) * (unsigned)nzp : 0u;
+            const double h = fma((double)n, R.dh, R.h0);
+            recs[wave][lane] = make_float4(__builtin_bit_cast(float, __double2loint(h)), __builtin_bit_cast(float, __double2hiint(h)), s.f, 1.0f - s.f);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const unsigned long long in_a = __ballot(a_ok), in_b = __ballot(b_ok), cross = __ballot(two);
+            // ---- wave-uniform walk over the slabs that meet the volume
+            for (unsigned long long mask = in_a | in_b; mask; mask &= mask - 1) {
+                const int e = __builtin_ctzll(mask);
+                const float4 rec = recs[wave][e];
+                const double s_h = __hiloint2double(__builtin_bit_cast(int, rec.y), __builtin_bit_cast(int, rec.x));
+                const __amdgpu_buffer_rsrc_t col_a = __builtin_amdgcn_make_buffer_rsrc(
+                    (void *)(volz + (unsigned)__builtin_amdgcn_readlane((int)base_a, e)), 0, (in_a >> e) & 1ull ? (int)col_bytes : 0, 0x00020000);
+                auto place = [&](int gq, float (&share)[2], int &off, unsigned &d) {
+                    unsigned hi0, hi1;
+                    sd_pair_place(A[gq][0], s_h, hi0, share[0]);
+                    sd_pair_place(A[gq][1], s_h, hi1, share[1]);
+                    asm("v_lshl_add_u32 %0, %1, 2, %2" : "=v"(off) : "v"(hi0), "s"(off_k));
+                    d = hi1 - hi0;                    // 0, 1 or 2 (SPREAD: 1 or 2) voxels between the rows' upper cells
+                };
+                auto load = [&](const __amdgpu_buffer_rsrc_t &col, int off, float (&x)[4]) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) x[t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(col, off + 4 * t, 0, 0));
+                };
+                auto upper_row = [&](const float (&x)[4], unsigned d, float &lo, float &up) {
+                    lo = d > 1u ? x[2] : x[1];
+                    up = d > 1u ? x[3] : x[2];
+                    if constexpr (!SPREAD) {
+                        lo = d == 0u ? x[0] : lo;
+                        up = d == 0u ? x[1] : up;
+                    }
+                };
+                if ((cross >> e) & 1ull) {
+                    const __amdgpu_buffer_rsrc_t col_b = __builtin_amdgcn_make_buffer_rsrc(
+                        (void *)(volz + (unsigned)__builtin_amdgcn_readlane((int)base_b, e)), 0, (in_b >> e) & 1ull ? (int)col_bytes : 0, 0x00020000);
+                    float share[RG][2], xa[RG][4], xb[RG][4];
+                    unsigned d[RG];
+#pragma unroll
+                    for (int gq = 0; gq < RG; ++gq) {
+                        int off;
+                        place(gq, share[gq], off, d[gq]);
+                        load(col_a, off, xa[gq]);
+                        load(col_b, off, xb[gq]);
+                    }
+#pragma unroll
+                    for (int gq = 0; gq < RG; ++gq) {
+                        acc[gq][0] = sd_pair_two(xa[gq][0], xa[gq][1], xb[gq][0], xb[gq][1], A[gq][0].inc, rec.z, rec.w, share[gq][0], acc[gq][0]);
+                        float alo, aup, blo, bup;
+                        upper_row(xa[gq], d[gq], alo, aup);
+                        upper_row(xb[gq], d[gq], blo, bup);
+                        acc[gq][1] = sd_pair_two(alo, aup, blo, bup, A[gq][1].inc, rec.z, rec.w, share[gq][1], acc[gq][1]);
+                    }
+                } else {
+                    float share[RG][2], x[RG][4];
+                    unsigned d[RG];
+#pragma unroll
+                    for (int gq = 0; gq < RG; ++gq) {
+                        int off;
+                        place(gq, share[gq], off, d[gq]);
+                        load(col_a, off, x[gq]);
+                    }
+#pragma unroll
+                    for (int gq = 0; gq < RG; ++gq) {
+                        float lo, up;
+                        upper_row(x[gq], d[gq], lo, up);
+                        acc[gq][0] = sd_pair_one(x[gq][0], x[gq][1], share[gq][0], acc[gq][0]);
+                        acc[gq][1] = sd_pair_one(lo, up, share[gq][1], acc[gq][1]);
+                    }
+                }
+            }
+        }
+    }
+    // ---- store: the four columns of a row together (each by itself is a 4-byte write into a line of its own)
+    if (lane == 0) live_waves[wave] = live;
+#pragma unroll
+    for (int gq = 0; gq < RG; ++gq)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+            reinterpret_cast<float *>(&out[128 * gq + 2 * lane + p])[wave] = sd_ray_length(R, A[gq][p].vr) * acc[gq][p];
+    __syncthreads();
+    const bool w0 = live_waves[0], w1 = live_waves[1], w2 = live_waves[2], w3 = live_waves[3];
+    if (!(w0 | w1 | w2 | w3)) return;
+    struct __attribute__((packed, aligned(4))) Quad { float a, b, c, d; };
+    float *__restrict__ ya = sino + (size_t)a * g.nrows * g.ncols + (size_t)ct * WAVES;
+#pragma unroll
+    for (int row = threadIdx.x; row < ROWS; row += 256) {
+        const int r = band0 + row;
+        if (r >= g.nrows) continue;
+        const float4 v = out[row];
+        float *__restrict__ dst = ya + (size_t)r * g.ncols;
+        if (w0 & w1 & w2 & w3) {
+            Quad q = {v.x, v.y, v.z, v.w};
+            if (!slab.first) {
+                const Quad old = *reinterpret_cast<const Quad *>(dst);
+                q.a += old.a; q.b += old.b; q.c += old.c; q.d += old.d;
+            }
+            *reinterpret_cast<Quad *>(dst) = q;
+        } else {
+            if (w0) dst[0] = slab.first ? v.x : dst[0] + v.x;
+            if (w1) dst[1] = slab.first ? v.y : dst[1] + v.y;
+            if (w2) dst[2] = slab.first ? v.z : dst[2] + v.z;
+            if (w3) dst[3] = slab.first ? v.w : dst[3] + v.w;
+        }
+    }
+}
 
 // MOD: modular geometry with upright modules: the wave's view brings its own parameter block geoms[a] (the scene
 // translated so that the view is a circular cone-beam view; gk holds the sizes, which all views share).
