@@ -432,6 +432,20 @@ static int run_forward_columns(const leap_geometry *G, const FwdScratch &S, cons
         const int items = batch - b < S.items ? batch - b : S.items;
         const float *vol = d_vol + (size_t)b * nvol;
         float *sino = d_sino + (size_t)b * nsino;
+        if (S.width >= (g.nx > g.ny ? g.nx : g.ny)) {
+            // The whole volume fits: one copy, and one launch for the rays of either axis.  (As two slabs the copy was made
+            // twice and each launch had half the rays to fill the chip with.)
+            const SfSlab whole = {0, 0, -1, 1, g.nx};
+            dim3 tgrid(cdiv(g.nx, 32), cdiv(g.nz, 32), (unsigned)(g.ny * items));
+            hipLaunchKernelGGL(sf_volume_to_columns, tgrid, dim3(32, 8, 1), 0, stream, vol, S.volz, g.nx, g.ny, g.nz, G->nzp, 0, 0, g.nx,
+                               g.ny, S.item_floats);
+            const bool ok = siddon ? launch_sd_slab(G, S, whole, sino, stream, items) : launch_fp_slab(G, S, whole, sino, stream, items);
+            if (!ok) {
+                leap_set_error("internal: no column-wise forward instance for this geometry");
+                return LEAP_UNSUPPORTED;
+            }
+            continue;
+        }
         for (int xmajor = 1; xmajor >= 0; --xmajor) {
             const int n_major = xmajor ? g.nx : g.ny;
             for (int n0 = 0; n0 < n_major; n0 += S.width) {

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
                                                                     const float *__restrict__ volz, float *__restrict__ sino,
                                                                     int nzp, size_t item_stride, unsigned zero_col, int col_tiles,
                                                                     int bands, int vb, int tb, int views_pad,
-                                                                    int tiles_per_xcd_pad, SfSlab slab)
+                                                                    int tiles_per_xcd_pad, SfSlab all)
 {
     volz += (size_t)blockIdx.y * item_stride;
     sino += (size_t)blockIdx.y * g.nviews * g.nrows * g.ncols;
@@ -131,22 +131,36 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
     MdAxial A[RG];
     float acc[RG];
     bool mine[RG];
-    bool any = false;
+    bool inside[RG];
 #pragma unroll
     for (int gq = 0; gq < RG; ++gq) {
         const int r = band0 + 64 * gq + lane;
         M[gq] = md_slab_ray(g, P, r < g.nrows ? r : g.nrows - 1, c);
         A[gq] = md_axial(M[gq]);
-        mine[gq] = r < g.nrows && M[gq].R.xmajor == slab.xmajor;
+        inside[gq] = r < g.nrows;
+        mine[gq] = false;
         acc[gq] = 0.0f;
-        any = any || mine[gq];
     }
-    if (__ballot(any) == 0ull) return;               // no ray of this wave reads this kind of slab
-
-    for (int n = slab.n0; n < slab.n1; ++n) {
+    // the slabs of this launch's kind; the whole volume serves the rays of either axis, one after the other
+    bool any = false;
+    for (int kind = 1; kind >= 0; --kind) {
+        const SfSlab slab = sf_slab_for(all, kind, g.nx, g.ny);
+        if (slab.xmajor != kind) continue;
+        bool now[RG], some = false;
 #pragma unroll
-        for (int gq = 0; gq < RG; ++gq) acc[gq] = md_slab_step(g, M[gq], A[gq], n, slab, volz, nzp, zero_col, mine[gq], acc[gq]);
+        for (int gq = 0; gq < RG; ++gq) {
+            now[gq] = inside[gq] && M[gq].R.xmajor == kind;
+            mine[gq] = mine[gq] || now[gq];
+            some = some || now[gq];
+        }
+        if (__ballot(some) == 0ull) continue;        // no ray of this wave reads this kind of slab
+        any = true;
+        for (int n = slab.n0; n < slab.n1; ++n) {
+#pragma unroll
+            for (int gq = 0; gq < RG; ++gq) acc[gq] = md_slab_step(g, M[gq], A[gq], n, slab, volz, nzp, zero_col, now[gq], acc[gq]);
+        }
     }
+    if (!any) return;
 
     float *__restrict__ ya = sino + (size_t)a * g.nrows * g.ncols + c;
 #pragma unroll
@@ -154,7 +168,7 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
         const int r = band0 + 64 * gq + lane;
         if (mine[gq]) {
             const float part = M[gq].len * acc[gq];
-            ya[(size_t)r * g.ncols] = slab.first ? part : ya[(size_t)r * g.ncols] + part;
+            ya[(size_t)r * g.ncols] = all.first ? part : ya[(size_t)r * g.ncols] + part;
         }
     }
 }

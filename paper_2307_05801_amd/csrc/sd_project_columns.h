@@ -144,7 +144,7 @@ SF_HD float sd_pair_two(float alo, float aup, float blo, float bup, bool inc, fl
 template <int RG, bool SPREAD, bool MOD>
 __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCol *__restrict__ rays, const float *__restrict__ volz,
                                                         float *__restrict__ sino, int nzp, size_t item_stride, int col_tiles, int bands,
-                                                        int vb, int tb, int views_pad, int tiles_per_xcd_pad, SfSlab slab,
+                                                        int vb, int tb, int views_pad, int tiles_per_xcd_pad, SfSlab all,
                                                         const SfGeom *__restrict__ geoms)
 {
     constexpr int WAVES = 4, ROWS = RG * 128;
@@ -172,6 +172,7 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
     const SfGeom &g = MOD ? geoms[a] : gk;
     const int band0 = band * ROWS;
     const SdRayCol R = rays[(size_t)a * g.ncols + (c < g.ncols ? c : g.ncols - 1)];
+    const SfSlab slab = sf_slab_for(all, R.xmajor, g.nx, g.ny);
     const bool live = c < g.ncols && R.xmajor == slab.xmajor;        // this column's rays read this kind of slab
 
     SdPairRow A[RG][2];
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(SD_WAVES * 64) void sd_project_columns(SfGeom gk, c
                                                                     const float *__restrict__ volz, float *__restrict__ sino,
                                                                     int nzp, size_t item_stride, unsigned zero_col, int col_tiles,
                                                                     int bands, int vb, int tb, int views_pad,
-                                                                    int tiles_per_xcd_pad, SfSlab slab,
+                                                                    int tiles_per_xcd_pad, SfSlab all,
                                                                     const SfGeom *__restrict__ geoms)
 {
     // blockIdx.y: item of a batch (its scratch copy and its sinogram)
@@ -337,6 +338,7 @@ __global__ __launch_bounds__(SD_WAVES * 64) void sd_project_columns(SfGeom gk, c
     const int band0 = band * (RG * 64);
 
     const SdRayCol R = rays[(size_t)a * g.ncols + c];
+    const SfSlab slab = sf_slab_for(all, R.xmajor, g.nx, g.ny);
     if (R.xmajor != slab.xmajor) return;             // this column's rays read the other kind of slab
     const int n_major = slab.n1;
     const int n_minor = R.xmajor ? g.ny : g.nx;

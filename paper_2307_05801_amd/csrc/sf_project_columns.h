@@ -7,7 +7,8 @@
 // (i0 = n0, ni = width, j0 = 0) serves the ray bundles that advance fastest along x, a slab across y (j0 = n0, ni = nx,
 // i0 = 0) those that advance fastest along y; the host walks the volume slab by slab, and every bundle adds the slab's
 // share to its sinogram samples (the first slab of its kind overwrites).  The scratch therefore holds a fraction of
-// the volume, chosen by the host.
+// the volume, chosen by the host.  Where the whole volume fits the scratch, its copy has the same layout whichever axis it is
+// cut across, and one copy and one launch serve both kinds of bundles.
 //
 // Work split.  One 64-lane wavefront owns CW adjacent detector columns of one view and a band of RG * 128 detector
 // rows: lane l owns the row PAIRS band0 + 128 g + 2 l + {0, 1}, g < RG, of each of its columns.  Because all lanes share
@@ -110,10 +111,21 @@ SF_HD void sf_candidates(const SfRayLines &L, int n, int &q_first, int &q_last)
 // One slab of the volume as the scratch copy holds it.
 struct SfSlab {
     int n0, n1;       // slab indices [n0, n1) along the marching axis
-    int xmajor;       // 1: the slab cuts x (serves bundles that advance fastest along x), 0: it cuts y
+    int xmajor;       // 1: the slab cuts x (serves bundles that advance fastest along x), 0: it cuts y, -1: the whole volume (serves all)
     int first;        // 1: bundles overwrite their sinogram samples, 0: they add to them
     int width;        // slabs the scratch layout is built for (>= n1 - n0)
 };
+
+// The slab as a bundle that advances fastest along x (xmajor == 1) or y sees it: the whole volume is cut across its axis.
+SF_HD SfSlab sf_slab_for(const SfSlab &s, int xmajor, int nx, int ny)
+{
+    SfSlab k = s;
+    if (s.xmajor < 0) {
+        k.xmajor = xmajor;
+        k.n1 = xmajor ? nx : ny;
+    }
+    return k;
+}
 
 // Index of voxel column (i, j) among the columns of the slab's scratch copy.
 SF_HD unsigned sf_slab_column(const SfSlab &s, int nx, int i, int j)
@@ -274,7 +286,7 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG <= 2 ? 4 : 3) : 1) voi
                                                                     const unsigned char *__restrict__ major, int nzp,
                                                                     size_t item_stride, int nq_log2, int col_tiles, int bands,
                                                                     int vb, int tb, int vgroups_pad, int tiles_per_xcd_pad,
-                                                                    SfSlab slab, const SfGeom *__restrict__ geoms)
+                                                                    SfSlab all, const SfGeom *__restrict__ geoms)
 {
     // GT == 2 (modular geometry, upright modules): the wave's view brings its own parameter block, the scene
     // translated so that the view is a circular cone-beam view; gk holds the sizes, which all views share.
@@ -306,6 +318,7 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG <= 2 ? 4 : 3) : 1) voi
     const int c0 = bundle * CW;                          // first detector column of this wave
     if (c0 >= gsz.ncols) return;
     const int nbundles = (gsz.ncols + CW - 1) / CW;
+    const SfSlab slab = sf_slab_for(all, __builtin_amdgcn_readfirstlane((int)major[(size_t)a * nbundles + bundle]), gsz.nx, gsz.ny);
     if ((int)major[(size_t)a * nbundles + bundle] != slab.xmajor) return;   // this bundle reads the other kind of slab
     const int band0 = band * (RG * 128);
 
