@@ -101,9 +101,21 @@ static void build_ray_table(leap_geometry *G)
                 R.h0 = 0.0; R.dh = 0.0; R.vscale = 0.0f;
             }
             max_dh = std::fmax(max_dh, std::fabs(R.dh));
-            const double h_near = R.h0, h_far = R.h0 + R.dh * (R.xmajor ? d.nx : d.ny);
-            min_h = std::fmin(min_h, std::fmin(h_near, h_far));
-            max_h = std::fmax(max_h, std::fmax(h_near, h_far));
+            // h over the slabs in which the line meets the volume (a slab and a cell to spare)
+            const double n_major = R.xmajor ? d.nx : d.ny, n_minor = R.xmajor ? d.ny : d.nx;
+            double x_in = 0.0, x_out = n_major;
+            if (R.m != 0.0) {
+                const double xa = (-1.0 - R.b) / R.m, xb = (n_minor + 1.0 - R.b) / R.m;
+                x_in = std::fmax(x_in, std::fmin(xa, xb) - 1.0);
+                x_out = std::fmin(x_out, std::fmax(xa, xb) + 1.0);
+            } else if (R.b < -1.0 || R.b > n_minor + 1.0) {
+                x_out = -1.0;
+            }
+            if (x_in <= x_out) {
+                const double ha = R.h0 + R.dh * x_in, hb = R.h0 + R.dh * x_out;
+                min_h = std::fmin(min_h, std::fmin(ha, hb));
+                max_h = std::fmax(max_h, std::fmax(ha, hb));
+            }
             G->raycols[(size_t)a * d.ncols + col] = R;
         }
         const double vmax = std::fmax(std::fabs(g.v0d), std::fabs(g.v0d + (d.nrows - 1) * g.pvd));
