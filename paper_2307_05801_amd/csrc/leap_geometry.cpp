@@ -240,10 +240,17 @@ static void select_footprint_tiled(leap_geometry *G)
     const float hx = 0.5f * (float)(BP_T - 1) * G->g.T;
     // 64-voxel chunks only pay off on tall volumes; the two-row instances keep 64 sums in registers in either 64-voxel
     // shape, the three-row instances in the tall one only
-    int order[BP_NSHAPES], norder = 0;
+    int order[BP_NSHAPES + 1], norder = 0;
     if (d->nz >= 128 && G->bp_nv == 2) order[norder++] = 0;
     if (d->nz >= 128 && G->bp_nv <= 3) order[norder++] = BP_TALL_SHAPE;
-    for (int sh = BP_FIRST_SHORT_SHAPE; sh <= BP_LAST_SHORT_SHAPE; ++sh) order[norder++] = sh;
+    // The wide window's 32 voxels per thread: for voxels of up to a row and a half (taller ones are limited by LDS reads), where
+    // it leaves the chip at least two workgroups per compute unit and no more than a fifth of the layers as padding.
+    const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T), chunks32 = (d->nz + 31) / 32;
+    const bool wide = G->bp_nv <= 3 && mr <= 1.5 && (G->bp_nc == 3 || G->bp_nc == 4) && tiles * chunks32 >= 512 && 160 * chunks32 <= 6 * d->nz;
+    for (int sh = BP_FIRST_SHORT_SHAPE; sh <= BP_LAST_SHORT_SHAPE; ++sh) {
+        if (wide && sh == 3) order[norder++] = BP_WIDE_SHAPE;        // before the 16-voxel shapes
+        order[norder++] = sh;
+    }
     long forced;
     if (debug_option("bp_shape", forced)) {        // start at a given shape, then the short ones after it
         forced = ((forced % BP_NSHAPES) + BP_NSHAPES) % BP_NSHAPES;

@@ -28,11 +28,18 @@ struct SfBpShape {
 // The last one keeps 64 voxels per thread for footprints up to two rows tall (its 96 rows hold what 64 voxels of up to
 // about 1.3 rows each project to); it is instantiated for NV <= 3 only, shape 0 for NV == 2 only (the general gather of
 // taller footprints would spill registers).
-constexpr SfBpShape BP_SHAPES[] = {{64, 32, 76}, {32, 32, 44}, {32, 32, 56}, {16, 32, 44}, {16, 64, 48}, {64, 32, 96}};
-constexpr int BP_NSHAPES = 6;
+constexpr SfBpShape BP_SHAPES[] = {{64, 32, 76}, {32, 32, 44}, {32, 32, 56}, {16, 32, 44}, {16, 64, 48}, {64, 32, 96}, {32, 42, 56}};
+constexpr int BP_NSHAPES = 6;                // of which the debugging override can start from
 constexpr int BP_FIRST_SHORT_SHAPE = 1;      // first shape with fewer than 64 voxels per thread
 constexpr int BP_LAST_SHORT_SHAPE = 4;       // last one
 constexpr int BP_TALL_SHAPE = 5;
+// 32 voxels per thread under a window wider than 32 columns (two- and three-row footprints, three or four columns wide): a
+// view's set-up (window, knots, transaxial weights: about 150 instructions) is paid once for 32 voxels instead of 16.  42
+// columns are what 252 threads stage six rows of at a time.  Instantiated for the footprint model only.  121 views of 211 x 187
+// x 149 voxels on 163 x 257 pixels: 0.81 -> 0.71 ms.  (A window of 51 x 80 for voxels of up to two rows and three columns measured
+// no better than 16 voxels under 64 x 48, 7.8 against 7.7 ms on eight 256^3 volumes of 60 views: eight samples per voxel from LDS are
+// the limit there.)
+constexpr int BP_WIDE_SHAPE = 6;
 
 // Window of the detector that one (view, tile, z-chunk) can touch.  Evaluated identically on the host
 // (limit check) and in the kernel; everything here is uniform over the workgroup.
@@ -214,9 +221,10 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC > 32) ? 3 : 4) voi
     };
     const SfBpScene scene0 = sf_bp_scene<BP_ZC>(geom_of(0), i0, j0, k0);
 
-    // staging role: element e = tid + 256 s  ->  window column tid % PW, window row tid / PW + RSTEP s
-    const int sc = tid & (BP_PW - 1), sr = tid / BP_PW;
-    constexpr int NSTAGE = (BP_PH * BP_PW + 255) / 256;
+    // staging role: window column tid % PW, window rows tid / PW + RSTEP s (threads left over where PW does not divide 256
+    // stage the next step's first row, as their owners do)
+    const int sc = tid % BP_PW, sr = tid / BP_PW;
+    constexpr int NSTAGE = (BP_PH + 256 / BP_PW - 1) / (256 / BP_PW);
     const size_t view_stride = (size_t)g.nrows * g.ncols;
 
     float acc[BP_ZC];
