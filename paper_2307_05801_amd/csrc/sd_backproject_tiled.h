@@ -124,14 +124,17 @@ SF_HD SdBpScene sd_bp_scene(const SfGeom &g, int i0, int j0, int k0)
 constexpr double SD_BP_MAGIC = 1572864.0;        // 1.5 * 2^20
 constexpr unsigned SD_BP_HI = 0x41380000u;       // its high word
 
+typedef __attribute__((address_space(3))) float SdLds;
+
+// apart: adjacent rows are at least one voxel apart wherever a ray meets the volume.
 template <int NCS, int ZC, int PW, int PH, bool MOD>
 __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
                                                             const SdRayCol *__restrict__ rays, const float *__restrict__ sino,
-                                                            float *__restrict__ vol, int tiles_x,
+                                                            float *__restrict__ vol, int tiles_x, int apart,
                                                             const SfGeom *__restrict__ geoms)
 {
     constexpr int PS = PW + BP_ROW_PAD;
-    constexpr int NSLOT = ZC + 4;                  // slot s holds voxel k0 + s - 2; slots 0, 1, ZC+2, ZC+3 are dumps
+    constexpr int NSLOT = ZC + 4;                  // slot s holds voxel k0 + ZC + 1 - s; slots 0, 1, ZC+2, ZC+3 are dumps
     __shared__ float patch[2][PH * PS];
     __shared__ float rinv[2][PH];
     __shared__ float sums[NSLOT * 256];
@@ -160,6 +163,8 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
 
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) sums[s * 256 + tid] = 0.0f;
+    // LDS address of this thread's slot SD_BP_HI (mod 2^32): a slot's address is that plus 1024 times its number
+    const unsigned sums_at = (unsigned)(uintptr_t)(SdLds *)(sums + tid) - (SD_BP_HI << 10);
 
     float stage[NSTAGE];
     SfWindow win, win_next;
@@ -199,8 +204,9 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
             const double ha = fma((double)n + (double)t0, R.dh, R.h0), hb = fma((double)n + (double)t1, R.dh, R.h0);
             // Every row of the window is walked (rows that cannot reach the chunk fall into the dump slots), in two
             // wave-uniform runs: rows below the source plane (v < 0), whose lower end in Z is where h is larger, and
-            // rows at or above it.  Within a run the lower end advances by pv * h per row; it is carried as a 32.32
-            // fixed-point number whose upper word is the slot and whose lower word the fraction.
+            // rows at or above it.  Within a run the lower end advances by pv * h per row; its negative is carried as a
+            // 32.32 fixed-point number, whose lower word is the way up to the next z-face and whose upper word counts slots
+            // downwards (the slots are laid out that way): neither needs an instruction of its own.
             const double hmin = fmin(ha, hb), hmax = fmax(ha, hb);
             const float dh = (float)(hmax - hmin);
             // dt over the piece's rise in Z is scale / |v_r| / 2^32 times the fixed-point distance to the next z-face
@@ -216,23 +222,60 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
                 // The fixed-point number lives in a double: with 1.5 * 2^20 added, a double's unit in the last place is
                 // 2^-32, so its low word is the fraction and its high word SD_BP_HI plus the slot, and advancing it is one
                 // double addition (exact: both terms are multiples of 2^-32) instead of a 64-bit integer add in two halves.
-                double q = floor(fma(sd_row_v(gv, win.r0 + rs), h, zrel0) * 4294967296.0) * 2.3283064365386963e-10 + SD_BP_MAGIC;
+                double q = floor(fma(sd_row_v(gv, win.r0 + rs), -h, (double)(NSLOT - 1) - zrel0) * 4294967296.0) * 2.3283064365386963e-10 + SD_BP_MAGIC;
                 const double dq = rint(gv.pvd * h * 4294967296.0) * 2.3283064365386963e-10;
-                unsigned ofs = (unsigned)(rs * PS + wc);
-                for (int row = rs; row < re; ++row) {
-                    const unsigned long long qbits = __builtin_bit_cast(unsigned long long, q);
-                    int slot = (int)((unsigned)(qbits >> 32) - SD_BP_HI);
-                    slot = slot < 0 ? 0 : (slot > ZC + 2 ? ZC + 2 : slot);
-                    const float up = (float)(~(unsigned)qbits) + 1.0f;  // (1 - fraction) * 2^32, at least 1
-                    const float wl = fminf(up * (scale * ri[row]), dt);
-                    const float y = buf[ofs];
-                    float *__restrict__ cell = sums + (slot * 256 + tid);
+                // One row: the slot's LDS address and the two shares' factors.
+                auto place = [&](double at, float inv, unsigned &cell, float &wl) {
+                    // (a lower end exactly on a face: the way up to it is 0 and the slot that of the cell below, which gets nothing)
+                    const unsigned long long qbits = __builtin_bit_cast(unsigned long long, at);
+                    unsigned slot = (unsigned)(qbits >> 32);
+                    slot = slot < SD_BP_HI ? SD_BP_HI : (slot > SD_BP_HI + ZC + 2 ? SD_BP_HI + ZC + 2 : slot);
+                    asm("v_lshl_add_u32 %0, %1, 10, %2" : "=v"(cell) : "v"(slot), "v"(sums_at));
+                    wl = fminf((float)(unsigned)qbits * (scale * inv), dt);       // way up to the next face * 2^32 over the rise
+                };
+                const float *yp = buf + (rs * PS + wc), *ip = ri + rs;
+                int row = rs;
+                // Rows at least a voxel apart: a row and the next but one share no slot, so two rows' sums can be fetched
+                // before the first of them is written back (the walk waits on that round trip).  A row clamped into the dump
+                // slots may meet another's dump slot, whose contents nobody reads.  512^3 x 720 views: 77.3 -> 68.9 ms.
+                if (apart) {
+                    for (; row + 4 <= re; row += 4) {
+                        float y[4], inv[4], wl[4];
+                        unsigned cell[4];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) { y[t] = yp[t * PS]; inv[t] = ip[t]; }
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            place(q, inv[t], cell[t], wl[t]);
+                            q -= dq;
+                        }
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) {
+                            SdLds *const c0 = (SdLds *)(uintptr_t)cell[t], *const c1 = (SdLds *)(uintptr_t)cell[t + 2];
+                            const float u0 = c0[0], l0 = c0[256], u1 = c1[0], l1 = c1[256];
+                            c0[0] = fmaf(dt - wl[t], y[t], u0);
+                            c0[256] = fmaf(wl[t], y[t], l0);
+                            c1[0] = fmaf(dt - wl[t + 2], y[t + 2], u1);
+                            c1[256] = fmaf(wl[t + 2], y[t + 2], l1);
+                        }
+                        yp += 4 * PS;
+                        ip += 4;
+                    }
+                }
+                for (; row < re; ++row) {
+                    unsigned cell;
+                    float wl;
+                    place(q, *ip, cell, wl);
+                    const float y = *yp;
                     // plain read-add-write: the slot has no other writer, and a wave's LDS accesses retire in order
                     // (the LDS float atomic measured 7x slower than this on the 512^3 case)
-                    cell[0] += wl * y;
-                    cell[256] += (dt - wl) * y;
-                    q += dq;
-                    ofs += PS;
+                    SdLds *const c = (SdLds *)(uintptr_t)cell;
+                    const float u = c[0], l = c[256];
+                    c[0] = fmaf(dt - wl, y, u);
+                    c[256] = fmaf(wl, y, l);
+                    q -= dq;
+                    yp += PS;
+                    ++ip;
                 }
             }
         }
@@ -247,7 +290,7 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
     if (i < g.nx && j < g.ny) {
 #pragma unroll
         for (int kk = 0; kk < ZC; ++kk)
-            if (k0 + kk < g.nz) vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sums[(kk + 2) * 256 + tid];
+            if (k0 + kk < g.nz) vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sums[(ZC + 1 - kk) * 256 + tid];
     }
 }
 
