@@ -155,9 +155,55 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
         }
         if (__ballot(some) == 0ull) continue;        // no ray of this wave reads this kind of slab
         any = true;
-        for (int n = slab.n0; n < slab.n1; ++n) {
+        // md_slab_step for all row groups at once, the same sums bit for bit.  The rays of a detector column run nearly
+        // together, so a slab usually finds all of them in the volume or none, and changing their in-plane cell or none: slabs
+        // that all miss are skipped, and the second cells are only read where some ray enters one.  A cell's place in the
+        // scratch copy is q pitch_q + n pitch_n: one integer multiplication per ray and slab instead of four.  256^3 x 360 views
+        // x 256^2: 8.35 -> 6.30 ms (8.87 with a branch per row group: the groups' loads must be in flight together).
+        const int n_minor = kind ? g.ny : g.nx;
+        const unsigned pitch_q = (unsigned)nzp * (kind ? (unsigned)slab.width : 1u), pitch_n = (unsigned)nzp * (kind ? 1u : (unsigned)g.nx);
+        unsigned base_n = 0;
+        for (int n = slab.n0; n < slab.n1; ++n, base_n += pitch_n) {
+            SdSplit s[RG];
+            bool a_ok[RG], b_ok[RG], meets = false, two = false;
 #pragma unroll
-            for (int gq = 0; gq < RG; ++gq) acc[gq] = md_slab_step(g, M[gq], A[gq], n, slab, volz, nzp, zero_col, now[gq], acc[gq]);
+            for (int gq = 0; gq < RG; ++gq) {
+                s[gq] = sd_slab_split(M[gq].R, n);
+                const bool live = now[gq] && md_slab_in_front(M[gq], n);
+                a_ok[gq] = live && (unsigned)s[gq].qa < (unsigned)n_minor;
+                b_ok[gq] = live && s[gq].qa != s[gq].qb && (unsigned)s[gq].qb < (unsigned)n_minor;
+                meets = meets || a_ok[gq] || b_ok[gq];
+                two = two || s[gq].qa != s[gq].qb;
+            }
+            if (__builtin_amdgcn_ballot_w64(meets) == 0) continue;
+            float tlow[RG], xa0[RG], xa1[RG];
+            unsigned at_a[RG], k[RG];
+#pragma unroll
+            for (int gq = 0; gq < RG; ++gq) {
+                int kf;
+                sd_axial_cell(fma((double)n, M[gq].R.dh, A[gq].zadj), A[gq].inv_amz, nzp - 2, kf, tlow[gq]);
+                k[gq] = (unsigned)kf;
+                at_a[gq] = (unsigned)s[gq].qa * pitch_q + base_n;
+                const float *__restrict__ xa = volz + ((a_ok[gq] ? at_a[gq] : zero_col) + k[gq]);
+                xa0[gq] = xa[0]; xa1[gq] = xa[1];
+            }
+            if (__builtin_amdgcn_ballot_w64(two)) {
+                float xb0[RG], xb1[RG];
+#pragma unroll
+                for (int gq = 0; gq < RG; ++gq) {
+                    const unsigned at_b = s[gq].qb > s[gq].qa ? at_a[gq] + pitch_q : at_a[gq] - pitch_q;
+                    const float *__restrict__ xb = volz + ((b_ok[gq] ? at_b : zero_col) + k[gq]);
+                    xb0[gq] = xb[0]; xb1[gq] = xb[1];
+                }
+#pragma unroll
+                for (int gq = 0; gq < RG; ++gq) {
+                    const float xa[2] = {xa0[gq], xa1[gq]}, xb[2] = {xb0[gq], xb1[gq]};
+                    acc[gq] = sd_gather_two(xa, xb, A[gq].inc, s[gq].f, 1.0f - s[gq].f, tlow[gq], acc[gq]);
+                }
+            } else {
+#pragma unroll
+                for (int gq = 0; gq < RG; ++gq) acc[gq] = fmaf(1.0f - tlow[gq], xa1[gq], fmaf(tlow[gq], xa0[gq], acc[gq]));
+            }
         }
     }
     if (!any) return;
