@@ -350,6 +350,15 @@ static void select_footprint_columns(leap_geometry *G)
     G->fp_columns = need <= 16;
     block_order_options(G);
     if (!G->fp_columns) return;
+    // Parallel beams: the axial overlaps go into the slab copy and a wave's lanes own adjacent rows, as many as it takes for
+    // one wave to hold the detector's height, up to 512 rows.  Only where the copy by rows of the whole volume fits either
+    // scratch (up to 256^3): a detector of many more rows than the volume has layers would otherwise take narrower slabs.
+    const double n_side = std::max(d->nx, d->ny);
+    if (d->type == LEAP_PARALLEL && G->fp_cw >= 2 &&
+        4.0 * (n_side * n_side + 1.0) * ((d->nrows + 3) / 4 * 4 + 2 * FP_PAD) <= (double)LEAP_STATIC_SCRATCH_BYTES) {
+        G->fp_rows = d->nrows <= 64 ? 1 : (d->nrows <= 128 ? 2 : 4);
+        G->fp_row_groups = d->nrows > 256 ? 2 : 1;
+    }
     const int nbundles = (d->ncols + G->fp_cw - 1) / G->fp_cw;
     G->major.resize((size_t)d->nviews * nbundles);
     for (int a = 0; a < d->nviews; ++a)
@@ -674,7 +683,7 @@ bool leap_plan_scratch(const leap_geometry *G, size_t floats, int batch, int &wi
 {
     const leap_geometry_desc *d = &G->desc;
     const int n_side = std::max(d->nx, d->ny);                  // a slab holds up to width * n_side voxel columns
-    const double nzp = d->nz + 2.0 * FP_PAD;
+    const double nzp = G->nzp;
     auto width_for = [&](int it) {
         const double w = std::floor(((double)floats / it - nzp) / (nzp * n_side));
         return w >= n_side ? n_side : (w < 4 ? 0 : ((int)w & ~3));
@@ -702,7 +711,7 @@ static void allocate_forward_scratch(leap_geometry *G)
 {
     const leap_geometry_desc *d = &G->desc;
     if (!G->fp_columns && !G->sd_columns) return;
-    G->nzp = d->nz + 2 * FP_PAD;
+    G->nzp = (G->fp_rows ? (d->nrows + 3) / 4 * 4 : d->nz) + 2 * FP_PAD;      // floats per voxel column of the copy
     const double volume_bytes = 4.0 * d->nx * d->ny * (double)d->nz;
     const double share = volume_bytes / (d->model == LEAP_MODEL_SIDDON ? 4.0 : 8.0);
     double budget = volume_bytes / 8.0 >= 64.0 * 1048576.0 ? share : 128.0 * 1048576.0;
@@ -1131,8 +1140,8 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
     if (siddon && G->sd_columns)
         std::snprintf(fwd, sizeof fwd, "columns(rg=%d,slab=%d%s)", G->fp_rg, G->slab_width, G->sd_pairs == 2 ? ",pairs apart" : (G->sd_pairs ? ",pairs" : ""));
     else if (!siddon && G->fp_columns)
-        std::snprintf(fwd, sizeof fwd, "columns(nq=%d/%d,nkp=%d,rg=%d,cw=%d,slab=%d)", G->fp_need_q, G->fp_nq, G->fp_nkp,
-                      G->fp_rg, G->fp_cw, G->slab_width);
+        std::snprintf(fwd, sizeof fwd, "columns(nq=%d/%d,nkp=%d,rg=%d,cw=%d,slab=%d%s)", G->fp_need_q, G->fp_nq, G->fp_nkp,
+                      G->fp_rg, G->fp_cw, G->slab_width, G->fp_rows ? ",rows" : "");
     else
         std::snprintf(fwd, sizeof fwd, G->flat ? "general(flat,span=%d)" : (G->mf_tiles ? "general(tiles)" : "general"), G->flat_span);
     if (G->bp_tiled && G->d_mdbp)

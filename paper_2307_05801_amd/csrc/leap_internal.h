@@ -40,6 +40,8 @@ struct leap_geometry {
     int fp_rg = 0;                      // row groups per wave (footprints: groups of 128 rows; Siddon: of 64)
     int fp_cw = 4, fp_vb = 128, fp_tb = 1;   // detector columns per wave; block order: views per run, tiles per chunk
     bool fp_columns = false;
+    int fp_rows = 0;                    // parallel beams: rows per lane of sf_project_rows (0: not used); fp_row_groups groups of 64 of them
+    int fp_row_groups = 1;
     bool flat = false;                  // one row, one layer: the kernels of sf_flat.h in both directions
     int flat_span = 0;                  // voxels of a slab that the beams of 64 adjacent columns cover, rounded up to 64
     float flat_fv = 1.0f;               // the scan's one axial weight

@@ -8,6 +8,7 @@
 #include "sf_general.h"
 #include "sf_backproject_tiled.h"
 #include "sf_project_columns.h"
+#include "sf_project_rows.h"
 #include "sf_flat.h"
 #include "sd_project_columns.h"
 #include "md_project_columns.h"
@@ -407,8 +408,39 @@ static bool launch_fp_rg(const leap_geometry *G, const FwdScratch &S, const SfSl
     }
 }
 
+template <int RV, int RG, int CW>
+static void launch_fp_rows(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
+{
+    const SfGeom &g = G->g;
+    const int col_tiles = (int)cdiv(g.ncols, FP_WAVES * CW), bands = (int)cdiv(g.nrows, RG * 64 * RV);
+    const int vb = G->fp_vb, tb = G->fp_tb;
+    const int vgroups_pad = (int)cdiv(g.nviews, vb) * vb;
+    const int tiles_per_xcd_pad = (int)cdiv(cdiv(col_tiles, 8), tb) * tb;
+    int nq_log2 = 2;
+    while ((1 << nq_log2) < G->fp_nq) ++nq_log2;
+    dim3 grid((unsigned)(8 * tiles_per_xcd_pad * vgroups_pad * bands), (unsigned)items, 1);
+    hipLaunchKernelGGL((sf_project_rows<RV, RG, CW>), grid, dim3(FP_WAVES * 64, 1, 1), 0, stream, g, G->d_views, S.volz, d_sino, G->d_major,
+                       G->nzp, S.item_floats, nq_log2, col_tiles, bands, vb, tb, vgroups_pad, tiles_per_xcd_pad, slab);
+}
+
+static bool launch_fp_rows_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
+{
+    switch (G->fp_rows * 100 + G->fp_row_groups * 10 + G->fp_cw) {
+    case 112: launch_fp_rows<1, 1, 2>(G, S, slab, d_sino, stream, items); return true;
+    case 114: launch_fp_rows<1, 1, 4>(G, S, slab, d_sino, stream, items); return true;
+    case 212: launch_fp_rows<2, 1, 2>(G, S, slab, d_sino, stream, items); return true;
+    case 214: launch_fp_rows<2, 1, 4>(G, S, slab, d_sino, stream, items); return true;
+    case 412: launch_fp_rows<4, 1, 2>(G, S, slab, d_sino, stream, items); return true;
+    case 414: launch_fp_rows<4, 1, 4>(G, S, slab, d_sino, stream, items); return true;
+    case 422: launch_fp_rows<4, 2, 2>(G, S, slab, d_sino, stream, items); return true;
+    case 424: launch_fp_rows<4, 2, 4>(G, S, slab, d_sino, stream, items); return true;
+    default: return false;
+    }
+}
+
 static bool launch_fp_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
 {
+    if (G->fp_rows) return launch_fp_rows_slab(G, S, slab, d_sino, stream, items);
     switch (G->fp_nkp) {
     case 2: return launch_fp_rg<2>(G, S, slab, d_sino, stream, items);
     case 3: return launch_fp_rg<3>(G, S, slab, d_sino, stream, items);
@@ -418,6 +450,19 @@ static bool launch_fp_slab(const leap_geometry *G, const FwdScratch &S, const Sf
     case 7: return launch_fp_rg<7>(G, S, slab, d_sino, stream, items);
     default: return false;
     }
+}
+
+// Copies voxel columns [i0, i0 + ni) x [j0, j0 + nj) of `items` volumes into the scratch: z-fastest, or by detector rows.
+static void copy_slab(const leap_geometry *G, const FwdScratch &S, const float *vol, int span, int i0, int j0, int ni, int nj, int items,
+                      hipStream_t stream)
+{
+    const SfGeom &g = G->g;
+    dim3 tgrid(cdiv(span, 32), cdiv(G->fp_rows ? g.nrows : g.nz, 32), (unsigned)(nj * items));
+    if (G->fp_rows)
+        hipLaunchKernelGGL(sf_volume_to_rows, tgrid, dim3(32, 8, 1), 0, stream, g, vol, S.volz, G->nzp, i0, j0, ni, nj, S.item_floats);
+    else
+        hipLaunchKernelGGL(sf_volume_to_columns, tgrid, dim3(32, 8, 1), 0, stream, vol, S.volz, g.nx, g.ny, g.nz, G->nzp, i0, j0, ni, nj,
+                           S.item_floats);
 }
 
 // The column-wise forward projection (footprint or Siddon weights) of a batch: up to S.items volumes at a time, each
@@ -437,9 +482,7 @@ static int run_forward_columns(const leap_geometry *G, const FwdScratch &S, cons
             // The whole volume fits: one copy, and one launch for the rays of either axis.  (As two slabs the copy was made
             // twice and each launch had half the rays to fill the chip with.)
             const SfSlab whole = {0, 0, -1, 1, g.nx};
-            dim3 tgrid(cdiv(g.nx, 32), cdiv(g.nz, 32), (unsigned)(g.ny * items));
-            hipLaunchKernelGGL(sf_volume_to_columns, tgrid, dim3(32, 8, 1), 0, stream, vol, S.volz, g.nx, g.ny, g.nz, G->nzp, 0, 0, g.nx,
-                               g.ny, S.item_floats);
+            copy_slab(G, S, vol, g.nx, 0, 0, g.nx, g.ny, items, stream);
             const bool ok = siddon ? launch_sd_slab(G, S, whole, sino, stream, items) : launch_fp_slab(G, S, whole, sino, stream, items);
             if (!ok) {
                 leap_set_error("internal: no column-wise forward instance for this geometry");
@@ -453,9 +496,7 @@ static int run_forward_columns(const leap_geometry *G, const FwdScratch &S, cons
                 const int n1 = n0 + S.width < n_major ? n0 + S.width : n_major;
                 const SfSlab slab = {n0, n1, xmajor, n0 == 0 ? 1 : 0, S.width};
                 const int i0 = xmajor ? n0 : 0, ni = xmajor ? S.width : g.nx, nj = xmajor ? g.ny : n1 - n0;
-                dim3 tgrid(cdiv(xmajor ? n1 - n0 : g.nx, 32), cdiv(g.nz, 32), (unsigned)(nj * items));
-                hipLaunchKernelGGL(sf_volume_to_columns, tgrid, dim3(32, 8, 1), 0, stream, vol, S.volz, g.nx, g.ny, g.nz, G->nzp, i0,
-                                   xmajor ? 0 : n0, ni, nj, S.item_floats);
+                copy_slab(G, S, vol, xmajor ? n1 - n0 : g.nx, i0, xmajor ? 0 : n0, ni, nj, items, stream);
                 const bool ok = siddon ? launch_sd_slab(G, S, slab, sino, stream, items) : launch_fp_slab(G, S, slab, sino, stream, items);
                 if (!ok) {
                     leap_set_error("internal: no column-wise forward instance for this geometry");
@@ -868,7 +909,7 @@ extern "C" int leap_project_static_scratch(const leap_geometry *G, const float *
     // the array keeps what the last call (of any handle) left in it: restore the zeros around this geometry's columns
     const unsigned ncolumns = (unsigned)width * (unsigned)n_side;
     const unsigned nthreads = ncolumns * 2u * FP_PAD > (unsigned)G->nzp ? ncolumns * 2u * FP_PAD : (unsigned)G->nzp;
-    for (int it = 0; it < per; ++it)
+    for (int it = 0; it < per && !G->fp_rows; ++it)          // (a copy by detector rows has no pads)
         hipLaunchKernelGGL(sf_clear_column_pads, dim3(cdiv(nthreads, 256)), dim3(256), 0, stream, volz + (size_t)it * S.item_floats,
                            ncolumns, g.nz, G->nzp);
     LEAP_HIP_CHECK(hipGetLastError());
