@@ -26,6 +26,8 @@
  *     volume through a z-fastest scratch copy, one SLAB of the volume at a time, so the handle
  *     owns a scratch of at most max(64 MiB, an eighth of one volume) -- leap_geometry_describe
  *     reports its size as "scratch=<bytes>"; small volumes share it between the items of a batch.
+ *     Flat scans (one row, one layer) keep room for a copy of up to 16 slices instead, which
+ *     leap_project uses for batches outside stream capture.
  *     If it cannot be allocated the handle works without it on a slower kernel, says so in
  *     leap_last_error at creation and in a "note=" of leap_geometry_describe.  A
  *     LEAP_MODEL_SIDDON handle also keeps a table of 48 bytes per (view, detector column): the
