@@ -240,7 +240,7 @@ static void select_footprint_tiled(leap_geometry *G)
     const float hx = 0.5f * (float)(BP_T - 1) * G->g.T;
     // 64-voxel chunks only pay off on tall volumes; the two-row instances keep 64 sums in registers in either 64-voxel
     // shape, the three-row instances in the tall one only
-    int order[BP_NSHAPES + 1], norder = 0;
+    int order[BP_NSHAPES], norder = 0;
     if (d->nz >= 128 && G->bp_nv == 2) order[norder++] = 0;
     if (d->nz >= 128 && G->bp_nv <= 3) order[norder++] = BP_TALL_SHAPE;
     // The wide window's 32 voxels per thread: for voxels of up to a row and a half (taller ones are limited by LDS reads), where
@@ -255,7 +255,7 @@ static void select_footprint_tiled(leap_geometry *G)
     if (debug_option("bp_shape", forced)) {        // start at a given shape, then the short ones after it
         forced = ((forced % BP_NSHAPES) + BP_NSHAPES) % BP_NSHAPES;
         norder = 0;
-        order[norder++] = (int)forced;
+        if (bp_instance_exists(G->bp_nc, G->bp_nv, (int)forced)) order[norder++] = (int)forced;
         for (int sh = std::max((int)forced + 1, BP_FIRST_SHORT_SHAPE); sh <= BP_LAST_SHORT_SHAPE; ++sh) order[norder++] = sh;
     }
     for (int n = 0; n < norder && !G->bp_tiled; ++n) {
@@ -1149,8 +1149,8 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
     else if (G->bp_tiled && siddon)
         std::snprintf(back, sizeof back, "tiled(nc=%d,zc=%d,window=%dx%d)", G->bp_nc, BP_SHAPES[G->bp_shape].zc, G->bp_need_w, G->bp_need_h);
     else if (G->bp_tiled)
-        std::snprintf(back, sizeof back, "tiled(nc=%d,nv=%d,zc=%d,window=%dx%d)", G->bp_nc, G->bp_nv, BP_SHAPES[G->bp_shape].zc,
-                      G->bp_need_w, G->bp_need_h);
+        std::snprintf(back, sizeof back, "tiled(nc=%d,nv=%d,zc=%d%s,window=%dx%d)", G->bp_nc, G->bp_nv, BP_SHAPES[G->bp_shape].zc,
+                      G->bp_shape == BP_WIDE_SHAPE ? ",wide" : "", G->bp_need_w, G->bp_need_h);
     else
         std::snprintf(back, sizeof back, G->flat ? "general(flat)" : (G->mf_tiled ? "general(tiled)" : "general"));
     const char *modules = G->g.type != SF_MODULAR ? "" : (G->geoms.empty() ? " (tilted modules)" : " (upright modules)");

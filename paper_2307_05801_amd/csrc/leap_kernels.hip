@@ -704,42 +704,29 @@ static void launch_bp_tiled_gt(const leap_geometry *G, const float *d_sino, floa
 }
 
 template <int NC, int NV, int SH>
-static void launch_bp_tiled(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
+static bool launch_bp_instance(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
 {
-    if (G->g.type == SF_CONE_CURVED) launch_bp_tiled_gt<NC, NV, SH, 1>(G, d_sino, d_vol, stream, items);
-    else if (G->g.type == SF_MODULAR) launch_bp_tiled_gt<NC, NV, SH, 2>(G, d_sino, d_vol, stream, items);
-    else launch_bp_tiled_gt<NC, NV, SH, 0>(G, d_sino, d_vol, stream, items);
+    if constexpr (bp_instance_exists(NC, NV, SH)) {
+        if (G->g.type == SF_CONE_CURVED) launch_bp_tiled_gt<NC, NV, SH, 1>(G, d_sino, d_vol, stream, items);
+        else if (G->g.type == SF_MODULAR) launch_bp_tiled_gt<NC, NV, SH, 2>(G, d_sino, d_vol, stream, items);
+        else launch_bp_tiled_gt<NC, NV, SH, 0>(G, d_sino, d_vol, stream, items);
+        return true;
+    } else {
+        return false;
+    }
 }
 
 template <int NC, int NV>
 static bool launch_bp_shape(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
 {
     switch (G->bp_shape) {
-    case 0:      // 64 voxels per thread: instances for two-row footprints only (taller ones would spill registers)
-        if constexpr (NV == 2) {
-            launch_bp_tiled<NC, NV, 0>(G, d_sino, d_vol, stream, items);
-            return true;
-        } else {
-            return false;
-        }
-    case 1: launch_bp_tiled<NC, NV, 1>(G, d_sino, d_vol, stream, items); return true;
-    case 2: launch_bp_tiled<NC, NV, 2>(G, d_sino, d_vol, stream, items); return true;
-    case 3: launch_bp_tiled<NC, NV, 3>(G, d_sino, d_vol, stream, items); return true;
-    case 4: launch_bp_tiled<NC, NV, 4>(G, d_sino, d_vol, stream, items); return true;
-    case BP_WIDE_SHAPE:
-        if constexpr (NV <= 3 && (NC == 3 || NC == 4)) {
-            launch_bp_tiled<NC, NV, BP_WIDE_SHAPE>(G, d_sino, d_vol, stream, items);
-            return true;
-        } else {
-            return false;
-        }
-    case BP_TALL_SHAPE:      // 64 voxels per thread under a taller window: two- and three-row instances
-        if constexpr (NV <= 3) {
-            launch_bp_tiled<NC, NV, BP_TALL_SHAPE>(G, d_sino, d_vol, stream, items);
-            return true;
-        } else {
-            return false;
-        }
+    case 0: return launch_bp_instance<NC, NV, 0>(G, d_sino, d_vol, stream, items);
+    case 1: return launch_bp_instance<NC, NV, 1>(G, d_sino, d_vol, stream, items);
+    case 2: return launch_bp_instance<NC, NV, 2>(G, d_sino, d_vol, stream, items);
+    case 3: return launch_bp_instance<NC, NV, 3>(G, d_sino, d_vol, stream, items);
+    case 4: return launch_bp_instance<NC, NV, 4>(G, d_sino, d_vol, stream, items);
+    case BP_TALL_SHAPE: return launch_bp_instance<NC, NV, BP_TALL_SHAPE>(G, d_sino, d_vol, stream, items);
+    case BP_WIDE_SHAPE: return launch_bp_instance<NC, NV, BP_WIDE_SHAPE>(G, d_sino, d_vol, stream, items);
     default: return false;
     }
 }

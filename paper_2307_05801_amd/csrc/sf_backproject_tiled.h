@@ -29,7 +29,7 @@ struct SfBpShape {
 // about 1.3 rows each project to); it is instantiated for NV <= 3 only, shape 0 for NV == 2 only (the general gather of
 // taller footprints would spill registers).
 constexpr SfBpShape BP_SHAPES[] = {{64, 32, 76}, {32, 32, 44}, {32, 32, 56}, {16, 32, 44}, {16, 64, 48}, {64, 32, 96}, {32, 42, 56}};
-constexpr int BP_NSHAPES = 6;                // of which the debugging override can start from
+constexpr int BP_NSHAPES = sizeof(BP_SHAPES) / sizeof(BP_SHAPES[0]);
 constexpr int BP_FIRST_SHORT_SHAPE = 1;      // first shape with fewer than 64 voxels per thread
 constexpr int BP_LAST_SHORT_SHAPE = 4;       // last one
 constexpr int BP_TALL_SHAPE = 5;
@@ -41,12 +41,34 @@ constexpr int BP_TALL_SHAPE = 5;
 // the limit there.)
 constexpr int BP_WIDE_SHAPE = 6;
 
+// Is the footprint kernel instantiated for NC columns, NV rows and this shape?
+constexpr bool bp_instance_exists(int nc, int nv, int shape)
+{
+    if (shape == 0) return nv == 2;
+    if (shape == BP_TALL_SHAPE) return nv <= 3;
+    if (shape == BP_WIDE_SHAPE) return nv <= 3 && (nc == 3 || nc == 4);
+    return true;
+}
+
 // Window of the detector that one (view, tile, z-chunk) can touch.  Evaluated identically on the host
 // (limit check) and in the kernel; everything here is uniform over the workgroup.
 struct SfWindow {
     int c0, r0;       // first staged column / row
     int need_w, need_h;
 };
+
+// Staging role of a thread under a window of pw columns and ph rows: it stages column sc of rows sr + (256 / pw) s, those
+// below ph.  Threads left over where pw does not divide 256 stage nothing: given the next step's first row, they would
+// write its cells without an order to the threads that own them, and not the same values either (the row's detector
+// coordinate comes from another number of float additions).
+struct SfStageRole {
+    int sc, sr;
+};
+
+SF_HD SfStageRole sf_stage_role(int tid, int pw, int ph)
+{
+    return {tid % pw, tid < 256 / pw * pw ? tid / pw : ph};
+}
 
 // Cylindrical detector: column-coordinate range [xi_lo, xi_hi] and the range [ilo, ihi] of 1 / (in-plane distance from
 // the source) over the square of half extent hx around (xc, yc).  The fan angle of a convex set is extreme at a
@@ -221,9 +243,8 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC > 32) ? 3 : 4) voi
     };
     const SfBpScene scene0 = sf_bp_scene<BP_ZC>(geom_of(0), i0, j0, k0);
 
-    // staging role: window column tid % PW, window rows tid / PW + RSTEP s (threads left over where PW does not divide 256
-    // stage the next step's first row, as their owners do)
-    const int sc = tid % BP_PW, sr = tid / BP_PW;
+    const SfStageRole role = sf_stage_role(tid, BP_PW, BP_PH);
+    const int sc = role.sc, sr = role.sr;
     constexpr int NSTAGE = (BP_PH + 256 / BP_PW - 1) / (256 / BP_PW);
     const size_t view_stride = (size_t)g.nrows * g.ncols;
 

@@ -208,6 +208,25 @@ extern "C" int host_check_backproject_windows(const leap_geometry *G, int64_t *r
     return bad != 0;
 }
 
+// ---- tiled back projection: who stages what ----------------------------------------------------------------------
+// Number of cells of any shape's window that are not written by exactly one (thread, step) of a workgroup: a cell without a
+// writer holds another view's sample, one with two writers in different steps is written without an order between them.
+extern "C" long host_check_staging_roles()
+{
+    long bad = 0;
+    for (const SfBpShape &S : BP_SHAPES) {
+        const int step = 256 / S.pw, nstage = (S.ph + step - 1) / step;
+        std::vector<int> writers((size_t)S.ph * S.pw, 0);
+        for (int tid = 0; tid < 256; ++tid) {
+            const SfStageRole role = sf_stage_role(tid, S.pw, S.ph);
+            for (int s = 0; s < nstage; ++s)
+                if (role.sr + step * s < S.ph) ++writers[(size_t)(role.sr + step * s) * S.pw + role.sc];
+        }
+        for (int w : writers) bad += w != 1;
+    }
+    return bad;
+}
+
 // ---- cylinder: the tile-relative column function of the tiled kernel against the general one ------------------------
 // out[0] = largest |difference| of the column coordinate (pixels), out[1] = of the four knot offsets, over every view,
 // tile and voxel column; out[2] = largest corner angle met (rad).

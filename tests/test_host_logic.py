@@ -254,6 +254,12 @@ def test_tiled_backprojection_reads_stay_inside_the_staged_window(host, name):
     assert rep[7] == 0, (rep, desc)
 
 
+def test_every_staged_sample_has_one_writer(host):
+    """Two threads that write one LDS cell in different steps race, even where they mean to write the same value."""
+    host.host_check_staging_roles.restype = C.c_long
+    assert host.host_check_staging_roles() == 0
+
+
 @pytest.mark.parametrize("name", ["curved_c3_div8", "curved_wide_fan"])
 def test_curved_tile_relative_columns_agree_with_the_general_function(host, name):
     """The tiled back projection takes a voxel column's fan angle relative to its tile's centre and the corner angles
