@@ -259,6 +259,9 @@ __global__ __launch_bounds__(256) void sf_volume_to_columns(const float *__restr
         const int ir = ib + ty + 8 * s, k = k0 + tx;
         if (i0 + ir < ihi && k < nz) volz[((size_t)jr * ni + ir) * nzp + FP_PAD + k] = tile[tx][ty + 8 * s];
     }
+    // The spare zero column at the copy's end lies where a copy of another layout (another slab width, chosen by the batch) may
+    // have held voxels: every copy clears it, its pads are zero in every layout.
+    if (blockIdx.x == 0 && jr == 0 && ty == 0 && k0 + tx < nz) volz[item_stride - nzp + FP_PAD + k0 + tx] = 0.0f;
 }
 
 // Zeroes what the column-wise kernels expect to be zero around the voxels that sf_volume_to_columns writes: FP_PAD
