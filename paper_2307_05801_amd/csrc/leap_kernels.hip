@@ -193,7 +193,7 @@ static void launch_sd_columns(const leap_geometry *G, const FwdScratch &S, const
     const int vb = G->fp_vb, tb = G->fp_tb;
     const int views_pad = (int)cdiv(g.nviews, vb) * vb;
     const int tiles_per_xcd_pad = (int)cdiv(cdiv(col_tiles, 8), tb) * tb;
-    const unsigned zero_col = (unsigned)(S.item_floats - (size_t)G->nzp);      // the column after the copy.s, which every copy clears
+    const unsigned zero_col = (unsigned)(S.item_floats - (size_t)G->nzp);      // the copy's last column, which every copy clears
     dim3 grid((unsigned)(8 * tiles_per_xcd_pad * views_pad * bands), (unsigned)items, 1);
     if (G->md_tilted) {
         if constexpr (RG <= 4)        // (the selection offers the per-lane kernel 1, 2 or 4 row groups)

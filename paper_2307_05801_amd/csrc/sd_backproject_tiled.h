@@ -50,6 +50,69 @@ SF_HD SfWindow sd_bp_window(const SfGeom &g, const SfView &v, float xc, float yc
     return w;
 }
 
+// Where a workgroup's tile and z-chunk lie in the scene a view sees.
+struct SdBpScene {
+    float xc, yc, z0, z1;
+    double zrel0;          // Z of the plane z = 0 measured in slots of this chunk
+};
+
+template <int ZC>
+SF_HD SdBpScene sd_bp_scene(const SfGeom &g, int i0, int j0, int k0)
+{
+    SdBpScene s;
+    s.z0 = (float)fma((double)k0, g.Tzd, g.zlo0d);
+    s.z1 = s.z0 + (float)ZC * g.Tz;
+    s.xc = (float)(g.x0d + ((double)i0 + 0.5 * (BP_T - 1)) * g.Td);
+    s.yc = (float)(g.y0d + ((double)j0 + 0.5 * (BP_T - 1)) * g.Td);
+    s.zrel0 = g.zk0d - (double)k0 + 2.0;
+    return s;
+}
+
+// ---- the axial part of the walk, shared by the kernel and by the host-side re-enactment of its arithmetic ---------------
+//
+// A thread's sums are ZC + 4 slots: slot s holds voxel k0 + ZC + 1 - s; slots 0, 1, ZC+2, ZC+3 are dumps.  The lower end of a
+// row's piece advances by pv * h per row; its negative is carried as a 32.32 fixed-point number, whose lower word is the way up
+// to the next z-face and whose upper word counts slots downwards (the slots are laid out that way): neither needs an
+// instruction of its own.  The number lives in a double: with 1.5 * 2^20 added, a double's unit in the last place is 2^-32, so its
+// low word is the fraction and its high word SD_BP_HI plus the slot, and advancing it is one double addition (exact: both
+// terms are multiples of 2^-32) instead of a 64-bit integer add in two halves.  The position itself is rounded down, before its
+// sign changes.  level: the piece does not rise whatever the row (parallel beams).
+constexpr double SD_BP_MAGIC = 1572864.0;        // 1.5 * 2^20
+constexpr unsigned SD_BP_HI = 0x41380000u;       // its high word
+
+template <int ZC>
+SF_HD double sd_bp_position(double vr, double h, double zrel0, bool level)
+{
+    return fma(floor(fma(vr, h, level ? zrel0 + SD_LEVEL_LIFT : zrel0) * 4294967296.0), -2.3283064365386963e-10, (double)(ZC + 3) + SD_BP_MAGIC);
+}
+
+// First row of the window (win_r0 its first row, H rows) at or above the source plane.
+SF_HD int sd_bp_plane_row(const SfGeom &g, int win_r0, int H)
+{
+    const int rz = (int)ceil(-g.v0d / g.pvd) - win_r0;
+    return rz < 0 ? 0 : (rz > H ? H : rz);
+}
+
+SF_HD double sd_bp_advance(double pv, double h) { return rint(pv * h * 4294967296.0) * 2.3283064365386963e-10; }
+
+// 1 / |v| of a row and 1 / (rise of h along a piece), at most 1e18: the product of the two and 2^32 then stays finite (an
+// infinite one times a way up of zero, a level ray on a face, would put the ray below the face), and one unit of the fixed-point
+// number still outweighs any piece of a level ray.
+SF_HD float sd_bp_inverse(float x) { return x > 1e-18f ? 1.0f / x : 1e18f; }
+
+// A row's slot (SD_BP_HI plus the one above; the next slot holds the cell below) and the part of the piece dt spent in the cell
+// below.  per_step: dt over the piece's rise in Z, per unit of the fixed-point number.  A lower end exactly on a face: the way up
+// to it is 0 and the next slot that of the cell below the face, which gets nothing.
+template <int ZC>
+SF_HD void sd_bp_place(double at, float per_step, float dt, unsigned &slot, float &wl)
+{
+    unsigned long long bits;
+    __builtin_memcpy(&bits, &at, 8);
+    slot = (unsigned)(bits >> 32);
+    slot = slot < SD_BP_HI ? SD_BP_HI : (slot > SD_BP_HI + ZC + 2 ? SD_BP_HI + ZC + 2 : slot);
+    wl = fminf((float)(unsigned)bits * per_step, dt);
+}
+
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
 
 // Staging, first half: fetch this thread's share of the window of one view into registers.
@@ -94,38 +157,16 @@ __device__ __forceinline__ void sd_store_view(const SfGeom &g, const SdRayCol *_
             const float t = vscale * vr;
             buf[row * PS + sc] = stage[s] * sf_sqrt(fmaf(t, t, lxy * lxy));
             if (sc == 0) {
-                const float av = fabsf(vr);
-                rinv[row] = av > 1e-30f ? 1.0f / av : 1e30f;
+                rinv[row] = sd_bp_inverse(fabsf(vr));
             }
         }
     }
 }
 
-// Where a workgroup's tile and z-chunk lie in the scene a view sees.
-struct SdBpScene {
-    float xc, yc, z0, z1;
-    double zrel0;          // Z of the plane z = 0 measured in slots of this chunk
-};
-
-template <int ZC>
-SF_HD SdBpScene sd_bp_scene(const SfGeom &g, int i0, int j0, int k0)
-{
-    SdBpScene s;
-    s.z0 = (float)fma((double)k0, g.Tzd, g.zlo0d);
-    s.z1 = s.z0 + (float)ZC * g.Tz;
-    s.xc = (float)(g.x0d + ((double)i0 + 0.5 * (BP_T - 1)) * g.Td);
-    s.yc = (float)(g.y0d + ((double)j0 + 0.5 * (BP_T - 1)) * g.Td);
-    s.zrel0 = g.zk0d - (double)k0 + 2.0;
-    return s;
-}
+typedef __attribute__((address_space(3))) float SdLds;
 
 // NCS: detector columns whose centre can fall inside one voxel's in-plane footprint.  MOD: modular geometry with
 // upright modules, one parameter block geoms[a] per view (g holds the sizes).
-constexpr double SD_BP_MAGIC = 1572864.0;        // 1.5 * 2^20
-constexpr unsigned SD_BP_HI = 0x41380000u;       // its high word
-
-typedef __attribute__((address_space(3))) float SdLds;
-
 // apart: adjacent rows are at least one voxel apart wherever a ray meets the volume.
 template <int NCS, int ZC, int PW, int PH, bool MOD>
 __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
@@ -134,7 +175,7 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
                                                             const SfGeom *__restrict__ geoms)
 {
     constexpr int PS = PW + BP_ROW_PAD;
-    constexpr int NSLOT = ZC + 4;                  // slot s holds voxel k0 + ZC + 1 - s; slots 0, 1, ZC+2, ZC+3 are dumps
+    constexpr int NSLOT = ZC + 4;
     __shared__ float patch[2][PH * PS];
     __shared__ float rinv[2][PH];
     __shared__ float sums[NSLOT * 256];
@@ -204,34 +245,25 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
             const double ha = fma((double)n + (double)t0, R.dh, R.h0), hb = fma((double)n + (double)t1, R.dh, R.h0);
             // Every row of the window is walked (rows that cannot reach the chunk fall into the dump slots), in two
             // wave-uniform runs: rows below the source plane (v < 0), whose lower end in Z is where h is larger, and
-            // rows at or above it.  Within a run the lower end advances by pv * h per row; its negative is carried as a
-            // 32.32 fixed-point number, whose lower word is the way up to the next z-face and whose upper word counts slots
-            // downwards (the slots are laid out that way): neither needs an instruction of its own.
+            // rows at or above it.  Within a run the lower end advances by pv * h per row.
             const double hmin = fmin(ha, hb), hmax = fmax(ha, hb);
             const float dh = (float)(hmax - hmin);
             // dt over the piece's rise in Z is scale / |v_r| / 2^32 times the fixed-point distance to the next z-face
-            const float scale = dt * (dh > 1e-30f ? 1.0f / dh : 1e30f) * 2.3283064365386963e-10f;
+            const float scale = dt * sd_bp_inverse(dh) * 2.3283064365386963e-10f;
             const int H = win.need_h < PH ? win.need_h : PH;
-            int rz = (int)ceil(-gv.v0d / gv.pvd) - win.r0;       // first window row with v >= 0
-            rz = rz < 0 ? 0 : (rz > H ? H : rz);
+            const int rz = sd_bp_plane_row(gv, win.r0, H);
 #pragma unroll
             for (int run = 0; run < 2; ++run) {
                 const int rs = run ? rz : 0, re = run ? H : rz;
                 if (rs >= re) continue;
                 const double h = run ? hmin : hmax;
-                // The fixed-point number lives in a double: with 1.5 * 2^20 added, a double's unit in the last place is
-                // 2^-32, so its low word is the fraction and its high word SD_BP_HI plus the slot, and advancing it is one
-                // double addition (exact: both terms are multiples of 2^-32) instead of a 64-bit integer add in two halves.
-                double q = floor(fma(sd_row_v(gv, win.r0 + rs), -h, (double)(NSLOT - 1) - zrel0) * 4294967296.0) * 2.3283064365386963e-10 + SD_BP_MAGIC;
-                const double dq = rint(gv.pvd * h * 4294967296.0) * 2.3283064365386963e-10;
-                // One row: the slot's LDS address and the two shares' factors.
+                double q = sd_bp_position<ZC>(sd_row_v(gv, win.r0 + rs), h, zrel0, !(dh > 0.0f));
+                const double dq = sd_bp_advance(gv.pvd, h);
+                // One row: the slot's LDS address and the part of the piece in the cell below.
                 auto place = [&](double at, float inv, unsigned &cell, float &wl) {
-                    // (a lower end exactly on a face: the way up to it is 0 and the slot that of the cell below, which gets nothing)
-                    const unsigned long long qbits = __builtin_bit_cast(unsigned long long, at);
-                    unsigned slot = (unsigned)(qbits >> 32);
-                    slot = slot < SD_BP_HI ? SD_BP_HI : (slot > SD_BP_HI + ZC + 2 ? SD_BP_HI + ZC + 2 : slot);
+                    unsigned slot;
+                    sd_bp_place<ZC>(at, scale * inv, dt, slot, wl);
                     asm("v_lshl_add_u32 %0, %1, 10, %2" : "=v"(cell) : "v"(slot), "v"(sums_at));
-                    wl = fminf((float)(unsigned)qbits * (scale * inv), dt);       // way up to the next face * 2^32 over the rise
                 };
                 const float *yp = buf + (rs * PS + wc), *ip = ri + rs;
                 int row = rs;

@@ -56,6 +56,11 @@ SF_HD SdSplit sd_slab_split(const SdRayCol &R, int n)
     return s;
 }
 
+// Rays that run level along a z-face belong to the voxels above it, but their Z carries rounding errors: a few units in the
+// last place of a double, and in kernels that step from row to row in fixed point half a unit of 2^-32 per row (at most 28 for the
+// tallest window).  Such kernels lift level rays by 2^-26 voxels, so that they agree with each other on either side of a face.
+constexpr double SD_LEVEL_LIFT = 1.4901161193847656e-08;
+
 SF_HD double sd_row_v(const SfGeom &g, int r) { return fma((double)r, g.pvd, g.v0d); }
 
 SF_HD float sd_ray_length(const SdRayCol &R, double vr)

@@ -19,6 +19,7 @@
 #include "../../paper_2307_05801_amd/csrc/sf_project_columns.h"
 #include "../../paper_2307_05801_amd/csrc/md_project_columns.h"
 #include "../../paper_2307_05801_amd/csrc/md_backproject_tiled.h"
+#include "../../paper_2307_05801_amd/csrc/sd_backproject_tiled.h"
 
 // ---- stubs of the HIP runtime calls made by leap_geometry.cpp: "device" memory is host memory ---------------
 extern "C" {
@@ -401,6 +402,102 @@ extern "C" long host_sd_project_columns(const leap_geometry *G, const float *vol
             }
         }
     return bad;
+}
+
+// ---- Siddon model, tiled back projection: tile by tile, with the kernel's own functions -------------------------------------
+// report[0]: (view, tile, chunk) windows beyond what the instance stages; report[1]: reads outside the staged window;
+// report[2]: slots outside the per-thread sums; report[3]: rows walked in pairs of which both add to the same voxel.
+// Returns -1 when the handle does not use that kernel, else the sum of the four.
+template <int ZC, int PW, int PH>
+static void host_sd_bp_shape(const leap_geometry *G, const float *sino, float *vol, int64_t *report)
+{
+    const SfGeom &g = G->g;
+    constexpr int NSLOT = ZC + 4;
+    const bool apart = G->sd_min_row_step > 1.0 + 1e-6;
+    const int tiles_x = (g.nx + BP_T - 1) / BP_T, tiles_y = (g.ny + BP_T - 1) / BP_T, chunks = (g.nz + ZC - 1) / ZC;
+    int64_t wide = 0, outside = 0, badslot = 0, shared = 0;
+#pragma omp parallel for collapse(2) reduction(+ : wide, outside, badslot, shared)
+    for (int ch = 0; ch < chunks; ++ch)
+        for (int tile = 0; tile < tiles_x * tiles_y; ++tile) {
+            const int i0 = (tile % tiles_x) * BP_T, j0 = (tile / tiles_x) * BP_T, k0 = ch * ZC;
+            std::vector<float> sums((size_t)NSLOT * 256, 0.f), buf((size_t)PH * PW), rinv(PH);
+            for (int a = 0; a < g.nviews; ++a) {
+                const SfGeom &gv = G->geoms.empty() ? G->g : G->geoms[a];
+                const SdBpScene scene = sd_bp_scene<ZC>(gv, i0, j0, k0);
+                const SfWindow win = sd_bp_window(gv, G->views[a], scene.xc, scene.yc, 0.5f * (float)BP_T * gv.T, scene.z0, scene.z1);
+                wide += win.need_w > PW || win.need_h > PH;
+                for (int row = 0; row < PH; ++row)
+                    for (int sc = 0; sc < PW; ++sc) {
+                        const int c = win.c0 + sc, r = win.r0 + row, cc = std::min(std::max(c, 0), g.ncols - 1);
+                        const bool in = c >= 0 && c < g.ncols && r >= 0 && r < g.nrows;
+                        const SdRayCol &R = G->raycols[(size_t)a * g.ncols + cc];
+                        const float vr = (float)sd_row_v(gv, r), t = R.vscale * vr;
+                        buf[(size_t)row * PW + sc] = in ? sino[((size_t)a * g.nrows + r) * g.ncols + c] * sf_sqrt(fmaf(t, t, R.lxy * R.lxy)) : 0.f;
+                        rinv[row] = sd_bp_inverse(fabsf(vr));
+                    }
+                for (int tid = 0; tid < 256; ++tid) {
+                    const int ic = std::min(i0 + (tid & (BP_T - 1)), g.nx - 1), jc = std::min(j0 + (tid >> 4), g.ny - 1);
+                    const SfColumn f = sf_column(gv, G->views[a], ic, jc);
+                    const int cfirst = (int)ceil(f.xi + (double)f.o0 - 1e-3), clast = (int)floor(f.xi + (double)f.o3 + 1e-3);
+                    for (int m = 0; m < G->bp_nc; ++m) {
+                        const int c = cfirst + m, wc = c - win.c0;
+                        if (c > clast || c < 0 || c >= g.ncols || wc < 0 || wc >= PW) continue;
+                        const SdRayCol R = G->raycols[(size_t)a * g.ncols + c];
+                        const int n = R.xmajor ? ic : jc, q = R.xmajor ? jc : ic;
+                        const SdSplit s = sd_slab_split(R, n);
+                        const float t0 = q == s.qa ? 0.0f : s.f, t1 = q == s.qa ? s.f : 1.0f;
+                        if ((q != s.qa && q != s.qb) || !(t1 - t0 > 0.0f)) continue;
+                        const float dt = t1 - t0;
+                        const double ha = fma((double)n + (double)t0, R.dh, R.h0), hb = fma((double)n + (double)t1, R.dh, R.h0);
+                        const double hmin = fmin(ha, hb), hmax = fmax(ha, hb);
+                        const float scale = dt * sd_bp_inverse((float)(hmax - hmin)) * 2.3283064365386963e-10f;
+                        const int H = std::min(win.need_h, PH);
+                        const int rz = sd_bp_plane_row(gv, win.r0, H);
+                        for (int run = 0; run < 2; ++run) {
+                            const int rs = run ? rz : 0, re = run ? H : rz;
+                            const double h = run ? hmin : hmax, dq = sd_bp_advance(gv.pvd, h);
+                            double at = sd_bp_position<ZC>(sd_row_v(gv, win.r0 + rs), h, scene.zrel0, !((float)(hmax - hmin) > 0.0f));
+                            std::vector<unsigned> slots;
+                            for (int row = rs; row < re; ++row, at -= dq) {
+                                if (row < 0 || row >= PH) { ++outside; continue; }
+                                unsigned slot;
+                                float wl;
+                                sd_bp_place<ZC>(at, scale * rinv[row], dt, slot, wl);
+                                slot -= SD_BP_HI;
+                                slots.push_back(slot);
+                                if (slot + 1 >= (unsigned)NSLOT) { ++badslot; continue; }
+                                const float y = buf[(size_t)row * PW + wc];
+                                sums[(size_t)slot * 256 + tid] = fmaf(dt - wl, y, sums[(size_t)slot * 256 + tid]);
+                                sums[(size_t)(slot + 1) * 256 + tid] = fmaf(wl, y, sums[(size_t)(slot + 1) * 256 + tid]);
+                            }
+                            for (size_t p = 0; apart && p + 2 < slots.size(); ++p)          // any row and the next but one
+                                for (unsigned cell = 2; cell < (unsigned)ZC + 2; ++cell)
+                                    shared += (slots[p] == cell || slots[p] + 1 == cell) && (slots[p + 2] == cell || slots[p + 2] + 1 == cell);
+                        }
+                    }
+                }
+            }
+            for (int tid = 0; tid < 256; ++tid) {
+                const int i = i0 + (tid & (BP_T - 1)), j = j0 + (tid >> 4);
+                if (i >= g.nx || j >= g.ny) continue;
+                for (int kk = 0; kk < ZC && k0 + kk < g.nz; ++kk)
+                    vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sums[(size_t)(ZC + 1 - kk) * 256 + tid];
+            }
+        }
+    report[0] = wide; report[1] = outside; report[2] = badslot; report[3] = shared;
+}
+
+extern "C" long host_sd_backproject_tiled(const leap_geometry *G, const float *sino, float *vol, int64_t *report)
+{
+    if (G->g.model != SF_MODEL_SIDDON || G->d_mdbp || !G->bp_tiled) return -1;
+    switch (G->bp_shape) {
+    case 1: host_sd_bp_shape<BP_SHAPES[1].zc, BP_SHAPES[1].pw, BP_SHAPES[1].ph>(G, sino, vol, report); break;
+    case 2: host_sd_bp_shape<BP_SHAPES[2].zc, BP_SHAPES[2].pw, BP_SHAPES[2].ph>(G, sino, vol, report); break;
+    case 3: host_sd_bp_shape<BP_SHAPES[3].zc, BP_SHAPES[3].pw, BP_SHAPES[3].ph>(G, sino, vol, report); break;
+    case 4: host_sd_bp_shape<BP_SHAPES[4].zc, BP_SHAPES[4].pw, BP_SHAPES[4].ph>(G, sino, vol, report); break;
+    default: return -1;
+    }
+    return report[0] + report[1] + report[2] + report[3];
 }
 
 // ---- Siddon model on tilted modules: the per-lane forward kernel, slab by slab, with the kernel's own functions ---------

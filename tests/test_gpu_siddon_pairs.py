@@ -4,7 +4,7 @@ modules with their own source heights, volumes walked in narrow slabs."""
 import numpy as np
 import pytest
 
-from synthetic import CTConfig, perturbed_poses, uniform_volume
+from synthetic import CTConfig, perturbed_poses, uniform_sinogram, uniform_volume
 from synthetic.configs import CONE, CONE_CURVED, PARALLEL
 
 pytestmark = pytest.mark.gpu
@@ -44,4 +44,29 @@ def test_two_rows_per_lane_match_oracle(oracle_mod, cfg, slab, monkeypatch):
         want = oracle_mod.siddon.project(cfg, x[b])
         assert np.linalg.norm(got[b] - want) <= TOL * np.linalg.norm(want)
         assert np.abs(got[b] - want).max() <= 2e-5 * np.abs(want).max()
+    geo.close()
+
+
+# an odd detector over a volume of even height: the middle row runs along a z-face and belongs to the voxels above it
+FACE = dict(nx=30, ny=28, nz=24, shift_v=0.0, center_z=0.0)
+FLAT_BEAM = dict(FACE, geom=PARALLEL, sod=0.0, sdd=0.0)
+FACES = [scan("parallel_on_face", 67, 60, 0.75, **FLAT_BEAM), scan("parallel_near_face", 67, 60, 0.7, **FLAT_BEAM),
+         scan("parallel_below_face", 131, 60, 0.35, **FLAT_BEAM), scan("parallel_short", 45, 60, 0.9, **FLAT_BEAM),
+         scan("parallel_on_face_apart", 69, 60, 1.25, **dict(FLAT_BEAM, nz=60)), scan("cone_on_face", 67, 60, 0.75, **FACE),
+         scan("cone_near_face", 67, 60, 0.7, **FACE)]
+
+
+@pytest.mark.parametrize("cfg", FACES, ids=lambda c: c.name)
+def test_back_projection_of_rows_on_a_face_matches_oracle(oracle_mod, cfg):
+    import torch
+    from paper_2307_05801_amd import Geometry
+    oracle_mod.siddon.build()
+    geo = Geometry(cfg, model="siddon")
+    print(f"[gpu] {cfg.name}: {geo.describe()}", flush=True)
+    assert "AT=tiled" in geo.describe(), geo.describe()
+    y = uniform_sinogram(cfg, 4, batch=2)
+    got = geo.backproject(torch.from_numpy(y).cuda()).cpu().numpy()
+    want = oracle_mod.siddon.backproject(cfg, y[1])
+    assert np.linalg.norm(got[1] - want) <= TOL * np.linalg.norm(want)
+    assert np.abs(got[1] - want).max() <= 2e-5 * np.abs(want).max()
     geo.close()
