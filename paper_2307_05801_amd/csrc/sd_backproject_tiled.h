@@ -86,10 +86,11 @@ SF_HD double sd_bp_position(double vr, double h, double zrel0, bool level)
     return fma(floor(fma(vr, h, level ? zrel0 + SD_LEVEL_LIFT : zrel0) * 4294967296.0), -2.3283064365386963e-10, (double)(ZC + 3) + SD_BP_MAGIC);
 }
 
-// First row of the window (win_r0 its first row, H rows) at or above the source plane.
+// First row of the window (win_r0 its first row, H rows) at or above the source plane; a row that lies in the plane but for
+// rounding starts the upper run.
 SF_HD int sd_bp_plane_row(const SfGeom &g, int win_r0, int H)
 {
-    const int rz = (int)ceil(-g.v0d / g.pvd) - win_r0;
+    const int rz = (int)ceil(-g.v0d / g.pvd - 1e-9) - win_r0;
     return rz < 0 ? 0 : (rz > H ? H : rz);
 }
 

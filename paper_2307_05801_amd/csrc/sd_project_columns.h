@@ -104,9 +104,8 @@ SF_HD SdPairRow sd_pair_row(const SfGeom &g, const SdRayCol &R, int r)
     const float amz = fabsf((float)mz);
     const bool level = !(amz > 1e-30f);
     A.zadj = g.zk0d + (double)FP_PAD + FP_KAP_MAGIC + fmax(mz, 0.0);
-    // a ray that runs level stays in its upper cell, on a face in the cell above it: the nudge of two units of the fraction
-    // keeps the share of a ray exactly on a face at 1
-    if (level) A.zadj += 4.6566128730773926e-10;
+    // a ray that runs level stays in its upper cell, on a face in the cell above it
+    if (level) A.zadj += SD_LEVEL_LIFT;
     A.inv = (level ? 1e30f : 1.0f / amz) * 2.3283064365386963e-10f;
     A.inc = mz >= 0.0;
     return A;
@@ -120,6 +119,19 @@ SF_HD void sd_pair_place(const SdPairRow &A, double h, unsigned &hi, float &shar
     __builtin_memcpy(&bits, &q, 8);
     hi = (unsigned)(bits >> 32);
     share = sf_clamp((float)(unsigned)bits * A.inv, 0.0f, 1.0f);
+}
+
+// Lower and upper axial cell of the pair's upper row among the four voxels loaded from the lower row's lower cell on; d: voxels
+// between the rows' upper cells (0, 1 or 2; SPREAD: 1 or 2).
+template <bool SPREAD>
+SF_HD void sd_pair_upper_row(const float (&x)[4], unsigned d, float &lo, float &up)
+{
+    lo = d > 1u ? x[2] : x[1];
+    up = d > 1u ? x[3] : x[2];
+    if constexpr (!SPREAD) {
+        lo = d == 0u ? x[0] : lo;
+        up = d == 0u ? x[1] : up;
+    }
 }
 
 // A slab whose piece stays in one in-plane cell: lo, up are the lower and the upper axial cell's voxel.  (The slab's value is
@@ -222,14 +234,6 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
 #pragma unroll
                     for (int t = 0; t < 4; ++t) x[t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(col, off + 4 * t, 0, 0));
                 };
-                auto upper_row = [&](const float (&x)[4], unsigned d, float &lo, float &up) {
-                    lo = d > 1u ? x[2] : x[1];
-                    up = d > 1u ? x[3] : x[2];
-                    if constexpr (!SPREAD) {
-                        lo = d == 0u ? x[0] : lo;
-                        up = d == 0u ? x[1] : up;
-                    }
-                };
                 if ((cross >> e) & 1ull) {
                     const __amdgpu_buffer_rsrc_t col_b = __builtin_amdgcn_make_buffer_rsrc(
                         (void *)(volz + (unsigned)__builtin_amdgcn_readlane((int)base_b, e)), 0, (in_b >> e) & 1ull ? (int)col_bytes : 0, 0x00020000);
@@ -246,8 +250,8 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
                     for (int gq = 0; gq < RG; ++gq) {
                         acc[gq][0] = sd_pair_two(xa[gq][0], xa[gq][1], xb[gq][0], xb[gq][1], A[gq][0].inc, rec.z, rec.w, share[gq][0], acc[gq][0]);
                         float alo, aup, blo, bup;
-                        upper_row(xa[gq], d[gq], alo, aup);
-                        upper_row(xb[gq], d[gq], blo, bup);
+                        sd_pair_upper_row<SPREAD>(xa[gq], d[gq], alo, aup);
+                        sd_pair_upper_row<SPREAD>(xb[gq], d[gq], blo, bup);
                         acc[gq][1] = sd_pair_two(alo, aup, blo, bup, A[gq][1].inc, rec.z, rec.w, share[gq][1], acc[gq][1]);
                     }
                 } else {
@@ -262,7 +266,7 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
 #pragma unroll
                     for (int gq = 0; gq < RG; ++gq) {
                         float lo, up;
-                        upper_row(x[gq], d[gq], lo, up);
+                        sd_pair_upper_row<SPREAD>(x[gq], d[gq], lo, up);
                         acc[gq][0] = sd_pair_one(x[gq][0], x[gq][1], share[gq][0], acc[gq][0]);
                         acc[gq][1] = sd_pair_one(lo, up, share[gq][1], acc[gq][1]);
                     }

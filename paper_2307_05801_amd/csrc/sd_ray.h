@@ -61,7 +61,13 @@ SF_HD SdSplit sd_slab_split(const SdRayCol &R, int n)
 // tallest window).  Such kernels lift level rays by 2^-26 voxels, so that they agree with each other on either side of a face.
 constexpr double SD_LEVEL_LIFT = 1.4901161193847656e-08;
 
-SF_HD double sd_row_v(const SfGeom &g, int r) { return fma((double)r, g.pvd, g.v0d); }
+// A row in the source plane but for rounding (an odd detector's middle row under most pixel heights) lies in it: its rays are
+// level, and on a face of the volume they belong to the voxels above in every kernel, whatever the last bit says.
+SF_HD double sd_row_v(const SfGeom &g, int r)
+{
+    const double v = fma((double)r, g.pvd, g.v0d);
+    return fabs(v) < 1e-9 * g.pvd ? 0.0 : v;
+}
 
 SF_HD float sd_ray_length(const SdRayCol &R, double vr)
 {

@@ -404,6 +404,67 @@ extern "C" long host_sd_project_columns(const leap_geometry *G, const float *vol
     return bad;
 }
 
+// The same for the kernel with two adjacent rows per lane: one load of four voxels per pair and in-plane cell, zero outside the
+// padded column, as the kernel's buffer loads return.  Returns -1 when the handle does not use that kernel, else the number of
+// pairs whose cells do not fit the load.
+template <bool SPREAD>
+static long host_sd_pairs(const leap_geometry *G, const float *vol, float *sino)
+{
+    const int nx = G->g.nx, ny = G->g.ny, nz = G->g.nz, nzp = nz + 2 * FP_PAD;
+    std::vector<float> volz((size_t)nx * ny * nzp, 0.f);
+    for (int k = 0; k < nz; ++k)
+        for (int j = 0; j < ny; ++j)
+            for (int i = 0; i < nx; ++i) volz[((size_t)j * nx + i) * nzp + FP_PAD + k] = vol[((size_t)k * ny + j) * nx + i];
+    long bad = 0;
+#pragma omp parallel for collapse(2) reduction(+ : bad)
+    for (int a = 0; a < G->g.nviews; ++a)
+        for (int c = 0; c < G->g.ncols; ++c) {
+            const SfGeom &g = G->geoms.empty() ? G->g : G->geoms[a];
+            const SdRayCol R = G->raycols[(size_t)a * g.ncols + c];
+            const int n_major = R.xmajor ? nx : ny, n_minor = R.xmajor ? ny : nx;
+            for (int r = 0; r < g.nrows; r += 2) {
+                const SdPairRow A[2] = {sd_pair_row(g, R, r), sd_pair_row(g, R, r + 1)};
+                float acc[2] = {0.f, 0.f};
+                for (int n = 0; n < n_major; ++n) {
+                    const SdSplit s = sd_slab_split(R, n);
+                    const float f = s.f, omf = 1.0f - s.f;
+                    const bool two = s.qa != s.qb, a_ok = s.qa >= 0 && s.qa < n_minor, b_ok = two && s.qb >= 0 && s.qb < n_minor;
+                    if (!a_ok && !b_ok) continue;
+                    unsigned hi[2];
+                    float share[2], x[2][4];
+                    for (int p = 0; p < 2; ++p) sd_pair_place(A[p], fma((double)n, R.dh, R.h0), hi[p], share[p]);
+                    const unsigned d = hi[1] - hi[0];
+                    if (d > 2u || (SPREAD && d == 0u)) ++bad;
+                    const long k0 = (long)(int)(hi[0] - FP_KAP_HI) - 1;
+                    for (int t = 0; t < 4; ++t)
+                        for (int p = 0; p < 2; ++p) {
+                            const int q = p ? s.qb : s.qa;
+                            const size_t col = (size_t)(R.xmajor ? q * nx + n : n * nx + q) * nzp;
+                            x[p][t] = (p ? b_ok : a_ok) && k0 + t >= 0 && k0 + t < nzp ? volz[col + k0 + t] : 0.f;
+                        }
+                    float lo[2], up[2];
+                    for (int p = 0; p < 2; ++p) sd_pair_upper_row<SPREAD>(x[p], d, lo[p], up[p]);
+                    if (two) {
+                        acc[0] = sd_pair_two(x[0][0], x[0][1], x[1][0], x[1][1], A[0].inc, f, omf, share[0], acc[0]);
+                        acc[1] = sd_pair_two(lo[0], up[0], lo[1], up[1], A[1].inc, f, omf, share[1], acc[1]);
+                    } else {
+                        acc[0] = sd_pair_one(x[0][0], x[0][1], share[0], acc[0]);
+                        acc[1] = sd_pair_one(lo[0], up[0], share[1], acc[1]);
+                    }
+                }
+                for (int p = 0; p < 2 && r + p < g.nrows; ++p)
+                    sino[((size_t)a * g.nrows + r + p) * g.ncols + c] = sd_ray_length(R, A[p].vr) * acc[p];
+            }
+        }
+    return bad;
+}
+
+extern "C" long host_sd_project_pairs(const leap_geometry *G, const float *vol, float *sino)
+{
+    if (!G->sd_pairs) return -1;
+    return G->sd_pairs == 2 ? host_sd_pairs<true>(G, vol, sino) : host_sd_pairs<false>(G, vol, sino);
+}
+
 // ---- Siddon model, tiled back projection: tile by tile, with the kernel's own functions -------------------------------------
 // report[0]: (view, tile, chunk) windows beyond what the instance stages; report[1]: reads outside the staged window;
 // report[2]: slots outside the per-thread sums; report[3]: rows walked in pairs of which both add to the same voxel.

@@ -53,20 +53,21 @@ FLAT_BEAM = dict(FACE, geom=PARALLEL, sod=0.0, sdd=0.0)
 FACES = [scan("parallel_on_face", 67, 60, 0.75, **FLAT_BEAM), scan("parallel_near_face", 67, 60, 0.7, **FLAT_BEAM),
          scan("parallel_below_face", 131, 60, 0.35, **FLAT_BEAM), scan("parallel_short", 45, 60, 0.9, **FLAT_BEAM),
          scan("parallel_on_face_apart", 69, 60, 1.25, **dict(FLAT_BEAM, nz=60)), scan("cone_on_face", 67, 60, 0.75, **FACE),
-         scan("cone_near_face", 67, 60, 0.7, **FACE)]
+         scan("cone_near_face", 67, 60, 0.7, **FACE), scan("cone_below_face", 67, 60, 0.85, **FACE)]
 
 
 @pytest.mark.parametrize("cfg", FACES, ids=lambda c: c.name)
-def test_back_projection_of_rows_on_a_face_matches_oracle(oracle_mod, cfg):
+def test_rows_on_a_face_match_oracle(oracle_mod, cfg):
     import torch
     from paper_2307_05801_amd import Geometry
     oracle_mod.siddon.build()
     geo = Geometry(cfg, model="siddon")
     print(f"[gpu] {cfg.name}: {geo.describe()}", flush=True)
-    assert "AT=tiled" in geo.describe(), geo.describe()
-    y = uniform_sinogram(cfg, 4, batch=2)
-    got = geo.backproject(torch.from_numpy(y).cuda()).cpu().numpy()
-    want = oracle_mod.siddon.backproject(cfg, y[1])
-    assert np.linalg.norm(got[1] - want) <= TOL * np.linalg.norm(want)
-    assert np.abs(got[1] - want).max() <= 2e-5 * np.abs(want).max()
+    assert "A=columns" in geo.describe() and "AT=tiled" in geo.describe(), geo.describe()
+    x, y = uniform_volume(cfg, 3, batch=2), uniform_sinogram(cfg, 4, batch=2)
+    ax = geo.project(torch.from_numpy(x).cuda()).cpu().numpy()
+    aty = geo.backproject(torch.from_numpy(y).cuda()).cpu().numpy()
+    for got, want in ((ax[1], oracle_mod.siddon.project(cfg, x[1])), (aty[1], oracle_mod.siddon.backproject(cfg, y[1]))):
+        assert np.linalg.norm(got - want) <= TOL * np.linalg.norm(want)
+        assert np.abs(got - want).max() <= 2e-5 * np.abs(want).max()
     geo.close()

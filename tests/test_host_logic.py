@@ -45,6 +45,8 @@ def host():
     lib.host_curved_column_deviation.argtypes = [C.c_void_p, C.POINTER(C.c_double)]
     lib.host_sd_project_columns.restype = C.c_long
     lib.host_sd_project_columns.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
+    lib.host_sd_project_pairs.restype = C.c_long
+    lib.host_sd_project_pairs.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
     lib.host_sd_backproject_tiled.restype = C.c_long
     lib.host_sd_backproject_tiled.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(C.c_int64)]
     lib.host_md_backproject_tiled.restype = C.c_long
@@ -272,6 +274,7 @@ SIDDON_TILED_CASES = {
     "level_parallel_exact": lambda: level_rows("level_parallel_exact", PARALLEL, pixel_v=0.75),
     "level_parallel_fine": lambda: level_rows("level_parallel_fine", PARALLEL, nrows=131, pixel_v=0.35),
     "level_parallel_short": lambda: level_rows("level_parallel_short", PARALLEL, nrows=45, pixel_v=0.9),
+    "level_cone_fine": lambda: level_rows("level_cone_fine", CONE, pixel_v=0.85),
     "level_parallel_apart": lambda: level_rows("level_parallel_apart", PARALLEL, nrows=69, pixel_v=1.25, nz=60),
     "level_cone": lambda: level_rows("level_cone", CONE, pixel_v=0.75), "level_cone_inexact": lambda: level_rows("level_cone_inexact", CONE),
 }
@@ -292,6 +295,31 @@ def test_tiled_siddon_back_projection_matches_oracle_on_cpu(host, oracle_mod, na
     want = oracle_mod.siddon.backproject(cfg, y)
     assert rel_l2(aty, want) <= 1e-6, desc
     assert np.abs(aty - want).max() <= 1e-5 * np.abs(want).max()
+
+
+# (those with more than 64 rows; the back projection's list holds shorter detectors too)
+SIDDON_PAIR_CASES = {n: m for n, m in SIDDON_TILED_CASES.items() if n.startswith("level") and n != "level_parallel_short"}
+SIDDON_PAIR_CASES.update(
+    cone=lambda: level_rows("cone", CONE, shift_v=0.31), cone_apart=lambda: level_rows("cone_apart", CONE, nrows=70, pixel_v=2.1, shift_v=0.31),
+    cone_either_side=lambda: level_rows("cone_either_side", CONE, nrows=70, pixel_v=1.5), rows_finer=lambda: level_rows("finer", CONE, nrows=140, pixel_v=0.4),
+    curved=lambda: level_rows("curved", CONE_CURVED, shift_v=0.2, pixel_v=1.3),
+    upright=lambda: perturbed_poses(level_rows("up", CONE, pixel_v=1.3, shift_v=0.2), 5, shift_mm=3.0, upright=True))
+
+
+@pytest.mark.parametrize("name", list(SIDDON_PAIR_CASES))
+def test_siddon_pairs_match_oracle_on_cpu(host, oracle_mod, name):
+    cfg = SIDDON_PAIR_CASES[name]()
+    cfg = cfg.replace(shift_u=cfg.shift_u + 0.123)      # no rays inside vertical voxel faces
+    x = uniform_volume(cfg, 3)[0]
+    h = handle(host, cfg, B.LEAP_MODEL_SIDDON)
+    ax = np.zeros(cfg.sino_shape, np.float32)
+    bad = host.host_sd_project_pairs(h, x.ctypes.data, ax.ctypes.data)
+    desc = B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
+    assert bad == 0, (bad, desc)
+    want = oracle_mod.siddon.project(cfg, x)
+    assert rel_l2(ax, want) <= 1e-6, desc
+    assert np.abs(ax - want).max() <= 1e-5 * np.abs(want).max()
 
 
 def test_every_staged_sample_has_one_writer(host):
