@@ -87,8 +87,8 @@ SF_HD float sd_gather_two(const float *__restrict__ xa, const float *__restrict_
 //
 // Placement without conversions, from the UPPER end of a row's piece: Z is formed by one double FMA to which 1.5 * 2^20 has
 // been added, so the sum's low word is 2^32 times the fraction, which is the way down to the face below, and its high word
-// is a constant plus the upper cell.  The share of the slab spent in the upper cell is that way over |dZ|, at most 1; the
-// rest is spent in the cell below.
+// is a constant plus the upper cell.  The share of the slab spent in the upper cell is that way over |dZ|, at most 1; what is
+// carried is the rest, spent in the cell below.
 
 struct SdPairRow {
     double vr, zadj;
@@ -111,14 +111,22 @@ SF_HD SdPairRow sd_pair_row(const SfGeom &g, const SdRayCol &R, int r)
     return A;
 }
 
-// Upper cell (FP_KAP_HI plus its index in the padded column) and the share of the slab spent in it.
-SF_HD void sd_pair_place(const SdPairRow &A, double h, unsigned &hi, float &share)
+// Upper cell (FP_KAP_HI plus its index in the padded column) and the share of the slab spent in the cell below it.
+SF_HD void sd_pair_place(const SdPairRow &A, double h, unsigned &hi, float &low)
 {
     const double q = fma(A.vr, h, A.zadj);
     unsigned long long bits;
     __builtin_memcpy(&bits, &q, 8);
     hi = (unsigned)(bits >> 32);
-    share = sf_clamp((float)(unsigned)bits * A.inv, 0.0f, 1.0f);
+    low = sf_clamp(fmaf(-(float)(unsigned)bits, A.inv, 1.0f), 0.0f, 1.0f);
+}
+
+// Shares f and omf of the in-plane cells before and after the crossing, both multiples of 2^-24 that add up to 1 exactly, so that
+// a cell the ray does not enter comes out with a weight of 0 below.
+SF_HD void sd_pair_crossing(float at, float &f, float &omf)
+{
+    omf = 1.0f - at;
+    f = 1.0f - omf;
 }
 
 // Lower and upper axial cell of the pair's upper row among the four voxels loaded from the lower row's lower cell on; d: voxels
@@ -136,17 +144,17 @@ SF_HD void sd_pair_upper_row(const float (&x)[4], unsigned d, float &lo, float &
 
 // A slab whose piece stays in one in-plane cell: lo, up are the lower and the upper axial cell's voxel.  (The slab's value is
 // formed by itself, so that the running sum is rounded once per slab: added in two parts, the sums of 160 slabs came out 1.4
-// times further off.)
-SF_HD float sd_pair_one(float lo, float up, float share, float acc) { return acc + fmaf(share, up - lo, lo); }
+// times further off.  Every cell has a weight of its own: as lo + share (up - lo), one instruction less, a voxel that the ray does
+// not meet would round the one that it does, and an infinite voxel come out as NaN.)
+SF_HD float sd_pair_one(float lo, float up, float low, float acc) { return acc + fmaf(low, lo, (1.0f - low) * up); }
 
-// A slab whose piece changes from in-plane cell a to b at tau = f (omf = 1 - f).  A rising ray is in the upper cell last: for
-// `share` of the slab, as far as that reaches in b and then in a; a falling ray first, in a and then in b.
-SF_HD float sd_pair_two(float alo, float aup, float blo, float bup, bool inc, float f, float omf, float share, float acc)
+// A slab whose piece changes from in-plane cell a to b at tau = f (omf = 1 - f): rising rays are in the lower axial cell first
+// (while still in a, then in b), falling rays last (in b, then in a).
+SF_HD float sd_pair_two(float alo, float aup, float blo, float bup, bool inc, float f, float omf, float low, float acc)
 {
-    const float first = inc ? bup - blo : aup - alo, second = inc ? aup - alo : bup - blo;
-    const float over = sf_clamp(share - (inc ? omf : f), 0.0f, 1.0f);       // what of the share reaches into the other cell
-    const float t = fmaf(share, first, fmaf(f, alo, omf * blo));
-    return acc + fmaf(over, second - first, t);
+    const float p = fminf(low, inc ? f : omf), q = low - p;
+    const float la = inc ? p : q, lb = inc ? q : p;
+    return acc + fmaf(lb, blo, fmaf(omf - lb, bup, fmaf(la, alo, (f - la) * aup)));
 }
 
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
@@ -211,7 +219,9 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
             const unsigned base_a = a_ok ? sf_slab_column(slab, g.nx, R.xmajor ? n : s.qa, R.xmajor ? s.qa : n) * (unsigned)nzp : 0u;
             const unsigned base_b = b_ok ? sf_slab_column(slab, g.nx, R.xmajor ? n : s.qb, R.xmajor ? s.qb : n) * (unsigned)nzp : 0u;
             const double h = fma((double)n, R.dh, R.h0);
-            recs[wave][lane] = make_float4(__builtin_bit_cast(float, __double2loint(h)), __builtin_bit_cast(float, __double2hiint(h)), s.f, 1.0f - s.f);
+            float f, omf;
+            sd_pair_crossing(s.f, f, omf);
+            recs[wave][lane] = make_float4(__builtin_bit_cast(float, __double2loint(h)), __builtin_bit_cast(float, __double2hiint(h)), f, omf);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -223,10 +233,10 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
                 const double s_h = __hiloint2double(__builtin_bit_cast(int, rec.y), __builtin_bit_cast(int, rec.x));
                 const __amdgpu_buffer_rsrc_t col_a = __builtin_amdgcn_make_buffer_rsrc(
                     (void *)(volz + (unsigned)__builtin_amdgcn_readlane((int)base_a, e)), 0, (in_a >> e) & 1ull ? (int)col_bytes : 0, 0x00020000);
-                auto place = [&](int gq, float (&share)[2], int &off, unsigned &d) {
+                auto place = [&](int gq, float (&low)[2], int &off, unsigned &d) {
                     unsigned hi0, hi1;
-                    sd_pair_place(A[gq][0], s_h, hi0, share[0]);
-                    sd_pair_place(A[gq][1], s_h, hi1, share[1]);
+                    sd_pair_place(A[gq][0], s_h, hi0, low[0]);
+                    sd_pair_place(A[gq][1], s_h, hi1, low[1]);
                     asm("v_lshl_add_u32 %0, %1, 2, %2" : "=v"(off) : "v"(hi0), "s"(off_k));
                     d = hi1 - hi0;                    // 0, 1 or 2 (SPREAD: 1 or 2) voxels between the rows' upper cells
                 };
@@ -237,38 +247,38 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
                 if ((cross >> e) & 1ull) {
                     const __amdgpu_buffer_rsrc_t col_b = __builtin_amdgcn_make_buffer_rsrc(
                         (void *)(volz + (unsigned)__builtin_amdgcn_readlane((int)base_b, e)), 0, (in_b >> e) & 1ull ? (int)col_bytes : 0, 0x00020000);
-                    float share[RG][2], xa[RG][4], xb[RG][4];
+                    float low[RG][2], xa[RG][4], xb[RG][4];
                     unsigned d[RG];
 #pragma unroll
                     for (int gq = 0; gq < RG; ++gq) {
                         int off;
-                        place(gq, share[gq], off, d[gq]);
+                        place(gq, low[gq], off, d[gq]);
                         load(col_a, off, xa[gq]);
                         load(col_b, off, xb[gq]);
                     }
 #pragma unroll
                     for (int gq = 0; gq < RG; ++gq) {
-                        acc[gq][0] = sd_pair_two(xa[gq][0], xa[gq][1], xb[gq][0], xb[gq][1], A[gq][0].inc, rec.z, rec.w, share[gq][0], acc[gq][0]);
+                        acc[gq][0] = sd_pair_two(xa[gq][0], xa[gq][1], xb[gq][0], xb[gq][1], A[gq][0].inc, rec.z, rec.w, low[gq][0], acc[gq][0]);
                         float alo, aup, blo, bup;
                         sd_pair_upper_row<SPREAD>(xa[gq], d[gq], alo, aup);
                         sd_pair_upper_row<SPREAD>(xb[gq], d[gq], blo, bup);
-                        acc[gq][1] = sd_pair_two(alo, aup, blo, bup, A[gq][1].inc, rec.z, rec.w, share[gq][1], acc[gq][1]);
+                        acc[gq][1] = sd_pair_two(alo, aup, blo, bup, A[gq][1].inc, rec.z, rec.w, low[gq][1], acc[gq][1]);
                     }
                 } else {
-                    float share[RG][2], x[RG][4];
+                    float low[RG][2], x[RG][4];
                     unsigned d[RG];
 #pragma unroll
                     for (int gq = 0; gq < RG; ++gq) {
                         int off;
-                        place(gq, share[gq], off, d[gq]);
+                        place(gq, low[gq], off, d[gq]);
                         load(col_a, off, x[gq]);
                     }
 #pragma unroll
                     for (int gq = 0; gq < RG; ++gq) {
                         float lo, up;
                         sd_pair_upper_row<SPREAD>(x[gq], d[gq], lo, up);
-                        acc[gq][0] = sd_pair_one(x[gq][0], x[gq][1], share[gq][0], acc[gq][0]);
-                        acc[gq][1] = sd_pair_one(lo, up, share[gq][1], acc[gq][1]);
+                        acc[gq][0] = sd_pair_one(x[gq][0], x[gq][1], low[gq][0], acc[gq][0]);
+                        acc[gq][1] = sd_pair_one(lo, up, low[gq][1], acc[gq][1]);
                     }
                 }
             }

@@ -427,12 +427,13 @@ static long host_sd_pairs(const leap_geometry *G, const float *vol, float *sino)
                 float acc[2] = {0.f, 0.f};
                 for (int n = 0; n < n_major; ++n) {
                     const SdSplit s = sd_slab_split(R, n);
-                    const float f = s.f, omf = 1.0f - s.f;
+                    float f, omf;
+                    sd_pair_crossing(s.f, f, omf);
                     const bool two = s.qa != s.qb, a_ok = s.qa >= 0 && s.qa < n_minor, b_ok = two && s.qb >= 0 && s.qb < n_minor;
                     if (!a_ok && !b_ok) continue;
                     unsigned hi[2];
-                    float share[2], x[2][4];
-                    for (int p = 0; p < 2; ++p) sd_pair_place(A[p], fma((double)n, R.dh, R.h0), hi[p], share[p]);
+                    float low[2], x[2][4];
+                    for (int p = 0; p < 2; ++p) sd_pair_place(A[p], fma((double)n, R.dh, R.h0), hi[p], low[p]);
                     const unsigned d = hi[1] - hi[0];
                     if (d > 2u || (SPREAD && d == 0u)) ++bad;
                     const long k0 = (long)(int)(hi[0] - FP_KAP_HI) - 1;
@@ -445,11 +446,11 @@ static long host_sd_pairs(const leap_geometry *G, const float *vol, float *sino)
                     float lo[2], up[2];
                     for (int p = 0; p < 2; ++p) sd_pair_upper_row<SPREAD>(x[p], d, lo[p], up[p]);
                     if (two) {
-                        acc[0] = sd_pair_two(x[0][0], x[0][1], x[1][0], x[1][1], A[0].inc, f, omf, share[0], acc[0]);
-                        acc[1] = sd_pair_two(lo[0], up[0], lo[1], up[1], A[1].inc, f, omf, share[1], acc[1]);
+                        acc[0] = sd_pair_two(x[0][0], x[0][1], x[1][0], x[1][1], A[0].inc, f, omf, low[0], acc[0]);
+                        acc[1] = sd_pair_two(lo[0], up[0], lo[1], up[1], A[1].inc, f, omf, low[1], acc[1]);
                     } else {
-                        acc[0] = sd_pair_one(x[0][0], x[0][1], share[0], acc[0]);
-                        acc[1] = sd_pair_one(lo[0], up[0], share[1], acc[1]);
+                        acc[0] = sd_pair_one(x[0][0], x[0][1], low[0], acc[0]);
+                        acc[1] = sd_pair_one(lo[0], up[0], low[1], acc[1]);
                     }
                 }
                 for (int p = 0; p < 2 && r + p < g.nrows; ++p)
@@ -457,6 +458,14 @@ static long host_sd_pairs(const leap_geometry *G, const float *vol, float *sino)
             }
         }
     return bad;
+}
+
+// One slab's value for given cells, in-plane crossing f and share `low` of the slab in the lower axial cells.
+extern "C" float host_sd_pair_slab(float alo, float aup, float blo, float bup, int two, int inc, float at, float low)
+{
+    float f, omf;
+    sd_pair_crossing(at, f, omf);
+    return two ? sd_pair_two(alo, aup, blo, bup, inc != 0, f, omf, low, 0.0f) : sd_pair_one(alo, aup, low, 0.0f);
 }
 
 extern "C" long host_sd_project_pairs(const leap_geometry *G, const float *vol, float *sino)

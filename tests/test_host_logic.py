@@ -322,6 +322,43 @@ def test_siddon_pairs_match_oracle_on_cpu(host, oracle_mod, name):
     assert np.abs(ax - want).max() <= 1e-5 * np.abs(want).max()
 
 
+def test_siddon_pairs_add_what_the_weights_say(host):
+    """One slab's value from its in-plane cells a, b and the lower and upper axial cell of each: a weight of zero adds nothing
+    however large its voxel (the same bits), an infinite voxel of positive weight gives infinity."""
+    host.host_sd_pair_slab.restype = C.c_float
+    host.host_sd_pair_slab.argtypes = [C.c_float] * 4 + [C.c_int, C.c_int, C.c_float, C.c_float]
+
+    def weights(two, inc, f, low):                  # alo, aup, blo, bup
+        if not two:
+            return np.array([low, 1.0 - low, 0.0, 0.0])
+        la = min(low, f) if inc else max(low - (1.0 - f), 0.0)
+        return np.array([la, f - la, low - la, 1.0 - f - (low - la)])
+
+    rng = np.random.default_rng(5)
+    for trial in range(6000):
+        two, inc = trial % 3 != 0, trial % 2 == 0
+        f = float(np.float32(rng.choice([rng.uniform(0, 1), 1e-3, 0.999, 0.5]))) if two else 1.0
+        low = float(np.float32(rng.choice([rng.uniform(0, 1), 0.0, 1.0])))
+        w, x = weights(two, inc, f, low), rng.uniform(0.5, 2.0, 4).astype(np.float32)
+
+        def slab(v):
+            return host.host_sd_pair_slab(*(float(t) for t in v), two, inc, f, low)
+
+        # weights good to 2^-24 each, four products and sums
+        assert abs(slab(x) - w @ x) <= 8 * 2.0 ** -24 * np.abs(x).sum(), (two, inc, f, low, x)
+        for c in range(4 if two else 2):
+            y = x.copy()
+            if low in (0.0, 1.0) and w[c] == 0.0:
+                for big in (1e8, -3e38):
+                    y[c] = big
+                    assert slab(y) == slab(x), (two, inc, f, low, c, big)
+            elif w[c] > 1e-4:
+                y[c] = np.inf
+                assert slab(y) == np.inf, (two, inc, f, low, c)
+    for low in (0.25, 0.5):
+        assert host.host_sd_pair_slab(np.inf, np.inf, 0.0, 0.0, 0, 1, 1.0, low) == np.inf
+
+
 def test_every_staged_sample_has_one_writer(host):
     """Two threads that write one LDS cell in different steps race, even where they mean to write the same value."""
     host.host_check_staging_roles.restype = C.c_long
