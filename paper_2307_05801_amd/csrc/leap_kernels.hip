@@ -282,13 +282,17 @@ static void launch_sd_tiled(const leap_geometry *G, const float *d_sino, float *
     const SfGeom &g = G->g;
     const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
     dim3 grid(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)items);
-    const int apart = G->sd_min_row_step > 1.0 + 1e-6;
-    if (g.type == SF_MODULAR)
-        hipLaunchKernelGGL((sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, true>), grid, dim3(256, 1, 1), 0, stream, g, G->d_views,
-                           G->d_raycols, d_sino, d_vol, (int)tiles_x, apart, (const SfGeom *)G->d_geoms);
-    else
-        hipLaunchKernelGGL((sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, false>), grid, dim3(256, 1, 1), 0, stream, g, G->d_views,
-                           G->d_raycols, d_sino, d_vol, (int)tiles_x, apart, (const SfGeom *)nullptr);
+    auto go = [&](auto kernel, const SfGeom *geoms) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256, 1, 1), 0, stream, g, G->d_views, G->d_raycols, d_sino, d_vol, (int)tiles_x, geoms);
+    };
+    const bool apart = G->sd_min_row_step > 1.0 + 1e-6;
+    if (g.type == SF_MODULAR) {
+        if (apart) go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, true, true>, G->d_geoms);
+        else go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, true, false>, G->d_geoms);
+    } else {
+        if (apart) go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, false, true>, nullptr);
+        else go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, false, false>, nullptr);
+    }
 }
 
 template <int NCS>

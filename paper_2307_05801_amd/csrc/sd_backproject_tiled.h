@@ -110,7 +110,12 @@ SF_HD void sd_bp_place(double at, float per_step, float dt, unsigned &slot, floa
     unsigned long long bits;
     __builtin_memcpy(&bits, &at, 8);
     slot = (unsigned)(bits >> 32);
+#if defined(__HIP_DEVICE_COMPILE__)
+    // (the compiler may compare the whole 64-bit number instead, four instructions for one: 74.6 against 68.8 ms at 512^3)
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(slot) : "v"(slot), "s"(SD_BP_HI), "v"(SD_BP_HI + ZC + 2));
+#else
     slot = slot < SD_BP_HI ? SD_BP_HI : (slot > SD_BP_HI + ZC + 2 ? SD_BP_HI + ZC + 2 : slot);
+#endif
     wl = fminf((float)(unsigned)bits * per_step, dt);
 }
 
@@ -168,11 +173,11 @@ typedef __attribute__((address_space(3))) float SdLds;
 
 // NCS: detector columns whose centre can fall inside one voxel's in-plane footprint.  MOD: modular geometry with
 // upright modules, one parameter block geoms[a] per view (g holds the sizes).
-// apart: adjacent rows are at least one voxel apart wherever a ray meets the volume.
-template <int NCS, int ZC, int PW, int PH, bool MOD>
+// APART: adjacent rows are at least one voxel apart wherever a ray meets the volume.
+template <int NCS, int ZC, int PW, int PH, bool MOD, bool APART>
 __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
                                                             const SdRayCol *__restrict__ rays, const float *__restrict__ sino,
-                                                            float *__restrict__ vol, int tiles_x, int apart,
+                                                            float *__restrict__ vol, int tiles_x,
                                                             const SfGeom *__restrict__ geoms)
 {
     constexpr int PS = PW + BP_ROW_PAD;
@@ -268,20 +273,24 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
                 };
                 const float *yp = buf + (rs * PS + wc), *ip = ri + rs;
                 int row = rs;
-                // Rows at least a voxel apart: a row and the next but one share no slot, so two rows' sums can be fetched
-                // before the first of them is written back (the walk waits on that round trip).  A row clamped into the dump
-                // slots may meet another's dump slot, whose contents nobody reads.  512^3 x 720 views: 77.3 -> 68.9 ms.
-                if (apart) {
-                    for (; row + 4 <= re; row += 4) {
-                        float y[4], inv[4], wl[4];
-                        unsigned cell[4];
+                // plain read-add-write: a slot has no other writer, and a wave's LDS accesses retire in order (the LDS float atomic
+                // measured 7x slower than this on the 512^3 case)
+                // Four rows' samples, slots and shares at a time: rows closer than a voxel, whose sums have to wait for each other,
+                // 89.2 -> 81.8 ms (512^3 x 720 views, rows 0.87 voxels apart and more).
+                for (; row + 4 <= re; row += 4) {
+                    float y[4], inv[4], wl[4];
+                    unsigned cell[4];
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) { y[t] = yp[t * PS]; inv[t] = ip[t]; }
+                    for (int t = 0; t < 4; ++t) { y[t] = yp[t * PS]; inv[t] = ip[t]; }
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            place(q, inv[t], cell[t], wl[t]);
-                            q -= dq;
-                        }
+                    for (int t = 0; t < 4; ++t) {
+                        place(q, inv[t], cell[t], wl[t]);
+                        q -= dq;
+                    }
+                    if constexpr (APART) {
+                        // A row and the next but one share no slot, so two rows' sums can be fetched before the first of them is
+                        // written back (the walk waits on that round trip).  A row clamped into the dump slots may meet
+                        // another's dump slot, whose contents nobody reads.  512^3 x 720 views: 77.3 -> 68.9 ms.
 #pragma unroll
                         for (int t = 0; t < 2; ++t) {
                             SdLds *const c0 = (SdLds *)(uintptr_t)cell[t], *const c1 = (SdLds *)(uintptr_t)cell[t + 2];
@@ -291,17 +300,23 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
                             c1[0] = fmaf(dt - wl[t + 2], y[t + 2], u1);
                             c1[256] = fmaf(wl[t + 2], y[t + 2], l1);
                         }
-                        yp += 4 * PS;
-                        ip += 4;
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            SdLds *const c = (SdLds *)(uintptr_t)cell[t];
+                            const float u = c[0], l = c[256];
+                            c[0] = fmaf(dt - wl[t], y[t], u);
+                            c[256] = fmaf(wl[t], y[t], l);
+                        }
                     }
+                    yp += 4 * PS;
+                    ip += 4;
                 }
                 for (; row < re; ++row) {
                     unsigned cell;
                     float wl;
                     place(q, *ip, cell, wl);
                     const float y = *yp;
-                    // plain read-add-write: the slot has no other writer, and a wave's LDS accesses retire in order
-                    // (the LDS float atomic measured 7x slower than this on the 512^3 case)
                     SdLds *const c = (SdLds *)(uintptr_t)cell;
                     const float u = c[0], l = c[256];
                     c[0] = fmaf(dt - wl, y, u);
