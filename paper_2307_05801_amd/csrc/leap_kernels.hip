@@ -519,7 +519,9 @@ static int run_forward_columns(const leap_geometry *G, const FwdScratch &S, cons
 
 // Waves of a workgroup that share one output tile's slabs or views: as many as it takes to put about eight waves on each of
 // the chip's 1024 SIMDs, while each keeps at least four of its `steps` (slabs, views).  A 64^2 slice has 64 tiles and 180
-// beams' waves: one wave each took 112 us (A) and 131 us (A^T), 16 of them 11 us each with their launches.
+// beams' waves: one wave each took 112 us (A) and 131 us (A^T), 16 of them 11 us each with their launches.  tiles: those of one
+// item.  The split orders the sums, so it depends on the scan alone: an item comes out the same bits in any batch, with and
+// without the copy.
 static int flat_waves(double tiles, int steps)
 {
     int w = 1;
@@ -533,7 +535,7 @@ static void launch_project_flat(const leap_geometry *G, const float *src, float 
     const SfGeom &g = G->g;
     const int tiles = (int)cdiv(g.ncols, FLAT_RAYS);
     const unsigned groups = cdiv((unsigned)items, NB);
-    int waves = flat_waves((double)tiles * g.nviews * groups, g.nx < g.ny ? g.nx : g.ny);
+    int waves = flat_waves((double)tiles * g.nviews, g.nx < g.ny ? g.nx : g.ny);
     while ((size_t)waves * G->flat_span * sizeof(SfFlatRec) > 65536) waves /= 2;        // (spans of up to 256: at least 8 fit)
     const size_t lds = (size_t)waves * G->flat_span * sizeof(SfFlatRec);
     hipLaunchKernelGGL(sf_project_flat<NB>, dim3((unsigned)tiles * (unsigned)g.nviews, groups), dim3(64 * waves), lds, stream, g, G->d_views,
@@ -606,7 +608,7 @@ static void launch_backproject_flat(const leap_geometry *G, const float *d_sino,
 {
     const SfGeom &g = G->g;
     const unsigned tiles_x = cdiv(g.nx, FLAT_T), tiles_y = cdiv(g.ny, FLAT_T), groups = cdiv((unsigned)items, NB);
-    const int waves = flat_waves((double)tiles_x * tiles_y * groups, g.nviews);
+    const int waves = flat_waves((double)tiles_x * tiles_y, g.nviews);
     hipLaunchKernelGGL(sf_backproject_flat<NB>, dim3(tiles_x * tiles_y, groups), dim3(64 * waves), (size_t)waves * 64 * NB * sizeof(float),
                        stream, g, G->d_views, d_sino, d_vol, (int)tiles_x, items, G->flat_fv);
 }

@@ -34,7 +34,7 @@ def rel(a, b):
 @pytest.mark.parametrize("batch", [1, 3, 21])
 def test_flat_kernels_match_oracle(oracle_mod, cfg, batch):
     import torch
-    from paper_2307_05801_amd import Geometry
+    from paper_2307_05801_amd import Geometry, binding as B
     geo = Geometry(cfg)
     assert "A=general(flat" in geo.describe() and "AT=general(flat" in geo.describe(), geo.describe()
     print(f"[gpu] {cfg.name} batch={batch}: {geo.describe()}", flush=True)
@@ -44,9 +44,16 @@ def test_flat_kernels_match_oracle(oracle_mod, cfg, batch):
     for b in {0, batch // 2, batch - 1}:
         assert rel(ax[b], oracle_mod.project(cfg, x[b])) <= TOL
         assert rel(aty[b], oracle_mod.backproject(cfg, y[b])) <= TOL
-    # an item's sums do not depend on how many others it shares a launch with, nor on the copy
-    one = geo.project(torch.from_numpy(x[-1:]).cuda()).cpu().numpy()
-    assert rel(one[0], ax[-1].astype(np.float64)) <= 1e-6
+    # an item's sums do not depend on how many others it shares a launch with
+    for b in {0, batch // 2, batch - 1}:
+        one = geo.project(torch.from_numpy(x[b:b + 1]).cuda()).cpu().numpy(), geo.backproject(torch.from_numpy(y[b:b + 1]).cuda()).cpu().numpy()
+        assert np.array_equal(one[0][0], ax[b]) and np.array_equal(one[1][0], aty[b])
+    # nor on the copy: the fixed-scratch entry point reads the slices as they lie
+    fixed = torch.full((batch,) + geo.sino_shape, float("nan"), device="cuda")
+    xt = torch.from_numpy(x).cuda()
+    B.leap_project_static_scratch(geo.handle, xt.data_ptr(), fixed.data_ptr(), batch, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert np.array_equal(fixed.cpu().numpy(), ax)
     geo.close()
 
 
@@ -93,6 +100,5 @@ def test_captured_calls_and_two_streams():
             other = geo.project(x)
         ref = geo.project(x)
         torch.cuda.synchronize()
-        assert torch.equal(other, ref)
-        assert float((got - ref).norm()) <= 1e-6 * float(ref.norm())
+        assert torch.equal(other, ref) and torch.equal(got, ref)
     geo.close()
