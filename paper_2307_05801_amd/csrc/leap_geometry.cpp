@@ -6,7 +6,9 @@
 #include <cstdlib>
 #include <algorithm>
 #include <cstring>
+#include <exception>
 #include <new>
+#include <thread>
 
 #include "leap_internal.h"
 #define SF_NO_KERNELS   // this file needs the kernels' host-side limit functions only
@@ -15,7 +17,6 @@
 #include "md_backproject_tiled.h"
 #include "sf_flat.h"
 #include "md_footprint_tiled.h"
-#include <thread>
 #include "sd_backproject_tiled.h"
 
 static thread_local std::string g_last_error;
@@ -186,6 +187,33 @@ static bool footprint_bounds(leap_geometry *G)
     return true;
 }
 
+// Runs share(0) .. share(workers - 1) on that many threads, the caller's among them; the caller takes over the shares of threads
+// that cannot be started.  What a share throws reaches the caller once all threads have ended.
+template <class Share>
+static void run_shares(int workers, Share share)
+{
+    std::vector<std::exception_ptr> thrown(workers);
+    std::vector<std::thread> pool;
+    pool.reserve(workers);
+    auto run = [&](int t) {
+        try {
+            share(t);
+        } catch (...) {
+            thrown[t] = std::current_exception();
+        }
+    };
+    int t = 1;
+    try {
+        for (; t < workers; ++t) pool.emplace_back(run, t);
+    } catch (...) {          // no further thread to be had
+    }
+    for (; t < workers; ++t) run(t);
+    run(0);
+    for (auto &th : pool) th.join();
+    for (auto &e : thrown)
+        if (e) std::rethrow_exception(e);
+}
+
 // Largest staged window any (view, tile, first or last z-chunk) of a tiled back projection asks for, evaluated with the
 // kernel's own window function on the view's own parameter block.
 template <class WindowFn>
@@ -216,10 +244,7 @@ static void staged_window_need(const leap_geometry *G, int zc, WindowFn window, 
         w[t] = wt;
         h[t] = ht;
     };
-    std::vector<std::thread> pool;
-    for (int t = 1; t < workers; ++t) pool.emplace_back(scan, t);
-    scan(0);
-    for (auto &th : pool) th.join();
+    run_shares(workers, scan);
     need_w = *std::max_element(w.begin(), w.end());
     need_h = *std::max_element(h.begin(), h.end());
 }
@@ -545,10 +570,7 @@ static void tilted_window_need(const leap_geometry *G, const std::vector<MdBpVie
         w[t] = sf_f2i(floorf(ew + 1.04f));
         h[t] = sf_f2i(floorf(eh + 1.04f));
     };
-    std::vector<std::thread> pool;
-    for (int t = 1; t < workers; ++t) pool.emplace_back(scan, t);
-    scan(0);
-    for (auto &th : pool) th.join();
+    run_shares(workers, scan);
     need_w = *std::max_element(w.begin(), w.end());
     need_h = *std::max_element(h.begin(), h.end());
 }
@@ -654,10 +676,7 @@ static void select_tilted_footprint_kernels(leap_geometry *G)
         }
         need[t] = worst;
     };
-    std::vector<std::thread> pool;
-    for (int t = 1; t < workers; ++t) pool.emplace_back(scan, t);
-    scan(0);
-    for (auto &th : pool) th.join();
+    run_shares(workers, scan);
     G->mf_tiled = *std::max_element(need.begin(), need.end()) <= MF_PATCH;
 }
 
@@ -854,15 +873,16 @@ static int finish_handle(leap_geometry *G, leap_geometry **out)
         e = upload((void **)&G->d_mfviews, G->mfviews.data(), sizeof(MfView) * G->mfviews.size());
     if (e == hipSuccess && d->type == LEAP_CONE_CURVED && d->model == LEAP_MODEL_SF && G->bp_tiled) upload_curved_tables(G);
     if (e != hipSuccess) {
+        const int rc = leap_hip_fail(e, "uploading the geometry tables");       // (may throw: the handle is freed after it)
         free_handle(G);
-        return leap_hip_fail(e, "uploading the geometry tables");
+        return rc;
     }
     *out = G;
     return LEAP_OK;
 }
 
 // Modular geometry: per-view poses instead of the angle list; only the fields the modular kernels read are filled.
-static int create_modular(const leap_geometry_desc *d, leap_geometry **out)
+static int create_modular(const leap_geometry_desc *d, leap_geometry **out, leap_geometry *&G)
 {
     if (!d->poses) return invalid("poses is null");
     if (d->nviews > 65535 || (double)d->nx * d->ny * d->nz >= 4294967296.0 ||
@@ -912,7 +932,7 @@ static int create_modular(const leap_geometry_desc *d, leap_geometry **out)
         leap_set_error("module does not face its source across the volume");
         return LEAP_BAD_GEOMETRY;
     }
-    leap_geometry *G = new (std::nothrow) leap_geometry;
+    G = new (std::nothrow) leap_geometry;
     if (!G) return invalid("out of host memory");
     G->desc = *d;
     G->desc.angles_rad = nullptr;
@@ -1024,10 +1044,9 @@ static int create_modular(const leap_geometry_desc *d, leap_geometry **out)
     return finish_handle(G, out);
 }
 
-extern "C" int leap_geometry_create(const leap_geometry_desc *d, leap_geometry **out)
+// G: the handle under construction (the caller frees it if anything throws).
+static int create_handle(const leap_geometry_desc *d, leap_geometry **out, leap_geometry *&G)
 {
-    if (out) *out = nullptr;
-    if (!d || !out) return invalid("null descriptor or output pointer");
     if (d->type != LEAP_PARALLEL && d->type != LEAP_FAN && d->type != LEAP_CONE && d->type != LEAP_CONE_CURVED &&
         d->type != LEAP_MODULAR)
         return invalid("unknown geometry type");
@@ -1039,7 +1058,7 @@ extern "C" int leap_geometry_create(const leap_geometry_desc *d, leap_geometry *
     if (!std::isfinite(d->shift_u) || !std::isfinite(d->shift_v)) return invalid("detector shifts must be finite");
     if (!std::isfinite(d->center_x) || !std::isfinite(d->center_y) || !std::isfinite(d->center_z))
         return invalid("volume centre must be finite");
-    if (d->type == LEAP_MODULAR) return create_modular(d, out);
+    if (d->type == LEAP_MODULAR) return create_modular(d, out, G);
     if (!d->angles_rad) return invalid("angles_rad is null");
     for (int a = 0; a < d->nviews; ++a)
         if (!std::isfinite(d->angles_rad[a])) return invalid("view angles must be finite");
@@ -1077,7 +1096,7 @@ extern "C" int leap_geometry_create(const leap_geometry_desc *d, leap_geometry *
         }
     }
 
-    leap_geometry *G = new (std::nothrow) leap_geometry;
+    G = new (std::nothrow) leap_geometry;
     if (!G) return invalid("out of host memory");
     G->desc = *d;
     G->angles.assign(d->angles_rad, d->angles_rad + d->nviews);
@@ -1128,6 +1147,19 @@ extern "C" int leap_geometry_create(const leap_geometry_desc *d, leap_geometry *
     if (d->model == LEAP_MODEL_SIDDON) build_ray_table(G);
     select_fast_kernels(G);
     return finish_handle(G, out);
+}
+
+extern "C" int leap_geometry_create(const leap_geometry_desc *d, leap_geometry **out)
+{
+    if (out) *out = nullptr;
+    if (!d || !out) return invalid("null descriptor or output pointer");
+    leap_geometry *G = nullptr;
+    try {
+        return create_handle(d, out, G);
+    } catch (...) {          // std::bad_alloc from the tables
+        free_handle(G);
+        return invalid("out of host memory");
+    }
 }
 
 extern "C" void leap_geometry_destroy(leap_geometry *G) { free_handle(G); }

@@ -6,10 +6,12 @@
 // thread of every workgroup stay inside the staged window?) and the arithmetic of the column-wise forward kernel
 // (candidate slots, padded z-columns, axial overlap cascade), so that mistakes in them show up without a GPU.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "../../paper_2307_05801_amd/csrc/leap_internal.h"
@@ -45,6 +47,27 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipSt
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostFree(void *p) { std::free(p); return hipSuccess; }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *, const void *) { return hipErrorInvalidValue; }
+}
+
+// The n-th allocation of this library from now on fails (n < 0: none does); returns how many the last setting has counted.
+static std::atomic<long> g_fail_at{-1}, g_allocations{0};
+static void *harness_new(size_t n)
+{
+    const long k = g_allocations++;
+    void *p = g_fail_at >= 0 && k == g_fail_at ? nullptr : std::malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void *operator new(size_t n) { return harness_new(n); }
+void *operator new[](size_t n) { return harness_new(n); }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete[](void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+void operator delete[](void *p, size_t) noexcept { std::free(p); }
+extern "C" long host_fail_allocation(long n)
+{
+    g_fail_at = n;
+    return g_allocations.exchange(0);
 }
 
 int leap_static_scratch_init(int) { return LEAP_OK; }   // the fixed device array exists on a GPU only

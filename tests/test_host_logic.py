@@ -601,6 +601,51 @@ def test_modular_argument_checks(host):
     assert host.leap_geometry_create(C.byref(d), C.byref(hnd)) == B.LEAP_BAD_GEOMETRY
 
 
+OUT_OF_MEMORY = """
+import ctypes as C, sys
+sys.path[:0] = [{root!r}, {here!r}]
+import test_host_logic as T
+from paper_2307_05801_amd import binding as B
+lib = C.CDLL(T.LIB)
+B.declare(lib, solvers=False)
+lib.host_fail_allocation.restype, lib.host_fail_allocation.argtypes = C.c_long, [C.c_long]
+failures = 0
+for cfg, model in T.memory_scans():
+    d, keep = B.desc_from_config(cfg, model)
+    h = C.c_void_p()
+    lib.host_fail_allocation(-1)
+    assert lib.leap_geometry_create(C.byref(d), C.byref(h)) == 0
+    lib.leap_geometry_destroy(h)
+    total = lib.host_fail_allocation(-1)
+    for n in list(range(min(total, 60))) + list(range(60, total, max(1, total // 60))):
+        lib.host_fail_allocation(n)
+        status = lib.leap_geometry_create(C.byref(d), C.byref(h))
+        if status != 0:
+            assert not h.value and lib.leap_last_error(), (cfg.name, n)
+            failures += 1
+        else:
+            lib.leap_geometry_destroy(h)
+    lib.host_fail_allocation(-1)
+    print(cfg.name, total, failures, flush=True)
+assert failures > 30
+print("done")
+"""
+
+
+def memory_scans():
+    cone = level_rows("cone", CONE, nviews=72)
+    return [(cone, 0), (cone, 1), (cone.replace(geom=CONE_CURVED), 0), (level_rows("par", PARALLEL, nviews=72), 0),
+            (perturbed_poses(cone, 5, shift_mm=3.0, upright=True), 0), (perturbed_poses(cone, 5, shift_mm=3.0, tilt_rad=0.1), 0),
+            (perturbed_poses(cone, 5, shift_mm=3.0, tilt_rad=0.1), 1)]
+
+
+def test_creation_that_runs_out_of_host_memory_reports_it(host):
+    """Every allocation of leap_geometry_create fails once, those of its worker threads among them: a status, no abort."""
+    import sys
+    res = subprocess.run([sys.executable, "-c", OUT_OF_MEMORY.format(root=ROOT, here=HERE)], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and "done" in res.stdout, (res.returncode, res.stdout[-500:], res.stderr[-1500:])
+
+
 def test_host_memory_pipeline_rotates_buffers_and_chunks_correctly(host, monkeypatch):
     """leap_project_host / leap_backproject_host against the device-pointer calls, with every asynchronous HIP call
     of the pipeline carried out at once (the harness' stubs): 5 items through the two-deep buffer rotation, staging
