@@ -359,6 +359,19 @@ def test_siddon_pairs_add_what_the_weights_say(host):
         assert host.host_sd_pair_slab(np.inf, np.inf, 0.0, 0.0, 0, 1, 1.0, low) == np.inf
 
 
+def test_flat_scans_beyond_one_launch_keep_the_general_kernels(host):
+    """65535 views of 65537 columns are 1025 wavefronts per view, more than 2^32 threads."""
+    def describe(ncols):
+        cfg = CTConfig("long", PARALLEL, nviews=65535, arc_deg=180.0, nrows=1, ncols=ncols, pixel_v=1.0, pixel_u=1.0, nx=8, ny=8, nz=1,
+                       voxel_xy=1.0, voxel_z=1.0)
+        h = handle(host, cfg)
+        desc = B.leap_geometry_describe(h, host)
+        B.leap_geometry_destroy(h, host)
+        return desc
+    assert "flat" in describe(64)
+    assert "flat" not in describe(65537)
+
+
 def test_every_staged_sample_has_one_writer(host):
     """Two threads that write one LDS cell in different steps race, even where they mean to write the same value."""
     host.host_check_staging_roles.restype = C.c_long
