@@ -236,8 +236,9 @@ static void staged_window_need(const leap_geometry *G, int zc, WindowFn window, 
                     for (int ch = 0; ch < chunks; ch += (chunks > 1 ? chunks - 1 : 1)) {   // extremes: first and last chunk
                         const float z0 = (float)(ga.zlo0d + (double)(ch * zc) * ga.Tzd), z1 = z0 + (float)zc * ga.Tz;
                         const SfWindow win = window(ga, G->views[a], xc, yc, z0, z1);
-                        wt = win.need_w > wt ? win.need_w : wt;
-                        ht = win.need_h > ht ? win.need_h : ht;
+                        const bool near = std::abs((float)win.c0) < BP_MAX_COORDINATE - 1024.0f && std::abs((float)win.r0) < BP_MAX_COORDINATE - 1024.0f;
+                        wt = std::max(wt, near ? win.need_w : 1 << 30);
+                        ht = std::max(ht, near ? win.need_h : 1 << 30);
                     }
                 }
         }
@@ -566,7 +567,7 @@ static void tilted_window_need(const leap_geometry *G, const std::vector<MdBpVie
                         }
                         ew = a1 - a0 > ew ? a1 - a0 : ew;
                         eh = b1 - b0 > eh ? b1 - b0 : eh;
-                        if (!(a1 - a0 < 1.0e6f && b1 - b0 < 1.0e6f)) ew = eh = 1.0e6f;      // NaN or absurd: no instance fits
+                        if (!(std::fmax(-a0, a1) < BP_MAX_COORDINATE && std::fmax(-b0, b1) < BP_MAX_COORDINATE)) ew = eh = 1.0e6f;   // NaN or too far out: no instance fits
                     }
         }
         w[t] = sf_f2i(floorf(ew + 1.04f));
@@ -673,7 +674,8 @@ static void select_tilted_footprint_kernels(leap_geometry *G)
                         }
                         const MfWindow w = mf_window(a0, a1, b0, b1);
                         // one spare row and column: host and device may round apart
-                        worst = std::max(worst, a1 - a0 < 4096.0f && b1 - b0 < 4096.0f ? (w.w + 1) * (w.h + 1) : 1 << 30);
+                        const bool near = std::fmax(-a0, a1) < BP_MAX_COORDINATE && std::fmax(-b0, b1) < BP_MAX_COORDINATE;
+                        worst = std::max(worst, near && a1 - a0 < 4096.0f && b1 - b0 < 4096.0f ? (w.w + 1) * (w.h + 1) : 1 << 30);
                     }
         }
         need[t] = worst;

@@ -57,6 +57,10 @@ struct SfWindow {
     int need_w, need_h;
 };
 
+// Largest detector coordinate at which float bounds of a window stand: their rounding, half of 2^-7 pixels, stays below the
+// hundredth of a pixel by which every window function widens them.
+constexpr float BP_MAX_COORDINATE = 131072.0f;
+
 // Staging role of a thread under a window of pw columns and ph rows: it stages column sc of rows sr + (256 / pw) s, those
 // below ph.  Threads left over where pw does not divide 256 stage nothing: given the next step's first row, they would
 // write its cells without an order to the threads that own them, and not the same values either (the row's detector

@@ -21,6 +21,7 @@
 #include "../../paper_2307_05801_amd/csrc/sf_project_columns.h"
 #include "../../paper_2307_05801_amd/csrc/md_project_columns.h"
 #include "../../paper_2307_05801_amd/csrc/md_backproject_tiled.h"
+#include "../../paper_2307_05801_amd/csrc/md_footprint_tiled.h"
 #include "../../paper_2307_05801_amd/csrc/sd_backproject_tiled.h"
 
 // ---- stubs of the HIP runtime calls made by leap_geometry.cpp: "device" memory is host memory ---------------
@@ -716,4 +717,117 @@ extern "C" long host_md_backproject_tiled(const leap_geometry *G, const float *s
     default: return -1;
     }
     return report[0] + report[1] + report[2];
+}
+
+// ---- footprints on tilted modules: the tiled kernels, with their own functions ------------------------------------------------
+// Back: voxel by voxel on the staged window of its workgroup's box; report[0]: windows larger than the staging buffer, report[1]: reads
+// of the common case (three rows of three columns) outside the window.  Returns -1 when the handle does not use that kernel.
+extern "C" long host_mf_backproject_tiled(const leap_geometry *G, const float *sino, float *vol, int64_t *report)
+{
+    const SfGeom &g = G->g;
+    if (!G->mf_tiled) return -1;
+    const int tiles_x = (g.nx + MF_T - 1) / MF_T, tiles_y = (g.ny + MF_T - 1) / MF_T, chunks = (g.nz + MF_ZC - 1) / MF_ZC;
+    int64_t large = 0, outside = 0;
+#pragma omp parallel for collapse(2) reduction(+ : large, outside)
+    for (int ch = 0; ch < chunks; ++ch)
+        for (int tile = 0; tile < tiles_x * tiles_y; ++tile) {
+            const int i0 = (tile % tiles_x) * MF_T, j0 = (tile / tiles_x) * MF_T, k0 = ch * MF_ZC;
+            const int i1 = std::min(i0 + MF_T, g.nx) - 1, j1 = std::min(j0 + MF_T, g.ny) - 1, k1 = std::min(k0 + MF_ZC, g.nz) - 1;
+            std::vector<double> acc((size_t)MF_T * MF_T * MF_ZC, 0.0);
+            for (int a = 0; a < g.nviews; ++a) {
+                const MfView &V = G->d_mfviews[a];
+                float x[4] = {3e38f, -3e38f, 3e38f, -3e38f};
+                for (int q = 0; q < 8; ++q) {
+                    float xi, eta;
+                    mf_box_corner(g, V, i0, i1, j0, j1, k0, k1, q, xi, eta);
+                    x[0] = std::min(x[0], xi); x[1] = std::max(x[1], xi); x[2] = std::min(x[2], eta); x[3] = std::max(x[3], eta);
+                }
+                const MfWindow w = mf_window(x[0], x[1], x[2], x[3]);
+                if ((int64_t)w.w * w.h > MF_PATCH || w.w < 1 || w.h < 1) { ++large; continue; }
+                std::vector<double> patch((size_t)w.w * w.h);
+                for (int rr = 0; rr < w.h; ++rr)
+                    for (int cc = 0; cc < w.w; ++cc) {
+                        const int r = w.r0 + rr, c = w.c0 + cc;
+                        const bool in = r >= 0 && r < g.nrows && c >= 0 && c < g.ncols;
+                        patch[(size_t)rr * w.w + cc] = in ? (double)sino[((size_t)a * g.nrows + r) * g.ncols + c] * mf_amp(g, V, r, c) : 0.0;
+                    }
+                for (int j = j0; j <= j1; ++j)
+                    for (int i = i0; i <= i1; ++i) {
+                        MfWalk at = mf_walk(g, V, mf_column(g, V, i, j), k0);
+                        for (int k = k0; k <= k1; ++k) {
+                            const MfFoot f = mf_next(V, at);
+                            const double fr0 = floor(f.e0), fc0 = floor(f.k0 + 0.5), above = f.e1 - fr0;
+                            const int rows = (int)(floor(f.e1) - fr0), cols = (int)(ceil(f.k3 - 0.5) - fc0);
+                            const int rr = (int)fr0 - w.r0, cc = (int)fc0 - w.c0;
+                            if (rr < 0 || cc < 0 || rr + std::max(rows, 2) >= w.h || cc + std::max(cols, 2) >= w.w) { ++outside; continue; }
+                            double fu[3], &sum = acc[((size_t)(k - k0) * MF_T + (j - j0)) * MF_T + (i - i0)];
+                            double x_edge = fc0 + 0.5, below = 0.0;
+                            mf_fu3(f, x_edge, fu);
+                            for (int m = 0; m <= std::max(cols, 2); ++m, x_edge += 1.0) {
+                                const double upto = mf_integral_at(f, x_edge), share = cols > 2 ? upto - below : fu[m];
+                                below = upto;
+                                for (int n = 0; n <= std::max(rows, 1); ++n) {
+                                    const double fv = n == 0 ? mf_min(above, 1.0) - (f.e0 - fr0) : mf_sub01(above, (double)n);
+                                    sum = fma(share * fv, patch[(size_t)(rr + n) * w.w + cc + m], sum);
+                                }
+                            }
+                        }
+                    }
+            }
+            for (int k = k0; k <= k1; ++k)
+                for (int j = j0; j <= j1; ++j)
+                    for (int i = i0; i <= i1; ++i)
+                        vol[((size_t)k * g.ny + j) * g.nx + i] = (float)acc[((size_t)(k - k0) * MF_T + (j - j0)) * MF_T + (i - i0)];
+        }
+    report[0] = large; report[1] = outside;
+    return large + outside;
+}
+
+// Forward: every voxel's shares on every detector tile (the kernel visits a subset: those its beams can meet).  Returns -1 when the
+// handle does not use that kernel, else the number of shares of the common case beside the tile's guarded sums.
+extern "C" long host_mf_project_tiles(const leap_geometry *G, const float *vol, float *sino)
+{
+    const SfGeom &g = G->g;
+    if (!G->mf_tiles) return -1;
+    long beside = 0;
+    const int tiles_c = (g.ncols + MF_TC - 1) / MF_TC, tiles_r = (g.nrows + MF_TR - 1) / MF_TR;
+#pragma omp parallel for collapse(2) reduction(+ : beside)
+    for (int a = 0; a < g.nviews; ++a)
+        for (int tile = 0; tile < tiles_c * tiles_r; ++tile) {
+            const MfView &V = G->d_mfviews[a];
+            const int c0 = (tile % tiles_c) * MF_TC, r0 = (tile / tiles_c) * MF_TR;
+            const int c1 = std::min(c0 + MF_TC, g.ncols) - 1, r1 = std::min(r0 + MF_TR, g.nrows) - 1;
+            std::vector<double> sums((size_t)(MF_TR + 2 * MF_TG) * MF_TS, 0.0);
+            auto add = [&](int r, int c, double v) {
+                const long cell = (long)(r + MF_TG) * MF_TS + c + MF_TG;
+                if (cell < 0 || cell >= (long)sums.size() || c + MF_TG < 0 || c + MF_TG >= MF_TS) ++beside;
+                else sums[cell] += v;
+            };
+            for (int j = 0; j < g.ny; ++j)
+                for (int i = 0; i < g.nx; ++i) {
+                    MfWalk at = mf_walk(g, V, mf_column(g, V, i, j), 0);
+                    for (int k = 0; k < g.nz; ++k) {
+                        const MfFoot f = mf_next(V, at);
+                        const double x = vol[((size_t)k * g.ny + j) * g.nx + i], fr0 = floor(f.e0), fc0 = floor(f.k0 + 0.5), above = f.e1 - fr0;
+                        const int rb = (int)fr0 - r0, cb = (int)fc0 - c0;
+                        const int rows = (int)(floor(f.e1) - fr0), cols = (int)(ceil(f.k3 - 0.5) - fc0);
+                        if (!(rb + rows >= 0 && rb <= r1 - r0 && cb + cols >= 0 && cb <= c1 - c0)) continue;
+                        const bool common = cols <= 2 && rows <= 2;
+                        double fu[3], below = 0.0, edge = fc0 + 0.5;
+                        mf_fu3(f, edge, fu);
+                        for (int m = 0; m <= (common ? 2 : cols); ++m, edge += 1.0) {
+                            const double upto = mf_integral_at(f, edge), share = common ? fu[m] : upto - below;
+                            below = upto;
+                            for (int n = 0; n <= (common ? 2 : rows); ++n) {
+                                const double fv = n == 0 ? mf_min(above, 1.0) - (f.e0 - fr0) : mf_sub01(above, (double)n);
+                                if (common || (rb + n >= 0 && rb + n <= r1 - r0 && cb + m >= 0 && cb + m <= c1 - c0)) add(rb + n, cb + m, share * (fv * x));
+                            }
+                        }
+                    }
+                }
+            for (int r = r0; r <= r1; ++r)
+                for (int c = c0; c <= c1; ++c)
+                    sino[((size_t)a * g.nrows + r) * g.ncols + c] = (float)(sums[(size_t)(r - r0 + MF_TG) * MF_TS + c - c0 + MF_TG] * mf_amp(g, V, r, c));
+        }
+    return beside;
 }

@@ -45,6 +45,10 @@ def host():
     lib.host_curved_column_deviation.argtypes = [C.c_void_p, C.POINTER(C.c_double)]
     lib.host_sd_project_columns.restype = C.c_long
     lib.host_sd_project_columns.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
+    lib.host_mf_backproject_tiled.restype = C.c_long
+    lib.host_mf_backproject_tiled.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(C.c_int64)]
+    lib.host_mf_project_tiles.restype = C.c_long
+    lib.host_mf_project_tiles.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
     lib.host_sd_project_pairs.restype = C.c_long
     lib.host_sd_project_pairs.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
     lib.host_sd_backproject_tiled.restype = C.c_long
@@ -523,6 +527,65 @@ def test_tilted_footprint_bodies_match_oracle_on_cpu(host, oracle_mod, name):
     assert rel_l2(ax, ref_a) <= 1e-6 and rel_l2(aty, ref_t) <= 1e-6
     assert np.abs(ax - ref_a).max() <= 2e-6 * np.abs(ref_a).max()
     assert np.abs(aty - ref_t).max() <= 2e-6 * np.abs(ref_t).max()
+
+
+@pytest.mark.parametrize("shift", [dict(shift_u=3e6), dict(shift_v=-3e6), dict(shift_u=-1e9), dict(shift_u=1e12)])
+@pytest.mark.parametrize("name", ["c3_div8_ragged", "curved_c3_div8"])
+def test_tiled_back_projections_far_beside_the_detector(host, name, shift):
+    cfg = CASES[name][1]()
+    cfg = cfg.replace(geom=CONE if name != "curved_c3_div8" or "shift_u" in shift else CONE_CURVED, **{k: v + 0.3 for k, v in shift.items()})
+    rep, desc = window_report(host, cfg)
+    assert rep[7] == 0, (list(rep), desc)
+    y = uniform_sinogram(cfg, 4)[0]
+    h = handle(host, cfg, B.LEAP_MODEL_SIDDON)
+    aty, rep4 = np.zeros(cfg.vol_shape, np.float32), (C.c_int64 * 4)()
+    assert host.host_sd_backproject_tiled(h, y.ctypes.data, aty.ctypes.data, rep4) in (0, -1), list(rep4)
+    B.leap_geometry_destroy(h, host)
+    tilted = perturbed_poses(level_rows("tilted", CONE, nx=40, ny=40), 3, shift_mm=2.0, tilt_rad=0.1).replace(**{k: v + 0.3 for k, v in shift.items()})
+    y = uniform_sinogram(tilted, 4)[0]
+    h = handle(host, tilted, B.LEAP_MODEL_SIDDON)
+    aty, rep3 = np.zeros(tilted.vol_shape, np.float32), (C.c_int64 * 3)()
+    assert host.host_md_backproject_tiled(h, y.ctypes.data, aty.ctypes.data, rep3) in (0, -1), list(rep3)
+    B.leap_geometry_destroy(h, host)
+
+
+TILED_FOOTPRINT_CASES = {
+    "ragged": dict(nx=17, ny=20, nz=11, nrows=70, ncols=37, pixel=1.5), "wide_angles": dict(nx=20, ny=15, nz=9, nrows=40, ncols=50, pixel=1.5, tilt=0.5),
+    "fine_pixels": dict(nx=9, ny=8, nz=10, nrows=90, ncols=60, pixel=0.45), "coarse_pixels": dict(nx=20, ny=18, nz=10, nrows=20, ncols=24, pixel=3.7),
+    "far_columns": dict(nx=9, ny=8, nz=10, nrows=20, ncols=24, pixel=1.5, shift_u=100000.25)}
+
+
+def tiled_footprint_scan(nx, ny, nz, nrows, ncols, pixel, tilt=0.1, **kw):
+    base = CTConfig("tiled", CONE, nviews=6, arc_deg=360.0, nrows=nrows, ncols=ncols, pixel_v=pixel, pixel_u=pixel, nx=nx, ny=ny, nz=nz,
+                    voxel_xy=1.0, voxel_z=1.1, sod=160.0, sdd=240.0, shift_v=-0.3, center_x=1.0, center_y=-2.0, center_z=0.5, start_deg=3.0)
+    return perturbed_poses(base, 3, shift_mm=4.0, tilt_rad=tilt).replace(**kw)
+
+
+@pytest.mark.parametrize("name", list(TILED_FOOTPRINT_CASES))
+def test_tiled_tilted_footprints_match_oracle_on_cpu(host, oracle_mod, name):
+    cfg = tiled_footprint_scan(**TILED_FOOTPRINT_CASES[name])
+    x, y = uniform_volume(cfg, 3)[0], uniform_sinogram(cfg, 4)[0]
+    h = handle(host, cfg)
+    ax, aty, rep = np.zeros(cfg.sino_shape, np.float32), np.zeros(cfg.vol_shape, np.float32), (C.c_int64 * 2)()
+    beside = host.host_mf_project_tiles(h, x.ctypes.data, ax.ctypes.data)
+    bad = host.host_mf_backproject_tiled(h, y.ctypes.data, aty.ctypes.data, rep)
+    B.leap_geometry_destroy(h, host)
+    assert beside == 0 and bad == 0, (beside, list(rep))
+    for got, want in ((ax, oracle_mod.project(cfg, x)), (aty, oracle_mod.backproject(cfg, y))):
+        assert np.linalg.norm(got - want) <= 6e-8 * np.linalg.norm(want) + 1e-12
+
+
+@pytest.mark.parametrize("shift_u", [0.0, 3e5, 3e6, 3e7, 1e9, 1e12])
+def test_tiled_tilted_footprints_far_beside_the_detector(host, shift_u):
+    """Columns far from the detector's own: a float holds a window's bounds to a fraction of a pixel only so far out."""
+    cfg = tiled_footprint_scan(nx=40, ny=40, nz=16, nrows=40, ncols=50, pixel=1.37, shift_u=shift_u + 0.3)
+    y = uniform_sinogram(cfg, 4)[0]
+    h = handle(host, cfg)
+    aty, rep = np.zeros(cfg.vol_shape, np.float32), (C.c_int64 * 2)()
+    bad = host.host_mf_backproject_tiled(h, y.ctypes.data, aty.ctypes.data, rep)
+    B.leap_geometry_destroy(h, host)
+    assert bad == 0 or bad == -1, (bad, list(rep))
+    assert bad == 0 or shift_u > 1e5
 
 
 def test_tilted_scans_without_footprints_are_refused(host):
