@@ -71,7 +71,7 @@ struct SfStageRole {
 
 SF_HD SfStageRole sf_stage_role(int tid, int pw, int ph)
 {
-    return {tid % pw, tid < 256 / pw * pw ? tid / pw : ph};
+    return {tid % pw, 256 % pw == 0 || tid < 256 / pw * pw ? tid / pw : ph};
 }
 
 // Cylindrical detector: column-coordinate range [xi_lo, xi_hi] and the range [ilo, ihi] of 1 / (in-plane distance from
