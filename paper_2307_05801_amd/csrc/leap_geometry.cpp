@@ -644,7 +644,15 @@ static void select_tilted_footprint_kernels(leap_geometry *G)
     // Forward: layers are walked along x or y, whichever a tile's central ray advances faster on.  Modules seen from above,
     // whose rays advance fastest along z, have beams that cross such a layer in long strips: they stay with the general
     // kernel, which can walk along z.
-    G->mf_tiles = tilted_rays_stay_flat(G, d->voxel_xy / d->voxel_z);
+    for (const MfView &V : G->mfviews) {
+        G->max_cols_per_voxel = std::max(G->max_cols_per_voxel, 2.0 * V.pad_u * V.ipu);
+        G->max_rows_per_voxel = std::max(G->max_rows_per_voxel, 2.0 * V.pad_v * V.ipv);
+    }
+    // A voxel that covers many pixels makes as many LDS additions in each of the tiles it reaches, where the general kernel's
+    // threads share its footprint between eight rows.  32^3 x 40 views, general / tiles: voxels of up to 13 x 9 pixels 798 / 602 us,
+    // 16 x 11 897 / 1021, 21 x 15 999 / 1737; 6 x 15 816 / 581, 2 x 19 638 / 715, 21 x 5 943 / 911.
+    G->mf_tiles = G->max_cols_per_voxel * G->max_rows_per_voxel <= 120.0 && G->max_rows_per_voxel <= 16.0 &&
+                  tilted_rays_stay_flat(G, d->voxel_xy / d->voxel_z);
     // Back: the staged window of every (view, tile, chunk) must fit.  The boxes' corners are the points of one lattice; the
     // views are shared out among a few threads.
     const int tiles_x = (d->nx + MF_T - 1) / MF_T, tiles_y = (d->ny + MF_T - 1) / MF_T, chunks = (d->nz + MF_ZC - 1) / MF_ZC;

@@ -794,8 +794,16 @@ int leap_launch_backproject(const leap_geometry *G, const float *d_sino, float *
     if (G->bp_tiled) return launch_bp_items(G, d_sino, d_vol, 1, stream);
     if (G->mf_tiled) {
         const unsigned tiles_x = cdiv(g.nx, MF_T), tiles_y = cdiv(g.ny, MF_T);
-        hipLaunchKernelGGL(mf_backproject_tiled, dim3(tiles_x * tiles_y, cdiv(g.nz, MF_ZC)), dim3(256), 0, stream, g, G->d_mfviews, d_sino,
-                           d_vol, (int)tiles_x);
+        auto go = [&](auto kernel, int zc) {
+            hipLaunchKernelGGL(kernel, dim3(tiles_x * tiles_y, cdiv(g.nz, zc)), dim3(256), 0, stream, g, G->d_mfviews, d_sino, d_vol, (int)tiles_x);
+        };
+        // Voxels per thread: the most that leave the chip's 256 compute units a workgroup each.  A workgroup takes 4.4 us a view for
+        // eight voxels per thread, 1.5 for one, whatever the others do.  60 views, 8 / 2 / 1 voxels: 112^2 x 64 (392 workgroups
+        // of eight) 376 / 412 us, 96^2 x 48 (216) 278 / 254, 48^3 (270 of two) 280 / 134 / 126, 32^3 (64 of two) 278 / 132 / 111.
+        const unsigned tiles = tiles_x * tiles_y;
+        if (tiles * cdiv(g.nz, MF_ZC) >= 320) go(mf_backproject_tiled<MF_ZC>, MF_ZC);
+        else if (tiles * cdiv(g.nz, MF_ZC_SMALL) >= 320) go(mf_backproject_tiled<MF_ZC_SMALL>, MF_ZC_SMALL);
+        else go(mf_backproject_tiled<1>, 1);
         LEAP_HIP_CHECK(hipGetLastError());
         return LEAP_OK;
     }

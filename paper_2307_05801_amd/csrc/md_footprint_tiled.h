@@ -25,7 +25,7 @@
 
 #include "md_footprint.h"
 
-constexpr int MF_T = 16, MF_ZC = 8;              // back projection: tile edge, voxels per thread
+constexpr int MF_T = 16, MF_ZC = 8, MF_ZC_SMALL = 2;      // back projection: tile edge, voxels per thread (small volumes: fewer)
 constexpr int MF_PATCH = 2048;                   // doubles per staged window
 constexpr int MF_TC = 16, MF_TR = 64;            // forward: detector tile of a wave, columns x rows
 constexpr int MF_TG = 2;                         // guard columns and rows around it, which take what falls beside the tile
@@ -204,26 +204,28 @@ __device__ __forceinline__ MfWindow mf_wave_window(const SfGeom &g, const MfView
     return w;
 }
 
+template <int ZC>
 __global__ __launch_bounds__(256, 4) void mf_backproject_tiled(SfGeom g, const MfView *__restrict__ views, const float *__restrict__ sino,
                                                             float *__restrict__ vol, int tiles_x)
 {
     __shared__ double patch[2][MF_PATCH];
     const int tid = threadIdx.x, lane = tid & 63;
     const int ty = blockIdx.x / tiles_x, tx = blockIdx.x - ty * tiles_x;
-    const int i0 = tx * MF_T, j0 = ty * MF_T, k0 = blockIdx.y * MF_ZC;
+    const int i0 = tx * MF_T, j0 = ty * MF_T, k0 = blockIdx.y * ZC;
     const int i1 = i0 + MF_T < g.nx ? i0 + MF_T - 1 : g.nx - 1, j1 = j0 + MF_T < g.ny ? j0 + MF_T - 1 : g.ny - 1;
-    const int k1 = k0 + MF_ZC < g.nz ? k0 + MF_ZC - 1 : g.nz - 1;
+    const int k1 = k0 + ZC < g.nz ? k0 + ZC - 1 : g.nz - 1;
     const int i = i0 + (tid & (MF_T - 1)), j = j0 + tid / MF_T;
     const int ic = i < g.nx ? i : g.nx - 1, jc = j < g.ny ? j : g.ny - 1;        // threads beyond the edge shadow it
     const size_t view_stride = (size_t)g.nrows * g.ncols;
 
-    double acc[MF_ZC];
+    double acc[ZC];
 #pragma unroll
-    for (int kk = 0; kk < MF_ZC; ++kk) acc[kk] = 0.0;
+    for (int kk = 0; kk < ZC; ++kk) acc[kk] = 0.0;
 
     constexpr int NSTAGE = MF_PATCH / 256;
     float stage[NSTAGE];
     MfWindow win, next;
+    auto sees = [&](const MfWindow &w) { return w.c0 < g.ncols && w.c0 + w.w > 0 && w.r0 < g.nrows && w.r0 + w.h > 0; };
     auto fetch = [&](int a, MfWindow &w) {
         w = mf_wave_window(g, views[a], i0, i1, j0, j1, k0, k1, lane);
         w.w = w.w < 1 ? 1 : (w.w > MF_PATCH ? MF_PATCH : w.w);                   // (the host checked that the window fits)
@@ -263,10 +265,11 @@ __global__ __launch_bounds__(256, 4) void mf_backproject_tiled(SfGeom g, const M
         if (a + 1 < g.nviews) fetch(a + 1, next);                 // loads in flight during the gather
         const MfView &V = views[a];
         MfWalk at = mf_walk(g, V, mf_column(g, V, ic, jc), k0);
+        const bool seen = sees(win);                              // uniform: a box beside the detector takes nothing from this view
         const bool finite = !(odd[a & 1][0] | odd[a & 1][1] | odd[a & 1][2] | odd[a & 1][3]);        // uniform
 #pragma unroll
-        for (int kk = 0; kk < MF_ZC; ++kk) {
-            if (k0 + kk >= g.nz) break;                           // uniform
+        for (int kk = 0; kk < ZC; ++kk) {
+            if (!seen || k0 + kk >= g.nz) break;                  // uniform
             const MfFoot f = mf_next(V, at);
             const double fr0 = floor(f.e0), fc0 = floor(f.k0 + 0.5);
             const int rows = (int)(floor(f.e1) - fr0), cols = (int)(ceil(f.k3 - 0.5) - fc0);    // further rows, columns it touches
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(256, 4) void mf_backproject_tiled(SfGeom g, const M
     }
     if (i < g.nx && j < g.ny) {
 #pragma unroll
-        for (int kk = 0; kk < MF_ZC; ++kk)
+        for (int kk = 0; kk < ZC; ++kk)
             if (k0 + kk < g.nz) vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = (float)acc[kk];
     }
 }

@@ -1,5 +1,5 @@
 """Footprints on tilted modules through the tiled kernels (md_footprint_tiled.h) against the oracle: edges of the voxel tiles
-(16 x 16 x 8) and of the detector tiles (16 x 64), footprints wider and taller than the three columns and rows of the common
+(16 x 16 of 8, 2 or 1) and of the detector tiles (16 x 64), footprints wider and taller than the three columns and rows of the common
 case, modules turned by a quarter, and values a weight of zero must not spread."""
 import numpy as np
 import pytest
@@ -30,7 +30,7 @@ def rolled(angle):
 
 SCANS = [scan(1, 1, 1, 3, 2), scan(16, 16, 8, 64, 16), scan(17, 15, 9, 65, 17), scan(33, 40, 23, 40, 63, tilt=0.5),
          scan(24, 24, 60, 130, 70, pixel_v=0.9), scan(9, 8, 12, 90, 60, pixel_u=0.42, pixel_v=0.45), scan(30, 30, 10, 20, 24, pixel_u=4.0, pixel_v=3.5),
-         scan(18, 20, 11, 60, 50, voxel_z=2.3, pixel_v=1.1), rolled(1.2), rolled(2.9), rolled("quarter")]
+         scan(18, 20, 11, 60, 50, voxel_z=2.3, pixel_v=1.1), scan(80, 79, 105, 60, 50), scan(47, 48, 81, 40, 40), scan(47, 48, 79, 40, 40), rolled(1.2), rolled(2.9), rolled("quarter")]
 
 
 @pytest.mark.parametrize("cfg", SCANS, ids=lambda c: c.name)

@@ -928,3 +928,14 @@ def test_tilted_siddon_kernels_on_random_scans_match_oracle_on_cpu(host, oracle_
         checked += 1
     B.leap_geometry_destroy(h, host)
     assert checked >= 1, desc
+
+
+@pytest.mark.parametrize("pixel_u,pixel_v,tiles", [(0.45, 0.45, True), (0.25, 0.25, True), (0.2, 0.2, False), (0.12, 1.5, True),
+                                                   (1.5, 0.12, False), (0.5, 0.15, True), (0.1, 0.5, False)])
+def test_forward_tiles_of_tilted_footprints_are_left_where_voxels_cover_many_pixels(host, pixel_u, pixel_v, tiles):
+    base = CTConfig("fine", CONE, nviews=8, arc_deg=360.0, nrows=40, ncols=40, pixel_v=pixel_v, pixel_u=pixel_u, nx=32, ny=32, nz=32,
+                    voxel_xy=1.0, voxel_z=1.0, sod=80.0, sdd=120.0, start_deg=3.0)
+    h = handle(host, perturbed_poses(base, 3, shift_mm=2.0, tilt_rad=0.05))
+    desc = B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
+    assert ("A=general(tiles)" in desc) == tiles, desc
