@@ -77,24 +77,39 @@ SF_HD MdAxial md_axial(const MdSlabRay &M)
     return A;
 }
 
-// One slab's contribution to a ray's sum.  volz: the z-fastest copy of the slab (columns of nzp floats; column
-// zero_col / nzp is all zero); live: the ray reads this kind of slab.  Returns acc plus the slab's share, in units of X.
-SF_HD float md_slab_step(const SfGeom &g, const MdSlabRay &M, const MdAxial &A, int n, const SfSlab &slab,
-                         const float *__restrict__ volz, int nzp, unsigned zero_col, bool live, float acc)
+// Where the voxel columns of a slab's scratch copy (columns of nzp floats) lie as a ray of marching axis x (xmajor) or y sees them:
+// column (slab n, minor index q) at base + q pitch_q, base growing by pitch_n per slab from 0 at slab.n0.  One integer
+// multiplication per ray and slab instead of four.
+struct MdPitch {
+    unsigned q, n;
+};
+
+SF_HD MdPitch md_pitch(const SfSlab &slab, bool xmajor, int nx, int nzp)
 {
-    const int n_minor = slab.xmajor ? g.ny : g.nx;
-    const SdSplit s = sd_slab_split(M.R, n);
-    live = live && md_slab_in_front(M, n);
-    const bool a_ok = live && s.qa >= 0 && s.qa < n_minor;
-    const bool b_ok = live && s.qa != s.qb && s.qb >= 0 && s.qb < n_minor;
-    const unsigned base_a = a_ok ? sf_slab_column(slab, g.nx, slab.xmajor ? n : s.qa, slab.xmajor ? s.qa : n) * (unsigned)nzp : zero_col;
-    const unsigned base_b = b_ok ? sf_slab_column(slab, g.nx, slab.xmajor ? n : s.qb, slab.xmajor ? s.qb : n) * (unsigned)nzp : zero_col;
-    int kf;
-    float tlow;
-    sd_axial_cell(fma((double)n, M.R.dh, A.zadj), A.inv_amz, nzp - 2, kf, tlow);
-    // (a slab without a crossing has f = 1 and reads the zero column for cell b: the same four terms serve both)
-    return sd_gather_two(volz + base_a + (unsigned)kf, volz + base_b + (unsigned)kf, A.inc, s.f, 1.0f - s.f, tlow, acc);
+    return {(unsigned)nzp * (xmajor ? (unsigned)slab.width : 1u), (unsigned)nzp * (xmajor ? 1u : (unsigned)nx)};
 }
+
+// Does the ray meet the volume in cell a (b) of slab n?  now: it reads this kind of slab.
+SF_HD void md_slab_meets(const MdSlabRay &M, const SdSplit &s, int n, int n_minor, bool now, bool &a_ok, bool &b_ok)
+{
+    const bool live = now && md_slab_in_front(M, n);
+    a_ok = live & ((unsigned)s.qa < (unsigned)n_minor);
+    b_ok = live & (s.qa != s.qb) & ((unsigned)s.qb < (unsigned)n_minor);
+}
+
+// Offset of cell a's column, of the neighbouring column that cell b is (only where the ray crosses), and of the lower axial cell
+// within a column; the share of the slab spent in it.  A cell outside the volume is read from the zero column instead.
+SF_HD unsigned md_cell_a(const SdSplit &s, const MdPitch &pitch, unsigned base) { return (unsigned)s.qa * pitch.q + base; }
+SF_HD unsigned md_cell_b(const SdSplit &s, const MdPitch &pitch, unsigned at_a) { return s.qb > s.qa ? at_a + pitch.q : at_a - pitch.q; }
+SF_HD void md_axial_place(const MdSlabRay &M, const MdAxial &A, int n, int nzp, unsigned &k, float &tlow)
+{
+    int kf;
+    sd_axial_cell(fma((double)n, M.R.dh, A.zadj), A.inv_amz, nzp - 2, kf, tlow);
+    k = (unsigned)kf;
+}
+
+// A slab in which the ray stays in one in-plane cell: sd_gather_two's sums without the second cell's, bit for bit.
+SF_HD float md_gather_one(float x0, float x1, float tlow, float acc) { return fmaf(1.0f - tlow, x1, fmaf(tlow, x0, acc)); }
 
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
 
@@ -155,23 +170,20 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
         }
         if (__ballot(some) == 0ull) continue;        // no ray of this wave reads this kind of slab
         any = true;
-        // md_slab_step for all row groups at once, the same sums bit for bit.  The rays of a detector column run nearly
-        // together, so a slab usually finds all of them in the volume or none, and changing their in-plane cell or none: slabs
-        // that all miss are skipped, and the second cells are only read where some ray enters one.  A cell's place in the
-        // scratch copy is q pitch_q + n pitch_n: one integer multiplication per ray and slab instead of four.  256^3 x 360 views
-        // x 256^2: 8.35 -> 6.30 ms (8.87 with a branch per row group: the groups' loads must be in flight together).
+        // The rays of a detector column run nearly together, so a slab usually finds all of them in the volume or none, and
+        // changing their in-plane cell or none: slabs that all miss are skipped, and the second cells are only read where some
+        // ray enters one.  256^3 x 360 views x 256^2: 8.35 -> 6.30 ms (8.87 with a branch per row group: the groups' loads must
+        // be in flight together).
         const int n_minor = kind ? g.ny : g.nx;
-        const unsigned pitch_q = (unsigned)nzp * (kind ? (unsigned)slab.width : 1u), pitch_n = (unsigned)nzp * (kind ? 1u : (unsigned)g.nx);
+        const MdPitch pitch = md_pitch(slab, kind != 0, g.nx, nzp);
         unsigned base_n = 0;
-        for (int n = slab.n0; n < slab.n1; ++n, base_n += pitch_n) {
+        for (int n = slab.n0; n < slab.n1; ++n, base_n += pitch.n) {
             SdSplit s[RG];
             bool a_ok[RG], b_ok[RG], meets = false, two = false;
 #pragma unroll
             for (int gq = 0; gq < RG; ++gq) {
                 s[gq] = sd_slab_split(M[gq].R, n);
-                const bool live = now[gq] && md_slab_in_front(M[gq], n);
-                a_ok[gq] = live && (unsigned)s[gq].qa < (unsigned)n_minor;
-                b_ok[gq] = live && s[gq].qa != s[gq].qb && (unsigned)s[gq].qb < (unsigned)n_minor;
+                md_slab_meets(M[gq], s[gq], n, n_minor, now[gq], a_ok[gq], b_ok[gq]);
                 meets = meets || a_ok[gq] || b_ok[gq];
                 two = two || s[gq].qa != s[gq].qb;
             }
@@ -180,10 +192,8 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
             unsigned at_a[RG], k[RG];
 #pragma unroll
             for (int gq = 0; gq < RG; ++gq) {
-                int kf;
-                sd_axial_cell(fma((double)n, M[gq].R.dh, A[gq].zadj), A[gq].inv_amz, nzp - 2, kf, tlow[gq]);
-                k[gq] = (unsigned)kf;
-                at_a[gq] = (unsigned)s[gq].qa * pitch_q + base_n;
+                md_axial_place(M[gq], A[gq], n, nzp, k[gq], tlow[gq]);
+                at_a[gq] = md_cell_a(s[gq], pitch, base_n);
                 const float *__restrict__ xa = volz + ((a_ok[gq] ? at_a[gq] : zero_col) + k[gq]);
                 xa0[gq] = xa[0]; xa1[gq] = xa[1];
             }
@@ -191,7 +201,7 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
                 float xb0[RG], xb1[RG];
 #pragma unroll
                 for (int gq = 0; gq < RG; ++gq) {
-                    const unsigned at_b = s[gq].qb > s[gq].qa ? at_a[gq] + pitch_q : at_a[gq] - pitch_q;
+                    const unsigned at_b = md_cell_b(s[gq], pitch, at_a[gq]);
                     const float *__restrict__ xb = volz + ((b_ok[gq] ? at_b : zero_col) + k[gq]);
                     xb0[gq] = xb[0]; xb1[gq] = xb[1];
                 }
@@ -202,7 +212,7 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
                 }
             } else {
 #pragma unroll
-                for (int gq = 0; gq < RG; ++gq) acc[gq] = fmaf(1.0f - tlow[gq], xa1[gq], fmaf(tlow[gq], xa0[gq], acc[gq]));
+                for (int gq = 0; gq < RG; ++gq) acc[gq] = md_gather_one(xa0[gq], xa1[gq], tlow[gq], acc[gq]);
             }
         }
     }

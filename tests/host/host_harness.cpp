@@ -628,7 +628,22 @@ extern "C" long host_md_project_columns(const leap_geometry *G, const float *vol
                         const MdAxial A = md_axial(M);
                         const bool mine = M.R.xmajor == xmajor;
                         float t = 0.f;
-                        for (int n = n0; n < n1; ++n) t = md_slab_step(g, M, A, n, slab, volz, nzp, zero_col, mine, t);
+                        const MdPitch pitch = md_pitch(slab, xmajor != 0, g.nx, nzp);
+                        unsigned base = 0;
+                        for (int n = n0; n < n1; ++n, base += pitch.n) {
+                            const SdSplit s = sd_slab_split(M.R, n);
+                            bool a_ok, b_ok;
+                            md_slab_meets(M, s, n, xmajor ? g.ny : g.nx, mine, a_ok, b_ok);
+                            if (!a_ok && !b_ok) continue;
+                            unsigned k;
+                            float tlow;
+                            md_axial_place(M, A, n, nzp, k, tlow);
+                            const unsigned at_a = md_cell_a(s, pitch, base);
+                            const float *xa = volz + (a_ok ? at_a : zero_col) + k, *xb = volz + (b_ok ? md_cell_b(s, pitch, at_a) : zero_col) + k;
+                            const float one = md_gather_one(xa[0], xa[1], tlow, t);
+                            t = sd_gather_two(xa, xb, A.inc, s.f, 1.0f - s.f, tlow, t);
+                            if (s.qa == s.qb && one != t) t = NAN;          // (a wave in which no ray crosses takes the short form)
+                        }
                         if (mine) acc[((size_t)a * g.nrows + r) * g.ncols + c] += M.len * t;
                     }
         }
