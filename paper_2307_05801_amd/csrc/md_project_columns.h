@@ -125,18 +125,7 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
-    {   // block -> (view, band, column tile) in the XCD-aware order of sd_project_columns
-        const int xcd = blockIdx.x & 7, sq = blockIdx.x >> 3;
-        const int per_chunk = tb * views_pad;
-        const int chunk = sq / per_chunk, r = sq - chunk * per_chunk;
-        const int vblk = r / (tb * vb), r2 = r - vblk * (tb * vb);
-        const int tloc = r2 / vb, v_in = r2 - tloc * vb;
-        const int tchunks = tiles_per_xcd_pad / tb;
-        band = chunk / tchunks;
-        ct = ((chunk - band * tchunks) * tb + tloc) * 8 + xcd;
-        a = vblk * vb + v_in;
-        if (ct >= col_tiles || a >= g.nviews || band >= bands) return;
-    }
+    if (!fp_block(tb, vb, views_pad, tiles_per_xcd_pad, col_tiles, g.nviews, bands, ct, band, a)) return;
     const int c = ct * SD_WAVES + wave;
     if (c >= g.ncols) return;
     const int band0 = band * (RG * 64);

@@ -178,18 +178,7 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
-    {   // block -> (view, band, column tile) in the XCD-aware order of sd_project_columns
-        const int xcd = blockIdx.x & 7, sq = blockIdx.x >> 3;
-        const int per_chunk = tb * views_pad;
-        const int chunk = sq / per_chunk, r = sq - chunk * per_chunk;
-        const int vblk = r / (tb * vb), r2 = r - vblk * (tb * vb);
-        const int tloc = r2 / vb, v_in = r2 - tloc * vb;
-        const int tchunks = tiles_per_xcd_pad / tb;
-        band = chunk / tchunks;
-        ct = ((chunk - band * tchunks) * tb + tloc) * 8 + xcd;
-        a = vblk * vb + v_in;
-        if (ct >= col_tiles || a >= gk.nviews || band >= bands) return;   // whole workgroups
-    }
+    if (!fp_block(tb, vb, views_pad, tiles_per_xcd_pad, col_tiles, gk.nviews, bands, ct, band, a)) return;   // whole workgroups
     const int c = ct * WAVES + wave;
     const SfGeom &g = MOD ? geoms[a] : gk;
     const int band0 = band * ROWS;
@@ -294,7 +283,6 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
     __syncthreads();
     const bool w0 = live_waves[0], w1 = live_waves[1], w2 = live_waves[2], w3 = live_waves[3];
     if (!(w0 | w1 | w2 | w3)) return;
-    struct __attribute__((packed, aligned(4))) Quad { float a, b, c, d; };
     float *__restrict__ ya = sino + (size_t)a * g.nrows * g.ncols + (size_t)ct * WAVES;
 #pragma unroll
     for (int row = threadIdx.x; row < ROWS; row += 256) {
@@ -303,12 +291,7 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
         const float4 v = out[row];
         float *__restrict__ dst = ya + (size_t)r * g.ncols;
         if (w0 & w1 & w2 & w3) {
-            Quad q = {v.x, v.y, v.z, v.w};
-            if (!slab.first) {
-                const Quad old = *reinterpret_cast<const Quad *>(dst);
-                q.a += old.a; q.b += old.b; q.c += old.c; q.d += old.d;
-            }
-            *reinterpret_cast<Quad *>(dst) = q;
+            fp_store_four(dst, v.x, v.y, v.z, v.w, slab.first);
         } else {
             if (w0) dst[0] = slab.first ? v.x : dst[0] + v.x;
             if (w1) dst[1] = slab.first ? v.y : dst[1] + v.y;
@@ -333,21 +316,8 @@ __global__ __launch_bounds__(SD_WAVES * 64) void sd_project_columns(SfGeom gk, c
     sino += (size_t)blockIdx.y * gk.nviews * gk.nrows * gk.ncols;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // Block -> (view, band, column tile), in the XCD-aware order of the footprint kernel: index = 8 s + xcd, and
-    // within an XCD's sequence s the view runs fastest inside a block of VB views, then TB tiles, then blocks of views.
     int ct, band, a;
-    {
-        const int xcd = blockIdx.x & 7, sq = blockIdx.x >> 3;
-        const int per_chunk = tb * views_pad;
-        const int chunk = sq / per_chunk, r = sq - chunk * per_chunk;
-        const int vblk = r / (tb * vb), r2 = r - vblk * (tb * vb);
-        const int tloc = r2 / vb, v_in = r2 - tloc * vb;
-        const int tchunks = tiles_per_xcd_pad / tb;
-        band = chunk / tchunks;
-        ct = ((chunk - band * tchunks) * tb + tloc) * 8 + xcd;
-        a = vblk * vb + v_in;
-        if (ct >= col_tiles || a >= gk.nviews || band >= bands) return;   // padding blocks (no barrier follows)
-    }
+    if (!fp_block(tb, vb, views_pad, tiles_per_xcd_pad, col_tiles, gk.nviews, bands, ct, band, a)) return;   // padding blocks (no barrier follows)
     const int c = ct * SD_WAVES + wave;
     if (c >= gk.ncols) return;
     const SfGeom &g = MOD ? geoms[a] : gk;

@@ -275,6 +275,37 @@ __global__ __launch_bounds__(256) void sf_clear_column_pads(float *__restrict__ 
     if (t < (unsigned)nzp) volz[(size_t)ncolumns * nzp + t] = 0.0f;
 }
 
+// Block -> (column tile, band of rows, view), for every column-wise forward kernel.  Workgroups are handed to the 8 XCDs
+// round-robin by index, and each XCD has its own L2, so the blocks one XCD runs at the same time are arranged as (a few column
+// tiles) x (a run of consecutive views), whose beams overlap almost entirely: index = 8 s + xcd, and within an XCD's sequence s
+// the view runs fastest inside a block of vb views, then tb tiles, then blocks of views.  Returns false for padding blocks.
+__device__ __forceinline__ bool fp_block(int tb, int vb, int views_pad, int tiles_per_xcd_pad, int col_tiles, int nviews, int bands, int &ct,
+                                         int &band, int &a)
+{
+    const int xcd = blockIdx.x & 7, sq = blockIdx.x >> 3;
+    const int per_chunk = tb * views_pad;                   // tb tiles x all (padded) views
+    const int chunk = sq / per_chunk, r = sq - chunk * per_chunk;
+    const int vblk = r / (tb * vb), r2 = r - vblk * (tb * vb);
+    const int tloc = r2 / vb, v_in = r2 - tloc * vb;
+    const int tchunks = tiles_per_xcd_pad / tb;
+    band = chunk / tchunks;
+    ct = ((chunk - band * tchunks) * tb + tloc) * 8 + xcd;
+    a = vblk * vb + v_in;
+    return ct < col_tiles && a < nviews && band < bands;
+}
+
+// Writes a row's samples of four adjacent columns together (first), or adds them to what is there.
+__device__ __forceinline__ void fp_store_four(float *__restrict__ dst, float a, float b, float c, float d, bool first)
+{
+    struct __attribute__((packed, aligned(4))) Quad { float a, b, c, d; };
+    Quad q = {a, b, c, d};
+    if (!first) {
+        const Quad old = *reinterpret_cast<const Quad *>(dst);
+        q.a += old.a; q.b += old.b; q.c += old.c; q.d += old.d;
+    }
+    *reinterpret_cast<Quad *>(dst) = q;
+}
+
 constexpr int FP_WAVES = 4;      // waves per workgroup: adjacent column bundles of one view (each wave its own LDS, no barrier)
 
 // NKP: voxels a pair of adjacent rows can overlap (2 .. FP_MAX_P); RG: groups of 128 rows per wave; CW: adjacent detector
@@ -300,23 +331,8 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG <= 2 ? 4 : 3) : 1) voi
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // Block -> (view, band, column tile).  Workgroups are handed to the 8 XCDs round-robin by index, and each XCD has
-    // its own L2, so the blocks one XCD runs at the same time are arranged as (a few column tiles) x (a run of
-    // consecutive views), whose beams overlap almost entirely: index = 8 s + xcd, and within an XCD's sequence s the
-    // view runs fastest inside a block of VB views, then TB tiles, then blocks of views.
     int ct, band, a;
-    {
-        const int xcd = blockIdx.x & 7, sq = blockIdx.x >> 3;
-        const int per_chunk = tb * vgroups_pad;                 // TB tiles x all (padded) views
-        const int chunk = sq / per_chunk, r = sq - chunk * per_chunk;
-        const int vblk = r / (tb * vb), r2 = r - vblk * (tb * vb);
-        const int tloc = r2 / vb, v_in = r2 - tloc * vb;
-        const int tchunks = tiles_per_xcd_pad / tb;
-        band = chunk / tchunks;
-        ct = ((chunk - band * tchunks) * tb + tloc) * 8 + xcd;
-        a = vblk * vb + v_in;
-        if (ct >= col_tiles || a >= gsz.nviews || band >= bands) return;   // padding blocks and padding views (no barrier follows)
-    }
+    if (!fp_block(tb, vb, vgroups_pad, tiles_per_xcd_pad, col_tiles, gsz.nviews, bands, ct, band, a)) return;   // (no barrier follows)
     const int bundle = ct * FP_WAVES + wave;
     const int c0 = bundle * CW;                          // first detector column of this wave
     if (c0 >= gsz.ncols) return;
@@ -472,7 +488,6 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG <= 2 ? 4 : 3) : 1) voi
 #pragma unroll
     for (int cw = 0; cw < CW; ++cw) ac[cw] = sf_amp_col<GT>(g, v, c0 + cw < g.ncols ? c0 + cw : g.ncols - 1);
     struct __attribute__((packed, aligned(4))) Pair { float lo, hi; };
-    struct __attribute__((packed, aligned(4))) Quad { float a, b, c, d; };
 #pragma unroll
     for (int gq = 0; gq < RG; ++gq) {
 #pragma unroll
@@ -497,13 +512,7 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG <= 2 ? 4 : 3) : 1) voi
             }
             if constexpr (CW == 4) {
                 if (c0 + 3 < g.ncols) {
-                    Quad qd;
-                    if (!slab.first) {
-                        qd = *reinterpret_cast<const Quad *>(dst);
-                        out[0] += qd.a; out[1] += qd.b; out[2] += qd.c; out[3] += qd.d;
-                    }
-                    qd.a = out[0]; qd.b = out[1]; qd.c = out[2]; qd.d = out[3];
-                    *reinterpret_cast<Quad *>(dst) = qd;
+                    fp_store_four(dst, out[0], out[1], out[2], out[3], slab.first);
                     continue;
                 }
             }

@@ -85,18 +85,7 @@ __global__ __launch_bounds__(FP_WAVES * 64) void sf_project_rows(SfGeom g, const
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
-    {   // block -> (view, band, column tile) in the XCD-aware order of sf_project_columns
-        const int xcd = blockIdx.x & 7, sq = blockIdx.x >> 3;
-        const int per_chunk = tb * vgroups_pad;
-        const int chunk = sq / per_chunk, r = sq - chunk * per_chunk;
-        const int vblk = r / (tb * vb), r2 = r - vblk * (tb * vb);
-        const int tloc = r2 / vb, v_in = r2 - tloc * vb;
-        const int tchunks = tiles_per_xcd_pad / tb;
-        band = chunk / tchunks;
-        ct = ((chunk - band * tchunks) * tb + tloc) * 8 + xcd;
-        a = vblk * vb + v_in;
-        if (ct >= col_tiles || a >= g.nviews || band >= bands) return;      // (no barrier follows)
-    }
+    if (!fp_block(tb, vb, vgroups_pad, tiles_per_xcd_pad, col_tiles, g.nviews, bands, ct, band, a)) return;      // (no barrier follows)
     const int bundle = ct * FP_WAVES + wave, c0 = bundle * CW;
     if (c0 >= g.ncols) return;
     const int nbundles = (g.ncols + CW - 1) / CW;
@@ -185,7 +174,6 @@ __global__ __launch_bounds__(FP_WAVES * 64) void sf_project_rows(SfGeom g, const
 
     // ---- amplitude and store: CW consecutive floats per row, written together
     float *__restrict__ ya = sino + (size_t)a * g.nrows * g.ncols;
-    struct __attribute__((packed, aligned(4))) Quad { float a, b, c, d; };
 #pragma unroll
     for (int gq = 0; gq < RG; ++gq)
 #pragma unroll
@@ -195,12 +183,8 @@ __global__ __launch_bounds__(FP_WAVES * 64) void sf_project_rows(SfGeom g, const
             float *__restrict__ dst = ya + (size_t)r * g.ncols + c0;
             if constexpr (CW == 4) {
                 if (c0 + 3 < g.ncols) {
-                    Quad qd = {v.par_amp * acc[0][gq][t], v.par_amp * acc[1][gq][t], v.par_amp * acc[2][gq][t], v.par_amp * acc[3][gq][t]};
-                    if (!slab.first) {
-                        const Quad old = *reinterpret_cast<const Quad *>(dst);
-                        qd.a += old.a; qd.b += old.b; qd.c += old.c; qd.d += old.d;
-                    }
-                    *reinterpret_cast<Quad *>(dst) = qd;
+                    fp_store_four(dst, v.par_amp * acc[0][gq][t], v.par_amp * acc[1][gq][t], v.par_amp * acc[2][gq][t],
+                                  v.par_amp * acc[3][gq][t], slab.first);
                     continue;
                 }
             }
