@@ -36,8 +36,8 @@ MEASURED_TRAFFIC = {
     ("c3_cone_512", "AT"): {"instance": "AT=tiled(nc=3,nv=2,zc=64,window=24x63)", "launches": 1,
                             "fetch_bytes": 6.36848e6 * 2048, "write_bytes": 524288 * 1024,
                             "source": "profiles/sf_backproject_tiled_c3_cone_512.md"},
-    ("c2_parallel3d_256", "A"): {"instance": "A=columns(nq=8/8,nkp=3,rg=2,cw=4,slab=256)", "launches": 2,
-                                 "fetch_bytes": 1.72456e6 * 2048, "write_bytes": 72767 * 1024,
+    ("c2_parallel3d_256", "A"): {"instance": "A=columns(nq=8/8,nkp=3,rg=2,cw=4,slab=256,rows)", "launches": 1,
+                                 "fetch_bytes": 2.08085e6 * 2048, "write_bytes": 152964 * 1024,
                                  "source": "profiles/sf_pair_c2_parallel_256.md"},
     ("c2_parallel3d_256", "AT"): {"instance": "AT=tiled(nc=3,nv=2,zc=64,window=25x67)", "launches": 1,
                                   "fetch_bytes": 178849 * 2048, "write_bytes": 65536 * 1024,
@@ -54,11 +54,11 @@ MEASURED_TRAFFIC = {
     ("c5_cone_1024", "AT"): {"instance": "AT=tiled(nc=3,nv=3,zc=64,window=31x86)", "launches": 1,
                              "fetch_bytes": 7.15103e8 * 2048, "write_bytes": 4.1943e6 * 1024,
                              "source": "profiles/sf_pair_c5_cone_1024.md"},
-    ("c3_cone_512:siddon", "A"): {"instance": "A=columns(rg=8,slab=124)", "launches": 10,
-                                  "fetch_bytes": 8.21501e7 * 2048, "write_bytes": 9.42225e6 * 1024,
-                                  "source": "profiles/sd_project_columns_c3_cone_512.md"},
+    ("c3_cone_512:siddon", "A"): {"instance": "A=columns(rg=8,slab=124,pairs apart)", "launches": 10,
+                                  "fetch_bytes": 6.87755e7 * 2048, "write_bytes": 8.48188e6 * 1024,
+                                  "source": "profiles/sd_project_pairs_c3_cone_512.md"},
     ("c3_cone_512:siddon", "AT"): {"instance": "AT=tiled(nc=2,zc=32,window=21x32)", "launches": 1,
-                                   "fetch_bytes": 2.19946e7 * 2048, "write_bytes": 524288 * 1024,
+                                   "fetch_bytes": 2.05427e7 * 2048, "write_bytes": 524288 * 1024,
                                    "source": "profiles/sd_backproject_tiled_c3_cone_512.md"},
 }
 

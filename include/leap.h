@@ -26,8 +26,9 @@
  *     volume through a z-fastest scratch copy, one SLAB of the volume at a time, so the handle
  *     owns a scratch of at most max(64 MiB, an eighth of one volume) -- leap_geometry_describe
  *     reports its size as "scratch=<bytes>"; small volumes share it between the items of a batch.
- *     Flat scans (one row, one layer) keep room for a copy of up to 16 slices instead, which
- *     leap_project uses for batches outside stream capture.
+ *     Flat scans (one row, one layer) keep room for a copy of up to 16 slices (128 MiB at most)
+ *     instead, which leap_project uses for batches outside stream capture; it is allocated with
+ *     the handle, because a call may arrive while another stream is being captured.
  *     If it cannot be allocated the handle works without it on a slower kernel, says so in
  *     leap_last_error at creation and in a "note=" of leap_geometry_describe.  A
  *     LEAP_MODEL_SIDDON handle also keeps a table of 48 bytes per (view, detector column): the
@@ -65,8 +66,9 @@ extern "C" {
  * the module's own axes: the trapezoid's knots are the column coordinates of the central projections, from the source
  * onto the module's plane, of the voxel's four in-plane corners at the height of its centre; the axial interval lies
  * between the row coordinates of the central projections of the centres of its lower and upper face; the amplitude is
- * T |D| / max(|Dx|, |Dy|) with D = pixel - source.  A scan with one such module runs on one thread per few rays / per voxel
- * in double precision.  It needs the whole volume in front of every source (on the module's side of the plane through
+ * T |D| / max(|Dx|, |Dy|) with D = pixel - source.  A scan with one such module runs in double
+ * precision: on tiled kernels, or on one thread per few rays / per voxel where those do not apply (modules seen from above,
+ * voxels that cover many pixels).  It needs the whole volume in front of every source (on the module's side of the plane through
  * the source parallel to the module) and no pixel whose ray runs along z, else LEAP_BAD_GEOMETRY; a source so close to
  * the volume that the nearest voxel's footprint spans more than 64 pixels is LEAP_UNSUPPORTED. */
 enum { LEAP_PARALLEL = 0, LEAP_FAN = 1, LEAP_CONE = 2, LEAP_CONE_CURVED = 3, LEAP_MODULAR = 4 };
@@ -78,7 +80,8 @@ enum { LEAP_MODEL_SF = 0, LEAP_MODEL_SIDDON = 1 };
 
 enum {
     LEAP_OK = 0,
-    LEAP_INVALID_ARG = -1,   /* null pointer, non-positive size or count, unknown type or model, FAN with nrows != 1 or nz != 1 */
+    LEAP_INVALID_ARG = -1,   /* null pointer, non-positive size or count, unknown type or model, FAN with nrows != 1 or nz != 1;
+                                leap_geometry_create also where host memory runs out */
     LEAP_BAD_GEOMETRY = -2,  /* cone/fan: source not strictly outside the volume's bounding circle, sdd <= 0, curved fan wider than +-1.5 rad;
                                 modular: a source inside the volume, a module with no footprints (see LEAP_MODULAR) */
     LEAP_HIP_ERROR = -3,     /* a HIP runtime call failed (the message is kept, see leap_last_error) */
@@ -180,7 +183,8 @@ const char *leap_last_error(void);
 
 /* Which kernel family the handle dispatches to: writes up to `cap` bytes of a short NUL-terminated
  * description (for logs and benchmarks): "A=..." and "AT=..." name the forward and the back projection kernel and
- * their instance, "scratch=<bytes>" the device memory the handle owns beyond its tables, "note=..." anything that went
+ * their instance ("general": plain loop nests over the caller's arrays; "general(flat...)", "general(tiles)" and
+ * "general(tiled)" are the fast kernels of flat scans and of footprints on tilted modules, which read those arrays too), "scratch=<bytes>" the device memory the handle owns beyond its tables, "note=..." anything that went
  * differently from the plan at creation.  Returns LEAP_OK or LEAP_INVALID_ARG.
  *
  * Debugging aid: the environment variable LEAP_DEBUG, read by leap_geometry_create, overrides the choices shown

@@ -19,7 +19,7 @@
 // wave, whose LDS operations execute in order: the sums do not depend on scheduling.
 //
 // Measured at 128^3 x 720 views x 128^2 against one thread per voxel / per eight rows of a column (md_footprint.h): A 60.4 ->
-// 13.2 ms, A^T 22.0 -> 7.4 ms, the same bits but for the last.  (Forward tiles of 32 x 32 pixels, with 16 x 4 or 8 x 8 lanes: 15.7 and
+// 13.0 ms, A^T 22.0 -> 7.4 ms, the same bits but for the last.  (Forward tiles of 32 x 32 pixels, with 16 x 4 or 8 x 8 lanes: 15.7 and
 // 15.0 ms; fewer than six voxels per lane along z pay too often for starting a column.)
 #pragma once
 

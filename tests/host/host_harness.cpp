@@ -19,6 +19,8 @@
 #define SF_NO_KERNELS
 #include "../../paper_2307_05801_amd/csrc/sf_backproject_tiled.h"
 #include "../../paper_2307_05801_amd/csrc/sf_project_columns.h"
+#include "../../paper_2307_05801_amd/csrc/sf_project_rows.h"
+#include "../../paper_2307_05801_amd/csrc/sf_flat.h"
 #include "../../paper_2307_05801_amd/csrc/md_project_columns.h"
 #include "../../paper_2307_05801_amd/csrc/md_backproject_tiled.h"
 #include "../../paper_2307_05801_amd/csrc/md_footprint_tiled.h"
@@ -845,4 +847,117 @@ extern "C" long host_mf_project_tiles(const leap_geometry *G, const float *vol, 
                     sino[((size_t)a * g.nrows + r) * g.ncols + c] = (float)(sums[(size_t)(r - r0 + MF_TG) * MF_TS + c - c0 + MF_TG] * mf_amp(g, V, r, c));
         }
     return beside;
+}
+
+// ---- parallel beams by detector rows: the copy's row overlaps, then the candidates' transaxial weights -------------------------
+// Returns -1 when the handle does not use that kernel, else the number of (view, bundle, slab) cases in which the candidate slots do
+// not cover the candidate range.
+template <int CW>
+static long host_rows(const leap_geometry *G, const std::vector<float> &rows, float *sino)
+{
+    const SfGeom &g = G->g;
+    const int nbundles = (g.ncols + CW - 1) / CW;
+    long uncovered = 0;
+#pragma omp parallel for collapse(2) reduction(+ : uncovered)
+    for (int a = 0; a < g.nviews; ++a)
+        for (int b = 0; b < nbundles; ++b) {
+            const SfView v = G->views[a];
+            const int c0 = b * CW, xmajor = G->major[(size_t)a * nbundles + b];
+            const SfRayLines L = sf_ray_lines<0>(g, v, c0, CW, xmajor);
+            const int n_major = xmajor ? g.nx : g.ny, n_minor = xmajor ? g.ny : g.nx;
+            std::vector<float> acc((size_t)g.nrows * CW, 0.f);
+            for (int n = 0; n < n_major; ++n) {
+                int qf, ql;
+                sf_candidates(L, n, qf, ql);
+                if (ql - qf + 1 > G->fp_nq) ++uncovered;
+                for (int q = std::max(qf, 0); q <= std::min(std::min(ql, qf + G->fp_nq - 1), n_minor - 1); ++q) {
+                    const int i = xmajor ? n : q, j = xmajor ? q : n;
+                    float fa[CW];
+                    double mu;
+                    if (!sf_candidate_record<CW, 0>(g, v, i, j, c0, true, fa, mu)) continue;
+                    const float *x = &rows[((size_t)j * g.nx + i) * g.nrows];
+                    for (int r = 0; r < g.nrows; ++r)
+                        for (int cw = 0; cw < CW; ++cw)
+                            if (fa[cw] != 0.0f) acc[(size_t)r * CW + cw] = fmaf(fa[cw], x[r], acc[(size_t)r * CW + cw]);
+                }
+            }
+            for (int cw = 0; cw < CW && c0 + cw < g.ncols; ++cw)
+                for (int r = 0; r < g.nrows; ++r) sino[((size_t)a * g.nrows + r) * g.ncols + c0 + cw] = v.par_amp * acc[(size_t)r * CW + cw];
+        }
+    return uncovered;
+}
+
+extern "C" long host_project_rows(const leap_geometry *G, const float *vol, float *sino)
+{
+    const SfGeom &g = G->g;
+    if (!G->fp_rows) return -1;
+    std::vector<float> rows((size_t)g.nx * g.ny * g.nrows, 0.f);
+    for (int r = 0; r < g.nrows; ++r) {
+        const SfRowOverlap o = sf_row_overlap(g, r);
+        for (int t = 0; t < o.n; ++t) {
+            const int k = o.kb + t;
+            const float w = sf_row_weight(o, t);
+            if (k < 0 || k >= g.nz || !(w > 0.0f)) continue;
+            for (size_t ij = 0; ij < (size_t)g.nx * g.ny; ++ij) rows[ij * g.nrows + r] = fmaf(w, vol[(size_t)k * g.nx * g.ny + ij], rows[ij * g.nrows + r]);
+        }
+    }
+    return G->fp_cw == 2 ? host_rows<2>(G, rows, sino) : host_rows<4>(G, rows, sino);
+}
+
+// ---- flat scans: a wave's records per slab, a thread's columns in the staged window ---------------------------------------------
+// report[0]: candidate voxels that the wave's outermost columns do not bound or the records do not hold; report[1]: columns read
+// outside the 64 staged ones.  Returns -1 when the handle does not use these kernels.
+extern "C" long host_flat(const leap_geometry *G, const float *vol, float *sino, const float *sino_in, float *vol_out, int64_t *report)
+{
+    const SfGeom &g = G->g;
+    if (!G->flat) return -1;
+    int64_t beyond = 0, outside = 0;
+    const int tiles = (g.ncols + FLAT_RAYS - 1) / FLAT_RAYS;
+#pragma omp parallel for collapse(2) reduction(+ : beyond)
+    for (int a = 0; a < g.nviews; ++a)
+        for (int t = 0; t < tiles; ++t) {
+            const SfView &v = G->views[a];
+            const int c0 = t * FLAT_RAYS, c1 = std::min(c0 + FLAT_RAYS, g.ncols) - 1, xmajor = sf_flat_xmajor(g, v, c0);
+            const int n_major = xmajor ? g.nx : g.ny, n_minor = xmajor ? g.ny : g.nx;
+            for (int c = c0; c <= c1; ++c) {
+                const SfRayLines L = sf_ray_lines<0>(g, v, c, 1, xmajor), L0 = sf_ray_lines<0>(g, v, c0, 1, xmajor), L1 = sf_ray_lines<0>(g, v, c1, 1, xmajor);
+                float acc = 0.f;
+                for (int n = 0; n < n_major; ++n) {
+                    int qf, ql, f0, l0, f1, l1;
+                    sf_candidates(L, n, qf, ql);
+                    sf_candidates(L0, n, f0, l0);
+                    sf_candidates(L1, n, f1, l1);
+                    const int q_lo = std::max(std::min(f0, f1), 0), q_hi = std::min(std::max(l0, l1), n_minor - 1);
+                    if (q_hi - q_lo + 1 > G->flat_span) ++beyond;
+                    for (int q = std::max(qf, 0); q <= std::min(ql, n_minor - 1); ++q) {
+                        const int i = xmajor ? n : q, j = xmajor ? q : n;
+                        const float fu = sf_flat_fu(sf_flat_record(sf_column<0>(g, v, i, j)), c);
+                        if (!(fu > 0.0f)) continue;
+                        if (q < q_lo || q > q_hi) ++beyond;
+                        acc = fmaf(fu, vol[(size_t)j * g.nx + i], acc);
+                    }
+                }
+                sino[(size_t)a * g.ncols + c] = sf_amp(g, v, sf_amp_col<0>(g, v, c), 0) * G->flat_fv * acc;
+            }
+        }
+#pragma omp parallel for collapse(2) reduction(+ : outside)
+    for (int j = 0; j < g.ny; ++j)
+        for (int i = 0; i < g.nx; ++i) {
+            const int tx = i / FLAT_T, ty = j / FLAT_T;
+            float acc = 0.f;
+            for (int a = 0; a < g.nviews; ++a) {
+                const SfView &v = G->views[a];
+                const SfColumn mid = sf_column<0>(g, v, std::min(tx * FLAT_T + FLAT_T / 2, g.nx - 1), std::min(ty * FLAT_T + FLAT_T / 2, g.ny - 1));
+                const int first = (int)floor(mid.xi) - 32;
+                const SfColumn f = sf_column<0>(g, v, i, j);
+                int cf, cl;
+                sf_col_range(f, cf, cl);
+                if (cf < first || cf + FLAT_NC - 1 >= first + 64 || cl - cf >= FLAT_NC) ++outside;
+                for (int c = std::max(cf, 0); c <= std::min(cl, g.ncols - 1); ++c)
+                    acc = fmaf(sf_fu(f, c), sino_in[(size_t)a * g.ncols + c] * (sf_amp(g, v, sf_amp_col<0>(g, v, c), 0) * G->flat_fv), acc);
+            }
+            vol_out[(size_t)j * g.nx + i] = acc;
+        }
+    report[0] = beyond; report[1] = outside;
+    return beyond + outside;
 }

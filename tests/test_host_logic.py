@@ -49,6 +49,9 @@ def host():
     lib.host_mf_backproject_tiled.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(C.c_int64)]
     lib.host_mf_project_tiles.restype = C.c_long
     lib.host_mf_project_tiles.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
+    lib.host_project_rows.restype = lib.host_flat.restype = C.c_long
+    lib.host_project_rows.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
+    lib.host_flat.argtypes = [C.c_void_p] * 5 + [C.POINTER(C.c_int64)]
     lib.host_sd_project_pairs.restype = C.c_long
     lib.host_sd_project_pairs.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p]
     lib.host_sd_backproject_tiled.restype = C.c_long
@@ -939,3 +942,34 @@ def test_forward_tiles_of_tilted_footprints_are_left_where_voxels_cover_many_pix
     desc = B.leap_geometry_describe(h, host)
     B.leap_geometry_destroy(h, host)
     assert ("A=general(tiles)" in desc) == tiles, desc
+
+
+@pytest.mark.parametrize("nrows,pixel_v,nz,kw", [(32, 1.9, 57, {}), (65, 0.9, 57, {}), (200, 0.31, 57, {}), (40, 2.9, 110, {}),
+                                                 (90, 1.3, 57, dict(shift_v=60.0)), (64, 1.0, 64, dict(shift_v=0.0, center_z=0.0))])
+def test_projection_by_rows_matches_oracle_on_cpu(host, oracle_mod, nrows, pixel_v, nz, kw):
+    cfg = CTConfig("rows", PARALLEL, nviews=7, arc_deg=180.0, nrows=nrows, ncols=75, pixel_v=pixel_v, pixel_u=1.1, nx=41, ny=50, nz=nz,
+                   voxel_xy=1.0, voxel_z=1.0, shift_u=0.3, shift_v=-0.4, center_x=1.0, center_y=-2.0, center_z=0.5, start_deg=3.0).replace(**kw)
+    x = uniform_volume(cfg, 3)[0]
+    h = handle(host, cfg)
+    ax = np.zeros(cfg.sino_shape, np.float32)
+    bad = host.host_project_rows(h, x.ctypes.data, ax.ctypes.data)
+    B.leap_geometry_destroy(h, host)
+    assert bad == 0
+    assert np.linalg.norm(ax - oracle_mod.project(cfg, x)) <= 1e-6 * np.linalg.norm(oracle_mod.project(cfg, x))
+
+
+@pytest.mark.parametrize("geom,nx,ny,ncols,pixel_u,kw", [
+    (FAN, 65, 71, 65, 1.3, {}), (FAN, 9, 7, 63, 1.3, {}), (FAN, 100, 90, 200, 1.4, dict(sod=150.0, sdd=260.0)), (FAN, 40, 40, 200, 0.55, {}),
+    (FAN, 48, 48, 96, 3.9, {}), (PARALLEL, 17, 66, 64, 0.4, {}), (PARALLEL, 90, 50, 70, 2.2, {}), (PARALLEL, 30, 31, 40, 1.1, dict(voxel_z=0.6, shift_v=0.4))])
+def test_flat_kernels_match_oracle_on_cpu(host, oracle_mod, geom, nx, ny, ncols, pixel_u, kw):
+    fan = dict(sod=400.0, sdd=700.0) if geom == FAN else {}
+    cfg = CTConfig("flat", geom, nviews=23, arc_deg=360.0, nrows=1, ncols=ncols, pixel_v=1.0, pixel_u=pixel_u, nx=nx, ny=ny, nz=1, voxel_xy=1.0,
+                   voxel_z=1.0, start_deg=11.0, shift_u=0.3, center_x=0.7, center_y=-1.1).replace(**fan).replace(**kw)
+    x, y = uniform_volume(cfg, 3)[0], uniform_sinogram(cfg, 4)[0]
+    h = handle(host, cfg)
+    ax, aty, rep = np.zeros(cfg.sino_shape, np.float32), np.zeros(cfg.vol_shape, np.float32), (C.c_int64 * 2)()
+    bad = host.host_flat(h, x.ctypes.data, ax.ctypes.data, y.ctypes.data, aty.ctypes.data, rep)
+    B.leap_geometry_destroy(h, host)
+    assert bad == 0, (bad, list(rep))
+    for got, want in ((ax, oracle_mod.project(cfg, x)), (aty, oracle_mod.backproject(cfg, y))):
+        assert np.linalg.norm(got - want) <= 2e-6 * np.linalg.norm(want)
