@@ -238,20 +238,27 @@ extern "C" int host_check_backproject_windows(const leap_geometry *G, int64_t *r
 // ---- tiled back projection: who stages what ----------------------------------------------------------------------
 // Number of cells of any shape's window that are not written by exactly one (thread, step) of a workgroup: a cell without a
 // writer holds another view's sample, one with two writers in different steps is written without an order between them.
+template <int SH>
+static long host_staging_roles()
+{
+    constexpr SfBpShape S = BP_SHAPES[SH];
+    constexpr int step = 256 / S.pw, nstage = (S.ph + step - 1) / step;
+    std::vector<int> writers((size_t)S.ph * S.pw, 0);
+    for (int tid = 0; tid < 256; ++tid)
+        for (int s = 0; s < nstage; ++s) {
+            const int row = sf_stage_row<S.pw, S.ph>(tid) + step * s;
+            if (row < S.ph) ++writers[(size_t)row * S.pw + sf_stage_column<S.pw>(tid)];
+        }
+    long bad = 0;
+    for (int w : writers) bad += w != 1;
+    return bad;
+}
+
 extern "C" long host_check_staging_roles()
 {
-    long bad = 0;
-    for (const SfBpShape &S : BP_SHAPES) {
-        const int step = 256 / S.pw, nstage = (S.ph + step - 1) / step;
-        std::vector<int> writers((size_t)S.ph * S.pw, 0);
-        for (int tid = 0; tid < 256; ++tid) {
-            const SfStageRole role = sf_stage_role(tid, S.pw, S.ph);
-            for (int s = 0; s < nstage; ++s)
-                if (role.sr + step * s < S.ph) ++writers[(size_t)(role.sr + step * s) * S.pw + role.sc];
-        }
-        for (int w : writers) bad += w != 1;
-    }
-    return bad;
+    static_assert(BP_NSHAPES == 7, "every shape is checked");
+    return host_staging_roles<0>() + host_staging_roles<1>() + host_staging_roles<2>() + host_staging_roles<3>() + host_staging_roles<4>() +
+           host_staging_roles<5>() + host_staging_roles<6>();
 }
 
 // ---- cylinder: the tile-relative column function of the tiled kernel against the general one ------------------------
