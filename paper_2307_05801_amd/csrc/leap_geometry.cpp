@@ -270,9 +270,11 @@ static void select_footprint_tiled(leap_geometry *G)
     if (d->nz >= 128 && G->bp_nv == 2) order[norder++] = 0;
     if (d->nz >= 128 && G->bp_nv <= 3) order[norder++] = BP_TALL_SHAPE;
     // The wide window's 32 voxels per thread: for voxels of up to a row and a half (taller ones are limited by LDS reads), where
-    // it leaves the chip at least two workgroups per compute unit and no more than a fifth of the layers as padding.
+    // it leaves the chip's 256 compute units 700 workgroups and no more than a fifth of the layers as padding.  60 views, 16 voxels'
+    // time over 32's: 500 to 605 workgroups 0.87 to 1.13 (below 1 on flat detectors), 720 to 845 1.12 to 1.35, 1092 0.98 to 1.12, 1280 to
+    // 2048 1.04 to 1.34.
     const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T), chunks32 = (d->nz + 31) / 32;
-    const bool wide = G->bp_nv <= 3 && mr <= 1.5 && (G->bp_nc == 3 || G->bp_nc == 4) && tiles * chunks32 >= 512 && 160 * chunks32 <= 6 * d->nz;
+    const bool wide = G->bp_nv <= 3 && mr <= 1.5 && (G->bp_nc == 3 || G->bp_nc == 4) && tiles * chunks32 >= 700 && 160 * chunks32 <= 6 * d->nz;
     for (int sh = BP_FIRST_SHORT_SHAPE; sh <= BP_LAST_SHORT_SHAPE; ++sh) {
         if (wide && sh == 3) order[norder++] = BP_WIDE_SHAPE;        // before the 16-voxel shapes
         order[norder++] = sh;

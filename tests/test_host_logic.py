@@ -973,3 +973,15 @@ def test_flat_kernels_match_oracle_on_cpu(host, oracle_mod, geom, nx, ny, ncols,
     assert bad == 0, (bad, list(rep))
     for got, want in ((ax, oracle_mod.project(cfg, x)), (aty, oracle_mod.backproject(cfg, y))):
         assert np.linalg.norm(got - want) <= 2e-6 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("nx,ny,nz,wide", [(157, 167, 140, False), (176, 176, 160, False), (192, 192, 160, True), (211, 187, 149, True),
+                                           (192, 192, 133, False)])
+def test_wide_windows_need_enough_workgroups(host, nx, ny, nz, wide):
+    """550, 605, 720 and 840 workgroups of 32 voxels per thread; 720 with a sixth of the layers as padding."""
+    cfg = CTConfig("w", CONE, nviews=8, arc_deg=360.0, nrows=int(1.3 * nz), ncols=int(1.5 * nx), pixel_v=1.45, pixel_u=1.5, nx=nx, ny=ny, nz=nz,
+                   voxel_xy=1.0, voxel_z=1.0, sod=2.2 * nx, sdd=3.08 * nx, start_deg=3.0)
+    h = handle(host, cfg)
+    desc = B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
+    assert ("zc=32,wide" in desc) == wide, desc
