@@ -1,0 +1,71 @@
+// Launchers of the tiled footprint back projection.
+#include <hip/hip_runtime.h>
+
+#include "leap_internal.h"
+#include "sf_backproject_tiled.h"
+
+template <int NC, int NV, int SH, int GT>
+static void launch_bp_tiled_gt(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
+{
+    constexpr SfBpShape S = BP_SHAPES[SH];
+    const SfGeom &g = G->g;
+    const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
+    dim3 grid(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)items);
+    hipLaunchKernelGGL((sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, GT>), grid, dim3(256, 1, 1), 0, stream, g, G->d_views,
+                       d_sino, d_vol, (int)tiles_x, G->bp_wh, GT == 1 ? (const void *)G->d_colcs : (const void *)G->d_geoms);
+}
+
+template <int NC, int NV, int SH>
+static bool launch_bp_instance(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
+{
+    if constexpr (bp_instance_exists(NC, NV, SH)) {
+        if (G->g.type == SF_CONE_CURVED) launch_bp_tiled_gt<NC, NV, SH, 1>(G, d_sino, d_vol, stream, items);
+        else if (G->g.type == SF_MODULAR) launch_bp_tiled_gt<NC, NV, SH, 2>(G, d_sino, d_vol, stream, items);
+        else launch_bp_tiled_gt<NC, NV, SH, 0>(G, d_sino, d_vol, stream, items);
+        return true;
+    } else {
+        return false;
+    }
+}
+
+template <int NC, int NV>
+static bool launch_bp_shape(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
+{
+    switch (G->bp_shape) {
+    case 0: return launch_bp_instance<NC, NV, 0>(G, d_sino, d_vol, stream, items);
+    case 1: return launch_bp_instance<NC, NV, 1>(G, d_sino, d_vol, stream, items);
+    case 2: return launch_bp_instance<NC, NV, 2>(G, d_sino, d_vol, stream, items);
+    case 3: return launch_bp_instance<NC, NV, 3>(G, d_sino, d_vol, stream, items);
+    case 4: return launch_bp_instance<NC, NV, 4>(G, d_sino, d_vol, stream, items);
+    case BP_TALL_SHAPE: return launch_bp_instance<NC, NV, BP_TALL_SHAPE>(G, d_sino, d_vol, stream, items);
+    case BP_WIDE_SHAPE: return launch_bp_instance<NC, NV, BP_WIDE_SHAPE>(G, d_sino, d_vol, stream, items);
+    default: return false;
+    }
+}
+
+// The tiled footprint back projection on `items` consecutive sinograms of a batch in one launch.
+int leap_launch_footprint_back(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
+{
+    bool ok = false;
+    switch (G->bp_nc * 10 + G->bp_nv) {
+    case 22: ok = launch_bp_shape<2, 2>(G, d_sino, d_vol, stream, items); break;
+    case 23: ok = launch_bp_shape<2, 3>(G, d_sino, d_vol, stream, items); break;
+    case 32: ok = launch_bp_shape<3, 2>(G, d_sino, d_vol, stream, items); break;
+    case 33: ok = launch_bp_shape<3, 3>(G, d_sino, d_vol, stream, items); break;
+    case 24: ok = launch_bp_shape<2, 4>(G, d_sino, d_vol, stream, items); break;
+    case 34: ok = launch_bp_shape<3, 4>(G, d_sino, d_vol, stream, items); break;
+    case 42: ok = launch_bp_shape<4, 2>(G, d_sino, d_vol, stream, items); break;
+    case 43: ok = launch_bp_shape<4, 3>(G, d_sino, d_vol, stream, items); break;
+    case 44: ok = launch_bp_shape<4, 4>(G, d_sino, d_vol, stream, items); break;
+    case 52: ok = launch_bp_shape<5, 2>(G, d_sino, d_vol, stream, items); break;
+    case 53: ok = launch_bp_shape<5, 3>(G, d_sino, d_vol, stream, items); break;
+    case 54: ok = launch_bp_shape<5, 4>(G, d_sino, d_vol, stream, items); break;
+    default: break;
+    }
+    if (!ok) {
+        leap_set_error("internal: no tiled back-projection instance for this footprint");
+        return LEAP_UNSUPPORTED;
+    }
+    LEAP_HIP_CHECK(hipGetLastError());
+    return LEAP_OK;
+}

@@ -1,0 +1,109 @@
+// Launchers of the column-wise footprint forward kernels.
+#include <hip/hip_runtime.h>
+
+#include "leap_internal.h"
+#include "sf_project_columns.h"
+#include "sf_project_rows.h"
+
+// Two volumes per wave where a batch brings them; an odd last item by itself.
+template <int HC, int RG, int CW, int GT, int NS>
+static void launch_fp_columns(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int first,
+                              int blocks)
+{
+    const SfGeom &g = G->g;
+    const int col_tiles = (int)cdiv(g.ncols, FP_WAVES * CW), bands = (int)cdiv(g.nrows, RG * 128);
+    // XCD-aware block order (see the kernel): pad views to blocks of vb and each XCD's tiles to chunks of tb
+    const int vb = G->fp_vb, tb = G->fp_tb;
+    const int vgroups_pad = (int)cdiv(g.nviews, vb) * vb;
+    const int tiles_per_xcd_pad = (int)cdiv(cdiv(col_tiles, 8), tb) * tb;
+    int nq_log2 = 2;
+    while ((1 << nq_log2) < G->fp_nq) ++nq_log2;
+    dim3 grid((unsigned)(8 * tiles_per_xcd_pad * vgroups_pad * bands), (unsigned)blocks, 1);
+    hipLaunchKernelGGL((sf_project_columns<HC, RG, CW, GT, NS>), grid, dim3(FP_WAVES * 64, 1, 1), 0, stream, g, G->d_views,
+                       S.volz + (size_t)first * S.item_floats, d_sino + (size_t)first * g.nviews * g.nrows * g.ncols, G->d_major, G->nzp,
+                       S.item_floats, nq_log2, col_tiles, bands, vb, tb, vgroups_pad, tiles_per_xcd_pad, slab, (const SfGeom *)G->d_geoms);
+}
+
+template <int HC, int RG, int NS>
+static bool launch_fp_w(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int first, int blocks)
+{
+    const int gt = G->g.type == SF_CONE_CURVED ? 1 : (G->g.type == SF_MODULAR ? 2 : 0);
+    switch (gt * 10 + G->fp_cw) {
+    case 1:
+        if constexpr (NS == 1) {
+            launch_fp_columns<HC, RG, 1, 0, NS>(G, S, slab, d_sino, stream, first, blocks);
+            return true;
+        }
+        return false;
+    case 2: launch_fp_columns<HC, RG, 2, 0, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
+    case 4: launch_fp_columns<HC, RG, 4, 0, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
+    case 12: launch_fp_columns<HC, RG, 2, 1, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
+    case 14: launch_fp_columns<HC, RG, 4, 1, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
+    case 22: launch_fp_columns<HC, RG, 2, 2, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
+    case 24: launch_fp_columns<HC, RG, 4, 2, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
+    default: return false;
+    }
+}
+
+template <int HC, int NS>
+static bool launch_fp_rg(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int first, int blocks)
+{
+    switch (NS == 2 ? G->fp_pair_rg : G->fp_rg) {
+    case 1: return launch_fp_w<HC, 1, NS>(G, S, slab, d_sino, stream, first, blocks);
+    case 2: return launch_fp_w<HC, 2, NS>(G, S, slab, d_sino, stream, first, blocks);
+    case 3: return launch_fp_w<HC, 3, NS>(G, S, slab, d_sino, stream, first, blocks);
+    case 4:
+        if constexpr (NS == 1) return launch_fp_w<HC, 4, NS>(G, S, slab, d_sino, stream, first, blocks);
+        return false;
+    default: return false;
+    }
+}
+
+template <int HC>
+static bool launch_fp_sets(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
+{
+    const int paired = G->fp_pair_rg ? items / 2 * 2 : 0;
+    return (!paired || launch_fp_rg<HC, 2>(G, S, slab, d_sino, stream, 0, paired / 2)) &&
+           (paired == items || launch_fp_rg<HC, 1>(G, S, slab, d_sino, stream, paired, items - paired));
+}
+
+template <int RV, int RG, int CW>
+static void launch_fp_rows(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
+{
+    const SfGeom &g = G->g;
+    const int col_tiles = (int)cdiv(g.ncols, FP_WAVES * CW), bands = (int)cdiv(g.nrows, RG * 64 * RV);
+    const int vb = G->fp_vb, tb = G->fp_tb;
+    const int vgroups_pad = (int)cdiv(g.nviews, vb) * vb;
+    const int tiles_per_xcd_pad = (int)cdiv(cdiv(col_tiles, 8), tb) * tb;
+    int nq_log2 = 2;
+    while ((1 << nq_log2) < G->fp_nq) ++nq_log2;
+    dim3 grid((unsigned)(8 * tiles_per_xcd_pad * vgroups_pad * bands), (unsigned)items, 1);
+    hipLaunchKernelGGL((sf_project_rows<RV, RG, CW>), grid, dim3(FP_WAVES * 64, 1, 1), 0, stream, g, G->d_views, S.volz, d_sino, G->d_major,
+                       G->nzp, S.item_floats, nq_log2, col_tiles, bands, vb, tb, vgroups_pad, tiles_per_xcd_pad, slab);
+}
+
+static bool launch_fp_rows_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
+{
+    switch (G->fp_rows * 100 + G->fp_row_groups * 10 + G->fp_cw) {
+    case 112: launch_fp_rows<1, 1, 2>(G, S, slab, d_sino, stream, items); return true;
+    case 114: launch_fp_rows<1, 1, 4>(G, S, slab, d_sino, stream, items); return true;
+    case 212: launch_fp_rows<2, 1, 2>(G, S, slab, d_sino, stream, items); return true;
+    case 214: launch_fp_rows<2, 1, 4>(G, S, slab, d_sino, stream, items); return true;
+    case 412: launch_fp_rows<4, 1, 2>(G, S, slab, d_sino, stream, items); return true;
+    case 414: launch_fp_rows<4, 1, 4>(G, S, slab, d_sino, stream, items); return true;
+    case 422: launch_fp_rows<4, 2, 2>(G, S, slab, d_sino, stream, items); return true;
+    case 424: launch_fp_rows<4, 2, 4>(G, S, slab, d_sino, stream, items); return true;
+    default: return false;
+    }
+}
+
+bool leap_launch_footprint_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
+{
+    if (G->fp_rows) return launch_fp_rows_slab(G, S, slab, d_sino, stream, items);
+    switch (G->fp_nkp) {                      // highest height class: rows of up to a voxel and a half, two, three
+    case 2: case 3: case 4: return launch_fp_sets<2>(G, S, slab, d_sino, stream, items);
+    case 5: return launch_fp_sets<3>(G, S, slab, d_sino, stream, items);
+    case 6: case 7: return launch_fp_sets<4>(G, S, slab, d_sino, stream, items);
+    default: return false;
+    }
+}

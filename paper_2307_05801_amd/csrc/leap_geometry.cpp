@@ -378,6 +378,7 @@ static void select_footprint_columns(leap_geometry *G)
     G->fp_columns = need <= 16;
     block_order_options(G);
     if (!G->fp_columns) return;
+    if (G->fp_cw >= 2 && !(debug_option("pairs", v) && v == 0)) G->fp_pair_rg = G->fp_rg == 4 ? 2 : G->fp_rg;
     // Parallel beams: the axial overlaps go into the slab copy and a wave's lanes own adjacent rows, as many as it takes for
     // one wave to hold the detector's height, up to 512 rows.  Only where the copy by rows of the whole volume fits either
     // scratch (up to 256^3): a detector of many more rows than the volume has layers would otherwise take narrower slabs.

@@ -40,6 +40,7 @@ struct leap_geometry {
     int fp_rg = 0;                      // row groups per wave (footprints: groups of 128 rows; Siddon: of 64)
     int fp_cw = 4, fp_vb = 128, fp_tb = 1;   // detector columns per wave; block order: views per run, tiles per chunk
     bool fp_columns = false;
+    int fp_pair_rg = 0;                 // row groups per wave with two volumes per wave (0: one volume per wave only)
     int fp_rows = 0;                    // parallel beams: rows per lane of sf_project_rows (0: not used); fp_row_groups groups of 64 of them
     int fp_row_groups = 1;
     bool flat = false;                  // one row, one layer: the kernels of sf_flat.h in both directions
@@ -104,8 +105,22 @@ bool leap_plan_scratch(const leap_geometry *G, size_t floats, int batch, int &wi
 // Frees what the host-memory entry points created on the handle (leap_host.cpp).
 void leap_host_stage_free(leap_geometry *G);
 
+// Where the column-wise forward kernels find their z-fastest copy of a slab: the handle's own scratch, or the library's
+// fixed array (leap_project_static_scratch).
+struct FwdScratch {
+    float *volz;
+    size_t item_floats;     // floats per copy (one per item of a batch in flight): (columns of a slab + 1) * nzp
+    int width;              // voxel layers across the marching axis per slab
+    int items;              // copies
+};
+
+inline unsigned cdiv(unsigned a, unsigned b) { return (a + b - 1) / b; }
+
 // kernel launchers (leap_kernels.hip); one batch item per call
 int leap_launch_project(const leap_geometry *geom, const float *d_vol, float *d_sino, hipStream_t stream);
 int leap_launch_project_batch(const leap_geometry *geom, const float *d_vol, float *d_sino, int batch, hipStream_t stream);
 int leap_launch_backproject(const leap_geometry *geom, const float *d_sino, float *d_vol, hipStream_t stream);
+struct SfSlab;
+bool leap_launch_footprint_slab(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward.hip
+int leap_launch_footprint_back(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                         // leap_footprint_back.hip
 int leap_launch_backproject_batch(const leap_geometry *geom, const float *d_sino, float *d_vol, int batch, hipStream_t stream);

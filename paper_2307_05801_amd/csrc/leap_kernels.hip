@@ -172,18 +172,7 @@ __global__ __launch_bounds__(256) void md_backproject_general(SfGeom g, const Md
     vol[((size_t)k * g.ny + j) * g.nx + i] = md_backproject_voxel(g, poses, sino, i, j, k);
 }
 
-static inline unsigned cdiv(unsigned a, unsigned b) { return (a + b - 1) / b; }
-
 constexpr int SD_WAVES = 4;   // adjacent detector columns per workgroup of the Siddon forward kernel
-
-// Where the column-wise forward kernels find their z-fastest copy of a slab: the handle's own scratch, or the library's
-// fixed array (leap_project_static_scratch).
-struct FwdScratch {
-    float *volz;
-    size_t item_floats;     // floats per copy (one per item of a batch in flight): (columns of a slab + 1) * nzp
-    int width;              // voxel layers across the marching axis per slab
-    int items;              // copies
-};
 
 template <int RG>
 static void launch_sd_columns(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
@@ -367,106 +356,18 @@ static int launch_sd_backproject(const leap_geometry *G, const float *d_sino, fl
     return LEAP_OK;
 }
 
-template <int NKP, int RG, int CW, int GT>
-static void launch_fp_columns(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
-{
-    const SfGeom &g = G->g;
-    const int col_tiles = (int)cdiv(g.ncols, FP_WAVES * CW), bands = (int)cdiv(g.nrows, RG * 128);
-    // XCD-aware block order (see the kernel): pad views to blocks of vb and each XCD's tiles to chunks of tb
-    const int vb = G->fp_vb, tb = G->fp_tb;
-    const int vgroups_pad = (int)cdiv(g.nviews, vb) * vb;
-    const int tiles_per_xcd_pad = (int)cdiv(cdiv(col_tiles, 8), tb) * tb;
-    int nq_log2 = 2;
-    while ((1 << nq_log2) < G->fp_nq) ++nq_log2;
-    dim3 grid((unsigned)(8 * tiles_per_xcd_pad * vgroups_pad * bands), (unsigned)items, 1);
-    hipLaunchKernelGGL((sf_project_columns<NKP, RG, CW, GT>), grid, dim3(FP_WAVES * 64, 1, 1), 0, stream, g, G->d_views, S.volz,
-                       d_sino, G->d_major, G->nzp, S.item_floats, nq_log2, col_tiles, bands, vb, tb, vgroups_pad, tiles_per_xcd_pad,
-                       slab, (const SfGeom *)G->d_geoms);
-}
-
-template <int NKP, int RG>
-static bool launch_fp_w(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
-{
-    const int gt = G->g.type == SF_CONE_CURVED ? 1 : (G->g.type == SF_MODULAR ? 2 : 0);
-    switch (gt * 10 + G->fp_cw) {
-    case 1: launch_fp_columns<NKP, RG, 1, 0>(G, S, slab, d_sino, stream, items); return true;
-    case 2: launch_fp_columns<NKP, RG, 2, 0>(G, S, slab, d_sino, stream, items); return true;
-    case 4: launch_fp_columns<NKP, RG, 4, 0>(G, S, slab, d_sino, stream, items); return true;
-    case 12: launch_fp_columns<NKP, RG, 2, 1>(G, S, slab, d_sino, stream, items); return true;
-    case 14: launch_fp_columns<NKP, RG, 4, 1>(G, S, slab, d_sino, stream, items); return true;
-    case 22: launch_fp_columns<NKP, RG, 2, 2>(G, S, slab, d_sino, stream, items); return true;
-    case 24: launch_fp_columns<NKP, RG, 4, 2>(G, S, slab, d_sino, stream, items); return true;
-    default: return false;
-    }
-}
-
-template <int NKP>
-static bool launch_fp_rg(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
-{
-    switch (G->fp_rg) {
-    case 1: return launch_fp_w<NKP, 1>(G, S, slab, d_sino, stream, items);
-    case 2: return launch_fp_w<NKP, 2>(G, S, slab, d_sino, stream, items);
-    case 3: return launch_fp_w<NKP, 3>(G, S, slab, d_sino, stream, items);
-    case 4: return launch_fp_w<NKP, 4>(G, S, slab, d_sino, stream, items);
-    default: return false;
-    }
-}
-
-template <int RV, int RG, int CW>
-static void launch_fp_rows(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
-{
-    const SfGeom &g = G->g;
-    const int col_tiles = (int)cdiv(g.ncols, FP_WAVES * CW), bands = (int)cdiv(g.nrows, RG * 64 * RV);
-    const int vb = G->fp_vb, tb = G->fp_tb;
-    const int vgroups_pad = (int)cdiv(g.nviews, vb) * vb;
-    const int tiles_per_xcd_pad = (int)cdiv(cdiv(col_tiles, 8), tb) * tb;
-    int nq_log2 = 2;
-    while ((1 << nq_log2) < G->fp_nq) ++nq_log2;
-    dim3 grid((unsigned)(8 * tiles_per_xcd_pad * vgroups_pad * bands), (unsigned)items, 1);
-    hipLaunchKernelGGL((sf_project_rows<RV, RG, CW>), grid, dim3(FP_WAVES * 64, 1, 1), 0, stream, g, G->d_views, S.volz, d_sino, G->d_major,
-                       G->nzp, S.item_floats, nq_log2, col_tiles, bands, vb, tb, vgroups_pad, tiles_per_xcd_pad, slab);
-}
-
-static bool launch_fp_rows_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
-{
-    switch (G->fp_rows * 100 + G->fp_row_groups * 10 + G->fp_cw) {
-    case 112: launch_fp_rows<1, 1, 2>(G, S, slab, d_sino, stream, items); return true;
-    case 114: launch_fp_rows<1, 1, 4>(G, S, slab, d_sino, stream, items); return true;
-    case 212: launch_fp_rows<2, 1, 2>(G, S, slab, d_sino, stream, items); return true;
-    case 214: launch_fp_rows<2, 1, 4>(G, S, slab, d_sino, stream, items); return true;
-    case 412: launch_fp_rows<4, 1, 2>(G, S, slab, d_sino, stream, items); return true;
-    case 414: launch_fp_rows<4, 1, 4>(G, S, slab, d_sino, stream, items); return true;
-    case 422: launch_fp_rows<4, 2, 2>(G, S, slab, d_sino, stream, items); return true;
-    case 424: launch_fp_rows<4, 2, 4>(G, S, slab, d_sino, stream, items); return true;
-    default: return false;
-    }
-}
-
-static bool launch_fp_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
-{
-    if (G->fp_rows) return launch_fp_rows_slab(G, S, slab, d_sino, stream, items);
-    switch (G->fp_nkp) {
-    case 2: return launch_fp_rg<2>(G, S, slab, d_sino, stream, items);
-    case 3: return launch_fp_rg<3>(G, S, slab, d_sino, stream, items);
-    case 4: return launch_fp_rg<4>(G, S, slab, d_sino, stream, items);
-    case 5: return launch_fp_rg<5>(G, S, slab, d_sino, stream, items);
-    case 6: return launch_fp_rg<6>(G, S, slab, d_sino, stream, items);
-    case 7: return launch_fp_rg<7>(G, S, slab, d_sino, stream, items);
-    default: return false;
-    }
-}
-
 // Copies voxel columns [i0, i0 + ni) x [j0, j0 + nj) of `items` volumes into the scratch: z-fastest, or by detector rows.
 static void copy_slab(const leap_geometry *G, const FwdScratch &S, const float *vol, int span, int i0, int j0, int ni, int nj, int items,
                       hipStream_t stream)
 {
     const SfGeom &g = G->g;
-    dim3 tgrid(cdiv(span, 32), cdiv(G->fp_rows ? g.nrows : g.nz, 32), (unsigned)(nj * items));
-    if (G->fp_rows)
-        hipLaunchKernelGGL(sf_volume_to_rows, tgrid, dim3(32, 8, 1), 0, stream, g, vol, S.volz, G->nzp, i0, j0, ni, nj, S.item_floats);
-    else
-        hipLaunchKernelGGL(sf_volume_to_columns, tgrid, dim3(32, 8, 1), 0, stream, vol, S.volz, g.nx, g.ny, g.nz, G->nzp, i0, j0, ni, nj,
-                           S.item_floats);
+    if (G->fp_rows) {
+        hipLaunchKernelGGL(sf_volume_to_rows, dim3(cdiv(span, 32), cdiv(g.nrows, 32), (unsigned)(nj * items)), dim3(32, 8, 1), 0, stream, g, vol,
+                           S.volz, G->nzp, i0, j0, ni, nj, S.item_floats);
+        return;
+    }
+    hipLaunchKernelGGL(sf_volume_to_columns, dim3(cdiv(span, 32), cdiv(g.nz, 32), (unsigned)(nj * items)), dim3(32, 8, 1), 0,
+                       stream, vol, S.volz, g.nx, g.ny, g.nz, G->nzp, i0, j0, ni, nj, S.item_floats);
 }
 
 // The column-wise forward projection (footprint or Siddon weights) of a batch: up to S.items volumes at a time, each
@@ -487,7 +388,7 @@ static int run_forward_columns(const leap_geometry *G, const FwdScratch &S, cons
             // twice and each launch had half the rays to fill the chip with.)
             const SfSlab whole = {0, 0, -1, 1, g.nx};
             copy_slab(G, S, vol, g.nx, 0, 0, g.nx, g.ny, items, stream);
-            const bool ok = siddon ? launch_sd_slab(G, S, whole, sino, stream, items) : launch_fp_slab(G, S, whole, sino, stream, items);
+            const bool ok = siddon ? launch_sd_slab(G, S, whole, sino, stream, items) : leap_launch_footprint_slab(G, S, whole, sino, stream, items);
             if (!ok) {
                 leap_set_error("internal: no column-wise forward instance for this geometry");
                 return LEAP_UNSUPPORTED;
@@ -501,7 +402,7 @@ static int run_forward_columns(const leap_geometry *G, const FwdScratch &S, cons
                 const SfSlab slab = {n0, n1, xmajor, n0 == 0 ? 1 : 0, S.width};
                 const int i0 = xmajor ? n0 : 0, ni = xmajor ? S.width : g.nx, nj = xmajor ? g.ny : n1 - n0;
                 copy_slab(G, S, vol, xmajor ? n1 - n0 : g.nx, i0, xmajor ? 0 : n0, ni, nj, items, stream);
-                const bool ok = siddon ? launch_sd_slab(G, S, slab, sino, stream, items) : launch_fp_slab(G, S, slab, sino, stream, items);
+                const bool ok = siddon ? launch_sd_slab(G, S, slab, sino, stream, items) : leap_launch_footprint_slab(G, S, slab, sino, stream, items);
                 if (!ok) {
                     leap_set_error("internal: no column-wise forward instance for this geometry");
                     return LEAP_UNSUPPORTED;
@@ -698,72 +599,6 @@ int leap_launch_project(const leap_geometry *G, const float *d_vol, float *d_sin
     return LEAP_OK;
 }
 
-template <int NC, int NV, int SH, int GT>
-static void launch_bp_tiled_gt(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
-{
-    constexpr SfBpShape S = BP_SHAPES[SH];
-    const SfGeom &g = G->g;
-    const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
-    dim3 grid(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)items);
-    hipLaunchKernelGGL((sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, GT>), grid, dim3(256, 1, 1), 0, stream, g, G->d_views,
-                       d_sino, d_vol, (int)tiles_x, G->bp_wh, GT == 1 ? (const void *)G->d_colcs : (const void *)G->d_geoms);
-}
-
-template <int NC, int NV, int SH>
-static bool launch_bp_instance(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
-{
-    if constexpr (bp_instance_exists(NC, NV, SH)) {
-        if (G->g.type == SF_CONE_CURVED) launch_bp_tiled_gt<NC, NV, SH, 1>(G, d_sino, d_vol, stream, items);
-        else if (G->g.type == SF_MODULAR) launch_bp_tiled_gt<NC, NV, SH, 2>(G, d_sino, d_vol, stream, items);
-        else launch_bp_tiled_gt<NC, NV, SH, 0>(G, d_sino, d_vol, stream, items);
-        return true;
-    } else {
-        return false;
-    }
-}
-
-template <int NC, int NV>
-static bool launch_bp_shape(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
-{
-    switch (G->bp_shape) {
-    case 0: return launch_bp_instance<NC, NV, 0>(G, d_sino, d_vol, stream, items);
-    case 1: return launch_bp_instance<NC, NV, 1>(G, d_sino, d_vol, stream, items);
-    case 2: return launch_bp_instance<NC, NV, 2>(G, d_sino, d_vol, stream, items);
-    case 3: return launch_bp_instance<NC, NV, 3>(G, d_sino, d_vol, stream, items);
-    case 4: return launch_bp_instance<NC, NV, 4>(G, d_sino, d_vol, stream, items);
-    case BP_TALL_SHAPE: return launch_bp_instance<NC, NV, BP_TALL_SHAPE>(G, d_sino, d_vol, stream, items);
-    case BP_WIDE_SHAPE: return launch_bp_instance<NC, NV, BP_WIDE_SHAPE>(G, d_sino, d_vol, stream, items);
-    default: return false;
-    }
-}
-
-// The tiled footprint back projection on `items` consecutive sinograms of a batch in one launch.
-static int launch_bp_items(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
-{
-    bool ok = false;
-    switch (G->bp_nc * 10 + G->bp_nv) {
-    case 22: ok = launch_bp_shape<2, 2>(G, d_sino, d_vol, stream, items); break;
-    case 23: ok = launch_bp_shape<2, 3>(G, d_sino, d_vol, stream, items); break;
-    case 32: ok = launch_bp_shape<3, 2>(G, d_sino, d_vol, stream, items); break;
-    case 33: ok = launch_bp_shape<3, 3>(G, d_sino, d_vol, stream, items); break;
-    case 24: ok = launch_bp_shape<2, 4>(G, d_sino, d_vol, stream, items); break;
-    case 34: ok = launch_bp_shape<3, 4>(G, d_sino, d_vol, stream, items); break;
-    case 42: ok = launch_bp_shape<4, 2>(G, d_sino, d_vol, stream, items); break;
-    case 43: ok = launch_bp_shape<4, 3>(G, d_sino, d_vol, stream, items); break;
-    case 44: ok = launch_bp_shape<4, 4>(G, d_sino, d_vol, stream, items); break;
-    case 52: ok = launch_bp_shape<5, 2>(G, d_sino, d_vol, stream, items); break;
-    case 53: ok = launch_bp_shape<5, 3>(G, d_sino, d_vol, stream, items); break;
-    case 54: ok = launch_bp_shape<5, 4>(G, d_sino, d_vol, stream, items); break;
-    default: break;
-    }
-    if (!ok) {
-        leap_set_error("internal: no tiled back-projection instance for this footprint");
-        return LEAP_UNSUPPORTED;
-    }
-    LEAP_HIP_CHECK(hipGetLastError());
-    return LEAP_OK;
-}
-
 int leap_launch_backproject_batch(const leap_geometry *G, const float *d_sino, float *d_vol, int batch, hipStream_t stream)
 {
     const SfGeom &g = G->g;
@@ -773,7 +608,7 @@ int leap_launch_backproject_batch(const leap_geometry *G, const float *d_sino, f
         // up to 16 items per launch (a batch of small training volumes fills the chip better that way)
         for (int b = 0; b < batch; b += 16) {
             const int items = batch - b < 16 ? batch - b : 16;
-            const int rc = g.model != SF_MODEL_SIDDON ? launch_bp_items(G, d_sino + b * nsino, d_vol + b * nvol, items, stream)
+            const int rc = g.model != SF_MODEL_SIDDON ? leap_launch_footprint_back(G, d_sino + b * nsino, d_vol + b * nvol, items, stream)
                                                       : launch_sd_bp_items(G, d_sino + b * nsino, d_vol + b * nvol, items, stream);
             if (rc != LEAP_OK) return rc;
         }
@@ -791,7 +626,7 @@ int leap_launch_backproject(const leap_geometry *G, const float *d_sino, float *
     const SfGeom &g = G->g;
     if (g.model == SF_MODEL_SIDDON) return launch_sd_backproject(G, d_sino, d_vol, stream);
     if (G->flat) return backproject_flat(G, d_sino, d_vol, 1, stream);
-    if (G->bp_tiled) return launch_bp_items(G, d_sino, d_vol, 1, stream);
+    if (G->bp_tiled) return leap_launch_footprint_back(G, d_sino, d_vol, 1, stream);
     if (G->mf_tiled) {
         const unsigned tiles_x = cdiv(g.nx, MF_T), tiles_y = cdiv(g.ny, MF_T);
         auto go = [&](auto kernel, int zc) {

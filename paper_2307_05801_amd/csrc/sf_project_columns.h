@@ -161,51 +161,109 @@ SF_HD void sf_place_row(double rd, double mu, double zkp, float &fr1, unsigned &
 // Voxels a row can overlap when a pair of rows overlaps P: rows of up to (P - 1) / 2 voxels.
 constexpr int sf_single_of_pair(int P) { return P / 2 + 1; }
 
-// Axial sums of a pair of adjacent rows.  x[0..P-1]: voxels from the one holding the lower row's lower edge; fr1 as
-// above; step = voxels per row, fr + 2 step <= P.  The lower row A covers [fr, fr + step) of that run, the upper row B
-// [fr + step, fr + 2 step).  With a_t = clamp(fr + step - t), b_t = clamp(fr + 2 step - t) and d_t = x_t - x_0 (t >= 1):
-//   S_A = step x_0 + sum a_t d_t,    S_B = 2 step x_0 + sum b_t d_t - S_A
-// (voxel 0 gets what the others leave of each row; additions with the clamp modifier are the cheapest way to an overlap).
-// What sf_pair_sums needs of a candidate besides the voxels: step and the offsets of the clamps, ka[t-1] = step - (t+1)
-// for 1 <= t < NK (NK = sf_single_of_pair(P)) and kb[t-1] = 2 step - (t+1) for 1 <= t < P.  The same for every row
-// of the detector, so the forward kernel works them out once per candidate, lane-parallel.
-template <int P>
-struct SfPairConsts {
-    float step;
-    float ka[sf_single_of_pair(P) > 1 ? sf_single_of_pair(P) - 1 : 1];
-    float kb[P > 1 ? P - 1 : 1];
+// Axial weights of a pair of adjacent rows.  x[0..P-1]: voxels from the one holding the lower row's lower edge; fr1 as
+// above; mu = voxels per row.  The lower row A covers [fr, fr + mu) of that run, the upper row B [fr + mu, fr + 2 mu).  With
+// a_t = clamp(fr + mu - t) and b_t = clamp(fr + 2 mu - t), the parts of voxel t below either row's upper edge, voxel t weighs a_t in A
+// and b_t - a_t in B for t >= 1; voxel 0 weighs 1 - fr in A (rows of a voxel and more) or mu - a_1 (shorter rows), and in B, which reaches
+// it where rows are shorter than a voxel, 1 - fr - mu (rows of half a voxel and more) or what the other voxels leave.
+// Rows are sorted into classes by their height, LO2 / 2 <= mu <= HI2 / 2, so that what is known to be 0 or 1 costs nothing: a pair
+// of rows of up to one voxel reads three voxels and takes six instructions for its weights and five for its sums, one of up to a
+// voxel and a half four voxels, seven and six (sixteen while one body served every height up to a voxel and a half).  The
+// weights depend on no voxel, so a lane that carries several volumes forms them once.
+// Offsets of the clamps, the same for every row of the detector, worked out once per candidate: ka[t-1] = mu - (t+1), kb[t-1] = 2 mu - (t+1).
+struct SfPairOffsets {
+    float mu;
+    float ka[3], kb[6];
 };
 
-template <int P>
-SF_HD SfPairConsts<P> sf_pair_consts(float step)
+SF_HD SfPairOffsets sf_pair_offsets(float mu)
 {
-    constexpr int NK = sf_single_of_pair(P);
-    SfPairConsts<P> k;
-    k.step = step;
-    const float step2 = step + step;
+    SfPairOffsets k;
+    k.mu = mu;
+    const float mu2 = mu + mu;
 #pragma unroll
-    for (int t = 1; t < NK && t < P; ++t) k.ka[t - 1] = step - (float)(t + 1);
+    for (int t = 1; t <= 3; ++t) k.ka[t - 1] = mu - (float)(t + 1);
 #pragma unroll
-    for (int t = 1; t < P; ++t) k.kb[t - 1] = step2 - (float)(t + 1);
+    for (int t = 1; t <= 6; ++t) k.kb[t - 1] = mu2 - (float)(t + 1);
     return k;
 }
 
-template <int P>
-SF_HD void sf_pair_sums(const float (&x)[P], float fr1, const SfPairConsts<P> &k, float &sa, float &sb)
+template <int LO2, int HI2>
+struct SfPairWeights {
+    static constexpr int P = HI2 + 1;                 // voxels a pair can overlap
+    static constexpr int NA = (HI2 + 3) / 2;          // voxels the lower row can overlap
+    static constexpr int B0 = LO2 >= 2 ? 1 : 0;       // first voxel the upper row can overlap
+    float a[NA], b[P];
+};
+
+template <int LO2, int HI2>
+SF_HD SfPairWeights<LO2, HI2> sf_pair_weights(float fr1, const SfPairOffsets &k)
 {
-    constexpr int NK = sf_single_of_pair(P);
-    float d[P];
+    using W = SfPairWeights<LO2, HI2>;
+    W w;
 #pragma unroll
-    for (int t = 1; t < P; ++t) d[t] = x[t] - x[0];
-    const float a0 = k.step * x[0];
-    float a = a0;
+    for (int t = 1; t < W::NA; ++t) w.a[t] = LO2 >= 2 * (t + 1) ? 1.0f : sf_clamp(fr1 + k.ka[t - 1], 0.0f, 1.0f);
+    w.a[0] = LO2 >= 2 ? 2.0f - fr1 : k.mu - w.a[1];
+    w.b[0] = LO2 >= 2 ? 0.0f : sf_clamp(-k.ka[0] - fr1, 0.0f, 1.0f);          // (LO2 == 0: below)
 #pragma unroll
-    for (int t = 1; t < NK && t < P; ++t) a = fmaf(sf_clamp(fr1 + k.ka[t - 1], 0.0f, 1.0f), d[t], a);
-    float b = a0 + a0;                              // 2 step x_0, exactly
+    for (int t = 1; t < W::P; ++t) {
+        const float upto = LO2 >= t + 1 ? 1.0f : sf_clamp(fr1 + k.kb[t - 1], 0.0f, 1.0f);
+        w.b[t] = t < W::NA ? upto - w.a[t] : upto;
+    }
+    if (LO2 == 0) w.b[0] = k.mu - w.b[1];
+    return w;
+}
+
+template <int LO2, int HI2>
+SF_HD void sf_pair_apply(const float *x, const SfPairWeights<LO2, HI2> &w, float &sa, float &sb)
+{
+    using W = SfPairWeights<LO2, HI2>;
+    sa = w.a[0] * x[0];
 #pragma unroll
-    for (int t = 1; t < P; ++t) b = fmaf(sf_clamp(fr1 + k.kb[t - 1], 0.0f, 1.0f), d[t], b);
-    sa = a;
-    sb = b - a;
+    for (int t = 1; t < W::NA; ++t) sa = (LO2 >= 2 * (t + 1)) ? sa + x[t] : fmaf(w.a[t], x[t], sa);
+    sb = w.b[W::B0] * x[W::B0];
+#pragma unroll
+    for (int t = W::B0 + 1; t < W::P; ++t) {
+        if (LO2 >= t + 1 && t < W::NA && LO2 >= 2 * (t + 1)) continue;       // the lower row holds all of it
+        sb = fmaf(w.b[t], x[t], sb);
+    }
+}
+
+// Height classes: 0 up to half a voxel, 1 up to a voxel, 2 up to a voxel and a half, 3 up to two, 4 up to three voxels.
+template <int CLS>
+struct SfPairClass {
+    static constexpr int LO2 = CLS, HI2 = CLS == 4 ? 6 : CLS + 1, P = HI2 + 1;
+};
+SF_HD int sf_pair_class(float mu) { return mu < 0.5f ? 0 : (mu <= 1.0f ? 1 : (mu <= 1.5f ? 2 : (mu <= 2.0f ? 3 : 4))); }
+
+template <int CLS>
+SF_HD void sf_pair_sums_of_class(const float *x, float fr1, const SfPairOffsets &k, float &sa, float &sb)
+{
+    using C = SfPairClass<CLS>;
+    sf_pair_apply<C::LO2, C::HI2>(x, sf_pair_weights<C::LO2, C::HI2>(fr1, k), sa, sb);
+}
+
+// The same for any height that fits P voxels per pair, the class picked per call (host).
+template <int P>
+struct SfPairConsts {
+    SfPairOffsets k;
+};
+
+template <int P>
+SF_HD SfPairConsts<P> sf_pair_consts(float mu) { return {sf_pair_offsets(mu)}; }
+
+template <int P>
+SF_HD void sf_pair_sums(const float (&x)[P], float fr1, const SfPairConsts<P> &c, float &sa, float &sb)
+{
+    float run[FP_MAX_P] = {};
+    for (int t = 0; t < P; ++t) run[t] = x[t];
+    switch (sf_pair_class(c.k.mu)) {
+    case 0: sf_pair_sums_of_class<0>(run, fr1, c.k, sa, sb); break;
+    case 1: sf_pair_sums_of_class<1>(run, fr1, c.k, sa, sb); break;
+    case 2: sf_pair_sums_of_class<2>(run, fr1, c.k, sa, sb); break;
+    case 3: sf_pair_sums_of_class<3>(run, fr1, c.k, sa, sb); break;
+    default: sf_pair_sums_of_class<4>(run, fr1, c.k, sa, sb); break;
+    }
 }
 
 // Transaxial record of one candidate voxel column (i, j) for the bundle of CW detector columns starting at c0:
@@ -236,7 +294,7 @@ SF_HD bool sf_candidate_record(const SfGeom &g, const SfView &v, int i, int j, i
 // vol [nz][ny][nx]  ->  the slab's scratch copy: columns (i, j), i0 <= i < i0 + ni, j0 <= j < j0 + nj, at
 // volz[((j - j0) ni + (i - i0)) nzp + FP_PAD + k].  Block 32 x 8 threads, tile 32 (i) x 32 (k) of one j.
 // blockIdx.z = (j - j0) + nj * item: several volumes of a batch go into consecutive scratch copies in one launch.
-__global__ __launch_bounds__(256) void sf_volume_to_columns(const float *__restrict__ vol, float *__restrict__ volz, int nx,
+static __global__ __launch_bounds__(256) void sf_volume_to_columns(const float *__restrict__ vol, float *__restrict__ volz, int nx,
                                                             int ny, int nz, int nzp, int i0, int j0, int ni, int nj,
                                                             size_t item_stride)
 {
@@ -267,7 +325,7 @@ __global__ __launch_bounds__(256) void sf_volume_to_columns(const float *__restr
 // Zeroes what the column-wise kernels expect to be zero around the voxels that sf_volume_to_columns writes: FP_PAD
 // floats before and after each of the ncolumns z-columns and the whole spare column that follows them (a fill kernel,
 // not a memset, so that a caller may capture the call in a graph).
-__global__ __launch_bounds__(256) void sf_clear_column_pads(float *__restrict__ volz, unsigned ncolumns, int nz, int nzp)
+static __global__ __launch_bounds__(256) void sf_clear_column_pads(float *__restrict__ volz, unsigned ncolumns, int nz, int nzp)
 {
     const unsigned t = blockIdx.x * 256u + threadIdx.x;
     const unsigned col = t / (2u * FP_PAD), e = t % (2u * FP_PAD);
@@ -308,14 +366,14 @@ __device__ __forceinline__ void fp_store_four(float *__restrict__ dst, float a, 
 
 constexpr int FP_WAVES = 4;      // waves per workgroup: adjacent column bundles of one view (each wave its own LDS, no barrier)
 
-// NKP: voxels a pair of adjacent rows can overlap (2 .. FP_MAX_P); RG: groups of 128 rows per wave; CW: adjacent detector
-// columns per wave; GT: 0 flat or parallel, 1 cylindrical detector, 2 modular geometry with upright modules.
+// HC: highest height class of the scan's rows (2 .. 4); RG: groups of 128 rows per wave; CW: adjacent detector columns per wave;
+// GT: 0 flat or parallel, 1 cylindrical detector, 2 modular geometry with upright modules; NS: volumes per wave.
 // (The cylinder's record phase needs more registers: its instances are held to the waves per SIMD they reach without
 // the records' staging, four up to two row groups, three beyond.)
 // nq_log2: log2 of the candidate slots per slab (a power of two <= 64).  major[a * nbundles + b]: 1 if bundle b of view
 // a advances fastest along x (decided once, on the host, so that both agree on which slabs a bundle reads).
-template <int NKP, int RG, int CW, int GT>
-__global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG <= 2 ? 4 : 3) : 1) void sf_project_columns(SfGeom gk, const SfView *__restrict__ views,
+template <int HC, int RG, int CW, int GT, int NS>
+__global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1) void sf_project_columns(SfGeom gk, const SfView *__restrict__ views,
                                                                     const float *__restrict__ volz, float *__restrict__ sino,
                                                                     const unsigned char *__restrict__ major, int nzp,
                                                                     size_t item_stride, int nq_log2, int col_tiles, int bands,
@@ -325,9 +383,11 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG <= 2 ? 4 : 3) : 1) voi
     // GT == 2 (modular geometry, upright modules): the wave's view brings its own parameter block, the scene
     // translated so that the view is a circular cone-beam view; gk holds the sizes, which all views share.
     const SfGeom &gsz = gk;
-    // blockIdx.y: item of a batch (its scratch copy and its sinogram)
-    volz += (size_t)blockIdx.y * item_stride;
-    sino += (size_t)blockIdx.y * gk.nviews * gk.nrows * gk.ncols;
+    // blockIdx.y: NS items of a batch (their scratch copies and sinograms).  Everything but the voxels and the sums is the same for
+    // two items: candidates, records, placement and axial weights are formed once (eight 256^3 volumes of 60 views, 7.4 -> 7.05 ms).
+    const size_t nsino = (size_t)gk.nviews * gk.nrows * gk.ncols;
+    volz += (size_t)blockIdx.y * NS * item_stride;
+    sino += (size_t)blockIdx.y * NS * nsino;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -356,24 +416,24 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG <= 2 ? 4 : 3) : 1) voi
     const unsigned off_k = 0u - (FP_KAP_HI << 2);
     const unsigned col_bytes = (unsigned)nzp * 4u;
 
-    float acc[CW][RG][2];
+    float acc[NS][CW][RG][2];
 #pragma unroll
-    for (int cw = 0; cw < CW; ++cw)
+    for (int q = 0; q < NS; ++q)
 #pragma unroll
-        for (int gq = 0; gq < RG; ++gq) acc[cw][gq][0] = acc[cw][gq][1] = 0.0f;
+        for (int cw = 0; cw < CW; ++cw)
+#pragma unroll
+            for (int gq = 0; gq < RG; ++gq) acc[q][cw][gq][0] = acc[q][cw][gq][1] = 0.0f;
 
     const int slot = lane & ((1 << nq_log2) - 1), nrel = lane >> nq_log2, sb_slabs = 64 >> nq_log2;
 
-    // What a candidate's visit needs as plain vector operands (the CW column factors, step and the clamp offsets of the
-    // four-voxel body) goes through LDS: every lane writes its candidate's record, the wave reads the record of the
+    // What a candidate's visit needs as plain vector operands (the CW column factors and the clamp offsets of its height class)
+    // goes through LDS: every lane writes its candidate's record, the wave reads the record of the
     // candidate it visits back at a uniform address, which the LDS serves as a broadcast without touching the vector
     // ALU (a v_readlane costs as much issue time as two and a half FMAs; the kernel is bound by that issue time).
     // Only what must sit in scalar registers still comes by v_readlane: the column's offset (buffer descriptor) and mu
     // (scalar operand of the placement FMAs).
-    constexpr int PB = NKP > 4 ? 4 : NKP;           // the body most candidates take
-    constexpr int FP_REC = 3;                       // float4s per record
-    __shared__ float4 recs[FP_WAVES][64][FP_REC];
-    float4 (*rec)[FP_REC] = recs[wave];
+    __shared__ float4 recs[FP_WAVES][64][2];
+    float4 (*rec)[2] = recs[wave];
 
     for (int nb = slab.n0; nb < slab.n1; nb += sb_slabs) {
         // ---- lane-parallel: one candidate voxel column per lane
@@ -390,135 +450,141 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG <= 2 ? 4 : 3) : 1) voi
         const unsigned colbase = sf_slab_column(slab, g.nx, ic, jc) * (unsigned)nzp;   // start of the padded column
         const int mu_lo = __double2loint(mu), mu_hi = __double2hiint(mu);
         const float muf = (float)mu;
+        const int cls = sf_pair_class(muf);
         {
-            const SfPairConsts<PB> k = sf_pair_consts<PB>(muf);
-            float w[4 * FP_REC];
-#pragma unroll
-            for (int t = 0; t < 4 * FP_REC; ++t) w[t] = 0.0f;
-#pragma unroll
-            for (int cw = 0; cw < CW; ++cw) w[cw] = fa[cw];
-            w[4] = k.step;
-#pragma unroll
-            for (int t = 0; t < sf_single_of_pair(PB) - 1; ++t) w[5 + t] = k.ka[t];
-#pragma unroll
-            for (int t = 0; t < PB - 1; ++t) w[8 + t] = k.kb[t];
+            const SfPairOffsets k = sf_pair_offsets(muf);
+            float4 f4 = make_float4(fa[0], 0.0f, 0.0f, 0.0f);
+            if constexpr (CW > 1) f4.y = fa[1];
+            if constexpr (CW > 2) { f4.z = fa[2]; f4.w = fa[3]; }
+            const bool below1 = cls <= 1, below2 = cls <= 2;
             // (the wave has consumed every value it read from the previous block's records)
-#pragma unroll
-            for (int t = 0; t < FP_REC; ++t) rec[lane][t] = make_float4(w[4 * t], w[4 * t + 1], w[4 * t + 2], w[4 * t + 3]);
+            rec[lane][0] = f4;
+            rec[lane][1] = make_float4(below1 || (HC > 3 && cls > 3) ? k.mu : k.ka[0], below1 ? k.ka[0] : k.ka[1],
+                                       below1 ? k.kb[0] : (below2 ? k.kb[1] : k.kb[2]), below1 ? k.kb[1] : (below2 ? k.kb[2] : k.kb[3]));
             // the records are read by the other lanes of this wave only: order the LDS accesses, no barrier
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
 
-        unsigned long long mask = __ballot(any);
+        const unsigned long long mask = __ballot(any);
         unsigned long long touch[CW];                              // candidates that touch detector column cw
 #pragma unroll
         for (int cw = 0; cw < CW; ++cw) touch[cw] = __ballot(fa[cw] != 0.0f);
-        // most candidates of a scan with NKP > 4 still fit four voxels per pair: one 16-byte load per pair
-        const unsigned long long wide = NKP > 4 ? __ballot(!(muf <= 1.4999f)) : 0ull;
-        // ---- wave-uniform walk over the candidates that matter
-        auto pairs = [&](auto pc, int e, const float (&r)[4 * FP_REC], float (&sa)[RG], float (&sb)[RG]) {
-            constexpr int P = decltype(pc)::value;
-            const unsigned s_base = (unsigned)__builtin_amdgcn_readlane((int)colbase, e);
-            const double s_mu = __hiloint2double(__builtin_amdgcn_readlane(mu_hi, e), __builtin_amdgcn_readlane(mu_lo, e));
-            SfPairConsts<P> k;
-            if constexpr (P == PB) {
-                k.step = r[4];
+        // ---- wave-uniform walk over the candidates that matter, one height class after the other (a block's candidates
+        // lie close together and mostly share theirs).
+        auto walk = [&](auto cc, unsigned long long todo) {
+            constexpr int CLS = decltype(cc)::value, P = SfPairClass<CLS>::P;
+            using C = SfPairClass<CLS>;
+            while (todo) {
+                const int e = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const float4 r0 = rec[e][0], r1 = rec[e][1];
+                const float fcol[4] = {r0.x, r0.y, r0.z, r0.w};
+                SfPairOffsets k;
+                if constexpr (CLS <= 1) { k.mu = r1.x; k.ka[0] = r1.y; k.kb[0] = r1.z; k.kb[1] = r1.w; }
+                if constexpr (CLS == 2) { k.ka[0] = r1.x; k.ka[1] = r1.y; k.kb[1] = r1.z; k.kb[2] = r1.w; }
+                if constexpr (CLS == 3) { k.ka[0] = r1.x; k.ka[1] = r1.y; k.kb[2] = r1.z; k.kb[3] = r1.w; }
+                if constexpr (CLS == 4) k = sf_pair_offsets(r1.x);
+                const unsigned s_base = (unsigned)__builtin_amdgcn_readlane((int)colbase, e);
+                const double s_mu = __hiloint2double(__builtin_amdgcn_readlane(mu_hi, e), __builtin_amdgcn_readlane(mu_lo, e));
+                float fr1[RG];
+                unsigned ko[RG];
 #pragma unroll
-                for (int t = 0; t < sf_single_of_pair(P) - 1; ++t) k.ka[t] = r[5 + t];
+                for (int gq = 0; gq < RG; ++gq) {
+                    unsigned hi;
+                    sf_place_row(rd[gq], s_mu, zkp, fr1[gq], hi);
+                    asm("v_lshl_add_u32 %0, %1, 2, %2" : "=v"(ko[gq]) : "v"(hi), "s"(off_k));
+                }
+                float xv[NS][RG][P];
 #pragma unroll
-                for (int t = 0; t < P - 1; ++t) k.kb[t] = r[8 + t];
-            } else {
-                k = sf_pair_consts<P>(r[4]);
-            }
-            // buffer resource of this candidate's padded z-column: loads beyond it return zero
-            const __amdgpu_buffer_rsrc_t col = __builtin_amdgcn_make_buffer_rsrc((void *)(volz + s_base), 0, (int)col_bytes, 0x00020000);
-            float fr1[RG];
-            unsigned ko[RG];
+                for (int s = 0; s < NS; ++s) {
+                    // buffer resource of this candidate's padded z-column: loads beyond it return zero
+                    const __amdgpu_buffer_rsrc_t col =
+                        __builtin_amdgcn_make_buffer_rsrc((void *)(volz + s * item_stride + s_base), 0, (int)col_bytes, 0x00020000);
 #pragma unroll
-            for (int gq = 0; gq < RG; ++gq) {
-                unsigned hi;
-                sf_place_row(rd[gq], s_mu, zkp, fr1[gq], hi);
-                asm("v_lshl_add_u32 %0, %1, 2, %2" : "=v"(ko[gq]) : "v"(hi), "s"(off_k));
-            }
-            float xv[RG][P];
+                    for (int gq = 0; gq < RG; ++gq)
 #pragma unroll
-            for (int gq = 0; gq < RG; ++gq)
+                        for (int t = 0; t < P; ++t)      // the compiler merges these into loads of up to 16 bytes
+                            xv[s][gq][t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(col, (int)ko[gq] + 4 * t, 0, 0));
+                }
+                float sa[NS][RG], sb[NS][RG];
 #pragma unroll
-                for (int t = 0; t < P; ++t)      // the compiler merges these into loads of up to 16 bytes
-                    xv[gq][t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(col, (int)ko[gq] + 4 * t, 0, 0));
+                for (int gq = 0; gq < RG; ++gq) {
+                    const SfPairWeights<C::LO2, C::HI2> w = sf_pair_weights<C::LO2, C::HI2>(fr1[gq], k);
 #pragma unroll
-            for (int gq = 0; gq < RG; ++gq) sf_pair_sums<P>(xv[gq], fr1[gq], k, sa[gq], sb[gq]);
-        };
-        while (mask) {
-            const int e = __builtin_ctzll(mask);
-            mask &= mask - 1;
-            float r[4 * FP_REC];
+                    for (int s = 0; s < NS; ++s) sf_pair_apply<C::LO2, C::HI2>(xv[s][gq], w, sa[s][gq], sb[s][gq]);
+                }
+                // a candidate usually touches only some of the bundle's columns: skip the others (wave-uniform branches)
 #pragma unroll
-            for (int t = 0; t < FP_REC; ++t) {
-                const float4 q4 = rec[e][t];
-                r[4 * t] = q4.x; r[4 * t + 1] = q4.y; r[4 * t + 2] = q4.z; r[4 * t + 3] = q4.w;
-            }
-            float sa[RG], sb[RG];
-            if constexpr (NKP > 4) {
-                if (!((wide >> e) & 1ull)) pairs(std::integral_constant<int, 4>{}, e, r, sa, sb);
-                else pairs(std::integral_constant<int, NKP>{}, e, r, sa, sb);
-            } else {
-                pairs(std::integral_constant<int, NKP>{}, e, r, sa, sb);
-            }
-            // a candidate usually touches only some of the bundle's columns: skip the others (wave-uniform branches)
+                for (int cw = 0; cw < CW; ++cw) {
+                    if ((touch[cw] >> e) & 1ull) {
 #pragma unroll
-            for (int cw = 0; cw < CW; ++cw) {
-                if ((touch[cw] >> e) & 1ull) {
+                        for (int s = 0; s < NS; ++s)
 #pragma unroll
-                    for (int gq = 0; gq < RG; ++gq) {
-                        acc[cw][gq][0] = fmaf(r[cw], sa[gq], acc[cw][gq][0]);
-                        acc[cw][gq][1] = fmaf(r[cw], sb[gq], acc[cw][gq][1]);
+                            for (int gq = 0; gq < RG; ++gq) {
+                                acc[s][cw][gq][0] = fmaf(fcol[cw], sa[s][gq], acc[s][cw][gq][0]);
+                                acc[s][cw][gq][1] = fmaf(fcol[cw], sb[s][gq], acc[s][cw][gq][1]);
+                            }
                     }
                 }
             }
-        }
+        };
+        unsigned long long todo = mask;
+        auto walk_up_to = [&](auto cc) {
+            constexpr int CLS = decltype(cc)::value;
+            const unsigned long long above = CLS < HC ? __ballot(cls > CLS) : 0ull;
+            walk(cc, todo & ~above);
+            todo &= above;
+        };
+        walk_up_to(std::integral_constant<int, 0>{});
+        walk_up_to(std::integral_constant<int, 1>{});
+        walk_up_to(std::integral_constant<int, 2>{});
+        if constexpr (HC > 2) walk_up_to(std::integral_constant<int, 3>{});
+        if constexpr (HC > 3) walk_up_to(std::integral_constant<int, 4>{});
     }
 
     // ---- amplitude and store: CW consecutive floats per lane and row, written together (storing the columns of a
     // bundle one after the other, hundreds of instructions apart, cost 3.7 times the sinogram in partial-line writes)
-    float *__restrict__ ya = sino + (size_t)a * g.nrows * g.ncols;
     SfAmpCol ac[CW];
 #pragma unroll
     for (int cw = 0; cw < CW; ++cw) ac[cw] = sf_amp_col<GT>(g, v, c0 + cw < g.ncols ? c0 + cw : g.ncols - 1);
     struct __attribute__((packed, aligned(4))) Pair { float lo, hi; };
 #pragma unroll
-    for (int gq = 0; gq < RG; ++gq) {
+    for (int s = 0; s < NS; ++s) {
+        float *__restrict__ ya = sino + s * nsino + (size_t)a * g.nrows * g.ncols;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int r = band0 + 128 * gq + 2 * lane + h;
-            if (r >= g.nrows) continue;
-            float out[CW];
+        for (int gq = 0; gq < RG; ++gq) {
 #pragma unroll
-            for (int cw = 0; cw < CW; ++cw) out[cw] = sf_amp(g, v, ac[cw], r) * acc[cw][gq][h];
-            float *__restrict__ dst = ya + (size_t)r * g.ncols + c0;
-            if constexpr (CW == 2) {
-                if (c0 + 1 < g.ncols) {
-                    Pair pr;
-                    if (!slab.first) {
-                        pr = *reinterpret_cast<const Pair *>(dst);
-                        out[0] += pr.lo; out[1] += pr.hi;
+            for (int h = 0; h < 2; ++h) {
+                const int r = band0 + 128 * gq + 2 * lane + h;
+                if (r >= g.nrows) continue;
+                float out[CW];
+#pragma unroll
+                for (int cw = 0; cw < CW; ++cw) out[cw] = sf_amp(g, v, ac[cw], r) * acc[s][cw][gq][h];
+                float *__restrict__ dst = ya + (size_t)r * g.ncols + c0;
+                if constexpr (CW == 2) {
+                    if (c0 + 1 < g.ncols) {
+                        Pair pr;
+                        if (!slab.first) {
+                            pr = *reinterpret_cast<const Pair *>(dst);
+                            out[0] += pr.lo; out[1] += pr.hi;
+                        }
+                        pr.lo = out[0]; pr.hi = out[1];
+                        *reinterpret_cast<Pair *>(dst) = pr;
+                        continue;
                     }
-                    pr.lo = out[0]; pr.hi = out[1];
-                    *reinterpret_cast<Pair *>(dst) = pr;
-                    continue;
                 }
-            }
-            if constexpr (CW == 4) {
-                if (c0 + 3 < g.ncols) {
-                    fp_store_four(dst, out[0], out[1], out[2], out[3], slab.first);
-                    continue;
+                if constexpr (CW == 4) {
+                    if (c0 + 3 < g.ncols) {
+                        fp_store_four(dst, out[0], out[1], out[2], out[3], slab.first);
+                        continue;
+                    }
                 }
-            }
 #pragma unroll
-            for (int cw = 0; cw < CW; ++cw)
-                if (c0 + cw < g.ncols) dst[cw] = slab.first ? out[cw] : dst[cw] + out[cw];
+                for (int cw = 0; cw < CW; ++cw)
+                    if (c0 + cw < g.ncols) dst[cw] = slab.first ? out[cw] : dst[cw] + out[cw];
+            }
         }
     }
 }

@@ -39,7 +39,7 @@ SF_HD float sf_row_weight(const SfRowOverlap &o, int t)
 
 // vol [nz][ny][nx]  ->  the slab's scratch copy by detector rows: columns (i, j), i0 <= i < i0 + ni, j0 <= j < j0 + nj, at
 // rows[((j - j0) ni + (i - i0)) nzp + r].  Block 32 x 8 threads, tile 32 (i) x 32 (r) of one j; blockIdx.z = (j - j0) + nj * item.
-__global__ __launch_bounds__(256) void sf_volume_to_rows(SfGeom g, const float *__restrict__ vol, float *__restrict__ rows, int nzp, int i0,
+static __global__ __launch_bounds__(256) void sf_volume_to_rows(SfGeom g, const float *__restrict__ vol, float *__restrict__ rows, int nzp, int i0,
                                                          int j0, int ni, int nj, size_t item_stride)
 {
     __shared__ float tile[32][33];
