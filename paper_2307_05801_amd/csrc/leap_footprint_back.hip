@@ -1,4 +1,4 @@
-// Launchers of the tiled footprint back projection.
+// Launchers of the tiled footprint back projection, one volume per workgroup.
 #include <hip/hip_runtime.h>
 
 #include "leap_internal.h"
@@ -11,8 +11,8 @@ static void launch_bp_tiled_gt(const leap_geometry *G, const float *d_sino, floa
     const SfGeom &g = G->g;
     const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
     dim3 grid(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)items);
-    hipLaunchKernelGGL((sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, GT>), grid, dim3(256, 1, 1), 0, stream, g, G->d_views,
-                       d_sino, d_vol, (int)tiles_x, G->bp_wh, GT == 1 ? (const void *)G->d_colcs : (const void *)G->d_geoms);
+    hipLaunchKernelGGL((sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, GT, 1>), grid, dim3(256, 1, 1), 0, stream, g, G->d_views,
+                       d_sino, d_vol, (int)tiles_x, G->bp_wh, GT == 1 ? (const void *)G->d_colcs : (const void *)G->d_geoms, SfBpSets{0, 0});
 }
 
 template <int NC, int NV, int SH>
@@ -47,6 +47,19 @@ static bool launch_bp_shape(const leap_geometry *G, const float *d_sino, float *
 int leap_launch_footprint_back(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     bool ok = false;
+    if (G->bp_pair_shape >= 0) {
+        // two volumes per workgroup: an item and its mirror image, or two items of the batch; an odd last item by itself
+        const int blocks = G->bp_mirror ? items : items / 2;
+        if (blocks && !leap_launch_backproject_pairs(G, d_sino, d_vol, blocks, stream)) {
+            leap_set_error("internal: no back-projection instance of two volumes for this footprint");
+            return LEAP_UNSUPPORTED;
+        }
+        LEAP_HIP_CHECK(hipGetLastError());
+        if (G->bp_mirror || items % 2 == 0) return LEAP_OK;
+        d_sino += (size_t)(items - 1) * G->g.nviews * G->g.nrows * G->g.ncols;
+        d_vol += (size_t)(items - 1) * G->g.nx * G->g.ny * G->g.nz;
+        items = 1;
+    }
     switch (G->bp_nc * 10 + G->bp_nv) {
     case 22: ok = launch_bp_shape<2, 2>(G, d_sino, d_vol, stream, items); break;
     case 23: ok = launch_bp_shape<2, 3>(G, d_sino, d_vol, stream, items); break;

@@ -214,40 +214,88 @@ static void run_shares(int workers, Share share)
         if (e) std::rethrow_exception(e);
 }
 
-// Largest staged window any (view, tile, first or last z-chunk) of a tiled back projection asks for, evaluated with the
-// kernel's own window function on the view's own parameter block.
-template <class WindowFn>
-static void staged_window_need(const leap_geometry *G, int zc, WindowFn window, int &need_w, int &need_h)
+// Chunks of zc voxels from voxel kfirst on, and the largest staged window any (view, tile, chunk) of theirs asks for.
+struct WindowNeed {
+    int zc, kfirst;
+    int w = 0, h = 0;
+};
+
+// Largest staged windows of a tiled back projection for several heights of chunk at once, evaluated with the kernel's own window
+// functions on the view's own parameter block.  tile(ga, view, xc, yc, window): what the windows of a tile have in common, their columns
+// among it; rows(ga, that, z0, z1, window): the rows of one.
+template <class TileFn, class RowsFn>
+static void staged_window_needs(const leap_geometry *G, std::vector<WindowNeed> &needs, TileFn tile, RowsFn rows)
 {
     const leap_geometry_desc *d = &G->desc;
     const int tiles_x = (d->nx + BP_T - 1) / BP_T, tiles_y = (d->ny + BP_T - 1) / BP_T;
-    const int chunks = (d->nz + zc - 1) / zc;
     // the views are shared out among a few threads (a thousand views of a few thousand tiles each)
     const int workers = (int)std::max(1, std::min(8, d->nviews / 32));
-    std::vector<int> w(workers, 0), h(workers, 0);
+    std::vector<std::vector<WindowNeed>> found(workers, needs);
     auto scan = [&](int t) {
-        int wt = 0, ht = 0;                   // kept local: the workers' slots of w and h share a cache line
+        std::vector<WindowNeed> mine = needs;       // kept local: the workers' results share cache lines
         for (int a = t; a < d->nviews; a += workers) {
             const SfGeom &ga = view_geom(G, a);
             for (int ty = 0; ty < tiles_y; ++ty)
                 for (int tx = 0; tx < tiles_x; ++tx) {
                     const float xc = (float)(ga.x0d + ((double)(tx * BP_T) + 0.5 * (BP_T - 1)) * ga.Td);
                     const float yc = (float)(ga.y0d + ((double)(ty * BP_T) + 0.5 * (BP_T - 1)) * ga.Td);
-                    for (int ch = 0; ch < chunks; ch += (chunks > 1 ? chunks - 1 : 1)) {   // extremes: first and last chunk
-                        const float z0 = (float)(ga.zlo0d + (double)(ch * zc) * ga.Tzd), z1 = z0 + (float)zc * ga.Tz;
-                        const SfWindow win = window(ga, G->views[a], xc, yc, z0, z1);
-                        const bool near = std::abs((float)win.c0) < BP_MAX_COORDINATE - 1024.0f && std::abs((float)win.r0) < BP_MAX_COORDINATE - 1024.0f;
-                        wt = std::max(wt, near ? win.need_w : 1 << 30);
-                        ht = std::max(ht, near ? win.need_h : 1 << 30);
+                    SfWindow win;
+                    const auto bounds = tile(ga, G->views[a], xc, yc, win);
+                    for (WindowNeed &n : mine) {
+                        const int chunks = (d->nz - n.kfirst + n.zc - 1) / n.zc;
+                        for (int ch = 0; ch < chunks; ch += (chunks > 1 ? chunks - 1 : 1)) {   // extremes: first and last chunk
+                            const float z0 = (float)(ga.zlo0d + (double)(n.kfirst + ch * n.zc) * ga.Tzd), z1 = z0 + (float)n.zc * ga.Tz;
+                            rows(ga, bounds, z0, z1, win);
+                            const bool near = std::abs((float)win.c0) < BP_MAX_COORDINATE - 1024.0f && std::abs((float)win.r0) < BP_MAX_COORDINATE - 1024.0f;
+                            n.w = std::max(n.w, near ? win.need_w : 1 << 30);
+                            n.h = std::max(n.h, near ? win.need_h : 1 << 30);
+                        }
                     }
                 }
         }
-        w[t] = wt;
-        h[t] = ht;
+        found[t] = mine;
     };
     run_shares(workers, scan);
-    need_w = *std::max_element(w.begin(), w.end());
-    need_h = *std::max_element(h.begin(), h.end());
+    for (const auto &mine : found)
+        for (size_t n = 0; n < needs.size(); ++n) {
+            needs[n].w = std::max(needs[n].w, mine[n].w);
+            needs[n].h = std::max(needs[n].h, mine[n].h);
+        }
+}
+
+// one spare row and column: host and device floats may round apart
+static bool window_fits(const WindowNeed &n, const SfBpShape &S) { return n.w <= S.pw - 1 && n.h <= S.ph - 1; }
+
+// Detector and volume symmetric about the source plane: the weight of voxel k for row r is that of voxel nz - 1 - k for row
+// nrows - 1 - r, in every view.
+static bool mirrored_about_source_plane(const leap_geometry *G)
+{
+    const leap_geometry_desc *d = &G->desc;
+    return (d->type == LEAP_CONE || d->type == LEAP_CONE_CURVED || d->type == LEAP_PARALLEL) && d->shift_v == 0.0 && d->center_z == 0.0;
+}
+
+// Tiled back projection, two volumes per workgroup: the shapes that leave the chip enough workgroups.
+static std::vector<int> backproject_pair_shapes(leap_geometry *G)
+{
+    const leap_geometry_desc *d = &G->desc;
+    std::vector<int> shapes;
+    if (G->bp_nv > 3 || d->type == LEAP_MODULAR) return shapes;
+    G->bp_mirror = mirrored_about_source_plane(G);
+    long only = -2;
+    if (debug_option("bp_pair", only) && only == -1) return shapes;
+    const int kfirst = G->bp_mirror ? sf_mirror_first_voxel_above(d->nz) : 0;
+    const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
+    for (int sh = 0; sh < BP_NPAIR_SHAPES; ++sh) {
+        const SfBpShape S = BP_PAIR_SHAPES[sh];
+        if ((only >= 0 && sh != only) || !bp_pair_instance_exists(G->bp_nc, G->bp_nv, sh)) continue;
+        // Mirror image, parallel beams, 120 views, one volume / 32 + 32 / 16 + 16 voxels per thread: 256^3 (1024 workgroups of the
+        // larger) 693 / 552 / 648 us, 224^3 (784) 689 / 537 / 534, 192^3 (432) 479 / 375 / 358, 160^3 (300; 500 of the smaller) 476 /
+        // 372 / 257, 128^3 (256 of the smaller) 465 / 378 / 262, 112^3 280 / 379 / 261, 64^3 267 / 369 / 247.
+        const int workgroups = tiles * ((d->nz - kfirst + S.zc - 1) / S.zc);
+        if (G->bp_mirror && only < 0 && workgroups < (S.zc == 32 ? 800 : 250)) continue;
+        shapes.push_back(sh);
+    }
+    return shapes;
 }
 
 // Footprint model, tiled back projection: pick the template instance and verify its staged window.
@@ -286,16 +334,47 @@ static void select_footprint_tiled(leap_geometry *G)
         if (bp_instance_exists(G->bp_nc, G->bp_nv, (int)forced)) order[norder++] = (int)forced;
         for (int sh = std::max((int)forced + 1, BP_FIRST_SHORT_SHAPE); sh <= BP_LAST_SHORT_SHAPE; ++sh) order[norder++] = sh;
     }
-    for (int n = 0; n < norder && !G->bp_tiled; ++n) {
-        const int sh = order[n];
-        staged_window_need(G, BP_SHAPES[sh].zc,
-                           [&](const SfGeom &ga, const SfView &v, float xc, float yc, float z0, float z1) {
-                               return sf_bp_window(ga, v, xc, yc, hx, z0, z1, G->bp_wh, G->bp_nc, G->bp_nv);
-                           },
-                           G->bp_need_w, G->bp_need_h);
-        G->bp_shape = sh;
-        // one spare row and column: host and device floats may round apart
-        G->bp_tiled = G->bp_need_w <= BP_SHAPES[sh].pw - 1 && G->bp_need_h <= BP_SHAPES[sh].ph - 1;
+    // One volume per workgroup and two: the first shape of either kind that fits, a pair of shapes per pass over the tiles.  Two items of a
+    // batch take chunks of the same height as one, so that an item comes out the same bits in any batch: known when one's shape is.
+    const std::vector<int> pair_shapes = backproject_pair_shapes(G);
+    const int kfirst = G->bp_mirror ? sf_mirror_first_voxel_above(d->nz) : 0;
+    std::vector<WindowNeed> known;               // by height and first chunk: shapes of one height share theirs
+    auto need_of = [&](int zc, int from) {
+        return std::find_if(known.begin(), known.end(), [&](const WindowNeed &k) { return k.zc == zc && k.kfirst == from; });
+    };
+    for (size_t n = 0, p = 0;;) {
+        std::vector<WindowNeed> needs;
+        const bool single = n < (size_t)norder && !G->bp_tiled;
+        if (!G->bp_mirror)
+            while (!single && p < pair_shapes.size() && BP_PAIR_SHAPES[pair_shapes[p]].zc != BP_SHAPES[G->bp_shape].zc) ++p;
+        const bool pair = p < pair_shapes.size() && G->bp_pair_shape < 0 && (single ? G->bp_mirror : G->bp_tiled);
+        if (!single && !pair) break;
+        const int single_zc = single ? BP_SHAPES[order[n]].zc : 0, pair_zc = pair ? BP_PAIR_SHAPES[pair_shapes[p]].zc : 0;
+        if (single && need_of(single_zc, 0) == known.end()) needs.push_back({single_zc, 0});
+        if (pair && need_of(pair_zc, kfirst) == known.end()) needs.push_back({pair_zc, kfirst});
+        if (!needs.empty())
+            staged_window_needs(G, needs,
+                            [&](const SfGeom &ga, const SfView &v, float xc, float yc, SfWindow &w) {
+                                const SfTileBounds b = sf_bp_tile_bounds(ga, v, xc, yc, hx);
+                                sf_bp_window_columns(b, G->bp_wh, G->bp_nc, w.c0, w.need_w);
+                                return b;
+                            },
+                            [&](const SfGeom &ga, const SfTileBounds &b, float z0, float z1, SfWindow &w) {
+                                sf_bp_window_rows(ga, b, z0, z1, G->bp_nv, w.r0, w.need_h);
+                            });
+        known.insert(known.end(), needs.begin(), needs.end());
+        if (single) {
+            const WindowNeed &need = *need_of(single_zc, 0);
+            G->bp_need_w = need.w;
+            G->bp_need_h = need.h;
+            G->bp_shape = order[n];
+            G->bp_tiled = window_fits(need, BP_SHAPES[order[n]]);
+            ++n;
+        }
+        if (pair) {
+            if (window_fits(*need_of(pair_zc, kfirst), BP_PAIR_SHAPES[pair_shapes[p]])) G->bp_pair_shape = pair_shapes[p];
+            ++p;
+        }
     }
     // Cylinder: the tiled kernel takes the angle between a voxel's centre and its corners from a short series,
     // good to 3e-9 rad below 0.08 rad.
@@ -304,6 +383,7 @@ static void select_footprint_tiled(leap_geometry *G)
         const double nearest = d->sod - std::sqrt(rx * rx + ry * ry);
         if (!(0.7072 * d->voxel_xy <= 0.08 * nearest)) G->bp_tiled = false;
     }
+    if (!G->bp_tiled) G->bp_pair_shape = -1;
 }
 
 // Row groups per wave of the column-wise forward kernels.  A wave pays a fixed share per candidate voxel column (its
@@ -464,13 +544,17 @@ static void select_siddon_fast_kernels(leap_geometry *G)
         if (debug_option("bp_shape", first_shape))
             first_shape = std::min((long)BP_LAST_SHORT_SHAPE, std::max((long)BP_FIRST_SHORT_SHAPE, first_shape % BP_NSHAPES));
         for (int sh = (int)first_shape; sh <= BP_LAST_SHORT_SHAPE && !G->bp_tiled; ++sh) {
-            staged_window_need(G, BP_SHAPES[sh].zc,
-                               [&](const SfGeom &ga, const SfView &v, float xc, float yc, float z0, float z1) {
-                                   return sd_bp_window(ga, v, xc, yc, hx, z0, z1);
-                               },
-                               G->bp_need_w, G->bp_need_h);
+            struct Tile {
+                const SfView *v;
+                float xc, yc;
+            };
+            std::vector<WindowNeed> need = {{BP_SHAPES[sh].zc, 0}};
+            staged_window_needs(G, need, [&](const SfGeom &, const SfView &v, float xc, float yc, SfWindow &) { return Tile{&v, xc, yc}; },
+                                [&](const SfGeom &ga, const Tile &t, float z0, float z1, SfWindow &w) { w = sd_bp_window(ga, *t.v, t.xc, t.yc, hx, z0, z1); });
+            G->bp_need_w = need[0].w;
+            G->bp_need_h = need[0].h;
             G->bp_shape = sh;
-            G->bp_tiled = G->bp_need_w <= BP_SHAPES[sh].pw - 1 && G->bp_need_h <= BP_SHAPES[sh].ph - 1;
+            G->bp_tiled = window_fits(need[0], BP_SHAPES[sh]);
         }
     }
 }
@@ -1182,7 +1266,7 @@ extern "C" void leap_geometry_destroy(leap_geometry *G) { free_handle(G); }
 extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t cap)
 {
     if (!G || !buf || cap <= 0) return invalid("null handle or buffer");
-    char fwd[160], back[96];
+    char fwd[160], back[128];
     const bool siddon = G->g.model == SF_MODEL_SIDDON;
     if (siddon && G->sd_columns)
         std::snprintf(fwd, sizeof fwd, "columns(rg=%d,slab=%d%s)", G->fp_rg, G->slab_width, G->sd_pairs == 2 ? ",pairs apart" : (G->sd_pairs ? ",pairs" : ""));
@@ -1200,6 +1284,11 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
                       G->bp_shape == BP_WIDE_SHAPE ? ",wide" : "", G->bp_need_w, G->bp_need_h);
     else
         std::snprintf(back, sizeof back, G->flat ? "general(flat)" : (G->mf_tiled ? "general(tiled)" : "general"));
+    if (G->bp_pair_shape >= 0) {
+        const SfBpShape &S = BP_PAIR_SHAPES[G->bp_pair_shape];
+        const size_t n = std::strlen(back);
+        std::snprintf(back + n, sizeof back - n, "+%s(zc=%d,%dx%d)", G->bp_mirror ? "mirror" : "pairs", S.zc, S.pw, S.ph);
+    }
     const char *modules = G->g.type != SF_MODULAR ? "" : (G->geoms.empty() ? " (tilted modules)" : " (upright modules)");
     std::snprintf(buf, (size_t)cap, "type=%d model=%s A=%s AT=%s scratch=%zu%s cols/voxel<=%.2f rows/voxel<=%.2f voxels/row<=%.2f%s%s",
                   G->g.type, siddon ? "siddon" : "sf", fwd, back, G->scratch_bytes, modules, G->max_cols_per_voxel,

@@ -41,6 +41,16 @@ constexpr int BP_TALL_SHAPE = 5;
 // the limit there.)
 constexpr int BP_WIDE_SHAPE = 6;
 
+// Two volumes per thread (see sf_backproject_tiled): voxels per thread of either, window.  Tried in this order.
+constexpr SfBpShape BP_PAIR_SHAPES[] = {{32, 32, 44}, {32, 32, 56}, {16, 32, 44}, {16, 51, 48}, {8, 64, 32}};
+constexpr int BP_NPAIR_SHAPES = sizeof(BP_PAIR_SHAPES) / sizeof(BP_PAIR_SHAPES[0]);
+
+// ... and which footprints they are instantiated for: narrow windows up to four columns, wide ones from four on.
+constexpr bool bp_pair_instance_exists(int nc, int nv, int shape)
+{
+    return nv <= 3 && (BP_PAIR_SHAPES[shape].pw <= 32 ? nc <= 4 : nc >= 4);
+}
+
 // Is the footprint kernel instantiated for NC columns, NV rows and this shape?
 constexpr bool bp_instance_exists(int nc, int nv, int shape)
 {
@@ -102,50 +112,95 @@ struct SfCurvedBounds {
     float xi_lo, xi_hi, ilo, ihi;
 };
 
+// Column-coordinate range and range of 1 / den of a tile in a view: what a window takes from the plane.
+struct SfTileBounds {
+    float xi_lo, xi_hi, ilo, ihi;
+};
+
+template <int GT = -1>
+SF_HD SfTileBounds sf_bp_tile_bounds(const SfGeom &g, const SfView &v, float xc, float yc, float hx, const SfCurvedBounds *pre = nullptr)
+{
+    SfTileBounds b;
+    b.ilo = b.ihi = 1.0f;               // smallest / largest 1/den over the tile
+    if (sf_is_curved<GT>(g)) {
+        if (pre) {
+            b.xi_lo = pre->xi_lo; b.xi_hi = pre->xi_hi; b.ilo = pre->ilo; b.ihi = pre->ihi;
+        } else {
+            sf_curved_tile_bounds(g, v, xc, yc, hx, b.xi_lo, b.xi_hi, b.ilo, b.ihi);
+        }
+        return b;
+    }
+    const float tc = fmaf(yc, v.c, -xc * v.s);
+    const float rho = hx * (fabsf(v.c) + fabsf(v.s));
+    const float tlo = tc - rho, thi = tc + rho;
+    if (g.type != SF_PARALLEL) {
+        const float lc = fmaf(xc, v.c, yc * v.s);
+        // a ragged edge tile's padding voxels may reach the source plane: keep the distance positive (the window then
+        // comes out huge and the host rejects the kernel)
+        b.ilo = sf_rcp(g.sod - lc + rho);
+        b.ihi = sf_rcp(fmaxf(g.sod - lc - rho, 1e-6f * g.sod));
+    }
+    b.xi_lo = fmaf(g.ku * tlo, tlo >= 0.0f ? b.ilo : b.ihi, g.col_off);
+    b.xi_hi = fmaf(g.ku * thi, thi >= 0.0f ? b.ihi : b.ilo, g.col_off);
+    return b;
+}
+
+// Columns of the window of a tile with those bounds; rows for a chunk between the heights z0 and z1.
+SF_HD void sf_bp_window_columns(const SfTileBounds &b, float wh, int nc, int &c0, int &need_w)
+{
+    c0 = sf_f2i(floorf(b.xi_lo - wh + 0.48f));
+    need_w = sf_f2i(floorf(b.xi_hi + 0.52f)) + nc - c0;    // a thread reads nc columns from its first one
+}
+
+SF_HD void sf_bp_window_rows(const SfGeom &g, const SfTileBounds &b, float z0, float z1, int nv, int &r0, int &need_h)
+{
+    const float kv = (float)g.kvd, row_off = (float)g.row_offd;
+    const float eta_lo = fmaf(kv * z0, z0 >= 0.0f ? b.ilo : b.ihi, row_off);
+    const float eta_hi = fmaf(kv * z1, z1 >= 0.0f ? b.ihi : b.ilo, row_off);
+    r0 = sf_f2i(floorf(eta_lo - 0.02f));
+    need_h = sf_f2i(floorf(eta_hi + 0.02f)) + nv - r0;     // and nv rows from the first row of each voxel
+}
+
 template <int GT = -1>
 SF_HD SfWindow sf_bp_window(const SfGeom &g, const SfView &v, float xc, float yc, float hx, float z0, float z1, float wh,
                             int nc, int nv, const SfCurvedBounds *pre = nullptr)
 {
     SfWindow w;
-    const float tc = fmaf(yc, v.c, -xc * v.s);
-    const float rho = hx * (fabsf(v.c) + fabsf(v.s));
-    const float tlo = tc - rho, thi = tc + rho;
-    float ilo = 1.0f, ihi = 1.0f;       // smallest / largest 1/den over the tile
-    float xi_lo, xi_hi;
-    if (sf_is_curved<GT>(g)) {
-        if (pre) {
-            xi_lo = pre->xi_lo; xi_hi = pre->xi_hi; ilo = pre->ilo; ihi = pre->ihi;
-        } else {
-            sf_curved_tile_bounds(g, v, xc, yc, hx, xi_lo, xi_hi, ilo, ihi);
-        }
-    } else {
-        if (g.type != SF_PARALLEL) {
-            const float lc = fmaf(xc, v.c, yc * v.s);
-            // a ragged edge tile's padding voxels may reach the source plane: keep the distance positive (the window then
-            // comes out huge and the host rejects the kernel)
-            ilo = sf_rcp(g.sod - lc + rho);
-            ihi = sf_rcp(fmaxf(g.sod - lc - rho, 1e-6f * g.sod));
-        }
-        xi_lo = fmaf(g.ku * tlo, tlo >= 0.0f ? ilo : ihi, g.col_off);
-        xi_hi = fmaf(g.ku * thi, thi >= 0.0f ? ihi : ilo, g.col_off);
-    }
-    const float kv = (float)g.kvd, row_off = (float)g.row_offd;
-    const float eta_lo = fmaf(kv * z0, z0 >= 0.0f ? ilo : ihi, row_off);
-    const float eta_hi = fmaf(kv * z1, z1 >= 0.0f ? ihi : ilo, row_off);
-    w.c0 = sf_f2i(floorf(xi_lo - wh + 0.48f));
-    w.r0 = sf_f2i(floorf(eta_lo - 0.02f));
-    w.need_w = sf_f2i(floorf(xi_hi + 0.52f)) + nc - w.c0;    // a thread reads nc columns from its first one
-    w.need_h = sf_f2i(floorf(eta_hi + 0.02f)) + nv - w.r0;   // and nv rows from the first row of each voxel
+    const SfTileBounds b = sf_bp_tile_bounds<GT>(g, v, xc, yc, hx, pre);
+    sf_bp_window_columns(b, wh, nc, w.c0, w.need_w);
+    sf_bp_window_rows(g, b, z0, z1, nv, w.r0, w.need_h);
     return w;
 }
 
+// Two volumes per workgroup (NS == 2).  All weights, placements and window bounds are the same for both, and a sample of either
+// lies beside the other's in LDS, one 8-byte read (which the LDS serves as fast as a 4-byte one).  They are two items of a batch
+// or, where the detector and the volume are symmetric about the source plane, the volume's upper half and the mirror image of its
+// lower half: voxel k's partner is voxel nz - 1 - k, row r's row nrows - 1 - r, and the chunks start at voxel nz / 2.
+struct SfBpSets {
+    int mirror;
+    int kfirst;       // first voxel of the first chunk
+};
+SF_HD int sf_mirror_first_voxel_above(int nz) { return nz / 2; }
+
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
 
-// Staging, first half: fetch this thread's share of the window of one view into registers.  ya points at the view.
-template <int NC, int NV, int PW, int PH, int NSTAGE, int GT>
+// LDS row stride in samples.  Two volumes' samples are eight bytes: 12 and 8 more than the window are alike within a per cent, and
+// under the 51-column window 8 leave room for a third workgroup (5.59 against 5.78 ms, eight 256^3 volumes of 60 views).
+template <int NS>
+constexpr int bp_row_stride(int pw) { return pw + (NS == 2 && pw > 32 ? 8 : BP_ROW_PAD); }
+
+template <int NS>
+struct alignas(4 * NS) SfBpSample {
+    float v[NS];
+};
+
+// Staging, first half: fetch this thread's share of the window of one view into registers.  ya points at the view; yb - ya
+// (bytes) leads from a sample to its partner's row 0 in the same column, rows up (batch) or down (mirror).
+template <int NC, int NV, int PW, int PH, int NSTAGE, int GT, int NS>
 __device__ __forceinline__ void bp_load_view(const SfGeom &g, const SfView v, const float *__restrict__ ya, float xc, float yc,
                                              float hx, float z0, float z1, float wh, int sc, int sr, SfWindow &w,
-                                             float (&stage)[NSTAGE], const SfCurvedBounds *pre = nullptr)
+                                             SfBpSample<NS> (&stage)[NSTAGE], const SfCurvedBounds *pre, const char *__restrict__ y2,
+                                             bool mirror)
 {
     constexpr int RSTEP = 256 / PW;
     w = sf_bp_window<GT>(g, v, xc, yc, hx, z0, z1, wh, NC, NV, pre);
@@ -157,23 +212,30 @@ __device__ __forceinline__ void bp_load_view(const SfGeom &g, const SfView v, co
     // (unsigned arithmetic: offsets of rows off the detector wrap around harmlessly)
     unsigned off = ((unsigned)(w.r0 + sr) * (unsigned)g.ncols + (unsigned)(cin ? c : 0)) * 4u;
     const unsigned step = (unsigned)RSTEP * (unsigned)g.ncols * 4u;
+    // the partner's: the same offsets, or from the other end of the detector downwards
+    unsigned off2 = mirror ? ((unsigned)(g.nrows - 1 - w.r0 - sr) * (unsigned)g.ncols + (unsigned)(cin ? c : 0)) * 4u : off;
+    const unsigned step2 = mirror ? 0u - step : step;
 #pragma unroll
     for (int s = 0; s < NSTAGE; ++s) {
         const int r = w.r0 + sr + RSTEP * s;
         // (rows from need_h on are never read: whole steps beyond it are left out, here and in bp_store_view)
         const bool in = cin && (unsigned)r < (unsigned)g.nrows && (sr + RSTEP * s) < PH && RSTEP * s < w.need_h;
-        stage[s] = in ? *reinterpret_cast<const float *>(yb + off) : 0.0f;
+        stage[s].v[0] = in ? *reinterpret_cast<const float *>(yb + off) : 0.0f;
+        if constexpr (NS == 2) {
+            stage[s].v[1] = in ? *reinterpret_cast<const float *>(y2 + off2) : 0.0f;
+        }
         off += step;
+        off2 += step2;
     }
 }
 
 // Staging, second half: scale by the ray amplitude and write to LDS.
-template <int PW, int PH, int NSTAGE, int GT>
+template <int PW, int PH, int NSTAGE, int GT, int NS>
 __device__ __forceinline__ void bp_store_view(const SfGeom &g, const SfView v, int sc, int sr, const SfWindow &w,
-                                              const float (&stage)[NSTAGE], float *__restrict__ buf,
+                                              const SfBpSample<NS> (&stage)[NSTAGE], SfBpSample<NS> *__restrict__ buf,
                                               const float2 *__restrict__ colcs = nullptr)
 {
-    constexpr int RSTEP = 256 / PW, PS = PW + BP_ROW_PAD;
+    constexpr int RSTEP = 256 / PW, PS = bp_row_stride<NS>(PW);
     SfAmpCol ac;
     if (GT == 1 && colcs) {      // cylinder: cosine and sine of the column's fan angle from the per-column table
         int c = w.c0 + sc;
@@ -183,15 +245,22 @@ __device__ __forceinline__ void bp_store_view(const SfGeom &g, const SfView v, i
     } else {
         ac = sf_amp_col<GT>(g, v, w.c0 + sc);
     }
-    float vv = fmaf((float)(w.r0 + sr), g.pv, g.v0);      // this thread's first row; RSTEP rows further per element
-    const float dv = (float)RSTEP * g.pv;
+    // this thread's first row; RSTEP rows further per element (whole numbers, so that a row's v does not depend on the window it is
+    // staged in)
+    float rf = (float)(w.r0 + sr);
 #pragma unroll
     for (int s = 0; s < NSTAGE; ++s) {
         const int row = sr + RSTEP * s;
         if (RSTEP * s < w.need_h) {        // uniform over the workgroup
-            if (row < PH) buf[row * PS + sc] = stage[s] * sf_amp_at(g, v, ac, vv);
+            if (row < PH) {
+                const float amp = sf_amp_at(g, v, ac, fmaf(rf, g.pv, g.v0));
+                SfBpSample<NS> q;
+#pragma unroll
+                for (int e = 0; e < NS; ++e) q.v[e] = stage[s].v[e] * amp;
+                buf[row * PS + sc] = q;
+            }
         }
-        vv += dv;
+        rf += (float)RSTEP;
     }
 }
 
@@ -215,10 +284,11 @@ SF_HD SfBpScene sf_bp_scene(const SfGeom &g, int i0, int j0, int k0)
 
 // GT: 0 flat or parallel, 1 cylindrical detector, 2 modular geometry with upright modules (every view brings its own
 // parameter block geoms[a]: the scene translated so that the view is a circular cone-beam view; g holds the sizes).
-template <int NC, int NV, int BP_ZC, int BP_PW, int BP_PH, int GT>
-__global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC > 32) ? 3 : 4) void sf_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
+// NS: volumes per workgroup.
+template <int NC, int NV, int BP_ZC, int BP_PW, int BP_PH, int GT, int NS>
+__global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC * NS > 32) ? 3 : (NS == 2 && BP_PW > 42 && BP_ZC > 8 ? 3 : 4)) void sf_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
                                                             const float *__restrict__ sino, float *__restrict__ vol,
-                                                            int tiles_x, float wh, const void *__restrict__ aux)
+                                                            int tiles_x, float wh, const void *__restrict__ aux, SfBpSets sets)
 {
     // aux: GT == 2: the per-view parameter blocks; GT == 1: cosine and sine of every detector column's fan angle
     // (ncols pairs of floats), followed by the per-(tile, view) table
@@ -227,17 +297,20 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC > 32) ? 3 : 4) voi
     const SfCurvedBounds *__restrict__ cvt =
         GT == 1 ? reinterpret_cast<const SfCurvedBounds *>(static_cast<const float2 *>(aux) + g.ncols) + (size_t)blockIdx.x * g.nviews
                 : nullptr;
-    constexpr int BP_PS = BP_PW + BP_ROW_PAD;      // LDS row stride (floats)
-    __shared__ float patch[2][BP_PH * BP_PS];
-    // blockIdx.z: item of a batch
-    sino += (size_t)blockIdx.z * g.nviews * g.nrows * g.ncols;
-    vol += (size_t)blockIdx.z * g.nx * g.ny * g.nz;
+    constexpr int BP_PS = bp_row_stride<NS>(BP_PW);      // LDS row stride (samples)
+    using Sample = SfBpSample<NS>;
+    __shared__ Sample patch[2][BP_PH * BP_PS];
+    // blockIdx.z: item of a batch, or pair of items
+    const bool mirror = NS == 2 && sets.mirror;
+    sino += (size_t)blockIdx.z * (mirror ? 1 : NS) * g.nviews * g.nrows * g.ncols;
+    vol += (size_t)blockIdx.z * (mirror ? 1 : NS) * g.nx * g.ny * g.nz;
+    const size_t to_second = mirror ? 0 : (size_t)g.nviews * g.nrows * g.ncols;
 
     const int tid = threadIdx.x;
     const int ti = tid & (BP_T - 1), tj = tid >> 4;
     const int tx = blockIdx.x % tiles_x, ty = blockIdx.x / tiles_x;
     const int i0 = tx * BP_T, j0 = ty * BP_T;
-    const int k0 = blockIdx.y * BP_ZC;
+    const int k0 = (NS == 2 ? sets.kfirst : 0) + blockIdx.y * BP_ZC;
     const int i = i0 + ti, j = j0 + tj;
     const int ic = i < g.nx ? i : g.nx - 1, jc = j < g.ny ? j : g.ny - 1;   // out-of-volume threads shadow the edge
 
@@ -252,11 +325,13 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC > 32) ? 3 : 4) voi
     constexpr int NSTAGE = (BP_PH + 256 / BP_PW - 1) / (256 / BP_PW);
     const size_t view_stride = (size_t)g.nrows * g.ncols;
 
-    float acc[BP_ZC];
+    float acc[BP_ZC][NS];
 #pragma unroll
-    for (int kk = 0; kk < BP_ZC; ++kk) acc[kk] = 0.0f;
+    for (int kk = 0; kk < BP_ZC; ++kk)
+#pragma unroll
+        for (int e = 0; e < NS; ++e) acc[kk][e] = 0.0f;
 
-    float stage[NSTAGE];
+    Sample stage[NSTAGE];
     SfWindow win_next;
 
     // tile centre in double (cylinder only)
@@ -267,20 +342,21 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC > 32) ? 3 : 4) voi
     };
 
     SfWindow win;
-    bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT>(geom_of(0), views[0], sino, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1, wh,
-                                                   sc, sr, win, stage, cv_pre(0));
+    bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(0), views[0], sino, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1, wh,
+                                                       sc, sr, win, stage, cv_pre(0), reinterpret_cast<const char *>(sino + to_second), mirror);
     win_next = win;
-    bp_store_view<BP_PW, BP_PH, NSTAGE, GT>(geom_of(0), views[0], sc, sr, win, stage, patch[0], colcs);
+    bp_store_view<BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(0), views[0], sc, sr, win, stage, patch[0], colcs);
     __syncthreads();
 
     for (int a = 0; a < g.nviews; ++a) {
-        const float *buf = patch[a & 1];
+        const Sample *buf = patch[a & 1];
         double gref = 0.0;
         if constexpr (GT == 1) gref = cvt[a].gref;
         if (a + 1 < g.nviews) {    // global loads in flight during the gather
             const SfBpScene sn = GT == 2 ? sf_bp_scene<BP_ZC>(geom_of(a + 1), i0, j0, k0) : scene0;
-            bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT>(geom_of(a + 1), views[a + 1], sino + (size_t)(a + 1) * view_stride, sn.xc,
-                                                           sn.yc, hx, sn.z0, sn.z1, wh, sc, sr, win_next, stage, cv_pre(a + 1));
+            const float *ya = sino + (size_t)(a + 1) * view_stride;
+            bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a + 1), views[a + 1], ya, sn.xc, sn.yc, hx, sn.z0, sn.z1, wh, sc, sr,
+                                                               win_next, stage, cv_pre(a + 1), reinterpret_cast<const char *>(ya + to_second), mirror);
         }
         const SfGeom &gv = geom_of(a);
         const double zlo_k0 = GT == 2 ? fma((double)k0, gv.Tzd, gv.zlo0d) : scene0.zlo_k0;
@@ -317,95 +393,129 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC > 32) ? 3 : 4) voi
         // short voxels even when the nearest voxels of the volume are tall; a wave that holds both kinds (rare: the line
         // where a voxel is exactly one row tall crosses its 16 x 4 columns) runs the two schemes one after the other.
         const bool shared_rows = NV == 2 || (NV == 3 ? ax.av <= 1.0f : __builtin_amdgcn_ballot_w64(ax.av > 1.0f) == 0);
-        auto row_sum = [&](const float *q) {
-            float s = fu[0] * q[0];
-#pragma unroll
-            for (int m = 1; m < NC; ++m) s = fmaf(fu[m], q[m], s);
-            return s;
-        };
         // The voxel's first row is carried as a byte offset into the patch array (both buffers), so that every LDS read is
         // that register plus an immediate and a row crossing costs one select and one add.
+        constexpr unsigned ROW = (unsigned)(BP_PS * sizeof(Sample));
         const char *const lds0 = reinterpret_cast<const char *>(&patch[0][0]);
-        unsigned pb = (unsigned)((a & 1) * (BP_PH * BP_PS) + (int)ofs) * 4u;
-        auto at = [&](unsigned byte_ofs) { return reinterpret_cast<const float *>(lds0 + byte_ofs); };
+        const unsigned lds_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) Sample *)&patch[0][0];
+        unsigned pb = (unsigned)((a & 1) * (BP_PH * BP_PS) + (int)ofs) * (unsigned)sizeof(Sample);
+        struct Sum {
+            float v[NS];
+        };
+        auto sample = [&](unsigned byte_ofs) {
+            if constexpr (NS == 1) {
+                return *reinterpret_cast<const Sample *>(lds0 + byte_ofs);
+            } else {
+                // (volatile: two merged into one 16-byte access at 8-byte alignment cost twice their time apart)
+                typedef const volatile __attribute__((address_space(3))) unsigned long long Lds;
+                const unsigned long long q = *(Lds *)(uintptr_t)(lds_at + byte_ofs);
+                Sample r;
+                __builtin_memcpy(&r, &q, 8);
+                return r;
+            }
+        };
+        auto row_sum = [&](unsigned byte_ofs) {
+            Sum s;
+            Sample q[NC];
+#pragma unroll
+            for (int m = 0; m < NC; ++m) q[m] = sample(byte_ofs + m * (unsigned)sizeof(Sample));
+#pragma unroll
+            for (int e = 0; e < NS; ++e) {
+                s.v[e] = fu[0] * q[0].v[e];
+#pragma unroll
+                for (int m = 1; m < NC; ++m) s.v[e] = fmaf(fu[m], q[m].v[e], s.v[e]);
+            }
+            return s;
+        };
+        // An opaque dependency every few voxels: the LDS reads of the next group need `pb` / `ofs`, which is only available once
+        // this group's sums exist.  Without it the compiler issues all reads of the unrolled loop first and spills them.
+        auto hold = [&](int kk, unsigned &reg) {
+            if constexpr (NS == 1) {
+                if ((kk & 3) == 3)
+                    asm volatile("" : "+v"(reg), "+v"(acc[kk - 3][0]), "+v"(acc[kk - 2][0]), "+v"(acc[kk - 1][0]), "+v"(acc[kk][0]));
+            } else {
+                if ((kk & 1) == 1)
+                    asm volatile("" : "+v"(reg), "+v"(acc[kk - 1][0]), "+v"(acc[kk - 1][1]), "+v"(acc[kk][0]), "+v"(acc[kk][1]));
+            }
+        };
         if (shared_rows) {
             // A voxel is at most one row tall, so consecutive voxels share a row: keep the u-combined samples of the
             // current and the next row in registers and fetch one new row per voxel (half the LDS traffic).
             // f: where the voxel's lower face lies inside its first row, in [0,1); the face moves up by av per voxel.
             float f = ax.phi0;
-            float s_cur = row_sum(at(pb)), s_next = row_sum(at(pb + 4u * BP_PS));
+            Sum s_cur = row_sum(pb), s_next = row_sum(pb + ROW);
 #pragma unroll
             for (int kk = 0; kk < BP_ZC; ++kk) {
                 const float t = f + ax.av;                        // upper face, still measured from the first row
                 const float w1 = sf_clamp(t - 1.0f, 0.0f, 1.0f);  // part of the voxel in the next row
                 const float w0 = ax.av - w1;
-                acc[kk] = fmaf(w1, s_next, fmaf(w0, s_cur, acc[kk]));
+#pragma unroll
+                for (int e = 0; e < NS; ++e) acc[kk][e] = fmaf(w1, s_next.v[e], fmaf(w0, s_cur.v[e], acc[kk][e]));
                 if (kk + 1 < BP_ZC) {
                     const bool cross = t >= 1.0f;                 // the next voxel starts in the next row
-                    pb += cross ? 4u * BP_PS : 0u;
-                    const float s_new = row_sum(at(pb + 4u * BP_PS));   // equals s_next when no row was crossed
-                    s_cur = cross ? s_next : s_cur;
+                    pb += cross ? ROW : 0u;
+                    const Sum s_new = row_sum(pb + ROW);          // equals s_next when no row was crossed
+#pragma unroll
+                    for (int e = 0; e < NS; ++e) s_cur.v[e] = cross ? s_next.v[e] : s_cur.v[e];
                     s_next = s_new;
                     f = cross ? w1 : t;                           // t - 1 where a row was crossed
                 }
-                if ((kk & 3) == 3)
-                    asm volatile("" : "+v"(pb), "+v"(acc[kk - 3]), "+v"(acc[kk - 2]), "+v"(acc[kk - 1]), "+v"(acc[kk]));
+                hold(kk, pb);
             }
         } else if constexpr (NV == 3) {
             // Between one and two rows tall: a voxel covers the rest of its first row, then up to one whole row, then
             // part of a third, and the next voxel starts one or two rows further: the u-combined sum of that row is
             // carried over (one select), the two rows after it are fetched fresh.
             float f = ax.phi0;
-            float s0 = row_sum(at(pb)), s1 = row_sum(at(pb + 4u * BP_PS)), s2 = row_sum(at(pb + 8u * BP_PS));
+            Sum s0 = row_sum(pb), s1 = row_sum(pb + ROW), s2 = row_sum(pb + 2u * ROW);
 #pragma unroll
             for (int kk = 0; kk < BP_ZC; ++kk) {
                 const float t = f + ax.av;                        // upper face from the first row's lower edge: in (1, 3)
                 const float w2 = sf_clamp(t - 2.0f, 0.0f, 1.0f);  // part in the third row
                 const float w0 = 1.0f - f;                        // the rest of the first row
                 const float w1 = (ax.av - w0) - w2;
-                acc[kk] = fmaf(w2, s2, fmaf(w1, s1, fmaf(w0, s0, acc[kk])));
+#pragma unroll
+                for (int e = 0; e < NS; ++e) acc[kk][e] = fmaf(w2, s2.v[e], fmaf(w1, s1.v[e], fmaf(w0, s0.v[e], acc[kk][e])));
                 if (kk + 1 < BP_ZC) {
                     const bool two = t >= 2.0f;                   // the next voxel starts two rows further
-                    pb += two ? 8u * BP_PS : 4u * BP_PS;
-                    s0 = two ? s2 : s1;
-                    s1 = row_sum(at(pb + 4u * BP_PS));
-                    s2 = row_sum(at(pb + 8u * BP_PS));
+                    pb += two ? 2u * ROW : ROW;
+#pragma unroll
+                    for (int e = 0; e < NS; ++e) s0.v[e] = two ? s2.v[e] : s1.v[e];
+                    s1 = row_sum(pb + ROW);
+                    s2 = row_sum(pb + 2u * ROW);
                     f = two ? w2 : t - 1.0f;                      // t - 2 where two rows were crossed
                 }
-                if ((kk & 3) == 3)
-                    asm volatile("" : "+v"(pb), "+v"(acc[kk - 3]), "+v"(acc[kk - 2]), "+v"(acc[kk - 1]), "+v"(acc[kk]));
+                hold(kk, pb);
             }
         } else if constexpr (NV > 3) {
-        float lo = ax.phi0;
+            static_assert(NS == 1, "taller footprints are back projected one volume at a time");
+            const float *bufs = reinterpret_cast<const float *>(buf);
+            float lo = ax.phi0;
 #pragma unroll
-        for (int kk = 0; kk < BP_ZC; ++kk) {
-            const float hi = fmaf(ax.av, (float)(kk + 1), ax.phi0);
-            const float fl = floorf(lo);
-            const float *q = buf + (ofs + __umul24((unsigned)(int)fl, (unsigned)BP_PS));   // 24-bit multiply: one full-rate op
-            float edge = fl + 1.0f;                                   // upper edge of the first row the voxel touches
-            float w = fminf(edge, hi) - lo;
-            float sum = acc[kk];
+            for (int kk = 0; kk < BP_ZC; ++kk) {
+                const float hi = fmaf(ax.av, (float)(kk + 1), ax.phi0);
+                const float fl = floorf(lo);
+                const float *q = bufs + (ofs + __umul24((unsigned)(int)fl, (unsigned)BP_PS));   // 24-bit multiply: one full-rate op
+                float edge = fl + 1.0f;                                   // upper edge of the first row the voxel touches
+                float w = fminf(edge, hi) - lo;
+                float sum = acc[kk][0];
 #pragma unroll
-            for (int jj = 0; jj < NV; ++jj) {
-                float s = fu[0] * q[jj * BP_PS];
+                for (int jj = 0; jj < NV; ++jj) {
+                    float s = fu[0] * q[jj * BP_PS];
 #pragma unroll
-                for (int m = 1; m < NC; ++m) s = fmaf(fu[m], q[jj * BP_PS + m], s);
-                sum = fmaf(w, s, sum);
-                w = sf_clamp(hi - edge, 0.0f, 1.0f);                  // overlap with the next row
-                edge += 1.0f;
+                    for (int m = 1; m < NC; ++m) s = fmaf(fu[m], q[jj * BP_PS + m], s);
+                    sum = fmaf(w, s, sum);
+                    w = sf_clamp(hi - edge, 0.0f, 1.0f);                  // overlap with the next row
+                    edge += 1.0f;
+                }
+                acc[kk][0] = sum;
+                lo = hi;
+                hold(kk, ofs);
             }
-            acc[kk] = sum;
-            lo = hi;
-            // An opaque dependency every few voxels: the LDS reads of the next group need `ofs`, which is only
-            // available once this group's sums exist.  Without it the compiler issues all reads of the unrolled
-            // loop first and spills them.
-            if ((kk & 3) == 3)
-                asm volatile("" : "+v"(ofs), "+v"(acc[kk - 3]), "+v"(acc[kk - 2]), "+v"(acc[kk - 1]), "+v"(acc[kk]));
-        }
         }
 
         if (a + 1 < g.nviews)
-            bp_store_view<BP_PW, BP_PH, NSTAGE, GT>(geom_of(a + 1), views[a + 1], sc, sr, win_next, stage, patch[(a + 1) & 1], colcs);
+            bp_store_view<BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a + 1), views[a + 1], sc, sr, win_next, stage, patch[(a + 1) & 1], colcs);
         win = win_next;
         __syncthreads();
     }
@@ -413,7 +523,14 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC > 32) ? 3 : 4) voi
     if (i < g.nx && j < g.ny) {
 #pragma unroll
         for (int kk = 0; kk < BP_ZC; ++kk)
-            if (k0 + kk < g.nz) vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = acc[kk];
+            if (k0 + kk < g.nz) {
+                const int k = k0 + kk;
+                vol[((size_t)k * g.ny + j) * g.nx + i] = acc[kk][0];
+                if constexpr (NS == 2) {
+                    const int k2 = mirror ? g.nz - 1 - k : k + g.nz;      // (an odd volume's middle layer is its own mirror image)
+                    if (k2 != k) vol[((size_t)k2 * g.ny + j) * g.nx + i] = acc[kk][1];
+                }
+            }
     }
 }
 

@@ -1,0 +1,84 @@
+"""Footprint back projection with two volumes per workgroup: a volume and its mirror image about the source plane, two items of a batch.
+
+Odd and even layers and rows (the middle layer is its own mirror image), ragged tiles and chunks, every window shape, parallel, flat
+and cylindrical detectors, against the oracle; off-centre detectors and volumes, which are not mirrored; batches bit for bit."""
+import pytest
+
+from synthetic import config, reduced, uniform_sinogram
+from synthetic.configs import CONE, CONE_CURVED, PARALLEL
+from tests.test_gpu_parity import TOL, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_mod():
+    import torch
+    return torch
+
+
+def scan(geometry, nz, nrows, pixel, nx=37, ny=34, **kw):
+    par = geometry == PARALLEL
+    return reduced(config(3), 8, nviews=10).replace(geom=geometry, nx=nx, ny=ny, nz=nz, voxel_xy=1.0, voxel_z=1.0, nrows=nrows,
+                                                    ncols=61, pixel_u=pixel, pixel_v=pixel, sod=0.0 if par else 150.0, sdd=0.0 if par else 225.0,
+                                                    shift_u=0.3, **kw)
+
+
+SIZES = [(9, 16), (40, 50), (41, 50), (41, 51), (70, 73), (131, 128)]
+# pixel (mm, at the detector) and window shape; the wide windows, for voxels of three columns and more, on diverging beams
+CASES = [(g, nz, nrows, pixel, shape) for g in (PARALLEL, CONE, CONE_CURVED) for nz, nrows in SIZES for pixel, shape in ((2.4, 0), (1.8, 1), (2.4, 2))]
+CASES += [(g, nz, nrows, 1.2, shape) for g in (CONE, CONE_CURVED) for nz, nrows in SIZES[:5] for shape in (3, 4)]
+
+
+@pytest.mark.parametrize("geometry,nz,nrows,pixel,shape", CASES)
+def test_mirror_image(torch_mod, oracle_mod, monkeypatch, geometry, nz, nrows, pixel, shape):
+    from paper_2307_05801_amd import Geometry
+    if geometry == PARALLEL:
+        pixel /= 1.5
+    monkeypatch.setenv("LEAP_DEBUG", f"bp_pair={shape}")
+    cfg = scan(geometry, nz, nrows, pixel)
+    geo = Geometry(cfg)
+    assert "+mirror" in geo.describe(), geo.describe()
+    print(f"[gpu] {geometry} {nz} {nrows} {pixel}: {geo.describe()}", flush=True)
+    y = uniform_sinogram(cfg, 7, batch=2)
+    yt = torch_mod.from_numpy(y).cuda()
+    out = geo.backproject(yt)
+    for b in range(2):
+        assert rel_l2(out[b].cpu().numpy(), oracle_mod.backproject(cfg, y[b])) <= TOL      # the parity tests' tolerance
+        assert torch_mod.equal(out[b], geo.backproject(yt[b].contiguous()))
+    geo.close()
+
+
+@pytest.mark.parametrize("geometry", [CONE, CONE_CURVED])
+@pytest.mark.parametrize("off", [dict(shift_v=0.25), dict(center_z=1.5)])
+def test_no_mirror_image_off_centre(torch_mod, oracle_mod, geometry, off):
+    """Two items per workgroup instead, the same bits as alone whatever the batch."""
+    from paper_2307_05801_amd import Geometry
+    cfg = scan(geometry, 40, 50, 1.4, **off)
+    geo = Geometry(cfg)
+    print(f"[gpu] {off}: {geo.describe()}", flush=True)
+    assert "+mirror" not in geo.describe(), geo.describe()
+    y = uniform_sinogram(cfg, 8, batch=5)
+    yt = torch_mod.from_numpy(y).cuda()
+    out = geo.backproject(yt)
+    for b in (0, 3, 4):
+        assert rel_l2(out[b].cpu().numpy(), oracle_mod.backproject(cfg, y[b])) <= TOL
+    for batch in (1, 2, 3, 4):
+        got = geo.backproject(yt[:batch].contiguous())
+        assert torch_mod.equal(out[:batch], got), batch
+    geo.close()
+
+
+def test_a_sample_that_is_not_finite_stays_in_its_half(torch_mod):
+    """A voxel and its mirror image share weights, not samples."""
+    from paper_2307_05801_amd import Geometry
+    cfg = scan(CONE, 256, 280, 2.0, nx=150, ny=150).replace(sod=500.0, sdd=750.0)
+    geo = Geometry(cfg)
+    assert "+mirror" in geo.describe(), geo.describe()
+    y = torch_mod.rand(cfg.sino_shape, device="cuda")
+    ref = geo.backproject(y)
+    y[3, 200, 30] = float("inf")
+    out = geo.backproject(y)
+    assert torch_mod.equal(out[:128], ref[:128])
+    assert bool((~out[128:].isfinite()).any())
+    geo.close()
