@@ -161,15 +161,17 @@ SF_HD void sf_place_row(double rd, double mu, double zkp, float &fr1, unsigned &
 // Voxels a row can overlap when a pair of rows overlaps P: rows of up to (P - 1) / 2 voxels.
 constexpr int sf_single_of_pair(int P) { return P / 2 + 1; }
 
-// Axial weights of a pair of adjacent rows.  x[0..P-1]: voxels from the one holding the lower row's lower edge; fr1 as
+// Axial sums of a pair of adjacent rows.  x[0..P-1]: voxels from the one holding the lower row's lower edge; fr1 as
 // above; mu = voxels per row.  The lower row A covers [fr, fr + mu) of that run, the upper row B [fr + mu, fr + 2 mu).  With
-// a_t = clamp(fr + mu - t) and b_t = clamp(fr + 2 mu - t), the parts of voxel t below either row's upper edge, voxel t weighs a_t in A
-// and b_t - a_t in B for t >= 1; voxel 0 weighs 1 - fr in A (rows of a voxel and more) or mu - a_1 (shorter rows), and in B, which reaches
-// it where rows are shorter than a voxel, 1 - fr - mu (rows of half a voxel and more) or what the other voxels leave.
+// a_t = clamp(fr + mu - t) and b_t = clamp(fr + 2 mu - t), the parts of voxel t below either row's upper edge (additions with the clamp
+// modifier are the cheapest way to an overlap), and rows shorter than a voxel, with d_t = x_t - x_0,
+//   S_A = mu x_0 + sum a_t d_t,    S_B = 2 mu x_0 + sum b_t d_t - S_A     (voxel 0 gets what the others leave of each row),
+// rows of a voxel and more
+//   S_A = (1 - fr) x_0 + sum a_t x_t,    S_B = sum (b_t - a_t) x_t        (t >= 1; the upper row does not reach voxel 0).
 // Rows are sorted into classes by their height, LO2 / 2 <= mu <= HI2 / 2, so that what is known to be 0 or 1 costs nothing: a pair
-// of rows of up to one voxel reads three voxels and takes six instructions for its weights and five for its sums, one of up to a
-// voxel and a half four voxels, seven and six (sixteen while one body served every height up to a voxel and a half).  The
-// weights depend on no voxel, so a lane that carries several volumes forms them once.
+// of rows of up to one voxel reads three voxels and takes eleven instructions, one of up to a voxel and a half four and thirteen
+// (sixteen while one body served every height up to a voxel and a half).  The clamps and weights depend on no voxel, so a lane that
+// carries several volumes forms them once.
 // Offsets of the clamps, the same for every row of the detector, worked out once per candidate: ka[t-1] = mu - (t+1), kb[t-1] = 2 mu - (t+1).
 struct SfPairOffsets {
     float mu;
@@ -192,7 +194,7 @@ template <int LO2, int HI2>
 struct SfPairWeights {
     static constexpr int P = HI2 + 1;                 // voxels a pair can overlap
     static constexpr int NA = (HI2 + 3) / 2;          // voxels the lower row can overlap
-    static constexpr int B0 = LO2 >= 2 ? 1 : 0;       // first voxel the upper row can overlap
+    static constexpr bool SHORT = LO2 < 2;            // rows shorter than a voxel: a and b are a_t and b_t, otherwise weights
     float a[NA], b[P];
 };
 
@@ -201,16 +203,15 @@ SF_HD SfPairWeights<LO2, HI2> sf_pair_weights(float fr1, const SfPairOffsets &k)
 {
     using W = SfPairWeights<LO2, HI2>;
     W w;
+    w.a[0] = W::SHORT ? k.mu : 2.0f - fr1;
+    w.b[0] = 0.0f;
 #pragma unroll
     for (int t = 1; t < W::NA; ++t) w.a[t] = LO2 >= 2 * (t + 1) ? 1.0f : sf_clamp(fr1 + k.ka[t - 1], 0.0f, 1.0f);
-    w.a[0] = LO2 >= 2 ? 2.0f - fr1 : k.mu - w.a[1];
-    w.b[0] = LO2 >= 2 ? 0.0f : sf_clamp(-k.ka[0] - fr1, 0.0f, 1.0f);          // (LO2 == 0: below)
 #pragma unroll
     for (int t = 1; t < W::P; ++t) {
         const float upto = LO2 >= t + 1 ? 1.0f : sf_clamp(fr1 + k.kb[t - 1], 0.0f, 1.0f);
-        w.b[t] = t < W::NA ? upto - w.a[t] : upto;
+        w.b[t] = !W::SHORT && t < W::NA ? upto - w.a[t] : upto;
     }
-    if (LO2 == 0) w.b[0] = k.mu - w.b[1];
     return w;
 }
 
@@ -218,14 +219,25 @@ template <int LO2, int HI2>
 SF_HD void sf_pair_apply(const float *x, const SfPairWeights<LO2, HI2> &w, float &sa, float &sb)
 {
     using W = SfPairWeights<LO2, HI2>;
-    sa = w.a[0] * x[0];
+    const float a0 = w.a[0] * x[0];
+    sa = a0;
+    if constexpr (W::SHORT) {
+        float d[W::P];
 #pragma unroll
-    for (int t = 1; t < W::NA; ++t) sa = (LO2 >= 2 * (t + 1)) ? sa + x[t] : fmaf(w.a[t], x[t], sa);
-    sb = w.b[W::B0] * x[W::B0];
+        for (int t = 1; t < W::P; ++t) d[t] = x[t] - x[0];
 #pragma unroll
-    for (int t = W::B0 + 1; t < W::P; ++t) {
-        if (LO2 >= t + 1 && t < W::NA && LO2 >= 2 * (t + 1)) continue;       // the lower row holds all of it
-        sb = fmaf(w.b[t], x[t], sb);
+        for (int t = 1; t < W::NA && t < W::P; ++t) sa = fmaf(w.a[t], d[t], sa);
+        float b = a0 + a0;                              // 2 mu x_0, exactly
+#pragma unroll
+        for (int t = 1; t < W::P; ++t) b = fmaf(w.b[t], d[t], b);
+        sb = b - sa;
+    } else {
+#pragma unroll
+        for (int t = 1; t < W::NA; ++t) sa = LO2 >= 2 * (t + 1) ? sa + x[t] : fmaf(w.a[t], x[t], sa);
+        constexpr int FIRST = LO2 >= 4 ? 2 : 1;         // (the lower row holds all of voxel 1 from two voxels on)
+        sb = w.b[FIRST] * x[FIRST];
+#pragma unroll
+        for (int t = FIRST + 1; t < W::P; ++t) sb = fmaf(w.b[t], x[t], sb);
     }
 }
 
@@ -384,7 +396,7 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
     // translated so that the view is a circular cone-beam view; gk holds the sizes, which all views share.
     const SfGeom &gsz = gk;
     // blockIdx.y: NS items of a batch (their scratch copies and sinograms).  Everything but the voxels and the sums is the same for
-    // two items: candidates, records, placement and axial weights are formed once (eight 256^3 volumes of 60 views, 7.4 -> 7.05 ms).
+    // two items: candidates, records, placement and axial weights are formed once (eight 256^3 volumes of 60 views, 7.6 -> 7.1 ms).
     const size_t nsino = (size_t)gk.nviews * gk.nrows * gk.ncols;
     volz += (size_t)blockIdx.y * NS * item_stride;
     sino += (size_t)blockIdx.y * NS * nsino;
