@@ -47,18 +47,32 @@ static bool launch_bp_shape(const leap_geometry *G, const float *d_sino, float *
 int leap_launch_footprint_back(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     bool ok = false;
+    if (G->bp_split_shape >= 0) {
+        if (!leap_launch_backproject_split(G, d_sino, d_vol, items, stream)) {
+            leap_set_error("internal: no back-projection instance that shares the views for this footprint");
+            return LEAP_UNSUPPORTED;
+        }
+        LEAP_HIP_CHECK(hipGetLastError());
+        return LEAP_OK;
+    }
     if (G->bp_pair_shape >= 0) {
         // two volumes per workgroup: an item and its mirror image, or two items of the batch; an odd last item by itself
-        const int blocks = G->bp_mirror ? items : items / 2;
+        int blocks = G->bp_mirror ? items : items / 2;
+        // Two items where there are workgroups enough (the bits are the same): eight volumes, 60 views, one by one / in twos, us: 32 voxels per
+        // thread 64^3 (128 workgroups of two) 145 / 195, 96^3 (432) 209 / 193; wide windows 64^3 (256) 202 / 230, 96^3 (864) 419 / 434, 128^3
+        // (2048) 890 / 742.
+        const SfBpShape S = BP_PAIR_SHAPES[G->bp_pair_shape];
+        if (!G->bp_mirror && cdiv(G->g.nx, BP_T) * cdiv(G->g.ny, BP_T) * cdiv(G->g.nz, S.zc) * (unsigned)blocks < (S.pw > 32 ? 1200u : 400u)) blocks = 0;
         if (blocks && !leap_launch_backproject_pairs(G, d_sino, d_vol, blocks, stream)) {
             leap_set_error("internal: no back-projection instance of two volumes for this footprint");
             return LEAP_UNSUPPORTED;
         }
         LEAP_HIP_CHECK(hipGetLastError());
-        if (G->bp_mirror || items % 2 == 0) return LEAP_OK;
-        d_sino += (size_t)(items - 1) * G->g.nviews * G->g.nrows * G->g.ncols;
-        d_vol += (size_t)(items - 1) * G->g.nx * G->g.ny * G->g.nz;
-        items = 1;
+        const int done = G->bp_mirror ? items : 2 * blocks;
+        if (done == items) return LEAP_OK;
+        d_sino += (size_t)done * G->g.nviews * G->g.nrows * G->g.ncols;
+        d_vol += (size_t)done * G->g.nx * G->g.ny * G->g.nz;
+        items -= done;
     }
     switch (G->bp_nc * 10 + G->bp_nv) {
     case 22: ok = launch_bp_shape<2, 2>(G, d_sino, d_vol, stream, items); break;

@@ -28,13 +28,12 @@ static bool launch_instance(const leap_geometry *G, const float *d_sino, float *
 template <int NC, int NV>
 static bool launch_shape(const leap_geometry *G, const float *d_sino, float *d_vol, int blocks, hipStream_t stream)
 {
-    static_assert(BP_NPAIR_SHAPES == 5, "every shape has a case");
+    static_assert(BP_NPAIR_SHAPES == 4, "every shape has a case");
     switch (G->bp_pair_shape) {
     case 0: return launch_instance<NC, NV, 0>(G, d_sino, d_vol, blocks, stream);
     case 1: return launch_instance<NC, NV, 1>(G, d_sino, d_vol, blocks, stream);
     case 2: return launch_instance<NC, NV, 2>(G, d_sino, d_vol, blocks, stream);
     case 3: return launch_instance<NC, NV, 3>(G, d_sino, d_vol, blocks, stream);
-    case 4: return launch_instance<NC, NV, 4>(G, d_sino, d_vol, blocks, stream);
     default: return false;
     }
 }

@@ -1,0 +1,71 @@
+// Launchers of the tiled footprint back projection with four groups of threads per workgroup that share the views.
+#include <hip/hip_runtime.h>
+
+#include "leap_internal.h"
+#include "sf_backproject_tiled.h"
+
+template <int NC, int NV, int SH, int NS>
+static bool launch_instance(const leap_geometry *G, const float *d_sino, float *d_vol, int blocks, hipStream_t stream)
+{
+    if constexpr (bp_split_instance_exists(NC, NV, SH)) {
+        constexpr SfBpShape S = BP_SPLIT_SHAPES[SH];
+        const SfGeom &g = G->g;
+        const bool mirror = NS == 2 && G->bp_mirror;
+        const SfBpSets sets = {mirror ? 1 : 0, mirror ? sf_mirror_first_voxel_above(g.nz) : 0};
+        const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
+        const dim3 grid(tiles_x * tiles_y, cdiv(g.nz - sets.kfirst, S.zc), (unsigned)blocks);
+        auto go = [&](auto kernel, const void *aux) {
+            hipLaunchKernelGGL(kernel, grid, dim3(256 * BP_SPLIT), 0, stream, g, G->d_views, d_sino, d_vol, (int)tiles_x, G->bp_wh, aux, sets);
+        };
+        if (g.type == SF_CONE_CURVED) {
+            go(sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, 1, NS, BP_SPLIT>, G->d_colcs);
+        } else if (g.type == SF_MODULAR) {
+            if constexpr (NS == 1) go(sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, 2, NS, BP_SPLIT>, G->d_geoms);
+            else return false;
+        } else {
+            go(sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, 0, NS, BP_SPLIT>, nullptr);
+        }
+        return true;
+    } else {
+        return false;
+    }
+}
+
+template <int NC, int NV, int NS>
+static bool launch_shape(const leap_geometry *G, const float *d_sino, float *d_vol, int blocks, hipStream_t stream)
+{
+    static_assert(BP_NSPLIT_SHAPES == 3, "every shape has a case");
+    switch (G->bp_split_shape) {
+    case 0: return launch_instance<NC, NV, 0, NS>(G, d_sino, d_vol, blocks, stream);
+    case 1: return launch_instance<NC, NV, 1, NS>(G, d_sino, d_vol, blocks, stream);
+    case 2: return launch_instance<NC, NV, 2, NS>(G, d_sino, d_vol, blocks, stream);
+    default: return false;
+    }
+}
+
+template <int NC, int NV>
+static bool launch_sets(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
+{
+    // two volumes per workgroup: an item and its mirror image, or two items of the batch; an odd last item by itself
+    const bool two = G->g.type != SF_MODULAR;
+    const int pairs = G->bp_mirror ? items : (two ? items / 2 : 0), left = G->bp_mirror ? 0 : items - 2 * pairs;
+    if (pairs && !launch_shape<NC, NV, 2>(G, d_sino, d_vol, pairs, stream)) return false;
+    d_sino += (size_t)(items - left) * G->g.nviews * G->g.nrows * G->g.ncols;
+    d_vol += (size_t)(items - left) * G->g.nx * G->g.ny * G->g.nz;
+    return !left || launch_shape<NC, NV, 1>(G, d_sino, d_vol, left, stream);
+}
+
+bool leap_launch_backproject_split(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
+{
+    switch (G->bp_nc * 10 + G->bp_nv) {
+    case 22: return launch_sets<2, 2>(G, d_sino, d_vol, items, stream);
+    case 23: return launch_sets<2, 3>(G, d_sino, d_vol, items, stream);
+    case 32: return launch_sets<3, 2>(G, d_sino, d_vol, items, stream);
+    case 33: return launch_sets<3, 3>(G, d_sino, d_vol, items, stream);
+    case 42: return launch_sets<4, 2>(G, d_sino, d_vol, items, stream);
+    case 43: return launch_sets<4, 3>(G, d_sino, d_vol, items, stream);
+    case 52: return launch_sets<5, 2>(G, d_sino, d_vol, items, stream);
+    case 53: return launch_sets<5, 3>(G, d_sino, d_vol, items, stream);
+    default: return false;
+    }
+}

@@ -291,8 +291,12 @@ static std::vector<int> backproject_pair_shapes(leap_geometry *G)
         // Mirror image, parallel beams, 120 views, one volume / 32 + 32 / 16 + 16 voxels per thread: 256^3 (1024 workgroups of the
         // larger) 693 / 552 / 648 us, 224^3 (784) 689 / 537 / 534, 192^3 (432) 479 / 375 / 358, 160^3 (300; 500 of the smaller) 476 /
         // 372 / 257, 128^3 (256 of the smaller) 465 / 378 / 262, 112^3 280 / 379 / 261, 64^3 267 / 369 / 247.
+        // Wide windows leave room for 768 workgroups: 60 views, one volume of 42 columns and 32 voxels or of 64 and 16 / 51 columns and 16 + 16
+        // voxels, us: 128^3 (256 workgroups) 196 / 229, 160^3 (500) 260 / 243, 192^3 (864: a second round nearly empty) 378 / 424,
+        // 224^3 (1372) 560 / 501, 256^3 (2048) 690 / 687.
         const int workgroups = tiles * ((d->nz - kfirst + S.zc - 1) / S.zc);
-        if (G->bp_mirror && only < 0 && workgroups < (S.zc == 32 ? 800 : 250)) continue;
+        const bool enough = S.pw <= 32 ? workgroups >= (S.zc == 32 ? 800 : 250) : 10 * workgroups >= 6 * 768 * ((workgroups + 767) / 768);
+        if (G->bp_mirror && only < 0 && !enough) continue;
         shapes.push_back(sh);
     }
     return shapes;
@@ -342,6 +346,19 @@ static void select_footprint_tiled(leap_geometry *G)
     auto need_of = [&](int zc, int from) {
         return std::find_if(known.begin(), known.end(), [&](const WindowNeed &k) { return k.zc == zc && k.kfirst == from; });
     };
+    auto look_at = [&](std::vector<WindowNeed> needs) {
+        if (needs.empty()) return;
+        staged_window_needs(G, needs,
+                            [&](const SfGeom &ga, const SfView &v, float xc, float yc, SfWindow &w) {
+                                const SfTileBounds b = sf_bp_tile_bounds(ga, v, xc, yc, hx);
+                                sf_bp_window_columns(b, G->bp_wh, G->bp_nc, w.c0, w.need_w);
+                                return b;
+                            },
+                            [&](const SfGeom &ga, const SfTileBounds &b, float z0, float z1, SfWindow &w) {
+                                sf_bp_window_rows(ga, b, z0, z1, G->bp_nv, w.r0, w.need_h);
+                            });
+        known.insert(known.end(), needs.begin(), needs.end());
+    };
     for (size_t n = 0, p = 0;;) {
         std::vector<WindowNeed> needs;
         const bool single = n < (size_t)norder && !G->bp_tiled;
@@ -352,17 +369,7 @@ static void select_footprint_tiled(leap_geometry *G)
         const int single_zc = single ? BP_SHAPES[order[n]].zc : 0, pair_zc = pair ? BP_PAIR_SHAPES[pair_shapes[p]].zc : 0;
         if (single && need_of(single_zc, 0) == known.end()) needs.push_back({single_zc, 0});
         if (pair && need_of(pair_zc, kfirst) == known.end()) needs.push_back({pair_zc, kfirst});
-        if (!needs.empty())
-            staged_window_needs(G, needs,
-                            [&](const SfGeom &ga, const SfView &v, float xc, float yc, SfWindow &w) {
-                                const SfTileBounds b = sf_bp_tile_bounds(ga, v, xc, yc, hx);
-                                sf_bp_window_columns(b, G->bp_wh, G->bp_nc, w.c0, w.need_w);
-                                return b;
-                            },
-                            [&](const SfGeom &ga, const SfTileBounds &b, float z0, float z1, SfWindow &w) {
-                                sf_bp_window_rows(ga, b, z0, z1, G->bp_nv, w.r0, w.need_h);
-                            });
-        known.insert(known.end(), needs.begin(), needs.end());
+        look_at(needs);
         if (single) {
             const WindowNeed &need = *need_of(single_zc, 0);
             G->bp_need_w = need.w;
@@ -374,6 +381,30 @@ static void select_footprint_tiled(leap_geometry *G)
         if (pair) {
             if (window_fits(*need_of(pair_zc, kfirst), BP_PAIR_SHAPES[pair_shapes[p]])) G->bp_pair_shape = pair_shapes[p];
             ++p;
+        }
+    }
+    // Volumes that leave the chip idle: four groups of threads share the views.  Chunks of 8 voxels where the workgroups of one volume
+    // are few, then of 16, then of 32; the lines keep a batch of eight (whose items take the same chunks, to come out the same bits)
+    // no slower than it is without.  60 views, one volume, unsplit / 8 / 16 / 32 voxels, us, with the workgroups of each in brackets:
+    // parallel beams, mirror image: 64^3 138 / 41 (64) / 53 (32) / 79 (16), 96^3 138 / 43 (216) / 54 (108) / 80 (72), 128^3 135 / 82
+    // (512) / 57 (256) / 82 (128), 160^3 131 / 160 / 106 (500) / 159 (300); off centre: 64^3 138 / 36 (128) / 44 (64) / 60 (32), 96^3
+    // 138 / 55 (432) / 46 (216) / 61 (108), 128^3 235 / 103 / 69 (512) / 67 (256), 192^3 245 / 334 / 224 / 233 (864), 224^3 352 / 521 / 341
+    // / 347 (1372).  Eight volumes of 96^3: mirror image 209 / 277 / 206 / 233, off centre 209 / 277 / 206 / 161; of 128^3 366 / 628 / 410 /
+    // 328 and 378 / 627 / 410 / 316.
+    // Wide windows, unsplit / 8 voxels: mirror image 96^3 186 / 65 (216), 128^3 196 / 129 (512), 144^3 248 / 183 (729), 160^3 243 / 233
+    // (1000); off centre 96^3 187 / 84 (432), 112^3 220 / 126 (686), 128^3 197 / 162 (1024; eight of them 742 / 954), 160^3 261 / 292.
+    if (G->bp_tiled && G->bp_nv <= 3) {
+        const bool narrow = known.front().w <= BP_SPLIT_SHAPES[0].pw - 1;
+        const int limits[2][3] = {{900, 256, narrow ? 128 : 700}, {256, 128, narrow ? 64 : 800}};     // [mirror][shape]
+        long only = -2;
+        debug_option("bp_split", only);
+        for (int sh = BP_NSPLIT_SHAPES - 1; sh >= 0 && only != -1 && G->bp_split_shape < 0; --sh) {
+            const SfBpShape S = BP_SPLIT_SHAPES[sh];
+            const int workgroups = tiles * ((d->nz - kfirst + S.zc - 1) / S.zc);
+            if (only >= 0 ? only != sh : workgroups > limits[G->bp_mirror][sh]) continue;
+            if (!bp_split_instance_exists(G->bp_nc, G->bp_nv, sh) || known.front().w > S.pw - 1) continue;
+            if (need_of(S.zc, kfirst) == known.end()) look_at({{S.zc, kfirst}});
+            if (window_fits(*need_of(S.zc, kfirst), S)) G->bp_split_shape = sh;
         }
     }
     // Cylinder: the tiled kernel takes the angle between a voxel's centre and its corners from a short series,
@@ -1288,6 +1319,11 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
         const SfBpShape &S = BP_PAIR_SHAPES[G->bp_pair_shape];
         const size_t n = std::strlen(back);
         std::snprintf(back + n, sizeof back - n, "+%s(zc=%d,%dx%d)", G->bp_mirror ? "mirror" : "pairs", S.zc, S.pw, S.ph);
+    }
+    if (G->bp_split_shape >= 0) {
+        const SfBpShape &S = BP_SPLIT_SHAPES[G->bp_split_shape];
+        const size_t n = std::strlen(back);
+        std::snprintf(back + n, sizeof back - n, "+split(%szc=%d,%dx%d)", G->bp_mirror ? "mirror," : "", S.zc, S.pw, S.ph);
     }
     const char *modules = G->g.type != SF_MODULAR ? "" : (G->geoms.empty() ? " (tilted modules)" : " (upright modules)");
     std::snprintf(buf, (size_t)cap, "type=%d model=%s A=%s AT=%s scratch=%zu%s cols/voxel<=%.2f rows/voxel<=%.2f voxels/row<=%.2f%s%s",

@@ -42,13 +42,23 @@ constexpr int BP_TALL_SHAPE = 5;
 constexpr int BP_WIDE_SHAPE = 6;
 
 // Two volumes per thread (see sf_backproject_tiled): voxels per thread of either, window.  Tried in this order.
-constexpr SfBpShape BP_PAIR_SHAPES[] = {{32, 32, 44}, {32, 32, 56}, {16, 32, 44}, {16, 51, 48}, {8, 64, 32}};
+constexpr SfBpShape BP_PAIR_SHAPES[] = {{32, 32, 44}, {32, 32, 56}, {16, 32, 44}, {16, 51, 48}};
 constexpr int BP_NPAIR_SHAPES = sizeof(BP_PAIR_SHAPES) / sizeof(BP_PAIR_SHAPES[0]);
 
-// ... and which footprints they are instantiated for: narrow windows up to four columns, wide ones from four on.
+// ... and which footprints they are instantiated for: narrow windows up to four columns, wide ones from three on.
 constexpr bool bp_pair_instance_exists(int nc, int nv, int shape)
 {
-    return nv <= 3 && (BP_PAIR_SHAPES[shape].pw <= 32 ? nc <= 4 : nc >= 4);
+    return nv <= 3 && (BP_PAIR_SHAPES[shape].pw <= 32 ? nc <= 4 : nc >= 3);
+}
+
+// Four groups of threads that share the views (VS == 4): voxels per thread of either volume, window; the last for windows wider than
+// 32 columns.
+constexpr int BP_SPLIT = 4;
+constexpr SfBpShape BP_SPLIT_SHAPES[] = {{32, 32, 44}, {16, 32, 44}, {8, 64, 32}};
+constexpr int BP_NSPLIT_SHAPES = 3;
+constexpr bool bp_split_instance_exists(int nc, int nv, int shape)
+{
+    return nv <= 3 && (BP_SPLIT_SHAPES[shape].pw <= 32 ? nc <= 4 : nc >= 3);
 }
 
 // Is the footprint kernel instantiated for NC columns, NV rows and this shape?
@@ -246,7 +256,7 @@ __device__ __forceinline__ void bp_store_view(const SfGeom &g, const SfView v, i
         ac = sf_amp_col<GT>(g, v, w.c0 + sc);
     }
     // this thread's first row; RSTEP rows further per element (whole numbers, so that a row's v does not depend on the window it is
-    // staged in)
+    // staged in: one volume and two may take different ones)
     float rf = (float)(w.r0 + sr);
 #pragma unroll
     for (int s = 0; s < NSTAGE; ++s) {
@@ -284,9 +294,11 @@ SF_HD SfBpScene sf_bp_scene(const SfGeom &g, int i0, int j0, int k0)
 
 // GT: 0 flat or parallel, 1 cylindrical detector, 2 modular geometry with upright modules (every view brings its own
 // parameter block geoms[a]: the scene translated so that the view is a circular cone-beam view; g holds the sizes).
-// NS: volumes per workgroup.
-template <int NC, int NV, int BP_ZC, int BP_PW, int BP_PH, int GT, int NS>
-__global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC * NS > 32) ? 3 : (NS == 2 && BP_PW > 42 && BP_ZC > 8 ? 3 : 4)) void sf_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
+// NS: volumes per workgroup.  VS: groups of 256 threads that share a tile's views, group q taking views q, q + VS, ...: a step from
+// one view to the next takes a microsecond and a half and more however few voxels a thread has (the window's loads, two barriers'
+// worth of waiting), so a volume too small to fill the chip is as slow as its views are many.  The groups' sums are added in order.
+template <int NC, int NV, int BP_ZC, int BP_PW, int BP_PH, int GT, int NS, int VS = 1>
+__global__ __launch_bounds__(256 * VS, VS > 1 ? (NS == 1 && BP_ZC <= 16 && GT != 1 ? 8 : 4) : (GT == 1 && NV > 2 && BP_ZC * NS > 32) ? 3 : (NS == 2 && BP_PW > 42 && BP_ZC > 8 ? 3 : 4)) void sf_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
                                                             const float *__restrict__ sino, float *__restrict__ vol,
                                                             int tiles_x, float wh, const void *__restrict__ aux, SfBpSets sets)
 {
@@ -299,14 +311,15 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC * NS > 32) ? 3 : (
                 : nullptr;
     constexpr int BP_PS = bp_row_stride<NS>(BP_PW);      // LDS row stride (samples)
     using Sample = SfBpSample<NS>;
-    __shared__ Sample patch[2][BP_PH * BP_PS];
+    __shared__ Sample patch[2 * VS][BP_PH * BP_PS];
     // blockIdx.z: item of a batch, or pair of items
     const bool mirror = NS == 2 && sets.mirror;
     sino += (size_t)blockIdx.z * (mirror ? 1 : NS) * g.nviews * g.nrows * g.ncols;
     vol += (size_t)blockIdx.z * (mirror ? 1 : NS) * g.nx * g.ny * g.nz;
     const size_t to_second = mirror ? 0 : (size_t)g.nviews * g.nrows * g.ncols;
 
-    const int tid = threadIdx.x;
+    const int tid = VS == 1 ? threadIdx.x : threadIdx.x & 255;
+    const int group = VS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
     const int ti = tid & (BP_T - 1), tj = tid >> 4;
     const int tx = blockIdx.x % tiles_x, ty = blockIdx.x / tiles_x;
     const int i0 = tx * BP_T, j0 = ty * BP_T;
@@ -319,7 +332,7 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC * NS > 32) ? 3 : (
         if constexpr (GT == 2) return geoms[a];
         else return g;
     };
-    const SfBpScene scene0 = sf_bp_scene<BP_ZC>(geom_of(0), i0, j0, k0);
+    const SfBpScene scene0 = sf_bp_scene<BP_ZC>(geom_of(VS == 1 || group < g.nviews ? group : 0), i0, j0, k0);     // of the group's first view
 
     const int sc = sf_stage_column<BP_PW>(tid), sr = sf_stage_row<BP_PW, BP_PH>(tid);
     constexpr int NSTAGE = (BP_PH + 256 / BP_PW - 1) / (256 / BP_PW);
@@ -341,22 +354,27 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC * NS > 32) ? 3 : (
         else return nullptr;
     };
 
-    SfWindow win;
-    bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(0), views[0], sino, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1, wh,
-                                                       sc, sr, win, stage, cv_pre(0), reinterpret_cast<const char *>(sino + to_second), mirror);
+    SfWindow win = {};
+    if (VS == 1 || group < g.nviews) {
+        const float *ya = sino + (size_t)group * view_stride;
+        bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(group), views[group], ya, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1, wh,
+                                                           sc, sr, win, stage, cv_pre(group), reinterpret_cast<const char *>(ya + to_second), mirror);
+        bp_store_view<BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(group), views[group], sc, sr, win, stage, patch[2 * group], colcs);
+    }
     win_next = win;
-    bp_store_view<BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(0), views[0], sc, sr, win, stage, patch[0], colcs);
     __syncthreads();
 
-    for (int a = 0; a < g.nviews; ++a) {
-        const Sample *buf = patch[a & 1];
+    for (int a = group; a - group < g.nviews; a += VS) {
+        const int buffer = 2 * group + (((a - group) / VS) & 1);
+        const Sample *buf = patch[buffer];
+        if (VS == 1 || a < g.nviews) {
         double gref = 0.0;
         if constexpr (GT == 1) gref = cvt[a].gref;
-        if (a + 1 < g.nviews) {    // global loads in flight during the gather
-            const SfBpScene sn = GT == 2 ? sf_bp_scene<BP_ZC>(geom_of(a + 1), i0, j0, k0) : scene0;
-            const float *ya = sino + (size_t)(a + 1) * view_stride;
-            bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a + 1), views[a + 1], ya, sn.xc, sn.yc, hx, sn.z0, sn.z1, wh, sc, sr,
-                                                               win_next, stage, cv_pre(a + 1), reinterpret_cast<const char *>(ya + to_second), mirror);
+        if (a + VS < g.nviews) {    // global loads in flight during the gather
+            const SfBpScene sn = GT == 2 ? sf_bp_scene<BP_ZC>(geom_of(a + VS), i0, j0, k0) : scene0;
+            const float *ya = sino + (size_t)(a + VS) * view_stride;
+            bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a + VS), views[a + VS], ya, sn.xc, sn.yc, hx, sn.z0, sn.z1, wh, sc, sr,
+                                                               win_next, stage, cv_pre(a + VS), reinterpret_cast<const char *>(ya + to_second), mirror);
         }
         const SfGeom &gv = geom_of(a);
         const double zlo_k0 = GT == 2 ? fma((double)k0, gv.Tzd, gv.zlo0d) : scene0.zlo_k0;
@@ -398,7 +416,7 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC * NS > 32) ? 3 : (
         constexpr unsigned ROW = (unsigned)(BP_PS * sizeof(Sample));
         const char *const lds0 = reinterpret_cast<const char *>(&patch[0][0]);
         const unsigned lds_at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) Sample *)&patch[0][0];
-        unsigned pb = (unsigned)((a & 1) * (BP_PH * BP_PS) + (int)ofs) * (unsigned)sizeof(Sample);
+        unsigned pb = (unsigned)(buffer * (BP_PH * BP_PS) + (int)ofs) * (unsigned)sizeof(Sample);
         struct Sum {
             float v[NS];
         };
@@ -514,10 +532,38 @@ __global__ __launch_bounds__(256, (GT == 1 && NV > 2 && BP_ZC * NS > 32) ? 3 : (
             }
         }
 
-        if (a + 1 < g.nviews)
-            bp_store_view<BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a + 1), views[a + 1], sc, sr, win_next, stage, patch[(a + 1) & 1], colcs);
+        if (a + VS < g.nviews)
+            bp_store_view<BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a + VS), views[a + VS], sc, sr, win_next, stage, patch[buffer ^ 1], colcs);
+        }
         win = win_next;
         __syncthreads();
+    }
+
+    if constexpr (VS > 1) {
+        // the groups' sums, a few voxels at a time through the windows' place
+        constexpr int FIT = (int)(sizeof(patch) / VS / (256 * NS * sizeof(float))), SLICE = FIT >= BP_ZC ? BP_ZC : (FIT >= 16 ? 16 : (FIT >= 8 ? 8 : 4));
+        static_assert(FIT >= 4 && BP_ZC % SLICE == 0, "a slice of every group's sums fits the windows' place");
+        float *const sums = reinterpret_cast<float *>(&patch[0][0]);
+#pragma unroll
+        for (int s0 = 0; s0 < BP_ZC; s0 += SLICE) {
+            if (group > 0) {
+#pragma unroll
+                for (int kk = 0; kk < SLICE; ++kk)
+#pragma unroll
+                    for (int e = 0; e < NS; ++e) sums[((group * SLICE + kk) * NS + e) * 256 + tid] = acc[s0 + kk][e];
+            }
+            __syncthreads();
+            if (group == 0) {
+#pragma unroll
+                for (int q = 1; q < VS; ++q)
+#pragma unroll
+                    for (int kk = 0; kk < SLICE; ++kk)
+#pragma unroll
+                        for (int e = 0; e < NS; ++e) acc[s0 + kk][e] += sums[((q * SLICE + kk) * NS + e) * 256 + tid];
+            }
+            __syncthreads();
+        }
+        if (group > 0) return;
     }
 
     if (i < g.nx && j < g.ny) {
