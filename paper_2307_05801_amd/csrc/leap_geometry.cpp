@@ -574,18 +574,38 @@ static void select_siddon_fast_kernels(leap_geometry *G)
         long first_shape = BP_FIRST_SHORT_SHAPE;       // the 64-voxel shapes do not fit: the sums live in LDS
         if (debug_option("bp_shape", first_shape))
             first_shape = std::min((long)BP_LAST_SHORT_SHAPE, std::max((long)BP_FIRST_SHORT_SHAPE, first_shape % BP_NSHAPES));
-        for (int sh = (int)first_shape; sh <= BP_LAST_SHORT_SHAPE && !G->bp_tiled; ++sh) {
-            struct Tile {
-                const SfView *v;
-                float xc, yc;
-            };
-            std::vector<WindowNeed> need = {{BP_SHAPES[sh].zc, 0}};
+        struct Tile {
+            const SfView *v;
+            float xc, yc;
+        };
+        auto window_of = [&](int zc) {
+            std::vector<WindowNeed> need = {{zc, 0}};
             staged_window_needs(G, need, [&](const SfGeom &, const SfView &v, float xc, float yc, SfWindow &) { return Tile{&v, xc, yc}; },
                                 [&](const SfGeom &ga, const Tile &t, float z0, float z1, SfWindow &w) { w = sd_bp_window(ga, *t.v, t.xc, t.yc, hx, z0, z1); });
-            G->bp_need_w = need[0].w;
-            G->bp_need_h = need[0].h;
+            return need[0];
+        };
+        for (int sh = (int)first_shape; sh <= BP_LAST_SHORT_SHAPE && !G->bp_tiled; ++sh) {
+            const WindowNeed need = window_of(BP_SHAPES[sh].zc);
+            G->bp_need_w = need.w;
+            G->bp_need_h = need.h;
             G->bp_shape = sh;
-            G->bp_tiled = window_fits(need[0], BP_SHAPES[sh]);
+            G->bp_tiled = window_fits(need, BP_SHAPES[sh]);
+        }
+        if (!G->bp_tiled) return;
+        const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
+        // Volumes that leave the chip idle: four groups of threads share the views.  60 views, unsplit / 16 / 8 voxels per thread, us, with
+        // the workgroups of each in brackets: parallel beams 64^3 333 / 88 (64) / 68 (128), 96^3 328 / 91 (216) / 132 (432), 128^3 329 / 177
+        // (512), 144^3 358 / 268 (729), 160^3 363 / 348 (1000), 224^3 818 / 952; four volumes of 64^3 333 / 93 / 134, of 128^3 684 / 689.
+        // Windows wider than 32 columns, unsplit / 8: 64^3 392 / 117 (128), 96^3 398 / 232 (432), 112^3 436 / 320 (686), 128^3 435 / 434 (1024);
+        // four volumes of 96^3 776 / 721.
+        const int limits[2] = {730, G->bp_need_w <= SD_BP_SPLIT_SHAPES[0].pw - 1 ? 128 : 700};
+        long only = -2;
+        debug_option("bp_split", only);
+        for (int sh = SD_BP_NSPLIT_SHAPES - 1; sh >= 0 && only != -1 && G->bp_split_shape < 0; --sh) {
+            const SfBpShape S = SD_BP_SPLIT_SHAPES[sh];
+            const int workgroups = tiles * ((d->nz + S.zc - 1) / S.zc);
+            if (only >= 0 ? only != sh : workgroups > limits[sh]) continue;
+            if (G->bp_need_w <= S.pw - 1 && window_fits(window_of(S.zc), S)) G->bp_split_shape = sh;
         }
     }
 }
@@ -1321,7 +1341,7 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
         std::snprintf(back + n, sizeof back - n, "+%s(zc=%d,%dx%d)", G->bp_mirror ? "mirror" : "pairs", S.zc, S.pw, S.ph);
     }
     if (G->bp_split_shape >= 0) {
-        const SfBpShape &S = BP_SPLIT_SHAPES[G->bp_split_shape];
+        const SfBpShape &S = siddon ? SD_BP_SPLIT_SHAPES[G->bp_split_shape] : BP_SPLIT_SHAPES[G->bp_split_shape];
         const size_t n = std::strlen(back);
         std::snprintf(back + n, sizeof back - n, "+split(%szc=%d,%dx%d)", G->bp_mirror ? "mirror," : "", S.zc, S.pw, S.ph);
     }

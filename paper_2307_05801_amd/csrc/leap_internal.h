@@ -34,7 +34,7 @@ struct leap_geometry {
     bool bp_tiled = false;
     int bp_need_w = 0, bp_need_h = 0;   // largest staged window any (view, tile, chunk) asks for
     int bp_pair_shape = -1;             // two volumes per workgroup: index into BP_PAIR_SHAPES (-1: one volume)
-    int bp_split_shape = -1;            // groups of threads that share the views: index into BP_SPLIT_SHAPES, -1: none
+    int bp_split_shape = -1;            // groups of threads that share the views: index into BP_SPLIT_SHAPES (Siddon: SD_BP_SPLIT_SHAPES), -1: none
     bool bp_mirror = false;             // ... the volume's upper half and its lower half's mirror image, whatever the batch
     // column-wise forward projection (footprint and Siddon models): the volume goes through a z-fastest scratch copy
     // slab by slab (sf_project_columns.h)
@@ -127,5 +127,6 @@ struct SfSlab;
 bool leap_launch_footprint_slab(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward.hip
 int leap_launch_footprint_back(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                         // leap_footprint_back.hip
 bool leap_launch_backproject_split(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                     // leap_footprint_back_split.hip
+bool leap_launch_siddon_back_split(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                     // leap_siddon_back_split.hip
 bool leap_launch_backproject_pairs(const leap_geometry *geom, const float *d_sino, float *d_vol, int blocks, hipStream_t stream);                     // leap_footprint_back_pairs.hip
 int leap_launch_backproject_batch(const leap_geometry *geom, const float *d_sino, float *d_vol, int batch, hipStream_t stream);

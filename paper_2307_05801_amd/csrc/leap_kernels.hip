@@ -321,6 +321,8 @@ static int launch_sd_bp_items(const leap_geometry *G, const float *d_sino, float
         case 5: launch_md_tiled<5>(G, d_sino, d_vol, stream, items); ok = true; break;
         default: break;
         }
+    } else if (G->bp_split_shape >= 0) {
+        ok = leap_launch_siddon_back_split(G, d_sino, d_vol, items, stream);
     } else
     switch (G->bp_nc) {
     case 2: ok = launch_sd_shape<2>(G, d_sino, d_vol, stream, items); break;

@@ -50,6 +50,11 @@ SF_HD SfWindow sd_bp_window(const SfGeom &g, const SfView &v, float xc, float yc
     return w;
 }
 
+// Four groups of threads that share the views: voxels per thread, window.  (Sums of 32 voxels would not fit four times.)
+constexpr int SD_BP_SPLIT = 4;
+constexpr SfBpShape SD_BP_SPLIT_SHAPES[] = {{16, 32, 44}, {8, 64, 32}};
+constexpr int SD_BP_NSPLIT_SHAPES = 2;
+
 // Where a workgroup's tile and z-chunk lie in the scene a view sees.
 struct SdBpScene {
     float xc, yc, z0, z1;
@@ -174,22 +179,26 @@ typedef __attribute__((address_space(3))) float SdLds;
 // NCS: detector columns whose centre can fall inside one voxel's in-plane footprint.  MOD: modular geometry with
 // upright modules, one parameter block geoms[a] per view (g holds the sizes).
 // APART: adjacent rows are at least one voxel apart wherever a ray meets the volume.
-template <int NCS, int ZC, int PW, int PH, bool MOD, bool APART>
-__global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
+// VS: groups of 256 threads that share a tile's views, group q taking views q, q + VS, ..., each with sums of its own that are added in
+// order at the end: as in the footprint kernel, a step from view to view takes a workgroup microseconds however little it holds.
+template <int NCS, int ZC, int PW, int PH, bool MOD, bool APART, int VS = 1>
+__global__ __launch_bounds__(256 * VS) void sd_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
                                                             const SdRayCol *__restrict__ rays, const float *__restrict__ sino,
                                                             float *__restrict__ vol, int tiles_x,
                                                             const SfGeom *__restrict__ geoms)
 {
     constexpr int PS = PW + BP_ROW_PAD;
     constexpr int NSLOT = ZC + 4;
-    __shared__ float patch[2][PH * PS];
-    __shared__ float rinv[2][PH];
-    __shared__ float sums[NSLOT * 256];
+    __shared__ float patch[2 * VS][PH * PS];
+    __shared__ float rinv[2 * VS][PH];
+    __shared__ float group_sums[VS][NSLOT * 256];
 
     // blockIdx.z: item of a batch
     sino += (size_t)blockIdx.z * g.nviews * g.nrows * g.ncols;
     vol += (size_t)blockIdx.z * g.nx * g.ny * g.nz;
-    const int tid = threadIdx.x;
+    const int tid = VS == 1 ? threadIdx.x : threadIdx.x & 255;
+    const int group = VS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+    float *const sums = group_sums[group];
     const int ti = tid & (BP_T - 1), tj = tid >> 4;
     const int tx = blockIdx.x % tiles_x, ty = blockIdx.x / tiles_x;
     const int i0 = tx * BP_T, j0 = ty * BP_T;
@@ -202,7 +211,7 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
         if constexpr (MOD) return geoms[a];
         else return g;
     };
-    const SdBpScene scene0 = sd_bp_scene<ZC>(geom_of(0), i0, j0, k0);
+    const SdBpScene scene0 = sd_bp_scene<ZC>(geom_of(VS == 1 || group < g.nviews ? group : 0), i0, j0, k0);     // of the group's first view
 
     const int sc = tid & (PW - 1), sr = tid / PW;
     constexpr int NSTAGE = (PH * PW + 255) / 256;
@@ -214,18 +223,23 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
     const unsigned sums_at = (unsigned)(uintptr_t)(SdLds *)(sums + tid) - (SD_BP_HI << 10);
 
     float stage[NSTAGE];
-    SfWindow win, win_next;
-    sd_load_view<PW, PH, NSTAGE>(geom_of(0), views[0], sino, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1, sc, sr, win, stage);
+    SfWindow win = {}, win_next;
+    if (VS == 1 || group < g.nviews) {
+        sd_load_view<PW, PH, NSTAGE>(geom_of(group), views[group], sino + (size_t)group * view_stride, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1,
+                                     sc, sr, win, stage);
+        sd_store_view<PW, PH, NSTAGE>(geom_of(group), rays + (size_t)group * g.ncols, sc, sr, win, stage, patch[2 * group], rinv[2 * group]);
+    }
     win_next = win;
-    sd_store_view<PW, PH, NSTAGE>(geom_of(0), rays, sc, sr, win, stage, patch[0], rinv[0]);
     __syncthreads();
 
-    for (int a = 0; a < g.nviews; ++a) {
-        const float *__restrict__ buf = patch[a & 1];
-        const float *__restrict__ ri = rinv[a & 1];
-        if (a + 1 < g.nviews) {    // global loads in flight during the gather
-            const SdBpScene sn = MOD ? sd_bp_scene<ZC>(geom_of(a + 1), i0, j0, k0) : scene0;
-            sd_load_view<PW, PH, NSTAGE>(geom_of(a + 1), views[a + 1], sino + (size_t)(a + 1) * view_stride, sn.xc, sn.yc, hx, sn.z0,
+    for (int a = group; a - group < g.nviews; a += VS) {
+        const int buffer = 2 * group + (((a - group) / VS) & 1);
+        if (VS == 1 || a < g.nviews) {
+        const float *__restrict__ buf = patch[buffer];
+        const float *__restrict__ ri = rinv[buffer];
+        if (a + VS < g.nviews) {    // global loads in flight during the gather
+            const SdBpScene sn = MOD ? sd_bp_scene<ZC>(geom_of(a + VS), i0, j0, k0) : scene0;
+            sd_load_view<PW, PH, NSTAGE>(geom_of(a + VS), views[a + VS], sino + (size_t)(a + VS) * view_stride, sn.xc, sn.yc, hx, sn.z0,
                                          sn.z1, sc, sr, win_next, stage);
         }
         const SfGeom &gv = geom_of(a);
@@ -328,17 +342,24 @@ __global__ __launch_bounds__(256) void sd_backproject_tiled(SfGeom g, const SfVi
             }
         }
 
-        if (a + 1 < g.nviews)
-            sd_store_view<PW, PH, NSTAGE>(geom_of(a + 1), rays + (size_t)(a + 1) * g.ncols, sc, sr, win_next, stage,
-                                          patch[(a + 1) & 1], rinv[(a + 1) & 1]);
+        if (a + VS < g.nviews)
+            sd_store_view<PW, PH, NSTAGE>(geom_of(a + VS), rays + (size_t)(a + VS) * g.ncols, sc, sr, win_next, stage, patch[buffer ^ 1],
+                                          rinv[buffer ^ 1]);
+        }
         win = win_next;
         __syncthreads();
     }
 
+    if (group > 0) return;             // (the loop's last barrier stands behind every group's last addition)
     if (i < g.nx && j < g.ny) {
 #pragma unroll
         for (int kk = 0; kk < ZC; ++kk)
-            if (k0 + kk < g.nz) vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sums[(ZC + 1 - kk) * 256 + tid];
+            if (k0 + kk < g.nz) {
+                float sum = sums[(ZC + 1 - kk) * 256 + tid];
+#pragma unroll
+                for (int q = 1; q < VS; ++q) sum += group_sums[q][(ZC + 1 - kk) * 256 + tid];
+                vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sum;
+            }
     }
 }
 
