@@ -100,8 +100,9 @@ static bool launch_fp_rows_slab(const leap_geometry *G, const FwdScratch &S, con
 bool leap_launch_footprint_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
 {
     if (G->fp_rows) return launch_fp_rows_slab(G, S, slab, d_sino, stream, items);
-    switch (G->fp_nkp) {                      // highest height class: rows of up to a voxel and a half, two, three
-    case 2: case 3: case 4: return launch_fp_sets<2>(G, S, slab, d_sino, stream, items);
+    switch (G->fp_nkp) {                      // highest height class: rows of up to a voxel, a voxel and a half, two, three
+    case 2: case 3: return launch_fp_sets<1>(G, S, slab, d_sino, stream, items);
+    case 4: return launch_fp_sets<2>(G, S, slab, d_sino, stream, items);
     case 5: return launch_fp_sets<3>(G, S, slab, d_sino, stream, items);
     case 6: case 7: return launch_fp_sets<4>(G, S, slab, d_sino, stream, items);
     default: return false;

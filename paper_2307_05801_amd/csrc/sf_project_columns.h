@@ -241,12 +241,12 @@ SF_HD void sf_pair_apply(const float *x, const SfPairWeights<LO2, HI2> &w, float
     }
 }
 
-// Height classes: 0 up to half a voxel, 1 up to a voxel, 2 up to a voxel and a half, 3 up to two, 4 up to three voxels.
+// Height classes: 1 up to a voxel, 2 up to a voxel and a half, 3 up to two, 4 up to three voxels.
 template <int CLS>
 struct SfPairClass {
-    static constexpr int LO2 = CLS, HI2 = CLS == 4 ? 6 : CLS + 1, P = HI2 + 1;
+    static constexpr int LO2 = CLS == 1 ? 0 : CLS, HI2 = CLS == 4 ? 6 : CLS + 1, P = HI2 + 1;
 };
-SF_HD int sf_pair_class(float mu) { return mu < 0.5f ? 0 : (mu <= 1.0f ? 1 : (mu <= 1.5f ? 2 : (mu <= 2.0f ? 3 : 4))); }
+SF_HD int sf_pair_class(float mu) { return mu <= 1.0f ? 1 : (mu <= 1.5f ? 2 : (mu <= 2.0f ? 3 : 4)); }
 
 template <int CLS>
 SF_HD void sf_pair_sums_of_class(const float *x, float fr1, const SfPairOffsets &k, float &sa, float &sb)
@@ -270,7 +270,6 @@ SF_HD void sf_pair_sums(const float (&x)[P], float fr1, const SfPairConsts<P> &c
     float run[FP_MAX_P] = {};
     for (int t = 0; t < P; ++t) run[t] = x[t];
     switch (sf_pair_class(c.k.mu)) {
-    case 0: sf_pair_sums_of_class<0>(run, fr1, c.k, sa, sb); break;
     case 1: sf_pair_sums_of_class<1>(run, fr1, c.k, sa, sb); break;
     case 2: sf_pair_sums_of_class<2>(run, fr1, c.k, sa, sb); break;
     case 3: sf_pair_sums_of_class<3>(run, fr1, c.k, sa, sb); break;
@@ -378,7 +377,7 @@ __device__ __forceinline__ void fp_store_four(float *__restrict__ dst, float a, 
 
 constexpr int FP_WAVES = 4;      // waves per workgroup: adjacent column bundles of one view (each wave its own LDS, no barrier)
 
-// HC: highest height class of the scan's rows (2 .. 4); RG: groups of 128 rows per wave; CW: adjacent detector columns per wave;
+// HC: highest height class of the scan's rows (1 .. 4); RG: groups of 128 rows per wave; CW: adjacent detector columns per wave;
 // GT: 0 flat or parallel, 1 cylindrical detector, 2 modular geometry with upright modules; NS: volumes per wave.
 // (The cylinder's record phase needs more registers: its instances are held to the waves per SIMD they reach without
 // the records' staging, four up to two row groups, three beyond.)
@@ -462,13 +461,13 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
         const unsigned colbase = sf_slab_column(slab, g.nx, ic, jc) * (unsigned)nzp;   // start of the padded column
         const int mu_lo = __double2loint(mu), mu_hi = __double2hiint(mu);
         const float muf = (float)mu;
-        const int cls = sf_pair_class(muf);
+        const int cls = HC > 1 ? sf_pair_class(muf) : 1;
         {
             const SfPairOffsets k = sf_pair_offsets(muf);
             float4 f4 = make_float4(fa[0], 0.0f, 0.0f, 0.0f);
             if constexpr (CW > 1) f4.y = fa[1];
             if constexpr (CW > 2) { f4.z = fa[2]; f4.w = fa[3]; }
-            const bool below1 = cls <= 1, below2 = cls <= 2;
+            const bool below1 = HC == 1 || cls <= 1, below2 = HC <= 2 || cls <= 2;
             // (the wave has consumed every value it read from the previous block's records)
             rec[lane][0] = f4;
             rec[lane][1] = make_float4(below1 || (HC > 3 && cls > 3) ? k.mu : k.ka[0], below1 ? k.ka[0] : k.ka[1],
@@ -494,7 +493,7 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
                 const float4 r0 = rec[e][0], r1 = rec[e][1];
                 const float fcol[4] = {r0.x, r0.y, r0.z, r0.w};
                 SfPairOffsets k;
-                if constexpr (CLS <= 1) { k.mu = r1.x; k.ka[0] = r1.y; k.kb[0] = r1.z; k.kb[1] = r1.w; }
+                if constexpr (CLS == 1) { k.mu = r1.x; k.ka[0] = r1.y; k.kb[0] = r1.z; k.kb[1] = r1.w; }
                 if constexpr (CLS == 2) { k.ka[0] = r1.x; k.ka[1] = r1.y; k.kb[1] = r1.z; k.kb[2] = r1.w; }
                 if constexpr (CLS == 3) { k.ka[0] = r1.x; k.ka[1] = r1.y; k.kb[2] = r1.z; k.kb[3] = r1.w; }
                 if constexpr (CLS == 4) k = sf_pair_offsets(r1.x);
@@ -549,9 +548,8 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
             walk(cc, todo & ~above);
             todo &= above;
         };
-        walk_up_to(std::integral_constant<int, 0>{});
         walk_up_to(std::integral_constant<int, 1>{});
-        walk_up_to(std::integral_constant<int, 2>{});
+        if constexpr (HC > 1) walk_up_to(std::integral_constant<int, 2>{});
         if constexpr (HC > 2) walk_up_to(std::integral_constant<int, 3>{});
         if constexpr (HC > 3) walk_up_to(std::integral_constant<int, 4>{});
     }
