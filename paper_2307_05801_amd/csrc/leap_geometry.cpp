@@ -760,6 +760,22 @@ static void select_tilted_siddon_kernels(leap_geometry *G)
         fits = G->bp_need_w <= MD_BP_SHAPES[sh].pw - 1 && G->bp_need_h <= MD_BP_SHAPES[sh].ph - 1;
     }
     if (!fits) return;
+    const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
+    // Groups of threads that share the views: where the volume leaves the chip idle, and at any size under windows that would leave a
+    // compute unit one or two workgroups of 256 threads.  Unsplit / four groups, 32 columns, us: 62 x 63 x 43 x 207 views (96 workgroups)
+    // 1796 / 422, 119 x 126 x 84 x 86 (704) 805 / 550, 149 x 141 x 118 x 60 (1350) 612 / 685; in place of two workgroups 135 x 140 x 148 x
+    // 156 (1539) 5598 / 1986.  Unsplit / two groups, 64 columns: 78 x 67 x 69 x 110 (225) 1125 / 353, 165 x 164 x 79 x 58 (1210) 2440 /
+    // 1216, 234 x 196 x 225 x 206 (5655) 22998 / 13630.
+    const bool crowded = G->bp_shape <= 1;             // three workgroups and more
+    long only = -2;
+    debug_option("bp_split", only);
+    for (int sh = 0; sh < MD_BP_NSPLIT_SHAPES && only != -1 && G->bp_split_shape < 0; ++sh) {
+        const SfBpShape S = MD_BP_SPLIT_SHAPES[sh];
+        if (G->bp_need_w > S.pw - 1 || (only >= 0 ? only != sh : crowded && (sh > 0 || tiles * ((d->nz + S.zc - 1) / S.zc) > 800))) continue;
+        int w, h;
+        tilted_window_need(G, views, S.zc, w, h);
+        if (w <= S.pw - 1 && h <= S.ph - 1) G->bp_split_shape = sh;
+    }
     hipError_t e = hipMalloc((void **)&G->d_mdbp, sizeof(MdBpView) * views.size());
     if (e == hipSuccess) e = hipMemcpy(G->d_mdbp, views.data(), sizeof(MdBpView) * views.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
@@ -1341,7 +1357,7 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
         std::snprintf(back + n, sizeof back - n, "+%s(zc=%d,%dx%d)", G->bp_mirror ? "mirror" : "pairs", S.zc, S.pw, S.ph);
     }
     if (G->bp_split_shape >= 0) {
-        const SfBpShape &S = siddon ? SD_BP_SPLIT_SHAPES[G->bp_split_shape] : BP_SPLIT_SHAPES[G->bp_split_shape];
+        const SfBpShape &S = (G->d_mdbp ? MD_BP_SPLIT_SHAPES : (siddon ? SD_BP_SPLIT_SHAPES : BP_SPLIT_SHAPES))[G->bp_split_shape];
         const size_t n = std::strlen(back);
         std::snprintf(back + n, sizeof back - n, "+split(%szc=%d,%dx%d)", G->bp_mirror ? "mirror," : "", S.zc, S.pw, S.ph);
     }

@@ -307,11 +307,26 @@ static void launch_md_tiled(const leap_geometry *G, const float *d_sino, float *
                        d_sino, d_vol, (int)tiles_x);
 }
 
+template <int SH>
+static void launch_md_split(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
+{
+    constexpr SfBpShape S = MD_BP_SPLIT_SHAPES[SH];
+    const SfGeom &g = G->g;
+    const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
+    hipLaunchKernelGGL((md_backproject_tiled<S.zc, S.pw, S.ph, MD_BP_SPLIT[SH]>), dim3(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)items),
+                       dim3(256 * MD_BP_SPLIT[SH]), 0, stream, g, (const MdBpView *)G->d_mdbp, d_sino, d_vol, (int)tiles_x);
+}
+
 // The tiled Siddon back projection on `items` consecutive sinograms of a batch in one launch.
 static int launch_sd_bp_items(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     bool ok = false;
-    if (G->md_tilted || G->d_mdbp) {
+    if (G->d_mdbp && G->bp_split_shape >= 0) {
+        static_assert(MD_BP_NSPLIT_SHAPES == 2, "every shape has a case");
+        if (G->bp_split_shape == 0) launch_md_split<0>(G, d_sino, d_vol, stream, items);
+        else launch_md_split<1>(G, d_sino, d_vol, stream, items);
+        ok = true;
+    } else if (G->md_tilted || G->d_mdbp) {
         switch (G->d_mdbp ? G->bp_shape : -1) {
         case 0: launch_md_tiled<0>(G, d_sino, d_vol, stream, items); ok = true; break;
         case 1: launch_md_tiled<1>(G, d_sino, d_vol, stream, items); ok = true; break;

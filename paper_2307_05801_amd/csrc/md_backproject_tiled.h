@@ -33,6 +33,10 @@
 // leaves room for four workgroups per compute unit, the second for three, the next two for two.
 constexpr SfBpShape MD_BP_SHAPES[] = {{16, 32, 21}, {16, 32, 35}, {32, 32, 44}, {16, 32, 44}, {32, 32, 56}, {16, 64, 48}};
 constexpr int MD_BP_NSHAPES = 6;
+// Groups of threads that share the views (as in sd_backproject_tiled.h): four where a window of 32 columns does, two under 64 columns.
+constexpr SfBpShape MD_BP_SPLIT_SHAPES[] = {{8, 32, 28}, {8, 64, 28}};
+constexpr int MD_BP_SPLIT[] = {4, 2};
+constexpr int MD_BP_NSPLIT_SHAPES = 2;
 constexpr double MD_BP_ZBIAS = 1048576.0;      // added to axial positions so that truncation is floor for every row of a window
 
 // One entry per view, built in double on the host.
@@ -258,20 +262,24 @@ SF_HD bool md_bp_row(const MdBpColumn &C, const MdBpPixel &p, int &slot, float &
 
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
 
-template <int ZC, int PW, int PH>
-__global__ __launch_bounds__(256) void md_backproject_tiled(SfGeom g, const MdBpView *__restrict__ views,
+// VS: groups of 256 threads that share a tile's views, group q taking views q, q + VS, ..., each with sums of its own.
+template <int ZC, int PW, int PH, int VS = 1>
+__global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const MdBpView *__restrict__ views,
                                                             const float *__restrict__ sino, float *__restrict__ vol, int tiles_x)
 {
     constexpr int PS = PW + 1;                     // odd row stride: the lanes of a wave sit in a few adjacent rows and columns
     constexpr int NSLOT = ZC + 4;                  // slot s holds voxel k0 + s - 2; slots 0, 1, ZC+2, ZC+3 are dumps
     constexpr int RSTEP = 256 / PW, NSTAGE = (PH * PW + 255) / 256;
-    __shared__ double l_m[PH * PS], l_mz[PH * PS];
-    __shared__ float l_wy[PH * PS], l_inv_m[PH * PS], l_inv_mz[PH * PS];
-    __shared__ float sums[NSLOT * 256];
+    __shared__ double group_m[VS][PH * PS], group_mz[VS][PH * PS];
+    __shared__ float group_wy[VS][PH * PS], group_inv_m[VS][PH * PS], group_inv_mz[VS][PH * PS];
+    __shared__ float group_sums[VS][NSLOT * 256];
+    const int group = VS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+    double *const l_m = group_m[group], *const l_mz = group_mz[group];
+    float *const l_wy = group_wy[group], *const l_inv_m = group_inv_m[group], *const l_inv_mz = group_inv_mz[group], *const sums = group_sums[group];
 
     sino += (size_t)blockIdx.z * g.nviews * g.nrows * g.ncols;
     vol += (size_t)blockIdx.z * g.nx * g.ny * g.nz;
-    const int tid = threadIdx.x;
+    const int tid = VS == 1 ? threadIdx.x : threadIdx.x & 255;
     const int ti = tid & (BP_T - 1), tj = tid >> 4;
     const int tx = blockIdx.x % tiles_x, ty = blockIdx.x / tiles_x;
     const int i0 = tx * BP_T, j0 = ty * BP_T;
@@ -316,13 +324,17 @@ __global__ __launch_bounds__(256) void md_backproject_tiled(SfGeom g, const MdBp
         }
     };
 
-    load_view(0);
-    store_view(0);
-    SfWindow cur = win;
+    SfWindow cur = {};
+    if (VS == 1 || group < g.nviews) {
+        load_view(group);
+        store_view(group);
+        cur = win;
+    }
     __syncthreads();
 
-    for (int a = 0; a < g.nviews; ++a) {
-        if (a + 1 < g.nviews) load_view(a + 1);        // global loads in flight during the gather
+    for (int a = group; a - group < g.nviews; a += VS) {
+        if (VS == 1 || a < g.nviews) {
+        if (a + VS < g.nviews) load_view(a + VS);      // global loads in flight during the gather
 
         const MdBpView &V = views[a];
         const bool xmajor = md_bp_tile_xmajor(g, V, i0, j0);
@@ -348,18 +360,25 @@ __global__ __launch_bounds__(256) void md_backproject_tiled(SfGeom g, const MdBp
             }
         }
 
+        }
         __syncthreads();                               // every thread is done with this view's window
-        if (a + 1 < g.nviews) {
-            store_view(a + 1);
+        if (a + VS < g.nviews) {
+            store_view(a + VS);
             cur = win;
         }
         __syncthreads();
     }
 
+    if (group > 0) return;             // (the loop's last barrier stands behind every group's last addition)
     if (i < g.nx && j < g.ny) {
 #pragma unroll
         for (int kk = 0; kk < ZC; ++kk)
-            if (k0 + kk < g.nz) vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sums[(kk + 2) * 256 + tid];
+            if (k0 + kk < g.nz) {
+                float sum = sums[(kk + 2) * 256 + tid];
+#pragma unroll
+                for (int q = 1; q < VS; ++q) sum += group_sums[q][(kk + 2) * 256 + tid];
+                vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sum;
+            }
     }
 }
 

@@ -48,3 +48,11 @@ def test_views_shared_between_groups(torch_mod, oracle_mod, monkeypatch, geometr
 @pytest.mark.parametrize("pixel", [1.3, 2.0])
 def test_upright_modules(torch_mod, oracle_mod, pixel):
     check(torch_mod, oracle_mod, perturbed_poses(scan(CONE, pixel, 7), 3, shift_mm=2.0, upright=True))
+
+
+@pytest.mark.parametrize("shape,pixel", [(0, 2.2), (1, 1.5)])
+@pytest.mark.parametrize("nviews", [1, 2, 3, 9])
+def test_tilted_modules(torch_mod, oracle_mod, monkeypatch, shape, pixel, nviews):
+    monkeypatch.setenv("LEAP_DEBUG", f"bp_split={shape}")
+    cfg = scan(CONE, pixel, nviews).replace(sod=180.0, sdd=270.0)
+    check(torch_mod, oracle_mod, perturbed_poses(cfg, 3, shift_mm=2.0, tilt_rad=0.05))
