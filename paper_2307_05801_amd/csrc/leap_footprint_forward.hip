@@ -24,23 +24,30 @@ static void launch_fp_columns(const leap_geometry *G, const FwdScratch &S, const
                        S.item_floats, nq_log2, col_tiles, bands, vb, tb, vgroups_pad, tiles_per_xcd_pad, slab, (const SfGeom *)G->d_geoms);
 }
 
+template <int HC, int RG, int CW, int GT, int NS>
+static bool launch_fp_instance(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int first,
+                               int blocks)
+{
+    if constexpr (fp_instance_exists(HC, RG, CW, GT, NS)) {
+        launch_fp_columns<HC, RG, CW, GT, NS>(G, S, slab, d_sino, stream, first, blocks);
+        return true;
+    } else {
+        return false;
+    }
+}
+
 template <int HC, int RG, int NS>
 static bool launch_fp_w(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int first, int blocks)
 {
     const int gt = G->g.type == SF_CONE_CURVED ? 1 : (G->g.type == SF_MODULAR ? 2 : 0);
     switch (gt * 10 + G->fp_cw) {
-    case 1:
-        if constexpr (NS == 1) {
-            launch_fp_columns<HC, RG, 1, 0, NS>(G, S, slab, d_sino, stream, first, blocks);
-            return true;
-        }
-        return false;
-    case 2: launch_fp_columns<HC, RG, 2, 0, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
-    case 4: launch_fp_columns<HC, RG, 4, 0, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
-    case 12: launch_fp_columns<HC, RG, 2, 1, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
-    case 14: launch_fp_columns<HC, RG, 4, 1, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
-    case 22: launch_fp_columns<HC, RG, 2, 2, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
-    case 24: launch_fp_columns<HC, RG, 4, 2, NS>(G, S, slab, d_sino, stream, first, blocks); return true;
+    case 1: return launch_fp_instance<HC, RG, 1, 0, NS>(G, S, slab, d_sino, stream, first, blocks);
+    case 2: return launch_fp_instance<HC, RG, 2, 0, NS>(G, S, slab, d_sino, stream, first, blocks);
+    case 4: return launch_fp_instance<HC, RG, 4, 0, NS>(G, S, slab, d_sino, stream, first, blocks);
+    case 12: return launch_fp_instance<HC, RG, 2, 1, NS>(G, S, slab, d_sino, stream, first, blocks);
+    case 14: return launch_fp_instance<HC, RG, 4, 1, NS>(G, S, slab, d_sino, stream, first, blocks);
+    case 22: return launch_fp_instance<HC, RG, 2, 2, NS>(G, S, slab, d_sino, stream, first, blocks);
+    case 24: return launch_fp_instance<HC, RG, 4, 2, NS>(G, S, slab, d_sino, stream, first, blocks);
     default: return false;
     }
 }
@@ -52,9 +59,7 @@ static bool launch_fp_rg(const leap_geometry *G, const FwdScratch &S, const SfSl
     case 1: return launch_fp_w<HC, 1, NS>(G, S, slab, d_sino, stream, first, blocks);
     case 2: return launch_fp_w<HC, 2, NS>(G, S, slab, d_sino, stream, first, blocks);
     case 3: return launch_fp_w<HC, 3, NS>(G, S, slab, d_sino, stream, first, blocks);
-    case 4:
-        if constexpr (NS == 1) return launch_fp_w<HC, 4, NS>(G, S, slab, d_sino, stream, first, blocks);
-        return false;
+    case 4: return launch_fp_w<HC, 4, NS>(G, S, slab, d_sino, stream, first, blocks);
     default: return false;
     }
 }
@@ -62,7 +67,7 @@ static bool launch_fp_rg(const leap_geometry *G, const FwdScratch &S, const SfSl
 template <int HC>
 static bool launch_fp_sets(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
 {
-    const int paired = G->fp_pair_rg ? items / 2 * 2 : 0;
+    const int paired = leap_forward_paired(G, items);
     return (!paired || launch_fp_rg<HC, 2>(G, S, slab, d_sino, stream, 0, paired / 2)) &&
            (paired == items || launch_fp_rg<HC, 1>(G, S, slab, d_sino, stream, paired, items - paired));
 }
@@ -100,11 +105,11 @@ static bool launch_fp_rows_slab(const leap_geometry *G, const FwdScratch &S, con
 bool leap_launch_footprint_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
 {
     if (G->fp_rows) return launch_fp_rows_slab(G, S, slab, d_sino, stream, items);
-    switch (G->fp_nkp) {                      // highest height class: rows of up to a voxel, a voxel and a half, two, three
-    case 2: case 3: return launch_fp_sets<1>(G, S, slab, d_sino, stream, items);
-    case 4: return launch_fp_sets<2>(G, S, slab, d_sino, stream, items);
-    case 5: return launch_fp_sets<3>(G, S, slab, d_sino, stream, items);
-    case 6: case 7: return launch_fp_sets<4>(G, S, slab, d_sino, stream, items);
+    switch (fp_height_class(G->fp_nkp)) {
+    case 1: return launch_fp_sets<1>(G, S, slab, d_sino, stream, items);
+    case 2: return launch_fp_sets<2>(G, S, slab, d_sino, stream, items);
+    case 3: return launch_fp_sets<3>(G, S, slab, d_sino, stream, items);
+    case 4: return launch_fp_sets<4>(G, S, slab, d_sino, stream, items);
     default: return false;
     }
 }

@@ -444,6 +444,24 @@ static void block_order_options(leap_geometry *G)
     if (debug_option("tb", v) && v >= 1 && v <= 1024) G->fp_tb = (int)v;
 }
 
+// Two volumes to a wave halve a launch's waves and take more registers: worth it where enough workgroups are left, and the launch of
+// its own that an odd last item takes must fill the chip too.  Times of two over one per wave, by workgroups of two volumes: one group
+// of rows 20 to 700 1.15 to 0.95, 900 and more 0.66 to 0.98; several groups 20 to 1400 1.20 to 0.78 (depending on how full the last
+// round of workgroups is), 3000 and more 0.83 to 0.96; cylinder 1000 and more 0.65 to 0.95.  Batches of three, by workgroups of one
+// volume: one group 20 to 700 1.98 to 1.38, 1000 to 1400 0.92 to 1.13, 1600 and more 0.88 to 1.00; several 20 to 2800 1.99 to 0.94, 4000
+// and more 0.94 to 1.00.  An item's bits are the same either way.
+int leap_forward_paired(const leap_geometry *G, int items)
+{
+    if (!G->fp_pair_rg || items < 2) return 0;
+    if (G->fp_pair_always) return items / 2 * 2;
+    const double blocks = (double)((G->g.ncols + FP_WAVES * G->fp_cw - 1) / (FP_WAVES * G->fp_cw)) * G->g.nviews *
+                          ((G->g.nrows + G->fp_pair_rg * 128 - 1) / (G->fp_pair_rg * 128));
+    const bool one_group = G->fp_pair_rg == 1;
+    if (blocks * (items / 2) < (one_group || G->g.type == SF_CONE_CURVED ? 1000.0 : 3000.0)) return 0;
+    if (items % 2 && blocks < (one_group ? 1600.0 : 4000.0)) return 0;
+    return items / 2 * 2;
+}
+
 // Footprint model, column-wise forward projection: static limits and the marching axis of every bundle.
 static void select_footprint_columns(leap_geometry *G)
 {
@@ -489,7 +507,12 @@ static void select_footprint_columns(leap_geometry *G)
     G->fp_columns = need <= 16;
     block_order_options(G);
     if (!G->fp_columns) return;
-    if (G->fp_cw >= 2 && !(debug_option("pairs", v) && v == 0)) G->fp_pair_rg = G->fp_rg == 4 ? 2 : G->fp_rg;
+    v = -1;
+    debug_option("pairs", v);
+    const int pair_rg = G->fp_rg == 4 ? 2 : G->fp_rg;
+    if (v != 0 && fp_instance_exists(fp_height_class(G->fp_nkp), pair_rg, G->fp_cw, d->type == LEAP_CONE_CURVED ? 1 : (d->type == LEAP_MODULAR ? 2 : 0), 2))
+        G->fp_pair_rg = pair_rg;
+    G->fp_pair_always = v > 0;
     // Parallel beams: the axial overlaps go into the slab copy and a wave's lanes own adjacent rows, as many as it takes for
     // one wave to hold the detector's height, up to 512 rows.  Only where the copy by rows of the whole volume fits either
     // scratch (up to 256^3): a detector of many more rows than the volume has layers would otherwise take narrower slabs.

@@ -44,6 +44,7 @@ struct leap_geometry {
     int fp_cw = 4, fp_vb = 128, fp_tb = 1;   // detector columns per wave; block order: views per run, tiles per chunk
     bool fp_columns = false;
     int fp_pair_rg = 0;                 // row groups per wave with two volumes per wave (0: one volume per wave only)
+    bool fp_pair_always = false;        // (debugging: two volumes per wave in every batch, however few its waves)
     int fp_rows = 0;                    // parallel beams: rows per lane of sf_project_rows (0: not used); fp_row_groups groups of 64 of them
     int fp_row_groups = 1;
     bool flat = false;                  // one row, one layer: the kernels of sf_flat.h in both directions
@@ -104,6 +105,9 @@ int leap_static_scratch_init(int device);
 
 // Slab width and batch items per launch that a scratch of `floats` floats affords (leap_geometry.cpp).
 bool leap_plan_scratch(const leap_geometry *G, size_t floats, int batch, int &width, int &items);
+
+// Footprint forward projection: how many of a launch's `items` volumes go two to a wave (leap_geometry.cpp).
+int leap_forward_paired(const leap_geometry *G, int items);
 
 // Frees what the host-memory entry points created on the handle (leap_host.cpp).
 void leap_host_stage_free(leap_geometry *G);

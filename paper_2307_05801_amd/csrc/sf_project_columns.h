@@ -38,6 +38,21 @@
 
 constexpr int FP_PAD = 8;        // zero voxels before and after every z-column of the scratch copy (>= the voxels a row pair spans)
 constexpr int FP_MAX_P = 7;      // most voxels a pair of adjacent rows may overlap (rows of up to 3 voxels)
+constexpr int FP_WAVES = 4;      // waves per workgroup: adjacent column bundles of one view (each wave its own LDS, no barrier)
+
+// Highest height class (see sf_pair_class) of a scan whose pairs of rows overlap up to nkp voxels.
+SF_HD int fp_height_class(int nkp) { return nkp <= 3 ? 1 : (nkp <= 5 ? nkp - 2 : 4); }
+
+// Instances of the column-wise kernel by height class, row groups, columns per wave, detector (GT) and volumes per wave.  Two volumes per
+// wave: rows of up to a voxel and a half, taller ones where the sums and voxels of two leave enough waves in flight.  Two against one per
+// wave, time ratios where the chip is full, one group of rows / more: rows of 1.5 to 2 voxels 0.69 to 0.92 / 0.91 to 1.16, of 2 to 3
+// 0.92 to 1.16 / 1.00 to 1.24; on a cylinder (few waves in flight either way) 0.69 to 0.79 / 0.74 to 0.95 and 0.70 to 0.83 / 0.89 to 1.06.
+constexpr bool fp_instance_exists(int hc, int rg, int cw, int gt, int ns)
+{
+    if (cw == 1) return gt == 0 && ns == 1;
+    if (ns == 1) return true;
+    return rg <= 3 && (hc <= 2 || (hc == 3 && (rg == 1 || gt == 1)) || (hc == 4 && rg == 1 && gt == 1));
+}
 
 // Candidate voxel columns of pixel columns c .. c+cw-1 in slab n: in-plane lines through the two outer u-edges of
 // the bundle, written as "minor index = m * major index + b".  Wave-uniform.
@@ -374,8 +389,6 @@ __device__ __forceinline__ void fp_store_four(float *__restrict__ dst, float a, 
     }
     *reinterpret_cast<Quad *>(dst) = q;
 }
-
-constexpr int FP_WAVES = 4;      // waves per workgroup: adjacent column bundles of one view (each wave its own LDS, no barrier)
 
 // HC: highest height class of the scan's rows (1 .. 4); RG: groups of 128 rows per wave; CW: adjacent detector columns per wave;
 // GT: 0 flat or parallel, 1 cylindrical detector, 2 modular geometry with upright modules; NS: volumes per wave.

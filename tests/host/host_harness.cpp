@@ -394,6 +394,9 @@ extern "C" long host_project_columns(const leap_geometry *G, const float *vol, f
     }
 }
 
+// How many of a launch's items go two to a wave.
+extern "C" int host_forward_paired(const leap_geometry *G, int items) { return leap_forward_paired(G, items); }
+
 // ---- Siddon column-wise forward projection: the kernel's own functions, serially, with every read of the padded copy
 // checked ----
 // Returns -1 when the handle does not use that kernel, else the number of reads that would leave the scratch array.

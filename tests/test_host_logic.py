@@ -985,3 +985,30 @@ def test_wide_windows_need_enough_workgroups(host, nx, ny, nz, wide):
     desc = B.leap_geometry_describe(h, host)
     B.leap_geometry_destroy(h, host)
     assert ("zc=32,wide" in desc) == wide, desc
+
+
+def scan_of(n, nviews, nrows, ncols, pixel_v=1.4, geom=CONE):
+    return CTConfig("batch", geom, nviews=nviews, arc_deg=360.0, nrows=nrows, ncols=ncols, pixel_v=pixel_v, pixel_u=1.5, nx=n, ny=n, nz=n,
+                    voxel_xy=1.0, voxel_z=1.0, sod=2.6 * n, sdd=3.9 * n, shift_u=0.3, shift_v=0.2)
+
+
+@pytest.mark.parametrize("cfg,pairs", [
+    # workgroups of one group of rows: views times column tiles of eight or sixteen
+    (scan_of(64, 30, 70, 89), {2: 0, 3: 0, 5: 0, 8: 8, 16: 16}),             # 360 a volume
+    (scan_of(64, 90, 70, 89), {2: 2, 3: 0, 4: 4, 5: 0, 8: 8}),               # 1080
+    (scan_of(64, 180, 70, 89), {1: 0, 2: 2, 3: 2, 7: 6, 16: 16}),            # 2160
+    # several groups of rows
+    (scan_of(192, 60, 264, 268), {2: 0, 3: 0, 5: 0, 8: 8}),                  # 1020
+    (scan_of(192, 250, 264, 268), {2: 2, 3: 2, 8: 8}),                       # 4250
+    (config(4), {1: 0, 2: 0, 3: 0, 4: 0, 6: 6, 7: 0, 8: 8}),                 # 1440
+    # rows of 1.5 voxels and more: one group only, of two voxels and more: none (but on a cylinder)
+    (scan_of(64, 180, 46, 89, pixel_v=2.2), {2: 2, 3: 2}),
+    (scan_of(192, 180, 264, 268, pixel_v=2.2), {2: 0, 8: 0, 16: 0}),
+    (scan_of(64, 720, 70, 89, pixel_v=3.4), {2: 0, 16: 0}),
+    (scan_of(64, 180, 70, 89, pixel_v=3.4, geom=CONE_CURVED), {2: 2, 3: 2}),
+])
+def test_two_volumes_per_wave_need_waves_enough(host, cfg, pairs):
+    """Batches whose pairs would leave the chip idle, and odd ones whose last item would, go one volume per wave."""
+    h = handle(host, cfg)
+    assert {items: host.host_forward_paired(C.c_void_p(h), items) for items in pairs} == pairs, B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
