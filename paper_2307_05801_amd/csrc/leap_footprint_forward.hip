@@ -106,6 +106,7 @@ bool leap_launch_footprint_slab(const leap_geometry *G, const FwdScratch &S, con
 {
     if (G->fp_rows) return launch_fp_rows_slab(G, S, slab, d_sino, stream, items);
     switch (fp_height_class(G->fp_nkp)) {
+    case 0: return launch_fp_sets<0>(G, S, slab, d_sino, stream, items);
     case 1: return launch_fp_sets<1>(G, S, slab, d_sino, stream, items);
     case 2: return launch_fp_sets<2>(G, S, slab, d_sino, stream, items);
     case 3: return launch_fp_sets<3>(G, S, slab, d_sino, stream, items);

@@ -40,8 +40,8 @@ constexpr int FP_PAD = 8;        // zero voxels before and after every z-column 
 constexpr int FP_MAX_P = 7;      // most voxels a pair of adjacent rows may overlap (rows of up to 3 voxels)
 constexpr int FP_WAVES = 4;      // waves per workgroup: adjacent column bundles of one view (each wave its own LDS, no barrier)
 
-// Highest height class (see sf_pair_class) of a scan whose pairs of rows overlap up to nkp voxels.
-SF_HD int fp_height_class(int nkp) { return nkp <= 3 ? 1 : (nkp <= 5 ? nkp - 2 : 4); }
+// Highest height class (see SfPairClass) of a scan whose pairs of rows overlap up to nkp voxels.
+SF_HD int fp_height_class(int nkp) { return nkp <= 5 ? nkp - 2 : 4; }
 
 // Instances of the column-wise kernel by height class, row groups, columns per wave, detector (GT) and volumes per wave.  Two volumes per
 // wave: rows of up to a voxel and a half, taller ones where the sums and voxels of two leave enough waves in flight.  Two against one per
@@ -184,7 +184,8 @@ constexpr int sf_single_of_pair(int P) { return P / 2 + 1; }
 // rows of a voxel and more
 //   S_A = (1 - fr) x_0 + sum a_t x_t,    S_B = sum (b_t - a_t) x_t        (t >= 1; the upper row does not reach voxel 0).
 // Rows are sorted into classes by their height, LO2 / 2 <= mu <= HI2 / 2, so that what is known to be 0 or 1 costs nothing: a pair
-// of rows of up to one voxel reads three voxels and takes eleven instructions, one of up to a voxel and a half four and thirteen
+// of rows of up to half a voxel reads two voxels and takes eight instructions, one of up to a voxel three and eleven, one of up to a voxel
+// and a half four and thirteen
 // (sixteen while one body served every height up to a voxel and a half).  The clamps and weights depend on no voxel, so a lane that
 // carries several volumes forms them once.
 // Offsets of the clamps, the same for every row of the detector, worked out once per candidate: ka[t-1] = mu - (t+1), kb[t-1] = 2 mu - (t+1).
@@ -256,10 +257,11 @@ SF_HD void sf_pair_apply(const float *x, const SfPairWeights<LO2, HI2> &w, float
     }
 }
 
-// Height classes: 1 up to a voxel, 2 up to a voxel and a half, 3 up to two, 4 up to three voxels.
+// Height classes: 1 up to a voxel, 2 up to a voxel and a half, 3 up to two, 4 up to three voxels; 0, up to half a voxel, is for scans all
+// of whose rows are as short.
 template <int CLS>
 struct SfPairClass {
-    static constexpr int LO2 = CLS == 1 ? 0 : CLS, HI2 = CLS == 4 ? 6 : CLS + 1, P = HI2 + 1;
+    static constexpr int LO2 = CLS <= 1 ? 0 : CLS, HI2 = CLS == 4 ? 6 : CLS + 1, P = HI2 + 1;
 };
 SF_HD int sf_pair_class(float mu) { return mu <= 1.0f ? 1 : (mu <= 1.5f ? 2 : (mu <= 2.0f ? 3 : 4)); }
 
@@ -284,7 +286,8 @@ SF_HD void sf_pair_sums(const float (&x)[P], float fr1, const SfPairConsts<P> &c
 {
     float run[FP_MAX_P] = {};
     for (int t = 0; t < P; ++t) run[t] = x[t];
-    switch (sf_pair_class(c.k.mu)) {
+    switch (P == 2 ? 0 : sf_pair_class(c.k.mu)) {
+    case 0: sf_pair_sums_of_class<0>(run, fr1, c.k, sa, sb); break;
     case 1: sf_pair_sums_of_class<1>(run, fr1, c.k, sa, sb); break;
     case 2: sf_pair_sums_of_class<2>(run, fr1, c.k, sa, sb); break;
     case 3: sf_pair_sums_of_class<3>(run, fr1, c.k, sa, sb); break;
@@ -390,7 +393,7 @@ __device__ __forceinline__ void fp_store_four(float *__restrict__ dst, float a, 
     *reinterpret_cast<Quad *>(dst) = q;
 }
 
-// HC: highest height class of the scan's rows (1 .. 4); RG: groups of 128 rows per wave; CW: adjacent detector columns per wave;
+// HC: highest height class of the scan's rows (0 .. 4); RG: groups of 128 rows per wave; CW: adjacent detector columns per wave;
 // GT: 0 flat or parallel, 1 cylindrical detector, 2 modular geometry with upright modules; NS: volumes per wave.
 // (The cylinder's record phase needs more registers: its instances are held to the waves per SIMD they reach without
 // the records' staging, four up to two row groups, three beyond.)
@@ -474,13 +477,13 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
         const unsigned colbase = sf_slab_column(slab, g.nx, ic, jc) * (unsigned)nzp;   // start of the padded column
         const int mu_lo = __double2loint(mu), mu_hi = __double2hiint(mu);
         const float muf = (float)mu;
-        const int cls = HC > 1 ? sf_pair_class(muf) : 1;
+        const int cls = HC > 1 ? sf_pair_class(muf) : HC;
         {
             const SfPairOffsets k = sf_pair_offsets(muf);
             float4 f4 = make_float4(fa[0], 0.0f, 0.0f, 0.0f);
             if constexpr (CW > 1) f4.y = fa[1];
             if constexpr (CW > 2) { f4.z = fa[2]; f4.w = fa[3]; }
-            const bool below1 = HC == 1 || cls <= 1, below2 = HC <= 2 || cls <= 2;
+            const bool below1 = HC <= 1 || cls <= 1, below2 = HC <= 2 || cls <= 2;
             // (the wave has consumed every value it read from the previous block's records)
             rec[lane][0] = f4;
             rec[lane][1] = make_float4(below1 || (HC > 3 && cls > 3) ? k.mu : k.ka[0], below1 ? k.ka[0] : k.ka[1],
@@ -506,7 +509,7 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
                 const float4 r0 = rec[e][0], r1 = rec[e][1];
                 const float fcol[4] = {r0.x, r0.y, r0.z, r0.w};
                 SfPairOffsets k;
-                if constexpr (CLS == 1) { k.mu = r1.x; k.ka[0] = r1.y; k.kb[0] = r1.z; k.kb[1] = r1.w; }
+                if constexpr (CLS <= 1) { k.mu = r1.x; k.ka[0] = r1.y; k.kb[0] = r1.z; k.kb[1] = r1.w; }
                 if constexpr (CLS == 2) { k.ka[0] = r1.x; k.ka[1] = r1.y; k.kb[1] = r1.z; k.kb[2] = r1.w; }
                 if constexpr (CLS == 3) { k.ka[0] = r1.x; k.ka[1] = r1.y; k.kb[2] = r1.z; k.kb[3] = r1.w; }
                 if constexpr (CLS == 4) k = sf_pair_offsets(r1.x);
@@ -561,7 +564,7 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
             walk(cc, todo & ~above);
             todo &= above;
         };
-        walk_up_to(std::integral_constant<int, 1>{});
+        walk_up_to(std::integral_constant<int, (HC < 1 ? HC : 1)>{});
         if constexpr (HC > 1) walk_up_to(std::integral_constant<int, 2>{});
         if constexpr (HC > 2) walk_up_to(std::integral_constant<int, 3>{});
         if constexpr (HC > 3) walk_up_to(std::integral_constant<int, 4>{});

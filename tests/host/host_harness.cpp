@@ -397,6 +397,13 @@ extern "C" long host_project_columns(const leap_geometry *G, const float *vol, f
 // How many of a launch's items go two to a wave.
 extern "C" int host_forward_paired(const leap_geometry *G, int items) { return leap_forward_paired(G, items); }
 
+// Voxels a pair of adjacent rows reads in the scan's highest height class.
+extern "C" int host_voxels_of_pair(const leap_geometry *G)
+{
+    static constexpr int voxels[] = {SfPairClass<0>::P, SfPairClass<1>::P, SfPairClass<2>::P, SfPairClass<3>::P, SfPairClass<4>::P};
+    return voxels[fp_height_class(G->fp_nkp)];
+}
+
 // ---- Siddon column-wise forward projection: the kernel's own functions, serially, with every read of the padded copy
 // checked ----
 // Returns -1 when the handle does not use that kernel, else the number of reads that would leave the scratch array.

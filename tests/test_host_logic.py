@@ -1012,3 +1012,11 @@ def test_two_volumes_per_wave_need_waves_enough(host, cfg, pairs):
     h = handle(host, cfg)
     assert {items: host.host_forward_paired(C.c_void_p(h), items) for items in pairs} == pairs, B.leap_geometry_describe(h, host)
     B.leap_geometry_destroy(h, host)
+
+
+@pytest.mark.parametrize("pixel_v,voxels", [(0.57, 2), (0.75, 3), (1.5, 4), (2.2, 5), (2.9, 7)])
+def test_pairs_of_rows_read_no_more_voxels_than_they_overlap(host, pixel_v, voxels):
+    """Rows of up to half a voxel, a voxel, a voxel and a half, two, three."""
+    h = handle(host, scan_of(64, 8, 60, 89, pixel_v=pixel_v))
+    assert host.host_voxels_of_pair(C.c_void_p(h)) == voxels, B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
