@@ -47,8 +47,9 @@ static bool launch_bp_shape(const leap_geometry *G, const float *d_sino, float *
 int leap_launch_footprint_back(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     bool ok = false;
-    if (G->bp_split_shape >= 0) {
-        if (!leap_launch_backproject_split(G, d_sino, d_vol, items, stream)) {
+    const int split = leap_back_split_shape(G, items);
+    if (split >= 0) {
+        if (!leap_launch_backproject_split(G, split, d_sino, d_vol, items, stream)) {
             leap_set_error("internal: no back-projection instance that shares the views for this footprint");
             return LEAP_UNSUPPORTED;
         }
@@ -57,12 +58,7 @@ int leap_launch_footprint_back(const leap_geometry *G, const float *d_sino, floa
     }
     if (G->bp_pair_shape >= 0) {
         // two volumes per workgroup: an item and its mirror image, or two items of the batch; an odd last item by itself
-        int blocks = G->bp_mirror ? items : items / 2;
-        // Two items where there are workgroups enough (the bits are the same): eight volumes, 60 views, one by one / in twos, us: 32 voxels per
-        // thread 64^3 (128 workgroups of two) 145 / 195, 96^3 (432) 209 / 193; wide windows 64^3 (256) 202 / 230, 96^3 (864) 419 / 434, 128^3
-        // (2048) 890 / 742.
-        const SfBpShape S = BP_PAIR_SHAPES[G->bp_pair_shape];
-        if (!G->bp_mirror && cdiv(G->g.nx, BP_T) * cdiv(G->g.ny, BP_T) * cdiv(G->g.nz, S.zc) * (unsigned)blocks < (S.pw > 32 ? 1200u : 400u)) blocks = 0;
+        const int blocks = leap_back_pairs(G, items);
         if (blocks && !leap_launch_backproject_pairs(G, d_sino, d_vol, blocks, stream)) {
             leap_set_error("internal: no back-projection instance of two volumes for this footprint");
             return LEAP_UNSUPPORTED;

@@ -32,10 +32,10 @@ static bool launch_instance(const leap_geometry *G, const float *d_sino, float *
 }
 
 template <int NC, int NV, int NS>
-static bool launch_shape(const leap_geometry *G, const float *d_sino, float *d_vol, int blocks, hipStream_t stream)
+static bool launch_shape(const leap_geometry *G, int shape, const float *d_sino, float *d_vol, int blocks, hipStream_t stream)
 {
     static_assert(BP_NSPLIT_SHAPES == 3, "every shape has a case");
-    switch (G->bp_split_shape) {
+    switch (shape) {
     case 0: return launch_instance<NC, NV, 0, NS>(G, d_sino, d_vol, blocks, stream);
     case 1: return launch_instance<NC, NV, 1, NS>(G, d_sino, d_vol, blocks, stream);
     case 2: return launch_instance<NC, NV, 2, NS>(G, d_sino, d_vol, blocks, stream);
@@ -44,28 +44,26 @@ static bool launch_shape(const leap_geometry *G, const float *d_sino, float *d_v
 }
 
 template <int NC, int NV>
-static bool launch_sets(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
+static bool launch_sets(const leap_geometry *G, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
-    // two volumes per workgroup: an item and its mirror image, or two items of the batch; an odd last item by itself
-    const bool two = G->g.type != SF_MODULAR;
-    const int pairs = G->bp_mirror ? items : (two ? items / 2 : 0), left = G->bp_mirror ? 0 : items - 2 * pairs;
-    if (pairs && !launch_shape<NC, NV, 2>(G, d_sino, d_vol, pairs, stream)) return false;
+    const int pairs = leap_back_split_pairs(G, items), left = G->bp_mirror ? 0 : items - 2 * pairs;
+    if (pairs && !launch_shape<NC, NV, 2>(G, shape, d_sino, d_vol, pairs, stream)) return false;
     d_sino += (size_t)(items - left) * G->g.nviews * G->g.nrows * G->g.ncols;
     d_vol += (size_t)(items - left) * G->g.nx * G->g.ny * G->g.nz;
-    return !left || launch_shape<NC, NV, 1>(G, d_sino, d_vol, left, stream);
+    return !left || launch_shape<NC, NV, 1>(G, shape, d_sino, d_vol, left, stream);
 }
 
-bool leap_launch_backproject_split(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
+bool leap_launch_backproject_split(const leap_geometry *G, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     switch (G->bp_nc * 10 + G->bp_nv) {
-    case 22: return launch_sets<2, 2>(G, d_sino, d_vol, items, stream);
-    case 23: return launch_sets<2, 3>(G, d_sino, d_vol, items, stream);
-    case 32: return launch_sets<3, 2>(G, d_sino, d_vol, items, stream);
-    case 33: return launch_sets<3, 3>(G, d_sino, d_vol, items, stream);
-    case 42: return launch_sets<4, 2>(G, d_sino, d_vol, items, stream);
-    case 43: return launch_sets<4, 3>(G, d_sino, d_vol, items, stream);
-    case 52: return launch_sets<5, 2>(G, d_sino, d_vol, items, stream);
-    case 53: return launch_sets<5, 3>(G, d_sino, d_vol, items, stream);
+    case 22: return launch_sets<2, 2>(G, shape, d_sino, d_vol, items, stream);
+    case 23: return launch_sets<2, 3>(G, shape, d_sino, d_vol, items, stream);
+    case 32: return launch_sets<3, 2>(G, shape, d_sino, d_vol, items, stream);
+    case 33: return launch_sets<3, 3>(G, shape, d_sino, d_vol, items, stream);
+    case 42: return launch_sets<4, 2>(G, shape, d_sino, d_vol, items, stream);
+    case 43: return launch_sets<4, 3>(G, shape, d_sino, d_vol, items, stream);
+    case 52: return launch_sets<5, 2>(G, shape, d_sino, d_vol, items, stream);
+    case 53: return launch_sets<5, 3>(G, shape, d_sino, d_vol, items, stream);
     default: return false;
     }
 }

@@ -274,6 +274,84 @@ static bool mirrored_about_source_plane(const leap_geometry *G)
     return (d->type == LEAP_CONE || d->type == LEAP_CONE_CURVED || d->type == LEAP_PARALLEL) && d->shift_v == 0.0 && d->center_z == 0.0;
 }
 
+// What a launch of the tiled back projections takes per view, in units of 32 voxels per thread under a narrow window on an idle chip
+// (2.8 us): `idle` while its workgroups have a compute unit each, `full` per round of 256 workgroups once the compute units are full; a
+// launch takes as long as `views` further views whatever it holds (the window's first loads, the sums of groups of threads that share
+// the views).
+struct LaunchTime {
+    double idle, full, views;
+};
+static double launch_time(const LaunchTime &t, double workgroups, int views)
+{
+    const double rounds = std::ceil(workgroups / 256.0);
+    return std::max(t.idle * (1.0 + 0.07 * (rounds - 1.0)), t.full * rounds) * (views + t.views);
+}
+
+// Footprint model: one volume and two volumes per workgroup by shape; views shared, one volume and two (one volume of 16 voxels or fewer: two
+// workgroups of 1024 threads per compute unit, but not on a cylinder).
+static const LaunchTime BP_TIMES[BP_NSHAPES] = {{1.35, 0.53, 0.5}, {1.0, 0.33, 0.5}, {1.15, 0.38, 0.5}, {0.7, 0.23, 0.5},
+                                                {1.18, 0.37, 0.5}, {1.85, 0.68, 0.5}, {1.35, 0.51, 0.5}};
+static const LaunchTime BP_PAIR_TIMES[BP_NPAIR_SHAPES] = {{1.35, 0.55, 1.0}, {1.4, 0.58, 1.0}, {0.9, 0.27, 1.0}, {1.35, 0.59, 1.0}};
+static const LaunchTime BP_SPLIT_TIMES[2][BP_NSPLIT_SHAPES] = {{{0.42, 0.43, 4.0}, {0.29, 0.24, 4.0}, {0.24, 0.20, 4.0}},
+                                                               {{0.56, 0.56, 4.0}, {0.34, 0.34, 4.0}, {0.29, 0.29, 4.0}}};
+constexpr int BP_FEW_VIEWS = 4;        // fewer leave a launch little but its start and end: 10 to 12 us whichever the kernel
+
+static int tile_chunks(const leap_geometry *G, int zc, int kfirst = 0)
+{
+    return ((G->g.nx + BP_T - 1) / BP_T) * ((G->g.ny + BP_T - 1) / BP_T) * ((G->g.nz - kfirst + zc - 1) / zc);
+}
+
+// Two items per workgroup where there are workgroups enough (the bits are the same): eight volumes, 60 views, one by one / in twos, us: 32
+// voxels per thread 64^3 (128 workgroups of two) 145 / 195, 96^3 (432) 209 / 193; wide windows 64^3 (256) 202 / 230, 96^3 (864) 419 / 434,
+// 128^3 (2048) 890 / 742.
+int leap_back_pairs(const leap_geometry *G, int items)
+{
+    if (G->bp_pair_shape < 0) return 0;
+    if (G->bp_mirror) return items;
+    const SfBpShape S = BP_PAIR_SHAPES[G->bp_pair_shape];
+    const int chunks = tile_chunks(G, S.zc), views = G->g.nviews;
+    if (chunks * (items / 2) < (S.pw > 32 ? 1200 : 400) || views < BP_FEW_VIEWS) return 0;
+    // (an odd last item is a launch of its own: one more than the two would save where a launch is a few rounds of workgroups)
+    const double twos = launch_time(BP_PAIR_TIMES[G->bp_pair_shape], (double)chunks * (items / 2), views);
+    if (items % 2 && twos + launch_time(BP_TIMES[G->bp_shape], chunks, views) > 0.93 * launch_time(BP_TIMES[G->bp_shape], (double)chunks * items, views)) return 0;
+    return items / 2;
+}
+
+// Launches that leave the chip idle: four groups of threads share the views.  A step from view to view takes a workgroup of 256 threads
+// much the same time until there are two or three per compute unit, so four groups beside each other save up to three quarters of it;
+// but a workgroup of 1024 threads fills a compute unit, and short chunks stage more rows per voxel.  One volume takes the shape of least
+// time by its workgroups and views; a batch takes that one too (its items then come out the same bits as alone) as long as it is a gain,
+// then another that is, then none.  60 views, us, unsplit / 8 / 16 / 32 voxels: mirror image 64^3 138 / 41 / 53 / 79, four of them 138 / 44 /
+// 54 / 79, sixteen 175 / 161 / 119 / 105; off centre 96^3 138 / 55 / 46 / 61, sixteen 373 / 583 / 370 / 308; 16 items of one view 96^3 26 /
+// 66 / 60 / 57.  (Lines by the workgroups of one volume alone, whatever the batch and the views, had 580 of 4260 launches of 24^3 to
+// 192^3, 1 to 16 items, 1 to 180 views above 1.035 times the unsplit time, up to 2.6.)
+int leap_back_split_shape(const leap_geometry *G, int items)
+{
+    const int views = G->g.nviews, kfirst = G->bp_mirror ? sf_mirror_first_voxel_above(G->g.nz) : 0;
+    if (!G->bp_split_fits || (views < BP_FEW_VIEWS && !G->bp_split_forced)) return -1;
+    const int pairs = leap_back_pairs(G, items), left = G->bp_mirror && pairs ? 0 : items - 2 * pairs;
+    double unsplit = 0.0;
+    if (pairs) unsplit += launch_time(BP_PAIR_TIMES[G->bp_pair_shape], (double)tile_chunks(G, BP_PAIR_SHAPES[G->bp_pair_shape].zc, kfirst) * pairs, views);
+    if (left) unsplit += launch_time(BP_TIMES[G->bp_shape], (double)tile_chunks(G, BP_SHAPES[G->bp_shape].zc) * left, views);
+    unsplit *= 0.93;                                   // (a clear gain: the times are good to some five per cent)
+    const int twos = leap_back_split_pairs(G, items), ones = G->bp_mirror ? 0 : items - 2 * twos;
+    auto time_of = [&](int sh) {
+        const double chunks = tile_chunks(G, BP_SPLIT_SHAPES[sh].zc, kfirst), wider = BP_SPLIT_SHAPES[sh].pw > 32 && G->bp_need_w > 31 ? 1.25 : 1.0;
+        return wider * ((twos ? launch_time(BP_SPLIT_TIMES[1][sh], chunks * twos, views) : 0.0) +
+                        (ones ? launch_time(BP_SPLIT_TIMES[G->g.type == SF_CONE_CURVED][sh], chunks * ones, views) : 0.0));
+    };
+    if (G->bp_split_shape >= 0 && (G->bp_split_forced || time_of(G->bp_split_shape) < unsplit)) return G->bp_split_shape;
+    if (G->bp_split_shape < 0 && items > 1) return -1;
+    int best = -1;
+    double least = unsplit;
+    for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh)
+        if ((G->bp_split_fits >> sh & 1u) && time_of(sh) < least) {
+            least = time_of(sh);
+            best = sh;
+        }
+    return best;
+}
+
 // Tiled back projection, two volumes per workgroup: the shapes that leave the chip enough workgroups.
 static std::vector<int> backproject_pair_shapes(leap_geometry *G)
 {
@@ -383,29 +461,26 @@ static void select_footprint_tiled(leap_geometry *G)
             ++p;
         }
     }
-    // Volumes that leave the chip idle: four groups of threads share the views.  Chunks of 8 voxels where the workgroups of one volume
-    // are few, then of 16, then of 32; the lines keep a batch of eight (whose items take the same chunks, to come out the same bits)
-    // no slower than it is without.  60 views, one volume, unsplit / 8 / 16 / 32 voxels, us, with the workgroups of each in brackets:
-    // parallel beams, mirror image: 64^3 138 / 41 (64) / 53 (32) / 79 (16), 96^3 138 / 43 (216) / 54 (108) / 80 (72), 128^3 135 / 82
-    // (512) / 57 (256) / 82 (128), 160^3 131 / 160 / 106 (500) / 159 (300); off centre: 64^3 138 / 36 (128) / 44 (64) / 60 (32), 96^3
-    // 138 / 55 (432) / 46 (216) / 61 (108), 128^3 235 / 103 / 69 (512) / 67 (256), 192^3 245 / 334 / 224 / 233 (864), 224^3 352 / 521 / 341
-    // / 347 (1372).  Eight volumes of 96^3: mirror image 209 / 277 / 206 / 233, off centre 209 / 277 / 206 / 161; of 128^3 366 / 628 / 410 /
-    // 328 and 378 / 627 / 410 / 316.
-    // Wide windows, unsplit / 8 voxels: mirror image 96^3 186 / 65 (216), 128^3 196 / 129 (512), 144^3 248 / 183 (729), 160^3 243 / 233
-    // (1000); off centre 96^3 187 / 84 (432), 112^3 220 / 126 (686), 128^3 197 / 162 (1024; eight of them 742 / 954), 160^3 261 / 292.
-    if (G->bp_tiled && G->bp_nv <= 3) {
-        const bool narrow = known.front().w <= BP_SPLIT_SHAPES[0].pw - 1;
-        const int limits[2][3] = {{900, 256, narrow ? 128 : 700}, {256, 128, narrow ? 64 : 800}};     // [mirror][shape]
-        long only = -2;
-        debug_option("bp_split", only);
-        for (int sh = BP_NSPLIT_SHAPES - 1; sh >= 0 && only != -1 && G->bp_split_shape < 0; --sh) {
-            const SfBpShape S = BP_SPLIT_SHAPES[sh];
-            const int workgroups = tiles * ((d->nz - kfirst + S.zc - 1) / S.zc);
-            if (only >= 0 ? only != sh : workgroups > limits[G->bp_mirror][sh]) continue;
-            if (!bp_split_instance_exists(G->bp_nc, G->bp_nv, sh) || known.front().w > S.pw - 1) continue;
-            if (need_of(S.zc, kfirst) == known.end()) look_at({{S.zc, kfirst}});
-            if (window_fits(*need_of(S.zc, kfirst), S)) G->bp_split_shape = sh;
+    // Four groups of threads that share the views: the shapes whose windows fit, where one volume would take any of them.
+    long only = -2;
+    debug_option("bp_split", only);
+    if (G->bp_tiled && G->bp_nv <= 3 && only != -1) {
+        const int wide = known.front().w;
+        auto exists = [&](int sh) { return bp_split_instance_exists(G->bp_nc, G->bp_nv, sh) && wide <= BP_SPLIT_SHAPES[sh].pw - 1 && (only < 0 || only == sh); };
+        unsigned candidates = 0;
+        for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh) candidates |= exists(sh) ? 1u << sh : 0u;
+        G->bp_split_fits = candidates;
+        if (only >= 0 || leap_back_split_shape(G, 1) >= 0) {
+            std::vector<WindowNeed> needs;
+            for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh)
+                if ((candidates >> sh & 1u) && need_of(BP_SPLIT_SHAPES[sh].zc, kfirst) == known.end()) needs.push_back({BP_SPLIT_SHAPES[sh].zc, kfirst});
+            look_at(needs);
+            for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh)
+                if ((candidates >> sh & 1u) && !window_fits(*need_of(BP_SPLIT_SHAPES[sh].zc, kfirst), BP_SPLIT_SHAPES[sh])) G->bp_split_fits &= ~(1u << sh);
+            G->bp_split_forced = only >= 0 && G->bp_split_fits != 0;
+            G->bp_split_shape = G->bp_split_forced ? (int)only : leap_back_split_shape(G, 1);
         }
+        if (G->bp_split_shape < 0) G->bp_split_fits = 0;
     }
     // Cylinder: the tiled kernel takes the angle between a voxel's centre and its corners from a short series,
     // good to 3e-9 rad below 0.08 rad.
@@ -414,7 +489,10 @@ static void select_footprint_tiled(leap_geometry *G)
         const double nearest = d->sod - std::sqrt(rx * rx + ry * ry);
         if (!(0.7072 * d->voxel_xy <= 0.08 * nearest)) G->bp_tiled = false;
     }
-    if (!G->bp_tiled) G->bp_pair_shape = -1;
+    if (!G->bp_tiled) {
+        G->bp_pair_shape = G->bp_split_shape = -1;
+        G->bp_split_fits = 0;
+    }
 }
 
 // Row groups per wave of the column-wise forward kernels.  A wave pays a fixed share per candidate voxel column (its

@@ -397,6 +397,10 @@ extern "C" long host_project_columns(const leap_geometry *G, const float *vol, f
 // How many of a launch's items go two to a wave.
 extern "C" int host_forward_paired(const leap_geometry *G, int items) { return leap_forward_paired(G, items); }
 
+// Back projection of a launch's items: the shape whose groups of threads share the views (-1: none), pairs of items per workgroup.
+extern "C" int host_back_split_shape(const leap_geometry *G, int items) { return leap_back_split_shape(G, items); }
+extern "C" int host_back_pairs(const leap_geometry *G, int items) { return leap_back_pairs(G, items); }
+
 // Voxels a pair of adjacent rows reads in the scan's highest height class.
 extern "C" int host_voxels_of_pair(const leap_geometry *G)
 {

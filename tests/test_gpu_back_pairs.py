@@ -123,3 +123,25 @@ def test_views_shared_on_upright_modules(torch_mod, oracle_mod):
         assert rel_l2(out[b].cpu().numpy(), oracle_mod.backproject(cfg, y[b])) <= TOL
         assert torch_mod.equal(out[b], geo.backproject(yt[b].contiguous()))
     geo.close()
+
+
+@pytest.mark.parametrize("geometry", [PARALLEL, CONE, CONE_CURVED])
+@pytest.mark.parametrize("shift_v", [0.0, 0.25])
+def test_batches_of_every_size(torch_mod, oracle_mod, geometry, shift_v):
+    """A batch that fills the chip takes another kernel than one volume: the same sums in another order, to the last bits."""
+    from paper_2307_05801_amd import Geometry
+    cfg = scan(geometry, 64, 70, 2.0 / 1.5 if geometry == PARALLEL else 2.0, nx=96, ny=93).replace(nviews=8, ncols=130, shift_v=shift_v)
+    if geometry != PARALLEL:
+        cfg = cfg.replace(sod=400.0, sdd=600.0)
+    geo = Geometry(cfg)
+    print(f"[gpu] {geometry} {shift_v}: {geo.describe()}", flush=True)
+    assert "+split" in geo.describe(), geo.describe()
+    y = torch_mod.from_numpy(uniform_sinogram(cfg, 9, batch=17)).cuda()
+    alone = torch_mod.stack([geo.backproject(y[b].contiguous()) for b in range(17)])
+    assert rel_l2(alone[16].cpu().numpy(), oracle_mod.backproject(cfg, y[16].cpu().numpy())) <= TOL
+    for batch in (1, 2, 3, 8, 15, 17):                      # (the seventeenth item is a launch of its own)
+        out = geo.backproject(y[:batch].contiguous())
+        assert torch_mod.equal(out, geo.backproject(y[:batch].contiguous())), batch
+        for b in range(batch):                              # sums of eight views' shares in two orders: 8 * 2^-24 at most
+            assert float((out[b] - alone[b]).norm()) <= 5e-7 * float(alone[b].norm()), (batch, b)
+    geo.close()

@@ -1020,3 +1020,43 @@ def test_pairs_of_rows_read_no_more_voxels_than_they_overlap(host, pixel_v, voxe
     h = handle(host, scan_of(64, 8, 60, 89, pixel_v=pixel_v))
     assert host.host_voxels_of_pair(C.c_void_p(h)) == voxels, B.leap_geometry_describe(h, host)
     B.leap_geometry_destroy(h, host)
+
+
+def small_scan(n, nviews, nz=None, shift_v=0.0, pixel=1.0, geom=PARALLEL):
+    par = geom == PARALLEL
+    nz = nz or n
+    return CTConfig("small", geom, nviews=nviews, arc_deg=180.0, nrows=int(1.1 * nz / pixel), ncols=int(1.4 * n / pixel),
+                    pixel_v=pixel if par else 1.5 * pixel, pixel_u=pixel if par else 1.5 * pixel, nx=n, ny=n, nz=nz, voxel_xy=1.0, voxel_z=1.0,
+                    sod=0.0 if par else 2.6 * n, sdd=0.0 if par else 3.9 * n, shift_u=0.3, shift_v=shift_v)
+
+
+# shapes: 0, 1, 2: 32, 16, 8 voxels per thread; what was measured fastest or within a few per cent of it
+@pytest.mark.parametrize("cfg,shapes", [
+    (small_scan(64, 60), {1: 2, 4: 2, 16: 0}),                          # mirror image
+    (small_scan(64, 60, shift_v=0.2), {1: 2, 2: 2, 8: 2, 16: 0}),
+    (small_scan(96, 60), {1: 2, 2: 2, 8: -1, 16: -1}),
+    (small_scan(96, 8, shift_v=0.2), {1: 1, 2: 1, 16: -1}),
+    (small_scan(64, 1), {1: -1, 16: -1}),                               # a single view: 12 us unsplit, up to 23 split
+    (small_scan(100, 60, pixel=0.6), {1: 2, 2: 2, 16: -1}),             # wide windows
+    (small_scan(224, 60, shift_v=0.2), {1: -1, 16: -1}),                # the chip is full
+    (small_scan(96, 119, pixel=0.9, geom=CONE, shift_v=0.3), {1: 2, 16: -1}),
+])
+def test_views_are_shared_where_the_launch_leaves_the_chip_idle(host, cfg, shapes):
+    """By the launch's workgroups, its items among them, and its views: a large batch of small volumes, or few views, are faster unsplit."""
+    h = handle(host, cfg)
+    got = {items: host.host_back_split_shape(C.c_void_p(h), items) for items in shapes}
+    assert got == shapes, B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
+
+
+@pytest.mark.parametrize("cfg,pairs", [
+    (small_scan(134, 60, nz=67, shift_v=0.2, pixel=1.4), {2: 0, 3: 0, 5: 0, 8: 4, 16: 8}),
+    (small_scan(134, 8, nz=67, shift_v=0.2, pixel=1.4), {5: 0, 8: 4}),
+    (small_scan(134, 1, nz=67, shift_v=0.2, pixel=1.4), {5: 0, 16: 0}),
+    (small_scan(134, 60, nz=67, pixel=1.4), {1: 0, 16: 0}),             # mirror image: too few workgroups for two volumes in each
+    (small_scan(256, 60), {1: 1, 3: 3}),                                # ... and enough
+])
+def test_two_items_per_workgroup_where_there_are_workgroups_enough(host, cfg, pairs):
+    h = handle(host, cfg)
+    assert {items: host.host_back_pairs(C.c_void_p(h), items) for items in pairs} == pairs, B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
