@@ -369,9 +369,8 @@ static std::vector<int> backproject_pair_shapes(leap_geometry *G)
         // Mirror image, parallel beams, 120 views, one volume / 32 + 32 / 16 + 16 voxels per thread: 256^3 (1024 workgroups of the
         // larger) 693 / 552 / 648 us, 224^3 (784) 689 / 537 / 534, 192^3 (432) 479 / 375 / 358, 160^3 (300; 500 of the smaller) 476 /
         // 372 / 257, 128^3 (256 of the smaller) 465 / 378 / 262, 112^3 280 / 379 / 261, 64^3 267 / 369 / 247.
-        // Wide windows leave room for 768 workgroups: 60 views, one volume of 42 columns and 32 voxels or of 64 and 16 / 51 columns and 16 + 16
-        // voxels, us: 128^3 (256 workgroups) 196 / 229, 160^3 (500) 260 / 243, 192^3 (864: a second round nearly empty) 378 / 424,
-        // 224^3 (1372) 560 / 501, 256^3 (2048) 690 / 687.
+        // Wide windows leave room for 768 workgroups: 60 views, one volume under 64 columns and 16 voxels / 51 columns and 16 + 16 voxels, us:
+        // 128^3 (256 workgroups) 196 / 229, 160^3 (500) 260 / 243; a second round nearly empty is none (192^3, 864 workgroups).
         const int workgroups = tiles * ((d->nz - kfirst + S.zc - 1) / S.zc);
         const bool enough = S.pw <= 32 ? workgroups >= (S.zc == 32 ? 800 : 250) : 10 * workgroups >= 6 * 768 * ((workgroups + 767) / 768);
         if (G->bp_mirror && only < 0 && !enough) continue;
@@ -461,6 +460,10 @@ static void select_footprint_tiled(leap_geometry *G)
             ++p;
         }
     }
+    // Where the 42-column window and its 32 voxels do, 16 + 16 under 51 columns are no gain.  42 columns / mirror image, 60 views, ratio, 256^3,
+    // three and eight of them, 256 x 256 x 128: rows of 0.85 voxels (voxels of up to 1.4 rows) 0.98, 1.03 and 1.14, of 1.05 1.02, 1.04 and
+    // 1.17, of 1.25 1.03, 1.07 and 1.18, of 1.4 1.08, 1.11 and 1.22; 224^3 0.89 to 1.00, three of them 1.01 to 1.12.
+    if (G->bp_mirror && G->bp_tiled && G->bp_shape == BP_WIDE_SHAPE && !debug_option("bp_pair", forced)) G->bp_pair_shape = -1;
     // Four groups of threads that share the views: the shapes whose windows fit, where one volume would take any of them.
     long only = -2;
     debug_option("bp_split", only);

@@ -1060,3 +1060,14 @@ def test_two_items_per_workgroup_where_there_are_workgroups_enough(host, cfg, pa
     h = handle(host, cfg)
     assert {items: host.host_back_pairs(C.c_void_p(h), items) for items in pairs} == pairs, B.leap_geometry_describe(h, host)
     B.leap_geometry_destroy(h, host)
+
+
+@pytest.mark.parametrize("pixel_u,shape", [(1.5, "zc=32,wide,window"), (1.1, "zc=16,window")])
+def test_mirror_image_under_wide_windows(host, pixel_u, shape):
+    """51 columns and 16 + 16 voxels where 42 columns do not hold the windows, 42 columns and 32 voxels of one volume where they do."""
+    cfg = CTConfig("w", CONE, nviews=8, arc_deg=360.0, nrows=180, ncols=400, pixel_v=1.45, pixel_u=pixel_u, nx=224, ny=224, nz=160,
+                   voxel_xy=1.0, voxel_z=1.0, sod=493.0, sdd=690.0, start_deg=3.0)
+    h = handle(host, cfg)
+    desc = B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
+    assert shape in desc and ("+mirror(zc=16,51x48)" in desc) == ("wide" not in desc), desc
