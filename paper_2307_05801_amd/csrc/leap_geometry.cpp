@@ -274,8 +274,8 @@ static bool mirrored_about_source_plane(const leap_geometry *G)
     return (d->type == LEAP_CONE || d->type == LEAP_CONE_CURVED || d->type == LEAP_PARALLEL) && d->shift_v == 0.0 && d->center_z == 0.0;
 }
 
-// What a launch of the tiled back projections takes per view, in units of 32 voxels per thread under a narrow window on an idle chip
-// (2.8 us): `idle` while its workgroups have a compute unit each, `full` per round of 256 workgroups once the compute units are full; a
+// What a launch of the tiled back projections takes per view, for footprints in units of 32 voxels per thread under a narrow window on an
+// idle chip (2.8 us): `idle` while its workgroups have a compute unit each, `full` per round of 256 workgroups once the compute units are full; a
 // launch takes as long as `views` further views whatever it holds (the window's first loads, the sums of groups of threads that share
 // the views).
 struct LaunchTime {
@@ -651,6 +651,58 @@ static void select_footprint_flat(leap_geometry *G)
     }
 }
 
+// Siddon model, launches that leave the chip idle: four groups of threads share the views (two under 64 columns on tilted modules), by the
+// launch's workgroups and views as for footprints (leap_back_split_shape); here the times are in us per view, and a round of the split
+// kernels is dearer where the window of the unsplit shape is larger (more pixels per voxel).  us, unsplit / 16 / 8 voxels per thread, 60
+// views: parallel beams 64^3 330 / 87 / 66, four of them 335 / 92 / 134, sixteen 358 / 351 / 524; 96^3 325 / 89 / 132, sixteen 1051 / 1215 /
+// 1764; 128^3 328 / 176 / 264, sixteen 2158 / 2765 / 4165; eight views of 128^3 43 / 29 / 44, sixteen 280 / 430 / 666.  Tilted modules, unsplit /
+// four groups: 64^3 437 / 111, sixteen 868 / 885, 128^3 460 / 432, four 1360 / 1700; 62 x 63 x 43 x 207 views 1796 / 422; where the window
+// leaves a compute unit one workgroup of 256 threads, 135 x 140 x 148 x 156 views 5598 / 1986, or two groups of threads 165 x 164 x 79 x 58 2440
+// / 1216, 234 x 196 x 225 x 206 22998 / 13630.
+int leap_siddon_split_shape(const leap_geometry *G, int items)
+{
+    static const LaunchTime one[BP_LAST_SHORT_SHAPE + 1] = {{}, {4.8, 1.95, 0.5}, {6.2, 3.25, 0.5}, {5.2, 2.05, 0.5}, {5.1, 2.05, 0.5}};
+    static const double split[BP_LAST_SHORT_SHAPE + 1][SD_BP_NSPLIT_SHAPES] = {{}, {1.3, 1.07}, {1.7, 1.45}, {1.95, 1.68}, {2.0, 1.45}};
+    static const LaunchTime tilted_one[MD_BP_NSHAPES] = {{6.9, 2.35, 0.5}, {8.5, 2.95, 0.5}, {14.0, 9.0, 0.5}, {10.0, 5.0, 0.5}, {18.0, 17.0, 0.5}, {12.4, 12.0, 0.5}};
+    static const double tilted_split[MD_BP_NSHAPES][MD_BP_NSPLIT_SHAPES] = {{1.65, 2.5}, {1.9, 2.9}, {2.2, 3.4}, {2.2, 3.4}, {2.2, 3.4}, {2.2, 3.4}};
+    const int views = G->g.nviews;
+    if (!G->bp_split_fits) return -1;
+    if (G->bp_split_shape >= 0 && G->bp_split_forced) return G->bp_split_shape;
+    if (views < 2 || (G->bp_split_shape < 0 && items > 1)) return -1;
+    const bool tilted = G->g.type == SF_MODULAR && G->geoms.empty();
+    auto workgroups = [&](const SfBpShape &S) { return (double)tile_chunks(G, S.zc) * items; };
+    const double unsplit = 0.93 * (tilted ? launch_time(tilted_one[G->bp_shape], workgroups(MD_BP_SHAPES[G->bp_shape]), views)
+                                          : launch_time(one[G->bp_shape], workgroups(BP_SHAPES[G->bp_shape]), views));
+    auto time_of = [&](int sh) {
+        const double round = (tilted ? tilted_split : split)[G->bp_shape][sh];
+        return launch_time({round, round, 3.0}, workgroups((tilted ? MD_BP_SPLIT_SHAPES : SD_BP_SPLIT_SHAPES)[sh]), views);
+    };
+    if (G->bp_split_shape >= 0 && time_of(G->bp_split_shape) < unsplit) return G->bp_split_shape;
+    int best = -1;
+    double least = unsplit;
+    for (int sh = 0; sh < (tilted ? MD_BP_NSPLIT_SHAPES : SD_BP_NSPLIT_SHAPES); ++sh)
+        if ((G->bp_split_fits >> sh & 1u) && time_of(sh) < least) {
+            least = time_of(sh);
+            best = sh;
+        }
+    return best;
+}
+
+// The shapes that fit (fits(shape): their windows do) and the one a single volume takes; `only`: the debugging option, -1 none, or that one.
+template <class FitsFn>
+static void choose_siddon_split(leap_geometry *G, long only, int nshapes, FitsFn fits)
+{
+    if (only == -1) return;
+    for (int sh = 0; sh < nshapes; ++sh)
+        if (only < 0 || only == sh) G->bp_split_fits |= 1u << sh;
+    if (only < 0 && leap_siddon_split_shape(G, 1) < 0) G->bp_split_fits = 0;
+    for (int sh = 0; sh < nshapes; ++sh)
+        if ((G->bp_split_fits >> sh & 1u) && !fits(sh)) G->bp_split_fits &= ~(1u << sh);
+    G->bp_split_forced = only >= 0 && G->bp_split_fits;
+    G->bp_split_shape = G->bp_split_forced ? (int)only : leap_siddon_split_shape(G, 1);
+    if (G->bp_split_shape < 0) G->bp_split_fits = 0;
+}
+
 // Siddon model: static limits of the two fast kernels.
 static void select_siddon_fast_kernels(leap_geometry *G)
 {
@@ -697,20 +749,11 @@ static void select_siddon_fast_kernels(leap_geometry *G)
         }
         if (!G->bp_tiled) return;
         const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
-        // Volumes that leave the chip idle: four groups of threads share the views.  60 views, unsplit / 16 / 8 voxels per thread, us, with
-        // the workgroups of each in brackets: parallel beams 64^3 333 / 88 (64) / 68 (128), 96^3 328 / 91 (216) / 132 (432), 128^3 329 / 177
-        // (512), 144^3 358 / 268 (729), 160^3 363 / 348 (1000), 224^3 818 / 952; four volumes of 64^3 333 / 93 / 134, of 128^3 684 / 689.
-        // Windows wider than 32 columns, unsplit / 8: 64^3 392 / 117 (128), 96^3 398 / 232 (432), 112^3 436 / 320 (686), 128^3 435 / 434 (1024);
-        // four volumes of 96^3 776 / 721.
-        const int limits[2] = {730, G->bp_need_w <= SD_BP_SPLIT_SHAPES[0].pw - 1 ? 128 : 700};
+        // Groups of threads that share the views: the shapes whose windows fit, where one volume would take any of them.
         long only = -2;
         debug_option("bp_split", only);
-        for (int sh = SD_BP_NSPLIT_SHAPES - 1; sh >= 0 && only != -1 && G->bp_split_shape < 0; --sh) {
-            const SfBpShape S = SD_BP_SPLIT_SHAPES[sh];
-            const int workgroups = tiles * ((d->nz + S.zc - 1) / S.zc);
-            if (only >= 0 ? only != sh : workgroups > limits[sh]) continue;
-            if (G->bp_need_w <= S.pw - 1 && window_fits(window_of(S.zc), S)) G->bp_split_shape = sh;
-        }
+        auto fits = [&](int sh) { return G->bp_need_w <= SD_BP_SPLIT_SHAPES[sh].pw - 1 && window_fits(window_of(SD_BP_SPLIT_SHAPES[sh].zc), SD_BP_SPLIT_SHAPES[sh]); };
+        choose_siddon_split(G, only, SD_BP_NSPLIT_SHAPES, fits);
     }
 }
 
@@ -865,21 +908,16 @@ static void select_tilted_siddon_kernels(leap_geometry *G)
     }
     if (!fits) return;
     const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
-    // Groups of threads that share the views: where the volume leaves the chip idle, and at any size under windows that would leave a
-    // compute unit one or two workgroups of 256 threads.  Unsplit / four groups, 32 columns, us: 62 x 63 x 43 x 207 views (96 workgroups)
-    // 1796 / 422, 119 x 126 x 84 x 86 (704) 805 / 550, 149 x 141 x 118 x 60 (1350) 612 / 685; in place of two workgroups 135 x 140 x 148 x
-    // 156 (1539) 5598 / 1986.  Unsplit / two groups, 64 columns: 78 x 67 x 69 x 110 (225) 1125 / 353, 165 x 164 x 79 x 58 (1210) 2440 /
-    // 1216, 234 x 196 x 225 x 206 (5655) 22998 / 13630.
-    const bool crowded = G->bp_shape <= 1;             // three workgroups and more
     long only = -2;
     debug_option("bp_split", only);
-    for (int sh = 0; sh < MD_BP_NSPLIT_SHAPES && only != -1 && G->bp_split_shape < 0; ++sh) {
+    auto split_fits = [&](int sh) {
         const SfBpShape S = MD_BP_SPLIT_SHAPES[sh];
-        if (G->bp_need_w > S.pw - 1 || (only >= 0 ? only != sh : crowded && (sh > 0 || tiles * ((d->nz + S.zc - 1) / S.zc) > 800))) continue;
         int w, h;
+        if (G->bp_need_w > S.pw - 1) return false;
         tilted_window_need(G, views, S.zc, w, h);
-        if (w <= S.pw - 1 && h <= S.ph - 1) G->bp_split_shape = sh;
-    }
+        return w <= S.pw - 1 && h <= S.ph - 1;
+    };
+    choose_siddon_split(G, only, MD_BP_NSPLIT_SHAPES, split_fits);
     hipError_t e = hipMalloc((void **)&G->d_mdbp, sizeof(MdBpView) * views.size());
     if (e == hipSuccess) e = hipMemcpy(G->d_mdbp, views.data(), sizeof(MdBpView) * views.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {

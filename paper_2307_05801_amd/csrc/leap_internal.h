@@ -36,8 +36,8 @@ struct leap_geometry {
     int bp_pair_shape = -1;             // two volumes per workgroup: index into BP_PAIR_SHAPES (-1: one volume)
     bool bp_mirror = false;             // ... the volume's upper half and its lower half's mirror image, whatever the batch
     // Groups of threads that share the views: the shape one volume takes, an index into BP_SPLIT_SHAPES (Siddon: SD_BP_SPLIT_SHAPES,
-    // tilted modules: MD_BP_SPLIT_SHAPES), -1: none.  Footprints: a batch may take another of those that fit, one bit each, or none
-    // (leap_back_split_shape).
+    // tilted modules: MD_BP_SPLIT_SHAPES), -1: none.  A batch may take another of those that fit, one bit each, or none
+    // (leap_back_split_shape, leap_siddon_split_shape).
     int bp_split_shape = -1;
     unsigned bp_split_fits = 0;
     bool bp_split_forced = false;       // (debugging: bp_split_shape, whatever the launch)
@@ -116,6 +116,8 @@ bool leap_plan_scratch(const leap_geometry *G, size_t floats, int batch, int &wi
 int leap_back_pairs(const leap_geometry *G, int items);
 inline int leap_back_split_pairs(const leap_geometry *G, int items) { return G->bp_mirror ? items : (G->g.type != SF_MODULAR ? items / 2 : 0); }
 int leap_back_split_shape(const leap_geometry *G, int items);
+// The same of the tiled Siddon back projection: a shape of SD_BP_SPLIT_SHAPES or, on tilted modules, MD_BP_SPLIT_SHAPES.
+int leap_siddon_split_shape(const leap_geometry *G, int items);
 
 // Footprint forward projection: how many of a launch's `items` volumes go two to a wave (leap_geometry.cpp).
 int leap_forward_paired(const leap_geometry *G, int items);
@@ -142,6 +144,6 @@ struct SfSlab;
 bool leap_launch_footprint_slab(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward.hip
 int leap_launch_footprint_back(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                         // leap_footprint_back.hip
 bool leap_launch_backproject_split(const leap_geometry *geom, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_footprint_back_split.hip
-bool leap_launch_siddon_back_split(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                     // leap_siddon_back_split.hip
+bool leap_launch_siddon_back_split(const leap_geometry *geom, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_siddon_back_split.hip
 bool leap_launch_backproject_pairs(const leap_geometry *geom, const float *d_sino, float *d_vol, int blocks, hipStream_t stream);                     // leap_footprint_back_pairs.hip
 int leap_launch_backproject_batch(const leap_geometry *geom, const float *d_sino, float *d_vol, int batch, hipStream_t stream);

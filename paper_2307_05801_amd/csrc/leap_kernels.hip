@@ -321,9 +321,10 @@ static void launch_md_split(const leap_geometry *G, const float *d_sino, float *
 static int launch_sd_bp_items(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     bool ok = false;
-    if (G->d_mdbp && G->bp_split_shape >= 0) {
+    const int split = leap_siddon_split_shape(G, items);
+    if (G->d_mdbp && split >= 0) {
         static_assert(MD_BP_NSPLIT_SHAPES == 2, "every shape has a case");
-        if (G->bp_split_shape == 0) launch_md_split<0>(G, d_sino, d_vol, stream, items);
+        if (split == 0) launch_md_split<0>(G, d_sino, d_vol, stream, items);
         else launch_md_split<1>(G, d_sino, d_vol, stream, items);
         ok = true;
     } else if (G->md_tilted || G->d_mdbp) {
@@ -336,8 +337,8 @@ static int launch_sd_bp_items(const leap_geometry *G, const float *d_sino, float
         case 5: launch_md_tiled<5>(G, d_sino, d_vol, stream, items); ok = true; break;
         default: break;
         }
-    } else if (G->bp_split_shape >= 0) {
-        ok = leap_launch_siddon_back_split(G, d_sino, d_vol, items, stream);
+    } else if (split >= 0) {
+        ok = leap_launch_siddon_back_split(G, split, d_sino, d_vol, items, stream);
     } else
     switch (G->bp_nc) {
     case 2: ok = launch_sd_shape<2>(G, d_sino, d_vol, stream, items); break;

@@ -26,22 +26,22 @@ static void launch_instance(const leap_geometry *G, const float *d_sino, float *
 }
 
 template <int NCS>
-static bool launch_shape(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
+static bool launch_shape(const leap_geometry *G, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     static_assert(SD_BP_NSPLIT_SHAPES == 2, "every shape has a case");
-    switch (G->bp_split_shape) {
+    switch (shape) {
     case 0: launch_instance<NCS, 0>(G, d_sino, d_vol, items, stream); return true;
     case 1: launch_instance<NCS, 1>(G, d_sino, d_vol, items, stream); return true;
     default: return false;
     }
 }
 
-bool leap_launch_siddon_back_split(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
+bool leap_launch_siddon_back_split(const leap_geometry *G, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     switch (G->bp_nc) {
-    case 2: return launch_shape<2>(G, d_sino, d_vol, items, stream);
-    case 3: return launch_shape<3>(G, d_sino, d_vol, items, stream);
-    case 4: return launch_shape<4>(G, d_sino, d_vol, items, stream);
+    case 2: return launch_shape<2>(G, shape, d_sino, d_vol, items, stream);
+    case 3: return launch_shape<3>(G, shape, d_sino, d_vol, items, stream);
+    case 4: return launch_shape<4>(G, shape, d_sino, d_vol, items, stream);
     default: return false;
     }
 }

@@ -399,6 +399,7 @@ extern "C" int host_forward_paired(const leap_geometry *G, int items) { return l
 
 // Back projection of a launch's items: the shape whose groups of threads share the views (-1: none), pairs of items per workgroup.
 extern "C" int host_back_split_shape(const leap_geometry *G, int items) { return leap_back_split_shape(G, items); }
+extern "C" int host_siddon_split_shape(const leap_geometry *G, int items) { return leap_siddon_split_shape(G, items); }
 extern "C" int host_back_pairs(const leap_geometry *G, int items) { return leap_back_pairs(G, items); }
 
 // Voxels a pair of adjacent rows reads in the scan's highest height class.

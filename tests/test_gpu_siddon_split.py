@@ -56,3 +56,26 @@ def test_tilted_modules(torch_mod, oracle_mod, monkeypatch, shape, pixel, nviews
     monkeypatch.setenv("LEAP_DEBUG", f"bp_split={shape}")
     cfg = scan(CONE, pixel, nviews).replace(sod=180.0, sdd=270.0)
     check(torch_mod, oracle_mod, perturbed_poses(cfg, 3, shift_mm=2.0, tilt_rad=0.05))
+
+
+@pytest.mark.parametrize("kind", ["parallel", "cone", "upright", "tilted"])
+def test_batches_of_every_size(torch_mod, oracle_mod, kind):
+    """A batch that fills the chip takes another kernel than one volume: the same sums in another order, to the last bits."""
+    from paper_2307_05801_amd import Geometry
+    cfg = scan(PARALLEL if kind == "parallel" else CONE, 1.5 if kind == "parallel" else 2.2, 8).replace(nx=80, ny=77, nz=64, nrows=60, ncols=100)
+    if kind != "parallel":
+        cfg = cfg.replace(sod=400.0, sdd=600.0)
+    if kind in ("upright", "tilted"):
+        cfg = perturbed_poses(cfg, 3, shift_mm=2.0, upright=kind == "upright", **({} if kind == "upright" else {"tilt_rad": 0.05}))
+    geo = Geometry(cfg, model="siddon")
+    print(f"[gpu] {kind}: {geo.describe()}", flush=True)
+    assert "+split" in geo.describe(), geo.describe()
+    y = torch_mod.from_numpy(uniform_sinogram(cfg, 9, batch=17)).cuda()
+    alone = torch_mod.stack([geo.backproject(y[b].contiguous()) for b in range(17)])
+    assert rel_l2(alone[16].cpu().numpy(), oracle_mod.siddon.backproject(cfg, y[16].cpu().numpy())) <= TOL
+    for batch in (1, 2, 8, 17):
+        out = geo.backproject(y[:batch].contiguous())
+        assert torch_mod.equal(out, geo.backproject(y[:batch].contiguous())), batch
+        for b in range(batch):                              # sums of eight views' shares in two orders: 8 * 2^-24 at most
+            assert float((out[b] - alone[b]).norm()) <= 5e-7 * float(alone[b].norm()), (batch, b)
+    geo.close()

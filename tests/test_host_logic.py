@@ -1071,3 +1071,21 @@ def test_mirror_image_under_wide_windows(host, pixel_u, shape):
     desc = B.leap_geometry_describe(h, host)
     B.leap_geometry_destroy(h, host)
     assert shape in desc and ("+mirror(zc=16,51x48)" in desc) == ("wide" not in desc), desc
+
+
+# shapes: 0, 1: 16, 8 voxels per thread; tilted modules 8 voxels under 32, 64 columns
+@pytest.mark.parametrize("cfg,shapes", [
+    (small_scan(64, 60, shift_v=0.2), {1: 1, 4: 1, 16: -1}),
+    (small_scan(96, 60, shift_v=0.2), {1: 0, 4: -1, 16: -1}),
+    (small_scan(128, 8, shift_v=0.2), {1: 0, 16: -1}),
+    (small_scan(64, 1, shift_v=0.2), {1: -1, 16: -1}),
+    (small_scan(200, 60, shift_v=0.2), {1: -1, 16: -1}),
+    ("tilted", {1: 0, 4: 0, 16: -1}),
+])
+def test_siddon_views_are_shared_where_the_launch_leaves_the_chip_idle(host, cfg, shapes):
+    if cfg == "tilted":
+        cfg = perturbed_poses(small_scan(64, 60, shift_v=0.2, pixel=1.3, geom=CONE).replace(nrows=54, ncols=68), 5, shift_mm=2.0, tilt_rad=0.05)
+    h = handle(host, cfg, B.LEAP_MODEL_SIDDON)
+    got = {items: host.host_siddon_split_shape(C.c_void_p(h), items) for items in shapes}
+    assert got == shapes, B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
