@@ -184,14 +184,18 @@ const char *leap_last_error(void);
 /* Which kernel family the handle dispatches to: writes up to `cap` bytes of a short NUL-terminated
  * description (for logs and benchmarks): "A=..." and "AT=..." name the forward and the back projection kernel and
  * their instance ("general": plain loop nests over the caller's arrays; "general(flat...)", "general(tiles)" and
- * "general(tiled)" are the fast kernels of flat scans and of footprints on tilted modules, which read those arrays too), "scratch=<bytes>" the device memory the handle owns beyond its tables, "note=..." anything that went
+ * "general(tiled)" are the fast kernels of flat scans and of footprints on tilted modules, which read those arrays too;
+ * "tiled(...)" is the kernel of one volume per workgroup, "+mirror(...)" a volume and its mirror image per workgroup in its
+ * place, "+pairs(...)" the kernel two items of a batch take, "+split(...)" the one with shared views that a single volume
+ * takes before any of them), "scratch=<bytes>" the device memory the handle owns beyond its tables, "note=..." anything that went
  * differently from the plan at creation.  Returns LEAP_OK or LEAP_INVALID_ARG.
  *
  * Debugging aid: the environment variable LEAP_DEBUG, read by leap_geometry_create, overrides the choices shown
  * there.  Comma-separated key=value pairs: general=1 (no fast kernels), cw=1|2|4 (detector columns per wavefront),
  * rg=1|2|4|8 (row groups per wavefront), vb=N / tb=N (views per run / tiles per chunk of the block order), bp_shape=0..6
- * (first back-projection tile shape tried), bp_pair=0..3|-1 (the shape for two volumes per workgroup, none),
- * bp_split=0..2|-1 (the shape for views shared between groups of threads, none), pairs=0|1 (forward: one item of a
+ * (first back-projection tile shape tried; two volumes per workgroup and shared views then only where the next two
+ * name them), bp_pair=0..3|-1 (the shape for two volumes per workgroup, none), bp_split=0..2|-1 (the shape for views
+ * shared between groups of threads, whatever the batch, none), pairs=0|1 (forward: one item of a
  * batch per wavefront, or two wherever there is a kernel for two, however small the batch), slab=N (voxel layers per scratch slab), items=N (batch items per launch),
  * scratch_mib=N (scratch budget), stage_kib=N (size of a pinned staging buffer of the host-memory entry points). */
 int leap_geometry_describe(const leap_geometry *geom, char *buf, int32_t cap);

@@ -149,6 +149,15 @@ static bool debug_option(const char *key, long &value)
     return false;
 }
 
+// bp_pair, bp_split: the shape asked for, -1 none, -2 the selection's own.  A back-projection shape asked for by bp_shape is one of the kernels
+// of one volume without shared views, so it leaves none of the others unless they are named too.
+static long back_option(const char *key)
+{
+    long shape, only = -2;
+    if (!debug_option(key, only) && debug_option("bp_shape", shape)) only = -1;
+    return only;
+}
+
 // The parameter block view a is projected with: its own (modular scans with upright modules) or the shared one.
 static const SfGeom &view_geom(const leap_geometry *G, int a) { return G->geoms.empty() ? G->g : G->geoms[a]; }
 
@@ -359,8 +368,8 @@ static std::vector<int> backproject_pair_shapes(leap_geometry *G)
     std::vector<int> shapes;
     if (G->bp_nv > 3 || d->type == LEAP_MODULAR) return shapes;
     G->bp_mirror = mirrored_about_source_plane(G);
-    long only = -2;
-    if (debug_option("bp_pair", only) && only == -1) return shapes;
+    const long only = back_option("bp_pair");
+    if (only == -1) return shapes;
     const int kfirst = G->bp_mirror ? sf_mirror_first_voxel_above(d->nz) : 0;
     const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
     for (int sh = 0; sh < BP_NPAIR_SHAPES; ++sh) {
@@ -379,6 +388,14 @@ static std::vector<int> backproject_pair_shapes(leap_geometry *G)
     return shapes;
 }
 
+// The general kernel instead, and none of the choices that go with the tiled ones.
+static void no_tiled_back_projection(leap_geometry *G)
+{
+    G->bp_tiled = G->bp_mirror = G->bp_split_forced = false;
+    G->bp_pair_shape = G->bp_split_shape = -1;
+    G->bp_split_fits = 0;
+}
+
 // Footprint model, tiled back projection: pick the template instance and verify its staged window.
 static void select_footprint_tiled(leap_geometry *G)
 {
@@ -386,6 +403,13 @@ static void select_footprint_tiled(leap_geometry *G)
     if (d->type == LEAP_FAN || d->nz < 8 || !std::isfinite(G->max_cols_per_voxel) || G->max_cols_per_voxel > 4.0 ||
         G->max_rows_per_voxel > 3.0 || !((double)d->nrows * d->ncols < 1073741824.0))     // 32-bit byte offsets within a view
         return;
+    // Cylinder: the tiled kernel takes the angle between a voxel's centre and its corners from a short series,
+    // good to 3e-9 rad below 0.08 rad.
+    if (d->type == LEAP_CONE_CURVED) {
+        const double rx = std::fabs(d->center_x) + 0.5 * d->nx * d->voxel_xy, ry = std::fabs(d->center_y) + 0.5 * d->ny * d->voxel_xy;
+        const double nearest = d->sod - std::sqrt(rx * rx + ry * ry);
+        if (!(0.7072 * d->voxel_xy <= 0.08 * nearest)) return;
+    }
     G->bp_nc = std::max(2, (int)std::ceil(G->max_cols_per_voxel) + 1);
     // rows a voxel can touch; the three-row instance runs schemes that need every voxel at most two rows tall, so a
     // bound that close to two rows takes the four-row instance
@@ -463,10 +487,9 @@ static void select_footprint_tiled(leap_geometry *G)
     // Where the 42-column window and its 32 voxels do, 16 + 16 under 51 columns are no gain.  42 columns / mirror image, 60 views, ratio, 256^3,
     // three and eight of them, 256 x 256 x 128: rows of 0.85 voxels (voxels of up to 1.4 rows) 0.98, 1.03 and 1.14, of 1.05 1.02, 1.04 and
     // 1.17, of 1.25 1.03, 1.07 and 1.18, of 1.4 1.08, 1.11 and 1.22; 224^3 0.89 to 1.00, three of them 1.01 to 1.12.
-    if (G->bp_mirror && G->bp_tiled && G->bp_shape == BP_WIDE_SHAPE && !debug_option("bp_pair", forced)) G->bp_pair_shape = -1;
+    if (G->bp_mirror && G->bp_tiled && G->bp_shape == BP_WIDE_SHAPE && back_option("bp_pair") < 0) G->bp_pair_shape = -1;
     // Four groups of threads that share the views: the shapes whose windows fit, where one volume would take any of them.
-    long only = -2;
-    debug_option("bp_split", only);
+    const long only = back_option("bp_split");
     if (G->bp_tiled && G->bp_nv <= 3 && only != -1) {
         const int wide = known.front().w;
         auto exists = [&](int sh) { return bp_split_instance_exists(G->bp_nc, G->bp_nv, sh) && wide <= BP_SPLIT_SHAPES[sh].pw - 1 && (only < 0 || only == sh); };
@@ -485,17 +508,7 @@ static void select_footprint_tiled(leap_geometry *G)
         }
         if (G->bp_split_shape < 0) G->bp_split_fits = 0;
     }
-    // Cylinder: the tiled kernel takes the angle between a voxel's centre and its corners from a short series,
-    // good to 3e-9 rad below 0.08 rad.
-    if (d->type == LEAP_CONE_CURVED) {
-        const double rx = std::fabs(d->center_x) + 0.5 * d->nx * d->voxel_xy, ry = std::fabs(d->center_y) + 0.5 * d->ny * d->voxel_xy;
-        const double nearest = d->sod - std::sqrt(rx * rx + ry * ry);
-        if (!(0.7072 * d->voxel_xy <= 0.08 * nearest)) G->bp_tiled = false;
-    }
-    if (!G->bp_tiled) {
-        G->bp_pair_shape = G->bp_split_shape = -1;
-        G->bp_split_fits = 0;
-    }
+    if (!G->bp_tiled) no_tiled_back_projection(G);
 }
 
 // Row groups per wave of the column-wise forward kernels.  A wave pays a fixed share per candidate voxel column (its
@@ -688,10 +701,11 @@ int leap_siddon_split_shape(const leap_geometry *G, int items)
     return best;
 }
 
-// The shapes that fit (fits(shape): their windows do) and the one a single volume takes; `only`: the debugging option, -1 none, or that one.
+// The shapes that fit (fits(shape): their windows do) and the one a single volume takes.
 template <class FitsFn>
-static void choose_siddon_split(leap_geometry *G, long only, int nshapes, FitsFn fits)
+static void choose_siddon_split(leap_geometry *G, int nshapes, FitsFn fits)
 {
+    const long only = back_option("bp_split");
     if (only == -1) return;
     for (int sh = 0; sh < nshapes; ++sh)
         if (only < 0 || only == sh) G->bp_split_fits |= 1u << sh;
@@ -750,10 +764,8 @@ static void select_siddon_fast_kernels(leap_geometry *G)
         if (!G->bp_tiled) return;
         const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
         // Groups of threads that share the views: the shapes whose windows fit, where one volume would take any of them.
-        long only = -2;
-        debug_option("bp_split", only);
         auto fits = [&](int sh) { return G->bp_need_w <= SD_BP_SPLIT_SHAPES[sh].pw - 1 && window_fits(window_of(SD_BP_SPLIT_SHAPES[sh].zc), SD_BP_SPLIT_SHAPES[sh]); };
-        choose_siddon_split(G, only, SD_BP_NSPLIT_SHAPES, fits);
+        choose_siddon_split(G, SD_BP_NSPLIT_SHAPES, fits);
     }
 }
 
@@ -908,8 +920,6 @@ static void select_tilted_siddon_kernels(leap_geometry *G)
     }
     if (!fits) return;
     const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
-    long only = -2;
-    debug_option("bp_split", only);
     auto split_fits = [&](int sh) {
         const SfBpShape S = MD_BP_SPLIT_SHAPES[sh];
         int w, h;
@@ -917,13 +927,14 @@ static void select_tilted_siddon_kernels(leap_geometry *G)
         tilted_window_need(G, views, S.zc, w, h);
         return w <= S.pw - 1 && h <= S.ph - 1;
     };
-    choose_siddon_split(G, only, MD_BP_NSPLIT_SHAPES, split_fits);
+    choose_siddon_split(G, MD_BP_NSPLIT_SHAPES, split_fits);
     hipError_t e = hipMalloc((void **)&G->d_mdbp, sizeof(MdBpView) * views.size());
     if (e == hipSuccess) e = hipMemcpy(G->d_mdbp, views.data(), sizeof(MdBpView) * views.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         if (G->d_mdbp) (void)hipFree(G->d_mdbp);
         G->d_mdbp = nullptr;
         (void)hipGetLastError();
+        no_tiled_back_projection(G);
         G->note = "table allocation failed: back projection runs on the general kernel";
         return;
     }
@@ -1151,7 +1162,7 @@ static void upload_curved_tables(leap_geometry *G)
     if (et != hipSuccess) {
         if (G->d_colcs) (void)hipFree(G->d_colcs);
         G->d_colcs = nullptr;
-        G->bp_tiled = false;
+        no_tiled_back_projection(G);
         G->note = "no room for the cylinder's tile tables: back projection runs on the general kernel";
         (void)hipGetLastError();
     }

@@ -29,7 +29,13 @@
 // ---- stubs of the HIP runtime calls made by leap_geometry.cpp: "device" memory is host memory ---------------
 extern "C" {
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
-hipError_t hipMalloc(void **p, size_t n) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+static long g_device_fail_at = -1;
+hipError_t hipMalloc(void **p, size_t n)
+{
+    *p = g_device_fail_at >= 0 && g_device_fail_at-- == 0 ? nullptr : std::malloc(n);
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+void host_fail_device_allocation(long n) { g_device_fail_at = n; }   // the n-th device allocation from now on fails (n < 0: none does)
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }

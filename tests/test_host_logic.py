@@ -1089,3 +1089,44 @@ def test_siddon_views_are_shared_where_the_launch_leaves_the_chip_idle(host, cfg
     got = {items: host.host_siddon_split_shape(C.c_void_p(h), items) for items in shapes}
     assert got == shapes, B.leap_geometry_describe(h, host)
     B.leap_geometry_destroy(h, host)
+
+
+@pytest.mark.parametrize("model,kind", [(B.LEAP_MODEL_SF, "curved"), (B.LEAP_MODEL_SIDDON, "tilted")])
+def test_back_projections_left_to_the_general_kernel_are_described_as_such(host, model, kind):
+    """The tables of the tiled kernels find no room on the device, or the source is too close for the cylinder's: nothing is left of the
+    choices that go with those kernels."""
+    cfg = small_scan(48, 8, geom=CONE_CURVED if kind == "curved" else CONE).replace(nrows=60, ncols=90)
+    if kind == "tilted":
+        cfg = perturbed_poses(small_scan(64, 8, shift_v=0.2, pixel=1.3, geom=CONE).replace(nrows=54, ncols=68), 5, shift_mm=2.0, tilt_rad=0.05)
+    described = []
+    for n in range(12):
+        host.host_fail_device_allocation(C.c_long(n))
+        try:
+            h = handle(host, cfg, model)
+        except B.LeapError:
+            continue
+        finally:
+            host.host_fail_device_allocation(C.c_long(-1))
+        described.append(B.leap_geometry_describe(h, host))
+        B.leap_geometry_destroy(h, host)
+    assert any("AT=tiled" in d and "+split" in d for d in described), described
+    assert any("AT=general" in d for d in described), described
+    assert not any("AT=general" in d and "+" in d.split("AT=")[1].split(" ")[0] for d in described), described
+    close = CTConfig("curved_close", CONE_CURVED, nviews=8, arc_deg=360.0, nrows=40, ncols=64, pixel_v=2.5, pixel_u=2.5,
+                     nx=16, ny=16, nz=16, voxel_xy=2.0, voxel_z=2.0, sod=28.0, sdd=60.0)
+    h = handle(host, close)
+    assert "AT=general " in B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
+
+
+@pytest.mark.parametrize("model", [B.LEAP_MODEL_SF, B.LEAP_MODEL_SIDDON])
+@pytest.mark.parametrize("debug,tokens,absent", [
+    ("bp_shape=1", ("tiled(",), ("+",)), ("bp_shape=3,bp_split=1", ("zc=16", "+split("), ("+mirror(", "+pairs(")),
+    ("bp_split=-1,bp_pair=-1", ("tiled(",), ("+",)), ("bp_split=1", ("+split(",), ())])
+def test_a_tile_shape_asked_for_is_the_one_that_runs(host, monkeypatch, model, debug, tokens, absent):
+    """LEAP_DEBUG=bp_shape=N: no kernel of two volumes or of shared views in its place, unless one is named."""
+    monkeypatch.setenv("LEAP_DEBUG", debug)
+    h = handle(host, small_scan(64, 60, shift_v=0.0 if model == B.LEAP_MODEL_SF else 0.2), model)
+    desc = B.leap_geometry_describe(h, host).split("AT=")[1].split(" scratch")[0]
+    B.leap_geometry_destroy(h, host)
+    assert all(t in desc for t in tokens) and not any(t in desc for t in absent), desc
