@@ -194,7 +194,8 @@ const char *leap_last_error(void);
  * there.  Comma-separated key=value pairs: general=1 (no fast kernels), cw=1|2|4 (detector columns per wavefront),
  * rg=1|2|4|8 (row groups per wavefront), vb=N / tb=N (views per run / tiles per chunk of the block order), bp_shape=0..6
  * (first back-projection tile shape tried; two volumes per workgroup and shared views then only where the next two
- * name them), bp_pair=0..3|-1 (the shape for two volumes per workgroup, none), bp_split=0..2|-1 (the shape for views
+ * name them), bp_pair=0..3|-1 (the shape for two volumes per
+ * workgroup, whatever the batch, none), bp_split=0..2|-1 (the shape for views
  * shared between groups of threads, whatever the batch, none), pairs=0|1 (forward: one item of a
  * batch per wavefront, or two wherever there is a kernel for two, however small the batch), slab=N (voxel layers per scratch slab), items=N (batch items per launch),
  * scratch_mib=N (scratch budget), stage_kib=N (size of a pinned staging buffer of the host-memory entry points). */

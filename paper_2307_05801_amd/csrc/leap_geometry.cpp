@@ -317,6 +317,7 @@ int leap_back_pairs(const leap_geometry *G, int items)
 {
     if (G->bp_pair_shape < 0) return 0;
     if (G->bp_mirror) return items;
+    if (G->bp_pair_forced) return items / 2;
     const SfBpShape S = BP_PAIR_SHAPES[G->bp_pair_shape];
     const int chunks = tile_chunks(G, S.zc), views = G->g.nviews;
     if (chunks * (items / 2) < (S.pw > 32 ? 1200 : 400) || views < BP_FEW_VIEWS) return 0;
@@ -391,7 +392,7 @@ static std::vector<int> backproject_pair_shapes(leap_geometry *G)
 // The general kernel instead, and none of the choices that go with the tiled ones.
 static void no_tiled_back_projection(leap_geometry *G)
 {
-    G->bp_tiled = G->bp_mirror = G->bp_split_forced = false;
+    G->bp_tiled = G->bp_mirror = G->bp_pair_forced = G->bp_split_forced = false;
     G->bp_pair_shape = G->bp_split_shape = -1;
     G->bp_split_fits = 0;
 }
@@ -484,10 +485,11 @@ static void select_footprint_tiled(leap_geometry *G)
             ++p;
         }
     }
+    G->bp_pair_forced = back_option("bp_pair") >= 0;
     // Where the 42-column window and its 32 voxels do, 16 + 16 under 51 columns are no gain.  42 columns / mirror image, 60 views, ratio, 256^3,
     // three and eight of them, 256 x 256 x 128: rows of 0.85 voxels (voxels of up to 1.4 rows) 0.98, 1.03 and 1.14, of 1.05 1.02, 1.04 and
     // 1.17, of 1.25 1.03, 1.07 and 1.18, of 1.4 1.08, 1.11 and 1.22; 224^3 0.89 to 1.00, three of them 1.01 to 1.12.
-    if (G->bp_mirror && G->bp_tiled && G->bp_shape == BP_WIDE_SHAPE && back_option("bp_pair") < 0) G->bp_pair_shape = -1;
+    if (G->bp_mirror && G->bp_tiled && G->bp_shape == BP_WIDE_SHAPE && !G->bp_pair_forced) G->bp_pair_shape = -1;
     // Four groups of threads that share the views: the shapes whose windows fit, where one volume would take any of them.
     const long only = back_option("bp_split");
     if (G->bp_tiled && G->bp_nv <= 3 && only != -1) {

@@ -34,6 +34,7 @@ struct leap_geometry {
     bool bp_tiled = false;
     int bp_need_w = 0, bp_need_h = 0;   // largest staged window any (view, tile, chunk) asks for
     int bp_pair_shape = -1;             // two volumes per workgroup: index into BP_PAIR_SHAPES (-1: one volume)
+    bool bp_pair_forced = false;        // (debugging: two items per workgroup in every batch)
     bool bp_mirror = false;             // ... the volume's upper half and its lower half's mirror image, whatever the batch
     // Groups of threads that share the views: the shape one volume takes, an index into BP_SPLIT_SHAPES (Siddon: SD_BP_SPLIT_SHAPES,
     // tilted modules: MD_BP_SPLIT_SHAPES), -1: none.  A batch may take another of those that fit, one bit each, or none

@@ -145,3 +145,31 @@ def test_batches_of_every_size(torch_mod, oracle_mod, geometry, shift_v):
         for b in range(batch):                              # sums of eight views' shares in two orders: 8 * 2^-24 at most
             assert float((out[b] - alone[b]).norm()) <= 5e-7 * float(alone[b].norm()), (batch, b)
     geo.close()
+
+
+# pair shape, the one-volume shape of the same height, pixel (voxels at the axis)
+@pytest.mark.parametrize("pair,single,pixel", [(0, 1, 2.4), (1, 2, 1.9), (2, 3, 2.4), (3, 4, 1.3)])
+@pytest.mark.parametrize("geometry", [PARALLEL, CONE, CONE_CURVED])
+@pytest.mark.parametrize("voxel_z", [0.7, 1.0, 1.35])
+def test_two_items_of_every_shape(torch_mod, oracle_mod, monkeypatch, geometry, pair, single, pixel, voxel_z):
+    """Off centre, voxels of up to one row and of up to two: two items per workgroup give the bits of one per workgroup, and the same on
+    every call (256 threads stage a window of 51 columns with one to spare)."""
+    from paper_2307_05801_amd import Geometry
+    cfg = scan(geometry, 41, 51, pixel / 1.5 if geometry == PARALLEL else pixel, shift_v=0.25).replace(voxel_z=voxel_z)
+    monkeypatch.setenv("LEAP_DEBUG", f"bp_pair={pair},bp_shape={single}")
+    geo = Geometry(cfg)
+    print(f"[gpu] {geometry} {pair} {voxel_z}: {geo.describe()}", flush=True)
+    if geometry == PARALLEL and pair == 3:
+        assert "tiled(" in geo.describe(), geo.describe()          # (three columns and more: diverging beams)
+    else:
+        assert "+pairs" in geo.describe() and "+split" not in geo.describe(), geo.describe()
+    y = uniform_sinogram(cfg, 8, batch=5)
+    yt = torch_mod.from_numpy(y).cuda()
+    out = geo.backproject(yt)
+    for b in (0, 3):
+        assert rel_l2(out[b].cpu().numpy(), oracle_mod.backproject(cfg, y[b])) <= TOL
+    for b in range(5):
+        assert torch_mod.equal(out[b], geo.backproject(yt[b].contiguous())), b
+    for _ in range(6):
+        assert torch_mod.equal(out, geo.backproject(yt))
+    geo.close()
