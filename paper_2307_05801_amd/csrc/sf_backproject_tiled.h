@@ -204,8 +204,8 @@ struct alignas(4 * NS) SfBpSample {
     float v[NS];
 };
 
-// Staging, first half: fetch this thread's share of the window of one view into registers.  ya points at the view; yb - ya
-// (bytes) leads from a sample to its partner's row 0 in the same column, rows up (batch) or down (mirror).
+// Staging, first half: fetch this thread's share of the window of one view into registers.  ya points at the view, y2 at the
+// same view of the second volume, which it takes from the same places or, mirrored, from as far from the detector's other end.
 template <int NC, int NV, int PW, int PH, int NSTAGE, int GT, int NS>
 __device__ __forceinline__ void bp_load_view(const SfGeom &g, const SfView v, const float *__restrict__ ya, float xc, float yc,
                                              float hx, float z0, float z1, float wh, int sc, int sr, SfWindow &w,

@@ -173,9 +173,6 @@ SF_HD void sf_place_row(double rd, double mu, double zkp, float &fr1, unsigned &
 #endif
 }
 
-// Voxels a row can overlap when a pair of rows overlaps P: rows of up to (P - 1) / 2 voxels.
-constexpr int sf_single_of_pair(int P) { return P / 2 + 1; }
-
 // Axial sums of a pair of adjacent rows.  x[0..P-1]: voxels from the one holding the lower row's lower edge; fr1 as
 // above; mu = voxels per row.  The lower row A covers [fr, fr + mu) of that run, the upper row B [fr + mu, fr + 2 mu).  With
 // a_t = clamp(fr + mu - t) and b_t = clamp(fr + 2 mu - t), the parts of voxel t below either row's upper edge (additions with the clamp
@@ -265,34 +262,28 @@ struct SfPairClass {
 };
 SF_HD int sf_pair_class(float mu) { return mu <= 1.0f ? 1 : (mu <= 1.5f ? 2 : (mu <= 2.0f ? 3 : 4)); }
 
-template <int CLS>
-SF_HD void sf_pair_sums_of_class(const float *x, float fr1, const SfPairOffsets &k, float &sa, float &sb)
-{
-    using C = SfPairClass<CLS>;
-    sf_pair_apply<C::LO2, C::HI2>(x, sf_pair_weights<C::LO2, C::HI2>(fr1, k), sa, sb);
-}
-
-// The same for any height that fits P voxels per pair, the class picked per call (host).
-template <int P>
-struct SfPairConsts {
-    SfPairOffsets k;
+// The four numbers that a candidate's visit needs, as its lane leaves them for the wave (cls: its own class, HC: the scan's highest, which also
+// takes candidates that rounding puts a class higher) and as the wave reads them in the body of class CLS.  (By value: by reference most
+// instances take one register more.)
+struct alignas(16) SfOffsetsRecord {
+    float x, y, z, w;
 };
 
-template <int P>
-SF_HD SfPairConsts<P> sf_pair_consts(float mu) { return {sf_pair_offsets(mu)}; }
-
-template <int P>
-SF_HD void sf_pair_sums(const float (&x)[P], float fr1, const SfPairConsts<P> &c, float &sa, float &sb)
+template <int HC>
+SF_HD SfOffsetsRecord sf_pack_offsets(int cls, SfPairOffsets k)
 {
-    float run[FP_MAX_P] = {};
-    for (int t = 0; t < P; ++t) run[t] = x[t];
-    switch (P == 2 ? 0 : sf_pair_class(c.k.mu)) {
-    case 0: sf_pair_sums_of_class<0>(run, fr1, c.k, sa, sb); break;
-    case 1: sf_pair_sums_of_class<1>(run, fr1, c.k, sa, sb); break;
-    case 2: sf_pair_sums_of_class<2>(run, fr1, c.k, sa, sb); break;
-    case 3: sf_pair_sums_of_class<3>(run, fr1, c.k, sa, sb); break;
-    default: sf_pair_sums_of_class<4>(run, fr1, c.k, sa, sb); break;
-    }
+    const bool below1 = HC <= 1 || cls <= 1, below2 = HC <= 2 || cls <= 2;
+    return {below1 || (HC > 3 && cls > 3) ? k.mu : k.ka[0], below1 ? k.ka[0] : k.ka[1],
+            below1 ? k.kb[0] : (below2 ? k.kb[1] : k.kb[2]), below1 ? k.kb[1] : (below2 ? k.kb[2] : k.kb[3])};
+}
+
+template <int CLS>
+SF_HD void sf_unpack_offsets(const SfOffsetsRecord &r, SfPairOffsets &k)
+{
+    if constexpr (CLS <= 1) { k.mu = r.x; k.ka[0] = r.y; k.kb[0] = r.z; k.kb[1] = r.w; }
+    if constexpr (CLS == 2) { k.ka[0] = r.x; k.ka[1] = r.y; k.kb[1] = r.z; k.kb[2] = r.w; }
+    if constexpr (CLS == 3) { k.ka[0] = r.x; k.ka[1] = r.y; k.kb[2] = r.z; k.kb[3] = r.w; }
+    if constexpr (CLS == 4) k = sf_pair_offsets(r.x);
 }
 
 // Transaxial record of one candidate voxel column (i, j) for the bundle of CW detector columns starting at c0:
@@ -483,11 +474,10 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
             float4 f4 = make_float4(fa[0], 0.0f, 0.0f, 0.0f);
             if constexpr (CW > 1) f4.y = fa[1];
             if constexpr (CW > 2) { f4.z = fa[2]; f4.w = fa[3]; }
-            const bool below1 = HC <= 1 || cls <= 1, below2 = HC <= 2 || cls <= 2;
             // (the wave has consumed every value it read from the previous block's records)
             rec[lane][0] = f4;
-            rec[lane][1] = make_float4(below1 || (HC > 3 && cls > 3) ? k.mu : k.ka[0], below1 ? k.ka[0] : k.ka[1],
-                                       below1 ? k.kb[0] : (below2 ? k.kb[1] : k.kb[2]), below1 ? k.kb[1] : (below2 ? k.kb[2] : k.kb[3]));
+            const SfOffsetsRecord offsets = sf_pack_offsets<HC>(cls, k);
+            rec[lane][1] = make_float4(offsets.x, offsets.y, offsets.z, offsets.w);
             // the records are read by the other lanes of this wave only: order the LDS accesses, no barrier
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -509,10 +499,7 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
                 const float4 r0 = rec[e][0], r1 = rec[e][1];
                 const float fcol[4] = {r0.x, r0.y, r0.z, r0.w};
                 SfPairOffsets k;
-                if constexpr (CLS <= 1) { k.mu = r1.x; k.ka[0] = r1.y; k.kb[0] = r1.z; k.kb[1] = r1.w; }
-                if constexpr (CLS == 2) { k.ka[0] = r1.x; k.ka[1] = r1.y; k.kb[1] = r1.z; k.kb[2] = r1.w; }
-                if constexpr (CLS == 3) { k.ka[0] = r1.x; k.ka[1] = r1.y; k.kb[2] = r1.z; k.kb[3] = r1.w; }
-                if constexpr (CLS == 4) k = sf_pair_offsets(r1.x);
+                sf_unpack_offsets<CLS>({r1.x, r1.y, r1.z, r1.w}, k);
                 const unsigned s_base = (unsigned)__builtin_amdgcn_readlane((int)colbase, e);
                 const double s_mu = __hiloint2double(__builtin_amdgcn_readlane(mu_hi, e), __builtin_amdgcn_readlane(mu_lo, e));
                 float fr1[RG];

@@ -184,16 +184,13 @@ int leap_launch_backproject_batch(const leap_geometry *G, const float *sino, flo
 }
 
 // ---- tiled back projection: every thread's LDS reads against the staged window --------------------------------
-// report[0..7] = {tiled?, nc, nv, zc, max column index read, max row index read, widest footprint in pixels, violations}
-extern "C" int host_check_backproject_windows(const leap_geometry *G, int64_t *report)
+// For one shape, chunks from voxel kfirst on: report[0..3] = {max column index read, max row index read, widest footprint in pixels,
+// violations}.
+static void host_check_windows(const leap_geometry *G, const SfBpShape S, int kfirst, int64_t *report)
 {
     const SfGeom &g = G->g;
-    std::fill(report, report + 8, 0);
-    report[0] = G->bp_tiled;
-    if (!G->bp_tiled) return 0;
     const int NC = G->bp_nc, NV = G->bp_nv;
-    const SfBpShape S = BP_SHAPES[G->bp_shape];
-    const int tiles_x = (g.nx + BP_T - 1) / BP_T, tiles_y = (g.ny + BP_T - 1) / BP_T, chunks = (g.nz + S.zc - 1) / S.zc;
+    const int tiles_x = (g.nx + BP_T - 1) / BP_T, tiles_y = (g.ny + BP_T - 1) / BP_T, chunks = (g.nz - kfirst + S.zc - 1) / S.zc;
     int maxc = -1, maxr = -1, maxspan = 0;
     long bad = 0;
 #pragma omp parallel for collapse(2) reduction(max : maxc, maxr, maxspan) reduction(+ : bad)
@@ -202,7 +199,7 @@ extern "C" int host_check_backproject_windows(const leap_geometry *G, int64_t *r
             for (int tx = 0; tx < tiles_x; ++tx)
                 for (int ch = 0; ch < chunks; ++ch) {
                     const SfGeom &g = G->geoms.empty() ? G->g : G->geoms[a];      // modular: the view's own parameter block
-                    const int i0 = tx * BP_T, j0 = ty * BP_T, k0 = ch * S.zc;
+                    const int i0 = tx * BP_T, j0 = ty * BP_T, k0 = kfirst + ch * S.zc;
                     const double zlo = fma((double)k0, g.Tzd, g.zlo0d);
                     const float z0 = (float)zlo, z1 = z0 + (float)S.zc * g.Tz;
                     const float hx = 0.5f * (float)(BP_T - 1) * g.T;
@@ -237,23 +234,44 @@ extern "C" int host_check_backproject_windows(const leap_geometry *G, int64_t *r
                             if (ax.av > (float)(NV - 1) * 1.000001f) ++bad;                       // voxel taller than NV-1 rows
                         }
                 }
-    report[1] = NC; report[2] = NV; report[3] = S.zc; report[4] = maxc; report[5] = maxr; report[6] = maxspan; report[7] = bad;
-    return bad != 0;
+    report[0] = maxc; report[1] = maxr; report[2] = maxspan; report[3] = bad;
+}
+
+// report[0..7] = {tiled?, nc, nv, zc, max column index read, max row index read, widest footprint in pixels, violations}: the kernel of one
+// volume per workgroup; violations also under the windows of two volumes and of shared views, every shape a launch of the handle may take.
+extern "C" int host_check_backproject_windows(const leap_geometry *G, int64_t *report)
+{
+    std::fill(report, report + 8, 0);
+    report[0] = G->bp_tiled;
+    if (!G->bp_tiled) return 0;
+    const int kfirst = G->bp_mirror ? sf_mirror_first_voxel_above(G->g.nz) : 0;
+    int64_t r[4];
+    host_check_windows(G, BP_SHAPES[G->bp_shape], 0, report + 4);
+    report[1] = G->bp_nc; report[2] = G->bp_nv; report[3] = BP_SHAPES[G->bp_shape].zc;
+    if (G->bp_pair_shape >= 0) {
+        host_check_windows(G, BP_PAIR_SHAPES[G->bp_pair_shape], kfirst, r);
+        report[7] += r[3];
+    }
+    for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh)
+        if (G->bp_split_fits >> sh & 1u) {
+            host_check_windows(G, BP_SPLIT_SHAPES[sh], kfirst, r);
+            report[7] += r[3];
+        }
+    return report[7] != 0;
 }
 
 // ---- tiled back projection: who stages what ----------------------------------------------------------------------
-// Number of cells of any shape's window that are not written by exactly one (thread, step) of a workgroup: a cell without a
+// Number of cells of a window that are not written by exactly one (thread, step) of a group of 256 threads: a cell without a
 // writer holds another view's sample, one with two writers in different steps is written without an order between them.
-template <int SH>
+template <int PW, int PH>
 static long host_staging_roles()
 {
-    constexpr SfBpShape S = BP_SHAPES[SH];
-    constexpr int step = 256 / S.pw, nstage = (S.ph + step - 1) / step;
-    std::vector<int> writers((size_t)S.ph * S.pw, 0);
+    constexpr int step = 256 / PW, nstage = (PH + step - 1) / step;
+    std::vector<int> writers((size_t)PH * PW, 0);
     for (int tid = 0; tid < 256; ++tid)
         for (int s = 0; s < nstage; ++s) {
-            const int row = sf_stage_row<S.pw, S.ph>(tid) + step * s;
-            if (row < S.ph) ++writers[(size_t)row * S.pw + sf_stage_column<S.pw>(tid)];
+            const int row = sf_stage_row<PW, PH>(tid) + step * s;
+            if (row < PH) ++writers[(size_t)row * PW + sf_stage_column<PW>(tid)];
         }
     long bad = 0;
     for (int w : writers) bad += w != 1;
@@ -262,9 +280,12 @@ static long host_staging_roles()
 
 extern "C" long host_check_staging_roles()
 {
-    static_assert(BP_NSHAPES == 7, "every shape is checked");
-    return host_staging_roles<0>() + host_staging_roles<1>() + host_staging_roles<2>() + host_staging_roles<3>() + host_staging_roles<4>() +
-           host_staging_roles<5>() + host_staging_roles<6>();
+    static_assert(BP_NSHAPES == 7 && BP_NPAIR_SHAPES == 4 && BP_NSPLIT_SHAPES == 3, "every shape is checked");
+#define ROLES(S) host_staging_roles<S.pw, S.ph>()
+    return ROLES(BP_SHAPES[0]) + ROLES(BP_SHAPES[1]) + ROLES(BP_SHAPES[2]) + ROLES(BP_SHAPES[3]) + ROLES(BP_SHAPES[4]) + ROLES(BP_SHAPES[5]) +
+           ROLES(BP_SHAPES[6]) + ROLES(BP_PAIR_SHAPES[0]) + ROLES(BP_PAIR_SHAPES[1]) + ROLES(BP_PAIR_SHAPES[2]) + ROLES(BP_PAIR_SHAPES[3]) +
+           ROLES(BP_SPLIT_SHAPES[0]) + ROLES(BP_SPLIT_SHAPES[1]) + ROLES(BP_SPLIT_SHAPES[2]);
+#undef ROLES
 }
 
 // ---- cylinder: the tile-relative column function of the tiled kernel against the general one ------------------------
@@ -304,21 +325,24 @@ extern "C" int host_curved_column_deviation(const leap_geometry *G, double *out)
 // One (view, bundle of CW detector columns) at a time, the way a wavefront of sf_project_columns works through it: the
 // host's marching axis for the bundle, candidate slots per slab, sf_candidate_record for every candidate, then for every
 // pair of adjacent rows sf_place_row, a window of P voxels read from the z-fastest copy (zero outside the padded
-// column, as the kernel's buffer loads return) and sf_pair_sums.  The whole volume stands in for one slab.
-template <int CW, int P>
+// column, as the kernel's buffer loads return) and the axial sums in the body of the candidate's height class, from the four numbers its lane
+// leaves in LDS.  The whole volume stands in for one slab.
+template <int CW, int HC, int CLS>
 static void host_pairs_of_candidate(const SfGeom &g, const float *col, int nzp, double mu, double zkp, const float (&fa)[CW],
                                     std::vector<float> &acc)
 {
-    const SfPairConsts<P> k = sf_pair_consts<P>((float)mu);      // per candidate, as the kernel's lanes work them out
+    using C = SfPairClass<CLS>;
+    SfPairOffsets k;
+    sf_unpack_offsets<CLS>(sf_pack_offsets<HC>(HC > 1 ? sf_pair_class((float)mu) : HC, sf_pair_offsets((float)mu)), k);
     for (int r = 0; r < g.nrows; r += 2) {
         float fr1;
         unsigned hi;
         sf_place_row((double)r - g.row_offd, mu, zkp, fr1, hi);
         const int kf = (int)(hi - FP_KAP_HI);
-        float x[P];
-        for (int t = 0; t < P; ++t) x[t] = (kf + t >= 0 && kf + t < nzp) ? col[kf + t] : 0.0f;
+        float x[C::P];
+        for (int t = 0; t < C::P; ++t) x[t] = (kf + t >= 0 && kf + t < nzp) ? col[kf + t] : 0.0f;
         float sa, sb;
-        sf_pair_sums<P>(x, fr1, k, sa, sb);
+        sf_pair_apply<C::LO2, C::HI2>(x, sf_pair_weights<C::LO2, C::HI2>(fr1, k), sa, sb);
         for (int cw = 0; cw < CW; ++cw) {
             acc[(size_t)r * CW + cw] = fmaf(fa[cw], sa, acc[(size_t)r * CW + cw]);
             if (r + 1 < g.nrows) acc[(size_t)(r + 1) * CW + cw] = fmaf(fa[cw], sb, acc[(size_t)(r + 1) * CW + cw]);
@@ -326,10 +350,23 @@ static void host_pairs_of_candidate(const SfGeom &g, const float *col, int nzp, 
     }
 }
 
+// The class whose body a candidate of a scan of highest class HC is walked in.
+template <int CW, int HC>
+static void host_pairs_of_scan(const SfGeom &g, const float *col, int nzp, double mu, double zkp, const float (&fa)[CW], std::vector<float> &acc)
+{
+    switch (HC > 1 ? std::min(sf_pair_class((float)mu), HC) : HC) {
+    case 0: host_pairs_of_candidate<CW, HC, 0>(g, col, nzp, mu, zkp, fa, acc); break;
+    case 1: host_pairs_of_candidate<CW, HC, 1>(g, col, nzp, mu, zkp, fa, acc); break;
+    case 2: host_pairs_of_candidate<CW, HC, 2>(g, col, nzp, mu, zkp, fa, acc); break;
+    case 3: host_pairs_of_candidate<CW, HC, 3>(g, col, nzp, mu, zkp, fa, acc); break;
+    default: host_pairs_of_candidate<CW, HC, 4>(g, col, nzp, mu, zkp, fa, acc); break;
+    }
+}
+
 template <int CW>
 static long host_project_bundles(const leap_geometry *G, const std::vector<float> (&volz)[2], int nzp, float *sino)
 {
-    const int NQ = G->fp_nq, NKP = G->fp_nkp;
+    const int NQ = G->fp_nq;
     const int nbundles = (G->g.ncols + CW - 1) / CW;
     long uncovered = 0;
 #pragma omp parallel for collapse(2) reduction(+ : uncovered)
@@ -356,14 +393,12 @@ static long host_project_bundles(const leap_geometry *G, const std::vector<float
                     double mu;
                     if (!sf_candidate_record<CW, -1>(g, v, i, j, c0, true, fa, mu)) continue;
                     const float *col = &volz[xmajor][(size_t)sf_slab_column(slab, g.nx, i, j) * nzp];
-                    const int P = (NKP > 4 && (float)mu <= 1.4999f) ? 4 : NKP;
-                    switch (P) {
-                    case 2: host_pairs_of_candidate<CW, 2>(g, col, nzp, mu, zkp, fa, acc); break;
-                    case 3: host_pairs_of_candidate<CW, 3>(g, col, nzp, mu, zkp, fa, acc); break;
-                    case 4: host_pairs_of_candidate<CW, 4>(g, col, nzp, mu, zkp, fa, acc); break;
-                    case 5: host_pairs_of_candidate<CW, 5>(g, col, nzp, mu, zkp, fa, acc); break;
-                    case 6: host_pairs_of_candidate<CW, 6>(g, col, nzp, mu, zkp, fa, acc); break;
-                    default: host_pairs_of_candidate<CW, 7>(g, col, nzp, mu, zkp, fa, acc); break;
+                    switch (fp_height_class(G->fp_nkp)) {
+                    case 0: host_pairs_of_scan<CW, 0>(g, col, nzp, mu, zkp, fa, acc); break;
+                    case 1: host_pairs_of_scan<CW, 1>(g, col, nzp, mu, zkp, fa, acc); break;
+                    case 2: host_pairs_of_scan<CW, 2>(g, col, nzp, mu, zkp, fa, acc); break;
+                    case 3: host_pairs_of_scan<CW, 3>(g, col, nzp, mu, zkp, fa, acc); break;
+                    default: host_pairs_of_scan<CW, 4>(g, col, nzp, mu, zkp, fa, acc); break;
                     }
                 }
             }
@@ -611,9 +646,16 @@ static void host_sd_bp_shape(const leap_geometry *G, const float *sino, float *v
     report[0] = wide; report[1] = outside; report[2] = badslot; report[3] = shared;
 }
 
+// The shape one volume takes.
 extern "C" long host_sd_backproject_tiled(const leap_geometry *G, const float *sino, float *vol, int64_t *report)
 {
     if (G->g.model != SF_MODEL_SIDDON || G->d_mdbp || !G->bp_tiled) return -1;
+    static_assert(SD_BP_NSPLIT_SHAPES == 2, "every shape has a case");
+    if (G->bp_split_shape >= 0) {             // (each group of threads takes every fourth view: the same windows and slots)
+        if (G->bp_split_shape == 0) host_sd_bp_shape<SD_BP_SPLIT_SHAPES[0].zc, SD_BP_SPLIT_SHAPES[0].pw, SD_BP_SPLIT_SHAPES[0].ph>(G, sino, vol, report);
+        else host_sd_bp_shape<SD_BP_SPLIT_SHAPES[1].zc, SD_BP_SPLIT_SHAPES[1].pw, SD_BP_SPLIT_SHAPES[1].ph>(G, sino, vol, report);
+        return report[0] + report[1] + report[2] + report[3];
+    }
     switch (G->bp_shape) {
     case 1: host_sd_bp_shape<BP_SHAPES[1].zc, BP_SHAPES[1].pw, BP_SHAPES[1].ph>(G, sino, vol, report); break;
     case 2: host_sd_bp_shape<BP_SHAPES[2].zc, BP_SHAPES[2].pw, BP_SHAPES[2].ph>(G, sino, vol, report); break;
@@ -752,6 +794,12 @@ static void host_md_bp_shape(const leap_geometry *G, const float *sino, float *v
 extern "C" long host_md_backproject_tiled(const leap_geometry *G, const float *sino, float *vol, int64_t *report)
 {
     if (!G->d_mdbp || !G->bp_tiled) return -1;
+    static_assert(MD_BP_NSPLIT_SHAPES == 2, "every shape has a case");
+    if (G->bp_split_shape >= 0) {
+        if (G->bp_split_shape == 0) host_md_bp_shape<MD_BP_SPLIT_SHAPES[0].zc, MD_BP_SPLIT_SHAPES[0].pw, MD_BP_SPLIT_SHAPES[0].ph>(G, sino, vol, report);
+        else host_md_bp_shape<MD_BP_SPLIT_SHAPES[1].zc, MD_BP_SPLIT_SHAPES[1].pw, MD_BP_SPLIT_SHAPES[1].ph>(G, sino, vol, report);
+        return report[0] + report[1] + report[2];
+    }
     switch (G->bp_shape) {
     case 0: host_md_bp_shape<MD_BP_SHAPES[0].zc, MD_BP_SHAPES[0].pw, MD_BP_SHAPES[0].ph>(G, sino, vol, report); break;
     case 1: host_md_bp_shape<MD_BP_SHAPES[1].zc, MD_BP_SHAPES[1].pw, MD_BP_SHAPES[1].ph>(G, sino, vol, report); break;

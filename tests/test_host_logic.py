@@ -287,8 +287,10 @@ SIDDON_TILED_CASES = {
 }
 
 
+@pytest.mark.parametrize("shape", ["bp_split=-1", "bp_split=0", "bp_split=1"])
 @pytest.mark.parametrize("name", list(SIDDON_TILED_CASES))
-def test_tiled_siddon_back_projection_matches_oracle_on_cpu(host, oracle_mod, name):
+def test_tiled_siddon_back_projection_matches_oracle_on_cpu(host, oracle_mod, monkeypatch, name, shape):
+    monkeypatch.setenv("LEAP_DEBUG", shape)             # no shared views, shared under either shape (where its windows fit)
     cfg = SIDDON_TILED_CASES[name]()
     cfg = cfg.replace(shift_u=cfg.shift_u + 0.123)      # no rays inside vertical voxel faces
     y = uniform_sinogram(cfg, 4)[0]
@@ -818,10 +820,12 @@ TILTED_SIDDON_TILED_CASES = {
 }
 
 
+@pytest.mark.parametrize("shape", ["bp_split=-1", "bp_split=0", "bp_split=1"])
 @pytest.mark.parametrize("name", list(TILTED_SIDDON_TILED_CASES))
-def test_tilted_siddon_tiled_back_projection_matches_oracle_on_cpu(host, oracle_mod, name):
+def test_tilted_siddon_tiled_back_projection_matches_oracle_on_cpu(host, oracle_mod, monkeypatch, name, shape):
     """The tiled back projection on tilted modules re-enacted tile by tile with the kernel's own functions: every staged
     window fits, every read stays inside it, every slot inside the sums, and the result is the oracle's."""
+    monkeypatch.setenv("LEAP_DEBUG", shape)
     cfg = TILTED_SIDDON_TILED_CASES[name]()
     y = uniform_sinogram(cfg, 6)[0]
     h = handle(host, cfg, B.LEAP_MODEL_SIDDON)
@@ -1130,3 +1134,20 @@ def test_a_tile_shape_asked_for_is_the_one_that_runs(host, monkeypatch, model, d
     desc = B.leap_geometry_describe(h, host).split("AT=")[1].split(" scratch")[0]
     B.leap_geometry_destroy(h, host)
     assert all(t in desc for t in tokens) and not any(t in desc for t in absent), desc
+
+
+@pytest.mark.parametrize("debug", ["", "bp_pair=0", "bp_pair=1", "bp_pair=2", "bp_pair=3", "bp_split=0", "bp_split=1", "bp_split=2"])
+@pytest.mark.parametrize("seed", range(12))
+def test_windows_of_mirror_images_and_shared_views_hold_what_is_read(host, monkeypatch, seed, debug):
+    """Random scans, every other one symmetric about the source plane (whose chunks start at the middle layer): no thread of any shape a
+    launch may take reads outside its window."""
+    from random_geometries import random_config
+    cfg = random_config(seed)
+    if seed % 2 == 0:
+        cfg = cfg.replace(shift_v=0.0, center_z=0.0)
+    if cfg.geom == CONE and seed % 3 == 0:
+        cfg = cfg.replace(geom=CONE_CURVED)
+    if debug:
+        monkeypatch.setenv("LEAP_DEBUG", debug)
+    rep, desc = window_report(host, cfg)
+    assert rep[7] == 0, (rep, desc)
