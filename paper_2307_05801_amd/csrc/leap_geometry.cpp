@@ -284,22 +284,22 @@ static bool mirrored_about_source_plane(const leap_geometry *G)
 }
 
 // What a launch of the tiled back projections takes per view, for footprints in units of 32 voxels per thread under a narrow window on an
-// idle chip (2.8 us): `idle` while its workgroups have a compute unit each, `full` per round of 256 workgroups once the compute units are full; a
-// launch takes as long as `views` further views whatever it holds (the window's first loads, the sums of groups of threads that share
-// the views).
+// idle chip (2.8 us): `idle` while its workgroups have a compute unit each, `full` per round of 256 workgroups once the compute units are
+// full and for `late` rounds more (the last of several workgroups per compute unit run beside fewer); a launch takes as long as `views`
+// further views whatever it holds (the window's first loads, the sums of groups of threads that share the views).
 struct LaunchTime {
-    double idle, full, views;
+    double idle, full, views, late = 0.0;
 };
 static double launch_time(const LaunchTime &t, double workgroups, int views)
 {
     const double rounds = std::ceil(workgroups / 256.0);
-    return std::max(t.idle * (1.0 + 0.07 * (rounds - 1.0)), t.full * rounds) * (views + t.views);
+    return std::max(t.idle * (1.0 + 0.07 * (rounds - 1.0)), t.full * (rounds + t.late)) * (views + t.views);
 }
 
 // Footprint model: one volume and two volumes per workgroup by shape; views shared, one volume and two (one volume of 16 voxels or fewer: two
 // workgroups of 1024 threads per compute unit, but not on a cylinder).
-static const LaunchTime BP_TIMES[BP_NSHAPES] = {{1.35, 0.53, 0.5}, {1.0, 0.33, 0.5}, {1.15, 0.38, 0.5}, {0.7, 0.23, 0.5},
-                                                {1.18, 0.37, 0.5}, {1.85, 0.68, 0.5}, {1.35, 0.51, 0.5}};
+static const LaunchTime BP_TIMES[BP_NSHAPES] = {{1.35, 0.46, 0.5, 1.0}, {1.0, 0.30, 0.5, 1.0}, {1.15, 0.35, 0.5, 1.0}, {0.7, 0.21, 0.5, 1.0},
+                                                {1.18, 0.33, 0.5, 1.0}, {1.85, 0.62, 0.5, 1.0}, {1.35, 0.42, 0.5, 1.0}};
 static const LaunchTime BP_PAIR_TIMES[BP_NPAIR_SHAPES] = {{1.35, 0.55, 1.0}, {1.4, 0.58, 1.0}, {0.9, 0.27, 1.0}, {1.35, 0.59, 1.0}};
 static const LaunchTime BP_SPLIT_TIMES[2][BP_NSPLIT_SHAPES] = {{{0.42, 0.43, 4.0}, {0.29, 0.24, 4.0}, {0.24, 0.20, 4.0}},
                                                                {{0.56, 0.56, 4.0}, {0.34, 0.34, 4.0}, {0.29, 0.29, 4.0}}};
