@@ -542,19 +542,22 @@ static void block_order_options(leap_geometry *G)
 
 // Two volumes to a wave halve a launch's waves and take more registers: worth it where enough workgroups are left, and the launch of
 // its own that an odd last item takes must fill the chip too.  Times of two over one per wave, by workgroups of two volumes: one group
-// of rows 20 to 700 1.15 to 0.95, 900 and more 0.66 to 0.98; several groups 20 to 1400 1.20 to 0.78 (depending on how full the last
-// round of workgroups is), 3000 and more 0.83 to 0.96; cylinder 1000 and more 0.65 to 0.95.  Batches of three, by workgroups of one
-// volume: one group 20 to 700 1.98 to 1.38, 1000 to 1400 0.92 to 1.13, 1600 and more 0.88 to 1.00; several 20 to 2800 1.99 to 0.94, 4000
-// and more 0.94 to 1.00.  An item's bits are the same either way.
+// of rows 20 to 600 1.15 to 0.92, 700 and more 0.66 to 1.02; two groups 20 to 700 1.20 to 0.94, 1000 and more 0.84 to 1.06; three groups,
+// four workgroups per compute unit, 1020, 2040 and 3060 0.78 to 0.87, but 1380 and 2200 (a last round nearly empty) 1.06 to 1.08, 3000
+// and more 0.83 to 0.92; cylinder 1000 and more 0.65 to 0.95.  Batches of three, by workgroups of one volume: one group 20 to 720 1.98 to
+// 1.38, 900 to 1400 0.92 to 1.13, 1600 and more 0.88 to 1.00; several groups 20 to 2800 1.99 to 0.94, 4000 and more 0.94 to 1.00.  An item's
+// bits are the same either way.
 int leap_forward_paired(const leap_geometry *G, int items)
 {
     if (!G->fp_pair_rg || items < 2) return 0;
     if (G->fp_pair_always) return items / 2 * 2;
+    const int groups = G->fp_pair_rg;
     const double blocks = (double)((G->g.ncols + FP_WAVES * G->fp_cw - 1) / (FP_WAVES * G->fp_cw)) * G->g.nviews *
-                          ((G->g.nrows + G->fp_pair_rg * 128 - 1) / (G->fp_pair_rg * 128));
-    const bool one_group = G->fp_pair_rg == 1;
-    if (blocks * (items / 2) < (one_group || G->g.type == SF_CONE_CURVED ? 1000.0 : 3000.0)) return 0;
-    if (items % 2 && blocks < (one_group ? 1600.0 : 4000.0)) return 0;
+                          ((G->g.nrows + groups * 128 - 1) / (groups * 128));
+    const double launch = blocks * (items / 2), rounds = launch / 1024.0;
+    if (launch < (groups == 1 ? 700.0 : 900.0)) return 0;
+    if (groups > 2 && G->g.type != SF_CONE_CURVED && launch < 3000.0 && rounds < 0.88 * std::ceil(rounds)) return 0;
+    if (items % 2 && blocks < (groups == 1 ? 1600.0 : 4000.0)) return 0;
     return items / 2 * 2;
 }
 

@@ -998,13 +998,14 @@ def scan_of(n, nviews, nrows, ncols, pixel_v=1.4, geom=CONE):
 
 @pytest.mark.parametrize("cfg,pairs", [
     # workgroups of one group of rows: views times column tiles of eight or sixteen
-    (scan_of(64, 30, 70, 89), {2: 0, 3: 0, 5: 0, 8: 8, 16: 16}),             # 360 a volume
+    (scan_of(64, 30, 70, 89), {2: 0, 3: 0, 4: 4, 5: 0, 8: 8, 16: 16}),       # 360 a volume
     (scan_of(64, 90, 70, 89), {2: 2, 3: 0, 4: 4, 5: 0, 8: 8}),               # 1080
     (scan_of(64, 180, 70, 89), {1: 0, 2: 2, 3: 2, 7: 6, 16: 16}),            # 2160
     # several groups of rows
-    (scan_of(192, 60, 264, 268), {2: 0, 3: 0, 5: 0, 8: 8}),                  # 1020
+    (scan_of(192, 40, 200, 268), {2: 0, 3: 0, 4: 4, 8: 8}),                  # two groups, 680
+    (scan_of(192, 60, 264, 268), {2: 2, 3: 0, 4: 4, 5: 0, 8: 8}),            # three, 1020: one round of workgroups, two, four
     (scan_of(192, 250, 264, 268), {2: 2, 3: 2, 8: 8}),                       # 4250
-    (config(4), {1: 0, 2: 0, 3: 0, 4: 0, 6: 6, 7: 0, 8: 8}),                 # 1440
+    (config(4), {1: 0, 2: 0, 3: 0, 4: 4, 6: 6, 7: 0, 8: 8}),                 # 1440: a round and a half, three rounds
     # rows of 1.5 voxels and more: one group only, of two voxels and more: none (but on a cylinder)
     (scan_of(64, 180, 46, 89, pixel_v=2.2), {2: 2, 3: 2}),
     (scan_of(192, 180, 264, 268, pixel_v=2.2), {2: 0, 8: 0, 16: 0}),
