@@ -102,11 +102,11 @@ def test_argument_checks(oracle_mod):
     geo.close()
 
 
-@pytest.mark.parametrize("voxels", [1.25, 1.7, 2.7])
+@pytest.mark.parametrize("voxels", [1.25, 1.7, 2.4])
 @pytest.mark.parametrize("geometry", [CONE, CONE_CURVED])
 def test_rows_of_several_voxels(oracle_mod, geometry, voxels):
     """Rows taller than a voxel are summed by weights, and SIRT divides by the sums of rays that hardly meet the volume.  Ten iterations are
-    2e-7 to 3e-6 from 64 bits, the farthest voxel up to 1.7e-3 of the root mean square: four times that."""
+    1.4e-7 from 64 bits, the farthest voxel 1.8e-6 of the root mean square (a weight lost in a sliver moves one by 3e-4): ten times either."""
     import torch
     from oracle import recon_oracle as ro
     from paper_2307_05801_amd import Geometry, recon
@@ -120,5 +120,5 @@ def test_rows_of_several_voxels(oracle_mod, geometry, voxels):
     geo.close()
     want = ro.sirt(A, AT, y, np.zeros(cfg.vol_shape), 10)
     print(f"rel {rel_l2(got, want):.2e} max {np.abs(got - want).max() / np.sqrt((want ** 2).mean()):.2e}")
-    assert rel_l2(got, want) <= 1.2e-5
-    assert np.abs(got - want).max() <= 7e-3 * np.sqrt((want ** 2).mean())
+    assert rel_l2(got, want) <= 1.4e-6
+    assert np.abs(got - want).max() <= 1.8e-5 * np.sqrt((want ** 2).mean())
