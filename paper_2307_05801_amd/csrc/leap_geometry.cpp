@@ -441,7 +441,7 @@ static void select_footprint_tiled(leap_geometry *G)
         for (int sh = std::max((int)forced + 1, BP_FIRST_SHORT_SHAPE); sh <= BP_LAST_SHORT_SHAPE; ++sh) order[norder++] = sh;
     }
     // One volume per workgroup and two: the first shape of either kind that fits, a pair of shapes per pass over the tiles.  Two items of a
-    // batch take chunks of the same height as one, so that an item comes out the same bits in any batch: known when one's shape is.
+    // batch take chunks of the same height as one, so that going in twos changes no item's bits: known when one's shape is.
     const std::vector<int> pair_shapes = backproject_pair_shapes(G);
     const int kfirst = G->bp_mirror ? sf_mirror_first_voxel_above(d->nz) : 0;
     std::vector<WindowNeed> known;               // by height and first chunk: shapes of one height share theirs
@@ -767,7 +767,6 @@ static void select_siddon_fast_kernels(leap_geometry *G)
             G->bp_tiled = window_fits(need, BP_SHAPES[sh]);
         }
         if (!G->bp_tiled) return;
-        const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
         // Groups of threads that share the views: the shapes whose windows fit, where one volume would take any of them.
         auto fits = [&](int sh) { return G->bp_need_w <= SD_BP_SPLIT_SHAPES[sh].pw - 1 && window_fits(window_of(SD_BP_SPLIT_SHAPES[sh].zc), SD_BP_SPLIT_SHAPES[sh]); };
         choose_siddon_split(G, SD_BP_NSPLIT_SHAPES, fits);

@@ -447,7 +447,7 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
     // What a candidate's visit needs as plain vector operands (the CW column factors and the clamp offsets of its height class)
     // goes through LDS: every lane writes its candidate's record, the wave reads the record of the
     // candidate it visits back at a uniform address, which the LDS serves as a broadcast without touching the vector
-    // ALU (a v_readlane costs as much issue time as two and a half FMAs; the kernel is bound by that issue time).
+    // ALU (a v_readlane costs as much issue time as two and a half FMAs, and issue is what binds beside the lane loads).
     // Only what must sit in scalar registers still comes by v_readlane: the column's offset (buffer descriptor) and mu
     // (scalar operand of the placement FMAs).
     __shared__ float4 recs[FP_WAVES][64][2];
