@@ -598,6 +598,11 @@ static void select_footprint_columns(leap_geometry *G)
         G->fp_cw /= 2;
         need = slots_needed(G->fp_cw);
     }
+    // cylinder: a candidate's fan angle is taken from its bundle's middle ray (detectors of a few dozen columns can be too coarse for that)
+    if (d->type == LEAP_CONE_CURVED) {
+        while (G->fp_cw > cw_min && sf_bundle_reach(G->fp_cw, G->max_cols_per_voxel) / G->g.kud >= std::atan(SF_ATAN_MAX)) need = slots_needed(G->fp_cw /= 2);
+        if (!(sf_bundle_reach(G->fp_cw, G->max_cols_per_voxel) / G->g.kud < std::atan(SF_ATAN_MAX))) return;
+    }
     G->fp_need_q = need;
     G->fp_nq = need <= 4 ? 4 : (need <= 8 ? 8 : 16);
     G->fp_nkp = std::min(FP_MAX_P, std::max(2, (int)std::ceil(2.0 * vpr - 1e-6) + 1));

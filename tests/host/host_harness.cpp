@@ -321,6 +321,38 @@ extern "C" int host_curved_column_deviation(const leap_geometry *G, double *out)
     return 0;
 }
 
+// ---- cylinder: the bundle-relative column function of the column-wise forward kernel against the general one ---------
+// Over every view, bundle of cw columns and voxel column that touches one of them: out[0] = largest |difference| of the column coordinate
+// (pixels), out[1] = of the knot offsets, out[2] = of the distance from the source (relative); out[3] = largest tangent fed to the
+// arc-tangent polynomials, out[4] = the number of voxel columns compared.
+extern "C" int host_curved_bundle_deviation(const leap_geometry *G, double *out)
+{
+    const SfGeom &g = G->g;
+    if (g.type != SF_CONE_CURVED || !G->fp_columns) return -1;
+    const int cw = G->fp_cw, nbundles = (g.ncols + cw - 1) / cw;
+    double dxi = 0.0, dof = 0.0, dden = 0.0, tangent = 0.0, count = 0.0;
+#pragma omp parallel for collapse(2) reduction(max : dxi, dof, dden, tangent) reduction(+ : count)
+    for (int a = 0; a < g.nviews; ++a)
+        for (int b = 0; b < nbundles; ++b) {
+            const SfView &v = G->views[a];
+            const SfNearRay ray = sf_near_ray(g, sf_bundle_middle(b * cw, cw));
+            for (int j = 0; j < g.ny; ++j)
+                for (int i = 0; i < g.nx; ++i) {
+                    const SfColumn p = sf_column(g, v, i, j);
+                    if (p.xi + p.o3 < b * cw - 0.5 || p.xi + p.o0 > b * cw + cw - 0.5) continue;
+                    const SfColumn q = sf_column_curved_near(g, v, i, j, ray);
+                    dxi = std::max(dxi, std::fabs(p.xi - q.xi));
+                    dof = std::max(dof, (double)std::max(std::max(std::fabs(p.o0 - q.o0), std::fabs(p.o1 - q.o1)),
+                                                         std::max(std::fabs(p.o2 - q.o2), std::fabs(p.o3 - q.o3))));
+                    dden = std::max(dden, std::max(std::fabs(q.den / p.den - 1.0), std::fabs(q.inv * p.den - 1.0)));
+                    tangent = std::max(tangent, std::tan(std::max(std::fabs(p.xi - ray.xi0), (double)std::max(std::fabs(p.o0), std::fabs(p.o3))) / g.kud));
+                    count += 1.0;
+                }
+        }
+    out[0] = dxi; out[1] = dof; out[2] = dden; out[3] = tangent; out[4] = count;
+    return 0;
+}
+
 // ---- column-wise forward projection: the kernel's own per-lane functions, stepped serially ------------------------------
 // One (view, bundle of CW detector columns) at a time, the way a wavefront of sf_project_columns works through it: the
 // host's marching axis for the bundle, candidate slots per slab, sf_candidate_record for every candidate, then for every

@@ -403,6 +403,22 @@ def test_curved_tile_relative_columns_agree_with_the_general_function(host, name
     assert out[2] < 0.08, list(out)
 
 
+@pytest.mark.parametrize("ncols,pixel_u", [(200, 2.0), (33, 8.0), (31, 9.0)])
+def test_curved_bundle_relative_columns_agree_with_the_general_function(host, ncols, pixel_u):
+    """The column-wise forward projection takes a voxel column's fan angle relative to its bundle's middle ray, from fine pixels to
+    ones so wide that the angles come near the polynomials' end.  Column coordinate: double throughout, relative error 7e-13 of a
+    few pixels.  Knot offsets: float, both functions within a few roundings (6e-8) of up to 4 pixels, atanf's own 2 ulp among them."""
+    cfg = CTConfig("curved_near", CONE_CURVED, nviews=7, arc_deg=360.0, nrows=40, ncols=ncols, pixel_v=2.5, pixel_u=pixel_u,
+                   nx=40, ny=37, nz=16, voxel_xy=2.0, voxel_z=2.0, sod=90.0, sdd=180.0, shift_u=0.3)
+    h = handle(host, cfg)
+    out = (C.c_double * 5)()
+    host.host_curved_bundle_deviation.argtypes = [C.c_void_p, C.POINTER(C.c_double)]
+    assert host.host_curved_bundle_deviation(h, out) == 0
+    B.leap_geometry_destroy(h, host)
+    assert out[4] > 1000 and out[3] < 0.32, list(out)
+    assert out[0] < 2e-11 and out[1] < 2e-6 and out[2] < 1e-14, list(out)
+
+
 def test_curved_source_too_close_for_the_series(host):
     """Corner angles above 0.08 rad: the tiled curved kernel is not chosen."""
     cfg = CTConfig("curved_close", CONE_CURVED, nviews=8, arc_deg=360.0, nrows=40, ncols=64, pixel_v=2.5, pixel_u=2.5,
