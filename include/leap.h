@@ -134,8 +134,8 @@ int leap_backproject(const leap_geometry *geom, const float *d_sino, float *d_vo
  * nothing and calls no allocating routine; the array's address is looked up once per device in leap_geometry_create.
  * Limit: four voxel layers of the copy, 4 * max(nx, ny) * (nz + 16) floats, must fit the array (volumes up to about
  * 2000^3 do; the fewer layers fit, the more passes the call makes), else LEAP_UNSUPPORTED with a message; geometries
- * whose forward kernel reads the caller's volume directly (fan-beam, tilted Siddon modules, very coarse detectors)
- * have no limit.  Items of a batch share the array, as many per launch as fit.  All calls on one GPU share the one
+ * whose forward kernel reads the caller's volume directly (fan-beam, tilted footprints, very coarse detectors, detectors of
+ * fewer than 32 rows, whose results differ from leap_project's in the last bits) have no limit.  Items of a batch share the array, as many per launch as fit.  All calls on one GPU share the one
  * array, whatever the handle: calls that overlap in time on one GPU (two streams, two threads) race; order them.
  * The array keeps the last call's contents; each call restores the zeros it relies on. */
 int leap_project_static_scratch(const leap_geometry *geom, const float *d_vol, float *d_sino, int32_t batch, void *hip_stream);
@@ -197,7 +197,8 @@ const char *leap_last_error(void);
  * name them), bp_pair=0..3|-1 (the shape for two volumes per
  * workgroup, whatever the batch, none), bp_split=0..2|-1 (the shape for views
  * shared between groups of threads, whatever the batch, none), pairs=0|1 (forward: one item of a
- * batch per wavefront, or two wherever there is a kernel for two, however small the batch), slab=N (voxel layers per scratch slab), items=N (batch items per launch),
+ * batch per wavefront, or two wherever there is a kernel for two, however small the batch), parts=1|4 (forward: a wavefront per bundle
+ * of columns, or four that share its layers; parallel beams also 2), slab=N (voxel layers per scratch slab), items=N (batch items per launch),
  * scratch_mib=N (scratch budget), stage_kib=N (size of a pinned staging buffer of the host-memory entry points). */
 int leap_geometry_describe(const leap_geometry *geom, char *buf, int32_t cap);
 

@@ -11,7 +11,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libleap_hip.so")
-SOURCES = ["leap_geometry.cpp", "leap_host.cpp", "leap_kernels.hip", "leap_footprint_forward.hip", "leap_footprint_back.hip",
+SOURCES = ["leap_geometry.cpp", "leap_host.cpp", "leap_kernels.hip", "leap_footprint_forward.hip", "leap_footprint_forward_parts.hip", "leap_footprint_back.hip",
            "leap_footprint_back_pairs.hip", "leap_footprint_back_split.hip", "leap_siddon_back_split.hip", "leap_recon.hip"]
 
 

@@ -561,12 +561,31 @@ int leap_forward_paired(const leap_geometry *G, int items)
     return items / 2 * 2;
 }
 
+// Waves of a workgroup that share a bundle's layers: where a volume has too few bundles to keep the chip's 1024 SIMDs supplied with
+// waves, each waiting for its own loads most of the time.  By the waves of one volume (its views, bundles and bands of rows), us for one
+// volume and for four at once, a wave per bundle -> four: cone 500 66 -> 34, 80 -> 59; 1350 200 -> 85, 267 -> 228; 2010 371 -> 177, 534 ->
+// 454; 2700 82 -> 54, 124 -> 107; 4020 133 -> 96, 258 -> 245; 5400 202 -> 174, 405 -> 428; 8040 436 -> 414, 1135 -> 1340; 10700 131 -> 128,
+// 309 -> 333.  Parallel beams by rows: 2040 55 -> 35, 97 -> 92; 2700 69 -> 46, 128 -> 133 (two waves 54, 127); 5400 183 -> 151, 447 -> 518.
+// The sums are added in another order, so the choice depends on the scan alone: an item has the same bits in any batch.
+static int forward_parts(const leap_geometry *G, int nbundles)
+{
+    const leap_geometry_desc *d = &G->desc;
+    if (G->fp_cw < 2) return 1;
+    const int band = G->fp_rows ? G->fp_row_groups * 64 * G->fp_rows : G->fp_rg * 128;
+    const double waves = (double)d->nviews * nbundles * ((d->nrows + band - 1) / band);
+    int parts = waves <= 4500.0 ? FP_PARTS : 1;
+    if (G->fp_rows && waves > 2200.0) parts = std::min(parts, 2);
+    long v;
+    if (debug_option("parts", v) && (v == 1 || v == FP_PARTS || (v == 2 && G->fp_rows))) parts = (int)v;
+    return parts;
+}
+
 // Footprint model, column-wise forward projection: static limits and the marching axis of every bundle.
 static void select_footprint_columns(leap_geometry *G)
 {
     const leap_geometry_desc *d = &G->desc;
     const double vpr = G->max_voxels_per_row;
-    if (d->type == LEAP_FAN || d->nrows < 32 || !std::isfinite(vpr) || vpr > 3.0) return;
+    if (d->type == LEAP_FAN || d->nrows < FP_MIN_ROWS || !std::isfinite(vpr) || vpr > 3.0) return;
     // kappa (the axial voxel coordinate of a row's edge) must stay within +-2^19 for the kernel's placement arithmetic
     if (!((d->nrows + 1024.0) * vpr + d->nz + 64.0 < 500000.0)) return;
     long v;
@@ -627,6 +646,7 @@ static void select_footprint_columns(leap_geometry *G)
         G->fp_row_groups = d->nrows > 256 ? 2 : 1;
     }
     const int nbundles = (d->ncols + G->fp_cw - 1) / G->fp_cw;
+    G->fp_parts = forward_parts(G, nbundles);
     G->major.resize((size_t)d->nviews * nbundles);
     for (int a = 0; a < d->nviews; ++a)
         for (int b = 0; b < nbundles; ++b)
@@ -734,7 +754,10 @@ static void select_siddon_fast_kernels(leap_geometry *G)
     if (d->type == LEAP_FAN || !(G->sd_max_axial_slope <= 0.999)) return;
 
     // wave-per-column forward projection: no ray may cross more than one z-face per slab
-    if (d->nrows >= 32) {
+    // (short detectors leave most lanes idle; column-wise over one thread per ray, 30 / 720 views: 256^2 x 20 voxels, 22 rows, cone 0.54 / 0.64,
+    // parallel 0.79 / 0.86; 128^2 x 15, 16 rows, 0.48 / 0.72 and 0.64 / 1.07; 256^2, 8 rows 0.85 / 1.64 and 1.02 / 2.16; tilted modules at 22
+    // rows 0.96 / 1.24: those from 32 rows on)
+    if (d->nrows >= (d->type == LEAP_PARALLEL ? 22 : 16)) {
         G->sd_columns = true;
         static const int single_groups[] = {1, 2, 4, 8};
         G->fp_rg = row_groups(d->nrows, 64, single_groups, 4);
@@ -1500,8 +1523,8 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
     if (siddon && G->sd_columns)
         std::snprintf(fwd, sizeof fwd, "columns(rg=%d,slab=%d%s)", G->fp_rg, G->slab_width, G->sd_pairs == 2 ? ",pairs apart" : (G->sd_pairs ? ",pairs" : ""));
     else if (!siddon && G->fp_columns)
-        std::snprintf(fwd, sizeof fwd, "columns(nq=%d/%d,nkp=%d,rg=%d,cw=%d,slab=%d%s)", G->fp_need_q, G->fp_nq, G->fp_nkp,
-                      G->fp_rg, G->fp_cw, G->slab_width, G->fp_rows ? ",rows" : "");
+        std::snprintf(fwd, sizeof fwd, G->fp_parts > 1 ? "columns(nq=%d/%d,nkp=%d,rg=%d,cw=%d,slab=%d,parts=%d%s)" : "columns(nq=%d/%d,nkp=%d,rg=%d,cw=%d,slab=%d%.0d%s)",
+                      G->fp_need_q, G->fp_nq, G->fp_nkp, G->fp_rg, G->fp_cw, G->slab_width, G->fp_parts > 1 ? G->fp_parts : 0, G->fp_rows ? ",rows" : "");
     else
         std::snprintf(fwd, sizeof fwd, G->flat ? "general(flat,span=%d)" : (G->mf_tiles ? "general(tiles)" : "general"), G->flat_span);
     if (G->bp_tiled && G->d_mdbp)

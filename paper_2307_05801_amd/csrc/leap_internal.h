@@ -48,6 +48,7 @@ struct leap_geometry {
     int fp_nkp = 0;                     // voxels a pair of adjacent detector rows can overlap
     int fp_rg = 0;                      // row groups per wave (footprints: groups of 128 rows; Siddon: of 64)
     int fp_cw = 4, fp_vb = 128, fp_tb = 1;   // detector columns per wave; block order: views per run, tiles per chunk
+    int fp_parts = 1;                   // waves of a workgroup that share a bundle's layers (1: none, each has a bundle of its own)
     bool fp_columns = false;
     int fp_pair_rg = 0;                 // row groups per wave with two volumes per wave (0: one volume per wave only)
     bool fp_pair_always = false;        // (debugging: two volumes per wave in every batch, however few its waves)
@@ -138,11 +139,11 @@ struct FwdScratch {
 inline unsigned cdiv(unsigned a, unsigned b) { return (a + b - 1) / b; }
 
 // kernel launchers (leap_kernels.hip); one batch item per call
-int leap_launch_project(const leap_geometry *geom, const float *d_vol, float *d_sino, hipStream_t stream);
 int leap_launch_project_batch(const leap_geometry *geom, const float *d_vol, float *d_sino, int batch, hipStream_t stream);
 int leap_launch_backproject(const leap_geometry *geom, const float *d_sino, float *d_vol, hipStream_t stream);
 struct SfSlab;
 bool leap_launch_footprint_slab(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward.hip
+bool leap_launch_footprint_slab_parts(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward_parts.hip
 int leap_launch_footprint_back(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                         // leap_footprint_back.hip
 bool leap_launch_backproject_split(const leap_geometry *geom, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_footprint_back_split.hip
 bool leap_launch_siddon_back_split(const leap_geometry *geom, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_siddon_back_split.hip

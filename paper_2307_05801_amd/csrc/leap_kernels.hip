@@ -244,16 +244,16 @@ static bool launch_sd_slab(const leap_geometry *G, const FwdScratch &S, const Sf
 static int run_forward_columns(const leap_geometry *G, const FwdScratch &S, const float *d_vol, float *d_sino, int batch,
                                hipStream_t stream);
 
+// On the general kernel, whatever the handle's fast one.
 static int launch_sd_project(const leap_geometry *G, const float *d_vol, float *d_sino, hipStream_t stream)
 {
     const SfGeom &g = G->g;
-    if (g.type == SF_MODULAR && !G->sd_columns) {     // sizes were checked against the grid limits at creation
+    if (g.type == SF_MODULAR) {                       // sizes were checked against the grid limits at creation
         dim3 grid(cdiv(g.ncols, 64), cdiv(g.nrows, 4), g.nviews);
         hipLaunchKernelGGL(md_project_general, grid, dim3(64, 4, 1), 0, stream, g, G->d_poses, d_vol, d_sino);
         LEAP_HIP_CHECK(hipGetLastError());
         return LEAP_OK;
     }
-    if (G->sd_columns) return leap_launch_project_batch(G, d_vol, d_sino, 1, stream);
     dim3 grid(cdiv(g.ncols, 64), cdiv(g.nrows, 4), g.nviews);
     if (grid.y > 65535u) {
         leap_set_error("detector has too many rows for one launch");
@@ -552,45 +552,12 @@ static int backproject_flat(const leap_geometry *G, const float *d_sino, float *
     return LEAP_OK;
 }
 
-int leap_launch_project_batch(const leap_geometry *G, const float *d_vol, float *d_sino, int batch, hipStream_t stream)
-{
-    const SfGeom &g = G->g;
-    const size_t nvol = (size_t)g.nx * g.ny * g.nz, nsino = (size_t)g.nviews * g.nrows * g.ncols;
-    if (G->flat) return project_flat(G, d_vol, d_sino, batch, stream, true);
-    const bool footprint_fast = g.model != SF_MODEL_SIDDON && G->fp_columns;
-    const bool siddon_fast = g.model == SF_MODEL_SIDDON && G->sd_columns;
-    if (footprint_fast || siddon_fast) {
-        // Calls on one handle share its scratch.  They are ordered on the device: a call that arrives on another stream
-        // than the last one first waits for that one's kernels.
-        std::lock_guard<std::mutex> lock(G->scratch_mutex);
-        if (G->scratch_used && G->scratch_stream != stream) LEAP_HIP_CHECK(hipStreamWaitEvent(stream, G->scratch_event, 0));
-        FwdScratch S;
-        S.volz = G->d_volz;
-        if (!leap_plan_scratch(G, G->scratch_bytes / sizeof(float), batch, S.width, S.items)) {
-            leap_set_error("internal: the handle's scratch holds no slab");
-            return LEAP_UNSUPPORTED;
-        }
-        S.item_floats = ((size_t)S.width * (size_t)(g.nx > g.ny ? g.nx : g.ny) + 1) * (size_t)G->nzp;
-        const int rc = run_forward_columns(G, S, d_vol, d_sino, batch, stream);
-        if (rc != LEAP_OK) return rc;
-        LEAP_HIP_CHECK(hipEventRecord(G->scratch_event, stream));
-        G->scratch_stream = stream;
-        G->scratch_used = true;
-        return LEAP_OK;
-    }
-    for (int b = 0; b < batch; ++b) {
-        const int rc = leap_launch_project(G, d_vol + b * nvol, d_sino + b * nsino, stream);
-        if (rc != LEAP_OK) return rc;
-    }
-    return LEAP_OK;
-}
-
-int leap_launch_project(const leap_geometry *G, const float *d_vol, float *d_sino, hipStream_t stream)
+// One volume on the kernels that read it as it lies: the flat ones, the tiled footprints', the general ones.
+static int launch_project_direct(const leap_geometry *G, const float *d_vol, float *d_sino, hipStream_t stream)
 {
     const SfGeom &g = G->g;
     if (g.model == SF_MODEL_SIDDON) return launch_sd_project(G, d_vol, d_sino, stream);
     if (G->flat) return project_flat(G, d_vol, d_sino, 1, stream, false);
-    if (G->fp_columns) return leap_launch_project_batch(G, d_vol, d_sino, 1, stream);
     if (G->mf_tiles) {
         dim3 grid(cdiv(cdiv(g.ncols, MF_TC), 4), cdiv(g.nrows, MF_TR), g.nviews);
         hipLaunchKernelGGL(mf_project_tiles, grid, dim3(256), 0, stream, g, G->d_mfviews, d_vol, d_sino);
@@ -614,6 +581,45 @@ int leap_launch_project(const leap_geometry *G, const float *d_vol, float *d_sin
     else
         hipLaunchKernelGGL(sf_project_general, grid, block, 0, stream, g, G->d_views, d_vol, d_sino);
     LEAP_HIP_CHECK(hipGetLastError());
+    return LEAP_OK;
+}
+
+int leap_launch_project_batch(const leap_geometry *G, const float *d_vol, float *d_sino, int batch, hipStream_t stream)
+{
+    const SfGeom &g = G->g;
+    const size_t nvol = (size_t)g.nx * g.ny * g.nz, nsino = (size_t)g.nviews * g.nrows * g.ncols;
+    if (G->flat) return project_flat(G, d_vol, d_sino, batch, stream, true);
+    const bool footprint_fast = g.model != SF_MODEL_SIDDON && G->fp_columns;
+    const bool siddon_fast = g.model == SF_MODEL_SIDDON && G->sd_columns;
+    bool direct = !footprint_fast && !siddon_fast;
+    if (!direct && g.nrows < FP_FREE_ROWS) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        LEAP_HIP_CHECK(hipStreamIsCapturing(stream, &capture));
+        direct = capture != hipStreamCaptureStatusNone;
+    }
+    if (!direct) {
+        // Calls on one handle share its scratch.  They are ordered on the device: a call that arrives on another stream
+        // than the last one first waits for that one's kernels.
+        std::lock_guard<std::mutex> lock(G->scratch_mutex);
+        if (G->scratch_used && G->scratch_stream != stream) LEAP_HIP_CHECK(hipStreamWaitEvent(stream, G->scratch_event, 0));
+        FwdScratch S;
+        S.volz = G->d_volz;
+        if (!leap_plan_scratch(G, G->scratch_bytes / sizeof(float), batch, S.width, S.items)) {
+            leap_set_error("internal: the handle's scratch holds no slab");
+            return LEAP_UNSUPPORTED;
+        }
+        S.item_floats = ((size_t)S.width * (size_t)(g.nx > g.ny ? g.nx : g.ny) + 1) * (size_t)G->nzp;
+        const int rc = run_forward_columns(G, S, d_vol, d_sino, batch, stream);
+        if (rc != LEAP_OK) return rc;
+        LEAP_HIP_CHECK(hipEventRecord(G->scratch_event, stream));
+        G->scratch_stream = stream;
+        G->scratch_used = true;
+        return LEAP_OK;
+    }
+    for (int b = 0; b < batch; ++b) {
+        const int rc = launch_project_direct(G, d_vol + b * nvol, d_sino + b * nsino, stream);
+        if (rc != LEAP_OK) return rc;
+    }
     return LEAP_OK;
 }
 
@@ -733,12 +739,12 @@ extern "C" int leap_project_static_scratch(const leap_geometry *G, const float *
     const SfGeom &g = G->g;
     const bool footprint_fast = g.model != SF_MODEL_SIDDON && G->fp_columns;
     const bool siddon_fast = g.model == SF_MODEL_SIDDON && G->sd_columns;
-    if (!footprint_fast && !siddon_fast) {
+    if ((!footprint_fast && !siddon_fast) || g.nrows < FP_FREE_ROWS) {
         // this geometry runs on kernels that read the caller's volume directly: no scratch is involved at all
         if (G->flat) return project_flat(G, d_vol, d_sino, batch, stream, false);
         const size_t nvol = (size_t)g.nx * g.ny * g.nz, nsino = (size_t)g.nviews * g.nrows * g.ncols;
         for (int b = 0; b < batch; ++b) {
-            const int rc = leap_launch_project(G, d_vol + b * nvol, d_sino + b * nsino, stream);
+            const int rc = launch_project_direct(G, d_vol + b * nvol, d_sino + b * nsino, stream);
             if (rc != LEAP_OK) return rc;
         }
         return LEAP_OK;

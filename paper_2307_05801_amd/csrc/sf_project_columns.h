@@ -40,6 +40,14 @@ constexpr int FP_PAD = 8;        // zero voxels before and after every z-column 
 constexpr int FP_MAX_P = 7;      // most voxels a pair of adjacent rows may overlap (rows of up to 3 voxels)
 constexpr int FP_WAVES = 4;      // waves per workgroup: adjacent column bundles of one view (each wave its own LDS, no barrier)
 
+constexpr int FP_PARTS = 4;      // waves of a workgroup that share a bundle's layers where a scan has few bundles
+// Fewest detector rows: below, the general kernel's eight rows per thread waste less than the lanes of a wave (5 rows, 716 columns, 512^2 x 5
+// voxels: 60 views 3.5 ms against 1.9 here, 360 views 6.6 against 8.8; 8 rows, 720 views 17.1 against 16.8, 24 rows 58.8 against 17.5).
+constexpr int FP_MIN_ROWS = 8;
+// Scans of fewer rows than this take the general kernels while a stream is being captured and on the fixed scratch array, so that such calls
+// need no scratch at all.
+constexpr int FP_FREE_ROWS = 32;
+
 // Highest height class (see SfPairClass) of a scan whose pairs of rows overlap up to nkp voxels.
 SF_HD int fp_height_class(int nkp) { return nkp <= 5 ? nkp - 2 : 4; }
 
@@ -47,9 +55,9 @@ SF_HD int fp_height_class(int nkp) { return nkp <= 5 ? nkp - 2 : 4; }
 // wave: rows of up to a voxel and a half, taller ones where the sums and voxels of two leave enough waves in flight.  Two against one per
 // wave, time ratios where the chip is full, one group of rows / more: rows of 1.5 to 2 voxels 0.69 to 0.92 / 0.91 to 1.16, of 2 to 3
 // 0.92 to 1.16 / 1.00 to 1.24; on a cylinder (few waves in flight either way) 0.69 to 0.79 / 0.74 to 0.95 and 0.70 to 0.83 / 0.89 to 1.06.
-constexpr bool fp_instance_exists(int hc, int rg, int cw, int gt, int ns)
+constexpr bool fp_instance_exists(int hc, int rg, int cw, int gt, int ns, int parts = 1)
 {
-    if (cw == 1) return gt == 0 && ns == 1;
+    if (cw == 1) return gt == 0 && ns == 1 && parts == 1;
     if (ns == 1) return true;
     return rg <= 3 && (hc <= 2 || (hc == 3 && (rg == 1 || gt == 1)) || (hc == 4 && rg == 1 && gt == 1));
 }
@@ -394,6 +402,39 @@ __device__ __forceinline__ void fp_store_four(float *__restrict__ dst, float a, 
     *reinterpret_cast<Quad *>(dst) = q;
 }
 
+// Waves of a workgroup that share a bundle (the rule stands at forward_parts) take consecutive runs of the slab's blocks of 64 / nq layers: those of this part.
+SF_HD void fp_part_of(const SfSlab &slab, int block, int part, int parts, int &n_first, int &n_end)
+{
+    const int blocks = (slab.n1 - slab.n0 + block - 1) / block;
+    n_first = slab.n0 + blocks * part / parts * block;
+    n_end = slab.n0 + blocks * (part + 1) / parts * block;
+    n_end = n_end < slab.n1 ? n_end : slab.n1;
+}
+
+// Adds the parts' N sums per lane in the order of the parts; the total is valid in part 0.  red: 8 floats per lane and wave, free to use
+// once every wave of the workgroup has arrived.
+template <int N, int PARTS>
+__device__ __forceinline__ void fp_sum_parts(float *acc, float *__restrict__ red, int part, int lane)
+{
+#pragma unroll
+    for (int s = 0; s < N; s += 8) {
+        __syncthreads();
+        if (part > 0) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if (s + t < N) red[(part * 8 + t) * 64 + lane] = acc[s + t];
+        }
+        __syncthreads();
+        if (part == 0) {
+#pragma unroll
+            for (int p = 1; p < PARTS; ++p)
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    if (s + t < N) acc[s + t] += red[(p * 8 + t) * 64 + lane];
+        }
+    }
+}
+
 // HC: highest height class of the scan's rows (0 .. 4); RG: groups of 128 rows per wave; CW: adjacent detector columns per wave;
 // GT: 0 flat or parallel, 1 cylindrical detector, 2 modular geometry with upright modules; NS: volumes per wave.
 // Cylinder: a candidate's fan angle is taken relative to the bundle's middle ray by a short polynomial.  With a double-precision atan2,
@@ -401,8 +442,8 @@ __device__ __forceinline__ void fp_store_four(float *__restrict__ dst, float a, 
 // 512^3, 720 views of 512^2 took 50.9 ms, now 46.5; 171 x 181 x 96, 323 views of 129 x 270 1.95, now 1.49 ms.
 // nq_log2: log2 of the candidate slots per slab (a power of two <= 64).  major[a * nbundles + b]: 1 if bundle b of view
 // a advances fastest along x (decided once, on the host, so that both agree on which slabs a bundle reads).
-template <int HC, int RG, int CW, int GT, int NS>
-__global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1) void sf_project_columns(SfGeom gk, const SfView *__restrict__ views,
+template <int HC, int RG, int CW, int GT, int NS, int PARTS>
+__global__ __launch_bounds__((PARTS > 1 ? PARTS : FP_WAVES) * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1) void sf_project_columns(SfGeom gk, const SfView *__restrict__ views,
                                                                     const float *__restrict__ volz, float *__restrict__ sino,
                                                                     const unsigned char *__restrict__ major, int nzp,
                                                                     size_t item_stride, int nq_log2, int col_tiles, int bands,
@@ -422,9 +463,9 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
     if (!fp_block(tb, vb, vgroups_pad, tiles_per_xcd_pad, col_tiles, gsz.nviews, bands, ct, band, a)) return;   // (no barrier follows)
-    const int bundle = ct * FP_WAVES + wave;
+    const int bundle = PARTS > 1 ? ct : ct * FP_WAVES + wave, part = PARTS > 1 ? wave : 0;
     const int c0 = bundle * CW;                          // first detector column of this wave
-    if (c0 >= gsz.ncols) return;
+    if (c0 >= gsz.ncols) return;                         // (waves that share a bundle return together)
     const int nbundles = (gsz.ncols + CW - 1) / CW;
     const SfSlab slab = sf_slab_for(all, __builtin_amdgcn_readfirstlane((int)major[(size_t)a * nbundles + bundle]), gsz.nx, gsz.ny);
     if ((int)major[(size_t)a * nbundles + bundle] != slab.xmajor) return;   // this bundle reads the other kind of slab
@@ -463,10 +504,12 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
     // ALU (a v_readlane costs as much issue time as two and a half FMAs, and issue is what binds beside the lane loads).
     // Only what must sit in scalar registers still comes by v_readlane: the column's offset (buffer descriptor) and mu
     // (scalar operand of the placement FMAs).
-    __shared__ float4 recs[FP_WAVES][64][2];
+    __shared__ float4 recs[PARTS > 1 ? PARTS : FP_WAVES][64][2];
     float4 (*rec)[2] = recs[wave];
 
-    for (int nb = slab.n0; nb < slab.n1; nb += sb_slabs) {
+    int nb_first = slab.n0, nb_end = slab.n1;
+    if constexpr (PARTS > 1) fp_part_of(slab, sb_slabs, part, PARTS, nb_first, nb_end);
+    for (int nb = nb_first; nb < nb_end; nb += sb_slabs) {
         // ---- lane-parallel: one candidate voxel column per lane
         const int n = nb + nrel;
         int qf, ql;
@@ -570,6 +613,11 @@ __global__ __launch_bounds__(FP_WAVES * 64, GT == 1 ? (RG * NS <= 2 ? 4 : 3) : 1
         if constexpr (HC > 1) walk_up_to(std::integral_constant<int, 2>{});
         if constexpr (HC > 2) walk_up_to(std::integral_constant<int, 3>{});
         if constexpr (HC > 3) walk_up_to(std::integral_constant<int, 4>{});
+    }
+
+    if constexpr (PARTS > 1) {
+        fp_sum_parts<NS * CW * RG * 2, PARTS>(&acc[0][0][0][0], &recs[0][0][0].x, part, lane);
+        if (part > 0) return;
     }
 
     // ---- amplitude and store: CW consecutive floats per lane and row, written together (storing the columns of a

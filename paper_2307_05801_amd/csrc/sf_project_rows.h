@@ -74,8 +74,8 @@ static __global__ __launch_bounds__(256) void sf_volume_to_rows(SfGeom g, const 
 }
 
 // RV: adjacent rows per lane and group (1, 2, 4); RG: groups of 64 RV rows per wave; CW: detector columns per wave.
-template <int RV, int RG, int CW>
-__global__ __launch_bounds__(FP_WAVES * 64) void sf_project_rows(SfGeom g, const SfView *__restrict__ views, const float *__restrict__ rows,
+template <int RV, int RG, int CW, int PARTS>
+__global__ __launch_bounds__((PARTS > 1 ? PARTS : FP_WAVES) * 64) void sf_project_rows(SfGeom g, const SfView *__restrict__ views, const float *__restrict__ rows,
                                                                  float *__restrict__ sino, const unsigned char *__restrict__ major, int nzp,
                                                                  size_t item_stride, int nq_log2, int col_tiles, int bands, int vb, int tb,
                                                                  int vgroups_pad, int tiles_per_xcd_pad, SfSlab all)
@@ -86,8 +86,8 @@ __global__ __launch_bounds__(FP_WAVES * 64) void sf_project_rows(SfGeom g, const
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
     if (!fp_block(tb, vb, vgroups_pad, tiles_per_xcd_pad, col_tiles, g.nviews, bands, ct, band, a)) return;      // (no barrier follows)
-    const int bundle = ct * FP_WAVES + wave, c0 = bundle * CW;
-    if (c0 >= g.ncols) return;
+    const int bundle = PARTS > 1 ? ct : ct * FP_WAVES + wave, part = PARTS > 1 ? wave : 0, c0 = bundle * CW;
+    if (c0 >= g.ncols) return;                                               // (waves that share a bundle return together)
     const int nbundles = (g.ncols + CW - 1) / CW;
     const int own = __builtin_amdgcn_readfirstlane((int)major[(size_t)a * nbundles + bundle]);
     const SfSlab slab = sf_slab_for(all, own, g.nx, g.ny);
@@ -107,10 +107,12 @@ __global__ __launch_bounds__(FP_WAVES * 64) void sf_project_rows(SfGeom g, const
     const int slot = lane & ((1 << nq_log2) - 1), nrel = lane >> nq_log2, sb_slabs = 64 >> nq_log2;
     const unsigned row_bytes = (unsigned)g.nrows * 4u;                       // rows beyond the detector read as zero
     const int off0 = (band0 + RV * lane) * 4;
-    __shared__ float4 recs[FP_WAVES][64];
+    __shared__ float4 recs[PARTS > 1 ? PARTS : FP_WAVES][PARTS > 1 ? 128 : 64];      // (the parts' sums take twice the records' room)
     float4 *rec = recs[wave];
 
-    for (int nb = slab.n0; nb < slab.n1; nb += sb_slabs) {
+    int nb_first = slab.n0, nb_end = slab.n1;
+    if constexpr (PARTS > 1) fp_part_of(slab, sb_slabs, part, PARTS, nb_first, nb_end);
+    for (int nb = nb_first; nb < nb_end; nb += sb_slabs) {
         // ---- lane-parallel: one candidate voxel column per lane
         const int n = nb + nrel;
         int qf, ql;
@@ -170,6 +172,11 @@ __global__ __launch_bounds__(FP_WAVES * 64) void sf_project_rows(SfGeom g, const
                 }
             }
         }
+    }
+
+    if constexpr (PARTS > 1) {
+        fp_sum_parts<CW * RG * RV, PARTS>(&acc[0][0][0], &recs[0][0].x, part, lane);
+        if (part > 0) return;
     }
 
     // ---- amplitude and store: CW consecutive floats per row, written together

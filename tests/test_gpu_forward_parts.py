@@ -1,0 +1,79 @@
+"""Forward projection of few bundles, whose layers the waves of a workgroup share, and of short detectors on the column-wise kernels.
+
+Layers shared by fewer blocks than waves, whole and slab by slab, against the oracle; a batch bit for bit what its items give alone;
+scans of under 32 rows captured in a graph, and on the fixed scratch array, as from the general kernels that they ran on before."""
+import pytest
+
+from synthetic import CTConfig, perturbed_poses, uniform_volume
+from synthetic.configs import CONE, CONE_CURVED, PARALLEL
+from tests.test_gpu_parity import TOL, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def scan(geom, nrows, nviews=6, **kw):
+    par = dict(sod=0.0, sdd=0.0) if geom == PARALLEL else dict(sod=150.0, sdd=225.0)
+    base = dict(nviews=nviews, arc_deg=360.0, nrows=nrows, ncols=43, pixel_v=1.5, pixel_u=1.6, nx=41, ny=37, nz=max(8, nrows), voxel_xy=1.0,
+                voxel_z=1.0, start_deg=3.0, shift_u=0.3, shift_v=-0.2)
+    return CTConfig("parts", geom, **{**base, **par, **kw})
+
+
+CASES = {"cone": (scan(CONE, 33), "sf"), "cone_8_rows": (scan(CONE, 8), "sf"), "cone_one_block": (scan(CONE, 40, nx=5, ny=7), "sf"),
+         "cone_300_rows": (scan(CONE, 300, nviews=2), "sf"), "cone_520_rows": (scan(CONE, 520, nviews=2, nx=12, ny=13), "sf"),
+         "curved": (scan(CONE_CURVED, 31), "sf"), "curved_200_rows": (scan(CONE_CURVED, 200, nviews=2), "sf"),
+         "upright": (perturbed_poses(scan(CONE, 21), 5, shift_mm=4.0, upright=True), "sf"),
+         "parallel": (scan(PARALLEL, 9), "sf"), "parallel_two_waves": (scan(PARALLEL, 70, nviews=160), "sf"),
+         "parallel_500_rows": (scan(PARALLEL, 500, nviews=3), "sf"),
+         "siddon_16_rows": (scan(CONE, 16), "siddon"), "siddon_parallel_22_rows": (scan(PARALLEL, 22), "siddon")}
+
+
+@pytest.mark.parametrize("slab", ["", "slab=8"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_shared_layers_and_short_detectors(oracle_mod, monkeypatch, name, slab):
+    import torch
+    from paper_2307_05801_amd import Geometry
+    cfg, model = CASES[name]
+    if slab:
+        monkeypatch.setenv("LEAP_DEBUG", slab)
+    geo = Geometry(cfg, model=model)
+    print(f"[gpu] {name} {slab}: {geo.describe()}", flush=True)
+    assert "A=columns" in geo.describe() and ("parts=" in geo.describe()) == (model == "sf"), geo.describe()
+    assert ("parts=2" in geo.describe()) == (name == "parallel_two_waves"), geo.describe()
+    x = uniform_volume(cfg, 5, batch=3)
+    xt = torch.from_numpy(x).cuda()
+    y = geo.project(xt)
+    ref = (oracle_mod if model == "sf" else oracle_mod.siddon).project(cfg, x[1])
+    assert rel_l2(y[1].cpu().numpy(), ref) <= TOL          # float sums of products whose positions are double: the parity tests' tolerance
+    for b in range(3):
+        assert torch.equal(y[b], geo.project(xt[b].contiguous())), b
+    geo.close()
+
+
+@pytest.mark.parametrize("name", ["cone_8_rows", "curved", "upright", "parallel", "siddon_16_rows"])
+def test_short_detectors_captured_and_on_the_fixed_array(monkeypatch, name):
+    """Neither needs a scratch, whatever stream the handle was last used on: the general kernel's results, bit for bit."""
+    import torch
+    from paper_2307_05801_amd import Geometry, binding
+    cfg, model = CASES[name]
+    geo = Geometry(cfg, model=model)
+    monkeypatch.setenv("LEAP_DEBUG", "general=1")
+    plain = Geometry(cfg, model=model)
+    x = torch.rand((2,) + geo.vol_shape, device="cuda")
+    want, eager = plain.project(x), geo.project(x)
+    assert rel_l2(eager.cpu().numpy(), want.cpu().numpy()) <= 1e-6        # the same sums in another order, TOL's tenth
+    out = torch.empty_like(want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        geo.project(x, out)
+    for _ in range(3):
+        x.copy_(torch.rand_like(x))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, plain.project(x))
+        out.zero_()
+    binding.leap_project_static_scratch(geo.handle, x.data_ptr(), out.data_ptr(), 2, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(out, plain.project(x))
+    plain.close()
+    geo.close()
