@@ -1,6 +1,7 @@
 // HIP kernels (gfx950) and launchers of the projector pairs (separable footprint and Siddon).
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdio>
 #include <mutex>
 
@@ -552,6 +553,37 @@ static int backproject_flat(const leap_geometry *G, const float *d_sino, float *
     return LEAP_OK;
 }
 
+// Voxels per thread and groups of threads that share the views, for the tilted footprints' tiled back projection: the shape of least
+// estimated time.  A step from one view to the next takes a compute unit `alone` us with one workgroup of 256 threads on it and `full` with
+// four, or with one of 1024; the least of those shapes supplies every unit.  60 views' worth per shape (8, 4, 1 voxels; four groups 4, 2, 1), us per
+// view: 48^2 x 38 voxels 6.4, 3.9, 2.4; 2.0, 1.3, 1.8; 64^2 x 51 6.4, 3.9, 3.5; 2.0, 2.5, 3.5; 96^2 x 76 8.4, 6.3, 8.4; 5.7, 7.0, 9.5; 128^2 x 102 12.1,
+// 12.6, 18.7; 13.2, 15.7, 22.8.
+static int mf_back_choice(double tiles, int nz, int views)
+{
+    static const struct {
+        int zc, groups;
+        double alone, full;
+    } shapes[] = {{8, 1, 5.3, 12.0}, {4, 1, 3.4, 7.1}, {1, 1, 1.9, 3.4}, {4, 4, 0.0, 7.1}, {2, 4, 0.0, 4.7}, {1, 4, 0.0, 3.4}};
+    int best = 0;
+    double least = 1e300;
+    for (int n = 0; n < 6; ++n) {
+        const auto &s = shapes[n];
+        const double per_unit = tiles * std::ceil((double)nz / s.zc) / 256.0;
+        double time;
+        if (s.groups > 1) {
+            time = std::ceil(per_unit) * std::ceil((double)views / s.groups) * s.full;
+        } else {
+            const double rounds = std::floor(per_unit / 4.0), left = std::ceil(per_unit - 4.0 * rounds);
+            time = views * (rounds * s.full + (left > 0.0 ? s.alone + (s.full - s.alone) * (left - 1.0) / 3.0 : 0.0));
+        }
+        if (time < 0.94 * least) {
+            least = time;
+            best = n;
+        }
+    }
+    return best;
+}
+
 // One volume on the kernels that read it as it lies: the flat ones, the tiled footprints', the general ones.
 static int launch_project_direct(const leap_geometry *G, const float *d_vol, float *d_sino, hipStream_t stream)
 {
@@ -559,8 +591,15 @@ static int launch_project_direct(const leap_geometry *G, const float *d_vol, flo
     if (g.model == SF_MODEL_SIDDON) return launch_sd_project(G, d_vol, d_sino, stream);
     if (G->flat) return project_flat(G, d_vol, d_sino, 1, stream, false);
     if (G->mf_tiles) {
-        dim3 grid(cdiv(cdiv(g.ncols, MF_TC), 4), cdiv(g.nrows, MF_TR), g.nviews);
-        hipLaunchKernelGGL(mf_project_tiles, grid, dim3(256), 0, stream, g, G->d_mfviews, d_vol, d_sino);
+        // Waves per tile: as many as it takes to supply the chip; four also where there are tiles in plenty (a tile's time is that of its
+        // beams' layers, which differ from tile to tile).  us, one / four / eight waves per tile, by tiles: 80 137 / 39 / 30; 200 940 / 241 /
+        // 174; 480 1965 / 517 / 523; 560 1023 / 270 / 234; 1200 1226 / 568 / 566; 3360 1269 / 738 / 842; 11520 13991 / 11187 / 13789.
+        const unsigned tiles = cdiv(g.ncols, MF_TC), bands = cdiv(g.nrows, MF_TR);
+        auto go = [&](auto kernel, unsigned waves) {
+            hipLaunchKernelGGL(kernel, dim3(tiles | 1u, bands, g.nviews), dim3(64 * waves), 0, stream, g, G->d_mfviews, d_vol, d_sino);
+        };
+        if ((double)tiles * bands * g.nviews <= 400.0) go(mf_project_tiles<8>, 8);
+        else go(mf_project_tiles<4>, 4);
         LEAP_HIP_CHECK(hipGetLastError());
         return LEAP_OK;
     }
@@ -653,16 +692,17 @@ int leap_launch_backproject(const leap_geometry *G, const float *d_sino, float *
     if (G->bp_tiled) return leap_launch_footprint_back(G, d_sino, d_vol, 1, stream);
     if (G->mf_tiled) {
         const unsigned tiles_x = cdiv(g.nx, MF_T), tiles_y = cdiv(g.ny, MF_T);
-        auto go = [&](auto kernel, int zc) {
-            hipLaunchKernelGGL(kernel, dim3(tiles_x * tiles_y, cdiv(g.nz, zc)), dim3(256), 0, stream, g, G->d_mfviews, d_sino, d_vol, (int)tiles_x);
+        auto go = [&](auto kernel, int zc, int groups) {
+            hipLaunchKernelGGL(kernel, dim3(tiles_x * tiles_y, cdiv(g.nz, zc)), dim3(256 * groups), 0, stream, g, G->d_mfviews, d_sino, d_vol, (int)tiles_x);
         };
-        // Voxels per thread: the most that leave the chip's 256 compute units a workgroup each.  A workgroup takes 4.4 us a view for
-        // eight voxels per thread, 1.5 for one, whatever the others do.  60 views, 8 / 2 / 1 voxels: 112^2 x 64 (392 workgroups
-        // of eight) 376 / 412 us, 96^2 x 48 (216) 278 / 254, 48^3 (270 of two) 280 / 134 / 126, 32^3 (64 of two) 278 / 132 / 111.
-        const unsigned tiles = tiles_x * tiles_y;
-        if (tiles * cdiv(g.nz, MF_ZC) >= 320) go(mf_backproject_tiled<MF_ZC>, MF_ZC);
-        else if (tiles * cdiv(g.nz, MF_ZC_SMALL) >= 320) go(mf_backproject_tiled<MF_ZC_SMALL>, MF_ZC_SMALL);
-        else go(mf_backproject_tiled<1>, 1);
+        switch (mf_back_choice((double)tiles_x * tiles_y, g.nz, g.nviews)) {
+        case 0: go(mf_backproject_tiled<8, 1>, 8, 1); break;
+        case 1: go(mf_backproject_tiled<4, 1>, 4, 1); break;
+        case 2: go(mf_backproject_tiled<1, 1>, 1, 1); break;
+        case 3: go(mf_backproject_tiled<4, 4>, 4, 4); break;
+        case 4: go(mf_backproject_tiled<2, 4>, 2, 4); break;
+        default: go(mf_backproject_tiled<1, 4>, 1, 4); break;
+        }
         LEAP_HIP_CHECK(hipGetLastError());
         return LEAP_OK;
     }

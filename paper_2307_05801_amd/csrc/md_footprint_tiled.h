@@ -16,16 +16,18 @@
 // Forward (mf_project_tiles): a wave owns a tile of MF_TC x MF_TR detector pixels whose sums live in LDS, walks the voxel layers
 // its beams cross, and adds every voxel's few shares with the LDS's double-precision add.  The 64 lanes take voxels spread
 // over the layer's box (16 positions along z times 4 across), so that they rarely meet in a pixel.  A tile belongs to one
-// wave, whose LDS operations execute in order: the sums do not depend on scheduling.
+// workgroup, whose waves share the layers and keep sums of their own; a wave's LDS operations execute in order, so the sums do not depend
+// on scheduling.
 //
 // Measured at 128^3 x 720 views x 128^2 against one thread per voxel / per eight rows of a column (md_footprint.h): A 60.4 ->
-// 13.0 ms, A^T 22.0 -> 7.4 ms, the same bits but for the last.  (Forward tiles of 32 x 32 pixels, with 16 x 4 or 8 x 8 lanes: 15.7 and
+// 13.0 ms, A^T 22.0 -> 7.4 ms, the same bits but for the last; A 11.2 ms since a tile's layers are shared by four waves, and 16 drawn scans of 28^2
+// x 14 to 128^3 voxels 0.37 (A) and 0.67 (A^T) of what one wave per tile and views one after the other took.  (Forward tiles of 32 x 32 pixels, with 16 x 4 or 8 x 8 lanes: 15.7 and
 // 15.0 ms; fewer than six voxels per lane along z pay too often for starting a column.)
 #pragma once
 
 #include "md_footprint.h"
 
-constexpr int MF_T = 16, MF_ZC = 8, MF_ZC_SMALL = 2;      // back projection: tile edge, voxels per thread (small volumes: fewer)
+constexpr int MF_T = 16, MF_ZC = 8;              // back projection: tile edge, most voxels per thread
 constexpr int MF_PATCH = 2048;                   // doubles per staged window
 constexpr int MF_TC = 16, MF_TR = 64;            // forward: detector tile of a wave, columns x rows
 constexpr int MF_TG = 2;                         // guard columns and rows around it, which take what falls beside the tile
@@ -204,12 +206,13 @@ __device__ __forceinline__ MfWindow mf_wave_window(const SfGeom &g, const MfView
     return w;
 }
 
-template <int ZC>
-__global__ __launch_bounds__(256, 4) void mf_backproject_tiled(SfGeom g, const MfView *__restrict__ views, const float *__restrict__ sino,
-                                                            float *__restrict__ vol, int tiles_x)
+template <int ZC, int VS>
+__global__ __launch_bounds__(256 * VS, VS == 1 ? 4 : 1) void mf_backproject_tiled(SfGeom g, const MfView *__restrict__ views, const float *__restrict__ sino,
+                                                                     float *__restrict__ vol, int tiles_x)
 {
-    __shared__ double patch[2][MF_PATCH];
-    const int tid = threadIdx.x, lane = tid & 63;
+    __shared__ double patches[VS][2][MF_PATCH];
+    const int tid = threadIdx.x & 255, lane = tid & 63, group = VS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    double (*patch)[MF_PATCH] = patches[group];
     const int ty = blockIdx.x / tiles_x, tx = blockIdx.x - ty * tiles_x;
     const int i0 = tx * MF_T, j0 = ty * MF_T, k0 = blockIdx.y * ZC;
     const int i1 = i0 + MF_T < g.nx ? i0 + MF_T - 1 : g.nx - 1, j1 = j0 + MF_T < g.ny ? j0 + MF_T - 1 : g.ny - 1;
@@ -241,8 +244,9 @@ __global__ __launch_bounds__(256, 4) void mf_backproject_tiled(SfGeom g, const M
             }
         }
     };
-    __shared__ int odd[2][4];                  // per wave: it staged an infinity or a NaN
-    auto store = [&](int a, const MfWindow &w, double *__restrict__ buf) {
+    __shared__ int odd_waves[VS][2][4];        // per wave: it staged an infinity or a NaN
+    int (*odd)[4] = odd_waves[group];
+    auto store = [&](int a, int slot, const MfWindow &w, double *__restrict__ buf) {
         bool bad = false;
 #pragma unroll
         for (int s = 0; s < NSTAGE; ++s) {
@@ -255,18 +259,21 @@ __global__ __launch_bounds__(256, 4) void mf_backproject_tiled(SfGeom g, const M
             }
         }
         const int any = __builtin_amdgcn_ballot_w64(bad) != 0;
-        if (lane == 0) odd[a & 1][tid >> 6] = any;
+        if (lane == 0) odd[slot][tid >> 6] = any;
     };
-    fetch(0, win);
-    store(0, win, patch[0]);
+    // group v takes views v, v + VS, ...; every group makes as many steps
+    if (group < g.nviews) {
+        fetch(group, win);
+        store(group, 0, win, patch[0]);
+    }
     __syncthreads();
-    for (int a = 0; a < g.nviews; ++a) {
-        const double *__restrict__ buf = patch[a & 1];
-        if (a + 1 < g.nviews) fetch(a + 1, next);                 // loads in flight during the gather
-        const MfView &V = views[a];
+    for (int a = group, step = 0; a - group < g.nviews; a += VS, step ^= 1) {
+        const double *__restrict__ buf = patch[step];
+        if (a + VS < g.nviews) fetch(a + VS, next);               // loads in flight during the gather
+        const MfView &V = views[a < g.nviews ? a : 0];
         MfWalk at = mf_walk(g, V, mf_column(g, V, ic, jc), k0);
-        const bool seen = sees(win);                              // uniform: a box beside the detector takes nothing from this view
-        const bool finite = !(odd[a & 1][0] | odd[a & 1][1] | odd[a & 1][2] | odd[a & 1][3]);        // uniform
+        const bool seen = a < g.nviews && sees(win);              // uniform: a box beside the detector takes nothing from this view
+        const bool finite = !(odd[step][0] | odd[step][1] | odd[step][2] | odd[step][3]);        // uniform
 #pragma unroll
         for (int kk = 0; kk < ZC; ++kk) {
             if (!seen || k0 + kk >= g.nz) break;                  // uniform
@@ -304,9 +311,21 @@ __global__ __launch_bounds__(256, 4) void mf_backproject_tiled(SfGeom g, const M
                 }
             }
         }
-        if (a + 1 < g.nviews) store(a + 1, next, patch[(a + 1) & 1]);
+        if (a + VS < g.nviews) store(a + VS, step ^ 1, next, patch[step ^ 1]);
         win = next;
         __syncthreads();
+    }
+    if constexpr (VS > 1) {                                       // the groups' sums, added in the order of the groups
+        static_assert(ZC * 256 <= MF_PATCH, "a group's sums fit its patch");
+        if (group > 0) {
+#pragma unroll
+            for (int kk = 0; kk < ZC; ++kk) patch[0][kk * 256 + tid] = acc[kk];
+        }
+        __syncthreads();
+        if (group > 0) return;
+        for (int v = 1; v < VS; ++v)
+#pragma unroll
+            for (int kk = 0; kk < ZC; ++kk) acc[kk] += patches[v][0][kk * 256 + tid];
     }
     if (i < g.nx && j < g.ny) {
 #pragma unroll
@@ -323,7 +342,7 @@ __device__ __forceinline__ void mf_add(double *cell, double v)
 // Adds the shares of all voxels that the tile's beams can meet, layer by layer along in-plane axis `m`.
 template <int m>
 __device__ __forceinline__ void mf_tile_along(const SfGeom &g, const MfView &V, const float *__restrict__ vol, int c0, int c1, int r0, int r1,
-                                              int lane, double *__restrict__ sums)
+                                              int lane, int first_layer, int layer_step, double *__restrict__ sums)
 {
     // corner rays of the tile's rectangle, widened by how far a footprint can reach: a pyramid from the source whose section
     // with a layer holds the centres of all voxels that can touch the tile
@@ -345,7 +364,7 @@ __device__ __forceinline__ void mf_tile_along(const SfGeom &g, const MfView &V, 
         tz[e] = fma(u, V.eu[2], fma(v, V.ev[2], V.C[2] - V.S[2])) * im[e];
     }
     const int kz = lane & 15, qz = lane >> 4;
-    for (int layer = 0; layer < n_layers; ++layer) {
+    for (int layer = first_layer; layer < n_layers; layer += layer_step) {
         int qlo = 0, qhi = n_p - 1, klo = 0, khi = g.nz - 1;
         if (narrow) {
             const double s = fma((double)layer, g.Td, first[m]) - V.S[m];
@@ -425,32 +444,38 @@ __device__ __forceinline__ void mf_tile_along(const SfGeom &g, const MfView &V, 
     }
 }
 
-// grid: x = groups of 4 column tiles, y = bands of MF_TR rows, z = views; block: 4 waves, a tile each.
-__global__ __launch_bounds__(256) void mf_project_tiles(SfGeom g, const MfView *__restrict__ views, const float *__restrict__ vol,
-                                                        float *__restrict__ sino)
+// grid: x = column tiles, one more where their number is even: workgroups go to the 8 XCDs by index in turn, and a tile at the detector's
+// edge is a fraction of one in its middle, so that on a detector of eight tiles most XCDs waited for two (112^2 x 89 voxels, 720 views of 78
+// x 125: 12.7 ms, 5.9 with a ninth in the grid; 128^3, 128 x 128: 14.6, now 11.2); y = bands of MF_TR rows, z = views; block: LS waves, which share the tile: each takes every LS-th layer and keeps
+// sums of its own, which are added in the order of the waves.
+template <int LS>
+__global__ __launch_bounds__(64 * LS) void mf_project_tiles(SfGeom g, const MfView *__restrict__ views, const float *__restrict__ vol,
+                                                            float *__restrict__ sino)
 {
-    __shared__ double tile_sums[4][(MF_TR + 2 * MF_TG) * MF_TS];
+    constexpr int CELLS = (MF_TR + 2 * MF_TG) * MF_TS;
+    __shared__ double tile_sums[LS][CELLS];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double *__restrict__ sums = tile_sums[wave];
-    const int c0 = (blockIdx.x * 4 + wave) * MF_TC, r0 = blockIdx.y * MF_TR, a = blockIdx.z;
-    if (c0 >= g.ncols) return;                                // (no barrier: a tile belongs to its wave)
+    const int c0 = blockIdx.x * MF_TC, r0 = blockIdx.y * MF_TR, a = blockIdx.z;
+    if (c0 >= g.ncols) return;                                // (a workgroup of the grid's padding, as a whole)
     const int c1 = (c0 + MF_TC < g.ncols ? c0 + MF_TC : g.ncols) - 1, r1 = (r0 + MF_TR < g.nrows ? r0 + MF_TR : g.nrows) - 1;
-    for (int e = lane; e < (MF_TR + 2 * MF_TG) * MF_TS; e += 64) sums[e] = 0.0;
+    for (int e = lane; e < CELLS; e += 64) sums[e] = 0.0;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const MfView &V = views[a];
     const double uc = (0.5 * (c0 + c1) - g.col_offd) * g.pu_d, vc = fma(0.5 * (r0 + r1), g.pvd, g.v0d);
     const double dx = fma(uc, V.eu[0], fma(vc, V.ev[0], V.C[0] - V.S[0])), dy = fma(uc, V.eu[1], fma(vc, V.ev[1], V.C[1] - V.S[1]));
-    if (__builtin_amdgcn_readfirstlane((int)(fabs(dx) >= fabs(dy)))) mf_tile_along<0>(g, V, vol, c0, c1, r0, r1, lane, sums);
-    else mf_tile_along<1>(g, V, vol, c0, c1, r0, r1, lane, sums);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int e = lane; e < MF_TR * MF_TC; e += 64) {
-        const int r = r0 + e / MF_TC, c = c0 + e % MF_TC;
-        if (r <= r1 && c <= c1)
-            sino[((size_t)a * g.nrows + r) * g.ncols + c] = (float)(sums[(e / MF_TC + MF_TG) * MF_TS + e % MF_TC + MF_TG] * mf_amp(g, V, r, c));
+    if (__builtin_amdgcn_readfirstlane((int)(fabs(dx) >= fabs(dy)))) mf_tile_along<0>(g, V, vol, c0, c1, r0, r1, lane, wave, LS, sums);
+    else mf_tile_along<1>(g, V, vol, c0, c1, r0, r1, lane, wave, LS, sums);
+    __syncthreads();
+    for (int e = threadIdx.x; e < MF_TR * MF_TC; e += 64 * LS) {
+        const int r = r0 + e / MF_TC, c = c0 + e % MF_TC, at = (e / MF_TC + MF_TG) * MF_TS + e % MF_TC + MF_TG;
+        if (r > r1 || c > c1) continue;
+        double sum = tile_sums[0][at];
+#pragma unroll
+        for (int w = 1; w < LS; ++w) sum += tile_sums[w][at];
+        sino[((size_t)a * g.nrows + r) * g.ncols + c] = (float)(sum * mf_amp(g, V, r, c));
     }
 }
 

@@ -66,3 +66,13 @@ def test_a_weight_of_zero_spreads_nothing():
     assert torch.equal(~axb.isfinite(), hit_rays) and torch.allclose(axb[~hit_rays], ax[~hit_rays], rtol=1e-6)
     assert torch.equal(atyb.isnan(), hit_voxels) and torch.allclose(atyb[~hit_voxels], aty[~hit_voxels], rtol=1e-6)
     geo.close()
+
+
+# 1, 2 and 4 voxels per thread with the views shared by four groups of threads; 1, 4 and 8 with none; four waves per detector tile (780 tiles)
+SHAPES = [scan(20, 24, 10, 30, 40, nviews=9), scan(47, 48, 38, 50, 70, nviews=10), scan(64, 62, 51, 60, 70, nviews=7), scan(20, 24, 10, 31, 40, nviews=1),
+          scan(96, 90, 76, 64, 100, nviews=2), scan(128, 126, 102, 70, 120, nviews=2), scan(20, 24, 10, 60, 200, nviews=60)]
+
+
+@pytest.mark.parametrize("cfg", SHAPES, ids=lambda c: f"{c.name}_{c.nviews}")
+def test_views_and_layers_shared(oracle_mod, cfg):
+    test_tiled_kernels_match_oracle(oracle_mod, cfg)
