@@ -1082,6 +1082,7 @@ static void allocate_forward_scratch(leap_geometry *G)
     const leap_geometry_desc *d = &G->desc;
     if (!G->fp_columns && !G->sd_columns) return;
     G->nzp = (G->fp_rows ? (d->nrows + 3) / 4 * 4 : d->nz) + 2 * FP_PAD;      // floats per voxel column of the copy
+    if (4.0 * d->nx * d->ny * (double)G->nzp <= FP_TURN_BYTES) G->fp_turn = 3;
     const double volume_bytes = 4.0 * d->nx * d->ny * (double)d->nz;
     const double share = volume_bytes / (d->model == LEAP_MODEL_SIDDON ? 4.0 : 8.0);
     double budget = volume_bytes / 8.0 >= 64.0 * 1048576.0 ? share : 128.0 * 1048576.0;

@@ -48,6 +48,7 @@ struct leap_geometry {
     int fp_nkp = 0;                     // voxels a pair of adjacent detector rows can overlap
     int fp_rg = 0;                      // row groups per wave (footprints: groups of 128 rows; Siddon: of 64)
     int fp_cw = 4, fp_vb = 128, fp_tb = 1;   // detector columns per wave; block order: views per run, tiles per chunk
+    int fp_turn = 31;                   // ... and log2 of the views after which tiles change XCD (31: never)
     int fp_parts = 1;                   // waves of a workgroup that share a bundle's layers (1: none, each has a bundle of its own)
     bool fp_columns = false;
     int fp_pair_rg = 0;                 // row groups per wave with two volumes per wave (0: one volume per wave only)

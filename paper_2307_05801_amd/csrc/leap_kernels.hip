@@ -188,15 +188,15 @@ static void launch_sd_columns(const leap_geometry *G, const FwdScratch &S, const
     if (G->md_tilted) {
         if constexpr (RG <= 4)        // (the selection offers the per-lane kernel 1, 2 or 4 row groups)
             hipLaunchKernelGGL((md_project_columns<RG, SD_WAVES>), grid, dim3(SD_WAVES * 64, 1, 1), 0, stream, g,
-                               (const MdPose *)G->d_poses, S.volz, d_sino, G->nzp, S.item_floats, zero_col, col_tiles, bands, vb, tb,
+                               (const MdPose *)G->d_poses, S.volz, d_sino, G->nzp, S.item_floats, zero_col, col_tiles, bands, vb, tb, G->fp_turn,
                                views_pad, tiles_per_xcd_pad, slab);
     } else if (g.type == SF_MODULAR)
         hipLaunchKernelGGL((sd_project_columns<RG, SD_WAVES, true>), grid, dim3(SD_WAVES * 64, 1, 1), 0, stream, g, G->d_raycols,
-                           S.volz, d_sino, G->nzp, S.item_floats, zero_col, col_tiles, bands, vb, tb, views_pad, tiles_per_xcd_pad,
+                           S.volz, d_sino, G->nzp, S.item_floats, zero_col, col_tiles, bands, vb, tb, G->fp_turn, views_pad, tiles_per_xcd_pad,
                            slab, (const SfGeom *)G->d_geoms);
     else
         hipLaunchKernelGGL((sd_project_columns<RG, SD_WAVES, false>), grid, dim3(SD_WAVES * 64, 1, 1), 0, stream, g, G->d_raycols,
-                           S.volz, d_sino, G->nzp, S.item_floats, zero_col, col_tiles, bands, vb, tb, views_pad, tiles_per_xcd_pad,
+                           S.volz, d_sino, G->nzp, S.item_floats, zero_col, col_tiles, bands, vb, tb, G->fp_turn, views_pad, tiles_per_xcd_pad,
                            slab, (const SfGeom *)nullptr);
 }
 
@@ -212,7 +212,7 @@ static void launch_sd_pairs(const leap_geometry *G, const FwdScratch &S, const S
     dim3 grid((unsigned)(8 * tiles_per_xcd_pad * views_pad * bands), (unsigned)items, 1);
     auto go = [&](auto kernel, const SfGeom *geoms) {
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, g, G->d_raycols, S.volz, d_sino, G->nzp, S.item_floats, col_tiles, bands, vb,
-                           tb, views_pad, tiles_per_xcd_pad, slab, geoms);
+                           tb, G->fp_turn, views_pad, tiles_per_xcd_pad, slab, geoms);
     };
     if (g.type == SF_MODULAR) {
         if (G->sd_pairs == 2) go(sd_project_pairs<RG, true, true>, G->d_geoms);

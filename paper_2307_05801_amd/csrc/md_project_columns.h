@@ -117,7 +117,7 @@ template <int RG, int SD_WAVES>
 __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, const MdPose *__restrict__ poses,
                                                                     const float *__restrict__ volz, float *__restrict__ sino,
                                                                     int nzp, size_t item_stride, unsigned zero_col, int col_tiles,
-                                                                    int bands, int vb, int tb, int views_pad,
+                                                                    int bands, int vb, int tb, int turn, int views_pad,
                                                                     int tiles_per_xcd_pad, SfSlab all)
 {
     volz += (size_t)blockIdx.y * item_stride;
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(SD_WAVES * 64) void md_project_columns(SfGeom g, co
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
-    if (!fp_block(tb, vb, views_pad, tiles_per_xcd_pad, col_tiles, g.nviews, bands, ct, band, a)) return;
+    if (!fp_block(tb, vb, turn, views_pad, tiles_per_xcd_pad, col_tiles, g.nviews, bands, ct, band, a)) return;
     const int c = ct * SD_WAVES + wave;
     if (c >= g.ncols) return;
     const int band0 = band * (RG * 64);

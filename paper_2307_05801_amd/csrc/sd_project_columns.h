@@ -166,7 +166,7 @@ SF_HD float sd_pair_two(float alo, float aup, float blo, float bup, bool inc, fl
 template <int RG, bool SPREAD, bool MOD>
 __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCol *__restrict__ rays, const float *__restrict__ volz,
                                                         float *__restrict__ sino, int nzp, size_t item_stride, int col_tiles, int bands,
-                                                        int vb, int tb, int views_pad, int tiles_per_xcd_pad, SfSlab all,
+                                                        int vb, int tb, int turn, int views_pad, int tiles_per_xcd_pad, SfSlab all,
                                                         const SfGeom *__restrict__ geoms)
 {
     constexpr int WAVES = 4, ROWS = RG * 128;
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void sd_project_pairs(SfGeom gk, const SdRayCo
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
-    if (!fp_block(tb, vb, views_pad, tiles_per_xcd_pad, col_tiles, gk.nviews, bands, ct, band, a)) return;   // whole workgroups
+    if (!fp_block(tb, vb, turn, views_pad, tiles_per_xcd_pad, col_tiles, gk.nviews, bands, ct, band, a)) return;   // whole workgroups
     const int c = ct * WAVES + wave;
     const SfGeom &g = MOD ? geoms[a] : gk;
     const int band0 = band * ROWS;
@@ -307,7 +307,7 @@ template <int RG, int SD_WAVES, bool MOD>
 __global__ __launch_bounds__(SD_WAVES * 64) void sd_project_columns(SfGeom gk, const SdRayCol *__restrict__ rays,
                                                                     const float *__restrict__ volz, float *__restrict__ sino,
                                                                     int nzp, size_t item_stride, unsigned zero_col, int col_tiles,
-                                                                    int bands, int vb, int tb, int views_pad,
+                                                                    int bands, int vb, int tb, int turn, int views_pad,
                                                                     int tiles_per_xcd_pad, SfSlab all,
                                                                     const SfGeom *__restrict__ geoms)
 {
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(SD_WAVES * 64) void sd_project_columns(SfGeom gk, c
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
-    if (!fp_block(tb, vb, views_pad, tiles_per_xcd_pad, col_tiles, gk.nviews, bands, ct, band, a)) return;   // padding blocks (no barrier follows)
+    if (!fp_block(tb, vb, turn, views_pad, tiles_per_xcd_pad, col_tiles, gk.nviews, bands, ct, band, a)) return;   // padding blocks (no barrier follows)
     const int c = ct * SD_WAVES + wave;
     if (c >= gk.ncols) return;
     const SfGeom &g = MOD ? geoms[a] : gk;

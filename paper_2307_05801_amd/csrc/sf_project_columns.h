@@ -44,6 +44,9 @@ constexpr int FP_PARTS = 4;      // waves of a workgroup that share a bundle's l
 // Fewest detector rows: below, the general kernel's eight rows per thread waste less than the lanes of a wave (5 rows, 716 columns, 512^2 x 5
 // voxels: 60 views 3.5 ms against 1.9 here, 360 views 6.6 against 8.8; 8 rows, 720 views 17.1 against 16.8, 24 rows 58.8 against 17.5).
 constexpr int FP_MIN_ROWS = 8;
+// Largest copy of a volume whose tiles of columns change XCD every eight views (fp_block).  Forward projection with over without: copies of
+// 0.9 to 2.8 MB, 7 to 13 tiles 0.73 to 0.99, 6 to 8 MB, 18 and 19 tiles 1.03 to 1.08, 512^3 1.05 (every view 1.36).
+constexpr double FP_TURN_BYTES = 3145728.0;
 // Scans of fewer rows than this take the general kernels while a stream is being captured and on the fixed scratch array, so that such calls
 // need no scratch at all.
 constexpr int FP_FREE_ROWS = 32;
@@ -375,7 +378,10 @@ static __global__ __launch_bounds__(256) void sf_clear_column_pads(float *__rest
 // round-robin by index, and each XCD has its own L2, so the blocks one XCD runs at the same time are arranged as (a few column
 // tiles) x (a run of consecutive views), whose beams overlap almost entirely: index = 8 s + xcd, and within an XCD's sequence s
 // the view runs fastest inside a block of vb views, then tb tiles, then blocks of views.  Returns false for padding blocks.
-__device__ __forceinline__ bool fp_block(int tb, int vb, int views_pad, int tiles_per_xcd_pad, int col_tiles, int nviews, int bands, int &ct,
+// turn: every 2^turn views the tiles move on by one XCD.  A tile at the detector's edge takes a fraction of the time of one in its middle, and
+// with a dozen tiles an XCD has one or two of them for every view; but neighbouring views of a tile read the same voxels, which a copy
+// larger than an XCD's L2 then fetches again (the rule stands at FP_TURN_BYTES).
+__device__ __forceinline__ bool fp_block(int tb, int vb, int turn, int views_pad, int tiles_per_xcd_pad, int col_tiles, int nviews, int bands, int &ct,
                                          int &band, int &a)
 {
     const int xcd = blockIdx.x & 7, sq = blockIdx.x >> 3;
@@ -385,8 +391,8 @@ __device__ __forceinline__ bool fp_block(int tb, int vb, int views_pad, int tile
     const int tloc = r2 / vb, v_in = r2 - tloc * vb;
     const int tchunks = tiles_per_xcd_pad / tb;
     band = chunk / tchunks;
-    ct = ((chunk - band * tchunks) * tb + tloc) * 8 + xcd;
     a = vblk * vb + v_in;
+    ct = ((chunk - band * tchunks) * tb + tloc) * 8 + ((xcd + (a >> turn)) & 7);
     return ct < col_tiles && a < nviews && band < bands;
 }
 
@@ -447,7 +453,7 @@ __global__ __launch_bounds__((PARTS > 1 ? PARTS : FP_WAVES) * 64, GT == 1 ? (RG 
                                                                     const float *__restrict__ volz, float *__restrict__ sino,
                                                                     const unsigned char *__restrict__ major, int nzp,
                                                                     size_t item_stride, int nq_log2, int col_tiles, int bands,
-                                                                    int vb, int tb, int vgroups_pad, int tiles_per_xcd_pad,
+                                                                    int vb, int tb, int turn, int vgroups_pad, int tiles_per_xcd_pad,
                                                                     SfSlab all, const SfGeom *__restrict__ geoms)
 {
     // GT == 2 (modular geometry, upright modules): the wave's view brings its own parameter block, the scene
@@ -462,7 +468,7 @@ __global__ __launch_bounds__((PARTS > 1 ? PARTS : FP_WAVES) * 64, GT == 1 ? (RG 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
-    if (!fp_block(tb, vb, vgroups_pad, tiles_per_xcd_pad, col_tiles, gsz.nviews, bands, ct, band, a)) return;   // (no barrier follows)
+    if (!fp_block(tb, vb, turn, vgroups_pad, tiles_per_xcd_pad, col_tiles, gsz.nviews, bands, ct, band, a)) return;   // (no barrier follows)
     const int bundle = PARTS > 1 ? ct : ct * FP_WAVES + wave, part = PARTS > 1 ? wave : 0;
     const int c0 = bundle * CW;                          // first detector column of this wave
     if (c0 >= gsz.ncols) return;                         // (waves that share a bundle return together)

@@ -21,7 +21,7 @@ static void launch_fp_columns(const leap_geometry *G, const FwdScratch &S, const
     dim3 grid((unsigned)(8 * tiles_per_xcd_pad * vgroups_pad * bands), (unsigned)blocks, 1);
     hipLaunchKernelGGL((sf_project_columns<HC, RG, CW, GT, NS, PARTS>), grid, dim3((PARTS > 1 ? PARTS : FP_WAVES) * 64, 1, 1), 0, stream, g, G->d_views,
                        S.volz + (size_t)first * S.item_floats, d_sino + (size_t)first * g.nviews * g.nrows * g.ncols, G->d_major, G->nzp,
-                       S.item_floats, nq_log2, col_tiles, bands, vb, tb, vgroups_pad, tiles_per_xcd_pad, slab,
+                       S.item_floats, nq_log2, col_tiles, bands, vb, tb, G->fp_turn, vgroups_pad, tiles_per_xcd_pad, slab,
                        (const SfGeom *)G->d_geoms);
 }
 
@@ -85,7 +85,7 @@ static void launch_fp_rows(const leap_geometry *G, const FwdScratch &S, const Sf
     while ((1 << nq_log2) < G->fp_nq) ++nq_log2;
     dim3 grid((unsigned)(8 * tiles_per_xcd_pad * vgroups_pad * bands), (unsigned)items, 1);
     hipLaunchKernelGGL((sf_project_rows<RV, RG, CW, PARTS>), grid, dim3((PARTS > 1 ? PARTS : FP_WAVES) * 64, 1, 1), 0, stream, g, G->d_views, S.volz, d_sino, G->d_major,
-                       G->nzp, S.item_floats, nq_log2, col_tiles, bands, vb, tb, vgroups_pad, tiles_per_xcd_pad, slab);
+                       G->nzp, S.item_floats, nq_log2, col_tiles, bands, vb, tb, G->fp_turn, vgroups_pad, tiles_per_xcd_pad, slab);
 }
 
 template <int PARTS>

@@ -77,7 +77,7 @@ static __global__ __launch_bounds__(256) void sf_volume_to_rows(SfGeom g, const 
 template <int RV, int RG, int CW, int PARTS>
 __global__ __launch_bounds__((PARTS > 1 ? PARTS : FP_WAVES) * 64) void sf_project_rows(SfGeom g, const SfView *__restrict__ views, const float *__restrict__ rows,
                                                                  float *__restrict__ sino, const unsigned char *__restrict__ major, int nzp,
-                                                                 size_t item_stride, int nq_log2, int col_tiles, int bands, int vb, int tb,
+                                                                 size_t item_stride, int nq_log2, int col_tiles, int bands, int vb, int tb, int turn,
                                                                  int vgroups_pad, int tiles_per_xcd_pad, SfSlab all)
 {
     rows += (size_t)blockIdx.y * item_stride;
@@ -85,7 +85,7 @@ __global__ __launch_bounds__((PARTS > 1 ? PARTS : FP_WAVES) * 64) void sf_projec
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
-    if (!fp_block(tb, vb, vgroups_pad, tiles_per_xcd_pad, col_tiles, g.nviews, bands, ct, band, a)) return;      // (no barrier follows)
+    if (!fp_block(tb, vb, turn, vgroups_pad, tiles_per_xcd_pad, col_tiles, g.nviews, bands, ct, band, a)) return;      // (no barrier follows)
     const int bundle = PARTS > 1 ? ct : ct * FP_WAVES + wave, part = PARTS > 1 ? wave : 0, c0 = bundle * CW;
     if (c0 >= g.ncols) return;                                               // (waves that share a bundle return together)
     const int nbundles = (g.ncols + CW - 1) / CW;
