@@ -26,7 +26,7 @@
  *     volume through a z-fastest scratch copy, one SLAB of the volume at a time, so the handle
  *     owns a scratch of at most max(64 MiB, an eighth of one volume) -- leap_geometry_describe
  *     reports its size as "scratch=<bytes>"; small volumes share it between the items of a batch.
- *     Flat scans (one row, one layer) keep room for a copy of up to 16 slices (128 MiB at most)
+ *     Flat scans (one row, one layer) keep room for two copies of up to 16 slices (256 MiB at most)
  *     instead, which leap_project uses for batches outside stream capture; it is allocated with
  *     the handle, because a call may arrive while another stream is being captured.
  *     If it cannot be allocated the handle works without it on a slower kernel, says so in

@@ -1125,14 +1125,14 @@ static void allocate_forward_scratch(leap_geometry *G)
     G->slab_width = width;
 }
 
-// Flat scans: room for the batch-fastest copy of up to 16 slices, 128 MiB at most.  Without it every item of a batch is
+// Flat scans: room for the batch-fastest copies, by rows and turned, of up to 16 slices, 256 MiB at most.  Without it every item of a batch is
 // projected by itself.
 static void allocate_flat_scratch(leap_geometry *G)
 {
     const double slice = 4.0 * G->desc.nx * (double)G->desc.ny;
     double items = std::fmin(16.0, std::floor(128.0 * 1048576.0 / slice));
     if (!(items >= 2.0)) return;
-    G->scratch_bytes = (size_t)(items * slice);
+    G->scratch_bytes = (size_t)(2.0 * items * slice);
     hipError_t e = hipMalloc((void **)&G->d_volz, G->scratch_bytes);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&G->scratch_event, hipEventDisableTiming);
     if (e == hipSuccess) return;

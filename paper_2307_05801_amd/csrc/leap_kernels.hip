@@ -450,24 +450,37 @@ static int flat_waves(double tiles, int steps)
 }
 
 template <int NB>
-static void launch_project_flat(const leap_geometry *G, const float *src, float *d_sino, int items, hipStream_t stream)
+static void launch_project_flat(const leap_geometry *G, const float *src, const float *turned, float *d_sino, int items, hipStream_t stream)
 {
     const SfGeom &g = G->g;
     const int tiles = (int)cdiv(g.ncols, FLAT_RAYS);
     const unsigned groups = cdiv((unsigned)items, NB);
+    const bool parallel = g.type == SF_PARALLEL;
     int waves = flat_waves((double)tiles * g.nviews, g.nx < g.ny ? g.nx : g.ny);
     while ((size_t)waves * G->flat_span * sizeof(SfFlatRec) > 65536) waves /= 2;        // (spans of up to 256: at least 8 fit)
-    const size_t lds = (size_t)waves * G->flat_span * sizeof(SfFlatRec);
-    hipLaunchKernelGGL(sf_project_flat<NB>, dim3((unsigned)tiles * (unsigned)g.nviews, groups), dim3(64 * waves), lds, stream, g, G->d_views,
-                       src, d_sino, tiles, G->flat_span, items, G->flat_fv);
+    const size_t lds = (size_t)waves * (parallel ? 64 * NB * sizeof(float) : G->flat_span * sizeof(SfFlatRec));
+    const int odd_tiles = tiles | 1;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)odd_tiles * (unsigned)g.nviews, groups), dim3(64 * waves), lds, stream, g, G->d_views, src, turned,
+                           d_sino, odd_tiles, G->flat_span, items, G->flat_fv);
+    };
+    if (parallel) go(sf_project_flat<NB, true>);
+    else go(sf_project_flat<NB, false>);
 }
 
+// `items` slices by way of the handle's scratch: the copy by rows and, behind it, the turned one.
 template <int NB>
 static void launch_interleaved_flat(const leap_geometry *G, const float *d_vol, float *d_sino, int items, hipStream_t stream)
 {
-    const unsigned nvol = (unsigned)G->g.nx * (unsigned)G->g.ny;
-    hipLaunchKernelGGL(sf_interleave<NB>, dim3(cdiv(nvol, 256), cdiv((unsigned)items, NB)), dim3(256), 0, stream, d_vol, G->d_volz, nvol, items);
-    launch_project_flat<NB>(G, G->d_volz, d_sino, items, stream);
+    const SfGeom &g = G->g;
+    const unsigned nvol = (unsigned)g.nx * (unsigned)g.ny, groups = cdiv((unsigned)items, NB);
+    hipLaunchKernelGGL(sf_interleave<NB>, dim3(cdiv(nvol, 256), groups), dim3(256), 0, stream, d_vol, G->d_volz, nvol, items);
+    float *turned = nullptr;
+    if ((double)cdiv(g.ncols, FLAT_RAYS) * g.nviews * (g.nx < g.ny ? g.nx : g.ny) >= (g.type == SF_PARALLEL ? FLAT_TURN_STEPS_PARALLEL : FLAT_TURN_STEPS)) {
+        turned = G->d_volz + (size_t)groups * NB * nvol;
+        hipLaunchKernelGGL(sf_interleave_turned<NB>, dim3(cdiv(g.nx, 32), cdiv(g.ny, 32), groups), dim3(32, 8), 0, stream, d_vol, turned, g.nx, g.ny, items);
+    }
+    launch_project_flat<NB>(G, G->d_volz, turned, d_sino, items, stream);
 }
 
 // The forward projection of `batch` slices.  With the handle's scratch a weight serves up to eight items; calls on one
@@ -485,14 +498,14 @@ static int project_flat(const leap_geometry *G, const float *d_vol, float *d_sin
     if (!scratch || batch == 1 || !G->d_volz) {
         for (int b = 0; b < batch; b += 32768) {
             const int items = batch - b < 32768 ? batch - b : 32768;
-            launch_project_flat<1>(G, d_vol + b * nvol, d_sino + b * nsino, items, stream);
+            launch_project_flat<1>(G, d_vol + b * nvol, nullptr, d_sino + b * nsino, items, stream);
         }
         LEAP_HIP_CHECK(hipGetLastError());
         return LEAP_OK;
     }
     std::lock_guard<std::mutex> lock(G->scratch_mutex);
     if (G->scratch_used && G->scratch_stream != stream) LEAP_HIP_CHECK(hipStreamWaitEvent(stream, G->scratch_event, 0));
-    const int room = (int)(G->scratch_bytes / (nvol * sizeof(float)));          // whole slices the scratch holds
+    const int room = (int)(G->scratch_bytes / (2 * nvol * sizeof(float)));      // whole slices the scratch holds, twice each
     for (int b = 0; b < batch;) {
         const float *vol = d_vol + b * nvol;
         float *sino = d_sino + b * nsino;
@@ -512,7 +525,7 @@ static int project_flat(const leap_geometry *G, const float *d_vol, float *d_sin
             launch_interleaved_flat<2>(G, vol, sino, items, stream);
         } else {
             items = 1;
-            launch_project_flat<1>(G, vol, sino, items, stream);
+            launch_project_flat<1>(G, vol, nullptr, sino, items, stream);
         }
         b += items;
     }

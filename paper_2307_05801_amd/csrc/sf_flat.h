@@ -11,13 +11,16 @@
 // in LDS, then every lane reads back the two or three its pixel can touch.  Small scans split the slabs over up to 16
 // waves of a workgroup (partial sums added through LDS in wave order, so the result does not depend on scheduling).
 // Several items: a copy of the slices with the batch fastest puts the items of a voxel side by side, one or two 16-byte
-// loads for all of them whatever the view angle.
+// loads for all of them whatever the view angle.  A wave whose slabs run along y reads a cache line per lane with every load, the
+// kernel's bound beside issue where there is much to do: it then has a copy of its own, whose rows run along y (FLAT_TURN_STEPS).
 // Back (sf_backproject_flat): a wave owns 8 x 8 voxels and its share of the views.  Per view it loads the 64 detector
 // samples around the tile's shadow, one column per lane, times the ray amplitude, into LDS (batch fastest), and every lane
 // gathers its few columns.  No barrier: a wave reads only what it wrote.  Loads of the next view are in flight meanwhile.
 //
 // Measured, A + A^T, against the general kernels (one thread per ray and item, three quarters of a block idle on one row):
-// 8 slices of 512^2, 720 views of 736 columns 40.7 -> 3.0 ms; one slice of 64^2, 90 views 237 -> 23 us.
+// 8 slices of 512^2, 720 views of 736 columns 40.7 -> 3.0 ms; one slice of 64^2, 90 views 237 -> 23 us.  A since then (an odd number of
+// tiles per view, voxels fetched ahead, the turned copy, no records for parallel beams): the 8 slices 1.95 -> 1.73 ms; one slice of 361 x 379,
+// 577 parallel views of 409 columns 636 -> 415 us; 223 x 246, 271 fan views 159 -> 131 us; 32 drawn scans 0.82 (geometric mean).
 #pragma once
 
 #include "sf_footprint.h"
@@ -26,6 +29,14 @@
 constexpr int FLAT_RAYS = 64;        // detector columns per wave (forward), staged columns per view (back)
 constexpr int FLAT_MAX_SPAN = 256;   // most voxels of a slab that a wave's beams may cover
 constexpr int FLAT_MAX_WAVES = 16;   // waves of a workgroup that share its slabs / its views
+// Candidates of a pixel in a slab whose voxels are fetched before the slab's records are formed, under eight items and from eight on.  One
+// item, none / 1 / 2 / 3 / 4 ahead: fan 223 x 246, 271 views of 295 160 / 136 / 132 / 129 / 132 us; eight: 450 x 373, 553 views of 408 816 /
+// 752 (none, without the grid's idle tiles) / 727 / 708 (2) us.
+constexpr int FLAT_AHEAD = 3, FLAT_AHEAD_8 = 2;
+// Fewest wave steps (views, tiles of 64 columns, slabs) for which a launch of several items makes the turned copy as well, fan / parallel
+// beams.  With over without: fan 36000 to 76000 steps 1.07 to 1.13, 1400000 and 4400000 0.96 and 0.95; parallel 32000 1.05, 46000 0.90,
+// 950000 0.77.  One item gains nothing.
+constexpr double FLAT_TURN_STEPS = 3e5, FLAT_TURN_STEPS_PARALLEL = 4e4;
 constexpr int FLAT_T = 8;            // tile edge of the back projection, voxels
 // Widest footprint of any voxel, in detector columns, and the columns a voxel can then touch.  A tile's voxel lies at most
 // 4 sqrt(2) T from the voxel the window is centred on, and a displacement of sqrt(2) T moves the shadow by at most the
@@ -50,6 +61,19 @@ SF_HD float sf_flat_fu(const SfFlatRec &r, int c)
     return sf_fu(f, c);
 }
 
+// Parallel beams: all footprints of a view have one shape, only their place differs.  (The same numbers as sf_column's.)
+SF_HD SfColumn sf_flat_parallel_column(const SfGeom &g, const SfView &v, int i, int j)
+{
+    SfColumn f;
+    const double x = fma((double)i, g.Td, g.x0d), y = fma((double)j, g.Td, g.y0d);
+    f.xi = fma(fma(y, v.cd, -x * v.sd), g.kud, g.col_offd);
+    f.den = f.inv = 1.0;
+    f.o0 = -v.par_out; f.o1 = -v.par_in; f.o2 = v.par_in; f.o3 = v.par_out;
+    f.h01 = 0.5f * sf_rcp(fmaxf(f.o1 - f.o0, 1e-20f));
+    f.h23 = 0.5f * sf_rcp(fmaxf(f.o3 - f.o2, 1e-20f));
+    return f;
+}
+
 // Marching axis of the wave whose first column is c0: that of its middle beam.
 SF_HD int sf_flat_xmajor(const SfGeom &g, const SfView &v, int c0)
 {
@@ -72,6 +96,31 @@ __global__ __launch_bounds__(256) void sf_interleave(const float *__restrict__ v
     float *__restrict__ d = dst + ((size_t)blockIdx.y * nvol + e) * NB;
 #pragma unroll
     for (int b = 0; b < NB; ++b) d[b] = x[b];
+}
+
+// The same with the slices' rows running along y: [ny][nx] to [group][nx][ny][NB].  Block 32 x 8 threads, tile 32 x 32 voxels; blockIdx.z: group.
+template <int NB>
+__global__ __launch_bounds__(256) void sf_interleave_turned(const float *__restrict__ vol, float *__restrict__ turned, int nx, int ny, int items)
+{
+    __shared__ float tile[32][33 * NB];
+    const size_t nvol = (size_t)nx * ny;
+    const int b0 = blockIdx.z * NB, i0 = blockIdx.x * 32, j0 = blockIdx.y * 32, tx = threadIdx.x, ty = threadIdx.y;
+    turned += (size_t)b0 * nvol;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int i = i0 + tx, j = j0 + ty + 8 * s;
+        const bool in = i < nx && j < ny;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) tile[ty + 8 * s][tx * NB + b] = in && b0 + b < items ? vol[(size_t)(b0 + b) * nvol + (size_t)j * nx + i] : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int i = i0 + ty + 8 * s, j = j0 + tx;
+        if (i >= nx || j >= ny) continue;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) turned[((size_t)i * ny + j) * NB + b] = tile[tx][(ty + 8 * s) * NB + b];
+    }
 }
 
 // Sums the waves' partial results of a workgroup in wave order; the total is valid in wave 0.  red: NB * 64 floats per wave.
@@ -100,27 +149,32 @@ __device__ __forceinline__ void flat_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// grid.x = views * tiles of 64 columns; grid.y: groups of NB items (NB == 1: items).  Block: waves that share the slabs.
-// src: NB == 1 the slices themselves, otherwise the batch-fastest copy of this launch's items.  span: records per wave.
-template <int NB>
+// grid.x = views * tiles of 64 columns, tiles rounded up to an odd number: workgroups go to the 8 XCDs by index in turn, and an XCD that gets
+// the same tile of every view finishes early if it is one at the detector's edge.  grid.y: groups of NB items (NB == 1: items).  Block: waves
+// that share the slabs.  src: NB == 1 the slices themselves, otherwise the batch-fastest copy of this launch's items; turned: the copy whose
+// rows run along y, for waves whose slabs do (nullptr: they read src across its rows).  span: records per wave
+// (PAR, parallel beams: none, every lane works out where its few voxels' footprints lie).
+template <int NB, bool PAR>
 __global__ __launch_bounds__(FLAT_MAX_WAVES * 64) void sf_project_flat(SfGeom g, const SfView *__restrict__ views,
-                                                                       const float *__restrict__ src, float *__restrict__ sino,
-                                                                       int tiles, int span, int items, float fv)
+                                                                       const float *__restrict__ src, const float *__restrict__ turned,
+                                                                       float *__restrict__ sino, int tiles, int span, int items, float fv)
 {
     extern __shared__ float4 flat_lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
-    const size_t lds_wave = (size_t)span * (sizeof(SfFlatRec) / sizeof(float4));
-    SfFlatRec *__restrict__ rec = reinterpret_cast<SfFlatRec *>(flat_lds + wave * lds_wave);
+    // a record's halves lie in arrays of their own: neighbouring lanes read neighbouring 16 bytes of either
+    float4 *__restrict__ rec_lo = flat_lds + (size_t)wave * span * 2, *__restrict__ rec_hi = rec_lo + span;
     const int a = blockIdx.x / tiles, c0 = (blockIdx.x - a * tiles) * FLAT_RAYS;
+    if (c0 >= g.ncols) return;                   // the grid's padding (whole workgroups)
     const unsigned nvol = (unsigned)g.nx * (unsigned)g.ny;
-    src += (size_t)blockIdx.y * nvol * NB;
 
     const SfView v = views[a];
     const int c = c0 + lane < g.ncols ? c0 + lane : g.ncols - 1;
     const int xmajor = __builtin_amdgcn_readfirstlane(sf_flat_xmajor(g, v, c0));
     const SfRayLines L = sf_ray_lines<0>(g, v, c, 1, xmajor);
     const int n_major = xmajor ? g.nx : g.ny, n_minor = xmajor ? g.ny : g.nx;
-    const unsigned n_stride = xmajor ? 1u : (unsigned)g.nx, q_stride = xmajor ? (unsigned)g.nx : 1u;
+    const bool across = xmajor && !turned;
+    src = (xmajor && turned ? turned : src) + (size_t)blockIdx.y * nvol * NB;
+    const unsigned n_stride = across ? 1u : (unsigned)n_minor, q_stride = across ? (unsigned)g.nx : 1u;
     const int n_end = (int)((long long)n_major * (wave + 1) / nwaves);
 
     float acc[NB];
@@ -137,22 +191,54 @@ __global__ __launch_bounds__(FLAT_MAX_WAVES * 64) void sf_project_flat(SfGeom g,
         q_hi = q_hi > n_minor - 1 ? n_minor - 1 : q_hi;
         q_hi = q_hi > q_lo + span - 1 ? q_lo + span - 1 : q_hi;        // (never: the host sized the span)
         if (q_lo > q_hi) continue;
-        for (int q0 = q_lo; q0 <= q_hi; q0 += 64) {
-            const int q = q0 + lane;
-            if (q <= q_hi) rec[q - q_lo] = sf_flat_record(sf_column<0>(g, v, xmajor ? n : q, xmajor ? q : n));
-        }
-        flat_wave_sync();
         qf = qf < q_lo ? q_lo : qf;
         ql = ql > q_hi ? q_hi : ql;
+        // the first candidates' voxels, in flight while the records are formed (a lane without candidates reads another's)
         const float *__restrict__ col = src + (size_t)((unsigned)n * n_stride) * NB;
-        for (int q = qf; q <= ql; ++q) {
-            const float fu = sf_flat_fu(rec[q - q_lo], c);
-            if (!(fu > 0.0f)) continue;          // a voxel beside the beam does not touch it, whatever it holds
+        constexpr int AHEAD = NB < 8 ? FLAT_AHEAD : FLAT_AHEAD_8;
+        float ahead[AHEAD > 0 ? AHEAD : 1][NB];
+#pragma unroll
+        for (int m = 0; m < AHEAD; ++m) {
+            const int q = qf + m < q_hi ? qf + m : q_hi;
+            const float *__restrict__ x = col + (size_t)((unsigned)q * q_stride) * NB;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) ahead[m][b] = x[b];
+        }
+        for (int q0 = q_lo; !PAR && q0 <= q_hi; q0 += 64) {
+            const int q = q0 + lane;
+            if (q <= q_hi) {
+                const SfFlatRec r = sf_flat_record(sf_column<0>(g, v, xmajor ? n : q, xmajor ? q : n));
+                rec_lo[q - q_lo] = reinterpret_cast<const float4 *>(&r)[0];
+                rec_hi[q - q_lo] = reinterpret_cast<const float4 *>(&r)[1];
+            }
+        }
+        if constexpr (!PAR) flat_wave_sync();
+        auto weight = [&](int q) {
+            if constexpr (PAR) return sf_flat_fu(sf_flat_record(sf_flat_parallel_column(g, v, xmajor ? n : q, xmajor ? q : n)), c);
+            SfFlatRec r;
+            reinterpret_cast<float4 *>(&r)[0] = rec_lo[q - q_lo];
+            reinterpret_cast<float4 *>(&r)[1] = rec_hi[q - q_lo];
+            return sf_flat_fu(r, c);
+        };
+        // (a voxel beside the beam does not touch it, whatever it holds)
+#pragma unroll
+        for (int m = 0; m < AHEAD; ++m) {
+            if (qf + m <= ql) {
+                const float fu = weight(qf + m);
+                if (fu > 0.0f) {
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) acc[b] = fmaf(fu, ahead[m][b], acc[b]);
+                }
+            }
+        }
+        for (int q = qf + AHEAD; q <= ql; ++q) {
+            const float fu = weight(q);
+            if (!(fu > 0.0f)) continue;
             const float *__restrict__ x = col + (size_t)((unsigned)q * q_stride) * NB;
 #pragma unroll
             for (int b = 0; b < NB; ++b) acc[b] = fmaf(fu, x[b], acc[b]);
         }
-        flat_wave_sync();
+        if constexpr (!PAR) flat_wave_sync();
     }
     flat_reduce<NB>(acc, reinterpret_cast<float *>(flat_lds), wave, lane, nwaves);
     if (wave == 0 && c0 + lane < g.ncols) {

@@ -102,3 +102,10 @@ def test_captured_calls_and_two_streams():
         torch.cuda.synchronize()
         assert torch.equal(other, ref) and torch.equal(got, ref)
     geo.close()
+
+
+@pytest.mark.parametrize("cfg", [scan(FAN, 131, 120, 129, 840), scan(FAN, 120, 131, 300, 520, pixel_u=0.9), scan(PARALLEL, 90, 50, 70, 400)], ids=lambda c: c.name)
+def test_slices_turned_for_beams_along_x(oracle_mod, cfg):
+    """Enough views that a batch is copied with its rows along y as well; an item alone reads the slice as it lies."""
+    test_flat_kernels_match_oracle(oracle_mod, cfg, 5)
+    test_flat_kernels_match_oracle(oracle_mod, cfg, 10)
