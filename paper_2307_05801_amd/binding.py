@@ -146,8 +146,8 @@ def leap_geometry_destroy(handle: int, lib=None) -> None:
 
 def leap_geometry_describe(handle: int, lib=None) -> str:
     lib = lib or load_library()
-    buf = C.create_string_buffer(256)
-    _check(lib, lib.leap_geometry_describe(C.c_void_p(handle), buf, 256))
+    buf = C.create_string_buffer(512)
+    _check(lib, lib.leap_geometry_describe(C.c_void_p(handle), buf, 512))
     return buf.value.decode()
 
 

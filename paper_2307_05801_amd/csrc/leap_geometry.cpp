@@ -303,6 +303,7 @@ static const LaunchTime BP_TIMES[BP_NSHAPES] = {{1.35, 0.46, 0.5, 1.0}, {1.0, 0.
 static const LaunchTime BP_PAIR_TIMES[BP_NPAIR_SHAPES] = {{1.35, 0.55, 1.0}, {1.4, 0.58, 1.0}, {0.9, 0.27, 1.0}, {1.35, 0.59, 1.0}};
 static const LaunchTime BP_SPLIT_TIMES[2][BP_NSPLIT_SHAPES] = {{{0.42, 0.43, 4.0}, {0.29, 0.24, 4.0}, {0.24, 0.20, 4.0}},
                                                                {{0.56, 0.56, 4.0}, {0.34, 0.34, 4.0}, {0.29, 0.29, 4.0}}};
+constexpr double BACK_MOST_FLOATS = 16777216.0;      // room for the volumes of parts, at most 64 MiB
 constexpr int BP_FEW_VIEWS = 4;        // fewer leave a launch little but its start and end: 10 to 12 us whichever the kernel
 
 static int tile_chunks(const leap_geometry *G, int zc, int kfirst = 0)
@@ -335,21 +336,30 @@ int leap_back_pairs(const leap_geometry *G, int items)
 // 54 / 79, sixteen 175 / 161 / 119 / 105; off centre 96^3 138 / 55 / 46 / 61, sixteen 373 / 583 / 370 / 308; 16 items of one view 96^3 26 /
 // 66 / 60 / 57.  (Lines by the workgroups of one volume alone, whatever the batch and the views, had 580 of 4260 launches of 24^3 to
 // 192^3, 1 to 16 items, 1 to 180 views above 1.035 times the unsplit time, up to 2.6.)
-int leap_back_split_shape(const leap_geometry *G, int items)
+static double back_unsplit_time(const leap_geometry *G, int items)
 {
     const int views = G->g.nviews, kfirst = G->bp_mirror ? sf_mirror_first_voxel_above(G->g.nz) : 0;
-    if (!G->bp_split_fits || (views < BP_FEW_VIEWS && !G->bp_split_forced)) return -1;
     const int pairs = leap_back_pairs(G, items), left = G->bp_mirror && pairs ? 0 : items - 2 * pairs;
     double unsplit = 0.0;
     if (pairs) unsplit += launch_time(BP_PAIR_TIMES[G->bp_pair_shape], (double)tile_chunks(G, BP_PAIR_SHAPES[G->bp_pair_shape].zc, kfirst) * pairs, views);
     if (left) unsplit += launch_time(BP_TIMES[G->bp_shape], (double)tile_chunks(G, BP_SHAPES[G->bp_shape].zc) * left, views);
-    unsplit *= 0.93;                                   // (a clear gain: the times are good to some five per cent)
+    return unsplit;
+}
+
+static double back_split_time(const leap_geometry *G, int sh, int items, int parts)
+{
+    const int views = (G->g.nviews + parts - 1) / parts, kfirst = G->bp_mirror ? sf_mirror_first_voxel_above(G->g.nz) : 0;
     const int twos = leap_back_split_pairs(G, items), ones = G->bp_mirror ? 0 : items - 2 * twos;
-    auto time_of = [&](int sh) {
-        const double chunks = tile_chunks(G, BP_SPLIT_SHAPES[sh].zc, kfirst), wider = BP_SPLIT_SHAPES[sh].pw > 32 && G->bp_need_w > 31 ? 1.25 : 1.0;
-        return wider * ((twos ? launch_time(BP_SPLIT_TIMES[1][sh], chunks * twos, views) : 0.0) +
-                        (ones ? launch_time(BP_SPLIT_TIMES[G->g.type == SF_CONE_CURVED][sh], chunks * ones, views) : 0.0));
-    };
+    const double chunks = (double)tile_chunks(G, BP_SPLIT_SHAPES[sh].zc, kfirst) * parts, wider = BP_SPLIT_SHAPES[sh].pw > 32 && G->bp_need_w > 31 ? 1.25 : 1.0;
+    return wider * ((twos ? launch_time(BP_SPLIT_TIMES[1][sh], chunks * twos, views) : 0.0) +
+                    (ones ? launch_time(BP_SPLIT_TIMES[G->g.type == SF_CONE_CURVED][sh], chunks * ones, views) : 0.0));
+}
+
+int leap_back_split_shape(const leap_geometry *G, int items)
+{
+    if (!G->bp_split_fits || (G->g.nviews < BP_FEW_VIEWS && !G->bp_split_forced)) return -1;
+    const double unsplit = 0.93 * back_unsplit_time(G, items);       // (a clear gain: the times are good to some five per cent)
+    auto time_of = [&](int sh) { return back_split_time(G, sh, items, 1); };
     if (G->bp_split_shape >= 0 && (G->bp_split_forced || time_of(G->bp_split_shape) < unsplit)) return G->bp_split_shape;
     if (G->bp_split_shape < 0 && items > 1) return -1;
     int best = -1;
@@ -359,6 +369,38 @@ int leap_back_split_shape(const leap_geometry *G, int items)
             least = time_of(sh);
             best = sh;
         }
+    return best;
+}
+
+// Workgroups that share the views, each with sums of its own: a volume of a few tiles leaves most compute units without a workgroup however
+// its views are shared within one, and has views enough for all of them.  The parts' volumes are added by a kernel of their own, which costs
+// a launch and their traffic.  The same estimate decides, by shapes and up to 32 parts of at least eight views each; a batch takes what one
+// volume takes as long as that is a gain.
+LeapBackParts leap_back_parts(const leap_geometry *G, int items)
+{
+    const size_t nvol = (size_t)G->g.nx * G->g.ny * G->g.nz;
+    const LeapBackParts none = {-1, 1, items};
+    if (!G->bp_parts_fits || G->bp_split_forced) return none;
+    const int split = leap_back_split_shape(G, items);
+    const double without = split >= 0 ? back_split_time(G, split, items, 1) : back_unsplit_time(G, items);
+    auto time_of = [&](int sh, int parts, int at_once) {
+        const double launches = std::ceil((double)items / at_once);
+        return launches * (back_split_time(G, sh, std::min(items, at_once), parts) + 1.8) + (parts + 1.0) * items * 4.0 * (double)nvol / 7e6;
+    };
+    if (items > 1) {
+        if (G->bp_parts == 1) return none;
+        const int at_once = (int)std::min<size_t>(items, G->back_floats / (nvol * G->bp_parts));
+        return at_once >= 1 && time_of(G->bp_parts_shape, G->bp_parts, at_once) < 0.93 * without ? LeapBackParts{G->bp_parts_shape, G->bp_parts, at_once} : none;
+    }
+    if (G->bp_parts > 1) return {G->bp_parts_shape, G->bp_parts, 1};
+    LeapBackParts best = none;
+    double least = 0.85 * without;
+    for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh)
+        for (const int parts : {2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32})
+            if ((G->bp_parts_fits >> sh & 1u) && G->g.nviews >= 8 * parts && (double)nvol * parts <= BACK_MOST_FLOATS && time_of(sh, parts, 1) < least) {
+                least = time_of(sh, parts, 1);
+                best = {sh, parts, 1};
+            }
     return best;
 }
 
@@ -393,8 +435,9 @@ static std::vector<int> backproject_pair_shapes(leap_geometry *G)
 static void no_tiled_back_projection(leap_geometry *G)
 {
     G->bp_tiled = G->bp_mirror = G->bp_pair_forced = G->bp_split_forced = false;
-    G->bp_pair_shape = G->bp_split_shape = -1;
-    G->bp_split_fits = 0;
+    G->bp_pair_shape = G->bp_split_shape = G->bp_parts_shape = -1;
+    G->bp_parts = 1;
+    G->bp_split_fits = G->bp_parts_fits = 0;
 }
 
 // Footprint model, tiled back projection: pick the template instance and verify its staged window.
@@ -498,17 +541,25 @@ static void select_footprint_tiled(leap_geometry *G)
         unsigned candidates = 0;
         for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh) candidates |= exists(sh) ? 1u << sh : 0u;
         G->bp_split_fits = candidates;
-        if (only >= 0 || leap_back_split_shape(G, 1) >= 0) {
+        long want = -1;
+        debug_option("bp_parts", want);
+        G->bp_parts_fits = only < 0 && want != 1 ? candidates : 0u;
+        if (only >= 0 || leap_back_split_shape(G, 1) >= 0 || leap_back_parts(G, 1).parts > 1) {
             std::vector<WindowNeed> needs;
             for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh)
                 if ((candidates >> sh & 1u) && need_of(BP_SPLIT_SHAPES[sh].zc, kfirst) == known.end()) needs.push_back({BP_SPLIT_SHAPES[sh].zc, kfirst});
             look_at(needs);
             for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh)
                 if ((candidates >> sh & 1u) && !window_fits(*need_of(BP_SPLIT_SHAPES[sh].zc, kfirst), BP_SPLIT_SHAPES[sh])) G->bp_split_fits &= ~(1u << sh);
+            G->bp_parts_fits &= G->bp_split_fits;
             G->bp_split_forced = only >= 0 && G->bp_split_fits != 0;
             G->bp_split_shape = G->bp_split_forced ? (int)only : leap_back_split_shape(G, 1);
+            const LeapBackParts plan = leap_back_parts(G, 1);
+            G->bp_parts_shape = plan.shape;
+            G->bp_parts = plan.parts;
         }
         if (G->bp_split_shape < 0) G->bp_split_fits = 0;
+        if (G->bp_parts == 1) G->bp_parts_fits = 0;
     }
     if (!G->bp_tiled) no_tiled_back_projection(G);
 }
@@ -1143,6 +1194,24 @@ static void allocate_flat_scratch(leap_geometry *G)
     (void)hipGetLastError();
 }
 
+// Room for the volumes of the parts in which the footprint back projection's views are shared among workgroups: for as many items at once as
+// fit 64 MiB.  Without it the views stay with one workgroup.
+static void allocate_back_room(leap_geometry *G)
+{
+    const size_t one = (size_t)G->g.nx * G->g.ny * G->g.nz * G->bp_parts;
+    G->back_floats = one * std::max<size_t>(1, std::min<size_t>(16, (size_t)BACK_MOST_FLOATS / one));
+    hipError_t e = hipMalloc((void **)&G->d_back, G->back_floats * sizeof(float));
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&G->back_event, hipEventDisableTiming);
+    if (e == hipSuccess) return;
+    if (G->d_back) (void)hipFree(G->d_back);
+    G->d_back = nullptr;
+    G->back_floats = 0;
+    G->bp_parts = 1;
+    G->bp_parts_fits = 0;
+    G->note = "no room for the back projection's parts: its views stay with one workgroup";
+    (void)hipGetLastError();
+}
+
 static void free_handle(leap_geometry *G)
 {
     if (!G) return;
@@ -1156,7 +1225,9 @@ static void free_handle(leap_geometry *G)
     if (G->d_mfviews) (void)hipFree(G->d_mfviews);
     if (G->d_mdbp) (void)hipFree(G->d_mdbp);
     if (G->d_colcs) (void)hipFree(G->d_colcs);
+    if (G->d_back) (void)hipFree(G->d_back);
     if (G->scratch_event) (void)hipEventDestroy(G->scratch_event);
+    if (G->back_event) (void)hipEventDestroy(G->back_event);
     delete G;
 }
 
@@ -1218,6 +1289,7 @@ static int finish_handle(leap_geometry *G, leap_geometry **out)
     if (e == hipSuccess && !G->views.empty()) e = upload((void **)&G->d_views, G->views.data(), sizeof(SfView) * G->views.size());
     if (e == hipSuccess) allocate_forward_scratch(G);
     if (e == hipSuccess && G->flat) allocate_flat_scratch(G);
+    if (e == hipSuccess && G->bp_parts > 1) allocate_back_room(G);
     if (e == hipSuccess && !G->raycols.empty()) e = upload((void **)&G->d_raycols, G->raycols.data(), sizeof(SdRayCol) * G->raycols.size());
     if (e == hipSuccess && !G->geoms.empty()) e = upload((void **)&G->d_geoms, G->geoms.data(), sizeof(SfGeom) * G->geoms.size());
     if (e == hipSuccess && !G->poses.empty()) e = upload((void **)&G->d_poses, G->poses.data(), sizeof(MdPose) * G->poses.size());
@@ -1519,7 +1591,7 @@ extern "C" void leap_geometry_destroy(leap_geometry *G) { free_handle(G); }
 extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t cap)
 {
     if (!G || !buf || cap <= 0) return invalid("null handle or buffer");
-    char fwd[160], back[128];
+    char fwd[160], back[160];
     const bool siddon = G->g.model == SF_MODEL_SIDDON;
     if (siddon && G->sd_columns)
         std::snprintf(fwd, sizeof fwd, "columns(rg=%d,slab=%d%s)", G->fp_rg, G->slab_width, G->sd_pairs == 2 ? ",pairs apart" : (G->sd_pairs ? ",pairs" : ""));
@@ -1546,6 +1618,11 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
         const SfBpShape &S = (G->d_mdbp ? MD_BP_SPLIT_SHAPES : (siddon ? SD_BP_SPLIT_SHAPES : BP_SPLIT_SHAPES))[G->bp_split_shape];
         const size_t n = std::strlen(back);
         std::snprintf(back + n, sizeof back - n, "+split(%szc=%d,%dx%d)", G->bp_mirror ? "mirror," : "", S.zc, S.pw, S.ph);
+    }
+    if (G->bp_parts > 1) {
+        const SfBpShape &S = BP_SPLIT_SHAPES[G->bp_parts_shape];
+        const size_t n = std::strlen(back);
+        std::snprintf(back + n, sizeof back - n, "+parts(%d,zc=%d,%dx%d)", G->bp_parts, S.zc, S.pw, S.ph);
     }
     const char *modules = G->g.type != SF_MODULAR ? "" : (G->geoms.empty() ? " (tilted modules)" : " (upright modules)");
     std::snprintf(buf, (size_t)cap, "type=%d model=%s A=%s AT=%s scratch=%zu%s cols/voxel<=%.2f rows/voxel<=%.2f voxels/row<=%.2f%s%s",

@@ -41,6 +41,16 @@ struct leap_geometry {
     // (leap_back_split_shape, leap_siddon_split_shape).
     int bp_split_shape = -1;
     unsigned bp_split_fits = 0;
+    // ... and workgroups of them, each with a volume of its own: what one volume takes (parts 1: none), the shapes that fit, the room for the
+    // parts' volumes (floats; calls on one handle share it and are ordered like those that share the forward scratch)
+    int bp_parts_shape = -1, bp_parts = 1;
+    unsigned bp_parts_fits = 0;
+    float *d_back = nullptr;
+    size_t back_floats = 0;
+    mutable std::mutex back_mutex;
+    mutable hipEvent_t back_event = nullptr;
+    mutable hipStream_t back_stream = nullptr;
+    mutable bool back_used = false;
     bool bp_split_forced = false;       // (debugging: bp_split_shape, whatever the launch)
     // column-wise forward projection (footprint and Siddon models): the volume goes through a z-fastest scratch copy
     // slab by slab (sf_project_columns.h)
@@ -119,6 +129,11 @@ bool leap_plan_scratch(const leap_geometry *G, size_t floats, int batch, int &wi
 int leap_back_pairs(const leap_geometry *G, int items);
 inline int leap_back_split_pairs(const leap_geometry *G, int items) { return G->bp_mirror ? items : (G->g.type != SF_MODULAR ? items / 2 : 0); }
 int leap_back_split_shape(const leap_geometry *G, int items);
+// ... or the shape and the number of workgroups that share the views, items of the batch at a time (parts 1: as above).
+struct LeapBackParts {
+    int shape, parts, items;
+};
+LeapBackParts leap_back_parts(const leap_geometry *G, int items);
 // The same of the tiled Siddon back projection: a shape of SD_BP_SPLIT_SHAPES or, on tilted modules, MD_BP_SPLIT_SHAPES.
 int leap_siddon_split_shape(const leap_geometry *G, int items);
 
@@ -146,7 +161,7 @@ struct SfSlab;
 bool leap_launch_footprint_slab(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward.hip
 bool leap_launch_footprint_slab_parts(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward_parts.hip
 int leap_launch_footprint_back(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                         // leap_footprint_back.hip
-bool leap_launch_backproject_split(const leap_geometry *geom, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_footprint_back_split.hip
+bool leap_launch_backproject_split(const leap_geometry *geom, int shape, int parts, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_footprint_back_split.hip
 bool leap_launch_siddon_back_split(const leap_geometry *geom, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_siddon_back_split.hip
 bool leap_launch_backproject_pairs(const leap_geometry *geom, const float *d_sino, float *d_vol, int blocks, hipStream_t stream);                     // leap_footprint_back_pairs.hip
 int leap_launch_backproject_batch(const leap_geometry *geom, const float *d_sino, float *d_vol, int batch, hipStream_t stream);

@@ -189,6 +189,7 @@ SF_HD SfWindow sf_bp_window(const SfGeom &g, const SfView &v, float xc, float yc
 struct SfBpSets {
     int mirror;
     int kfirst;       // first voxel of the first chunk
+    int parts = 1;    // VS > 1: workgroups that share the views of a tile and chunk, each with sums of its own in a volume of its own
 };
 SF_HD int sf_mirror_first_voxel_above(int nz) { return nz / 2; }
 
@@ -292,6 +293,18 @@ SF_HD SfBpScene sf_bp_scene(const SfGeom &g, int i0, int j0, int k0)
     return s;
 }
 
+// The parts' volumes summed in the order of the parts: item n of `per` to a workgroup at [n / per][part][n % per].  grid.y: items.
+static __global__ __launch_bounds__(256) void sf_sum_parts(const float *__restrict__ from, float *__restrict__ vol, unsigned nvol, int parts, int per)
+{
+    const unsigned e = blockIdx.x * 256u + threadIdx.x;
+    if (e >= nvol) return;
+    const unsigned item = blockIdx.y;
+    from += (size_t)(item / per * parts * per + item % per) * nvol + e;
+    float sum = from[0];
+    for (int p = 1; p < parts; ++p) sum += from[(size_t)p * per * nvol];
+    vol[(size_t)item * nvol + e] = sum;
+}
+
 // GT: 0 flat or parallel, 1 cylindrical detector, 2 modular geometry with upright modules (every view brings its own
 // parameter block geoms[a]: the scene translated so that the view is a circular cone-beam view; g holds the sizes).
 // NS: volumes per workgroup.  VS: groups of 256 threads that share a tile's views, group q taking views q, q + VS, ...: a step from
@@ -312,9 +325,13 @@ __global__ __launch_bounds__(256 * VS, VS > 1 ? (NS == 1 && BP_ZC <= 16 && GT !=
     constexpr int BP_PS = bp_row_stride<NS>(BP_PW);      // LDS row stride (samples)
     using Sample = SfBpSample<NS>;
     __shared__ Sample patch[2 * VS][BP_PH * BP_PS];
-    // blockIdx.z: item of a batch, or pair of items
+    // blockIdx.z: item of a batch, or pair of items; VS > 1: times the parts of its views, the volumes of an item's parts side by side
     const bool mirror = NS == 2 && sets.mirror;
-    sino += (size_t)blockIdx.z * (mirror ? 1 : NS) * g.nviews * g.nrows * g.ncols;
+    const unsigned block = VS == 1 ? blockIdx.z : blockIdx.z / (unsigned)sets.parts;
+    const int part = VS == 1 ? 0 : (int)(blockIdx.z - block * (unsigned)sets.parts);
+    const int a_first = VS == 1 ? 0 : (int)((long long)g.nviews * part / sets.parts);
+    const int a_end = VS == 1 ? g.nviews : (int)((long long)g.nviews * (part + 1) / sets.parts);
+    sino += (size_t)block * (mirror ? 1 : NS) * g.nviews * g.nrows * g.ncols;
     vol += (size_t)blockIdx.z * (mirror ? 1 : NS) * g.nx * g.ny * g.nz;
     const size_t to_second = mirror ? 0 : (size_t)g.nviews * g.nrows * g.ncols;
 
@@ -332,7 +349,7 @@ __global__ __launch_bounds__(256 * VS, VS > 1 ? (NS == 1 && BP_ZC <= 16 && GT !=
         if constexpr (GT == 2) return geoms[a];
         else return g;
     };
-    const SfBpScene scene0 = sf_bp_scene<BP_ZC>(geom_of(VS == 1 || group < g.nviews ? group : 0), i0, j0, k0);     // of the group's first view
+    const SfBpScene scene0 = sf_bp_scene<BP_ZC>(geom_of(VS == 1 || a_first + group < a_end ? a_first + group : 0), i0, j0, k0);     // of the group's first view
 
     const int sc = sf_stage_column<BP_PW>(tid), sr = sf_stage_row<BP_PW, BP_PH>(tid);
     constexpr int NSTAGE = (BP_PH + 256 / BP_PW - 1) / (256 / BP_PW);
@@ -355,22 +372,23 @@ __global__ __launch_bounds__(256 * VS, VS > 1 ? (NS == 1 && BP_ZC <= 16 && GT !=
     };
 
     SfWindow win = {};
-    if (VS == 1 || group < g.nviews) {
-        const float *ya = sino + (size_t)group * view_stride;
-        bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(group), views[group], ya, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1, wh,
-                                                           sc, sr, win, stage, cv_pre(group), reinterpret_cast<const char *>(ya + to_second), mirror);
-        bp_store_view<BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(group), views[group], sc, sr, win, stage, patch[2 * group], colcs);
+    if (VS == 1 || a_first + group < a_end) {
+        const int a = a_first + group;
+        const float *ya = sino + (size_t)a * view_stride;
+        bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a), views[a], ya, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1, wh,
+                                                           sc, sr, win, stage, cv_pre(a), reinterpret_cast<const char *>(ya + to_second), mirror);
+        bp_store_view<BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a), views[a], sc, sr, win, stage, patch[2 * group], colcs);
     }
     win_next = win;
     __syncthreads();
 
-    for (int a = group; a - group < g.nviews; a += VS) {
-        const int buffer = 2 * group + (((a - group) / VS) & 1);
+    for (int a = a_first + group; a - group < a_end; a += VS) {
+        const int buffer = 2 * group + (((a - a_first - group) / VS) & 1);
         const Sample *buf = patch[buffer];
-        if (VS == 1 || a < g.nviews) {
+        if (VS == 1 || a < a_end) {
         double gref = 0.0;
         if constexpr (GT == 1) gref = cvt[a].gref;
-        if (a + VS < g.nviews) {    // global loads in flight during the gather
+        if (a + VS < a_end) {    // global loads in flight during the gather
             const SfBpScene sn = GT == 2 ? sf_bp_scene<BP_ZC>(geom_of(a + VS), i0, j0, k0) : scene0;
             const float *ya = sino + (size_t)(a + VS) * view_stride;
             bp_load_view<NC, NV, BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a + VS), views[a + VS], ya, sn.xc, sn.yc, hx, sn.z0, sn.z1, wh, sc, sr,
@@ -532,7 +550,7 @@ __global__ __launch_bounds__(256 * VS, VS > 1 ? (NS == 1 && BP_ZC <= 16 && GT !=
             }
         }
 
-        if (a + VS < g.nviews)
+        if (a + VS < a_end)
             bp_store_view<BP_PW, BP_PH, NSTAGE, GT, NS>(geom_of(a + VS), views[a + VS], sc, sr, win_next, stage, patch[buffer ^ 1], colcs);
         }
         win = win_next;

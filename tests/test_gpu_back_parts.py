@@ -1,0 +1,69 @@
+"""Footprint back projection of a few tiles and many views: the views shared among workgroups, each with a volume of its own.
+
+Against the oracle; views that the parts and their groups of threads do not divide evenly; two items per workgroup and an odd last one; calls on
+two streams; a captured call, which needs no room and takes the views in one workgroup."""
+import pytest
+
+from synthetic import CTConfig, perturbed_poses, uniform_sinogram
+from synthetic.configs import CONE, CONE_CURVED, PARALLEL
+from tests.test_gpu_parity import TOL, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def scan(geom=CONE, nviews=203, **kw):
+    par = dict(sod=0.0, sdd=0.0) if geom == PARALLEL else dict(sod=150.0, sdd=225.0)
+    base = dict(nviews=nviews, arc_deg=360.0, nrows=40, ncols=60, pixel_v=1.5, pixel_u=1.6, nx=37, ny=35, nz=27, voxel_xy=1.0, voxel_z=1.0,
+                start_deg=3.0, shift_u=0.3)
+    return CTConfig("parts", geom, **{**base, **par, **kw})
+
+
+CASES = {"mirror": scan(), "off_centre": scan(shift_v=0.3), "odd_middle": scan(nz=29, nviews=331), "taller": scan(pixel_v=1.1, nrows=60, shift_v=0.2),
+         "wide_window": scan(pixel_u=0.8, ncols=110, shift_v=0.2), "curved": scan(CONE_CURVED, shift_v=-0.2),
+         "upright": perturbed_poses(scan(shift_v=0.2), 5, shift_mm=4.0, upright=True), "parallel": scan(PARALLEL, pixel_u=1.0, pixel_v=1.0, nviews=500)}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_parts_match_oracle(oracle_mod, name):
+    import torch
+    from paper_2307_05801_amd import Geometry
+    cfg = CASES[name]
+    geo = Geometry(cfg)
+    print(f"[gpu] {name}: {geo.describe()}", flush=True)
+    assert "+parts(" in geo.describe(), geo.describe()
+    y = uniform_sinogram(cfg, 5, batch=3)
+    yt = torch.from_numpy(y).cuda()
+    one = [geo.backproject(yt[b].contiguous()) for b in range(3)]
+    # float sums whose positions are double: the parity tests' tolerance
+    assert rel_l2(one[1].cpu().numpy(), oracle_mod.backproject(cfg, y[1])) <= TOL
+    three = geo.backproject(yt)
+    for b in range(3):
+        assert torch.equal(one[b], geo.backproject(yt[b].contiguous()))
+        # a batch takes the same parts as long as they are a gain, else its sums come in another order (a few roundings)
+        assert rel_l2(three[b].cpu().numpy(), one[b].cpu().numpy()) <= 1e-6
+    geo.close()
+
+
+def test_two_streams_and_a_captured_call():
+    import torch
+    from paper_2307_05801_amd import Geometry
+    geo = Geometry(CASES["off_centre"])
+    y, z = (torch.rand(geo.sino_shape, device="cuda") for _ in range(2))
+    ref_y, ref_z, out = geo.backproject(y), geo.backproject(z), torch.empty(geo.vol_shape, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        geo.backproject(y, out=out)
+    side = torch.cuda.Stream()
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        captured = out.clone()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            beside = geo.backproject(z)
+        here = geo.backproject(y)
+        torch.cuda.synchronize()
+        assert torch.equal(here, ref_y) and torch.equal(beside, ref_z)
+        assert rel_l2(captured.cpu().numpy(), ref_y.cpu().numpy()) <= 1e-6
+    geo.close()
