@@ -375,17 +375,17 @@ int leap_back_split_shape(const leap_geometry *G, int items)
 // Workgroups that share the views, each with sums of its own: a volume of a few tiles leaves most compute units without a workgroup however
 // its views are shared within one, and has views enough for all of them.  The parts' volumes are added by a kernel of their own, which costs
 // a launch and their traffic.  The same estimate decides, by shapes and up to 32 parts of at least eight views each; a batch takes what one
-// volume takes as long as that is a gain.
-LeapBackParts leap_back_parts(const leap_geometry *G, int items)
+// volume takes as long as that is a gain.  us, before / in parts: 57 x 65 x 37, 310 views 274 / 79; 58 x 57 x 28, 626 views 533 / 78; 142 x 148 x
+// 108, 677 parallel views 1265 / 1083; 81 x 66 x 67, 53 views 45 / 36.
+// without: the time of the launch as it is else; split_time(shape, items, parts); both in units of `unit` us.
+template <class SplitTime>
+static LeapBackParts choose_parts(const leap_geometry *G, int items, int nshapes, double without, double unit, SplitTime split_time)
 {
     const size_t nvol = (size_t)G->g.nx * G->g.ny * G->g.nz;
     const LeapBackParts none = {-1, 1, items};
-    if (!G->bp_parts_fits || G->bp_split_forced) return none;
-    const int split = leap_back_split_shape(G, items);
-    const double without = split >= 0 ? back_split_time(G, split, items, 1) : back_unsplit_time(G, items);
     auto time_of = [&](int sh, int parts, int at_once) {
         const double launches = std::ceil((double)items / at_once);
-        return launches * (back_split_time(G, sh, std::min(items, at_once), parts) + 1.8) + (parts + 1.0) * items * 4.0 * (double)nvol / 7e6;
+        return launches * (split_time(sh, std::min(items, at_once), parts) + 5.0 / unit) + (parts + 1.0) * items * 4.0 * (double)nvol / (2.5e6 * unit);
     };
     if (items > 1) {
         if (G->bp_parts == 1) return none;
@@ -395,13 +395,21 @@ LeapBackParts leap_back_parts(const leap_geometry *G, int items)
     if (G->bp_parts > 1) return {G->bp_parts_shape, G->bp_parts, 1};
     LeapBackParts best = none;
     double least = 0.85 * without;
-    for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh)
+    for (int sh = 0; sh < nshapes; ++sh)
         for (const int parts : {2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32})
             if ((G->bp_parts_fits >> sh & 1u) && G->g.nviews >= 8 * parts && (double)nvol * parts <= BACK_MOST_FLOATS && time_of(sh, parts, 1) < least) {
                 least = time_of(sh, parts, 1);
                 best = {sh, parts, 1};
             }
     return best;
+}
+
+LeapBackParts leap_back_parts(const leap_geometry *G, int items)
+{
+    if (!G->bp_parts_fits || G->bp_split_forced) return {-1, 1, items};
+    const int split = leap_back_split_shape(G, items);
+    return choose_parts(G, items, BP_NSPLIT_SHAPES, split >= 0 ? back_split_time(G, split, items, 1) : back_unsplit_time(G, items), 2.8,
+                        [&](int sh, int n, int parts) { return back_split_time(G, sh, n, parts); });
 }
 
 // Tiled back projection, two volumes per workgroup: the shapes that leave the chip enough workgroups.
@@ -753,24 +761,34 @@ static void select_footprint_flat(leap_geometry *G)
 // four groups: 64^3 437 / 111, sixteen 868 / 885, 128^3 460 / 432, four 1360 / 1700; 62 x 63 x 43 x 207 views 1796 / 422; where the window
 // leaves a compute unit one workgroup of 256 threads, 135 x 140 x 148 x 156 views 5598 / 1986, or two groups of threads 165 x 164 x 79 x 58 2440
 // / 1216, 234 x 196 x 225 x 206 22998 / 13630.
+static const LaunchTime SD_BP_TIMES[BP_LAST_SHORT_SHAPE + 1] = {{}, {4.8, 1.95, 0.5}, {6.2, 3.25, 0.5}, {5.2, 2.05, 0.5}, {5.1, 2.05, 0.5}};
+static const double SD_BP_SPLIT_TIMES[BP_LAST_SHORT_SHAPE + 1][SD_BP_NSPLIT_SHAPES] = {{}, {1.3, 1.07}, {1.7, 1.45}, {1.95, 1.68}, {2.0, 1.45}};
+static const LaunchTime MD_BP_TIMES[MD_BP_NSHAPES] = {{6.9, 2.35, 0.5}, {8.5, 2.95, 0.5}, {14.0, 9.0, 0.5}, {10.0, 5.0, 0.5}, {18.0, 17.0, 0.5}, {12.4, 12.0, 0.5}};
+static const double MD_BP_SPLIT_TIMES[MD_BP_NSHAPES][MD_BP_NSPLIT_SHAPES] = {{1.65, 2.5, 2.7}, {1.9, 2.9, 3.1}, {2.2, 3.4, 3.6}, {2.2, 3.4, 3.6}, {2.2, 3.4, 3.6}, {2.2, 3.4, 3.6}};
+
+static double siddon_unsplit_time(const leap_geometry *G, int items)
+{
+    const bool tilted = G->g.type == SF_MODULAR && G->geoms.empty();
+    const SfBpShape &S = tilted ? MD_BP_SHAPES[G->bp_shape] : BP_SHAPES[G->bp_shape];
+    return launch_time(tilted ? MD_BP_TIMES[G->bp_shape] : SD_BP_TIMES[G->bp_shape], (double)tile_chunks(G, S.zc) * items, G->g.nviews);
+}
+
+static double siddon_split_time(const leap_geometry *G, int sh, int items, int parts)
+{
+    const bool tilted = G->g.type == SF_MODULAR && G->geoms.empty();
+    const SfBpShape &S = tilted ? MD_BP_SPLIT_SHAPES[sh] : SD_BP_SPLIT_SHAPES[sh];
+    const double round = tilted ? MD_BP_SPLIT_TIMES[G->bp_shape][sh] : SD_BP_SPLIT_TIMES[G->bp_shape][sh];
+    return launch_time({round, round, 3.0}, (double)tile_chunks(G, S.zc) * items * parts, (G->g.nviews + parts - 1) / parts);
+}
+
 int leap_siddon_split_shape(const leap_geometry *G, int items)
 {
-    static const LaunchTime one[BP_LAST_SHORT_SHAPE + 1] = {{}, {4.8, 1.95, 0.5}, {6.2, 3.25, 0.5}, {5.2, 2.05, 0.5}, {5.1, 2.05, 0.5}};
-    static const double split[BP_LAST_SHORT_SHAPE + 1][SD_BP_NSPLIT_SHAPES] = {{}, {1.3, 1.07}, {1.7, 1.45}, {1.95, 1.68}, {2.0, 1.45}};
-    static const LaunchTime tilted_one[MD_BP_NSHAPES] = {{6.9, 2.35, 0.5}, {8.5, 2.95, 0.5}, {14.0, 9.0, 0.5}, {10.0, 5.0, 0.5}, {18.0, 17.0, 0.5}, {12.4, 12.0, 0.5}};
-    static const double tilted_split[MD_BP_NSHAPES][MD_BP_NSPLIT_SHAPES] = {{1.65, 2.5}, {1.9, 2.9}, {2.2, 3.4}, {2.2, 3.4}, {2.2, 3.4}, {2.2, 3.4}};
-    const int views = G->g.nviews;
     if (!G->bp_split_fits) return -1;
     if (G->bp_split_shape >= 0 && G->bp_split_forced) return G->bp_split_shape;
-    if (views < 2 || (G->bp_split_shape < 0 && items > 1)) return -1;
+    if (G->g.nviews < 2 || (G->bp_split_shape < 0 && items > 1)) return -1;
     const bool tilted = G->g.type == SF_MODULAR && G->geoms.empty();
-    auto workgroups = [&](const SfBpShape &S) { return (double)tile_chunks(G, S.zc) * items; };
-    const double unsplit = 0.93 * (tilted ? launch_time(tilted_one[G->bp_shape], workgroups(MD_BP_SHAPES[G->bp_shape]), views)
-                                          : launch_time(one[G->bp_shape], workgroups(BP_SHAPES[G->bp_shape]), views));
-    auto time_of = [&](int sh) {
-        const double round = (tilted ? tilted_split : split)[G->bp_shape][sh];
-        return launch_time({round, round, 3.0}, workgroups((tilted ? MD_BP_SPLIT_SHAPES : SD_BP_SPLIT_SHAPES)[sh]), views);
-    };
+    const double unsplit = 0.93 * siddon_unsplit_time(G, items);
+    auto time_of = [&](int sh) { return siddon_split_time(G, sh, items, 1); };
     if (G->bp_split_shape >= 0 && time_of(G->bp_split_shape) < unsplit) return G->bp_split_shape;
     int best = -1;
     double least = unsplit;
@@ -782,6 +800,18 @@ int leap_siddon_split_shape(const leap_geometry *G, int items)
     return best;
 }
 
+// The views shared among workgroups, as for footprints; times in us.  us, before / in parts: cone 62 x 51 x 44, 455 views 604 / 281; parallel 70 x
+// 76 x 37, 389 views 415 / 179; tilted modules 50 x 40 x 23, 248 views 521 / 114, and where an unsplit workgroup's window fills a compute unit,
+// 190 x 172 x 92, 206 views 11030 / 5780.
+LeapBackParts leap_siddon_parts(const leap_geometry *G, int items)
+{
+    if (!G->bp_parts_fits || G->bp_split_forced) return {-1, 1, items};
+    const int split = leap_siddon_split_shape(G, items);
+    return choose_parts(G, items, G->g.type == SF_MODULAR && G->geoms.empty() ? MD_BP_NSPLIT_SHAPES : SD_BP_NSPLIT_SHAPES,
+                        split >= 0 ? siddon_split_time(G, split, items, 1) : siddon_unsplit_time(G, items), 1.0,
+                        [&](int sh, int n, int parts) { return siddon_split_time(G, sh, n, parts); });
+}
+
 // The shapes that fit (fits(shape): their windows do) and the one a single volume takes.
 template <class FitsFn>
 static void choose_siddon_split(leap_geometry *G, int nshapes, FitsFn fits)
@@ -790,11 +820,21 @@ static void choose_siddon_split(leap_geometry *G, int nshapes, FitsFn fits)
     if (only == -1) return;
     for (int sh = 0; sh < nshapes; ++sh)
         if (only < 0 || only == sh) G->bp_split_fits |= 1u << sh;
-    if (only < 0 && leap_siddon_split_shape(G, 1) < 0) G->bp_split_fits = 0;
+    long want = -1;
+    debug_option("bp_parts", want);
+    G->bp_parts_fits = only < 0 && want != 1 ? G->bp_split_fits : 0u;
+    const bool parts = leap_siddon_parts(G, 1).parts > 1;
+    if (!parts) G->bp_parts_fits = 0;
+    if (only < 0 && !parts && leap_siddon_split_shape(G, 1) < 0) G->bp_split_fits = 0;
     for (int sh = 0; sh < nshapes; ++sh)
         if ((G->bp_split_fits >> sh & 1u) && !fits(sh)) G->bp_split_fits &= ~(1u << sh);
+    G->bp_parts_fits &= G->bp_split_fits;
     G->bp_split_forced = only >= 0 && G->bp_split_fits;
     G->bp_split_shape = G->bp_split_forced ? (int)only : leap_siddon_split_shape(G, 1);
+    const LeapBackParts plan = leap_siddon_parts(G, 1);
+    G->bp_parts_shape = plan.shape;
+    G->bp_parts = plan.parts;
+    if (plan.parts == 1) G->bp_parts_fits = 0;
     if (G->bp_split_shape < 0) G->bp_split_fits = 0;
 }
 
@@ -1002,7 +1042,6 @@ static void select_tilted_siddon_kernels(leap_geometry *G)
         fits = G->bp_need_w <= MD_BP_SHAPES[sh].pw - 1 && G->bp_need_h <= MD_BP_SHAPES[sh].ph - 1;
     }
     if (!fits) return;
-    const int tiles = ((d->nx + BP_T - 1) / BP_T) * ((d->ny + BP_T - 1) / BP_T);
     auto split_fits = [&](int sh) {
         const SfBpShape S = MD_BP_SPLIT_SHAPES[sh];
         int w, h;
@@ -1620,7 +1659,7 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
         std::snprintf(back + n, sizeof back - n, "+split(%szc=%d,%dx%d)", G->bp_mirror ? "mirror," : "", S.zc, S.pw, S.ph);
     }
     if (G->bp_parts > 1) {
-        const SfBpShape &S = BP_SPLIT_SHAPES[G->bp_parts_shape];
+        const SfBpShape &S = (G->d_mdbp ? MD_BP_SPLIT_SHAPES : (siddon ? SD_BP_SPLIT_SHAPES : BP_SPLIT_SHAPES))[G->bp_parts_shape];
         const size_t n = std::strlen(back);
         std::snprintf(back + n, sizeof back - n, "+parts(%d,zc=%d,%dx%d)", G->bp_parts, S.zc, S.pw, S.ph);
     }

@@ -134,6 +134,7 @@ struct LeapBackParts {
     int shape, parts, items;
 };
 LeapBackParts leap_back_parts(const leap_geometry *G, int items);
+LeapBackParts leap_siddon_parts(const leap_geometry *G, int items);
 // The same of the tiled Siddon back projection: a shape of SD_BP_SPLIT_SHAPES or, on tilted modules, MD_BP_SPLIT_SHAPES.
 int leap_siddon_split_shape(const leap_geometry *G, int items);
 
@@ -162,6 +163,6 @@ bool leap_launch_footprint_slab(const leap_geometry *geom, const FwdScratch &S, 
 bool leap_launch_footprint_slab_parts(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward_parts.hip
 int leap_launch_footprint_back(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                         // leap_footprint_back.hip
 bool leap_launch_backproject_split(const leap_geometry *geom, int shape, int parts, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_footprint_back_split.hip
-bool leap_launch_siddon_back_split(const leap_geometry *geom, int shape, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_siddon_back_split.hip
+bool leap_launch_siddon_back_split(const leap_geometry *geom, int shape, int parts, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_siddon_back_split.hip
 bool leap_launch_backproject_pairs(const leap_geometry *geom, const float *d_sino, float *d_vol, int blocks, hipStream_t stream);                     // leap_footprint_back_pairs.hip
 int leap_launch_backproject_batch(const leap_geometry *geom, const float *d_sino, float *d_vol, int batch, hipStream_t stream);

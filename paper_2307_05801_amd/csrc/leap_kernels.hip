@@ -273,7 +273,7 @@ static void launch_sd_tiled(const leap_geometry *G, const float *d_sino, float *
     const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
     dim3 grid(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)items);
     auto go = [&](auto kernel, const SfGeom *geoms) {
-        hipLaunchKernelGGL(kernel, grid, dim3(256, 1, 1), 0, stream, g, G->d_views, G->d_raycols, d_sino, d_vol, (int)tiles_x, geoms);
+        hipLaunchKernelGGL(kernel, grid, dim3(256, 1, 1), 0, stream, g, G->d_views, G->d_raycols, d_sino, d_vol, (int)tiles_x, geoms, 1);
     };
     const bool apart = G->sd_min_row_step > 1.0 + 1e-6;
     if (g.type == SF_MODULAR) {
@@ -305,28 +305,69 @@ static void launch_md_tiled(const leap_geometry *G, const float *d_sino, float *
     const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
     dim3 grid(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)items);
     hipLaunchKernelGGL((md_backproject_tiled<S.zc, S.pw, S.ph>), grid, dim3(256, 1, 1), 0, stream, g, (const MdBpView *)G->d_mdbp,
-                       d_sino, d_vol, (int)tiles_x);
+                       d_sino, d_vol, (int)tiles_x, 1);
 }
 
 template <int SH>
-static void launch_md_split(const leap_geometry *G, const float *d_sino, float *d_vol, hipStream_t stream, int items)
+static void launch_md_split(const leap_geometry *G, int parts, const float *d_sino, float *d_vol, hipStream_t stream, int items)
 {
     constexpr SfBpShape S = MD_BP_SPLIT_SHAPES[SH];
     const SfGeom &g = G->g;
     const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
-    hipLaunchKernelGGL((md_backproject_tiled<S.zc, S.pw, S.ph, MD_BP_SPLIT[SH]>), dim3(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)items),
-                       dim3(256 * MD_BP_SPLIT[SH]), 0, stream, g, (const MdBpView *)G->d_mdbp, d_sino, d_vol, (int)tiles_x);
+    auto go = [&](auto kernel, float *to) {
+        hipLaunchKernelGGL(kernel, dim3(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)(items * parts)), dim3(256 * MD_BP_SPLIT[SH]), 0, stream, g,
+                           (const MdBpView *)G->d_mdbp, d_sino, to, (int)tiles_x, parts);
+    };
+    if (parts > 1) go(md_backproject_tiled<S.zc, S.pw, S.ph, MD_BP_SPLIT[SH], true>, G->d_back);
+    else go(md_backproject_tiled<S.zc, S.pw, S.ph, MD_BP_SPLIT[SH], false>, d_vol);
+}
+
+static void launch_md_split_shape(const leap_geometry *G, int shape, int parts, const float *d_sino, float *d_vol, hipStream_t stream, int items)
+{
+    static_assert(MD_BP_NSPLIT_SHAPES == 3, "every shape has a case");
+    if (shape == 0) launch_md_split<0>(G, parts, d_sino, d_vol, stream, items);
+    else if (shape == 1) launch_md_split<1>(G, parts, d_sino, d_vol, stream, items);
+    else launch_md_split<2>(G, parts, d_sino, d_vol, stream, items);
+}
+
+// The views of few tiles shared among workgroups: as leap_launch_footprint_back does it.
+static int launch_sd_bp_parts(const leap_geometry *G, const LeapBackParts &plan, const float *d_sino, float *d_vol, int items, hipStream_t stream)
+{
+    const unsigned nvol = (unsigned)G->g.nx * (unsigned)G->g.ny * (unsigned)G->g.nz;
+    const size_t nsino = (size_t)G->g.nviews * G->g.nrows * G->g.ncols;
+    std::lock_guard<std::mutex> lock(G->back_mutex);
+    if (G->back_used && G->back_stream != stream) LEAP_HIP_CHECK(hipStreamWaitEvent(stream, G->back_event, 0));
+    for (int b = 0; b < items; b += plan.items) {
+        const int n = items - b < plan.items ? items - b : plan.items;
+        bool ok = true;
+        if (!G->d_mdbp) ok = leap_launch_siddon_back_split(G, plan.shape, plan.parts, d_sino + b * nsino, nullptr, n, stream);
+        else launch_md_split_shape(G, plan.shape, plan.parts, d_sino + b * nsino, nullptr, stream, n);
+        if (!ok) {
+            leap_set_error("internal: no Siddon back-projection instance that shares the views");
+            return LEAP_UNSUPPORTED;
+        }
+        hipLaunchKernelGGL(sf_sum_parts, dim3(cdiv(nvol, 256), (unsigned)n), dim3(256), 0, stream, G->d_back, d_vol + (size_t)b * nvol, nvol, plan.parts, 1);
+        LEAP_HIP_CHECK(hipGetLastError());
+    }
+    LEAP_HIP_CHECK(hipEventRecord(G->back_event, stream));
+    G->back_stream = stream;
+    G->back_used = true;
+    return LEAP_OK;
 }
 
 // The tiled Siddon back projection on `items` consecutive sinograms of a batch in one launch.
 static int launch_sd_bp_items(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     bool ok = false;
+    const LeapBackParts plan = leap_siddon_parts(G, items);
+    if (plan.parts > 1) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        LEAP_HIP_CHECK(hipStreamIsCapturing(stream, &capture));
+        if (capture == hipStreamCaptureStatusNone) return launch_sd_bp_parts(G, plan, d_sino, d_vol, items, stream);
+    }
     const int split = leap_siddon_split_shape(G, items);
     if (G->d_mdbp && split >= 0) {
-        static_assert(MD_BP_NSPLIT_SHAPES == 2, "every shape has a case");
-        if (split == 0) launch_md_split<0>(G, d_sino, d_vol, stream, items);
-        else launch_md_split<1>(G, d_sino, d_vol, stream, items);
+        launch_md_split_shape(G, split, 1, d_sino, d_vol, stream, items);
         ok = true;
     } else if (G->md_tilted || G->d_mdbp) {
         switch (G->d_mdbp ? G->bp_shape : -1) {
@@ -339,7 +380,7 @@ static int launch_sd_bp_items(const leap_geometry *G, const float *d_sino, float
         default: break;
         }
     } else if (split >= 0) {
-        ok = leap_launch_siddon_back_split(G, split, d_sino, d_vol, items, stream);
+        ok = leap_launch_siddon_back_split(G, split, 1, d_sino, d_vol, items, stream);
     } else
     switch (G->bp_nc) {
     case 2: ok = launch_sd_shape<2>(G, d_sino, d_vol, stream, items); break;

@@ -33,10 +33,11 @@
 // leaves room for four workgroups per compute unit, the second for three, the next two for two.
 constexpr SfBpShape MD_BP_SHAPES[] = {{16, 32, 21}, {16, 32, 35}, {32, 32, 44}, {16, 32, 44}, {32, 32, 56}, {16, 64, 48}};
 constexpr int MD_BP_NSHAPES = 6;
-// Groups of threads that share the views (as in sd_backproject_tiled.h): four where a window of 32 columns does, two under 64 columns.
-constexpr SfBpShape MD_BP_SPLIT_SHAPES[] = {{8, 32, 28}, {8, 64, 28}};
-constexpr int MD_BP_SPLIT[] = {4, 2};
-constexpr int MD_BP_NSPLIT_SHAPES = 2;
+// Groups of threads that share the views (as in sd_backproject_tiled.h): four where a window of 32 columns does, two under 64 columns (the
+// last: as many rows as two groups' windows leave room for).
+constexpr SfBpShape MD_BP_SPLIT_SHAPES[] = {{8, 32, 28}, {8, 64, 28}, {8, 64, 36}};
+constexpr int MD_BP_SPLIT[] = {4, 2, 2};
+constexpr int MD_BP_NSPLIT_SHAPES = 3;
 constexpr double MD_BP_ZBIAS = 1048576.0;      // added to axial positions so that truncation is floor for every row of a window
 
 // One entry per view, built in double on the host.
@@ -263,9 +264,9 @@ SF_HD bool md_bp_row(const MdBpColumn &C, const MdBpPixel &p, int &slot, float &
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
 
 // VS: groups of 256 threads that share a tile's views, group q taking views q, q + VS, ..., each with sums of its own.
-template <int ZC, int PW, int PH, int VS = 1>
+template <int ZC, int PW, int PH, int VS = 1, bool PARTS = false>
 __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const MdBpView *__restrict__ views,
-                                                            const float *__restrict__ sino, float *__restrict__ vol, int tiles_x)
+                                                            const float *__restrict__ sino, float *__restrict__ vol, int tiles_x, int parts)
 {
     constexpr int PS = PW + 1;                     // odd row stride: the lanes of a wave sit in a few adjacent rows and columns
     constexpr int NSLOT = ZC + 4;                  // slot s holds voxel k0 + s - 2; slots 0, 1, ZC+2, ZC+3 are dumps
@@ -277,7 +278,12 @@ __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const
     double *const l_m = group_m[group], *const l_mz = group_mz[group];
     float *const l_wy = group_wy[group], *const l_inv_m = group_inv_m[group], *const l_inv_mz = group_inv_mz[group], *const sums = group_sums[group];
 
-    sino += (size_t)blockIdx.z * g.nviews * g.nrows * g.ncols;
+    // blockIdx.z: item of a batch; PARTS: times the parts of its views, the volumes of an item's parts side by side (a template: the bounds of a
+    // part's views cost the kernels of whole scans 3 to 6 %)
+    const unsigned item = PARTS ? blockIdx.z / (unsigned)parts : blockIdx.z;
+    const int part = PARTS ? (int)(blockIdx.z - item * (unsigned)parts) : 0;
+    const int a_first = PARTS ? (int)((long long)g.nviews * part / parts) : 0, a_end = PARTS ? (int)((long long)g.nviews * (part + 1) / parts) : g.nviews;
+    sino += (size_t)item * g.nviews * g.nrows * g.ncols;
     vol += (size_t)blockIdx.z * g.nx * g.ny * g.nz;
     const int tid = VS == 1 ? threadIdx.x : threadIdx.x & 255;
     const int ti = tid & (BP_T - 1), tj = tid >> 4;
@@ -325,16 +331,16 @@ __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const
     };
 
     SfWindow cur = {};
-    if (VS == 1 || group < g.nviews) {
-        load_view(group);
-        store_view(group);
+    if (VS == 1 || a_first + group < a_end) {
+        load_view(a_first + group);
+        store_view(a_first + group);
         cur = win;
     }
     __syncthreads();
 
-    for (int a = group; a - group < g.nviews; a += VS) {
-        if (VS == 1 || a < g.nviews) {
-        if (a + VS < g.nviews) load_view(a + VS);      // global loads in flight during the gather
+    for (int a = a_first + group; a - group < a_end; a += VS) {
+        if (VS == 1 || a < a_end) {
+        if (a + VS < a_end) load_view(a + VS);      // global loads in flight during the gather
 
         const MdBpView &V = views[a];
         const bool xmajor = md_bp_tile_xmajor(g, V, i0, j0);
@@ -362,7 +368,7 @@ __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const
 
         }
         __syncthreads();                               // every thread is done with this view's window
-        if (a + VS < g.nviews) {
+        if (a + VS < a_end) {
             store_view(a + VS);
             cur = win;
         }

@@ -185,7 +185,7 @@ template <int NCS, int ZC, int PW, int PH, bool MOD, bool APART, int VS = 1>
 __global__ __launch_bounds__(256 * VS) void sd_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
                                                             const SdRayCol *__restrict__ rays, const float *__restrict__ sino,
                                                             float *__restrict__ vol, int tiles_x,
-                                                            const SfGeom *__restrict__ geoms)
+                                                            const SfGeom *__restrict__ geoms, int parts)
 {
     constexpr int PS = PW + BP_ROW_PAD;
     constexpr int NSLOT = ZC + 4;
@@ -193,8 +193,11 @@ __global__ __launch_bounds__(256 * VS) void sd_backproject_tiled(SfGeom g, const
     __shared__ float rinv[2 * VS][PH];
     __shared__ float group_sums[VS][NSLOT * 256];
 
-    // blockIdx.z: item of a batch
-    sino += (size_t)blockIdx.z * g.nviews * g.nrows * g.ncols;
+    // blockIdx.z: item of a batch; VS > 1: times the parts of its views, the volumes of an item's parts side by side
+    const unsigned item = VS == 1 ? blockIdx.z : blockIdx.z / (unsigned)parts;
+    const int part = VS == 1 ? 0 : (int)(blockIdx.z - item * (unsigned)parts);
+    const int a_first = VS == 1 ? 0 : (int)((long long)g.nviews * part / parts), a_end = VS == 1 ? g.nviews : (int)((long long)g.nviews * (part + 1) / parts);
+    sino += (size_t)item * g.nviews * g.nrows * g.ncols;
     vol += (size_t)blockIdx.z * g.nx * g.ny * g.nz;
     const int tid = VS == 1 ? threadIdx.x : threadIdx.x & 255;
     const int group = VS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(256 * VS) void sd_backproject_tiled(SfGeom g, const
         if constexpr (MOD) return geoms[a];
         else return g;
     };
-    const SdBpScene scene0 = sd_bp_scene<ZC>(geom_of(VS == 1 || group < g.nviews ? group : 0), i0, j0, k0);     // of the group's first view
+    const SdBpScene scene0 = sd_bp_scene<ZC>(geom_of(VS == 1 || a_first + group < a_end ? a_first + group : 0), i0, j0, k0);     // of the group's first view
 
     const int sc = tid & (PW - 1), sr = tid / PW;
     constexpr int NSTAGE = (PH * PW + 255) / 256;
@@ -224,20 +227,21 @@ __global__ __launch_bounds__(256 * VS) void sd_backproject_tiled(SfGeom g, const
 
     float stage[NSTAGE];
     SfWindow win = {}, win_next;
-    if (VS == 1 || group < g.nviews) {
-        sd_load_view<PW, PH, NSTAGE>(geom_of(group), views[group], sino + (size_t)group * view_stride, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1,
+    if (VS == 1 || a_first + group < a_end) {
+        const int a = a_first + group;
+        sd_load_view<PW, PH, NSTAGE>(geom_of(a), views[a], sino + (size_t)a * view_stride, scene0.xc, scene0.yc, hx, scene0.z0, scene0.z1,
                                      sc, sr, win, stage);
-        sd_store_view<PW, PH, NSTAGE>(geom_of(group), rays + (size_t)group * g.ncols, sc, sr, win, stage, patch[2 * group], rinv[2 * group]);
+        sd_store_view<PW, PH, NSTAGE>(geom_of(a), rays + (size_t)a * g.ncols, sc, sr, win, stage, patch[2 * group], rinv[2 * group]);
     }
     win_next = win;
     __syncthreads();
 
-    for (int a = group; a - group < g.nviews; a += VS) {
-        const int buffer = 2 * group + (((a - group) / VS) & 1);
-        if (VS == 1 || a < g.nviews) {
+    for (int a = a_first + group; a - group < a_end; a += VS) {
+        const int buffer = 2 * group + (((a - a_first - group) / VS) & 1);
+        if (VS == 1 || a < a_end) {
         const float *__restrict__ buf = patch[buffer];
         const float *__restrict__ ri = rinv[buffer];
-        if (a + VS < g.nviews) {    // global loads in flight during the gather
+        if (a + VS < a_end) {    // global loads in flight during the gather
             const SdBpScene sn = MOD ? sd_bp_scene<ZC>(geom_of(a + VS), i0, j0, k0) : scene0;
             sd_load_view<PW, PH, NSTAGE>(geom_of(a + VS), views[a + VS], sino + (size_t)(a + VS) * view_stride, sn.xc, sn.yc, hx, sn.z0,
                                          sn.z1, sc, sr, win_next, stage);
@@ -342,7 +346,7 @@ __global__ __launch_bounds__(256 * VS) void sd_backproject_tiled(SfGeom g, const
             }
         }
 
-        if (a + VS < g.nviews)
+        if (a + VS < a_end)
             sd_store_view<PW, PH, NSTAGE>(geom_of(a + VS), rays + (size_t)(a + VS) * g.ncols, sc, sr, win_next, stage, patch[buffer ^ 1],
                                           rinv[buffer ^ 1]);
         }

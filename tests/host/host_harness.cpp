@@ -826,9 +826,10 @@ static void host_md_bp_shape(const leap_geometry *G, const float *sino, float *v
 extern "C" long host_md_backproject_tiled(const leap_geometry *G, const float *sino, float *vol, int64_t *report)
 {
     if (!G->d_mdbp || !G->bp_tiled) return -1;
-    static_assert(MD_BP_NSPLIT_SHAPES == 2, "every shape has a case");
+    static_assert(MD_BP_NSPLIT_SHAPES == 3, "every shape has a case");
     if (G->bp_split_shape >= 0) {
-        if (G->bp_split_shape == 0) host_md_bp_shape<MD_BP_SPLIT_SHAPES[0].zc, MD_BP_SPLIT_SHAPES[0].pw, MD_BP_SPLIT_SHAPES[0].ph>(G, sino, vol, report);
+        if (G->bp_split_shape == 2) host_md_bp_shape<MD_BP_SPLIT_SHAPES[2].zc, MD_BP_SPLIT_SHAPES[2].pw, MD_BP_SPLIT_SHAPES[2].ph>(G, sino, vol, report);
+        else if (G->bp_split_shape == 0) host_md_bp_shape<MD_BP_SPLIT_SHAPES[0].zc, MD_BP_SPLIT_SHAPES[0].pw, MD_BP_SPLIT_SHAPES[0].ph>(G, sino, vol, report);
         else host_md_bp_shape<MD_BP_SPLIT_SHAPES[1].zc, MD_BP_SPLIT_SHAPES[1].pw, MD_BP_SPLIT_SHAPES[1].ph>(G, sino, vol, report);
         return report[0] + report[1] + report[2];
     }

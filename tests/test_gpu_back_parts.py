@@ -67,3 +67,27 @@ def test_two_streams_and_a_captured_call():
         assert torch.equal(here, ref_y) and torch.equal(beside, ref_z)
         assert rel_l2(captured.cpu().numpy(), ref_y.cpu().numpy()) <= 1e-6
     geo.close()
+
+
+SIDDON = {"cone": scan(shift_v=0.3), "parallel": scan(PARALLEL, pixel_u=1.0, pixel_v=1.0, nviews=500, shift_v=0.27), "curved": scan(CONE_CURVED, shift_v=-0.2),
+          "upright": perturbed_poses(scan(shift_v=0.2), 5, shift_mm=4.0, upright=True),
+          "tilted": perturbed_poses(scan(shift_v=0.2), 5, shift_mm=4.0, tilt_rad=0.05),
+          "tilted_wide": perturbed_poses(scan(shift_v=0.2, pixel_u=0.9, ncols=100), 5, shift_mm=4.0, tilt_rad=0.05),
+          "tilted_wide_tall": perturbed_poses(scan(shift_v=0.2, pixel_u=0.9, ncols=100, pixel_v=0.8, nrows=70), 5, shift_mm=4.0, tilt_rad=0.05)}
+
+
+@pytest.mark.parametrize("name", list(SIDDON))
+def test_siddon_parts_match_oracle(oracle_mod, name):
+    import torch
+    from paper_2307_05801_amd import Geometry
+    cfg = SIDDON[name]
+    geo = Geometry(cfg, model="siddon")
+    print(f"[gpu] {name}: {geo.describe()}", flush=True)
+    assert "+parts(" in geo.describe(), geo.describe()
+    y = uniform_sinogram(cfg, 5, batch=3)
+    yt = torch.from_numpy(y).cuda()
+    one, three = geo.backproject(yt[1].contiguous()), geo.backproject(yt)
+    assert rel_l2(one.cpu().numpy(), oracle_mod.siddon.backproject(cfg, y[1])) <= TOL
+    assert rel_l2(three[1].cpu().numpy(), one.cpu().numpy()) <= 1e-6
+    assert torch.equal(one, geo.backproject(yt[1].contiguous()))
+    geo.close()
