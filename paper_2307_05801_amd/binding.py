@@ -153,8 +153,10 @@ def leap_geometry_describe(handle: int, lib=None) -> str:
 
 def leap_project(handle: int, d_vol: int, d_sino: int, batch: int, stream: int = 0, lib=None) -> None:
     """d_vol, d_sino: device addresses (tensor.data_ptr()); stream: hipStream_t as an integer."""
-    lib = lib or load_library()
-    _check(lib, lib.leap_project(C.c_void_p(handle), C.c_void_p(d_vol), C.c_void_p(d_sino), batch, C.c_void_p(stream)))
+    lib = lib or _lib or load_library()
+    status = lib.leap_project(handle, d_vol, d_sino, batch, stream)       # (the prototypes turn the integers into pointers)
+    if status != LEAP_OK:
+        _check(lib, status)
 
 
 def leap_project_static_scratch(handle: int, d_vol: int, d_sino: int, batch: int, stream: int = 0, lib=None) -> None:
@@ -176,8 +178,10 @@ def leap_backproject_host(handle: int, h_sino: int, h_vol: int, batch: int, lib=
 
 
 def leap_backproject(handle: int, d_sino: int, d_vol: int, batch: int, stream: int = 0, lib=None) -> None:
-    lib = lib or load_library()
-    _check(lib, lib.leap_backproject(C.c_void_p(handle), C.c_void_p(d_sino), C.c_void_p(d_vol), batch, C.c_void_p(stream)))
+    lib = lib or _lib or load_library()
+    status = lib.leap_backproject(handle, d_sino, d_vol, batch, stream)
+    if status != LEAP_OK:
+        _check(lib, status)
 
 
 def leap_recon_workspace_floats(handle: int, lib=None) -> int:

@@ -11,6 +11,10 @@ import torch
 from . import binding as B
 
 
+# The current HIP stream of a device as an integer, without a Stream object around it (which takes as long to make as half a launch).
+_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 class Geometry:
     """Owns one leap_geometry handle on one GPU."""
 
@@ -29,17 +33,11 @@ class Geometry:
             desc, keep = B.make_desc(model=B.MODELS[model], **desc_kwargs)
         self.nviews, self.nrows, self.ncols = desc.nviews, desc.nrows, desc.ncols
         self.nx, self.ny, self.nz = desc.nx, desc.ny, desc.nz
+        self.vol_shape = (self.nz, self.ny, self.nx)
+        self.sino_shape = (self.nviews, self.nrows, self.ncols)
         with torch.cuda.device(self.device):
             self.handle = B.leap_geometry_create(desc)
         del keep
-
-    @property
-    def vol_shape(self):
-        return (self.nz, self.ny, self.nx)
-
-    @property
-    def sino_shape(self):
-        return (self.nviews, self.nrows, self.ncols)
 
     def describe(self) -> str:
         return B.leap_geometry_describe(self.handle)
@@ -62,35 +60,45 @@ class Geometry:
     def _check(self, t: torch.Tensor, shape, what: str) -> int:
         if t.device != self.device or t.dtype != torch.float32 or not t.is_contiguous():
             raise ValueError(f"{what} must be a contiguous float32 tensor on {self.device}")
-        if tuple(t.shape[-3:]) != tuple(shape):
-            raise ValueError(f"{what} must end in shape {tuple(shape)}, got {tuple(t.shape)}")
+        dims = t.shape
+        if dims == shape:
+            return 1
+        if dims[-3:] != shape:
+            raise ValueError(f"{what} must end in shape {tuple(shape)}, got {tuple(dims)}")
         batch = 1
-        for n in t.shape[:-3]:
+        for n in dims[:-3]:
             batch *= n
         if batch < 1:
             raise ValueError("empty batch")
         return batch
 
+    def _call(self, operator, src: torch.Tensor, out: torch.Tensor, batch: int) -> None:
+        """operator(handle, src, out, batch, stream) with this geometry's device current, on its current stream."""
+        index = src.device.index
+        if torch.cuda.current_device() == index:          # (entering a device context takes longer than a small call's launch)
+            operator(self.handle, src.data_ptr(), out.data_ptr(), batch, _current_stream(index))
+        else:
+            with torch.cuda.device(index):
+                operator(self.handle, src.data_ptr(), out.data_ptr(), batch, _current_stream(index))
+
     def project(self, vol: torch.Tensor, out: torch.Tensor = None) -> torch.Tensor:
         """A vol; vol [..., nz, ny, nx] -> [..., nviews, nrows, ncols]."""
         batch = self._check(vol, self.vol_shape, "volume")
         if out is None:
-            out = torch.empty(tuple(vol.shape[:-3]) + self.sino_shape, dtype=torch.float32, device=self.device)
+            out = vol.new_empty(vol.shape[:-3] + self.sino_shape)
         elif self._check(out, self.sino_shape, "output sinogram") != batch:
             raise ValueError("output batch mismatch")
-        with torch.cuda.device(self.device):
-            B.leap_project(self.handle, vol.data_ptr(), out.data_ptr(), batch, torch.cuda.current_stream().cuda_stream)
+        self._call(B.leap_project, vol, out, batch)
         return out
 
     def backproject(self, sino: torch.Tensor, out: torch.Tensor = None) -> torch.Tensor:
         """A^T sino; sino [..., nviews, nrows, ncols] -> [..., nz, ny, nx]."""
         batch = self._check(sino, self.sino_shape, "sinogram")
         if out is None:
-            out = torch.empty(tuple(sino.shape[:-3]) + self.vol_shape, dtype=torch.float32, device=self.device)
+            out = sino.new_empty(sino.shape[:-3] + self.vol_shape)
         elif self._check(out, self.vol_shape, "output volume") != batch:
             raise ValueError("output batch mismatch")
-        with torch.cuda.device(self.device):
-            B.leap_backproject(self.handle, sino.data_ptr(), out.data_ptr(), batch, torch.cuda.current_stream().cuda_stream)
+        self._call(B.leap_backproject, sino, out, batch)
         return out
 
 
