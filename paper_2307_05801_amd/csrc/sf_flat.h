@@ -19,8 +19,8 @@
 //
 // Measured, A + A^T, against the general kernels (one thread per ray and item, three quarters of a block idle on one row):
 // 8 slices of 512^2, 720 views of 736 columns 40.7 -> 3.0 ms; one slice of 64^2, 90 views 237 -> 23 us.  A since then (an odd number of
-// tiles per view, voxels fetched ahead, the turned copy, no records for parallel beams): the 8 slices 1.95 -> 1.73 ms; one slice of 361 x 379,
-// 577 parallel views of 409 columns 636 -> 415 us; 223 x 246, 271 fan views 159 -> 131 us; 32 drawn scans 0.82 (geometric mean).
+// tiles per view where there are many, voxels fetched ahead, the turned copy, no records for parallel beams): the 8 slices 1.95 -> 1.73 ms; one slice of 361 x 379,
+// 577 parallel views of 409 columns 636 -> 415 us; 223 x 246, 271 fan views 159 -> 131 us; one slice of 64^2, 90 parallel views, the kernel alone 10.5 -> 7.8 us.
 #pragma once
 
 #include "sf_footprint.h"
@@ -33,10 +33,10 @@ constexpr int FLAT_MAX_WAVES = 16;   // waves of a workgroup that share its slab
 // item, none / 1 / 2 / 3 / 4 ahead: fan 223 x 246, 271 views of 295 160 / 136 / 132 / 129 / 132 us; eight: 450 x 373, 553 views of 408 816 /
 // 752 (none, without the grid's idle tiles) / 727 / 708 (2) us.
 constexpr int FLAT_AHEAD = 3, FLAT_AHEAD_8 = 2;
-// Fewest wave steps (views, tiles of 64 columns, slabs) for which a launch of several items makes the turned copy as well, fan / parallel
-// beams.  With over without: fan 36000 to 76000 steps 1.07 to 1.13, 1400000 and 4400000 0.96 and 0.95; parallel 32000 1.05, 46000 0.90,
-// 950000 0.77.  One item gains nothing.
-constexpr double FLAT_TURN_STEPS = 3e5, FLAT_TURN_STEPS_PARALLEL = 4e4;
+// Fewest wave steps (views, tiles of 64 columns, slabs, groups of items) for which a launch of several items makes the turned copy as well,
+// fan / parallel beams.  With over without: fan 36000 to 148000 steps 1.04 to 1.13, 226000 0.83, 282000 1.00, 1400000 and 4400000 0.96 and
+// 0.95; parallel 32000 1.05, 46000 0.90, 950000 0.77.  One item gains nothing.
+constexpr double FLAT_TURN_STEPS = 2e5, FLAT_TURN_STEPS_PARALLEL = 4e4;
 constexpr int FLAT_T = 8;            // tile edge of the back projection, voxels
 // Widest footprint of any voxel, in detector columns, and the columns a voxel can then touch.  A tile's voxel lies at most
 // 4 sqrt(2) T from the voxel the window is centred on, and a displacement of sqrt(2) T moves the shadow by at most the
@@ -149,7 +149,7 @@ __device__ __forceinline__ void flat_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// grid.x = views * tiles of 64 columns, tiles rounded up to an odd number: workgroups go to the 8 XCDs by index in turn, and an XCD that gets
+// grid.x = views * tiles of 64 columns, tiles rounded up to an odd number where there are many: workgroups go to the 8 XCDs by index in turn, and an XCD that gets
 // the same tile of every view finishes early if it is one at the detector's edge.  grid.y: groups of NB items (NB == 1: items).  Block: waves
 // that share the slabs.  src: NB == 1 the slices themselves, otherwise the batch-fastest copy of this launch's items; turned: the copy whose
 // rows run along y, for waves whose slabs do (nullptr: they read src across its rows).  span: records per wave
@@ -175,12 +175,16 @@ __global__ __launch_bounds__(FLAT_MAX_WAVES * 64) void sf_project_flat(SfGeom g,
     const bool across = xmajor && !turned;
     src = (xmajor && turned ? turned : src) + (size_t)blockIdx.y * nvol * NB;
     const unsigned n_stride = across ? 1u : (unsigned)n_minor, q_stride = across ? (unsigned)g.nx : 1u;
-    const int n_end = (int)((long long)n_major * (wave + 1) / nwaves);
+    // the wave's slabs: n_major * wave / nwaves on, nwaves a power of two (64-bit divisions cost the smallest calls a microsecond)
+    const int share = 31 - __builtin_clz(nwaves), whole = n_major >> share, rest = n_major - (whole << share);
+    const int n_begin = whole * wave + (rest * wave >> share), n_end = n_begin + whole + ((rest * (wave + 1) >> share) - (rest * wave >> share));
+    // PAR: how far the footprint moves on the detector from one voxel of a slab to the next
+    const double step = xmajor ? g.Td * v.cd * g.kud : -g.Td * v.sd * g.kud;
 
     float acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = 0.0f;
-    for (int n = (int)((long long)n_major * wave / nwaves); n < n_end; ++n) {
+    for (int n = n_begin; n < n_end; ++n) {
         int qf, ql;
         sf_candidates(L, n, qf, ql);
         // the beams of the outermost columns bound the run of voxels
@@ -213,8 +217,15 @@ __global__ __launch_bounds__(FLAT_MAX_WAVES * 64) void sf_project_flat(SfGeom g,
             }
         }
         if constexpr (!PAR) flat_wave_sync();
+        // PAR: the footprint of the lane's first candidate and the pixel's lower edge from its centre; the others' lie whole steps on
+        SfColumn first;
+        double edge = 0.0;
+        if constexpr (PAR) {
+            first = sf_flat_parallel_column(g, v, xmajor ? n : qf, xmajor ? qf : n);
+            edge = ((double)c - 0.5) - first.xi;
+        }
         auto weight = [&](int q) {
-            if constexpr (PAR) return sf_flat_fu(sf_flat_record(sf_flat_parallel_column(g, v, xmajor ? n : q, xmajor ? q : n)), c);
+            if constexpr (PAR) return sf_fu_at(first, (float)fma((double)(qf - q), step, edge));
             SfFlatRec r;
             reinterpret_cast<float4 *>(&r)[0] = rec_lo[q - q_lo];
             reinterpret_cast<float4 *>(&r)[1] = rec_hi[q - q_lo];

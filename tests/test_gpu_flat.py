@@ -109,3 +109,9 @@ def test_slices_turned_for_beams_along_x(oracle_mod, cfg):
     """Enough views that a batch is copied with its rows along y as well; an item alone reads the slice as it lies."""
     test_flat_kernels_match_oracle(oracle_mod, cfg, 5)
     test_flat_kernels_match_oracle(oracle_mod, cfg, 10)
+
+
+@pytest.mark.parametrize("cfg", [scan(kind, 61, 67, nviews, 170) for kind in (PARALLEL, FAN) for nviews in (170, 171)], ids=lambda c: f"{c.name}-{c.nviews}")
+def test_tiles_of_a_view_rounded_up_to_an_odd_number(oracle_mod, cfg):
+    """More than two tiles of 64 columns, on either side of the number of workgroups from which they are rounded up, and a batch of three."""
+    test_flat_kernels_match_oracle(oracle_mod, cfg, 3)
