@@ -579,14 +579,31 @@ static int project_flat(const leap_geometry *G, const float *d_vol, float *d_sin
     return LEAP_OK;
 }
 
+// Slices of up to 64 or 128 tiles of 8 x 8 voxels leave most of the compute units idle: their waves take the views in runs of four or two,
+// and in a launch of so few tiles (those of its groups of items together) four or two views of a run at a time, on tiles of 4 x 4 or
+// 8 x 4 voxels.  Four / two over one view at a time: 16 tiles 0.86 / 0.85, 64 (90 to 400 views) 0.44 to 0.78 / 0.69 to 0.82, 81 to 121
+// 0.65 to 1.16 / 0.68 to 0.75, 162 1.72 / 1.36, 169 to 256 0.83 to 1.20 / 1.04 to 1.09.
+constexpr double FLAT_FOUR_TILES = 64.0, FLAT_TWO_TILES = 128.0;
+
 template <int NB>
 static void launch_backproject_flat(const leap_geometry *G, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     const SfGeom &g = G->g;
-    const unsigned tiles_x = cdiv(g.nx, FLAT_T), tiles_y = cdiv(g.ny, FLAT_T), groups = cdiv((unsigned)items, NB);
-    const int waves = flat_waves((double)tiles_x * tiles_y, g.nviews);
-    hipLaunchKernelGGL(sf_backproject_flat<NB>, dim3(tiles_x * tiles_y, groups), dim3(64 * waves), (size_t)waves * 64 * NB * sizeof(float),
-                       stream, g, G->d_views, d_sino, d_vol, (int)tiles_x, items, G->flat_fv);
+    const unsigned groups = cdiv((unsigned)items, NB);
+    const double tiles = (double)cdiv(g.nx, FLAT_T) * cdiv(g.ny, FLAT_T);
+    const int waves = flat_waves(tiles, g.nviews);
+    const auto few = [&](double n) { return waves < FLAT_MAX_WAVES || n > FLAT_TWO_TILES ? 1 : (n > FLAT_FOUR_TILES ? 2 : 4); };
+    const int shares = few(tiles);                // (of the scan alone: an item comes out the same bits in any batch)
+    auto go = [&](auto kernel, auto tile, size_t lds) {
+        const unsigned tiles_x = cdiv(g.nx, decltype(tile)::TX), tiles_y = cdiv(g.ny, decltype(tile)::TY);
+        hipLaunchKernelGGL(kernel, dim3(tiles_x * tiles_y, groups), dim3(64 * waves), lds, stream, g, G->d_views, d_sino, d_vol, (int)tiles_x, items,
+                           shares, G->flat_fv);
+    };
+    switch (few(tiles * groups)) {
+    case 4: go(sf_backproject_flat<NB, 4>, FlatTile<4>(), 0); break;
+    case 2: go(sf_backproject_flat<NB, 2>, FlatTile<2>(), 0); break;
+    default: go(sf_backproject_flat<NB, 1>, FlatTile<1>(), (size_t)waves * 64 * NB * sizeof(float));
+    }
 }
 
 static int backproject_flat(const leap_geometry *G, const float *d_sino, float *d_vol, int batch, hipStream_t stream)

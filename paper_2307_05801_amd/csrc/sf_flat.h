@@ -15,12 +15,15 @@
 // kernel's bound beside issue where there is much to do: it then has a copy of its own, whose rows run along y (FLAT_TURN_STEPS).
 // Back (sf_backproject_flat): a wave owns 8 x 8 voxels and its share of the views.  Per view it loads the 64 detector
 // samples around the tile's shadow, one column per lane, times the ray amplitude, into LDS (batch fastest), and every lane
-// gathers its few columns.  No barrier: a wave reads only what it wrote.  Loads of the next view are in flight meanwhile.
+// gathers its few columns.  No barrier: a wave reads only what it wrote.  Loads of the next view are in flight meanwhile.  Slices of few such
+// tiles leave units idle (64 of 256 at work on 64^2): a wave then takes two or four views at a time on smaller tiles.  90 parallel views of
+// 64^2 7.1 -> 5.8 us, 360 20.8 -> 9.1; 90 fan views 9.2 -> 5.2; 16 slices, 360 fan views 37.9 -> 27.6.
 //
 // Measured, A + A^T, against the general kernels (one thread per ray and item, three quarters of a block idle on one row):
 // 8 slices of 512^2, 720 views of 736 columns 40.7 -> 3.0 ms; one slice of 64^2, 90 views 237 -> 23 us.  A since then (an odd number of
-// tiles per view where there are many, voxels fetched ahead, the turned copy, no records for parallel beams): the 8 slices 1.95 -> 1.73 ms; one slice of 361 x 379,
-// 577 parallel views of 409 columns 636 -> 415 us; 223 x 246, 271 fan views 159 -> 131 us; one slice of 64^2, 90 parallel views, the kernel alone 10.5 -> 7.8 us.
+// tiles per view where there are many, voxels fetched ahead, the turned copy, no records for parallel beams): the 8 slices 1.95 -> 1.73 ms;
+// one slice of 361 x 379, 577 parallel views of 409 columns 636 -> 415 us; 223 x 246, 271 fan views 159 -> 131 us; one slice of 64^2, 90
+// parallel views, the kernel alone 10.5 -> 7.8 us.
 #pragma once
 
 #include "sf_footprint.h"
@@ -262,71 +265,113 @@ __global__ __launch_bounds__(FLAT_MAX_WAVES * 64) void sf_project_flat(SfGeom g,
     }
 }
 
-// grid.x = tiles of 8 x 8 voxels; grid.y: groups of NB items.  Block: waves that share the views.
-template <int NB>
+// Tile and staged columns of the back projection by the number of views a wave takes at a time (SUB: 1, 2 or 4; 64 / SUB lanes each).  The
+// lanes beside the tile's middle voxel lie at most 4 sqrt(2), sqrt(20), 2 sqrt(2) voxels from it, so the columns they read lie within
+// 29, 25, 19 of its own (see FLAT_MAX_COLS).
+template <int SUB>
+struct FlatTile {
+    static constexpr int TX = SUB == 4 ? 4 : 8, TY = SUB == 1 ? 8 : 4, LANES = 64 / SUB, COLS = SUB == 4 ? 48 : 64, LOADS = COLS / LANES;
+};
+
+// grid.x = tiles of TX x TY voxels; grid.y: groups of NB items.  Block: waves that share the views; wave w takes runs of `shares` adjacent
+// views, shares w on, a run of every wave apart, and sums the first of every run, then the second, ...  SUB > 1 (16 waves, shares a multiple of SUB):
+// SUB views of a run at a time, so that slices whose 8 x 8 tiles are fewer than the compute units give every unit a workgroup.  The order of
+// the sums depends on shares alone: however many views a wave takes at a time, the bits are the same.
+template <int NB, int SUB>
 __global__ __launch_bounds__(FLAT_MAX_WAVES * 64) void sf_backproject_flat(SfGeom g, const SfView *__restrict__ views,
                                                                            const float *__restrict__ sino, float *__restrict__ vol,
-                                                                           int tiles_x, int items, float fv)
+                                                                           int tiles_x, int items, int shares, float fv)
 {
-    extern __shared__ float4 flat_lds[];
+    typedef FlatTile<SUB> Tile;
+    constexpr int LOADS = Tile::LOADS;
+    float *lds;
+    if constexpr (SUB > 1) {
+        __shared__ float room[FLAT_MAX_WAVES * SUB * Tile::COLS * NB];
+        lds = room;
+    } else {
+        extern __shared__ float4 flat_lds[];
+        lds = reinterpret_cast<float *>(flat_lds);
+    }
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
-    float *__restrict__ buf = reinterpret_cast<float *>(flat_lds) + wave * (64 * NB);       // [column][item]
+    const int sub = SUB == 1 ? 0 : lane / Tile::LANES, l = SUB == 1 ? lane : lane % Tile::LANES;
+    float *__restrict__ buf = lds + (wave * SUB + sub) * (Tile::COLS * NB);       // [column][item]
     const int ty = blockIdx.x / tiles_x, tx = blockIdx.x - ty * tiles_x;
-    const int i = tx * FLAT_T + (lane & 7), j = ty * FLAT_T + (lane >> 3);
+    const int i = tx * Tile::TX + l % Tile::TX, j = ty * Tile::TY + l / Tile::TX;
     const int ic = i < g.nx ? i : g.nx - 1, jc = j < g.ny ? j : g.ny - 1;    // lanes beyond the edge shadow it
     const size_t nsino = (size_t)g.nviews * g.ncols;
     const int b0 = blockIdx.y * NB;
     sino += (size_t)b0 * nsino;
 
-    float acc[NB], stage[NB];
+    float total[NB], acc[NB], stage[LOADS][NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = 0.0f;
+    for (int b = 0; b < NB; ++b) total[b] = 0.0f;
     SfColumn f;
     int first = 0;                              // first staged column
+    // a: the first of the SUB views; one beyond the last is read as zeros
+    auto view_of = [&](int a) { return SUB == 1 ? a : (a + sub < g.nviews ? a + sub : g.nviews - 1); };
     auto fetch = [&](int a) {
-        f = sf_column<0>(g, views[a], ic, jc);
+        f = sf_column<0>(g, views[view_of(a)], ic, jc);
         const int centre = (int)floor(f.xi);
-        first = __builtin_amdgcn_readlane(centre, (FLAT_T / 2) * (FLAT_T + 1)) - 32;
-        const int c = first + lane;
-        const bool in = (unsigned)c < (unsigned)g.ncols;
-        const float *__restrict__ y = sino + (size_t)a * g.ncols + (in ? c : 0);
+        constexpr int MIDDLE = (Tile::TY / 2) * Tile::TX + Tile::TX / 2;
+        if constexpr (SUB == 1) first = __builtin_amdgcn_readlane(centre, MIDDLE) - Tile::COLS / 2;
+        else first = __shfl(centre, sub * Tile::LANES + MIDDLE) - Tile::COLS / 2;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) stage[b] = in && b0 + b < items ? y[b * nsino] : 0.0f;
-    };
-    if (wave < g.nviews) fetch(wave);
-    for (int a = wave; a < g.nviews; a += nwaves) {
-        const SfView &v = views[a];
-        const float amp = sf_amp(g, v, sf_amp_col<0>(g, v, first + lane), 0) * fv;
+        for (int k = 0; k < LOADS; ++k) {
+            const int c = first + l + k * Tile::LANES;
+            const bool in = (unsigned)c < (unsigned)g.ncols && (SUB == 1 || a + sub < g.nviews);
+            const float *__restrict__ y = sino + (size_t)view_of(a) * g.ncols + (in ? c : 0);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) buf[lane * NB + b] = stage[b] * amp;
-        flat_wave_sync();
-        int cf, cl;
-        sf_col_range(f, cf, cl);
-        const float *__restrict__ q = buf + (cf - first) * NB;
-        float e = sf_pixel_edge(f, cf);
-        const SfColumn now = f;
-        if (a + nwaves < g.nviews) fetch(a + nwaves);               // in flight during the gather
-        float g0 = sf_trap_integral(now, e);
-#pragma unroll
-        for (int m = 0; m < FLAT_NC; ++m) {
-            if (m > 1 && __builtin_amdgcn_ballot_w64(cf + m <= cl) == 0) break;      // no lane's footprint reaches this far
-            e += 1.0f;
-            const float g1 = sf_trap_integral(now, e), fu = fmaxf(g1 - g0, 0.0f);
-            g0 = g1;
-            if (fu > 0.0f) {
-#pragma unroll
-                for (int b = 0; b < NB; ++b) acc[b] = fmaf(fu, q[m * NB + b], acc[b]);
-            }
+            for (int b = 0; b < NB; ++b) stage[k][b] = in && b0 + b < items ? y[b * nsino] : 0.0f;
         }
-        flat_wave_sync();
+    };
+    const int run = wave * shares;
+    if (run < g.nviews) fetch(run);
+    for (int s = 0; s < shares && run + s < g.nviews; s += SUB) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b] = 0.0f;
+        for (int a = run + s; a < g.nviews; a += nwaves * shares) {
+            const SfView &v = views[view_of(a)];
+#pragma unroll
+            for (int k = 0; k < LOADS; ++k) {
+                const float amp = sf_amp(g, v, sf_amp_col<0>(g, v, first + l + k * Tile::LANES), 0) * fv;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) buf[(l + k * Tile::LANES) * NB + b] = stage[k][b] * amp;
+            }
+            flat_wave_sync();
+            int cf, cl;
+            sf_col_range(f, cf, cl);
+            const float *__restrict__ q = buf + (cf - first) * NB;
+            float e = sf_pixel_edge(f, cf);
+            const SfColumn now = f;
+            // the next views, in flight during the gather
+            const int next = a + nwaves * shares < g.nviews ? a + nwaves * shares : run + s + SUB;
+            if (next < g.nviews && (next > a || s + SUB < shares)) fetch(next);
+            float g0 = sf_trap_integral(now, e);
+#pragma unroll
+            for (int m = 0; m < FLAT_NC; ++m) {
+                if (m > 1 && __builtin_amdgcn_ballot_w64(cf + m <= cl) == 0) break;      // no lane's footprint reaches this far
+                e += 1.0f;
+                const float g1 = sf_trap_integral(now, e), fu = fmaxf(g1 - g0, 0.0f);
+                g0 = g1;
+                if (fu > 0.0f) {
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) acc[b] = fmaf(fu, q[m * NB + b], acc[b]);
+                }
+            }
+            flat_wave_sync();
+        }
+#pragma unroll
+        for (int k = 0; k < SUB; ++k)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) total[b] += SUB == 1 ? acc[b] : __shfl(acc[b], k * Tile::LANES + l);
     }
-    flat_reduce<NB>(acc, reinterpret_cast<float *>(flat_lds), wave, lane, nwaves);
-    if (wave == 0 && i < g.nx && j < g.ny) {
+    flat_reduce<NB>(total, lds, wave, lane, nwaves);
+    if (wave == 0 && sub == 0 && i < g.nx && j < g.ny) {
         const size_t nvol = (size_t)g.nx * g.ny;
         float *__restrict__ x = vol + (size_t)b0 * nvol + (size_t)j * g.nx + i;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
-            if (b0 + b < items) x[b * nvol] = acc[b];
+            if (b0 + b < items) x[b * nvol] = total[b];
     }
 }
 

@@ -115,3 +115,12 @@ def test_slices_turned_for_beams_along_x(oracle_mod, cfg):
 def test_tiles_of_a_view_rounded_up_to_an_odd_number(oracle_mod, cfg):
     """More than two tiles of 64 columns, on either side of the number of workgroups from which they are rounded up, and a batch of three."""
     test_flat_kernels_match_oracle(oracle_mod, cfg, 3)
+
+
+@pytest.mark.parametrize("nx,ny", [(64, 64), (65, 64), (121, 61), (128, 64), (129, 64)])
+@pytest.mark.parametrize("geom,nviews", [(PARALLEL, 64), (FAN, 63), (FAN, 64), (FAN, 131)])
+def test_few_tiles_take_several_views_at_a_time(oracle_mod, geom, nx, ny, nviews):
+    """Numbers of 8 x 8 tiles and of views on either side of the rule, in launches of one, two and three groups of items: the same bits."""
+    cfg = scan(geom, nx, ny, 130, nviews, pixel_u=2.3 if geom == FAN else 1.3)
+    test_flat_kernels_match_oracle(oracle_mod, cfg, 10)
+    test_flat_kernels_match_oracle(oracle_mod, cfg, 21)
