@@ -26,7 +26,7 @@
 #pragma once
 
 #include "md_siddon.h"
-#include "sf_backproject_tiled.h"
+#include "sd_backproject_tiled.h"
 
 // Shapes this kernel is instantiated for (voxels along z per thread, staged window columns x rows), in the order they
 // are tried.  LDS per workgroup: 28 bytes per staged sample (row stride pw + 1) plus (zc + 4) KiB of sums; the first shape
@@ -38,7 +38,6 @@ constexpr int MD_BP_NSHAPES = 6;
 constexpr SfBpShape MD_BP_SPLIT_SHAPES[] = {{8, 32, 28}, {8, 64, 28}, {8, 64, 36}};
 constexpr int MD_BP_SPLIT[] = {4, 2, 2};
 constexpr int MD_BP_NSPLIT_SHAPES = 3;
-constexpr double MD_BP_ZBIAS = 1048576.0;      // added to axial positions so that truncation is floor for every row of a window
 
 // One entry per view, built in double on the host.
 struct MdBpView {
@@ -159,7 +158,7 @@ struct MdBpPixel {
     double m, mz;        // slopes along the tile's axis
     float wy;            // sample times mm of ray per unit of X
     float inv_m;         // 1 / m (1e30 where m vanishes)
-    float inv_mz;        // 1 / mz (1e30 where mz vanishes)
+    float inv_mz;        // 1 / mz per unit of a fixed-point position, 2^-32 voxel (2e20 where mz vanishes)
 };
 
 SF_HD MdBpPixel md_bp_pixel(const MdBpSlopes &s, float y)
@@ -170,7 +169,7 @@ SF_HD MdBpPixel md_bp_pixel(const MdBpSlopes &s, float y)
     p.wy = y * s.len;
     const float mf = (float)s.m, mzf = (float)s.mz;
     p.inv_m = fabsf(mf) > 1e-30f ? 1.0f / mf : 1e30f;
-    p.inv_mz = fabsf(mzf) > 1e-30f ? 1.0f / mzf : 1e30f;
+    p.inv_mz = (fabsf(mzf) > 1e-30f ? 1.0f / mzf : 1e30f) * 2.3283064365386963e-10f;
     return p;
 }
 
@@ -180,7 +179,7 @@ struct MdBpColumn {
     float ub[4], vb[4], slope[4];    // the four vertical edges of the column's box: shadow of the lower end, rows per column
     bool slanted;                    // false: the edges' shadows are too close to vertical to bound the rows
     float eta_lo, eta_hi;
-    double ln, bq, bz;               // n - xs; minor of the source minus the cell's minor index; Z of the source in slots + MD_BP_ZBIAS
+    double ln, bq, bz;               // n - xs; minor of the source minus the cell's minor index; the source's fixed-point position (sd_bp_place)
 };
 
 template <int ZC>
@@ -206,7 +205,7 @@ SF_HD MdBpColumn md_bp_column(const SfGeom &g, const MdBpView &V, bool xmajor, i
     const int n = xmajor ? ic : jc, q = xmajor ? jc : ic;
     C.ln = (double)n - V.sidx[xmajor ? 0 : 1];
     C.bq = V.sidx[xmajor ? 1 : 0] - (double)q;
-    C.bz = V.sidx[2] - (double)k0 + 2.0 + MD_BP_ZBIAS;
+    C.bz = (double)(ZC + 1) + SD_BP_MAGIC - (V.sidx[2] - (double)k0);
     return C;
 }
 
@@ -229,12 +228,14 @@ SF_HD void md_bp_rows(const MdBpColumn &C, int c, int r0, int H, int &rs, int &r
     re = re > H ? H : re;
 }
 
-// One row of one detector column against one voxel column: the two shares and the slot of the lower one.
-// Returns false when the ray misses the column's in-plane cell.  Positions are formed in double and reduced to the
-// distance from the cell's faces before they become floats, so that those distances carry an absolute error of 1e-7 of a
-// voxel whatever the lever arm; that keeps the shares good to 1e-6 on average although they are divided by m and mz.
+// One row of one detector column against one voxel column: the two shares and the slot of the upper one (SD_BP_HI plus it; the next
+// slot holds the cell below, see sd_bp_place).  Returns false when the ray misses the column's in-plane cell.  The in-plane position is formed
+// in double and reduced to the distance from the cell's faces before it becomes a float, so that those distances carry an absolute error
+// of 1e-7 of a voxel whatever the lever arm; that keeps the shares good to 1e-6 on average although they are divided by m.  The axial
+// position of the piece's lower end stays in double, in the circular kernel's fixed point (downwards, units of 2^-32 voxel), whose two words
+// are the way up to the next face and the slot.
 template <int ZC>
-SF_HD bool md_bp_row(const MdBpColumn &C, const MdBpPixel &p, int &slot, float &w_low, float &w_high)
+SF_HD bool md_bp_row(const MdBpColumn &C, const MdBpPixel &p, unsigned &slot, float &w_above, float &w_below)
 {
     const float y0 = (float)fma(C.ln, p.m, C.bq);                // minor position at X = n, relative to the cell
     // (clamping is monotone: the clamped crossing times of the cell's two faces, then their order; the clamp rides on
@@ -243,21 +244,11 @@ SF_HD bool md_bp_row(const MdBpColumn &C, const MdBpPixel &p, int &slot, float &
     const float t0 = fminf(ta, tb), t1 = fmaxf(ta, tb);
     const float dt = t1 - t0;
     if (!(dt > 0.0f)) return false;
-    const double zin = fma(C.ln, p.mz, C.bz);                    // Z at X = n in slots, plus MD_BP_ZBIAS (positive)
-#if defined(__HIP_DEVICE_COMPILE__)
-    const float fz = (float)__builtin_amdgcn_fract(zin);
-    const int kz = (int)zin - (int)MD_BP_ZBIAS;                  // (the device's conversion saturates; the slot is clamped below)
-#else
-    const float fz = (float)(zin - floor(zin));
-    const int kz = (int)fmin(fmax(zin, 0.0), 2.0 * MD_BP_ZBIAS) - (int)MD_BP_ZBIAS;
-#endif
-    const float lo = fmaf(p.inv_mz >= 0.0f ? t0 : t1, (float)p.mz, fz);      // lower end of the piece, relative to cell kz
-    const float kl = floorf(lo);
-    const int s = kz + (int)kl;
-    slot = s < 0 ? 0 : (s > ZC + 2 ? ZC + 2 : s);
-    const float wl = fminf((1.0f - (lo - kl)) * fabsf(p.inv_mz), dt);
-    w_low = wl * p.wy;
-    w_high = (dt - wl) * p.wy;
+    const double lower = C.ln + (double)(p.inv_mz >= 0.0f ? t0 : t1);        // along X, from the source
+    float wl;
+    sd_bp_place<ZC>(fma(-lower, p.mz, C.bz), fabsf(p.inv_mz), dt, slot, wl);
+    w_above = (dt - wl) * p.wy;
+    w_below = wl * p.wy;
     return true;
 }
 
@@ -269,7 +260,7 @@ __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const
                                                             const float *__restrict__ sino, float *__restrict__ vol, int tiles_x, int parts)
 {
     constexpr int PS = PW + 1;                     // odd row stride: the lanes of a wave sit in a few adjacent rows and columns
-    constexpr int NSLOT = ZC + 4;                  // slot s holds voxel k0 + s - 2; slots 0, 1, ZC+2, ZC+3 are dumps
+    constexpr int NSLOT = ZC + 4;                  // slot s holds voxel k0 + ZC + 1 - s; slots 0, 1, ZC+2, ZC+3 are dumps
     constexpr int RSTEP = 256 / PW, NSTAGE = (PH * PW + 255) / 256;
     __shared__ double group_m[VS][PH * PS], group_mz[VS][PH * PS];
     __shared__ float group_wy[VS][PH * PS], group_inv_m[VS][PH * PS], group_inv_mz[VS][PH * PS];
@@ -297,6 +288,8 @@ __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const
 
 #pragma unroll
     for (int s = 0; s < NSLOT; ++s) sums[s * 256 + tid] = 0.0f;
+    // LDS address of this thread's slot SD_BP_HI (mod 2^32): a slot's address is that plus 1024 times its number
+    const unsigned sums_at = (unsigned)(uintptr_t)(SdLds *)(sums + tid) - (SD_BP_HI << 10);
 
     float stage[NSTAGE];
     SfWindow win;
@@ -356,13 +349,15 @@ __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const
             for (int row = rs; row < re; ++row) {
                 const int o = row * PS + wc;
                 const MdBpPixel p = {l_m[o], l_mz[o], l_wy[o], l_inv_m[o], l_inv_mz[o]};
-                int slot;
-                float w_low, w_high;
-                if (!md_bp_row<ZC>(C, p, slot, w_low, w_high)) continue;
-                float *__restrict__ cell = sums + (slot * 256 + tid);
+                unsigned slot, at;
+                float w_above, w_below;
+                if (!md_bp_row<ZC>(C, p, slot, w_above, w_below)) continue;
+                asm("v_lshl_add_u32 %0, %1, 10, %2" : "=v"(at) : "v"(slot), "v"(sums_at));
+                SdLds *const cell = (SdLds *)(uintptr_t)at;
                 // plain read-add-write: the slot has no other writer, and a wave's LDS accesses retire in order
-                cell[0] += w_low;
-                cell[256] += w_high;
+                const float u = cell[0], l = cell[256];
+                cell[0] = u + w_above;
+                cell[256] = l + w_below;
             }
         }
 
@@ -380,9 +375,9 @@ __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const
 #pragma unroll
         for (int kk = 0; kk < ZC; ++kk)
             if (k0 + kk < g.nz) {
-                float sum = sums[(kk + 2) * 256 + tid];
+                float sum = sums[(ZC + 1 - kk) * 256 + tid];
 #pragma unroll
-                for (int q = 1; q < VS; ++q) sum += group_sums[q][(kk + 2) * 256 + tid];
+                for (int q = 1; q < VS; ++q) sum += group_sums[q][(ZC + 1 - kk) * 256 + tid];
                 vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sum;
             }
     }

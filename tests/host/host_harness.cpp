@@ -803,12 +803,13 @@ static void host_md_bp_shape(const leap_geometry *G, const float *sino, float *v
                         md_bp_rows(C, c, win.r0, H, rs, re);
                         for (int row = rs; row < re; ++row) {
                             if (row < 0 || row >= PH) { ++outside; continue; }
-                            int slot;
-                            float w_low, w_high;
-                            if (!md_bp_row<ZC>(C, px[(size_t)row * PS + wc], slot, w_low, w_high)) continue;
-                            if (slot < 0 || slot + 1 >= NSLOT) { ++badslot; continue; }
-                            sums[(size_t)slot * 256 + tid] += w_low;
-                            sums[(size_t)(slot + 1) * 256 + tid] += w_high;
+                            unsigned slot;
+                            float w_above, w_below;
+                            if (!md_bp_row<ZC>(C, px[(size_t)row * PS + wc], slot, w_above, w_below)) continue;
+                            slot -= SD_BP_HI;
+                            if (slot + 1 >= (unsigned)NSLOT) { ++badslot; continue; }
+                            sums[(size_t)slot * 256 + tid] += w_above;
+                            sums[(size_t)(slot + 1) * 256 + tid] += w_below;
                         }
                     }
                 }
@@ -817,7 +818,7 @@ static void host_md_bp_shape(const leap_geometry *G, const float *sino, float *v
                 const int i = i0 + (tid & (BP_T - 1)), j = j0 + (tid >> 4);
                 if (i >= g.nx || j >= g.ny) continue;
                 for (int kk = 0; kk < ZC && k0 + kk < g.nz; ++kk)
-                    vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sums[(size_t)(kk + 2) * 256 + tid];
+                    vol[((size_t)(k0 + kk) * g.ny + j) * g.nx + i] = sums[(size_t)(ZC + 1 - kk) * 256 + tid];
             }
         }
     report[0] = wide; report[1] = outside; report[2] = badslot;
