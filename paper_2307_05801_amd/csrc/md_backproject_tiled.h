@@ -2,6 +2,11 @@
 // Geometries": sources and detectors at any position and orientation; matched transpose): voxel-driven, no atomics,
 // bitwise reproducible.
 //
+// Bound by instruction issue.  256^3, 360 views of 256^2: 11.9 ms while a row's axial position was a float beside an integer; 11.1 in the
+// circular kernel's fixed point, 10.8 with one branch per row instead of two, 10.1 with the windows of 64 views worked out at once, a view
+// per lane, and reciprocals instead of divisions where the samples are staged (eight drawn scans 0.82 over all of it).  Fetching
+// the next row's sample ahead or counting LDS addresses instead of rows made it slower (1.08, 1.015).
+//
 // Same plan as the circular kernel (sd_backproject_tiled.h): a workgroup of 256 threads owns a 16 x 16 tile of voxel
 // columns and ZC voxels along z, a thread one column; per view the workgroup stages into LDS the window of the
 // detector that its tile's box projects into; a thread walks rows of the window and adds each row's (at most) two
@@ -168,8 +173,9 @@ SF_HD MdBpPixel md_bp_pixel(const MdBpSlopes &s, float y)
     p.mz = s.mz;
     p.wy = y * s.len;
     const float mf = (float)s.m, mzf = (float)s.mz;
-    p.inv_m = fabsf(mf) > 1e-30f ? 1.0f / mf : 1e30f;
-    p.inv_mz = (fabsf(mzf) > 1e-30f ? 1.0f / mzf : 1e30f) * 2.3283064365386963e-10f;
+    // (sf_rcp: the float reciprocal and a Newton step, a third of a division's instructions)
+    p.inv_m = fabsf(mf) > 1e-30f ? sf_rcp(mf) : 1e30f;
+    p.inv_mz = (fabsf(mzf) > 1e-30f ? sf_rcp(mzf) : 1e30f) * 2.3283064365386963e-10f;
     return p;
 }
 
@@ -228,28 +234,31 @@ SF_HD void md_bp_rows(const MdBpColumn &C, int c, int r0, int H, int &rs, int &r
     re = re > H ? H : re;
 }
 
-// One row of one detector column against one voxel column: the two shares and the slot of the upper one (SD_BP_HI plus it; the next
-// slot holds the cell below, see sd_bp_place).  Returns false when the ray misses the column's in-plane cell.  The in-plane position is formed
-// in double and reduced to the distance from the cell's faces before it becomes a float, so that those distances carry an absolute error
-// of 1e-7 of a voxel whatever the lever arm; that keeps the shares good to 1e-6 on average although they are divided by m.  The axial
-// position of the piece's lower end stays in double, in the circular kernel's fixed point (downwards, units of 2^-32 voxel), whose two words
+// One row of one detector column against one voxel column: md_bp_piece the part [t0, t1] of the slab in its in-plane cell (not positive:
+// the ray misses it), md_bp_shares the two shares and the slot of the upper one (SD_BP_HI plus it; the next slot holds the cell below, see
+// sd_bp_place).  The in-plane position is formed in double and reduced to the distance from the cell's faces before it becomes a float, so
+// that those distances carry an absolute error of 1e-7 of a voxel whatever the lever arm; that keeps the shares good to 1e-6 on average
+// although they are divided by m.  The axial position of the piece's lower end stays in double, in the circular kernel's fixed point (downwards, units of 2^-32 voxel), whose two words
 // are the way up to the next face and the slot.
-template <int ZC>
-SF_HD bool md_bp_row(const MdBpColumn &C, const MdBpPixel &p, unsigned &slot, float &w_above, float &w_below)
+SF_HD float md_bp_piece(const MdBpColumn &C, const MdBpPixel &p, float &t0, float &t1)
 {
     const float y0 = (float)fma(C.ln, p.m, C.bq);                // minor position at X = n, relative to the cell
     // (clamping is monotone: the clamped crossing times of the cell's two faces, then their order; the clamp rides on
     // the multiplication)
     const float ta = sf_clamp(-y0 * p.inv_m, 0.0f, 1.0f), tb = sf_clamp((1.0f - y0) * p.inv_m, 0.0f, 1.0f);
-    const float t0 = fminf(ta, tb), t1 = fmaxf(ta, tb);
+    t0 = fminf(ta, tb), t1 = fmaxf(ta, tb);
+    return t1 - t0;
+}
+
+template <int ZC>
+SF_HD void md_bp_shares(const MdBpColumn &C, const MdBpPixel &p, float t0, float t1, unsigned &slot, float &w_above, float &w_below)
+{
     const float dt = t1 - t0;
-    if (!(dt > 0.0f)) return false;
     const double lower = C.ln + (double)(p.inv_mz >= 0.0f ? t0 : t1);        // along X, from the source
     float wl;
     sd_bp_place<ZC>(fma(-lower, p.mz, C.bz), fabsf(p.inv_mz), dt, slot, wl);
     w_above = (dt - wl) * p.wy;
     w_below = wl * p.wy;
-    return true;
 }
 
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
@@ -292,9 +301,18 @@ __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const
     const unsigned sums_at = (unsigned)(uintptr_t)(SdLds *)(sums + tid) - (SD_BP_HI << 10);
 
     float stage[NSTAGE];
-    SfWindow win;
+    SfWindow win, windows = {};
     auto load_view = [&](int a) {           // this thread's share of the raw samples of view a's window, into registers
-        win = md_bp_window(g, views[a], i0, j0, k0, ZC);
+        // a window takes a hundred instructions and is the same for all threads: every lane works out that of one of the next 64 views
+        const int lane = threadIdx.x & 63, n = (a - a_first - group) / VS;
+        if ((n & 63) == 0) {
+            const int mine = a + VS * lane;
+            windows = md_bp_window(g, views[mine < a_end ? mine : a_end - 1], i0, j0, k0, ZC);
+        }
+        win.c0 = __builtin_amdgcn_readlane(windows.c0, n & 63);
+        win.r0 = __builtin_amdgcn_readlane(windows.r0, n & 63);
+        win.need_w = __builtin_amdgcn_readlane(windows.need_w, n & 63);
+        win.need_h = __builtin_amdgcn_readlane(windows.need_h, n & 63);
         const int c = win.c0 + sc;
         const bool cin = (unsigned)c < (unsigned)g.ncols;
         const char *__restrict__ yb = reinterpret_cast<const char *>(sino + (size_t)a * view_stride);
@@ -349,9 +367,11 @@ __global__ __launch_bounds__(256 * VS) void md_backproject_tiled(SfGeom g, const
             for (int row = rs; row < re; ++row) {
                 const int o = row * PS + wc;
                 const MdBpPixel p = {l_m[o], l_mz[o], l_wy[o], l_inv_m[o], l_inv_mz[o]};
+                float t0, t1;
+                if (!(md_bp_piece(C, p, t0, t1) > 0.0f)) continue;
                 unsigned slot, at;
                 float w_above, w_below;
-                if (!md_bp_row<ZC>(C, p, slot, w_above, w_below)) continue;
+                md_bp_shares<ZC>(C, p, t0, t1, slot, w_above, w_below);
                 asm("v_lshl_add_u32 %0, %1, 10, %2" : "=v"(at) : "v"(slot), "v"(sums_at));
                 SdLds *const cell = (SdLds *)(uintptr_t)at;
                 // plain read-add-write: the slot has no other writer, and a wave's LDS accesses retire in order

@@ -803,9 +803,11 @@ static void host_md_bp_shape(const leap_geometry *G, const float *sino, float *v
                         md_bp_rows(C, c, win.r0, H, rs, re);
                         for (int row = rs; row < re; ++row) {
                             if (row < 0 || row >= PH) { ++outside; continue; }
+                            const MdBpPixel &p = px[(size_t)row * PS + wc];
+                            float t0, t1, w_above, w_below;
+                            if (!(md_bp_piece(C, p, t0, t1) > 0.0f)) continue;
                             unsigned slot;
-                            float w_above, w_below;
-                            if (!md_bp_row<ZC>(C, px[(size_t)row * PS + wc], slot, w_above, w_below)) continue;
+                            md_bp_shares<ZC>(C, p, t0, t1, slot, w_above, w_below);
                             slot -= SD_BP_HI;
                             if (slot + 1 >= (unsigned)NSLOT) { ++badslot; continue; }
                             sums[(size_t)slot * 256 + tid] += w_above;
