@@ -187,7 +187,7 @@ const char *leap_last_error(void);
  * "general(tiled)" are the fast kernels of flat scans and of footprints on tilted modules, which read those arrays too;
  * "tiled(...)" is the kernel of one volume per workgroup, "+mirror(...)" a volume and its mirror image per workgroup in its
  * place, "+pairs(...)" the kernel two items of a batch take, "+split(...)" the one with shared views that a single volume
- * takes before any of them), "scratch=<bytes>" the device memory the handle owns beyond its tables, "note=..." anything that went
+ * takes before any of them, "+parts(n,...)" the views shared among n workgroups outside stream capture), "scratch=<bytes>" the device memory the handle owns beyond its tables, "note=..." anything that went
  * differently from the plan at creation.  Returns LEAP_OK or LEAP_INVALID_ARG.
  *
  * Debugging aid: the environment variable LEAP_DEBUG, read by leap_geometry_create, overrides the choices shown
@@ -196,7 +196,7 @@ const char *leap_last_error(void);
  * (first back-projection tile shape tried; two volumes per workgroup and shared views then only where the next two
  * name them), bp_pair=0..3|-1 (the shape for two volumes per
  * workgroup, whatever the batch, none), bp_split=0..2|-1 (the shape for views
- * shared between groups of threads, whatever the batch, none), pairs=0|1 (forward: one item of a
+ * shared between groups of threads, whatever the batch, none), bp_parts=1 (no views shared among workgroups), pairs=0|1 (forward: one item of a
  * batch per wavefront, or two wherever there is a kernel for two, however small the batch), parts=1|4 (forward: a wavefront per bundle
  * of columns, or four that share its layers; parallel beams also 2), slab=N (voxel layers per scratch slab), items=N (batch items per launch),
  * scratch_mib=N (scratch budget), stage_kib=N (size of a pinned staging buffer of the host-memory entry points). */
