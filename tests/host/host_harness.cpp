@@ -468,6 +468,19 @@ extern "C" long host_project_columns(const leap_geometry *G, const float *vol, f
 }
 
 // How many of a launch's items go two to a wave.
+// Tiles that the back projection's order of workgroups leaves out or names twice, in one layer of chunks.
+extern "C" long host_check_tile_order(unsigned tiles_x, unsigned tiles_y, unsigned y)
+{
+    const unsigned tiles = tiles_x * tiles_y;
+    std::vector<int> seen(tiles, 0);
+    long wrong = 0;
+    for (unsigned x = 0; x < tiles; ++x) {
+        const unsigned tile = sf_bp_tile(x, y, tiles, tiles_x);
+        if (tile >= tiles || seen[tile]++) ++wrong;
+    }
+    return wrong;
+}
+
 extern "C" int host_forward_paired(const leap_geometry *G, int items) { return leap_forward_paired(G, items); }
 
 // Back projection of a launch's items: the shape whose groups of threads share the views (-1: none), pairs of items per workgroup.

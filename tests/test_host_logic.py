@@ -1168,3 +1168,10 @@ def test_windows_of_mirror_images_and_shared_views_hold_what_is_read(host, monke
         monkeypatch.setenv("LEAP_DEBUG", debug)
     rep, desc = window_report(host, cfg)
     assert rep[7] == 0, (rep, desc)
+
+
+@pytest.mark.parametrize("tiles_x", [1, 3, 7, 8, 9, 16, 21, 64])
+def test_the_back_projection_s_order_of_tiles_names_every_tile_once(host, tiles_x):
+    for tiles_y in range(1, 34):
+        for y in (0, 1, 7, 8):
+            assert host.host_check_tile_order(tiles_x, tiles_y, y) == 0, (tiles_y, y)
