@@ -2,6 +2,8 @@
 // workgroups of them, by way of the handle's d_back.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "leap_internal.h"
 #include "sf_backproject_tiled.h"
 
@@ -19,13 +21,18 @@ static bool launch_instance(const leap_geometry *G, int parts, const float *d_si
         auto go = [&](auto kernel, const void *aux) {
             hipLaunchKernelGGL(kernel, grid, dim3(256 * BP_SPLIT), 0, stream, g, G->d_views, d_sino, to, (int)tiles_x, G->bp_wh, aux, sets);
         };
+        auto launch = [&](auto gt, const void *aux) {
+            constexpr int GT = decltype(gt)::value;
+            if (parts > 1) go(sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, GT, NS, BP_SPLIT, true>, aux);
+            else go(sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, GT, NS, BP_SPLIT, false>, aux);
+        };
         if (g.type == SF_CONE_CURVED) {
-            go(sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, 1, NS, BP_SPLIT>, G->d_colcs);
+            launch(std::integral_constant<int, 1>(), G->d_colcs);
         } else if (g.type == SF_MODULAR) {
-            if constexpr (NS == 1) go(sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, 2, NS, BP_SPLIT>, G->d_geoms);
+            if constexpr (NS == 1) launch(std::integral_constant<int, 2>(), G->d_geoms);
             else return false;
         } else {
-            go(sf_backproject_tiled<NC, NV, S.zc, S.pw, S.ph, 0, NS, BP_SPLIT>, nullptr);
+            launch(std::integral_constant<int, 0>(), nullptr);
         }
         if (parts > 1) {
             const unsigned nvol = (unsigned)g.nx * (unsigned)g.ny * (unsigned)g.nz;

@@ -2,6 +2,8 @@
 // > 1: that many workgroups of them, into the handle's d_back.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "leap_internal.h"
 #include "sd_backproject_tiled.h"
 
@@ -17,13 +19,18 @@ static void launch_instance(const leap_geometry *G, int parts, const float *d_si
         hipLaunchKernelGGL(kernel, grid, dim3(256 * VS), 0, stream, g, G->d_views, G->d_raycols, d_sino, parts > 1 ? G->d_back : d_vol, (int)tiles_x, geoms, parts);
     };
     const bool apart = G->sd_min_row_step > 1.0 + 1e-6;
-    if (g.type == SF_MODULAR) {
-        if (apart) go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, true, true, VS>, G->d_geoms);
-        else go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, true, false, VS>, G->d_geoms);
-    } else {
-        if (apart) go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, false, true, VS>, nullptr);
-        else go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, false, false, VS>, nullptr);
-    }
+    auto launch = [&](auto shared) {
+        constexpr bool PARTS = decltype(shared)::value;
+        if (g.type == SF_MODULAR) {
+            if (apart) go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, true, true, VS, PARTS>, G->d_geoms);
+            else go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, true, false, VS, PARTS>, G->d_geoms);
+        } else {
+            if (apart) go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, false, true, VS, PARTS>, nullptr);
+            else go(sd_backproject_tiled<NCS, S.zc, S.pw, S.ph, false, false, VS, PARTS>, nullptr);
+        }
+    };
+    if (parts > 1) launch(std::true_type());
+    else launch(std::false_type());
 }
 
 template <int NCS>

@@ -181,7 +181,7 @@ typedef __attribute__((address_space(3))) float SdLds;
 // APART: adjacent rows are at least one voxel apart wherever a ray meets the volume.
 // VS: groups of 256 threads that share a tile's views, group q taking views q, q + VS, ..., each with sums of its own that are added in
 // order at the end: as in the footprint kernel, a step from view to view takes a workgroup microseconds however little it holds.
-template <int NCS, int ZC, int PW, int PH, bool MOD, bool APART, int VS = 1>
+template <int NCS, int ZC, int PW, int PH, bool MOD, bool APART, int VS = 1, bool PARTS = false>
 __global__ __launch_bounds__(256 * VS) void sd_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
                                                             const SdRayCol *__restrict__ rays, const float *__restrict__ sino,
                                                             float *__restrict__ vol, int tiles_x,
@@ -193,10 +193,10 @@ __global__ __launch_bounds__(256 * VS) void sd_backproject_tiled(SfGeom g, const
     __shared__ float rinv[2 * VS][PH];
     __shared__ float group_sums[VS][NSLOT * 256];
 
-    // blockIdx.z: item of a batch; VS > 1: times the parts of its views, the volumes of an item's parts side by side
-    const unsigned item = VS == 1 ? blockIdx.z : blockIdx.z / (unsigned)parts;
-    const int part = VS == 1 ? 0 : (int)(blockIdx.z - item * (unsigned)parts);
-    const int a_first = VS == 1 ? 0 : (int)((long long)g.nviews * part / parts), a_end = VS == 1 ? g.nviews : (int)((long long)g.nviews * (part + 1) / parts);
+    // blockIdx.z: item of a batch; PARTS: times the parts of its views, the volumes of an item's parts side by side (a template, as for footprints)
+    const unsigned item = PARTS ? blockIdx.z / (unsigned)parts : blockIdx.z;
+    const int part = PARTS ? (int)(blockIdx.z - item * (unsigned)parts) : 0;
+    const int a_first = PARTS ? (int)((long long)g.nviews * part / parts) : 0, a_end = PARTS ? (int)((long long)g.nviews * (part + 1) / parts) : g.nviews;
     sino += (size_t)item * g.nviews * g.nrows * g.ncols;
     vol += (size_t)blockIdx.z * g.nx * g.ny * g.nz;
     const int tid = VS == 1 ? threadIdx.x : threadIdx.x & 255;
