@@ -45,13 +45,12 @@ static bool launch_bp_shape(const leap_geometry *G, const float *d_sino, float *
     }
 }
 
-// As many items at a time as the handle's room for the parts' volumes holds.  Calls on one handle share it and are ordered on the device, as
-// those that share the forward scratch are.
+// As many items at a time as the handle's room for the parts' volumes holds.
 static int launch_in_parts(const leap_geometry *G, const LeapBackParts &plan, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     const size_t nvol = (size_t)G->g.nx * G->g.ny * G->g.nz, nsino = (size_t)G->g.nviews * G->g.nrows * G->g.ncols;
-    std::lock_guard<std::mutex> lock(G->back_mutex);
-    if (G->back_used && G->back_stream != stream) LEAP_HIP_CHECK(hipStreamWaitEvent(stream, G->back_event, 0));
+    LeapTurn turn(G->back, stream);
+    LEAP_HIP_CHECK(turn.begin());
     for (int b = 0; b < items;) {
         const int n = std::min(items - b, plan.items);
         if (!leap_launch_backproject_split(G, plan.shape, plan.parts, d_sino + b * nsino, d_vol + b * nvol, n, stream)) {
@@ -61,9 +60,7 @@ static int launch_in_parts(const leap_geometry *G, const LeapBackParts &plan, co
         LEAP_HIP_CHECK(hipGetLastError());
         b += n;
     }
-    LEAP_HIP_CHECK(hipEventRecord(G->back_event, stream));
-    G->back_stream = stream;
-    G->back_used = true;
+    LEAP_HIP_CHECK(turn.end());
     return LEAP_OK;
 }
 
@@ -72,11 +69,7 @@ int leap_launch_footprint_back(const leap_geometry *G, const float *d_sino, floa
 {
     bool ok = false;
     const LeapBackParts plan = leap_back_parts(G, items);
-    if (plan.parts > 1) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        LEAP_HIP_CHECK(hipStreamIsCapturing(stream, &capture));
-        if (capture == hipStreamCaptureStatusNone) return launch_in_parts(G, plan, d_sino, d_vol, items, stream);
-    }
+    if (plan.parts > 1 && !leap_capturing(stream)) return launch_in_parts(G, plan, d_sino, d_vol, items, stream);
     const int split = leap_back_split_shape(G, items);
     if (split >= 0) {
         if (!leap_launch_backproject_split(G, split, 1, d_sino, d_vol, items, stream)) {

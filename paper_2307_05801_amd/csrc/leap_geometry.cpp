@@ -1200,7 +1200,7 @@ static void allocate_forward_scratch(leap_geometry *G)
         e = hipMalloc((void **)&G->d_major, G->major.size());
         if (e == hipSuccess) e = hipMemcpy(G->d_major, G->major.data(), G->major.size(), hipMemcpyHostToDevice);
     }
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&G->scratch_event, hipEventDisableTiming);
+    if (e == hipSuccess) e = G->scratch.create();
     if (e != hipSuccess) {
         if (G->d_volz) (void)hipFree(G->d_volz);
         if (G->d_major) (void)hipFree(G->d_major);
@@ -1224,7 +1224,7 @@ static void allocate_flat_scratch(leap_geometry *G)
     if (!(items >= 2.0)) return;
     G->scratch_bytes = (size_t)(2.0 * items * slice);
     hipError_t e = hipMalloc((void **)&G->d_volz, G->scratch_bytes);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&G->scratch_event, hipEventDisableTiming);
+    if (e == hipSuccess) e = G->scratch.create();
     if (e == hipSuccess) return;
     if (G->d_volz) (void)hipFree(G->d_volz);
     G->d_volz = nullptr;
@@ -1240,7 +1240,7 @@ static void allocate_back_room(leap_geometry *G)
     const size_t one = (size_t)G->g.nx * G->g.ny * G->g.nz * G->bp_parts;
     G->back_floats = one * std::max<size_t>(1, std::min<size_t>(16, (size_t)BACK_MOST_FLOATS / one));
     hipError_t e = hipMalloc((void **)&G->d_back, G->back_floats * sizeof(float));
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&G->back_event, hipEventDisableTiming);
+    if (e == hipSuccess) e = G->back.create();
     if (e == hipSuccess) return;
     if (G->d_back) (void)hipFree(G->d_back);
     G->d_back = nullptr;
@@ -1265,8 +1265,6 @@ static void free_handle(leap_geometry *G)
     if (G->d_mdbp) (void)hipFree(G->d_mdbp);
     if (G->d_colcs) (void)hipFree(G->d_colcs);
     if (G->d_back) (void)hipFree(G->d_back);
-    if (G->scratch_event) (void)hipEventDestroy(G->scratch_event);
-    if (G->back_event) (void)hipEventDestroy(G->back_event);
     delete G;
 }
 

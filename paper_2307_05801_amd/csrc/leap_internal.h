@@ -16,6 +16,82 @@
 struct MdBpView;                       // per-view table of the tiled Siddon back projection on tilted modules (md_backproject_tiled.h)
 struct LeapHostStage;                  // streams, events, staging and device buffers of the host-memory entry points (leap_host.cpp)
 
+// Device memory of a handle that its calls use in turn, from any stream and thread.  The turns are ordered on the device: each waits for the
+// event that the last one recorded, whatever its stream, because equal stream handles need not be one stream (hipStreamPerThread is one handle
+// for a stream of every thread; a destroyed stream's handle is given out again).  Under capture an eager event says nothing about the graph's launches:
+// captured turns are ordered among those of their own capture, and eager ones among the eager ones.
+struct LeapShared {
+    std::mutex mutex;
+    hipEvent_t done = nullptr, captured = nullptr;     // the last eager turn's end; the last captured one's, in capture `capture`
+    bool used = false, captured_used = false;
+    unsigned long long capture = 0;
+
+    hipError_t create()
+    {
+        hipError_t e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
+        return e == hipSuccess ? hipEventCreateWithFlags(&captured, hipEventDisableTiming) : e;
+    }
+    ~LeapShared()
+    {
+        if (done) (void)hipEventDestroy(done);
+        if (captured) (void)hipEventDestroy(captured);
+    }
+};
+
+// Is work on the stream being captured?  (Also where the runtime will not say: such a call takes the kernels that share nothing.)
+inline bool leap_capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// One call's turn at a handle's shared memory, from begin() to end(); a call that returns early, some of its kernels perhaps launched, ends it too.
+class LeapTurn {
+public:
+    LeapTurn(LeapShared &memory, hipStream_t s) : shared(memory), lock(memory.mutex), stream(s) {}
+    ~LeapTurn()
+    {
+        if (begun) (void)record();
+    }
+    hipError_t begin()
+    {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
+        hipError_t e = hipSuccess;
+        capturing = status == hipStreamCaptureStatusActive;
+        if (capturing) e = hipStreamGetCaptureInfo(stream, &status, &capture);
+        if (e == hipSuccess && capturing && shared.captured_used && shared.capture == capture) e = hipStreamWaitEvent(stream, shared.captured, 0);
+        if (e == hipSuccess && !capturing && shared.used) e = hipStreamWaitEvent(stream, shared.done, 0);
+        begun = e == hipSuccess;
+        return e;
+    }
+    hipError_t end()
+    {
+        begun = false;
+        return record();
+    }
+
+private:
+    hipError_t record()
+    {
+        const hipError_t e = hipEventRecord(capturing ? shared.captured : shared.done, stream);
+        if (capturing) {
+            shared.captured_used = e == hipSuccess;
+            shared.capture = capture;
+        } else {
+            shared.used = shared.used || e == hipSuccess;
+        }
+        return e;
+    }
+    LeapShared &shared;
+    std::lock_guard<std::mutex> lock;
+    hipStream_t stream;
+    bool capturing = false, begun = false;
+    unsigned long long capture = 0;
+};
+
 struct leap_geometry {
     leap_geometry_desc desc;            // caller's parameters (angles_rad re-pointed at `angles`)
     std::vector<double> angles;
@@ -42,15 +118,12 @@ struct leap_geometry {
     int bp_split_shape = -1;
     unsigned bp_split_fits = 0;
     // ... and workgroups of them, each with a volume of its own: what one volume takes (parts 1: none), the shapes that fit, the room for the
-    // parts' volumes (floats; calls on one handle share it and are ordered like those that share the forward scratch)
+    // parts' volumes (floats)
     int bp_parts_shape = -1, bp_parts = 1;
     unsigned bp_parts_fits = 0;
     float *d_back = nullptr;
     size_t back_floats = 0;
-    mutable std::mutex back_mutex;
-    mutable hipEvent_t back_event = nullptr;
-    mutable hipStream_t back_stream = nullptr;
-    mutable bool back_used = false;
+    mutable LeapShared back;
     bool bp_split_forced = false;       // (debugging: bp_split_shape, whatever the launch)
     // column-wise forward projection (footprint and Siddon models): the volume goes through a z-fastest scratch copy
     // slab by slab (sf_project_columns.h)
@@ -76,11 +149,7 @@ struct leap_geometry {
     std::vector<unsigned char> major;   // footprints: [view][bundle of fp_cw columns] 1 if the bundle advances fastest along x
     unsigned char *d_major = nullptr;
     std::string note;                   // what went differently from the plan at creation (shown by leap_geometry_describe)
-    // calls on one handle share its scratch: a call on another stream than the last first waits for that one's kernels
-    mutable std::mutex scratch_mutex;
-    mutable hipEvent_t scratch_event = nullptr;
-    mutable hipStream_t scratch_stream = nullptr;
-    mutable bool scratch_used = false;
+    mutable LeapShared scratch;         // the turns of its calls at d_volz
     // Siddon model: per-(view, detector column) ray constants, host copy and device copy
     std::vector<SdRayCol> raycols;
     SdRayCol *d_raycols = nullptr;

@@ -335,8 +335,8 @@ static int launch_sd_bp_parts(const leap_geometry *G, const LeapBackParts &plan,
 {
     const unsigned nvol = (unsigned)G->g.nx * (unsigned)G->g.ny * (unsigned)G->g.nz;
     const size_t nsino = (size_t)G->g.nviews * G->g.nrows * G->g.ncols;
-    std::lock_guard<std::mutex> lock(G->back_mutex);
-    if (G->back_used && G->back_stream != stream) LEAP_HIP_CHECK(hipStreamWaitEvent(stream, G->back_event, 0));
+    LeapTurn turn(G->back, stream);
+    LEAP_HIP_CHECK(turn.begin());
     for (int b = 0; b < items; b += plan.items) {
         const int n = items - b < plan.items ? items - b : plan.items;
         bool ok = true;
@@ -349,9 +349,7 @@ static int launch_sd_bp_parts(const leap_geometry *G, const LeapBackParts &plan,
         hipLaunchKernelGGL(sf_sum_parts, dim3(cdiv(nvol, 256), (unsigned)n), dim3(256), 0, stream, G->d_back, d_vol + (size_t)b * nvol, nvol, plan.parts, 1);
         LEAP_HIP_CHECK(hipGetLastError());
     }
-    LEAP_HIP_CHECK(hipEventRecord(G->back_event, stream));
-    G->back_stream = stream;
-    G->back_used = true;
+    LEAP_HIP_CHECK(turn.end());
     return LEAP_OK;
 }
 
@@ -360,11 +358,7 @@ static int launch_sd_bp_items(const leap_geometry *G, const float *d_sino, float
 {
     bool ok = false;
     const LeapBackParts plan = leap_siddon_parts(G, items);
-    if (plan.parts > 1) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        LEAP_HIP_CHECK(hipStreamIsCapturing(stream, &capture));
-        if (capture == hipStreamCaptureStatusNone) return launch_sd_bp_parts(G, plan, d_sino, d_vol, items, stream);
-    }
+    if (plan.parts > 1 && !leap_capturing(stream)) return launch_sd_bp_parts(G, plan, d_sino, d_vol, items, stream);
     const int split = leap_siddon_split_shape(G, items);
     if (G->d_mdbp && split >= 0) {
         launch_md_split_shape(G, split, 1, d_sino, d_vol, stream, items);
@@ -546,8 +540,8 @@ static int project_flat(const leap_geometry *G, const float *d_vol, float *d_sin
         LEAP_HIP_CHECK(hipGetLastError());
         return LEAP_OK;
     }
-    std::lock_guard<std::mutex> lock(G->scratch_mutex);
-    if (G->scratch_used && G->scratch_stream != stream) LEAP_HIP_CHECK(hipStreamWaitEvent(stream, G->scratch_event, 0));
+    LeapTurn turn(G->scratch, stream);
+    LEAP_HIP_CHECK(turn.begin());
     const int room = (int)(G->scratch_bytes / (2 * nvol * sizeof(float)));      // whole slices the scratch holds, twice each
     for (int b = 0; b < batch;) {
         const float *vol = d_vol + b * nvol;
@@ -573,9 +567,7 @@ static int project_flat(const leap_geometry *G, const float *d_vol, float *d_sin
         b += items;
     }
     LEAP_HIP_CHECK(hipGetLastError());
-    LEAP_HIP_CHECK(hipEventRecord(G->scratch_event, stream));
-    G->scratch_stream = stream;
-    G->scratch_used = true;
+    LEAP_HIP_CHECK(turn.end());
     return LEAP_OK;
 }
 
@@ -704,16 +696,10 @@ int leap_launch_project_batch(const leap_geometry *G, const float *d_vol, float 
     const bool footprint_fast = g.model != SF_MODEL_SIDDON && G->fp_columns;
     const bool siddon_fast = g.model == SF_MODEL_SIDDON && G->sd_columns;
     bool direct = !footprint_fast && !siddon_fast;
-    if (!direct && g.nrows < FP_FREE_ROWS) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        LEAP_HIP_CHECK(hipStreamIsCapturing(stream, &capture));
-        direct = capture != hipStreamCaptureStatusNone;
-    }
+    if (!direct && g.nrows < FP_FREE_ROWS) direct = leap_capturing(stream);
     if (!direct) {
-        // Calls on one handle share its scratch.  They are ordered on the device: a call that arrives on another stream
-        // than the last one first waits for that one's kernels.
-        std::lock_guard<std::mutex> lock(G->scratch_mutex);
-        if (G->scratch_used && G->scratch_stream != stream) LEAP_HIP_CHECK(hipStreamWaitEvent(stream, G->scratch_event, 0));
+        LeapTurn turn(G->scratch, stream);
+        LEAP_HIP_CHECK(turn.begin());
         FwdScratch S;
         S.volz = G->d_volz;
         if (!leap_plan_scratch(G, G->scratch_bytes / sizeof(float), batch, S.width, S.items)) {
@@ -723,9 +709,7 @@ int leap_launch_project_batch(const leap_geometry *G, const float *d_vol, float 
         S.item_floats = ((size_t)S.width * (size_t)(g.nx > g.ny ? g.nx : g.ny) + 1) * (size_t)G->nzp;
         const int rc = run_forward_columns(G, S, d_vol, d_sino, batch, stream);
         if (rc != LEAP_OK) return rc;
-        LEAP_HIP_CHECK(hipEventRecord(G->scratch_event, stream));
-        G->scratch_stream = stream;
-        G->scratch_used = true;
+        LEAP_HIP_CHECK(turn.end());
         return LEAP_OK;
     }
     for (int b = 0; b < batch; ++b) {

@@ -41,16 +41,28 @@ hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hi
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = nullptr; return hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = (hipEvent_t)std::malloc(1); return *e ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipEventDestroy(hipEvent_t e) { std::free((void *)e); return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "stub"; }
 // the host-memory entry points (leap_host.cpp): every asynchronous call happens at once, so the pipeline's buffer
 // rotation and chunk arithmetic are checked, not its overlap
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = nullptr; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+static long long g_capture = 0;                             // the capture every stream is in (0: none, below: the runtime will not say)
+static std::vector<std::pair<char, hipEvent_t>> g_order;    // waits 'w' and records 'r', in order
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t e, unsigned) { g_order.push_back({'w', e}); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { g_order.push_back({'r', e}); return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s)
+{
+    *s = g_capture > 0 ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return g_capture < 0 ? hipErrorStreamCaptureImplicit : hipSuccess;
+}
+hipError_t hipStreamGetCaptureInfo(hipStream_t, hipStreamCaptureStatus *s, unsigned long long *id)
+{
+    *id = (unsigned long long)g_capture;
+    return hipStreamIsCapturing(nullptr, s);
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
@@ -77,6 +89,28 @@ extern "C" long host_fail_allocation(long n)
 {
     g_fail_at = n;
     return g_allocations.exchange(0);
+}
+
+// n turns at one shared memory, on streams[k] in capture captures[k]; turn `abandoned` is not ended by its call.  out: per turn the event waited for
+// and the one recorded (0: none, 1: the eager turns', 2: the captured turns'), and what leap_capturing says of its stream.
+extern "C" void host_shared_turns(const int64_t *streams, const int64_t *captures, int n, int abandoned, int64_t (*out)[3])
+{
+    LeapShared shared;
+    (void)shared.create();
+    auto name = [&](hipEvent_t e) { return e == shared.done ? 1 : (e == shared.captured ? 2 : -1); };
+    for (int k = 0; k < n; ++k) {
+        g_capture = captures[k];
+        g_order.clear();
+        out[k][2] = leap_capturing((hipStream_t)streams[k]);
+        {
+            LeapTurn turn(shared, (hipStream_t)streams[k]);
+            (void)turn.begin();
+            if (k != abandoned) (void)turn.end();
+        }
+        out[k][0] = out[k][1] = 0;
+        for (const auto &call : g_order) out[k][call.first == 'r'] = name(call.second);
+    }
+    g_capture = 0;
 }
 
 int leap_static_scratch_init(int) { return LEAP_OK; }   // the fixed device array exists on a GPU only

@@ -69,6 +69,42 @@ def test_two_streams_and_a_captured_call():
     geo.close()
 
 
+@pytest.mark.parametrize("model,forward", [("sf", False), ("siddon", False), ("sf", True), ("siddon", True)])
+def test_threads_on_their_per_thread_streams(model, forward):
+    """hipStreamPerThread (the handle 2) is a stream of each thread's own: calls of two threads on one geometry share its memory in turn."""
+    import threading
+    import torch
+    from paper_2307_05801_amd import Geometry, binding
+    geo = Geometry(CASES["off_centre"].replace(nrows=24) if forward else CASES["off_centre"], model=model)
+    print(f"[gpu] {model}: {geo.describe()}", flush=True)
+    assert ("A=columns" if forward else "+parts(") in geo.describe(), geo.describe()
+    run, operator = (binding.leap_project, geo.project) if forward else (binding.leap_backproject, geo.backproject)
+    shape = geo.vol_shape if forward else geo.sino_shape
+    src = [torch.rand(shape, device="cuda") for _ in range(2)]
+    ref = [operator(s) for s in src]
+    out = [[torch.empty_like(ref[0]) for _ in range(20)] for _ in range(2)]
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(n):
+        try:
+            for o in out[n]:
+                run(geo.handle, src[n].data_ptr(), o.data_ptr(), 1, 2)
+            torch.cuda.ExternalStream(2, device="cuda:0").synchronize()      # (the stream goes with its thread)
+        except Exception as e:
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(n,)) for n in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    assert all(torch.equal(o, ref[n]) for n in range(2) for o in out[n])
+    geo.close()
+
+
 SIDDON = {"cone": scan(shift_v=0.3), "parallel": scan(PARALLEL, pixel_u=1.0, pixel_v=1.0, nviews=500, shift_v=0.27), "curved": scan(CONE_CURVED, shift_v=-0.2),
           "upright": perturbed_poses(scan(shift_v=0.2), 5, shift_mm=4.0, upright=True),
           "tilted": perturbed_poses(scan(shift_v=0.2), 5, shift_mm=4.0, tilt_rad=0.05),

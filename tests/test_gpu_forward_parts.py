@@ -77,3 +77,34 @@ def test_short_detectors_captured_and_on_the_fixed_array(monkeypatch, name):
     assert torch.equal(out, plain.project(x))
     plain.close()
     geo.close()
+
+
+def test_taller_detectors_captured():
+    """A graph of a scan that uses the handle's scratch, after eager calls on another stream: two branches of the capture take the scratch in turn,
+    and eager calls on other streams than the graph's follow."""
+    import torch
+    from paper_2307_05801_amd import Geometry
+    geo = Geometry(CASES["cone"][0])
+    x, z = (torch.rand(geo.vol_shape, device="cuda") for _ in range(2))
+    ref_x, ref_z = geo.project(x), geo.project(z)
+    out_x, out_z = torch.empty_like(ref_x), torch.empty_like(ref_z)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            geo.project(z, out_z)
+        geo.project(x, out_x)
+        torch.cuda.current_stream().wait_stream(side)
+    for _ in range(4):
+        out_x.zero_(), out_z.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out_x, ref_x) and torch.equal(out_z, ref_z)
+        with torch.cuda.stream(side):
+            beside = geo.project(z)
+        here = geo.project(x)
+        torch.cuda.synchronize()
+        assert torch.equal(here, ref_x) and torch.equal(beside, ref_z)
+    geo.close()

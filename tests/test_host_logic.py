@@ -1175,3 +1175,18 @@ def test_the_back_projection_s_order_of_tiles_names_every_tile_once(host, tiles_
     for tiles_y in range(1, 34):
         for y in (0, 1, 7, 8):
             assert host.host_check_tile_order(tiles_x, tiles_y, y) == 0, (tiles_y, y)
+
+
+def test_turns_at_a_handle_s_shared_memory_wait_for_one_another(host):
+    """Whatever the streams' handles: 2 is hipStreamPerThread, another stream in every thread, and a destroyed stream's handle may come back as
+    another stream's.  A call that returns early leaves its event too; captured turns are ordered within their capture, eager ones apart from them."""
+    def turns(streams, captures=None, abandoned=-1):
+        n = len(streams)
+        out = (C.c_int64 * 3 * n)()
+        host.host_shared_turns((C.c_int64 * n)(*streams), (C.c_int64 * n)(*(captures or [0] * n)), n, abandoned, out)
+        return [tuple(o) for o in out]
+
+    assert turns([2, 2, 7, 7, 0]) == [(0, 1, 0)] + [(1, 1, 0)] * 4
+    assert turns([2, 7, 7], abandoned=0) == [(0, 1, 0), (1, 1, 0), (1, 1, 0)]
+    assert turns([7, 5, 6, 5, 7, 7], [0, 11, 11, 12, 0, 0]) == [(0, 1, 0), (0, 2, 1), (2, 2, 1), (0, 2, 1), (1, 1, 0), (1, 1, 0)]
+    assert turns([0, 0], [0, -1]) == [(0, 1, 0), (1, 1, 1)]
