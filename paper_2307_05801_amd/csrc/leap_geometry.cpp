@@ -838,6 +838,25 @@ static void choose_siddon_split(leap_geometry *G, int nshapes, FitsFn fits)
     if (G->bp_split_shape < 0) G->bp_split_fits = 0;
 }
 
+// Siddon model, detectors of fewer than 32 rows: does the column-wise forward projection gain on one thread per ray, which reads only the voxels the
+// rays cross and copies nothing?  On circular scanners with one copy of the whole volume, at any number of views; with slabs of the volume (copied
+// once for either axis) where every voxel is crossed often enough.  Modules need more rows, crossings and views: their thread-per-ray kernel
+// is faster on few rays.  By a voxel's crossings (rays times slabs over voxels), column-wise over thread-per-ray: one copy, 16 to 31 rows, cone and cylinder
+// of 16^3 to 256^2 x 400 voxels 0.35 to 0.9, parallel beams from 22 rows 0.4 to 0.9; slabs, cone 16 rows 2.6 (0.2 crossings), 1.3 (2), 1.08 (6), 0.98
+// (18), 0.92 (22), 28 rows 2.6 (0.05), 1.1 (1.6), 0.6 (10), parallel 22 rows 3.3 (0.3), 1.3 (4), 1.05 (12), 0.87 (25); modules, one copy, 16 to 21 rows 0.7 to
+// 1.5, 22 rows and more 1.5 (0.1), 1.07 (4.4), 0.6 to 0.85 from 16 on, but 1.44 with four views of 16^2 x 7 voxels; slabs 5.6 (0.1), 1.16 (4), 1.0 (12).
+static bool siddon_columns_gain(const leap_geometry_desc *d)
+{
+    if (d->nrows >= 32) return true;
+    const bool modules = d->type == LEAP_MODULAR;
+    if (d->nrows < (d->type == LEAP_PARALLEL || modules ? 22 : 16)) return false;
+    const double n_side = std::max(d->nx, d->ny);
+    const bool whole = 4.0 * (n_side * n_side + 1.0) * (d->nz + 2.0 * FP_PAD) <= 128.0 * 1048576.0;
+    if (whole && !modules) return true;
+    const double crossings = (double)d->nviews * d->nrows * d->ncols * n_side / ((double)d->nx * d->ny * d->nz);
+    return crossings >= 16.0 && (!modules || d->nviews >= 15);
+}
+
 // Siddon model: static limits of the two fast kernels.
 static void select_siddon_fast_kernels(leap_geometry *G)
 {
@@ -848,7 +867,7 @@ static void select_siddon_fast_kernels(leap_geometry *G)
     // (short detectors leave most lanes idle; column-wise over one thread per ray, 30 / 720 views: 256^2 x 20 voxels, 22 rows, cone 0.54 / 0.64,
     // parallel 0.79 / 0.86; 128^2 x 15, 16 rows, 0.48 / 0.72 and 0.64 / 1.07; 256^2, 8 rows 0.85 / 1.64 and 1.02 / 2.16; tilted modules at 22
     // rows 0.96 / 1.24: those from 32 rows on)
-    if (d->nrows >= (d->type == LEAP_PARALLEL ? 22 : 16)) {
+    if (siddon_columns_gain(d)) {
         G->sd_columns = true;
         static const int single_groups[] = {1, 2, 4, 8};
         G->fp_rg = row_groups(d->nrows, 64, single_groups, 4);

@@ -1190,3 +1190,18 @@ def test_turns_at_a_handle_s_shared_memory_wait_for_one_another(host):
     assert turns([2, 7, 7], abandoned=0) == [(0, 1, 0), (1, 1, 0), (1, 1, 0)]
     assert turns([7, 5, 6, 5, 7, 7], [0, 11, 11, 12, 0, 0]) == [(0, 1, 0), (0, 2, 1), (2, 2, 1), (0, 2, 1), (1, 1, 0), (1, 1, 0)]
     assert turns([0, 0], [0, -1]) == [(0, 1, 0), (1, 1, 1)]
+
+
+@pytest.mark.parametrize("geom,n,nz,nrows,nviews,columns", [
+    (CONE, 96, 400, 16, 1, True), (CONE, 96, 400, 15, 60, False), (PARALLEL, 96, 400, 22, 1, True), (PARALLEL, 96, 400, 21, 60, False),
+    (CONE, 512, 512, 24, 15, False), (CONE, 512, 512, 24, 360, True), (CONE, 512, 512, 32, 1, True), (PARALLEL, 512, 512, 31, 100, False),
+    ("upright", 96, 400, 31, 60, False), ("upright", 96, 20, 31, 12, False), ("upright", 96, 20, 31, 15, True), ("upright", 96, 20, 21, 60, False)])
+def test_siddon_short_detectors_copy_a_volume_only_where_it_pays(host, geom, n, nz, nrows, nviews, columns):
+    """The column-wise forward projection copies the volume, the thread-per-ray kernel reads the few layers its rays cross."""
+    par = dict(sod=0.0, sdd=0.0) if geom == PARALLEL else dict(sod=2.0 * n, sdd=3.0 * n)
+    cfg = CTConfig("short", CONE if geom == "upright" else geom, nviews=nviews, arc_deg=360.0, nrows=nrows, ncols=n, pixel_v=1.0, pixel_u=1.5,
+                   nx=n, ny=n, nz=nz, voxel_xy=1.0, voxel_z=1.0, shift_v=0.2, **par)
+    h = handle(host, perturbed_poses(cfg, 5, shift_mm=3.0, upright=True) if geom == "upright" else cfg, B.LEAP_MODEL_SIDDON)
+    desc = B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
+    assert ("A=columns" in desc) == columns, desc
