@@ -592,9 +592,12 @@ static void launch_backproject_flat(const leap_geometry *G, const float *d_sino,
                            shares, G->flat_fv);
     };
     switch (few(tiles * groups)) {
-    case 4: go(sf_backproject_flat<NB, 4>, FlatTile<4>(), 0); break;
-    case 2: go(sf_backproject_flat<NB, 2>, FlatTile<2>(), 0); break;
-    default: go(sf_backproject_flat<NB, 1>, FlatTile<1>(), (size_t)waves * 64 * NB * sizeof(float));
+    case 4: go(sf_backproject_flat<NB, 4, true>, FlatTile<4>(), 0); break;
+    case 2: go(sf_backproject_flat<NB, 2, true>, FlatTile<2>(), 0); break;
+    default:
+        const size_t lds = (size_t)waves * 64 * NB * sizeof(float);
+        if (NB > 1 || shares > 1) go(sf_backproject_flat<NB, 1, true>, FlatTile<1>(), lds);
+        else go(sf_backproject_flat<1, 1, false>, FlatTile<1>(), lds);
     }
 }
 
