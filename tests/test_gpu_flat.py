@@ -117,6 +117,13 @@ def test_tiles_of_a_view_rounded_up_to_an_odd_number(oracle_mod, cfg):
     test_flat_kernels_match_oracle(oracle_mod, cfg, 3)
 
 
+@pytest.mark.parametrize("cfg", [scan(kind, 40, 41, 60, nviews) for kind in (PARALLEL, FAN) for nviews in (64, 65)], ids=lambda c: c.name)
+@pytest.mark.parametrize("batch", [5, 16, 23])
+def test_groups_of_four_items_where_eight_leave_units_idle(oracle_mod, cfg, batch):
+    """On either side of the number of workgroups, whole and ragged groups, and the rest of a batch that the scratch holds no more of."""
+    test_flat_kernels_match_oracle(oracle_mod, cfg, batch)
+
+
 @pytest.mark.parametrize("nx,ny", [(64, 64), (65, 64), (121, 61), (128, 64), (129, 64)])
 @pytest.mark.parametrize("geom,nviews", [(PARALLEL, 64), (FAN, 63), (FAN, 64), (FAN, 131)])
 def test_few_tiles_take_several_views_at_a_time(oracle_mod, geom, nx, ny, nviews):
