@@ -24,18 +24,29 @@
  *     leap_geometry_create.  Device memory beyond the caller's arrays ("Performance and
  *     Memory Usage" asks for one copy of each array only): the fast forward kernels read the
  *     volume through a z-fastest scratch copy, one SLAB of the volume at a time, so the handle
- *     owns a scratch of at most max(64 MiB, an eighth of one volume) -- leap_geometry_describe
- *     reports its size as "scratch=<bytes>"; small volumes share it between the items of a batch.
+ *     owns a scratch: an eighth of one volume (LEAP_MODEL_SIDDON: a quarter) from 512 MiB volumes
+ *     on, up to 128 MiB below, which small volumes share between the items of a batch.
  *     Flat scans (one row, one layer) keep room for two copies of up to 16 slices (256 MiB at most)
- *     instead, which leap_project uses for batches outside stream capture; it is allocated with
+ *     instead, which leap_project uses for batches outside stream capture.  Back projections of
+ *     few voxels and many views, shared among many workgroups outside stream capture, keep room for
+ *     the workgroups' partial volumes (64 MiB at most: those of up to 16 items at once).
+ *     leap_geometry_describe reports the sum of these as "scratch=<bytes>".  They are allocated with
  *     the handle, because a call may arrive while another stream is being captured.
- *     If it cannot be allocated the handle works without it on a slower kernel, says so in
- *     leap_last_error at creation and in a "note=" of leap_geometry_describe.  A
+ *     What cannot be allocated the handle works without, on slower kernels, and says so in a
+ *     "note=" of leap_geometry_describe (the forward scratch: in leap_last_error at creation too).  A
  *     LEAP_MODEL_SIDDON handle also keeps a table of 48 bytes per (view, detector column): the
  *     constants of each ray's line; a LEAP_CONE_CURVED footprint handle 24 bytes per (16x16
- *     voxel-column tile, view).  leap_project calls on one handle share its scratch; the library
- *     orders them on the device (a call arriving on another stream than the previous one first
- *     waits for that one's kernels), so any stream may be used; distinct handles are independent.
+ *     voxel-column tile, view).  leap_project calls on one handle share its scratch, and
+ *     leap_backproject calls that share the views among workgroups its room for them; the library
+ *     orders the calls that do on the device (each first waits for the previous one's kernels), so any
+ *     stream and thread may be used, but such calls do not overlap; distinct handles are independent.
+ *     A captured leap_project call of 32 detector rows or more uses the scratch when its graph is
+ *     launched, which the library does not see: order such launches with the handle's other calls.
+ *   - Results: the same call on the same handle gives the same bits every time, whatever else runs.
+ *     Sums may come in another order, and differ in the last bits, between an item by itself and the
+ *     same item in a batch; between an eager and a captured leap_backproject call of few voxels and
+ *     many views ("+parts(...)" in leap_geometry_describe); between an eager leap_project call of
+ *     fewer than 32 detector rows (with "A=columns") and a captured one or leap_project_static_scratch.
  *   - World frame: voxel centres x_i = center_x + (i-(nx-1)/2) voxel_xy (y, z alike); view
  *     angle phi counter-clockwise from +x, the source sits at sod*(cos phi, sin phi, 0);
  *     detector columns grow along (-sin phi, cos phi, 0), rows along +z; pixel centres
@@ -124,11 +135,13 @@ void leap_geometry_destroy(leap_geometry *geom);
 int leap_project(const leap_geometry *geom, const float *d_vol, float *d_sino, int32_t batch, void *hip_stream);
 
 /* Back projection x = A^T y, the exact transpose of leap_project ("matched projectors"), voxel-driven
- * gather without atomics (bitwise reproducible): d_vol[b] = A^T d_sino[b].  Asynchronous on hip_stream. */
+ * gather without atomics (bitwise reproducible, see "Results" above): d_vol[b] = A^T d_sino[b].  Asynchronous on
+ * hip_stream.  Scans of few voxels and many views use the handle's room for partial volumes (see above). */
 int leap_backproject(const leap_geometry *geom, const float *d_sino, float *d_vol, int32_t batch, void *hip_stream);
 
 /* leap_project for callers that cannot allocate device memory: code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc.  Same arguments, same result as leap_project, same kernels; the z-fastest copy of
+ * harnesses that forbid hipMalloc.  Same arguments and, from 32 detector rows on, the kernels of leap_project and its
+ * results (to the last bits where its slabs are narrower than the handle's); the z-fastest copy of
  * the volume's slabs is kept in a fixed array of 72 MiB inside the library's device code (every GPU the library runs
  * on holds that array until the process ends) instead of the handle's own scratch.  The call allocates and frees
  * nothing and calls no allocating routine; the array's address is looked up once per device in leap_geometry_create.
@@ -187,7 +200,8 @@ const char *leap_last_error(void);
  * "general(tiled)" are the fast kernels of flat scans and of footprints on tilted modules, which read those arrays too;
  * "tiled(...)" is the kernel of one volume per workgroup, "+mirror(...)" a volume and its mirror image per workgroup in its
  * place, "+pairs(...)" the kernel two items of a batch take, "+split(...)" the one with shared views that a single volume
- * takes before any of them, "+parts(n,...)" the views shared among n workgroups outside stream capture), "scratch=<bytes>" the device memory the handle owns beyond its tables, "note=..." anything that went
+ * takes before any of them, "+parts(n,...)" the views shared among n workgroups outside stream capture), "scratch=<bytes>" the device memory
+ * the handle owns beyond its tables (forward scratch and room for partial volumes), "note=..." anything that went
  * differently from the plan at creation.  Returns LEAP_OK or LEAP_INVALID_ARG.
  *
  * Debugging aid: the environment variable LEAP_DEBUG, read by leap_geometry_create, overrides the choices shown

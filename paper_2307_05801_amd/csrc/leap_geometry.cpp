@@ -49,6 +49,12 @@ static int invalid(const char *why)
     return LEAP_INVALID_ARG;
 }
 
+static void add_note(leap_geometry *G, const char *what)
+{
+    if (!G->note.empty()) G->note += "; ";
+    G->note += what;
+}
+
 static bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
 // Siddon model: constants of the line of every (view, detector column), in double ("sd_ray.h" states the formulation).
@@ -1076,7 +1082,7 @@ static void select_tilted_siddon_kernels(leap_geometry *G)
         G->d_mdbp = nullptr;
         (void)hipGetLastError();
         no_tiled_back_projection(G);
-        G->note = "table allocation failed: back projection runs on the general kernel";
+        add_note(G, "table allocation failed: back projection runs on the general kernel");
         return;
     }
     G->bp_tiled = true;
@@ -1226,8 +1232,9 @@ static void allocate_forward_scratch(leap_geometry *G)
         G->d_volz = nullptr; G->d_major = nullptr;
         G->fp_columns = G->sd_columns = false;
         G->scratch_bytes = 0;
-        G->note = "scratch allocation failed: forward projection runs on the general kernel";
-        leap_set_error(std::string("leap_geometry_create: ") + G->note + " (" + hipGetErrorString(e) + ")");
+        const char *const what = "scratch allocation failed: forward projection runs on the general kernel";
+        add_note(G, what);
+        leap_set_error(std::string("leap_geometry_create: ") + what + " (" + hipGetErrorString(e) + ")");
         (void)hipGetLastError();
         return;
     }
@@ -1248,7 +1255,7 @@ static void allocate_flat_scratch(leap_geometry *G)
     if (G->d_volz) (void)hipFree(G->d_volz);
     G->d_volz = nullptr;
     G->scratch_bytes = 0;
-    G->note = "scratch allocation failed: the items of a batch are projected one by one";
+    add_note(G, "scratch allocation failed: the items of a batch are projected one by one");
     (void)hipGetLastError();
 }
 
@@ -1266,7 +1273,7 @@ static void allocate_back_room(leap_geometry *G)
     G->back_floats = 0;
     G->bp_parts = 1;
     G->bp_parts_fits = 0;
-    G->note = "no room for the back projection's parts: its views stay with one workgroup";
+    add_note(G, "no room for the back projection's parts: its views stay with one workgroup");
     (void)hipGetLastError();
 }
 
@@ -1323,7 +1330,7 @@ static void upload_curved_tables(leap_geometry *G)
         if (G->d_colcs) (void)hipFree(G->d_colcs);
         G->d_colcs = nullptr;
         no_tiled_back_projection(G);
-        G->note = "no room for the cylinder's tile tables: back projection runs on the general kernel";
+        add_note(G, "no room for the cylinder's tile tables: back projection runs on the general kernel");
         (void)hipGetLastError();
     }
 }
@@ -1682,7 +1689,7 @@ extern "C" int leap_geometry_describe(const leap_geometry *G, char *buf, int32_t
     }
     const char *modules = G->g.type != SF_MODULAR ? "" : (G->geoms.empty() ? " (tilted modules)" : " (upright modules)");
     std::snprintf(buf, (size_t)cap, "type=%d model=%s A=%s AT=%s scratch=%zu%s cols/voxel<=%.2f rows/voxel<=%.2f voxels/row<=%.2f%s%s",
-                  G->g.type, siddon ? "siddon" : "sf", fwd, back, G->scratch_bytes, modules, G->max_cols_per_voxel,
+                  G->g.type, siddon ? "siddon" : "sf", fwd, back, G->scratch_bytes + G->back_floats * sizeof(float), modules, G->max_cols_per_voxel,
                   G->max_rows_per_voxel, G->max_voxels_per_row, G->note.empty() ? "" : " note=", G->note.c_str());
     return LEAP_OK;
 }

@@ -30,12 +30,14 @@
 extern "C" {
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 static long g_device_fail_at = -1;
+static size_t g_device_limit = ~(size_t)0;
 hipError_t hipMalloc(void **p, size_t n)
 {
-    *p = g_device_fail_at >= 0 && g_device_fail_at-- == 0 ? nullptr : std::malloc(n);
+    *p = (g_device_fail_at >= 0 && g_device_fail_at-- == 0) || n > g_device_limit ? nullptr : std::malloc(n);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 void host_fail_device_allocation(long n) { g_device_fail_at = n; }   // the n-th device allocation from now on fails (n < 0: none does)
+void host_limit_device_allocations(size_t bytes) { g_device_limit = bytes ? bytes : ~(size_t)0; }         // larger ones fail from now on (0: none does)
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }

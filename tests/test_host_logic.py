@@ -1205,3 +1205,33 @@ def test_siddon_short_detectors_copy_a_volume_only_where_it_pays(host, geom, n, 
     desc = B.leap_geometry_describe(h, host)
     B.leap_geometry_destroy(h, host)
     assert ("A=columns" in desc) == columns, desc
+
+
+FEW_TILES = CTConfig("few_tiles", CONE, nviews=203, arc_deg=360.0, nrows=40, ncols=60, pixel_v=1.5, pixel_u=1.6, nx=37, ny=35, nz=27, voxel_xy=1.0,
+                     voxel_z=1.0, start_deg=3.0, shift_u=0.3, shift_v=0.3, sod=150.0, sdd=225.0)
+
+
+@pytest.mark.parametrize("model", [B.LEAP_MODEL_SF, B.LEAP_MODEL_SIDDON])
+def test_room_for_the_parts_of_a_back_projection_is_reported(host, monkeypatch, model):
+    """scratch= is all the device memory the handle owns beyond its tables; what was not to be had is in the notes, every one of them."""
+    def describe(lib):
+        h = handle(lib, FEW_TILES, model)
+        desc = B.leap_geometry_describe(h, lib)
+        B.leap_geometry_destroy(h, lib)
+        return desc
+
+    desc = describe(host)
+    parts = int(desc.split("+parts(")[1].split(",")[0])
+    monkeypatch.setenv("LEAP_DEBUG", "bp_parts=1")
+    whole = describe(host)
+    one = 4 * parts * FEW_TILES.nx * FEW_TILES.ny * FEW_TILES.nz
+    assert "+parts(" not in whole and scratch_bytes(desc) - scratch_bytes(whole) == one * min(16, (64 << 20) // one), (desc, whole)
+    if model == B.LEAP_MODEL_SF:                              # (the other's ray table is as large as its scratch)
+        monkeypatch.delenv("LEAP_DEBUG")
+        host.host_limit_device_allocations.argtypes = [C.c_size_t]
+        host.host_limit_device_allocations(100 << 10)
+        try:
+            poor = describe(host)
+        finally:
+            host.host_limit_device_allocations(0)
+        assert scratch_bytes(poor) == 0 and "forward projection runs on the general kernel" in poor and "no room for the back projection's parts" in poor, poor
