@@ -1241,15 +1241,19 @@ static void allocate_forward_scratch(leap_geometry *G)
     G->slab_width = width;
 }
 
-// Flat scans: room for the batch-fastest copies, by rows and turned, of up to 16 slices, 256 MiB at most.  Without it every item of a batch is
-// projected by itself.
+// Flat scans: room for the batch-fastest copies, by rows and turned, of up to 16 slices, 256 MiB at most; of half as many, and so on
+// down to two, where that cannot be had.  Without it every item of a batch is projected by itself.
 static void allocate_flat_scratch(leap_geometry *G)
 {
     const double slice = 4.0 * G->desc.nx * (double)G->desc.ny;
     double items = std::fmin(16.0, std::floor(128.0 * 1048576.0 / slice));
     if (!(items >= 2.0)) return;
-    G->scratch_bytes = (size_t)(2.0 * items * slice);
-    hipError_t e = hipMalloc((void **)&G->d_volz, G->scratch_bytes);
+    hipError_t e = hipErrorOutOfMemory;
+    for (; e != hipSuccess && items >= 2.0; items = std::floor(0.5 * items)) {
+        G->scratch_bytes = (size_t)(2.0 * items * slice);
+        e = hipMalloc((void **)&G->d_volz, G->scratch_bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+    }
     if (e == hipSuccess) e = G->scratch.create();
     if (e == hipSuccess) return;
     if (G->d_volz) (void)hipFree(G->d_volz);

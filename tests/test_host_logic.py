@@ -1235,3 +1235,18 @@ def test_room_for_the_parts_of_a_back_projection_is_reported(host, monkeypatch, 
         finally:
             host.host_limit_device_allocations(0)
         assert scratch_bytes(poor) == 0 and "forward projection runs on the general kernel" in poor and "no room for the back projection's parts" in poor, poor
+
+
+@pytest.mark.parametrize("limit,items", [(0, 16), (20 << 20, 8), (5 << 20, 2), (3 << 20, 0)])
+def test_flat_scratch_shrinks_to_what_can_be_had(host, limit, items):
+    """Two copies of 16 slices of 1 MB where there is room for them, of fewer where there is not, none below two slices."""
+    cfg = CTConfig("slice", PARALLEL, nviews=90, arc_deg=180.0, nrows=1, ncols=600, pixel_v=1.0, pixel_u=1.0, nx=500, ny=500, nz=1, voxel_xy=1.0, voxel_z=1.0)
+    host.host_limit_device_allocations.argtypes = [C.c_size_t]
+    host.host_limit_device_allocations(limit)
+    try:
+        h = handle(host, cfg)
+    finally:
+        host.host_limit_device_allocations(0)
+    desc = B.leap_geometry_describe(h, host)
+    B.leap_geometry_destroy(h, host)
+    assert scratch_bytes(desc) == 2 * items * 1000000 and ("note=" in desc) == (items == 0), desc
