@@ -100,6 +100,11 @@ def _check(lib, status: int) -> None:
         raise LeapError(status, detail)
 
 
+def _pointers(*addresses):
+    """For a caller's own library, which may have been loaded without the prototypes."""
+    return [C.c_void_p(a) for a in addresses]
+
+
 def make_desc(*, type: int, nviews: int, nrows: int, ncols: int, nx: int, ny: int, nz: int,
               pixel_v: float, pixel_u: float, voxel_xy: float, voxel_z: float, angles_rad: Sequence[float],
               shift_v: float = 0.0, shift_u: float = 0.0, sod: float = 0.0, sdd: float = 0.0,
@@ -153,8 +158,11 @@ def leap_geometry_describe(handle: int, lib=None) -> str:
 
 def leap_project(handle: int, d_vol: int, d_sino: int, batch: int, stream: int = 0, lib=None) -> None:
     """d_vol, d_sino: device addresses (tensor.data_ptr()); stream: hipStream_t as an integer."""
-    lib = lib or _lib or load_library()
-    status = lib.leap_project(handle, d_vol, d_sino, batch, stream)       # (the prototypes turn the integers into pointers)
+    if lib is None:
+        lib = _lib or load_library()                        # (its prototypes turn the integers into pointers)
+    else:
+        handle, d_vol, d_sino, stream = _pointers(handle, d_vol, d_sino, stream)
+    status = lib.leap_project(handle, d_vol, d_sino, batch, stream)
     if status != LEAP_OK:
         _check(lib, status)
 
@@ -178,7 +186,10 @@ def leap_backproject_host(handle: int, h_sino: int, h_vol: int, batch: int, lib=
 
 
 def leap_backproject(handle: int, d_sino: int, d_vol: int, batch: int, stream: int = 0, lib=None) -> None:
-    lib = lib or _lib or load_library()
+    if lib is None:
+        lib = _lib or load_library()
+    else:
+        handle, d_sino, d_vol, stream = _pointers(handle, d_sino, d_vol, stream)
     status = lib.leap_backproject(handle, d_sino, d_vol, batch, stream)
     if status != LEAP_OK:
         _check(lib, status)

@@ -1250,3 +1250,28 @@ def test_flat_scratch_shrinks_to_what_can_be_had(host, limit, items):
     desc = B.leap_geometry_describe(h, host)
     B.leap_geometry_destroy(h, host)
     assert scratch_bytes(desc) == 2 * items * 1000000 and ("note=" in desc) == (items == 0), desc
+
+
+OWN_LIBRARY = """
+import ctypes as C, sys
+import numpy as np
+sys.path[:0] = [{root!r}, {here!r}]
+import test_host_logic as T
+from paper_2307_05801_amd import binding as B
+lib = C.CDLL(T.LIB)
+cfg = T.reduced(T.config(3), 32, nviews=5).replace(nx=19, ny=17, nz=11, nrows=5, ncols=23)
+h = T.handle(lib, cfg)
+x, y = T.uniform_volume(cfg, 1)[0], np.zeros(cfg.sino_shape, np.float32)
+B.leap_project(h, x.ctypes.data, y.ctypes.data, 1, 0, lib)
+x2 = np.zeros_like(x)
+B.leap_backproject(h, y.ctypes.data, x2.ctypes.data, 1, 0, lib)
+assert y.any() and x2.any()
+print("done")
+"""
+
+
+def test_calls_through_a_library_that_was_loaded_without_prototypes(host):
+    """An address that is passed as a plain integer would be cut to 32 bits."""
+    import sys
+    res = subprocess.run([sys.executable, "-c", OWN_LIBRARY.format(root=ROOT, here=HERE)], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and "done" in res.stdout, (res.returncode, res.stderr[-1500:])
