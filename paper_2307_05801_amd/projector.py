@@ -15,6 +15,13 @@ from . import binding as B
 _current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
+def _empty(like: torch.Tensor, shape) -> torch.Tensor:
+    """A plain tensor beside `like` (new_empty takes 0.4 us less than torch.empty, but keeps a subclass)."""
+    if type(like) is torch.Tensor:
+        return like.new_empty(shape)
+    return torch.empty(shape, dtype=like.dtype, device=like.device)
+
+
 class Geometry:
     """Owns one leap_geometry handle on one GPU."""
 
@@ -33,11 +40,19 @@ class Geometry:
             desc, keep = B.make_desc(model=B.MODELS[model], **desc_kwargs)
         self.nviews, self.nrows, self.ncols = desc.nviews, desc.nrows, desc.ncols
         self.nx, self.ny, self.nz = desc.nx, desc.ny, desc.nz
-        self.vol_shape = (self.nz, self.ny, self.nx)
-        self.sino_shape = (self.nviews, self.nrows, self.ncols)
+        self._vol_shape = (self.nz, self.ny, self.nx)
+        self._sino_shape = (self.nviews, self.nrows, self.ncols)
         with torch.cuda.device(self.device):
             self.handle = B.leap_geometry_create(desc)
         del keep
+
+    @property
+    def vol_shape(self):
+        return self._vol_shape
+
+    @property
+    def sino_shape(self):
+        return self._sino_shape
 
     def describe(self) -> str:
         return B.leap_geometry_describe(self.handle)
@@ -83,9 +98,9 @@ class Geometry:
 
     def project(self, vol: torch.Tensor, out: torch.Tensor = None) -> torch.Tensor:
         """A vol; vol [..., nz, ny, nx] -> [..., nviews, nrows, ncols]."""
-        batch = self._check(vol, self.vol_shape, "volume")
+        batch = self._check(vol, self._vol_shape, "volume")
         if out is None:
-            out = vol.new_empty(vol.shape[:-3] + self.sino_shape)
+            out = _empty(vol, vol.shape[:-3] + self._sino_shape)
         elif self._check(out, self.sino_shape, "output sinogram") != batch:
             raise ValueError("output batch mismatch")
         self._call(B.leap_project, vol, out, batch)
@@ -93,9 +108,9 @@ class Geometry:
 
     def backproject(self, sino: torch.Tensor, out: torch.Tensor = None) -> torch.Tensor:
         """A^T sino; sino [..., nviews, nrows, ncols] -> [..., nz, ny, nx]."""
-        batch = self._check(sino, self.sino_shape, "sinogram")
+        batch = self._check(sino, self._sino_shape, "sinogram")
         if out is None:
-            out = sino.new_empty(sino.shape[:-3] + self.vol_shape)
+            out = _empty(sino, sino.shape[:-3] + self._vol_shape)
         elif self._check(out, self.vol_shape, "output volume") != batch:
             raise ValueError("output batch mismatch")
         self._call(B.leap_backproject, sino, out, batch)

@@ -498,3 +498,19 @@ def test_tilted_scan_without_footprints_is_refused(torch_mod):
     with pytest.raises(B.LeapError) as err:
         Geometry(cfg, model="sf")
     assert err.value.status == B.LEAP_BAD_GEOMETRY
+
+
+def test_outputs_are_plain_tensors_whatever_the_input_s_class():
+    import torch
+    from paper_2307_05801_amd import Geometry
+
+    class Tagged(torch.Tensor):
+        pass
+
+    geo = Geometry(reduced(config(3), 32, nviews=5))
+    y = geo.project(torch.ones(geo.vol_shape, device="cuda").as_subclass(Tagged))
+    x = geo.backproject(y.as_subclass(Tagged))
+    assert type(y) is torch.Tensor and type(x) is torch.Tensor
+    with pytest.raises(AttributeError):
+        geo.vol_shape = (1, 1, 1)
+    geo.close()
