@@ -725,8 +725,8 @@ static void select_footprint_flat(leap_geometry *G)
     const leap_geometry_desc *d = &G->desc;
     const SfGeom &g = G->g;
     if (!(d->type == LEAP_FAN || (d->type == LEAP_PARALLEL && d->nrows == 1 && d->nz == 1))) return;
-    // a launch holds fewer than 2^32 threads, and the forward kernel needs a wave per view and 64 columns
-    if (!((double)((d->ncols + FLAT_RAYS - 1) / FLAT_RAYS) * d->nviews * 64.0 < 4294967296.0)) return;
+    // a launch holds fewer than 2^32 threads, and the forward kernel needs a wave per view and tile of 64 columns
+    if (!((double)flat_tiles(d->ncols, d->nviews) * d->nviews * 64.0 < 4294967296.0)) return;
     // widest footprint of any voxel, on the detector or beside it (footprint_bounds looks at the detector's fan only)
     const double rx = std::fabs(d->center_x) + 0.5 * d->nx * d->voxel_xy, ry = std::fabs(d->center_y) + 0.5 * d->ny * d->voxel_xy;
     const double reach = std::sqrt(rx * rx + ry * ry);

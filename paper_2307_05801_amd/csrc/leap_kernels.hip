@@ -494,12 +494,10 @@ static void launch_project_flat(const leap_geometry *G, const float *src, const 
     int waves = flat_waves((double)tiles * g.nviews, g.nx < g.ny ? g.nx : g.ny);
     while ((size_t)waves * G->flat_span * sizeof(SfFlatRec) > 65536) waves /= 2;        // (spans of up to 256: at least 8 fit)
     const size_t lds = (size_t)waves * (parallel ? 64 * NB * sizeof(float) : G->flat_span * sizeof(SfFlatRec));
-    // an odd number of tiles (see the kernel) where there are more than two and more than two workgroups per CU: over the number as it is
-    // 4 tiles of 200 views 0.91 to 0.98, of 60 views 1.15; 2 tiles, 90 to 2000 views 1.02 to 1.40
-    const int odd_tiles = tiles > 2 && (double)tiles * g.nviews > 512.0 ? tiles | 1 : tiles;
+    const int grid_tiles = flat_tiles(g.ncols, g.nviews);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)odd_tiles * (unsigned)g.nviews, groups), dim3(64 * waves), lds, stream, g, G->d_views, src, turned,
-                           d_sino, odd_tiles, G->flat_span, items, G->flat_fv);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid_tiles * (unsigned)g.nviews, groups), dim3(64 * waves), lds, stream, g, G->d_views, src, turned,
+                           d_sino, grid_tiles, G->flat_span, items, G->flat_fv);
     };
     if (parallel) go(sf_project_flat<NB, true>);
     else go(sf_project_flat<NB, false>);

@@ -40,6 +40,15 @@ constexpr int FLAT_AHEAD = 3, FLAT_AHEAD_8 = 2;
 // fan / parallel beams.  With over without: fan 36000 to 148000 steps 1.04 to 1.13, 226000 0.83, 282000 1.00, 1400000 and 4400000 0.96 and
 // 0.95; parallel 32000 1.05, 46000 0.90, 950000 0.77.  One item gains nothing.
 constexpr double FLAT_TURN_STEPS = 2e5, FLAT_TURN_STEPS_PARALLEL = 4e4;
+// Tiles of 64 columns per view: an odd number (see sf_project_flat) where there are more than two and more than two workgroups per CU, and
+// one launch (fewer than 2^32 threads) holds it.  Odd over the number as it is: 4 tiles of 200 views 0.91 to 0.98, of 60 views 1.15; 2 tiles, 90 to 2000
+// views 1.02 to 1.40.
+SF_HD int flat_tiles(int ncols, int nviews)
+{
+    const int tiles = ncols / FLAT_RAYS + (ncols % FLAT_RAYS != 0);
+    return tiles > 2 && (double)tiles * nviews > 512.0 && (double)(tiles | 1) * nviews * 64.0 < 4294967296.0 ? tiles | 1 : tiles;
+}
+
 constexpr int FLAT_T = 8;            // tile edge of the back projection, voxels
 // Widest footprint of any voxel, in detector columns, and the columns a voxel can then touch.  A tile's voxel lies at most
 // 4 sqrt(2) T from the voxel the window is centred on, and a displacement of sqrt(2) T moves the shadow by at most the

@@ -85,7 +85,7 @@ __global__ __launch_bounds__((PARTS > 1 ? PARTS : FP_WAVES) * 64) void sf_projec
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int ct, band, a;
-    if (!fp_block(tb, vb, turn, vgroups_pad, tiles_per_xcd_pad, col_tiles, g.nviews, bands, ct, band, a)) return;      // (no barrier follows)
+    if (!fp_block(tb, vb, turn, vgroups_pad, tiles_per_xcd_pad, col_tiles, g.nviews, bands, ct, band, a)) return;      // (whole workgroups)
     const int bundle = PARTS > 1 ? ct : ct * FP_WAVES + wave, part = PARTS > 1 ? wave : 0, c0 = bundle * CW;
     if (c0 >= g.ncols) return;                                               // (waves that share a bundle return together)
     const int nbundles = (g.ncols + CW - 1) / CW;

@@ -1068,6 +1068,7 @@ extern "C" long host_project_rows(const leap_geometry *G, const float *vol, floa
 // ---- flat scans: a wave's records per slab, a thread's columns in the staged window ---------------------------------------------
 // report[0]: candidate voxels that the wave's outermost columns do not bound or the records do not hold; report[1]: columns read
 // outside the 64 staged ones.  Returns -1 when the handle does not use these kernels.
+extern "C" int host_flat_tiles(int ncols, int nviews) { return flat_tiles(ncols, nviews); }
 extern "C" long host_flat(const leap_geometry *G, const float *vol, float *sino, const float *sino_in, float *vol_out, int64_t *report)
 {
     const SfGeom &g = G->g;

@@ -381,6 +381,15 @@ def test_flat_scans_beyond_one_launch_keep_the_general_kernels(host):
     assert "flat" not in describe(65537)
 
 
+def test_flat_launches_hold_what_the_selection_admits(host):
+    """Fewer than 2^32 threads of 64 per view and tile, although an even number of tiles is rounded up to an odd one."""
+    assert [host.host_flat_tiles(c, v) for c, v in ((128, 4000), (129, 100), (256, 128), (256, 129), (320, 200))] == [2, 3, 4, 5, 5]
+    for tiles, nviews in ((671088, 100), (671087, 100), (671086, 100), (1024, 65535), (1022, 65535), (4, 65535)):
+        assert tiles * nviews * 64 < 1 << 32
+        assert host.host_flat_tiles(64 * tiles, nviews) * nviews * 64 < 1 << 32, (tiles, nviews)
+    assert host.host_flat_tiles(64 * 671088, 100) == 671088 and host.host_flat_tiles(64 * 671086, 100) == 671087
+
+
 def test_every_staged_sample_has_one_writer(host):
     """Two threads that write one LDS cell in different steps race, even where they mean to write the same value."""
     host.host_check_staging_roles.restype = C.c_long
