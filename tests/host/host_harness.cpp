@@ -289,7 +289,7 @@ extern "C" int host_check_backproject_windows(const leap_geometry *G, int64_t *r
         report[7] += r[3];
     }
     for (int sh = 0; sh < BP_NSPLIT_SHAPES; ++sh)
-        if (G->bp_split_fits >> sh & 1u) {
+        if ((G->bp_split_fits | G->bp_parts_fits) >> sh & 1u) {
             host_check_windows(G, BP_SPLIT_SHAPES[sh], kfirst, r);
             report[7] += r[3];
         }
@@ -727,13 +727,16 @@ static void host_sd_bp_shape(const leap_geometry *G, const float *sino, float *v
     report[0] = wide; report[1] = outside; report[2] = badslot; report[3] = shared;
 }
 
-// The shape one volume takes.
+// The shape with shared views that one volume takes, -1: none (each group of threads, and each part, takes some of the views: the same windows and slots).
+static int host_shared_views_shape(const leap_geometry *G) { return G->bp_parts > 1 ? G->bp_parts_shape : G->bp_split_shape; }
+
 extern "C" long host_sd_backproject_tiled(const leap_geometry *G, const float *sino, float *vol, int64_t *report)
 {
     if (G->g.model != SF_MODEL_SIDDON || G->d_mdbp || !G->bp_tiled) return -1;
     static_assert(SD_BP_NSPLIT_SHAPES == 2, "every shape has a case");
-    if (G->bp_split_shape >= 0) {             // (each group of threads takes every fourth view: the same windows and slots)
-        if (G->bp_split_shape == 0) host_sd_bp_shape<SD_BP_SPLIT_SHAPES[0].zc, SD_BP_SPLIT_SHAPES[0].pw, SD_BP_SPLIT_SHAPES[0].ph>(G, sino, vol, report);
+    const int split = host_shared_views_shape(G);
+    if (split >= 0) {
+        if (split == 0) host_sd_bp_shape<SD_BP_SPLIT_SHAPES[0].zc, SD_BP_SPLIT_SHAPES[0].pw, SD_BP_SPLIT_SHAPES[0].ph>(G, sino, vol, report);
         else host_sd_bp_shape<SD_BP_SPLIT_SHAPES[1].zc, SD_BP_SPLIT_SHAPES[1].pw, SD_BP_SPLIT_SHAPES[1].ph>(G, sino, vol, report);
         return report[0] + report[1] + report[2] + report[3];
     }
@@ -879,9 +882,10 @@ extern "C" long host_md_backproject_tiled(const leap_geometry *G, const float *s
 {
     if (!G->d_mdbp || !G->bp_tiled) return -1;
     static_assert(MD_BP_NSPLIT_SHAPES == 3, "every shape has a case");
-    if (G->bp_split_shape >= 0) {
-        if (G->bp_split_shape == 2) host_md_bp_shape<MD_BP_SPLIT_SHAPES[2].zc, MD_BP_SPLIT_SHAPES[2].pw, MD_BP_SPLIT_SHAPES[2].ph>(G, sino, vol, report);
-        else if (G->bp_split_shape == 0) host_md_bp_shape<MD_BP_SPLIT_SHAPES[0].zc, MD_BP_SPLIT_SHAPES[0].pw, MD_BP_SPLIT_SHAPES[0].ph>(G, sino, vol, report);
+    const int split = host_shared_views_shape(G);
+    if (split >= 0) {
+        if (split == 2) host_md_bp_shape<MD_BP_SPLIT_SHAPES[2].zc, MD_BP_SPLIT_SHAPES[2].pw, MD_BP_SPLIT_SHAPES[2].ph>(G, sino, vol, report);
+        else if (split == 0) host_md_bp_shape<MD_BP_SPLIT_SHAPES[0].zc, MD_BP_SPLIT_SHAPES[0].pw, MD_BP_SPLIT_SHAPES[0].ph>(G, sino, vol, report);
         else host_md_bp_shape<MD_BP_SPLIT_SHAPES[1].zc, MD_BP_SPLIT_SHAPES[1].pw, MD_BP_SPLIT_SHAPES[1].ph>(G, sino, vol, report);
         return report[0] + report[1] + report[2];
     }
@@ -1068,6 +1072,13 @@ extern "C" long host_project_rows(const leap_geometry *G, const float *vol, floa
 // ---- flat scans: a wave's records per slab, a thread's columns in the staged window ---------------------------------------------
 // report[0]: candidate voxels that the wave's outermost columns do not bound or the records do not hold; report[1]: columns read
 // outside the 64 staged ones.  Returns -1 when the handle does not use these kernels.
+// Back projection of a launch's items with the views shared among workgroups: out = {parts, shape, items at a time, shape one volume takes without parts}.
+extern "C" void host_back_parts(const leap_geometry *G, int items, int32_t *out)
+{
+    const bool siddon = G->g.model == SF_MODEL_SIDDON;
+    const LeapBackParts p = siddon ? leap_siddon_parts(G, items) : leap_back_parts(G, items);
+    out[0] = p.parts; out[1] = p.shape; out[2] = p.items; out[3] = G->bp_split_shape;
+}
 extern "C" int host_flat_tiles(int ncols, int nviews) { return flat_tiles(ncols, nviews); }
 extern "C" long host_flat(const leap_geometry *G, const float *vol, float *sino, const float *sino_in, float *vol_out, int64_t *report)
 {

@@ -127,3 +127,28 @@ def test_siddon_parts_match_oracle(oracle_mod, name):
     assert rel_l2(three[1].cpu().numpy(), one.cpu().numpy()) <= 1e-6
     assert torch.equal(one, geo.backproject(yt[1].contiguous()))
     geo.close()
+
+
+# name: scan, model, batch of which the room holds some items at a time (what each launch of theirs takes: test_host_logic.py)
+ROUNDS = {"cone": (scan(nviews=301, nx=80, ny=95, nz=65, nrows=65, ncols=95, pixel_v=1.5, pixel_u=1.2, shift_v=0.3, sod=345.0, sdd=517.5), "sf", 7),
+          "parallel": (scan(PARALLEL, nviews=180, nx=101, ny=105, nz=64, nrows=64, ncols=105, pixel_v=1.5, pixel_u=1.2, shift_v=0.3), "sf", 7),
+          "siddon_cone": (scan(nviews=408, nx=43, ny=37, nz=11, nrows=11, ncols=43, shift_v=0.3, sod=189.0, sdd=283.5), "siddon", 21),
+          "siddon_tilted": (perturbed_poses(scan(nviews=479, nx=12, ny=28, nz=14, nrows=14, ncols=28, shift_v=0.3), 5, shift_mm=3.0, tilt_rad=0.05), "siddon", 21)}
+
+
+@pytest.mark.parametrize("name", list(ROUNDS))
+def test_batches_that_take_the_room_several_times(oracle_mod, name):
+    """Every item the bits it has by itself (a batch that takes the views as one volume does); the first and the last against the oracle."""
+    import torch
+    from paper_2307_05801_amd import Geometry
+    cfg, model, batch = ROUNDS[name]
+    geo = Geometry(cfg, model=model)
+    print(f"[gpu] {name}: {geo.describe()}", flush=True)
+    y = uniform_sinogram(cfg, 5, batch=batch)
+    yt = torch.from_numpy(y).cuda()
+    got = geo.backproject(yt)
+    for b in range(batch):
+        assert torch.equal(got[b], geo.backproject(yt[b].contiguous())), b
+    for b in (0, batch - 1):
+        assert rel_l2(got[b].cpu().numpy(), (oracle_mod if model == "sf" else oracle_mod.siddon).backproject(cfg, y[b])) <= TOL
+    geo.close()

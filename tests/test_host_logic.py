@@ -1284,3 +1284,64 @@ def test_calls_through_a_library_that_was_loaded_without_prototypes(host):
     import sys
     res = subprocess.run([sys.executable, "-c", OWN_LIBRARY.format(root=ROOT, here=HERE)], capture_output=True, text=True, timeout=300)
     assert res.returncode == 0 and "done" in res.stdout, (res.returncode, res.stderr[-1500:])
+
+
+def back_parts(host, h, items):
+    """(parts, shape, items at a time, shape one volume takes without parts) of a back projection of `items` volumes."""
+    out = (C.c_int32 * 4)()
+    host.host_back_parts.argtypes = [C.c_void_p, C.c_int, C.POINTER(C.c_int32)]
+    host.host_back_parts(h, items, out)
+    return tuple(out)
+
+
+def test_batches_of_the_gpu_tests_take_parts_in_the_rounds_they_are_meant_to(host):
+    from tests.test_gpu_back_parts import CASES as SF_PARTS, ROUNDS, SIDDON as SIDDON_PARTS
+    runs = [(n, c, "sf", 3, 3) for n, c in SF_PARTS.items()] + [(n, c, "siddon", 3, 3) for n, c in SIDDON_PARTS.items()]
+    runs += [(n, c, m, batch, {7: 4, 21: 16}[batch]) for n, (c, m, batch) in ROUNDS.items()]
+    for name, cfg, model, batch, at_once in runs:
+        h = handle(host, cfg, B.MODELS[model])
+        one, many = back_parts(host, h, 1), back_parts(host, h, batch)
+        B.leap_geometry_destroy(h, host)
+        assert one[0] > 1 and many == one[:2] + (at_once,) + one[3:], (name, model, one, many)
+
+
+def parts_scan(kind, nx, ny, nz, nviews, nrows, ncols, pixel_v, pixel_u):
+    flat = kind == "parallel"
+    far = 0.0 if flat else max(nx, ny) * 1.0
+    cfg = CTConfig("parts", {"parallel": PARALLEL, "curved": CONE_CURVED}.get(kind, CONE), nviews=nviews, arc_deg=360.0, nrows=nrows, ncols=ncols,
+                   pixel_v=pixel_v / (1.5 if flat else 1.0), pixel_u=pixel_u / (1.5 if flat else 1.0), nx=nx, ny=ny, nz=nz, voxel_xy=1.0, voxel_z=1.0,
+                   start_deg=3.0, shift_u=0.3, shift_v=0.0 if kind == "mirror" else 0.3, sod=3.0 * far + 60.0 * (not flat), sdd=4.5 * far + 90.0 * (not flat))
+    if kind == "upright":
+        return perturbed_poses(cfg, 5, shift_mm=3.0, upright=True)
+    return perturbed_poses(cfg, 5, shift_mm=3.0, tilt_rad=0.05) if kind == "tilted" else cfg
+
+
+@pytest.mark.parametrize("case,shape,alone", [
+    (("cone", 106, 60, 26, 332, 26, 105, 1.65, 1.6), 0, 2), (("cone", 23, 69, 64, 53, 65, 67, 1.4, 1.74), 1, 2), (("curved", 31, 99, 18, 92, 24, 86, 1.47, 1.39), 1, 2),
+    (("parallel", 35, 33, 84, 149, 130, 36, 1.64, 1.7), 0, 2), (("mirror", 52, 67, 45, 55, 66, 77, 1.15, 1.6), 1, 2), (("upright", 78, 74, 40, 68, 49, 87, 1.34, 1.61), 1, 2)])
+def test_windows_of_views_shared_among_workgroups_hold_what_is_read(host, case, shape, alone):
+    """Scans whose parts take another shape than one volume's views would within a workgroup."""
+    cfg = parts_scan(*case)
+    h = handle(host, cfg)
+    plan = back_parts(host, h, 1)
+    B.leap_geometry_destroy(h, host)
+    rep, desc = window_report(host, cfg)
+    assert plan[0] > 1 and plan[1] == shape and plan[3] == alone and rep[7] == 0, (plan, rep, desc)
+
+
+@pytest.mark.parametrize("case,shape,alone", [
+    (("cone", 66, 77, 46, 54, 47, 94, 1.67, 1.52), 0, 1), (("curved", 28, 62, 29, 108, 42, 91, 1.49, 1.61), 0, 1), (("parallel", 72, 24, 14, 162, 15, 80, 0.73, 1.17), 0, 1),
+    (("upright", 44, 47, 11, 207, 11, 69, 1.35, 1.58), 0, 1), (("tilted", 21, 38, 58, 67, 54, 49, 1.04, 1.41), 0, 0), (("tilted", 37, 35, 27, 203, 76, 100, 0.74, 0.9), 2, 2)])
+def test_siddon_views_shared_among_workgroups_match_oracle_on_cpu(host, oracle_mod, case, shape, alone):
+    """The shape that the parts take, re-enacted: every window and slot holds what is read and written, and the result is the oracle's."""
+    cfg = parts_scan(*case)
+    y = uniform_sinogram(cfg, 6)[0]
+    h = handle(host, cfg, B.LEAP_MODEL_SIDDON)
+    desc, plan = B.leap_geometry_describe(h, host), back_parts(host, h, 1)
+    out, rep = np.full(cfg.vol_shape, np.nan, np.float32), (C.c_int64 * 4)()
+    run = host.host_md_backproject_tiled if case[0] == "tilted" else host.host_sd_backproject_tiled
+    bad = run(h, y.ctypes.data, out.ctypes.data, rep)
+    B.leap_geometry_destroy(h, host)
+    assert plan[0] > 1 and plan[1] == shape and plan[3] == alone and bad == 0, (plan, bad, list(rep), desc)
+    ref = oracle_mod.siddon.backproject(cfg, y)
+    assert rel_l2(out, ref) <= TOL and np.abs(out - ref).max() <= 2e-5 * np.abs(ref).max(), desc       # (the tilted re-enactments' tolerance)
