@@ -1356,13 +1356,13 @@ static int finish_handle(leap_geometry *G, leap_geometry **out)
     if (e == hipSuccess && !G->views.empty()) e = upload((void **)&G->d_views, G->views.data(), sizeof(SfView) * G->views.size());
     if (e == hipSuccess) allocate_forward_scratch(G);
     if (e == hipSuccess && G->flat) allocate_flat_scratch(G);
-    if (e == hipSuccess && G->bp_parts > 1) allocate_back_room(G);
     if (e == hipSuccess && !G->raycols.empty()) e = upload((void **)&G->d_raycols, G->raycols.data(), sizeof(SdRayCol) * G->raycols.size());
     if (e == hipSuccess && !G->geoms.empty()) e = upload((void **)&G->d_geoms, G->geoms.data(), sizeof(SfGeom) * G->geoms.size());
     if (e == hipSuccess && !G->poses.empty()) e = upload((void **)&G->d_poses, G->poses.data(), sizeof(MdPose) * G->poses.size());
     if (e == hipSuccess && !G->mfviews.empty())
         e = upload((void **)&G->d_mfviews, G->mfviews.data(), sizeof(MfView) * G->mfviews.size());
     if (e == hipSuccess && d->type == LEAP_CONE_CURVED && d->model == LEAP_MODEL_SF && G->bp_tiled) upload_curved_tables(G);
+    if (e == hipSuccess && G->bp_parts > 1) allocate_back_room(G);         // (after what may still leave the general kernel)
     if (e != hipSuccess) {
         const int rc = leap_hip_fail(e, "uploading the geometry tables");       // (may throw: the handle is freed after it)
         free_handle(G);

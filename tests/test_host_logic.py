@@ -1286,6 +1286,25 @@ def test_calls_through_a_library_that_was_loaded_without_prototypes(host):
     assert res.returncode == 0 and "done" in res.stdout, (res.returncode, res.stderr[-1500:])
 
 
+def test_no_room_for_parts_is_kept_where_the_general_kernel_runs(host):
+    """The cylinder's tables find no room on the device: the back projection has no parts and keeps no memory for them."""
+    cfg, seen = FEW_TILES.replace(geom=CONE_CURVED), set()
+    for n in range(12):
+        host.host_fail_device_allocation(C.c_long(n))
+        try:
+            h = handle(host, cfg)
+        except B.LeapError:
+            continue
+        finally:
+            host.host_fail_device_allocation(C.c_long(-1))
+        desc = B.leap_geometry_describe(h, host)
+        B.leap_geometry_destroy(h, host)
+        general = "AT=general" in desc
+        seen.add(general)
+        assert not general or scratch_bytes(desc) < 4 << 20, desc            # (the forward scratch alone)
+    assert seen == {True, False}
+
+
 def back_parts(host, h, items):
     """(parts, shape, items at a time, shape one volume takes without parts) of a back projection of `items` volumes."""
     out = (C.c_int32 * 4)()
