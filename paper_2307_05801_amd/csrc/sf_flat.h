@@ -86,12 +86,34 @@ SF_HD SfColumn sf_flat_parallel_column(const SfGeom &g, const SfView &v, int i, 
     return f;
 }
 
+// ... and how far it moves on the detector from one voxel of a slab to the next.
+SF_HD double sf_flat_step(const SfGeom &g, const SfView &v, int xmajor) { return xmajor ? g.Td * v.cd * g.kud : -g.Td * v.sd * g.kud; }
+
+// F_u of a voxel whole steps beyond the footprint `first`, `edge` the pixel's lower edge from that one's centre.
+SF_HD float sf_flat_stepped_fu(const SfColumn &first, double edge, double step, int steps) { return sf_fu_at(first, (float)fma((double)-steps, step, edge)); }
+
+// Slabs [begin, end) of a wave: n_major * wave / nwaves on, nwaves a power of two (64-bit divisions cost the smallest calls a microsecond).
+SF_HD void sf_flat_share(int n_major, int wave, int nwaves, int &begin, int &end)
+{
+    const int share = 31 - __builtin_clz(nwaves), whole = n_major >> share, rest = n_major - (whole << share);
+    begin = whole * wave + (rest * wave >> share);
+    end = begin + whole + ((rest * (wave + 1) >> share) - (rest * wave >> share));
+}
+
 // Marching axis of the wave whose first column is c0: that of its middle beam.
 SF_HD int sf_flat_xmajor(const SfGeom &g, const SfView &v, int c0)
 {
     const int mid = c0 + FLAT_RAYS / 2 < g.ncols ? c0 + FLAT_RAYS / 2 : g.ncols - 1;
     return sf_ray_lines<0>(g, v, mid, 1).xmajor;
 }
+
+// Tile and staged columns of the back projection by the number of views a wave takes at a time (SUB: 1, 2 or 4; 64 / SUB lanes each).  The
+// lanes beside the tile's middle voxel lie at most 4 sqrt(2), sqrt(20), 2 sqrt(2) voxels from it, so the columns they read lie within
+// 29, 25, 19 of its own (see FLAT_MAX_COLS).
+template <int SUB>
+struct FlatTile {
+    static constexpr int TX = SUB == 4 ? 4 : 8, TY = SUB == 1 ? 8 : 4, LANES = 64 / SUB, COLS = SUB == 4 ? 48 : 64, LOADS = COLS / LANES;
+};
 
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
 
@@ -187,11 +209,9 @@ __global__ __launch_bounds__(FLAT_MAX_WAVES * 64) void sf_project_flat(SfGeom g,
     const bool across = xmajor && !turned;
     src = (xmajor && turned ? turned : src) + (size_t)blockIdx.y * nvol * NB;
     const unsigned n_stride = across ? 1u : (unsigned)n_minor, q_stride = across ? (unsigned)g.nx : 1u;
-    // the wave's slabs: n_major * wave / nwaves on, nwaves a power of two (64-bit divisions cost the smallest calls a microsecond)
-    const int share = 31 - __builtin_clz(nwaves), whole = n_major >> share, rest = n_major - (whole << share);
-    const int n_begin = whole * wave + (rest * wave >> share), n_end = n_begin + whole + ((rest * (wave + 1) >> share) - (rest * wave >> share));
-    // PAR: how far the footprint moves on the detector from one voxel of a slab to the next
-    const double step = xmajor ? g.Td * v.cd * g.kud : -g.Td * v.sd * g.kud;
+    int n_begin, n_end;
+    sf_flat_share(n_major, wave, nwaves, n_begin, n_end);
+    const double step = sf_flat_step(g, v, xmajor);         // (PAR)
 
     float acc[NB];
 #pragma unroll
@@ -237,7 +257,7 @@ __global__ __launch_bounds__(FLAT_MAX_WAVES * 64) void sf_project_flat(SfGeom g,
             edge = ((double)c - 0.5) - first.xi;
         }
         auto weight = [&](int q) {
-            if constexpr (PAR) return sf_fu_at(first, (float)fma((double)(qf - q), step, edge));
+            if constexpr (PAR) return sf_flat_stepped_fu(first, edge, step, q - qf);
             SfFlatRec r;
             reinterpret_cast<float4 *>(&r)[0] = rec_lo[q - q_lo];
             reinterpret_cast<float4 *>(&r)[1] = rec_hi[q - q_lo];
@@ -273,14 +293,6 @@ __global__ __launch_bounds__(FLAT_MAX_WAVES * 64) void sf_project_flat(SfGeom g,
             if ((int)blockIdx.y * NB + b < items) y[b * nsino] = amp * acc[b];
     }
 }
-
-// Tile and staged columns of the back projection by the number of views a wave takes at a time (SUB: 1, 2 or 4; 64 / SUB lanes each).  The
-// lanes beside the tile's middle voxel lie at most 4 sqrt(2), sqrt(20), 2 sqrt(2) voxels from it, so the columns they read lie within
-// 29, 25, 19 of its own (see FLAT_MAX_COLS).
-template <int SUB>
-struct FlatTile {
-    static constexpr int TX = SUB == 4 ? 4 : 8, TY = SUB == 1 ? 8 : 4, LANES = 64 / SUB, COLS = SUB == 4 ? 48 : 64, LOADS = COLS / LANES;
-};
 
 // grid.x = tiles of TX x TY voxels; grid.y: groups of NB items.  Block: waves that share the views; wave w takes runs of `shares` adjacent
 // views, shares w on, a run of every wave apart, and sums the first of every run, then the second, ...  SUB > 1 (16 waves, shares a multiple of SUB):

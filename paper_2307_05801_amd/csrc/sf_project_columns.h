@@ -330,6 +330,15 @@ SF_HD bool sf_candidate_record(const SfGeom &g, const SfView &v, int i, int j, i
 SF_HD double sf_bundle_middle(int c0, int cw) { return (double)c0 + 0.5 * (cw - 1); }
 SF_HD double sf_bundle_reach(int cw, double max_cols_per_voxel) { return 0.5 * cw + max_cols_per_voxel + 0.5; }
 
+// Waves of a workgroup that share a bundle (the rule stands at forward_parts) take consecutive runs of the slab's blocks of 64 / nq layers: those of this part.
+SF_HD void fp_part_of(const SfSlab &slab, int block, int part, int parts, int &n_first, int &n_end)
+{
+    const int blocks = (slab.n1 - slab.n0 + block - 1) / block;
+    n_first = slab.n0 + blocks * part / parts * block;
+    n_end = slab.n0 + blocks * (part + 1) / parts * block;
+    n_end = n_end < slab.n1 ? n_end : slab.n1;
+}
+
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
 
 // vol [nz][ny][nx]  ->  the slab's scratch copy: columns (i, j), i0 <= i < i0 + ni, j0 <= j < j0 + nj, at
@@ -406,15 +415,6 @@ __device__ __forceinline__ void fp_store_four(float *__restrict__ dst, float a, 
         q.a += old.a; q.b += old.b; q.c += old.c; q.d += old.d;
     }
     *reinterpret_cast<Quad *>(dst) = q;
-}
-
-// Waves of a workgroup that share a bundle (the rule stands at forward_parts) take consecutive runs of the slab's blocks of 64 / nq layers: those of this part.
-SF_HD void fp_part_of(const SfSlab &slab, int block, int part, int parts, int &n_first, int &n_end)
-{
-    const int blocks = (slab.n1 - slab.n0 + block - 1) / block;
-    n_first = slab.n0 + blocks * part / parts * block;
-    n_end = slab.n0 + blocks * (part + 1) / parts * block;
-    n_end = n_end < slab.n1 ? n_end : slab.n1;
 }
 
 // Adds the parts' N sums per lane in the order of the parts; the total is valid in part 0.  red: 8 floats per lane and wave, free to use

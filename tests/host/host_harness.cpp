@@ -431,6 +431,27 @@ static void host_pairs_of_scan(const SfGeom &g, const float *col, int nzp, doubl
     }
 }
 
+// The layers of a bundle as the waves that share it take them: layer(n, sums) for every layer of every part, the parts' sums added in order.  Returns
+// how many layers were not taken once.
+template <class Layer>
+static long host_layers(const leap_geometry *G, const SfSlab &slab, std::vector<float> &acc, Layer layer)
+{
+    int nq_log2 = 2;
+    while ((1 << nq_log2) < G->fp_nq) ++nq_log2;
+    std::vector<int> taken(slab.n1 - slab.n0, 0);
+    for (int part = 0; part < G->fp_parts; ++part) {
+        std::vector<float> sums(acc.size(), 0.f);
+        int n_first = slab.n0, n_end = slab.n1;
+        if (G->fp_parts > 1) fp_part_of(slab, 64 >> nq_log2, part, G->fp_parts, n_first, n_end);
+        for (int n = n_first; n < n_end; ++n) {
+            if (n >= slab.n0 && n < slab.n1) ++taken[n - slab.n0];
+            layer(n, sums);
+        }
+        for (size_t e = 0; e < acc.size(); ++e) acc[e] = part ? acc[e] + sums[e] : sums[e];
+    }
+    return (long)taken.size() - (long)std::count(taken.begin(), taken.end(), 1);
+}
+
 template <int CW>
 static long host_project_bundles(const leap_geometry *G, const std::vector<float> (&volz)[2], int nzp, float *sino)
 {
@@ -448,8 +469,11 @@ static long host_project_bundles(const leap_geometry *G, const std::vector<float
             const SfRayLines L = sf_ray_lines(g, v, c0, CW, xmajor);
             const int n_major = xmajor ? g.nx : g.ny, n_minor = xmajor ? g.ny : g.nx;
             const SfSlab slab = {0, n_major, xmajor, 1, n_major};
-            std::vector<float> acc((size_t)g.nrows * CW, 0.f);
-            for (int n = 0; n < n_major; ++n) {
+            std::vector<float> total((size_t)g.nrows * CW, 0.f);
+            const bool curved = g.type == SF_CONE_CURVED;
+            SfNearRay ray = {};
+            if (curved) ray = sf_near_ray(g, sf_bundle_middle(c0, CW));
+            uncovered += host_layers(G, slab, total, [&](int n, std::vector<float> &acc) {
                 int qf, ql;
                 sf_candidates(L, n, qf, ql);
                 if (ql - qf + 1 > NQ) ++uncovered;
@@ -459,7 +483,7 @@ static long host_project_bundles(const leap_geometry *G, const std::vector<float
                     const int i = xmajor ? n : q, j = xmajor ? q : n;
                     float fa[CW];
                     double mu;
-                    if (!sf_candidate_record<CW, -1>(g, v, i, j, c0, true, fa, mu)) continue;
+                    if (!sf_footprint_record<CW>(g, curved ? sf_column_curved_near(g, v, i, j, ray) : sf_column(g, v, i, j), c0, true, fa, mu)) continue;
                     const float *col = &volz[xmajor][(size_t)sf_slab_column(slab, g.nx, i, j) * nzp];
                     switch (fp_height_class(G->fp_nkp)) {
                     case 0: host_pairs_of_scan<CW, 0>(g, col, nzp, mu, zkp, fa, acc); break;
@@ -469,11 +493,11 @@ static long host_project_bundles(const leap_geometry *G, const std::vector<float
                     default: host_pairs_of_scan<CW, 4>(g, col, nzp, mu, zkp, fa, acc); break;
                     }
                 }
-            }
+            });
             for (int cw = 0; cw < CW && c0 + cw < g.ncols; ++cw) {
                 const SfAmpCol ac = sf_amp_col(g, v, c0 + cw);
                 for (int r = 0; r < g.nrows; ++r)
-                    sino[((size_t)a * g.nrows + r) * g.ncols + c0 + cw] = sf_amp(g, v, ac, r) * acc[(size_t)r * CW + cw];
+                    sino[((size_t)a * g.nrows + r) * g.ncols + c0 + cw] = sf_amp(g, v, ac, r) * total[(size_t)r * CW + cw];
             }
         }
     return uncovered;
@@ -503,7 +527,6 @@ extern "C" long host_project_columns(const leap_geometry *G, const float *vol, f
     }
 }
 
-// How many of a launch's items go two to a wave.
 // Tiles that the back projection's order of workgroups leaves out or names twice, in one layer of chunks.
 extern "C" long host_check_tile_order(unsigned tiles_x, unsigned tiles_y, unsigned y)
 {
@@ -517,6 +540,7 @@ extern "C" long host_check_tile_order(unsigned tiles_x, unsigned tiles_y, unsign
     return wrong;
 }
 
+// How many of a launch's items go two to a wave.
 extern "C" int host_forward_paired(const leap_geometry *G, int items) { return leap_forward_paired(G, items); }
 
 // Back projection of a launch's items: the shape whose groups of threads share the views (-1: none), pairs of items per workgroup.
@@ -1030,8 +1054,9 @@ static long host_rows(const leap_geometry *G, const std::vector<float> &rows, fl
             const int c0 = b * CW, xmajor = G->major[(size_t)a * nbundles + b];
             const SfRayLines L = sf_ray_lines<0>(g, v, c0, CW, xmajor);
             const int n_major = xmajor ? g.nx : g.ny, n_minor = xmajor ? g.ny : g.nx;
-            std::vector<float> acc((size_t)g.nrows * CW, 0.f);
-            for (int n = 0; n < n_major; ++n) {
+            const SfSlab slab = {0, n_major, xmajor, 1, n_major};
+            std::vector<float> total((size_t)g.nrows * CW, 0.f);
+            uncovered += host_layers(G, slab, total, [&](int n, std::vector<float> &acc) {
                 int qf, ql;
                 sf_candidates(L, n, qf, ql);
                 if (ql - qf + 1 > G->fp_nq) ++uncovered;
@@ -1045,9 +1070,9 @@ static long host_rows(const leap_geometry *G, const std::vector<float> &rows, fl
                         for (int cw = 0; cw < CW; ++cw)
                             if (fa[cw] != 0.0f) acc[(size_t)r * CW + cw] = fmaf(fa[cw], x[r], acc[(size_t)r * CW + cw]);
                 }
-            }
+            });
             for (int cw = 0; cw < CW && c0 + cw < g.ncols; ++cw)
-                for (int r = 0; r < g.nrows; ++r) sino[((size_t)a * g.nrows + r) * g.ncols + c0 + cw] = v.par_amp * acc[(size_t)r * CW + cw];
+                for (int r = 0; r < g.nrows; ++r) sino[((size_t)a * g.nrows + r) * g.ncols + c0 + cw] = v.par_amp * total[(size_t)r * CW + cw];
         }
     return uncovered;
 }
@@ -1069,9 +1094,6 @@ extern "C" long host_project_rows(const leap_geometry *G, const float *vol, floa
     return G->fp_cw == 2 ? host_rows<2>(G, rows, sino) : host_rows<4>(G, rows, sino);
 }
 
-// ---- flat scans: a wave's records per slab, a thread's columns in the staged window ---------------------------------------------
-// report[0]: candidate voxels that the wave's outermost columns do not bound or the records do not hold; report[1]: columns read
-// outside the 64 staged ones.  Returns -1 when the handle does not use these kernels.
 // Back projection of a launch's items with the views shared among workgroups: out = {parts, shape, items at a time, shape one volume takes without parts}.
 extern "C" void host_back_parts(const leap_geometry *G, int items, int32_t *out)
 {
@@ -1079,13 +1101,42 @@ extern "C" void host_back_parts(const leap_geometry *G, int items, int32_t *out)
     const LeapBackParts p = siddon ? leap_siddon_parts(G, items) : leap_back_parts(G, items);
     out[0] = p.parts; out[1] = p.shape; out[2] = p.items; out[3] = G->bp_split_shape;
 }
+
+// ---- flat scans: a wave's records per slab (parallel beams: the footprints stepped along it), a thread's columns in the staged window -----------
+// report[0]: candidate voxels that the wave's outermost columns do not bound or the records do not hold; report[1]: columns read
+// outside the staged ones, for the tiles of one, two and four views at a time.  Returns -1 when the handle does not use these kernels.
 extern "C" int host_flat_tiles(int ncols, int nviews) { return flat_tiles(ncols, nviews); }
+
+// Slabs that the waves of a workgroup do not take once, in order.
+extern "C" long host_check_flat_shares(int n_major, int nwaves)
+{
+    long wrong = 0;
+    int at = 0;
+    for (int w = 0; w < nwaves; ++w) {
+        int begin, end;
+        sf_flat_share(n_major, w, nwaves, begin, end);
+        wrong += begin != at || end < begin;
+        at = end;
+    }
+    return wrong + (at != n_major);
+}
+
+template <int SUB>
+static bool host_flat_outside(const SfGeom &g, const SfView &v, int i, int j, int cf)
+{
+    typedef FlatTile<SUB> Tile;
+    const int ic = i / Tile::TX * Tile::TX + Tile::TX / 2, jc = j / Tile::TY * Tile::TY + Tile::TY / 2;      // the tile's middle voxel
+    const int first = (int)floor(sf_column<0>(g, v, std::min(ic, g.nx - 1), std::min(jc, g.ny - 1)).xi) - Tile::COLS / 2;
+    return cf < first || cf + FLAT_NC - 1 >= first + Tile::COLS;
+}
+
 extern "C" long host_flat(const leap_geometry *G, const float *vol, float *sino, const float *sino_in, float *vol_out, int64_t *report)
 {
     const SfGeom &g = G->g;
     if (!G->flat) return -1;
     int64_t beyond = 0, outside = 0;
     const int tiles = (g.ncols + FLAT_RAYS - 1) / FLAT_RAYS;
+    const bool parallel = g.type == SF_PARALLEL;
 #pragma omp parallel for collapse(2) reduction(+ : beyond)
     for (int a = 0; a < g.nviews; ++a)
         for (int t = 0; t < tiles; ++t) {
@@ -1102,9 +1153,17 @@ extern "C" long host_flat(const leap_geometry *G, const float *vol, float *sino,
                     sf_candidates(L1, n, f1, l1);
                     const int q_lo = std::max(std::min(f0, f1), 0), q_hi = std::min(std::max(l0, l1), n_minor - 1);
                     if (q_hi - q_lo + 1 > G->flat_span) ++beyond;
-                    for (int q = std::max(qf, 0); q <= std::min(ql, n_minor - 1); ++q) {
+                    qf = std::max(qf, q_lo);
+                    SfColumn stepped = {};
+                    double edge = 0.0;
+                    if (parallel) {
+                        stepped = sf_flat_parallel_column(g, v, xmajor ? n : qf, xmajor ? qf : n);
+                        edge = ((double)c - 0.5) - stepped.xi;
+                    }
+                    for (int q = qf; q <= std::min(ql, n_minor - 1); ++q) {
                         const int i = xmajor ? n : q, j = xmajor ? q : n;
-                        const float fu = sf_flat_fu(sf_flat_record(sf_column<0>(g, v, i, j)), c);
+                        const float fu = parallel ? sf_flat_stepped_fu(stepped, edge, sf_flat_step(g, v, xmajor), q - qf)
+                                                  : sf_flat_fu(sf_flat_record(sf_column<0>(g, v, i, j)), c);
                         if (!(fu > 0.0f)) continue;
                         if (q < q_lo || q > q_hi) ++beyond;
                         acc = fmaf(fu, vol[(size_t)j * g.nx + i], acc);
@@ -1116,16 +1175,13 @@ extern "C" long host_flat(const leap_geometry *G, const float *vol, float *sino,
 #pragma omp parallel for collapse(2) reduction(+ : outside)
     for (int j = 0; j < g.ny; ++j)
         for (int i = 0; i < g.nx; ++i) {
-            const int tx = i / FLAT_T, ty = j / FLAT_T;
             float acc = 0.f;
             for (int a = 0; a < g.nviews; ++a) {
                 const SfView &v = G->views[a];
-                const SfColumn mid = sf_column<0>(g, v, std::min(tx * FLAT_T + FLAT_T / 2, g.nx - 1), std::min(ty * FLAT_T + FLAT_T / 2, g.ny - 1));
-                const int first = (int)floor(mid.xi) - 32;
                 const SfColumn f = sf_column<0>(g, v, i, j);
                 int cf, cl;
                 sf_col_range(f, cf, cl);
-                if (cf < first || cf + FLAT_NC - 1 >= first + 64 || cl - cf >= FLAT_NC) ++outside;
+                if (host_flat_outside<1>(g, v, i, j, cf) || host_flat_outside<2>(g, v, i, j, cf) || host_flat_outside<4>(g, v, i, j, cf) || cl - cf >= FLAT_NC) ++outside;
                 for (int c = std::max(cf, 0); c <= std::min(cl, g.ncols - 1); ++c)
                     acc = fmaf(sf_fu(f, c), sino_in[(size_t)a * g.ncols + c] * (sf_amp(g, v, sf_amp_col<0>(g, v, c), 0) * G->flat_fv), acc);
             }

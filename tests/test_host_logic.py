@@ -1004,6 +1004,11 @@ def test_flat_kernels_match_oracle_on_cpu(host, oracle_mod, geom, nx, ny, ncols,
         assert np.linalg.norm(got - want) <= 2e-6 * np.linalg.norm(want)
 
 
+def test_waves_of_a_flat_workgroup_take_every_slab_once(host):
+    for nwaves in (1, 2, 4, 8, 16):
+        assert not any(host.host_check_flat_shares(n, nwaves) for n in list(range(1, 300)) + [16383, 65536, 268435455])
+
+
 @pytest.mark.parametrize("nx,ny,nz,wide", [(157, 167, 140, False), (176, 176, 160, False), (192, 192, 160, True), (211, 187, 149, True),
                                            (192, 192, 133, False)])
 def test_wide_windows_need_enough_workgroups(host, nx, ny, nz, wide):
