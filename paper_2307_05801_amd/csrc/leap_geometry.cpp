@@ -612,6 +612,9 @@ static void block_order_options(leap_geometry *G)
 // and more 0.83 to 0.92; cylinder 1000 and more 0.65 to 0.95.  Batches of three, by workgroups of one volume: one group 20 to 720 1.98 to
 // 1.38, 900 to 1400 0.92 to 1.13, 1600 and more 0.88 to 1.00; several groups 20 to 2800 1.99 to 0.94, 4000 and more 0.94 to 1.00.  An item's
 // bits are the same either way.
+// Those are of a wave per bundle.  Where four waves share one (forward_parts) a launch has four times the waves, and two volumes would pay before
+// these lines: by workgroups as they are counted here, one group of rows, even batches up to 100 0.84 to 1.07, 100 to 200 0.67 to 1.02, 200 to 700 0.64
+// to 0.87, above 0.62 to 0.82; odd ones 1.28 to 1.64, 1.11 to 1.36, 200 to 400 0.85 to 1.20, 400 to 700 0.89 to 1.05, above 0.77 to 0.99.
 int leap_forward_paired(const leap_geometry *G, int items)
 {
     if (!G->fp_pair_rg || items < 2) return 0;

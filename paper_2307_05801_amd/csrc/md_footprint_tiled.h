@@ -206,6 +206,7 @@ __device__ __forceinline__ MfWindow mf_wave_window(const SfGeom &g, const MfView
     return w;
 }
 
+// (Eight voxels per thread spill four registers at four waves per SIMD.)
 template <int ZC, int VS>
 __global__ __launch_bounds__(256 * VS, VS == 1 ? 4 : 1) void mf_backproject_tiled(SfGeom g, const MfView *__restrict__ views, const float *__restrict__ sino,
                                                                      float *__restrict__ vol, int tiles_x)

@@ -323,6 +323,8 @@ static __global__ __launch_bounds__(256) void sf_sum_parts(const float *__restri
 // NS: volumes per workgroup.  VS: groups of 256 threads that share a tile's views, group q taking views q, q + VS, ...: a step from
 // one view to the next takes a microsecond and a half and more however few voxels a thread has (the window's loads, two barriers'
 // worth of waiting), so a volume too small to fill the chip is as slow as its views are many.  The groups' sums are added in order.
+// Registers spilled at the bounds below (waves of 64 or 128 registers): four to six by the cylinder's two volumes of 32 voxels in parts, one to three by
+// single volumes of 16 voxels and voxels three rows tall.
 template <int NC, int NV, int BP_ZC, int BP_PW, int BP_PH, int GT, int NS, int VS = 1, bool PARTS = false>
 __global__ __launch_bounds__(256 * VS, VS > 1 ? (NS == 1 && BP_ZC <= 16 && GT != 1 ? 8 : 4) : (GT == 1 && NV > 2 && BP_ZC * NS > 32) ? 3 : (NS == 2 && BP_PW > 42 && BP_ZC > 8 ? 3 : 4)) void sf_backproject_tiled(SfGeom g, const SfView *__restrict__ views,
                                                             const float *__restrict__ sino, float *__restrict__ vol,
