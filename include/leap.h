@@ -38,8 +38,10 @@
  *     constants of each ray's line; a LEAP_CONE_CURVED footprint handle 24 bytes per (16x16
  *     voxel-column tile, view).  leap_project calls on one handle share its scratch, and
  *     leap_backproject calls that share the views among workgroups its room for them; the library
- *     orders the calls that do on the device (each first waits for the previous one's kernels), so any
- *     stream and thread may be used, but such calls do not overlap; distinct handles are independent.
+ *     orders the calls that do on the device (each first waits for the kernels of the one before it),
+ *     so any stream and thread may be used.  The room, and the scratch of detectors of fewer than 32 rows,
+ *     are kept in up to four slots where that much memory holds them: calls of one or a few items on as
+ *     many streams overlap there, others do not.  Distinct handles are independent.
  *     A captured leap_project call of 32 detector rows or more uses the scratch when its graph is
  *     launched, which the library does not see: order such launches with the handle's other calls.
  *   - Results: the same call on the same handle gives the same bits every time, whatever else runs.

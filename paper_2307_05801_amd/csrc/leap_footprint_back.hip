@@ -45,15 +45,18 @@ static bool launch_bp_shape(const leap_geometry *G, const float *d_sino, float *
     }
 }
 
-// As many items at a time as the handle's room for the parts' volumes holds.
+// As many items at a time as the handle's room for the parts' volumes holds; in one slot of it where that holds them all.
 static int launch_in_parts(const leap_geometry *G, const LeapBackParts &plan, const float *d_sino, float *d_vol, int items, hipStream_t stream)
 {
     const size_t nvol = (size_t)G->g.nx * G->g.ny * G->g.nz, nsino = (size_t)G->g.nviews * G->g.nrows * G->g.ncols;
-    LeapTurn turn(G->back, stream);
+    const bool one = items <= std::min(plan.items, G->back_slot_items);
+    const int slot = one ? G->back.pick(stream) : 0;
+    LeapTurn turn(&G->back.slot[slot], one ? 1 : G->back.slots, stream);
     LEAP_HIP_CHECK(turn.begin());
+    float *const room = G->d_back + (size_t)slot * G->back_slot_items * nvol * plan.parts;
     for (int b = 0; b < items;) {
         const int n = std::min(items - b, plan.items);
-        if (!leap_launch_backproject_split(G, plan.shape, plan.parts, d_sino + b * nsino, d_vol + b * nvol, n, stream)) {
+        if (!leap_launch_backproject_split(G, plan.shape, plan.parts, d_sino + b * nsino, room, d_vol + b * nvol, n, stream)) {
             leap_set_error("internal: no back-projection instance that shares the views for this footprint");
             return LEAP_UNSUPPORTED;
         }
@@ -72,7 +75,7 @@ int leap_launch_footprint_back(const leap_geometry *G, const float *d_sino, floa
     if (plan.parts > 1 && !leap_capturing(stream)) return launch_in_parts(G, plan, d_sino, d_vol, items, stream);
     const int split = leap_back_split_shape(G, items);
     if (split >= 0) {
-        if (!leap_launch_backproject_split(G, split, 1, d_sino, d_vol, items, stream)) {
+        if (!leap_launch_backproject_split(G, split, 1, d_sino, nullptr, d_vol, items, stream)) {
             leap_set_error("internal: no back-projection instance that shares the views for this footprint");
             return LEAP_UNSUPPORTED;
         }

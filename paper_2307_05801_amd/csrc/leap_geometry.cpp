@@ -1228,7 +1228,11 @@ static void allocate_forward_scratch(leap_geometry *G)
         e = hipMalloc((void **)&G->d_major, G->major.size());
         if (e == hipSuccess) e = hipMemcpy(G->d_major, G->major.data(), G->major.size(), hipMemcpyHostToDevice);
     }
-    if (e == hipSuccess) e = G->scratch.create();
+    // Short detectors, which share no scratch under capture: a slot per copy of the whole volume.
+    const double n_side = std::max(d->nx, d->ny), copy = (n_side * n_side + 1.0) * G->nzp;
+    const int slots = d->nrows < FP_FREE_ROWS ? std::max(1, (int)std::min((double)LeapRoom::MOST_SLOTS, std::floor((double)(G->scratch_bytes / sizeof(float)) / copy))) : 1;
+    G->scratch_slot_floats = G->scratch_bytes / sizeof(float) / G->nzp / slots * G->nzp;       // (whole columns: the pads lie alike)
+    if (e == hipSuccess) e = G->scratch.create(slots);
     if (e != hipSuccess) {
         if (G->d_volz) (void)hipFree(G->d_volz);
         if (G->d_major) (void)hipFree(G->d_major);
@@ -1257,7 +1261,7 @@ static void allocate_flat_scratch(leap_geometry *G)
         e = hipMalloc((void **)&G->d_volz, G->scratch_bytes);
         if (e != hipSuccess) (void)hipGetLastError();
     }
-    if (e == hipSuccess) e = G->scratch.create();
+    if (e == hipSuccess) e = G->scratch.create(1);
     if (e == hipSuccess) return;
     if (G->d_volz) (void)hipFree(G->d_volz);
     G->d_volz = nullptr;
@@ -1266,14 +1270,16 @@ static void allocate_flat_scratch(leap_geometry *G)
     (void)hipGetLastError();
 }
 
-// Room for the volumes of the parts in which the footprint back projection's views are shared among workgroups: for as many items at once as
-// fit 64 MiB.  Without it the views stay with one workgroup.
+// Room for the volumes of the parts in which a back projection's views are shared among workgroups: for as many items at once as
+// fit 64 MiB, in slots for calls on several streams.  Without it the views stay with one workgroup.
 static void allocate_back_room(leap_geometry *G)
 {
     const size_t one = (size_t)G->g.nx * G->g.ny * G->g.nz * G->bp_parts;
-    G->back_floats = one * std::max<size_t>(1, std::min<size_t>(16, (size_t)BACK_MOST_FLOATS / one));
+    const int items = (int)std::max<size_t>(1, std::min<size_t>(16, (size_t)BACK_MOST_FLOATS / one)), slots = std::min(items, LeapRoom::MOST_SLOTS);
+    G->back_floats = one * items;
+    G->back_slot_items = items / slots;
     hipError_t e = hipMalloc((void **)&G->d_back, G->back_floats * sizeof(float));
-    if (e == hipSuccess) e = G->back.create();
+    if (e == hipSuccess) e = G->back.create(slots);
     if (e == hipSuccess) return;
     if (G->d_back) (void)hipFree(G->d_back);
     G->d_back = nullptr;

@@ -47,14 +47,22 @@ inline bool leap_capturing(hipStream_t stream)
     return true;
 }
 
-// One call's turn at a handle's shared memory, from begin() to end(); a call that returns early, some of its kernels perhaps launched, ends it too.
+// One call's turn at a handle's shared memory, or at n of them at once, from begin() to end(); a call that returns early, some of its kernels perhaps
+// launched, ends it too.
 class LeapTurn {
 public:
-    LeapTurn(LeapShared &memory, hipStream_t s) : shared(memory), lock(memory.mutex), stream(s) {}
+    LeapTurn(LeapShared &memory, hipStream_t s) : LeapTurn(&memory, 1, s) {}
+    LeapTurn(LeapShared *memory, int n, hipStream_t s) : shared(memory), count(n), stream(s)
+    {
+        for (int i = 0; i < count; ++i) shared[i].mutex.lock();
+    }
     ~LeapTurn()
     {
         if (begun) (void)record();
+        for (int i = 0; i < count; ++i) shared[i].mutex.unlock();
     }
+    LeapTurn(const LeapTurn &) = delete;
+    LeapTurn &operator=(const LeapTurn &) = delete;
     hipError_t begin()
     {
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -62,8 +70,11 @@ public:
         hipError_t e = hipSuccess;
         capturing = status == hipStreamCaptureStatusActive;
         if (capturing) e = hipStreamGetCaptureInfo(stream, &status, &capture);
-        if (e == hipSuccess && capturing && shared.captured_used && shared.capture == capture) e = hipStreamWaitEvent(stream, shared.captured, 0);
-        if (e == hipSuccess && !capturing && shared.used) e = hipStreamWaitEvent(stream, shared.done, 0);
+        for (int i = 0; i < count && e == hipSuccess; ++i) {
+            const LeapShared &s = shared[i];
+            if (capturing && s.captured_used && s.capture == capture) e = hipStreamWaitEvent(stream, s.captured, 0);
+            if (!capturing && s.used) e = hipStreamWaitEvent(stream, s.done, 0);
+        }
         begun = e == hipSuccess;
         return e;
     }
@@ -76,20 +87,61 @@ public:
 private:
     hipError_t record()
     {
-        const hipError_t e = hipEventRecord(capturing ? shared.captured : shared.done, stream);
-        if (capturing) {
-            shared.captured_used = e == hipSuccess;
-            shared.capture = capture;
-        } else {
-            shared.used = shared.used || e == hipSuccess;
+        hipError_t failed = hipSuccess;
+        for (int i = 0; i < count; ++i) {
+            LeapShared &s = shared[i];
+            const hipError_t e = hipEventRecord(capturing ? s.captured : s.done, stream);
+            if (capturing) {
+                s.captured_used = e == hipSuccess;
+                s.capture = capture;
+            } else {
+                s.used = s.used || e == hipSuccess;
+            }
+            if (e != hipSuccess) failed = e;
         }
-        return e;
+        return failed;
     }
-    LeapShared &shared;
-    std::lock_guard<std::mutex> lock;
+    LeapShared *shared;
+    int count;
     hipStream_t stream;
     bool capturing = false, begun = false;
     unsigned long long capture = 0;
+};
+
+// Shared memory in up to four equal slots, a turn each for the calls that one holds, so that they run beside each other on as many streams; a call that needs
+// more takes all of them.  Four, as many as the hardware queues that HIP spreads streams over.  us per call on 1 / 2 / 4 streams, kernels that share nothing; one
+// slot; four: footprint A^T 57^2 x 37, 310 views 316 / 159 / 81; 72 / 77 / 75; 72 / 60 / 48; 81^2 x 67, 53 views 59 / 38 / 36; 52 / 58 / 59; 52 / 33 / 30; 128^2 x 20, 60
+// views 60 / 32 / 28; 35 / 40 / 40; 34 / 25 / 21; Siddon A, 20 rows, 64^2 x 20, 30 views 63 / 35 / 23; 34 / 41 / 42; 34 / 20 / 17.
+struct LeapRoom {
+    static constexpr int MOST_SLOTS = 4;
+    LeapShared slot[MOST_SLOTS];
+    int slots = 1;
+
+    hipError_t create(int n)
+    {
+        slots = n;
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < slots && e == hipSuccess; ++i) e = slot[i].create();
+        return e;
+    }
+    // A stream's calls stay with the slot it took first, where their order is the stream's own, until more streams have come than there are slots.
+    int pick(hipStream_t stream)
+    {
+        std::lock_guard<std::mutex> lock(picking);
+        for (int i = 0; i < slots; ++i)
+            if (taken[i] && last[i] == stream && stream != hipStreamPerThread) return i;
+        const int i = next;
+        next = (next + 1) % slots;
+        taken[i] = true;
+        last[i] = stream;
+        return i;
+    }
+
+private:
+    std::mutex picking;
+    bool taken[MOST_SLOTS] = {};
+    hipStream_t last[MOST_SLOTS] = {};
+    int next = 0;
 };
 
 struct leap_geometry {
@@ -123,7 +175,8 @@ struct leap_geometry {
     unsigned bp_parts_fits = 0;
     float *d_back = nullptr;
     size_t back_floats = 0;
-    mutable LeapShared back;
+    int back_slot_items = 0;            // items whose parts a slot of the room holds
+    mutable LeapRoom back;
     bool bp_split_forced = false;       // (debugging: bp_split_shape, whatever the launch)
     // column-wise forward projection (footprint and Siddon models): the volume goes through a z-fastest scratch copy
     // slab by slab (sf_project_columns.h)
@@ -149,7 +202,8 @@ struct leap_geometry {
     std::vector<unsigned char> major;   // footprints: [view][bundle of fp_cw columns] 1 if the bundle advances fastest along x
     unsigned char *d_major = nullptr;
     std::string note;                   // what went differently from the plan at creation (shown by leap_geometry_describe)
-    mutable LeapShared scratch;         // the turns of its calls at d_volz
+    mutable LeapRoom scratch;           // the turns of its calls at d_volz
+    size_t scratch_slot_floats = 0;     // ... of which each of its slots has so many (where it has more than one)
     // Siddon model: per-(view, detector column) ray constants, host copy and device copy
     std::vector<SdRayCol> raycols;
     SdRayCol *d_raycols = nullptr;
@@ -231,7 +285,7 @@ struct SfSlab;
 bool leap_launch_footprint_slab(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward.hip
 bool leap_launch_footprint_slab_parts(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward_parts.hip
 int leap_launch_footprint_back(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                         // leap_footprint_back.hip
-bool leap_launch_backproject_split(const leap_geometry *geom, int shape, int parts, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_footprint_back_split.hip
+bool leap_launch_backproject_split(const leap_geometry *geom, int shape, int parts, const float *d_sino, float *room, float *d_vol, int items, hipStream_t stream);          // leap_footprint_back_split.hip
 bool leap_launch_siddon_back_split(const leap_geometry *geom, int shape, int parts, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_siddon_back_split.hip
 bool leap_launch_backproject_pairs(const leap_geometry *geom, const float *d_sino, float *d_vol, int blocks, hipStream_t stream);                     // leap_footprint_back_pairs.hip
 int leap_launch_backproject_batch(const leap_geometry *geom, const float *d_sino, float *d_vol, int batch, hipStream_t stream);

@@ -314,12 +314,12 @@ static void launch_md_split(const leap_geometry *G, int parts, const float *d_si
     constexpr SfBpShape S = MD_BP_SPLIT_SHAPES[SH];
     const SfGeom &g = G->g;
     const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
-    auto go = [&](auto kernel, float *to) {
+    auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)(items * parts)), dim3(256 * MD_BP_SPLIT[SH]), 0, stream, g,
-                           (const MdBpView *)G->d_mdbp, d_sino, to, (int)tiles_x, parts);
+                           (const MdBpView *)G->d_mdbp, d_sino, d_vol, (int)tiles_x, parts);
     };
-    if (parts > 1) go(md_backproject_tiled<S.zc, S.pw, S.ph, MD_BP_SPLIT[SH], true>, G->d_back);
-    else go(md_backproject_tiled<S.zc, S.pw, S.ph, MD_BP_SPLIT[SH], false>, d_vol);
+    if (parts > 1) go(md_backproject_tiled<S.zc, S.pw, S.ph, MD_BP_SPLIT[SH], true>);
+    else go(md_backproject_tiled<S.zc, S.pw, S.ph, MD_BP_SPLIT[SH], false>);
 }
 
 static void launch_md_split_shape(const leap_geometry *G, int shape, int parts, const float *d_sino, float *d_vol, hipStream_t stream, int items)
@@ -335,18 +335,21 @@ static int launch_sd_bp_parts(const leap_geometry *G, const LeapBackParts &plan,
 {
     const unsigned nvol = (unsigned)G->g.nx * (unsigned)G->g.ny * (unsigned)G->g.nz;
     const size_t nsino = (size_t)G->g.nviews * G->g.nrows * G->g.ncols;
-    LeapTurn turn(G->back, stream);
+    const bool one = items <= plan.items && items <= G->back_slot_items;
+    const int slot = one ? G->back.pick(stream) : 0;
+    LeapTurn turn(&G->back.slot[slot], one ? 1 : G->back.slots, stream);
     LEAP_HIP_CHECK(turn.begin());
+    float *const room = G->d_back + (size_t)slot * G->back_slot_items * nvol * plan.parts;
     for (int b = 0; b < items; b += plan.items) {
         const int n = items - b < plan.items ? items - b : plan.items;
         bool ok = true;
-        if (!G->d_mdbp) ok = leap_launch_siddon_back_split(G, plan.shape, plan.parts, d_sino + b * nsino, nullptr, n, stream);
-        else launch_md_split_shape(G, plan.shape, plan.parts, d_sino + b * nsino, nullptr, stream, n);
+        if (!G->d_mdbp) ok = leap_launch_siddon_back_split(G, plan.shape, plan.parts, d_sino + b * nsino, room, n, stream);
+        else launch_md_split_shape(G, plan.shape, plan.parts, d_sino + b * nsino, room, stream, n);
         if (!ok) {
             leap_set_error("internal: no Siddon back-projection instance that shares the views");
             return LEAP_UNSUPPORTED;
         }
-        hipLaunchKernelGGL(sf_sum_parts, dim3(cdiv(nvol, 256), (unsigned)n), dim3(256), 0, stream, G->d_back, d_vol + (size_t)b * nvol, nvol, plan.parts, 1);
+        hipLaunchKernelGGL(sf_sum_parts, dim3(cdiv(nvol, 256), (unsigned)n), dim3(256), 0, stream, room, d_vol + (size_t)b * nvol, nvol, plan.parts, 1);
         LEAP_HIP_CHECK(hipGetLastError());
     }
     LEAP_HIP_CHECK(turn.end());
@@ -543,7 +546,7 @@ static int project_flat(const leap_geometry *G, const float *d_vol, float *d_sin
         LEAP_HIP_CHECK(hipGetLastError());
         return LEAP_OK;
     }
-    LeapTurn turn(G->scratch, stream);
+    LeapTurn turn(G->scratch.slot[0], stream);
     LEAP_HIP_CHECK(turn.begin());
     const int room = (int)(G->scratch_bytes / (2 * nvol * sizeof(float)));      // whole slices the scratch holds, twice each
     for (int b = 0; b < batch;) {
@@ -708,15 +711,17 @@ int leap_launch_project_batch(const leap_geometry *G, const float *d_vol, float 
     bool direct = !footprint_fast && !siddon_fast;
     if (!direct && g.nrows < FP_FREE_ROWS) direct = leap_capturing(stream);
     if (!direct) {
-        LeapTurn turn(G->scratch, stream);
-        LEAP_HIP_CHECK(turn.begin());
         FwdScratch S;
-        S.volz = G->d_volz;
         if (!leap_plan_scratch(G, G->scratch_bytes / sizeof(float), batch, S.width, S.items)) {
             leap_set_error("internal: the handle's scratch holds no slab");
             return LEAP_UNSUPPORTED;
         }
         S.item_floats = ((size_t)S.width * (size_t)(g.nx > g.ny ? g.nx : g.ny) + 1) * (size_t)G->nzp;
+        const bool one = G->scratch.slots > 1 && batch <= S.items && batch * S.item_floats <= G->scratch_slot_floats;
+        const int slot = one ? G->scratch.pick(stream) : 0;
+        S.volz = G->d_volz + slot * G->scratch_slot_floats;
+        LeapTurn turn(&G->scratch.slot[slot], one ? 1 : G->scratch.slots, stream);
+        LEAP_HIP_CHECK(turn.begin());
         const int rc = run_forward_columns(G, S, d_vol, d_sino, batch, stream);
         if (rc != LEAP_OK) return rc;
         LEAP_HIP_CHECK(turn.end());

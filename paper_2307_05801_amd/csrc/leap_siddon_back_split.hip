@@ -1,5 +1,5 @@
 // Launchers of the tiled Siddon back projection with four groups of threads per workgroup that share the views; parts
-// > 1: that many workgroups of them, into the handle's d_back.
+// > 1: that many workgroups of them, into a volume each behind d_vol.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -16,7 +16,7 @@ static void launch_instance(const leap_geometry *G, int parts, const float *d_si
     const unsigned tiles_x = cdiv(g.nx, BP_T), tiles_y = cdiv(g.ny, BP_T);
     const dim3 grid(tiles_x * tiles_y, cdiv(g.nz, S.zc), (unsigned)(items * parts));
     auto go = [&](auto kernel, const SfGeom *geoms) {
-        hipLaunchKernelGGL(kernel, grid, dim3(256 * VS), 0, stream, g, G->d_views, G->d_raycols, d_sino, parts > 1 ? G->d_back : d_vol, (int)tiles_x, geoms, parts);
+        hipLaunchKernelGGL(kernel, grid, dim3(256 * VS), 0, stream, g, G->d_views, G->d_raycols, d_sino, d_vol, (int)tiles_x, geoms, parts);
     };
     const bool apart = G->sd_min_row_step > 1.0 + 1e-6;
     auto launch = [&](auto shared) {

@@ -115,6 +115,24 @@ extern "C" void host_shared_turns(const int64_t *streams, const int64_t *capture
     g_capture = 0;
 }
 
+// The slots that n calls on streams[k] take of a room of `slots`; a call on a stream below 0 takes them all.  out: the slot (-1: all), and how many
+// waits the call's turn makes.
+extern "C" void host_room_slots(const int64_t *streams, int n, int slots, int64_t (*out)[2])
+{
+    LeapRoom room;
+    (void)room.create(slots);
+    for (int k = 0; k < n; ++k) {
+        const bool all = streams[k] < 0;
+        const int slot = all ? 0 : room.pick((hipStream_t)streams[k]);
+        g_order.clear();
+        LeapTurn turn(&room.slot[slot], all ? room.slots : 1, (hipStream_t)streams[k]);
+        (void)turn.begin();
+        out[k][0] = all ? -1 : slot;
+        out[k][1] = (int64_t)g_order.size();
+        (void)turn.end();
+    }
+}
+
 int leap_static_scratch_init(int) { return LEAP_OK; }   // the fixed device array exists on a GPU only
 
 // ---- CPU launchers: the general kernel bodies, one "thread" at a time ----------------------------------------

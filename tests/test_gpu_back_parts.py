@@ -105,6 +105,33 @@ def test_threads_on_their_per_thread_streams(model, forward):
     geo.close()
 
 
+@pytest.mark.parametrize("model,forward", [("sf", False), ("siddon", False), ("sf", True), ("siddon", True)])
+def test_six_streams_and_batches_beside_them(model, forward):
+    """Single volumes on more streams than the memory has slots, and batches that take it whole between them."""
+    import torch
+    from paper_2307_05801_amd import Geometry
+    cfg = CASES["off_centre"]
+    geo = Geometry(cfg.replace(nrows=24) if forward else cfg, model=model)
+    print(f"[gpu] {model}: {geo.describe()}", flush=True)
+    assert ("A=columns" if forward else "+parts(") in geo.describe(), geo.describe()
+    operator, shape = (geo.project, geo.vol_shape) if forward else (geo.backproject, geo.sino_shape)
+    src = [torch.rand(shape, device="cuda") for _ in range(6)]
+    many = torch.rand((12,) + tuple(shape), device="cuda")
+    ref, ref_many = [operator(s) for s in src], operator(many)
+    torch.cuda.synchronize()
+    streams, got, got_many = [torch.cuda.Stream() for _ in src], [[] for _ in src], []
+    for turn in range(8):
+        for n, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                got[n].append(operator(src[n]))
+                if (turn + n) % 5 == 0:
+                    got_many.append(operator(many))
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, ref[n]) for n in range(6) for o in got[n])
+    assert got_many and all(torch.equal(o, ref_many) for o in got_many)
+    geo.close()
+
+
 SIDDON = {"cone": scan(shift_v=0.3), "parallel": scan(PARALLEL, pixel_u=1.0, pixel_v=1.0, nviews=500, shift_v=0.27), "curved": scan(CONE_CURVED, shift_v=-0.2),
           "upright": perturbed_poses(scan(shift_v=0.2), 5, shift_mm=4.0, upright=True),
           "tilted": perturbed_poses(scan(shift_v=0.2), 5, shift_mm=4.0, tilt_rad=0.05),

@@ -1206,6 +1206,22 @@ def test_turns_at_a_handle_s_shared_memory_wait_for_one_another(host):
     assert turns([0, 0], [0, -1]) == [(0, 1, 0), (1, 1, 1)]
 
 
+def test_calls_on_several_streams_take_slots_of_their_own(host):
+    """A stream keeps its slot while there are slots for all; hipStreamPerThread (2) may be another stream each time; a call that takes them all
+    waits for each, and each next one for it."""
+    def take(streams, slots):
+        n = len(streams)
+        out = (C.c_int64 * 2 * n)()
+        host.host_room_slots((C.c_int64 * n)(*streams), n, slots, out)
+        return [tuple(o) for o in out]
+
+    assert take([7, 0, 7, 5, 6, 7, 0], 4) == [(0, 0), (1, 0), (0, 1), (2, 0), (3, 0), (0, 1), (1, 1)]
+    assert take([2, 2, 2, 2, 2], 4) == [(0, 0), (1, 0), (2, 0), (3, 0), (0, 1)]
+    assert take([3, 4, 5, 3, 4], 2) == [(0, 0), (1, 0), (0, 1), (1, 1), (0, 1)]
+    assert take([7, 5, -1, 6, 7], 4) == [(0, 0), (1, 0), (-1, 2), (2, 1), (0, 1)]
+    assert take([7, 5, -1], 1) == [(0, 0), (0, 1), (-1, 1)]
+
+
 @pytest.mark.parametrize("geom,n,nz,nrows,nviews,columns", [
     (CONE, 96, 400, 16, 1, True), (CONE, 96, 400, 15, 60, False), (PARALLEL, 96, 400, 22, 1, True), (PARALLEL, 96, 400, 21, 60, False),
     (CONE, 512, 512, 24, 15, False), (CONE, 512, 512, 24, 360, True), (CONE, 512, 512, 32, 1, True), (PARALLEL, 512, 512, 31, 100, False),
