@@ -51,7 +51,7 @@ static int launch_in_parts(const leap_geometry *G, const LeapBackParts &plan, co
     const size_t nvol = (size_t)G->g.nx * G->g.ny * G->g.nz, nsino = (size_t)G->g.nviews * G->g.nrows * G->g.ncols;
     const bool one = items <= std::min(plan.items, G->back_slot_items);
     const int slot = one ? G->back.pick(stream) : 0;
-    LeapTurn turn(&G->back.slot[slot], one ? 1 : G->back.slots, stream);
+    LeapTurn turn = one ? G->back.turn(slot, stream) : G->back.turn_at_all(stream);
     LEAP_HIP_CHECK(turn.begin());
     float *const room = G->d_back + (size_t)slot * G->back_slot_items * nvol * plan.parts;
     for (int b = 0; b < items;) {

@@ -22,8 +22,9 @@ struct LeapHostStage;                  // streams, events, staging and device bu
 // captured turns are ordered among those of their own capture, and eager ones among the eager ones.
 struct LeapShared {
     std::mutex mutex;
-    hipEvent_t done = nullptr, captured = nullptr;     // the last eager turn's end; the last captured one's, in capture `capture`
-    bool used = false, captured_used = false;
+    hipEvent_t done = nullptr, captured = nullptr;     // its last eager turn's end; the last captured one's, in capture `capture`
+    hipEvent_t latest = nullptr;                       // the last eager turn's event, of this memory's or of a turn at several (null: there was none)
+    bool captured_used = false;
     unsigned long long capture = 0;
 
     hipError_t create()
@@ -51,8 +52,9 @@ inline bool leap_capturing(hipStream_t stream)
 // launched, ends it too.
 class LeapTurn {
 public:
-    LeapTurn(LeapShared &memory, hipStream_t s) : LeapTurn(&memory, 1, s) {}
-    LeapTurn(LeapShared *memory, int n, hipStream_t s) : shared(memory), count(n), stream(s)
+    LeapTurn(LeapShared &memory, hipStream_t s) : LeapTurn(&memory, 1, memory.done, s) {}
+    // done: the event that the turn records, and the next ones at any of the n wait for
+    LeapTurn(LeapShared *memory, int n, hipEvent_t event, hipStream_t s) : shared(memory), count(n), done(event), stream(s)
     {
         for (int i = 0; i < count; ++i) shared[i].mutex.lock();
     }
@@ -73,7 +75,9 @@ public:
         for (int i = 0; i < count && e == hipSuccess; ++i) {
             const LeapShared &s = shared[i];
             if (capturing && s.captured_used && s.capture == capture) e = hipStreamWaitEvent(stream, s.captured, 0);
-            if (!capturing && s.used) e = hipStreamWaitEvent(stream, s.done, 0);
+            bool waits = !capturing && s.latest;
+            for (int k = 0; k < i; ++k) waits = waits && shared[k].latest != s.latest;
+            if (waits) e = hipStreamWaitEvent(stream, s.latest, 0);
         }
         begun = e == hipSuccess;
         return e;
@@ -87,22 +91,23 @@ public:
 private:
     hipError_t record()
     {
-        hipError_t failed = hipSuccess;
+        hipError_t failed = capturing ? hipSuccess : hipEventRecord(done, stream);
         for (int i = 0; i < count; ++i) {
             LeapShared &s = shared[i];
-            const hipError_t e = hipEventRecord(capturing ? s.captured : s.done, stream);
             if (capturing) {
+                const hipError_t e = hipEventRecord(s.captured, stream);
                 s.captured_used = e == hipSuccess;
                 s.capture = capture;
-            } else {
-                s.used = s.used || e == hipSuccess;
+                if (e != hipSuccess) failed = e;
+            } else if (failed == hipSuccess) {
+                s.latest = done;
             }
-            if (e != hipSuccess) failed = e;
         }
         return failed;
     }
     LeapShared *shared;
     int count;
+    hipEvent_t done;
     hipStream_t stream;
     bool capturing = false, begun = false;
     unsigned long long capture = 0;
@@ -115,15 +120,22 @@ private:
 struct LeapRoom {
     static constexpr int MOST_SLOTS = 4;
     LeapShared slot[MOST_SLOTS];
+    hipEvent_t whole = nullptr;                            // the end of the last turn at all of them
     int slots = 1;
 
     hipError_t create(int n)
     {
         slots = n;
-        hipError_t e = hipSuccess;
+        hipError_t e = hipEventCreateWithFlags(&whole, hipEventDisableTiming);
         for (int i = 0; i < slots && e == hipSuccess; ++i) e = slot[i].create();
         return e;
     }
+    ~LeapRoom()
+    {
+        if (whole) (void)hipEventDestroy(whole);
+    }
+    LeapTurn turn(int i, hipStream_t stream) { return LeapTurn(&slot[i], 1, slot[i].done, stream); }
+    LeapTurn turn_at_all(hipStream_t stream) { return LeapTurn(&slot[0], slots, whole, stream); }
     // A stream's calls stay with the slot it took first, where their order is the stream's own, until more streams have come than there are slots.
     int pick(hipStream_t stream)
     {

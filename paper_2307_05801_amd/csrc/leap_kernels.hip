@@ -337,7 +337,7 @@ static int launch_sd_bp_parts(const leap_geometry *G, const LeapBackParts &plan,
     const size_t nsino = (size_t)G->g.nviews * G->g.nrows * G->g.ncols;
     const bool one = items <= plan.items && items <= G->back_slot_items;
     const int slot = one ? G->back.pick(stream) : 0;
-    LeapTurn turn(&G->back.slot[slot], one ? 1 : G->back.slots, stream);
+    LeapTurn turn = one ? G->back.turn(slot, stream) : G->back.turn_at_all(stream);
     LEAP_HIP_CHECK(turn.begin());
     float *const room = G->d_back + (size_t)slot * G->back_slot_items * nvol * plan.parts;
     for (int b = 0; b < items; b += plan.items) {
@@ -546,7 +546,7 @@ static int project_flat(const leap_geometry *G, const float *d_vol, float *d_sin
         LEAP_HIP_CHECK(hipGetLastError());
         return LEAP_OK;
     }
-    LeapTurn turn(G->scratch.slot[0], stream);
+    LeapTurn turn = G->scratch.turn(0, stream);
     LEAP_HIP_CHECK(turn.begin());
     const int room = (int)(G->scratch_bytes / (2 * nvol * sizeof(float)));      // whole slices the scratch holds, twice each
     for (int b = 0; b < batch;) {
@@ -720,7 +720,7 @@ int leap_launch_project_batch(const leap_geometry *G, const float *d_vol, float 
         const bool one = G->scratch.slots > 1 && batch <= S.items && batch * S.item_floats <= G->scratch_slot_floats;
         const int slot = one ? G->scratch.pick(stream) : 0;
         S.volz = G->d_volz + slot * G->scratch_slot_floats;
-        LeapTurn turn(&G->scratch.slot[slot], one ? 1 : G->scratch.slots, stream);
+        LeapTurn turn = one ? G->scratch.turn(slot, stream) : G->scratch.turn_at_all(stream);
         LEAP_HIP_CHECK(turn.begin());
         const int rc = run_forward_columns(G, S, d_vol, d_sino, batch, stream);
         if (rc != LEAP_OK) return rc;

@@ -125,7 +125,7 @@ extern "C" void host_room_slots(const int64_t *streams, int n, int slots, int64_
         const bool all = streams[k] < 0;
         const int slot = all ? 0 : room.pick((hipStream_t)streams[k]);
         g_order.clear();
-        LeapTurn turn(&room.slot[slot], all ? room.slots : 1, (hipStream_t)streams[k]);
+        LeapTurn turn = all ? room.turn_at_all((hipStream_t)streams[k]) : room.turn(slot, (hipStream_t)streams[k]);
         (void)turn.begin();
         out[k][0] = all ? -1 : slot;
         out[k][1] = (int64_t)g_order.size();

@@ -1219,6 +1219,7 @@ def test_calls_on_several_streams_take_slots_of_their_own(host):
     assert take([2, 2, 2, 2, 2], 4) == [(0, 0), (1, 0), (2, 0), (3, 0), (0, 1)]
     assert take([3, 4, 5, 3, 4], 2) == [(0, 0), (1, 0), (0, 1), (1, 1), (0, 1)]
     assert take([7, 5, -1, 6, 7], 4) == [(0, 0), (1, 0), (-1, 2), (2, 1), (0, 1)]
+    assert take([7, 5, -1, -1, 5, 6, -1], 4) == [(0, 0), (1, 0), (-1, 2), (-1, 1), (1, 1), (2, 1), (-1, 3)]
     assert take([7, 5, -1], 1) == [(0, 0), (0, 1), (-1, 1)]
 
 
