@@ -1177,7 +1177,9 @@ bool leap_plan_scratch(const leap_geometry *G, size_t floats, int batch, int &wi
         return w >= n_side ? n_side : (w < 4 ? 0 : ((int)w & ~3));
     };
     items = std::max(1, std::min(batch, 16));
-    while (items > 1 && width_for(items) < std::min(32, n_side)) items = (items + 1) / 2;
+    // (a slab whose layers four waves share: as wide as for one item)
+    const int least = G->fp_parts > 1 ? width_for(1) : std::min(32, n_side);
+    while (items > 1 && width_for(items) < least) items = (items + 1) / 2;
     width = width_for(items);
     if (G->dbg_items > 0) items = std::min(G->dbg_items, std::max(1, batch));
     if (G->dbg_slab > 0) width = std::min(G->dbg_slab, n_side);

@@ -559,6 +559,15 @@ extern "C" long host_check_tile_order(unsigned tiles_x, unsigned tiles_y, unsign
 }
 
 // How many of a launch's items go two to a wave.
+// The slab width and the items per launch of a batch on the handle's scratch.
+extern "C" void host_plan_scratch(const leap_geometry *G, int batch, int64_t out[2])
+{
+    int width = 0, items = 0;
+    (void)leap_plan_scratch(G, G->scratch_bytes / sizeof(float), batch, width, items);
+    out[0] = width;
+    out[1] = items;
+}
+
 extern "C" int host_forward_paired(const leap_geometry *G, int items) { return leap_forward_paired(G, items); }
 
 // Back projection of a launch's items: the shape whose groups of threads share the views (-1: none), pairs of items per workgroup.

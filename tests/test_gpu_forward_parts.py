@@ -49,6 +49,21 @@ def test_shared_layers_and_short_detectors(oracle_mod, monkeypatch, name, slab):
     geo.close()
 
 
+@pytest.mark.parametrize("name", ["cone", "cone_8_rows", "parallel"])
+def test_items_of_a_large_batch_keep_their_bits(name):
+    """Seventeen volumes, longer than wide, of whose copies the scratch holds fewer than sixteen."""
+    import torch
+    from paper_2307_05801_amd import Geometry
+    geo = Geometry(CASES[name][0].replace(nx=60, ny=37))
+    print(f"[gpu] {name}: {geo.describe()}", flush=True)
+    assert "parts=" in geo.describe(), geo.describe()
+    x = torch.rand((17,) + tuple(geo.vol_shape), device="cuda")
+    y = geo.project(x)
+    for b in range(17):
+        assert torch.equal(y[b], geo.project(x[b].contiguous())), b
+    geo.close()
+
+
 @pytest.mark.parametrize("name", ["cone_8_rows", "curved", "upright", "parallel", "siddon_16_rows"])
 def test_short_detectors_captured_and_on_the_fixed_array(monkeypatch, name):
     """Neither needs a scratch, whatever stream the handle was last used on: the general kernel's results, bit for bit."""

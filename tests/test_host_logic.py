@@ -1206,6 +1206,24 @@ def test_turns_at_a_handle_s_shared_memory_wait_for_one_another(host):
     assert turns([0, 0], [0, -1]) == [(0, 1, 0), (1, 1, 1)]
 
 
+@pytest.mark.parametrize("nviews,shared", [(2, True), (200, False)])
+def test_batches_whose_layers_are_shared_keep_one_volume_s_slabs(host, nviews, shared):
+    """Narrow slabs leave waves that share a slab's layers without any; waves of a bundle each take them for the sake of more items per launch."""
+    cfg = CTConfig("oblong", CONE, nviews=nviews, arc_deg=360.0, nrows=39, ncols=127, pixel_v=0.9, pixel_u=1.2, nx=100, ny=76, nz=34, voxel_xy=1.0,
+                   voxel_z=1.0, sod=450.0, sdd=675.0, shift_v=-0.4)
+    h = handle(host, cfg)
+    assert ("parts=4" in B.leap_geometry_describe(h, host)) == shared
+    plan = (C.c_int64 * 2)()
+    host.host_plan_scratch.argtypes = [C.c_void_p, C.c_int, C.c_void_p]
+    plans = {}
+    for batch in (1, 8, 16, 17):
+        host.host_plan_scratch(h, batch, plan)
+        plans[batch] = tuple(plan)
+    B.leap_geometry_destroy(h, host)
+    assert plans[1] == (100, 1) and plans[8] == (100, 8), plans
+    assert plans[16] == plans[17] == (100, 8) if shared else plans[16][0] < 100 and plans[16][1] == 16, plans
+
+
 def test_calls_on_several_streams_take_slots_of_their_own(host):
     """A stream keeps its slot while there are slots for all; hipStreamPerThread (2) may be another stream each time; a call that takes them all
     waits for each, and each next one for it."""
