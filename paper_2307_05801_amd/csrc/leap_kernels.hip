@@ -632,29 +632,32 @@ static int backproject_flat(const leap_geometry *G, const float *d_sino, float *
 }
 
 // Voxels per thread and groups of threads that share the views, for the tilted footprints' tiled back projection: the shape of least
-// estimated time.  A step from one view to the next takes a compute unit `alone` us with one workgroup of 256 threads on it and `full` with
-// four, or with one of 1024; the least of those shapes supplies every unit.  60 views' worth per shape (8, 4, 1 voxels; four groups 4, 2, 1), us per
-// view: 48^2 x 38 voxels 6.4, 3.9, 2.4; 2.0, 1.3, 1.8; 64^2 x 51 6.4, 3.9, 3.5; 2.0, 2.5, 3.5; 96^2 x 76 8.4, 6.3, 8.4; 5.7, 7.0, 9.5; 128^2 x 102 12.1,
-// 12.6, 18.7; 13.2, 15.7, 22.8.
-static int mf_back_choice(double tiles, int nz, int views)
+// estimated time, in us.  A view costs a workgroup its staging and a time per voxel and pixel of a voxel's rectangle, alone on a compute unit or one of
+// four of 256 threads (one of 1024).  The constants are fitted to 525 scans (12^2 to 230^2 x 140 voxels, 1 to 200 views, rectangles of 4 to 11 pixels; all seven
+// shapes each, 20 % rms): the chosen shape takes 1.015 times the best one's time, 1.45 at most.  Against the choice among 8, 2 and 1 voxels by
+// workgroups alone 0.76, at most 1.10.  60 views' worth per shape (8, 4, 1 voxels; four groups 4, 2, 1), us per view: 48^2 x 38 voxels 6.4, 3.9, 2.4; 2.0,
+// 1.3, 1.8; 64^2 x 51 6.4, 3.9, 3.5; 2.0, 2.5, 3.5; 96^2 x 76 8.4, 6.3, 8.4; 5.7, 7.0, 9.5; 128^2 x 102 12.1, 12.6, 18.7; 13.2, 15.7, 22.8.  Two voxels in
+// one group are for few views: 64 x 73 x 67, 6 views 38 us, four groups of 4 or 2 44 and 40; 51 x 60 x 81, 9 views 57, 69 and 62.
+static int mf_back_choice(const leap_geometry *G, double tiles)
 {
     static const struct {
         int zc, groups;
-        double alone, full;
-    } shapes[] = {{8, 1, 5.3, 12.0}, {4, 1, 3.4, 7.1}, {1, 1, 1.9, 3.4}, {4, 4, 0.0, 7.1}, {2, 4, 0.0, 4.7}, {1, 4, 0.0, 3.4}};
+    } shapes[] = {{8, 1}, {4, 1}, {2, 1}, {1, 1}, {4, 4}, {2, 4}, {1, 4}};
+    const double pixels = (G->max_cols_per_voxel + 1.0) * (G->max_rows_per_voxel + 1.0), views = G->g.nviews;
     int best = 0;
     double least = 1e300;
-    for (int n = 0; n < 6; ++n) {
-        const auto &s = shapes[n];
-        const double per_unit = tiles * std::ceil((double)nz / s.zc) / 256.0;
-        double time;
-        if (s.groups > 1) {
-            time = std::ceil(per_unit) * std::ceil((double)views / s.groups) * s.full;
+    for (int n = 0; n < 7; ++n) {
+        const double per_unit = tiles * cdiv(G->g.nz, shapes[n].zc) / 256.0, work = (shapes[n].zc < G->g.nz ? shapes[n].zc : G->g.nz) * pixels;
+        double time = 4.5;
+        if (shapes[n].groups > 1) {
+            const double rounds = 0.56 * std::ceil(per_unit) + 0.44 * per_unit;
+            time += (rounds > 1.0 ? rounds : 1.0) * (std::ceil(views / shapes[n].groups) * (1.8 + 0.169 * work) + 0.85);
         } else {
-            const double rounds = std::floor(per_unit / 4.0), left = std::ceil(per_unit - 4.0 * rounds);
-            time = views * (rounds * s.full + (left > 0.0 ? s.alone + (s.full - s.alone) * (left - 1.0) / 3.0 : 0.0));
+            const double alone = 1.19 + 0.085 * work, full = 1.58 + 0.152 * work;
+            if (per_unit <= 4.0) time += views * (alone + (full - alone) * (std::ceil(per_unit) - 1.0) / 3.0) + 1.25;
+            else time += views * full * (0.29 * std::ceil(per_unit / 4.0) + 0.71 * per_unit / 4.0) + 1.25 * per_unit / 4.0;
         }
-        if (time < 0.94 * least) {
+        if (time < 0.97 * least) {
             least = time;
             best = n;
         }
@@ -767,12 +770,13 @@ int leap_launch_backproject(const leap_geometry *G, const float *d_sino, float *
         auto go = [&](auto kernel, int zc, int groups) {
             hipLaunchKernelGGL(kernel, dim3(tiles_x * tiles_y, cdiv(g.nz, zc)), dim3(256 * groups), 0, stream, g, G->d_mfviews, d_sino, d_vol, (int)tiles_x);
         };
-        switch (mf_back_choice((double)tiles_x * tiles_y, g.nz, g.nviews)) {
+        switch (mf_back_choice(G, (double)tiles_x * tiles_y)) {
         case 0: go(mf_backproject_tiled<8, 1>, 8, 1); break;
         case 1: go(mf_backproject_tiled<4, 1>, 4, 1); break;
-        case 2: go(mf_backproject_tiled<1, 1>, 1, 1); break;
-        case 3: go(mf_backproject_tiled<4, 4>, 4, 4); break;
-        case 4: go(mf_backproject_tiled<2, 4>, 2, 4); break;
+        case 2: go(mf_backproject_tiled<2, 1>, 2, 1); break;
+        case 3: go(mf_backproject_tiled<1, 1>, 1, 1); break;
+        case 4: go(mf_backproject_tiled<4, 4>, 4, 4); break;
+        case 5: go(mf_backproject_tiled<2, 4>, 2, 4); break;
         default: go(mf_backproject_tiled<1, 4>, 1, 4); break;
         }
         LEAP_HIP_CHECK(hipGetLastError());

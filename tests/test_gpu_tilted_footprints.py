@@ -52,6 +52,28 @@ def test_tiled_kernels_match_oracle(oracle_mod, cfg):
     geo.close()
 
 
+# back projections of few views or many tiles: eight, four and two voxels per thread, four groups of four and of two
+SHAPES = [scan(130, 140, 90, 40, 60, nviews=2), scan(80, 79, 105, 60, 50, nviews=2), scan(51, 60, 81, 80, 50, nviews=9), scan(40, 41, 101, 60, 40, nviews=3),
+          scan(48, 47, 51, 60, 50, nviews=17)]
+
+
+@pytest.mark.parametrize("cfg", SHAPES, ids=lambda c: c.name)
+def test_every_shape_of_the_back_projection_matches_oracle(oracle_mod, cfg):
+    import torch
+    from paper_2307_05801_amd import Geometry
+    geo = Geometry(cfg)
+    print(f"[gpu] {cfg.name}: {geo.describe()}", flush=True)
+    assert "AT=general(tiled)" in geo.describe(), geo.describe()
+    y = uniform_sinogram(cfg, 4)[0]
+    yt = torch.from_numpy(y).cuda()
+    got = geo.backproject(yt)
+    assert torch.equal(geo.backproject(yt), got)
+    got, want = got.cpu().numpy(), oracle_mod.backproject(cfg, y)
+    assert np.linalg.norm(got - want) <= TOL * np.linalg.norm(want) + 1e-12
+    assert np.abs(got - want).max() <= 2e-7 * np.abs(want).max() + 1e-12
+    geo.close()
+
+
 def test_a_weight_of_zero_spreads_nothing():
     import torch
     from paper_2307_05801_amd import Geometry
