@@ -34,25 +34,25 @@ MEASURED_TRAFFIC = {
                            "fetch_bytes": 3.74292e7 * 2048, "write_bytes": 9.83713e6 * 1024,
                            "source": "profiles/sf_two_volumes_c2_to_c5.md"},
     ("c3_cone_512", "AT"): {"instance": "AT=tiled(nc=3,nv=2,zc=64,window=24x63)+mirror(zc=32,32x44)", "launches": 1,
-                            "fetch_bytes": 7.64992e6 * 2048, "write_bytes": 524288 * 1024,
+                            "fetch_bytes": 3.41713e6 * 2048, "write_bytes": 530215 * 1024,
                             "source": "profiles/sf_two_volumes_c2_to_c5.md"},
     ("c2_parallel3d_256", "A"): {"instance": "A=columns(nq=8/8,nkp=3,rg=2,cw=4,slab=256,rows)", "launches": 1,
                                  "fetch_bytes": 1.99523e6 * 2048, "write_bytes": 87015 * 1024,
                                  "source": "profiles/sf_two_volumes_c2_to_c5.md"},
     ("c2_parallel3d_256", "AT"): {"instance": "AT=tiled(nc=3,nv=2,zc=64,window=25x67)+mirror(zc=32,32x44)", "launches": 1,
-                                  "fetch_bytes": 185899 * 2048, "write_bytes": 65536 * 1024,
+                                  "fetch_bytes": 115440 * 2048, "write_bytes": 65684 * 1024,
                                   "source": "profiles/sf_two_volumes_c2_to_c5.md"},
     ("c4_cone_limited_batch8_256", "A"): {"instance": "A=columns(nq=8/8,nkp=3,rg=3,cw=4,slab=256)", "launches": 10,
                                           "fetch_bytes": 7.34131e6 * 2048, "write_bytes": 2.12474e6 * 1024,
                                           "source": "profiles/sf_two_volumes_c2_to_c5.md"},
     ("c4_cone_limited_batch8_256", "AT"): {"instance": "AT=tiled(nc=4,nv=3,zc=16,window=49x46)+mirror(zc=16,51x48)", "launches": 1,
-                                           "fetch_bytes": 2.03274e6 * 2048, "write_bytes": 524288 * 1024,
+                                           "fetch_bytes": 899310 * 2048, "write_bytes": 609365 * 1024,
                                            "source": "profiles/sf_two_volumes_c2_to_c5.md"},
     ("c5_cone_1024", "A"): {"instance": "A=columns(nq=11/16,nkp=4,rg=4,cw=4,slab=124)", "launches": 18,
                             "fetch_bytes": 9.38479e8 * 2048, "write_bytes": 9.71500e7 * 1024,
                             "source": "profiles/sf_two_volumes_c2_to_c5.md"},
     ("c5_cone_1024", "AT"): {"instance": "AT=tiled(nc=3,nv=3,zc=64,window=31x86)+mirror(zc=32,32x56)", "launches": 1,
-                             "fetch_bytes": 7.70538e8 * 2048, "write_bytes": 4.1943e6 * 1024,
+                             "fetch_bytes": 5.08265e8 * 2048, "write_bytes": 4.27996e6 * 1024,
                              "source": "profiles/sf_two_volumes_c2_to_c5.md"},
     ("c3_cone_512:siddon", "A"): {"instance": "A=columns(rg=8,slab=124,pairs apart)", "launches": 10,
                                   "fetch_bytes": 6.87755e7 * 2048, "write_bytes": 8.48188e6 * 1024,
