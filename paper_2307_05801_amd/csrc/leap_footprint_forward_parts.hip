@@ -3,7 +3,7 @@
 
 #include "sf_project_launch.h"
 
-bool leap_launch_footprint_slab_parts(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
+bool leap_launch_footprint_slab_parts(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, int waves, float *d_sino, hipStream_t stream, int items)
 {
-    return launch_fp_slab<FP_PARTS>(G, S, slab, d_sino, stream, items);
+    return launch_fp_slab<FP_PARTS>(G, S, slab, waves, d_sino, stream, items);
 }

@@ -295,7 +295,7 @@ int leap_launch_project_batch(const leap_geometry *geom, const float *d_vol, flo
 int leap_launch_backproject(const leap_geometry *geom, const float *d_sino, float *d_vol, hipStream_t stream);
 struct SfSlab;
 bool leap_launch_footprint_slab(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward.hip
-bool leap_launch_footprint_slab_parts(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward_parts.hip
+bool leap_launch_footprint_slab_parts(const leap_geometry *geom, const FwdScratch &S, const SfSlab &slab, int waves, float *d_sino, hipStream_t stream, int items);   // leap_footprint_forward_parts.hip
 int leap_launch_footprint_back(const leap_geometry *geom, const float *d_sino, float *d_vol, int items, hipStream_t stream);                         // leap_footprint_back.hip
 bool leap_launch_backproject_split(const leap_geometry *geom, int shape, int parts, const float *d_sino, float *room, float *d_vol, int items, hipStream_t stream);          // leap_footprint_back_split.hip
 bool leap_launch_siddon_back_split(const leap_geometry *geom, int shape, int parts, const float *d_sino, float *d_vol, int items, hipStream_t stream);          // leap_siddon_back_split.hip

@@ -339,6 +339,15 @@ SF_HD void fp_part_of(const SfSlab &slab, int block, int part, int parts, int &n
     n_end = n_end < slab.n1 ? n_end : slab.n1;
 }
 
+// Of `parts` waves those that get a block of a slab of n layers, where a kernel of so many exists (by rows: 1, 2 and 4, else 1 and 4): waves without one
+// add zeros, so the sums are the same bits without them, and a batch of volumes of one or two blocks is not held up by idle waves (us, a wave per bundle; four;
+// now: 30 x 26 x 79, 37 parallel views, 17 volumes 158, 178, below 165; 14 x 12 x 146, one view, 5 volumes 26, 30, below 27).
+SF_HD int fp_waves_for(int n, int block, int parts, bool rows)
+{
+    const int blocks = (n + block - 1) / block;
+    return parts == 1 || blocks <= 1 ? 1 : (rows && blocks == 2 ? 2 : parts);
+}
+
 #if defined(__HIPCC__) && !defined(SF_NO_KERNELS)
 
 // vol [nz][ny][nx]  ->  the slab's scratch copy: columns (i, j), i0 <= i < i0 + ni, j0 <= j < j0 + nj, at

@@ -105,9 +105,9 @@ static bool launch_fp_rows_slab(const leap_geometry *G, const FwdScratch &S, con
 }
 
 template <int PARTS>
-static bool launch_fp_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, float *d_sino, hipStream_t stream, int items)
+static bool launch_fp_slab(const leap_geometry *G, const FwdScratch &S, const SfSlab &slab, int waves, float *d_sino, hipStream_t stream, int items)
 {
-    if (G->fp_rows) return G->fp_parts == 2 ? launch_fp_rows_slab<PARTS == 1 ? 1 : 2>(G, S, slab, d_sino, stream, items) : launch_fp_rows_slab<PARTS>(G, S, slab, d_sino, stream, items);
+    if (G->fp_rows) return waves == 2 ? launch_fp_rows_slab<PARTS == 1 ? 1 : 2>(G, S, slab, d_sino, stream, items) : launch_fp_rows_slab<PARTS>(G, S, slab, d_sino, stream, items);
     switch (fp_height_class(G->fp_nkp)) {
     case 0: return launch_fp_sets<0, PARTS>(G, S, slab, d_sino, stream, items);
     case 1: return launch_fp_sets<1, PARTS>(G, S, slab, d_sino, stream, items);

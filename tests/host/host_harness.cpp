@@ -559,6 +559,29 @@ extern "C" long host_check_tile_order(unsigned tiles_x, unsigned tiles_y, unsign
 }
 
 // How many of a launch's items go two to a wave.
+// Blocks of a slab by the waves that fp_waves_for leaves: the groups that are added must be those of all the parts, in their order (empty ones aside).
+extern "C" long host_check_waves_for()
+{
+    long bad = 0;
+    auto groups = [](int n, int block, int parts) {
+        std::vector<std::pair<int, int>> out;
+        for (int p = 0; p < parts; ++p) {
+            int first = 0, end = n;
+            if (parts > 1) fp_part_of({0, n, 1, 1, n}, block, p, parts, first, end);
+            if (end > first) out.push_back({first, end});
+        }
+        return out;
+    };
+    for (int block : {4, 8, 16})
+        for (int n = 1; n <= 200; ++n)
+            for (int parts : {1, 2, 4})
+                for (int rows = parts == 2; rows < 2; ++rows) {
+                    const int waves = fp_waves_for(n, block, parts, rows);
+                    if (!(waves == 1 || waves == FP_PARTS || (waves == 2 && rows)) || waves > parts || groups(n, block, waves) != groups(n, block, parts)) ++bad;
+                }
+    return bad;
+}
+
 // The slab width and the items per launch of a batch on the handle's scratch.
 extern "C" void host_plan_scratch(const leap_geometry *G, int batch, int64_t out[2])
 {

@@ -49,6 +49,29 @@ def test_shared_layers_and_short_detectors(oracle_mod, monkeypatch, name, slab):
     geo.close()
 
 
+@pytest.mark.parametrize("geom", [CONE, CONE_CURVED, PARALLEL])
+@pytest.mark.parametrize("nx", [4, 8, 9, 16, 17, 32, 33])
+def test_slabs_of_fewer_blocks_than_waves(oracle_mod, monkeypatch, geom, nx):
+    """Blocks are of 4 to 16 layers.  Waves without one are left out: the oracle's results, and those of a wave per bundle where there is one block."""
+    import torch
+    from paper_2307_05801_amd import Geometry
+    cfg = scan(geom, 36, nviews=4, nx=nx, ny=max(4, nx - 1))
+    geo = Geometry(cfg)
+    print(f"[gpu] {geo.describe()}", flush=True)
+    assert "parts=4" in geo.describe(), geo.describe()
+    x = uniform_volume(cfg, 5)[0]
+    xt = torch.from_numpy(x).cuda()
+    y = geo.project(xt)
+    assert rel_l2(y.cpu().numpy(), oracle_mod.project(cfg, x)) <= TOL
+    monkeypatch.setenv("LEAP_DEBUG", "parts=1")
+    plain = Geometry(cfg)
+    slots = int(plain.describe().split("nq=")[1].split(",")[0].split("/")[1])
+    if nx <= 64 // slots:
+        assert torch.equal(y, plain.project(xt))
+    plain.close()
+    geo.close()
+
+
 @pytest.mark.parametrize("name", ["cone", "cone_8_rows", "parallel"])
 def test_items_of_a_large_batch_keep_their_bits(name):
     """Seventeen volumes, longer than wide, of whose copies the scratch holds fewer than sixteen."""

@@ -1224,6 +1224,11 @@ def test_batches_whose_layers_are_shared_keep_one_volume_s_slabs(host, nviews, s
     assert plans[16] == plans[17] == (100, 8) if shared else plans[16][0] < 100 and plans[16][1] == 16, plans
 
 
+def test_waves_without_a_block_are_left_out(host):
+    """... and with them gone every block still has one wave, the next block the same or the next one."""
+    assert host.host_check_waves_for() == 0
+
+
 def test_calls_on_several_streams_take_slots_of_their_own(host):
     """A stream keeps its slot while there are slots for all; hipStreamPerThread (2) may be another stream each time; a call that takes them all
     waits for each, and each next one for it."""
